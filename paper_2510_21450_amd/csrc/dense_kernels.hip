@@ -1,6 +1,10 @@
 // Dense-Jacobian path: h' = tanh(W h + u), J_l = diag(1 - F_l^2) W (the generic
 // dense case of Sec. 2.1), H = 64, fp32.
 //
+// The linear solve of a Newton iteration is block bi-diagonal.  Two ways through it (wavefront_pays chooses):
+// forward substitution, all iterations of a block at once as a wavefront (dense_wavefront_kernel,
+// dense_adjoint_kernel: latency-bound, one workgroup per sequence, whole solves in two launches), and the chunked scan:
+//
 // One Newton iteration (Alg. 1a) is four launches (chunk_products and the local sweep share one):
 //   residual  F_l = tanh(W h_{l-1} + u_l), d_l = 1 - F_l^2, r_l = F_l - h_l   (Eq. (3))
 //   chunk_products   A_c = J_e ... J_s for every chunk of CD timesteps: the
@@ -125,7 +129,8 @@ __device__ __forceinline__ void load_w_operand16(const float *W, int w, int n, i
 //         first iteration are formed from it.  The guess of the row before, which the residual needs, is
 //         recomputed rather than read (it is tanh(W h0 + u_{l-1}), and W h0 is one product per row's sequence,
 //         shared with the row's own guess): same bits as the two launches, one pass over u instead of two and
-//         none over h.
+//         none over h;
+// mode 5: d alone (no control block is read).
 __device__ __forceinline__ void residual_body(const DenseArgs &a, int mode)
 {
     float nmax = 0.0f;
@@ -219,7 +224,7 @@ __device__ __forceinline__ void residual_body(const DenseArgs &a, int mode)
         f4v uv = zero, hv = zero;
         if (ok) {
             uv = *reinterpret_cast<const f4v *>(a.u + row * DH + chn);
-            if (mode != 1) hv = *reinterpret_cast<const f4v *>(a.h + row * DH + chn);
+            if (mode != 1 && mode != 5) hv = *reinterpret_cast<const f4v *>(a.h + row * DH + chn);
         }
         f4v acc0 = zero, acc1 = zero;
 #pragma unroll
@@ -241,7 +246,7 @@ __device__ __forceinline__ void residual_body(const DenseArgs &a, int mode)
                 for (int v = 0; v < 4; ++v) nmax = nanmax(nmax, fabsf(hv[v] - F[v]));
             } else {
                 *reinterpret_cast<f4v *>(a.d + row * DH + chn) = (1.0f - F * F) * wdiag;
-                *reinterpret_cast<f4v *>(a.r + row * DH + chn) = F - hv;
+                if (mode != 5) *reinterpret_cast<f4v *>(a.r + row * DH + chn) = F - hv;
             }
         }
     }
@@ -261,7 +266,7 @@ __device__ __forceinline__ void residual_body(const DenseArgs &a, int mode)
 
 __global__ __launch_bounds__(256) void dense_residual_kernel(const DenseArgs a, int mode)
 {
-    if (mode != 2 && a.ctrl->stop) return;
+    if (mode != 2 && mode != 5 && a.ctrl->stop) return;
     residual_body(a, mode);
 }
 
@@ -969,6 +974,436 @@ int newton_grid(int prod)
     return cap[prod];
 }
 
+// ------------------------------------------- forward substitution, iterations as a wavefront
+// The linear system of an iteration is block bi-diagonal: forward substitution solves it with one mat-vec
+// W delta per timestep, 64 times fewer operations than composing the Jacobians, at the price of L sequential
+// steps.  Iteration k at timestep l needs only iteration k-1 at timesteps l-1 and l, so the iterations of a
+// block of kWaveIters run together, each one step behind the one before it: at step t, wave w of a sequence's
+// workgroup is iteration w+1 of the block at timestep l = t - w, and a block costs L + kWaveIters - 1 steps
+// whatever the number of its iterations.
+//
+// A step is the product z = W [delta of the four iterations], 64 x 64 x 4, on v_mfma_f32_4x4x1_16b_f32, and
+//     F = tanh(y + u_l), d = 1 - F^2, delta = (F - h) + d z;   h += delta;   y_next = y + z
+// for every row and iteration, with y = W h_{l-1} and h = h_l of the iterate before.  y advances by z = W delta as
+// h does by delta, so W is applied to nothing but the updates; y of the first iterate of a block comes from
+// dense_guess_kernel, later blocks continue from the y their predecessor left behind.
+// What bounds a step is latency (LDS read, products, sum, LDS write, barrier), so it has one exchange: wave w owns
+// rows 16 w .. 16 w + 15 and all of k.  The instruction's 16 blocks are four groups of four; a group covers the
+// wave's 16 rows (4 columns of the B operand in each block: W) and one quarter of k, and the A operand (the four
+// iterations' delta at that k) is broadcast inside the group, so 16 instructions cover k.  The four
+// groups' partial sums meet by lane-row swaps that leave iteration i with lane group i: a lane is then one row of
+// one iteration, and what an iteration hands to the next (h, y) moves up sixteen lanes within the wave.
+// F and d are formed while the delta of the step before is on its way.  With one wave per SIMD every instruction counts (a vector instruction
+// takes four cycles to issue, 1.8 ns), so the four waves touch no memory and compute no addresses: a fifth brings the
+// rows of u, h and y in, sixteen bytes per lane, and takes the results out, by way of a ring of records in LDS, one
+// per step, in which each iteration finds its inputs and leaves its results where the next one looks for them.
+// Measured: see the rule at wavefront_pays().
+constexpr int kWaveIters = 4;
+constexpr int kWaveGroup = 8;         // steps per group: the mover wave brings in and takes out the rows of a group at a time
+constexpr int kRing = 16;             // steps a ring in LDS holds: the group in use and the one that is ready
+
+// tanh(y + u) of us = kTanhScale * u: one FMA into the exponential.
+constexpr float kTanhScale = 2.8853900817779268f;
+__device__ __forceinline__ float tanh_scaled(float y, float us)
+{
+    return fmaf(-2.0f, __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(fmaf(kTanhScale, y, us))), 1.0f);
+}
+
+// The first iterate and its y = W h, for every row at once: the initial guess
+// h_l = tanh(W h0 + u_l) (App. A), written here; W h0 itself goes to a.r, one row per sequence.  Also clears the control block and the n_gm maxima.
+__global__ __launch_bounds__(256) void dense_guess_kernel(const DenseArgs a, unsigned int *gm, int n_gm)
+{
+    if (blockIdx.x == 0) {
+        if (threadIdx.x < 64) reinterpret_cast<unsigned int *>(a.ctrl)[threadIdx.x] = 0u;
+        for (int i = threadIdx.x; i < n_gm; i += 256) gm[i] = 0u;
+    }
+    __shared__ f4v s_h[4][64];
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int n = lane & 15, g = lane >> 4;
+    const int chn = 16 * w + 4 * g;
+    const size_t rows = (size_t)a.B * a.L;
+    const size_t n_items = (rows + 15) / 16;
+    float wa[4][4];
+    load_w_operand16(a.W, w, n, g, wa);
+    const f4v zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (size_t item = blockIdx.x; item < n_items; item += gridDim.x) {
+        const size_t row = item * 16 + n;
+        const bool ok = row < rows;
+        f4v uv = zero, c0 = zero;
+        if (ok) uv = *reinterpret_cast<const f4v *>(a.u + row * DH + chn);
+        if (a.h0) {
+            const float *hp = a.h0 + (ok ? row / a.L : 0) * DH;
+            f4v c1 = zero;
+#pragma unroll
+            for (int ww = 0; ww < 4; ww += 2) {
+                const f4v xa = *reinterpret_cast<const f4v *>(hp + 16 * ww + 4 * g);
+                const f4v xb = *reinterpret_cast<const f4v *>(hp + 16 * (ww + 1) + 4 * g);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    c0 = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[ww][v], xa[v], c0, 0, 0, 0);
+                    c1 = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[ww + 1][v], xb[v], c1, 0, 0, 0);
+                }
+            }
+            c0 = c0 + c1;
+            if (ok && row % a.L == 0) *reinterpret_cast<f4v *>(a.r + (row / a.L) * DH + chn) = c0;
+        }
+        f4v hv;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) hv[v] = tanh_scaled(c0[v], kTanhScale * uv[v]);
+        if (ok) *reinterpret_cast<f4v *>(a.h + row * DH + chn) = hv;
+        __syncthreads();                              // the previous item's reads of s_h
+        s_h[w][lane] = hv;
+        __syncthreads();
+        f4v acc0 = zero, acc1 = zero;
+#pragma unroll
+        for (int ww = 0; ww < 4; ww += 2) {
+            const f4v xa = s_h[ww][lane], xb = s_h[ww + 1][lane];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[ww][v], xa[v], acc0, 0, 0, 0);
+                acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[ww + 1][v], xb[v], acc1, 0, 0, 0);
+            }
+        }
+        if (ok) *reinterpret_cast<f4v *>(a.d + row * DH + chn) = acc0 + acc1;
+    }
+}
+
+// z of this lane's row from the exchanged vectors xv (lane 4 (4 s + m) + i, component g: row 16 s + 4 m + g of
+// column i) and wr[4 m + g] = W[16 w + lane % 16][16 (lane / 16) + 4 m + g], as four partial sums over k:
+// register i is column i, over the quarter lane / 16 of k.
+__device__ __forceinline__ f4v wave_products(const f4v xv, const float (&wr)[16])
+{
+    f4v acc0 = {0.0f, 0.0f, 0.0f, 0.0f}, acc1 = acc0;
+#define PARARNN_M(m)                                                                         \
+    acc0 = __builtin_amdgcn_mfma_f32_4x4x1f32(xv[0], wr[4 * m + 0], acc0, 2, m, 0);          \
+    acc1 = __builtin_amdgcn_mfma_f32_4x4x1f32(xv[1], wr[4 * m + 1], acc1, 2, m, 0);          \
+    acc0 = __builtin_amdgcn_mfma_f32_4x4x1f32(xv[2], wr[4 * m + 2], acc0, 2, m, 0);          \
+    acc1 = __builtin_amdgcn_mfma_f32_4x4x1f32(xv[3], wr[4 * m + 3], acc1, 2, m, 0);
+    PARARNN_M(0) PARARNN_M(1) PARARNN_M(2) PARARNN_M(3)
+#undef PARARNN_M
+    return acc0 + acc1;
+}
+
+// x and y with the upper 32 lanes of x and the lower 32 of y exchanged, added up: lanes 0-31 hold x over both
+// halves, lanes 32-63 y.  swap16: the same with the odd and even rows of 16 lanes.
+__device__ __forceinline__ float swap32_add(float x, float y)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float swap16_add(float x, float y)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// the rows of one sequence, as a buffer whose bounds are the sequence's
+__device__ __forceinline__ buf_rsrc seq_rsrc(const float *base, unsigned int bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(base), 0, bytes, 0x27000);
+}
+
+// Rows of one group of steps between memory and the mover wave's registers: sixteen lanes and 16 bytes each per row.
+// row_of(t) is the row of the sequence that belongs to step t; rows outside it read zero and are not stored.
+template <class F> __device__ __forceinline__ void rows_load(buf_rsrc r, f4v (&x)[2], int lane, int t, F row_of)
+{
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+        x[j] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(
+                   r, (unsigned int)row_of(t + 4 * j + (lane >> 4)) * (DH * 4u) + 16u * (lane & 15), 0, 0));
+}
+template <class F> __device__ __forceinline__ void rows_store(buf_rsrc r, const f4v (&x)[2], int lane, int t, F row_of)
+{
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4v, x[j]), r,
+                                               (unsigned int)row_of(t + 4 * j + (lane >> 4)) * (DH * 4u) + 16u * (lane & 15), 0, 0);
+}
+// The same rows in a ring of kRing records of N floats each: the row at float `at` of the records of steps t .. t + 3.
+template <int N> __device__ __forceinline__ f4v *ring_slot(float (*ring)[N], int at, int lane, int t)
+{
+    return reinterpret_cast<f4v *>(&ring[(t + (lane >> 4)) & (kRing - 1)][at + 4 * (lane & 15)]);
+}
+
+// One workgroup per sequence.  A sequence whose own update meets the tolerance at the end of a block is done:
+// the blocks after it are run by the sequences that are not.  gm[k-1]: max |delta| of iteration k over the
+// sequences that ran it.  The last workgroup to finish reports the first iteration whose maximum met the tolerance.
+//
+// Record of step t: for iteration i (0 ..) at timestep l = t - i three rows from float kPer i on: h_l and y_{l-1} of the
+// iterate before (left there by iteration i - 1 in step t - 1, by the mover for i = 0), and kTanhScale * u_l.  The
+// sixteen floats behind them put the four iterations of a wave's access into four different quarters of the banks.
+// Steps before an iteration's first timestep find zeros there, which give delta = 0.
+__global__ __launch_bounds__(320) void dense_wavefront_kernel(const DenseArgs a, unsigned int *gm)
+{
+    constexpr int kPer = 3 * DH + 16, kRec = kWaveIters * kPer + 2 * DH;
+    __shared__ __attribute__((aligned(16))) float s_x[2][DH * kWaveIters];   // delta, in the order of wave_products
+    __shared__ __attribute__((aligned(16))) float s_rec[kRing][kRec];
+    __shared__ unsigned int s_m[kWaveIters];
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int b = blockIdx.x, L = a.L;
+    const unsigned int seq_bytes = (unsigned int)L * (DH * 4u);
+    const int it = lane >> 4, r = lane & 15, row = 16 * (w & 3) + r;  // this lane: iteration `it` of a block, one row
+    float wr[16];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        const f4v t = *reinterpret_cast<const f4v *>(a.W + row * DH + 16 * it + 4 * m);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) wr[4 * m + v] = t[v];
+    }
+    const int xw = 64 * (w & 3) + 16 * (r >> 2) + 4 * it + (r & 3);  // where this lane's delta goes
+
+    for (int k0 = 0; k0 < a.max_iter; k0 += kWaveIters) {
+        const int K = min(kWaveIters, a.max_iter - k0);
+        const int n_groups = (L + K - 1 + kWaveGroup - 1) / kWaveGroup;
+        if (threadIdx.x < DH * kWaveIters) s_x[0][threadIdx.x] = 0.0f;
+        if (threadIdx.x < kWaveIters) s_m[threadIdx.x] = 0u;
+        if (w == 4) {
+            const buf_rsrc ru = seq_rsrc(a.u + (size_t)b * L * DH, seq_bytes), rh = seq_rsrc(a.h + (size_t)b * L * DH, seq_bytes),
+                           ry = seq_rsrc(a.d + (size_t)b * L * DH, seq_bytes);
+            f4v xh[2], xy[2], xu[2];
+            auto same = [](int t) { return t; };
+            auto before = [](int t) { return t - 1; };
+            auto bring = [&](int t) {
+                rows_load(rh, xh, lane, t, same);
+                rows_load(ry, xy, lane, t, before);
+                rows_load(ru, xu, lane, t, same);
+            };
+            auto put = [&](int t) {
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    *ring_slot(s_rec, 0, lane, t + 4 * j) = xh[j];
+                    *ring_slot(s_rec, DH, lane, t + 4 * j) = xy[j];
+#pragma unroll
+                    for (int i = 0; i < kWaveIters; ++i) *ring_slot(s_rec, kPer * i + 2 * DH, lane, t + 4 * j + i) = xu[j] * kTanhScale;
+                }
+            };
+            auto take = [&](int t) {                       // what iteration K - 1 left in the records t .. t + 7
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    xh[j] = *ring_slot(s_rec, kPer * K, lane, t + 4 * j);
+                    xy[j] = *ring_slot(s_rec, kPer * K + DH, lane, t + 4 * j);
+                }
+                rows_store(rh, xh, lane, t - K, same);
+                rows_store(ry, xy, lane, t - K, before);
+            };
+#pragma unroll
+            for (int i = 1; i < kWaveIters; ++i)
+                for (int t = 0; t < i; ++t) s_rec[t][kPer * i + 2 * DH + lane] = 0.0f;
+            bring(0);
+            put(0);
+            // y in front of the first row: W h0, the same for every iteration
+            s_rec[0][DH + lane] = a.h0 ? a.r[(size_t)b * DH + lane] : 0.0f;
+            lds_barrier();
+            for (int g = 0; g < n_groups; ++g) {
+                const int t0 = g * kWaveGroup;
+                lds_barrier();
+                if (g > 0) take(t0 - kWaveGroup + 1);      // records t0 - 7 .. t0: complete with the first step of this group
+                bring(t0 + kWaveGroup);
+#pragma unroll 1
+                for (int i = 1; i < kWaveGroup - 2; ++i) lds_barrier();
+                put(t0 + kWaveGroup);                      // the group's last step reads the first of these records
+                lds_barrier();
+                lds_barrier();
+            }
+            lds_barrier();
+            take((n_groups - 1) * kWaveGroup + 1);
+        } else {
+            float mymax = 0.0f, h_in, y_in, us;
+            // what this lane's iteration leaves for the next one in record `rec`, and what it finds there itself
+            auto hand_on = [&](float *record, float hn, float yn) {
+                float *rec = record + kPer * it + row;
+                rec[kPer] = hn;
+                rec[kPer + DH] = yn;
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the reader is in this wave
+                __builtin_amdgcn_wave_barrier();
+                h_in = rec[0];
+                y_in = rec[DH];
+                us = rec[2 * DH];
+            };
+            auto step = [&](auto tail, int kB, float *next_rec, int t) {
+                const f4v xv = *reinterpret_cast<const f4v *>(&s_x[kB][4 * lane]);
+                __builtin_amdgcn_sched_barrier(0);
+                const float F = tanh_scaled(y_in, us), d = fmaf(-F, F, 1.0f), res = F - h_in;
+                __builtin_amdgcn_sched_barrier(0);
+                const f4v p = wave_products(xv, wr);
+                const float z = swap16_add(swap32_add(p[0], p[2]), swap32_add(p[1], p[3]));
+                const float delta = fmaf(d, z, res);
+                s_x[kB ^ 1][xw] = delta;
+                __builtin_amdgcn_sched_barrier(0);
+                hand_on(next_rec, fmaf(d, z, F), y_in + z);
+                if constexpr (decltype(tail)::value) {     // timesteps past the end do not count; a NaN has reached the last one
+                    if (t - it < L) mymax = nanmax(mymax, fabsf(delta));
+                } else {
+                    mymax = fmaxf(mymax, fabsf(delta));
+                }
+                // delta is written; the (at least three) LDS instructions of hand_on may be on their way still
+                asm volatile("s_waitcnt lgkmcnt(3)\n\ts_barrier" ::: "memory");
+            };
+            lds_barrier();
+            hand_on(s_rec[0], 0.0f, 0.0f);
+            for (int g = 0; g < n_groups; ++g) {
+                const int t0 = g * kWaveGroup;
+                float *rec = s_rec[t0 & (kRing - 1)], *rec_next = s_rec[(t0 + kWaveGroup) & (kRing - 1)];
+                if (t0 + kWaveGroup < L) {
+#pragma unroll
+                    for (int i = 0; i < kWaveGroup; ++i)
+                        step(std::false_type(), i & 1, i + 1 < kWaveGroup ? rec + kRec * (i + 1) : rec_next, t0 + i);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < kWaveGroup; ++i)
+                        step(std::true_type(), i & 1, i + 1 < kWaveGroup ? rec + kRec * (i + 1) : rec_next, t0 + i);
+                }
+            }
+            lds_barrier();
+            if (it < K) atomicMax(&s_m[it], __float_as_uint(mymax) & 0x7fffffffu);
+        }
+        __threadfence();                                   // the next block reads the rows that this one wrote
+        __syncthreads();
+        bool met = false;
+        for (int i = 0; i < K; ++i) {
+            const float mk = __uint_as_float(s_m[i]);
+            met = met || !(mk - mk == 0.0f) || (i == K - 1 && a.tol >= 0.0f && mk <= a.tol);
+        }
+        if ((int)threadIdx.x < K) atomicMax(&gm[k0 + threadIdx.x], s_m[threadIdx.x]);
+        __syncthreads();
+        if (met) break;
+    }
+    if (threadIdx.x == 0) {
+        __threadfence();
+        if (atomicAdd(&a.ctrl->done, 1u) == gridDim.x - 1) {
+            __threadfence();
+            int status = a.tol < 0.0f ? kStOk : kStNotConverged, k = 1;
+            for (; k <= a.max_iter; ++k) {
+                const float mk = __uint_as_float(__hip_atomic_load(&gm[k - 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+                if (a.trace) a.trace[k - 1] = mk;
+                if (!(mk - mk == 0.0f)) { status = kStNonFinite; break; }
+                if (a.tol >= 0.0f && mk <= a.tol) { status = kStOk; break; }
+            }
+            a.iters_out[0] = min(k, a.max_iter);
+            a.iters_out[1] = status;
+        }
+    }
+}
+
+// Backward by substitution: mu_l = d_l (W^T mu_{l+1} + g_l), one workgroup per sequence; row factors d in a.d.
+// A single column leaves the matrix instruction's other three idle, and sixteen vector FMAs per lane (68 cycles)
+// are quicker than sixteen of it (150): wave w owns rows 16 w .. + 15, lane group q the terms 16 q .. + 15 of their
+// sums, which two lane-row swaps complete.  mu reaches the FMAs one value per lane, broadcast inside the lane row by
+// the instruction itself (as 16-byte reads of all terms it cost 16 LDS transactions of 1 KB per step: 164 ns a step).  A fifth wave moves rows as in the forward kernel.  Ends with
+// dL/dh0 = W^T mu_1.
+__global__ __launch_bounds__(320) void dense_adjoint_kernel(const DenseArgs a, float *dh0)
+{
+    // step t of the recurrence is row L - 1 - t; its record holds d and d g, and mu is in the slot of the same number
+    __shared__ __attribute__((aligned(16))) float s_rec[kRing][2 * DH], s_mu[kRing][DH];
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int q = lane >> 4, row = 16 * (w & 3) + (lane & 15), b = blockIdx.x, L = a.L;
+    const unsigned int seq_bytes = (unsigned int)L * (DH * 4u);
+    auto rev = [L](int t) { return L - 1 - t; };
+    float wr[16];                                          // W^T[row][16 q ..]
+#pragma unroll
+    for (int i = 0; i < 16; ++i) wr[i] = a.W[(16 * q + i) * DH + row];
+    const int n_groups = (L + kWaveGroup - 1) / kWaveGroup;
+    if (w == 4) {
+        const buf_rsrc rd = seq_rsrc(a.d + (size_t)b * L * DH, seq_bytes), rg = seq_rsrc(a.g + (size_t)b * L * DH, seq_bytes),
+                       ro = seq_rsrc(a.du + (size_t)b * L * DH, seq_bytes);
+        f4v xd[2], xg[2], xm[2];
+        auto bring = [&](int t) { rows_load(rd, xd, lane, t, rev); rows_load(rg, xg, lane, t, rev); };
+        auto put = [&](int t) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                *ring_slot(s_rec, 0, lane, t + 4 * j) = xd[j];
+                *ring_slot(s_rec, DH, lane, t + 4 * j) = xd[j] * xg[j];
+            }
+        };
+        auto take = [&](int t) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) xm[j] = *ring_slot(s_mu, 0, lane, t + 4 * j);
+            rows_store(ro, xm, lane, t, rev);
+        };
+        bring(0);
+        put(0);
+        lds_barrier();
+        for (int g = 0; g < n_groups; ++g) {
+            const int t0 = g * kWaveGroup;
+            bring(t0 + kWaveGroup);
+            if (g > 0) take(t0 - kWaveGroup);
+#pragma unroll 1
+            for (int i = 0; i < kWaveGroup - 2; ++i) lds_barrier();
+            put(t0 + kWaveGroup);                          // the group's last step reads the first of these records
+            lds_barrier();
+            lds_barrier();
+        }
+        take((n_groups - 1) * kWaveGroup);
+        return;
+    }
+    // W^T mu, this lane's row, of the wave's lanes holding mu: lane 16 q + i the term 16 q + i
+    auto sum = [&](float x) {
+        float s[4];
+        // as one statement: the compiler makes a move and an FMA of each.  The wait states are those of a DPP source
+        // that a vector instruction may just have written.
+        asm("s_nop 1\n\t"
+            "v_mul_f32_dpp %0, %4, %5 row_newbcast:0 row_mask:0xf bank_mask:0xf\n\t"
+            "v_mul_f32_dpp %1, %4, %6 row_newbcast:1 row_mask:0xf bank_mask:0xf\n\t"
+            "v_mul_f32_dpp %2, %4, %7 row_newbcast:2 row_mask:0xf bank_mask:0xf\n\t"
+            "v_mul_f32_dpp %3, %4, %8 row_newbcast:3 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32_dpp %0, %4, %9 row_newbcast:4 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32_dpp %1, %4, %10 row_newbcast:5 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32_dpp %2, %4, %11 row_newbcast:6 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32_dpp %3, %4, %12 row_newbcast:7 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32_dpp %0, %4, %13 row_newbcast:8 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32_dpp %1, %4, %14 row_newbcast:9 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32_dpp %2, %4, %15 row_newbcast:10 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32_dpp %3, %4, %16 row_newbcast:11 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32_dpp %0, %4, %17 row_newbcast:12 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32_dpp %1, %4, %18 row_newbcast:13 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32_dpp %2, %4, %19 row_newbcast:14 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32_dpp %3, %4, %20 row_newbcast:15 row_mask:0xf bank_mask:0xf"
+            : "=&v"(s[0]), "=&v"(s[1]), "=&v"(s[2]), "=&v"(s[3])
+            : "v"(x), "v"(wr[0]), "v"(wr[1]), "v"(wr[2]), "v"(wr[3]), "v"(wr[4]), "v"(wr[5]), "v"(wr[6]), "v"(wr[7]),
+              "v"(wr[8]), "v"(wr[9]), "v"(wr[10]), "v"(wr[11]), "v"(wr[12]), "v"(wr[13]), "v"(wr[14]), "v"(wr[15]));
+        const float p = (s[0] + s[1]) + (s[2] + s[3]);
+        const float t = swap32_add(p, p);
+        return swap16_add(t, t);
+    };
+    lds_barrier();
+    float d = s_rec[0][row], dg = s_rec[0][DH + row], x = 0.0f;
+    for (int g = 0; g < n_groups; ++g) {
+        const int s0 = (g * kWaveGroup) & (kRing - 1), s1 = (s0 + kWaveGroup) & (kRing - 1);
+        float *mus = s_mu[s0];
+        const float *rec = s_rec[s0], *rec_next = s_rec[s1];
+#pragma unroll
+        for (int i = 0; i < kWaveGroup; ++i) {
+            mus[i * DH + row] = fmaf(d, sum(x), dg);       // the four lane groups store the same value
+            __builtin_amdgcn_sched_barrier(0);
+            const float *nr = i + 1 < kWaveGroup ? rec + 2 * (i + 1) * DH : rec_next;
+            d = nr[row];
+            dg = nr[DH + row];
+            // mu is written; the read of the next factors may be on its way still
+            asm volatile("s_waitcnt lgkmcnt(1)\n\ts_barrier" ::: "memory");
+            x = mus[i * DH + lane];
+        }
+    }
+    if (dh0) {
+        const float s = sum(s_mu[(L - 1) & (kRing - 1)][lane]);
+        if (q == 0) dh0[(size_t)b * DH + row] = s;
+    }
+}
+
+// Substitution or chunk products?  Nanoseconds, measured on config 4's shape and on 1 to 16 sequences of 500 to 2000
+// steps: a forward substitution step takes 225, an adjoint one 160, whatever the number of sequences while
+// each has a compute unit (config 4: 1.26 ms with chunk products, 0.24 with substitution; 6 sequences of 523 steps:
+// 0.44 and 0.13 ms); an iteration with chunk products takes 3.94 per row but at least 67 us (the chain of one
+// chunk), 17 per step for the carry and 25-30 us for the sweeps, and four iterations are what a solve
+// needs.  Substitution wins but for few long sequences: forward beyond 2500 steps for fewer than ten of
+// them, backward beyond 650 steps of a single one.
+bool wavefront_pays(int B, int L, bool backward)
+{
+    const double rows = (double)B * L;
+    const double products = (rows * 3.94 > 67e3 ? rows * 3.94 : 67e3) + 17.0 * L + 27e3;
+    const double rounds = (B + 511) / 512;              // two workgroups share a compute unit
+    return backward ? 160.0 * L * rounds < products : 225.0 * L * rounds < 4.0 * products;
+}
+
 // ------------------------------------------------------------ backward extras
 // Wt = W^T (16 KB)
 __global__ __launch_bounds__(256) void dense_transpose_kernel(const float *W, float *Wt)
@@ -1004,21 +1439,31 @@ __global__ __launch_bounds__(256) void dense_dw_kernel(const DenseArgs a, float 
         for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
             for (int v = 0; v < 16; ++v) Q[mt][nt][v] = 0.0f;
-    for (size_t r = r0; r < r1; r += 2) {
-        const size_t row = r + half;               // this lane half's row of the pair
-        const bool ok = row < r1;
-        float m0 = 0.0f, m1 = 0.0f, h0v = 0.0f, h1v = 0.0f;
-        if (ok) {
-            m0 = a.du[row * DH + n];
-            m1 = a.du[row * DH + 32 + n];
-            const int l = (int)(row % a.L);
-            const float *hp = l == 0 ? (a.h0 ? a.h0 + (row / a.L) * DH : nullptr) : a.h + (row - 1) * DH;
-            if (hp) { h0v = hp[n]; h1v = hp[32 + n]; }
+    // batches of eight rows: all their loads travel together
+    constexpr int kPairs = 4;
+    for (size_t r = r0; r < r1; r += 2 * kPairs) {
+        float m0[kPairs], m1[kPairs], h0v[kPairs], h1v[kPairs];
+#pragma unroll
+        for (int i = 0; i < kPairs; ++i) {
+            const unsigned int row = (unsigned int)r + 2 * i + half;   // this lane half's row of the pair (rows < 2^29)
+            const bool ok = row < r1;
+            const unsigned int rc = ok ? row : (unsigned int)rows - 1, bq = rc / (unsigned int)a.L;
+            const bool first = rc == bq * (unsigned int)a.L, zero = !ok || (first && !a.h0);
+            const float *hp = !first ? a.h + (size_t)(rc - 1) * DH : a.h0 ? a.h0 + (size_t)bq * DH : a.h;
+            m0[i] = a.du[(size_t)rc * DH + n];
+            m1[i] = a.du[(size_t)rc * DH + 32 + n];
+            h0v[i] = hp[n];
+            h1v[i] = hp[32 + n];
+            if (!ok) { m0[i] = 0.0f; m1[i] = 0.0f; }
+            if (zero) { h0v[i] = 0.0f; h1v[i] = 0.0f; }
         }
-        Q[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(m0, h0v, Q[0][0], 0, 0, 0);
-        Q[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(m0, h1v, Q[0][1], 0, 0, 0);
-        Q[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(m1, h0v, Q[1][0], 0, 0, 0);
-        Q[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(m1, h1v, Q[1][1], 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < kPairs; ++i) {
+            Q[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(m0[i], h0v[i], Q[0][0], 0, 0, 0);
+            Q[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(m0[i], h1v[i], Q[0][1], 0, 0, 0);
+            Q[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(m1[i], h0v[i], Q[1][0], 0, 0, 0);
+            Q[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(m1[i], h1v[i], Q[1][1], 0, 0, 0);
+        }
     }
     float *out = part + (size_t)p * DH * DH;
 #pragma unroll
@@ -1094,7 +1539,7 @@ int dense_chunk_products(const float *W, const float *d, int B, int L, int H, fl
 int dw_waves(int B, int L)
 {
     const size_t rows = (size_t)B * L;
-    size_t wv = (rows + 63) / 64;                 // at least 64 rows per wave
+    size_t wv = (rows + 15) / 16;                 // at least 16 rows per wave: 52 waves for 3138 rows took 19 us, 197 take 7
     if (wv > 1024) wv = 1024;
     return (int)((wv + 3) / 4 * 4);
 }
@@ -1106,6 +1551,18 @@ size_t dense_workspace_bytes(int dtype, int B, int L, int H, int backward)
     if (!backward) return lo.total;
     // the forward layout, then W^T and the dL/dW partials
     return lo.total + r256((size_t)DH * DH * 4) + r256((size_t)dw_waves(B, L) * DH * DH * 4);
+}
+
+// dL/dW from mu (a.du) and the states
+static int dense_weight_gradient(const DenseArgs &a, float *part, float *dW, hipStream_t st)
+{
+    const int wv = dw_waves(a.B, a.L);
+    const size_t rows = (size_t)a.B * a.L;
+    int rows_per_wave = (int)((rows + wv - 1) / wv);
+    rows_per_wave += rows_per_wave & 1;           // pairs of rows
+    hipLaunchKernelGGL(dense_dw_kernel, dim3(wv / 4), dim3(256), 0, st, a, part, rows_per_wave);
+    if (hipGetLastError() != hipSuccess) return PARARNN_HIP_ERROR;
+    return launch_param_reduce(part, dW, wv, DH * DH, st) == hipSuccess ? PARARNN_OK : PARARNN_HIP_ERROR;
 }
 
 int dense_backward(int dtype, const float *W, const void *u, const void *h0, const void *h, const void *g, int B,
@@ -1132,6 +1589,13 @@ int dense_backward(int dtype, const float *W, const void *u, const void *h0, con
     a.ctrl = reinterpret_cast<Ctrl *>(ws);
     a.g = static_cast<const float *>(g); a.du = static_cast<float *>(du);
     a.B = B; a.L = L; a.n_c = lo.n_c;
+    if (wavefront_pays(B, L, true)) {
+        const size_t items = ((size_t)B * L + 15) / 16, most = (size_t)device_cu_count() * 8;
+        a.W = W;
+        hipLaunchKernelGGL(dense_residual_kernel, dim3((unsigned)(items < most ? items : most)), dim3(256), 0, st, a, 5);
+        hipLaunchKernelGGL(dense_adjoint_kernel, dim3(B), dim3(320), 0, st, a, static_cast<float *>(dh0));
+        return dense_weight_gradient(a, part, dW, st);
+    }
     if (launch_reset(a.ctrl, nullptr, 0, nullptr, 0, st) != hipSuccess) return PARARNN_HIP_ERROR;
     hipLaunchKernelGGL(dense_transpose_kernel, dim3(1), dim3(256), 0, st, W, Wt);
     // d_l = 1 - tanh^2(W h_{l-1} + u_l) at the given states (forward addressing, W itself)
@@ -1151,13 +1615,7 @@ int dense_backward(int dtype, const float *W, const void *u, const void *h0, con
     hipLaunchKernelGGL(dense_final_sweep_kernel<true>, dim3(n_sweep), dim3(256), 0, st, a);
     // step-local gradients
     if (dh0) hipLaunchKernelGGL(dense_dh0_kernel, dim3(B), dim3(64), 0, st, W, a.du, L, static_cast<float *>(dh0));
-    const int wv = dw_waves(B, L);
-    const size_t rows = (size_t)B * L;
-    int rows_per_wave = (int)((rows + wv - 1) / wv);
-    rows_per_wave += rows_per_wave & 1;           // pairs of rows
-    hipLaunchKernelGGL(dense_dw_kernel, dim3(wv / 4), dim3(256), 0, st, a, part, rows_per_wave);
-    if (hipGetLastError() != hipSuccess) return PARARNN_HIP_ERROR;
-    return launch_param_reduce(part, dW, wv, DH * DH, st) == hipSuccess ? PARARNN_OK : PARARNN_HIP_ERROR;
+    return dense_weight_gradient(a, part, dW, st);
 }
 
 int dense_residual_norm(int dtype, const float *W, const void *u, const void *h0, const void *h, int B, int L, int H,
@@ -1230,6 +1688,13 @@ int dense_forward(int dtype, const float *W, const void *u, const void *h0, int 
             const hipError_t e = Kernels<RawScan<1>, float>::newton_iter(sl.cfg, f, false, st);
             if (e != hipSuccess) return PARARNN_HIP_ERROR;
         }
+        return hipGetLastError() == hipSuccess ? PARARNN_OK : PARARNN_HIP_ERROR;
+    }
+    // the maxima of the iterations lie where the chunk products would (at least 4096 words)
+    if (g_dense_products == 0 && max_iter > 0 && max_iter <= DH * DH && wavefront_pays(B, L, false)) {
+        unsigned int *gm = reinterpret_cast<unsigned int *>(ws + lo.off_A);
+        hipLaunchKernelGGL(dense_guess_kernel, dim3(res_blocks), dim3(256), 0, st, a, gm, max_iter);
+        hipLaunchKernelGGL(dense_wavefront_kernel, dim3(B), dim3(320), 0, st, a, gm);
         return hipGetLastError() == hipSuccess ? PARARNN_OK : PARARNN_HIP_ERROR;
     }
     if (launch_reset(a.ctrl, nullptr, 0, iters, status0, st) != hipSuccess) return PARARNN_HIP_ERROR;

@@ -429,3 +429,53 @@ def test_dense_persistent_launch_gives_up_after_a_bounded_wait(tail_mode):
     h, iters, _ = P.forward(w.cell, d["params"], d["u"], None, tol=w.tol, max_iter=32)
     torch.cuda.synchronize()
     assert int(iters.cpu()[1]) == 0
+
+
+# ------------------------------------------- substitution and chunk products
+
+@pytest.mark.parametrize("shape", [(1, 2), (2, 7), (1, 8), (3, 9), (2, 15), (1, 24), (2, 31), (600, 5)])
+def test_dense_substitution_iterates(oracle_mod, shape):
+    """Iterates of solves by forward substitution around its edges: groups of eight steps, blocks of four
+    iterations (one, an incomplete one, several), more sequences than the device runs at once."""
+    import paper_2510_21450_amd as P
+    B, L = shape
+    H = 64
+    print(f"dense substitution B={B} L={L}", flush=True)
+    W = normal(930 + L, 5, (H, H), std=0.8 / H ** 0.5, device="cuda")
+    u = normal(930 + L, 1, (B, L, 1, H), device="cuda")
+    h0 = normal(930 + L, 3, (B, 1, H), std=0.3, device="cuda")
+    for k in (1, 3, 4, 5, 9):
+        h, iters, tr = P.forward("tanh_dense", W, u, h0, tol=-1.0, max_iter=k, trace=True)
+        torch.cuda.synchronize()
+        hk, _, _, trk = oracle_mod.newton("tanh_dense", f64(W), f64(u), f64(h0), tol=-1.0, max_iter=k)
+        assert iters.cpu().tolist() == [k, 0]
+        assert relerr(f64(h), hk) <= 2e-5, k
+        assert np.allclose(tr.cpu().numpy()[:k], trk, rtol=1e-3, atol=2e-6), (k, tr, trk)
+
+
+@pytest.mark.parametrize("shape", [(2, 2700), (1, 2560), (1, 700)])
+def test_dense_long_sequences(oracle_mod, tail_mode, as_stored, shape):
+    """Few long sequences, on both sides of the line between substitution and chunk products: states,
+    counts and gradients against the oracle under every launch plan."""
+    import paper_2510_21450_amd as P
+    B, L = shape
+    H = 64
+    W = normal(920 + L, 5, (H, H), std=0.8 / H ** 0.5, device="cuda")
+    u = normal(920 + L, 1, (B, L, 1, H), device="cuda")
+    h0 = normal(920 + L, 3, (B, 1, H), std=0.3, device="cuda")
+    g = normal(920 + L, 4, (B, L, 1, H), device="cuda")
+    Wn, un, h0n = f64(W), f64(u), f64(h0)
+    ref = oracle_mod.seq_unroll("tanh_dense", Wn, un, h0n)
+    tol, want = well_posed_tol(oracle_mod, "tanh_dense", Wn, un, h0n, max_iter=32, probe_tol=1e-4)
+    for mode in (0, 1, 2):
+        print(f"dense long B={B} L={L} mode={mode}", flush=True)
+        tail_mode(mode)
+        h, iters, _ = P.forward("tanh_dense", W, u, h0, tol=tol, max_iter=32)
+        torch.cuda.synchronize()
+        assert iters.cpu().tolist() == [want, 0]
+        assert relerr(f64(h), ref) <= 1e-5
+    hs = as_stored(ref, u)
+    du, dW, dh0 = P.backward("tanh_dense", W, u, h0, hs, g)
+    torch.cuda.synchronize()
+    rdu, rdW, rdh0 = oracle_mod.backward("tanh_dense", Wn, un, h0n, f64(hs), f64(g))
+    assert relerr(f64(du), rdu) <= 1e-5 and relerr(f64(dW), rdW) <= 1e-5 and relerr(f64(dh0), rdh0) <= 1e-5
