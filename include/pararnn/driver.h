@@ -187,6 +187,59 @@ inline Layout make_layout(const CellInfo &ci, int dtype, int B, int L, int H, bo
     return lo;
 }
 
+// Shape of the one-workgroup kernels for a problem (short_kernels.h): c steps per thread, 64 >> lps_log2 segments per
+// wave, w waves; n_items workgroups.  fixed: a solve of a fixed number of iterations.  False where the kernels with
+// carry records do better.
+struct ShortShape { int c, lps_log2, w, n_cg, n_items; };
+inline bool short_shape(const CellInfo &ci, int dtype, int B, int L, int H, bool backward, bool fixed, ShortShape *out)
+{
+    const double n = (double)B * L * H, esz = dtype == PARARNN_BF16 ? 2.0 : 4.0;
+    // Steps per thread.  Below half a wave per SIMD at eight steps the chunk's own latency counts (4 x 250 x 100 GRU
+    // 10.9 -> 9.8 us with four).  Sixteen spread the wave and workgroup levels of an iteration over more cell
+    // evaluations and are what makes longer sequences fit; the adjoint scan passes those levels once.
+    int c = ci.S > 2 || n < 512.0 * 512.0 ? 4 : backward || L <= 512 ? 8 : 16;
+    if (c == 4 && ci.S <= 2 && L > 1024) c = backward ? 8 : 16;
+    // Waves per workgroup: four iterate fastest (two barriers in every iteration; workgroups of eight leave fewer of
+    // them on a compute unit); the single pass backward takes all there may be, for longer pieces of rows.
+    const int wmax = ci.S * c <= 8 ? 16 : 8, want = backward ? wmax : 4;
+    int ll = 1;
+    while (ll < 16 && c * ll * want < L) ll *= 2;
+    const int w = (L + c * ll - 1) / (c * ll);
+    if (w > wmax) return false;
+    // Long sequences mean 16-byte pieces of rows (four channels per group), for which the memory pipeline needs as
+    // many cycles as for whole lines: fine where latency bounds the other kernels too, not on large tensors.
+    if (backward) {
+        // GRU fp32 (us, record kernels / these): 64 steps x 32 x 4096 66 / 52; 250 x 16 x 1000 36 / 26 but x 32 x 4096
+        // 203 / 214; 500 x 16 x 1024 59 / 56; 1000 x 8 x 1536 87 / 122; 2000 x 2 x 1000 36 / 47; two-state cells
+        // 777 x 5 x 333 25 / 30
+        if (ci.S >= 2 && L > 512) return false;
+        const double bytes = n * esz * (2 * ci.G + 2 * ci.S);
+        const double most = L <= 128 ? 1e30 : L <= 256 ? 512e6 : L <= 512 ? 192e6 : L <= 1024 ? 96e6 : 32e6;
+        if (bytes > most) return false;
+    } else if (L > 1024) {
+        // 2000 x 8 x 1000: GRU fp32 156 / 137, bf16 160 / 133, two-state cells 264 / 379 (5 iterations) and 450 / 358
+        // (LSTM: 6; what wins there is that groups of channels stop on their own, which a fixed count does not:
+        // 1531 x 3 x 1001, three iterations, 81 / 118); 2048 x 8 x 2048: GRU fp32 264 / 279, bf16 287 / 242
+        if (ci.S >= 2 && fixed) return false;
+        const double most = ci.S >= 2 ? (ci.kind == PARARNN_LSTM_DIAG ? 64e6 : 16e6) : 68e6;
+        if (n * esz > most) return false;
+    }
+    const double row = (double)ci.G * H * esz;
+    if (row * ((double)c * ll * w + 1.0) >= 2147483647.0) return false;       // 32-bit offsets within a sequence
+    int lps = 6;
+    while ((64 >> lps) < ll) --lps;
+    out->c = c; out->lps_log2 = lps; out->w = w;
+    out->n_cg = (H + (1 << lps) - 1) >> lps;
+    if ((double)B * out->n_cg > 131072.0) return false;      // verdicts that workgroup 0 collects
+    out->n_items = B * out->n_cg;
+    return true;
+}
+// workspace of such a solve: the control block (not used) and the workgroups' verdicts
+inline size_t short_workspace_bytes(const ShortShape &sh)
+{
+    return round256(sizeof(Ctrl)) + round256((size_t)sh.n_items * 2 * sizeof(rec_t));
+}
+
 inline bool dims_ok(int B, int L, int H)
 {
     if (B < 1 || L < 1 || H < 1) return false;
@@ -234,6 +287,9 @@ inline size_t diag_workspace_bytes(const CellInfo &ci, int dtype, int B, int L, 
             if (lf.total > need) need = lf.total;
         }
     }
+    ShortShape sh;
+    if (!backward && short_shape(ci, dtype, B, L, H, false, false, &sh) && short_workspace_bytes(sh) > need)
+        need = short_workspace_bytes(sh);
     return need;
 }
 
@@ -363,6 +419,29 @@ inline int check_backward_args(int dtype, const float *params, const void *u, co
     return PARARNN_OK;
 }
 
+// The whole solve in one launch, sequences inside workgroups.
+template <class Cell>
+int forward_short(int dtype, const ShortShape &sh, const float *params, const void *u, const void *h0, int B, int L,
+                  int H, float tol, int max_iter, void *h, int *iters, void *workspace, hipStream_t st)
+{
+    char *ws = static_cast<char *>(workspace);
+    ShortArgs a;
+    memset(&a, 0, sizeof(a));
+    a.B = B; a.L = L; a.H = H; a.n_cg = sh.n_cg; a.lps_log2 = sh.lps_log2; a.n_items = sh.n_items;
+    a.params = params; a.u = u; a.h0 = h0; a.h = h; a.tol = tol; a.max_iter = max_iter; a.iters_out = iters;
+    a.spin_limit = settings().spin_limit;
+    a.slots = reinterpret_cast<rec_t *>(ws + round256(sizeof(Ctrl)));
+    a.nonce = call_nonce();
+    workspace_forget(workspace);
+    // a captured launch replays its nonce: the verdicts are cleared in front of it
+    if (sh.n_items > 1 && stream_is_capturing(st) &&
+        launch_reset(reinterpret_cast<Ctrl *>(ws), a.slots, (size_t)sh.n_items * 2, nullptr, 0, st) != hipSuccess)
+        return PARARNN_HIP_ERROR;
+    const hipError_t e = dtype == PARARNN_BF16 ? Kernels<Cell, unsigned short>::newton_short(sh.c, sh.w, a, st)
+                                               : Kernels<Cell, float>::newton_short(sh.c, sh.w, a, st);
+    return e == hipSuccess ? PARARNN_OK : PARARNN_HIP_ERROR;
+}
+
 // A forward solve with checked arguments: layout, then the launches.
 template <class Cell>
 int forward_solve(const CellInfo &ci, int dtype, const float *params, const void *u, const void *h0, int B, int L,
@@ -371,6 +450,10 @@ int forward_solve(const CellInfo &ci, int dtype, const float *params, const void
 {
     const size_t esz = dtype == PARARNN_BF16 ? 2 : 4;
     const int status0 = tol < 0.0f ? PARARNN_OK : PARARNN_NOT_CONVERGED;
+    ShortShape sh;
+    if (opts.fused_enabled && opts.fused_head > 0 && max_iter > 0 && !delta_trace && settings().tile[0] <= 0 &&
+        short_shape(ci, dtype, B, L, H, false, tol < 0.0f, &sh) && workspace_bytes >= short_workspace_bytes(sh))
+        return forward_short<Cell>(dtype, sh, params, u, h0, B, L, H, tol, max_iter, h, iters, workspace, st);
     int al = align_elems(esz, {u, h, h0});
     const int alp = align_elems(4, {params});
     if (alp < al) al = alp;
@@ -450,6 +533,19 @@ int backward_pass(const CellInfo &ci, int dtype, const float *params, const void
     if (alp < al) al = alp;
     const Layout lo = make_layout(ci, dtype, B, L, H, true, al);
     if (workspace_bytes < lo.total) return PARARNN_WORKSPACE_TOO_SMALL;
+    ShortShape sh;
+    if (settings().tile[0] <= 0 && short_shape(ci, dtype, B, L, H, true, false, &sh)) {
+        ShortArgs a;
+        memset(&a, 0, sizeof(a));
+        a.B = B; a.L = L; a.H = H; a.n_cg = sh.n_cg; a.lps_log2 = sh.lps_log2; a.n_items = sh.n_items;
+        a.params = params; a.u = u; a.h0 = h0; a.hs = h; a.gl = dL_dh; a.du = dL_du; a.dh0 = dL_dh0;
+        a.part = B > 1 ? static_cast<float *>(workspace) : dL_dparams;   // a single sequence's sums are the gradient
+        workspace_forget(workspace);
+        hipError_t e = dtype == PARARNN_BF16 ? Kernels<Cell, unsigned short>::backward_short(sh.c, sh.w, a, st)
+                                             : Kernels<Cell, float>::backward_short(sh.c, sh.w, a, st);
+        if (e == hipSuccess && B > 1) e = launch_param_reduce(a.part, dL_dparams, B, ci.PR * H, st);
+        return e == hipSuccess ? PARARNN_OK : PARARNN_HIP_ERROR;
+    }
     char *ws = static_cast<char *>(workspace);
     BwdArgs a;
     memset(&a, 0, sizeof(a));

@@ -2,6 +2,7 @@
 // instantiations (each cell / storage type is compiled in its own file).
 #pragma once
 #include "fused_kernels.h"
+#include "short_kernels.h"
 
 namespace pararnn {
 
@@ -30,6 +31,9 @@ template <class Cell, typename UT> struct Kernels {
     static hipError_t backward(const TileCfg &cfg, const BwdArgs &a, hipStream_t st);
     // all iterations of a fixed-count solve in one launch
     static hipError_t newton_fused(const TileCfg &cfg, const FusedArgs &a, hipStream_t st);
+    // sequences that fit one workgroup of w waves, c steps per thread (short_kernels.h)
+    static hipError_t newton_short(int c, int w, const ShortArgs &a, hipStream_t st);
+    static hipError_t backward_short(int c, int w, const ShortArgs &a, hipStream_t st);
 };
 
 hipError_t launch_reset(Ctrl *ctrl, unsigned long long *rec, size_t n_rec, int *iters_out, int status0,
@@ -47,6 +51,9 @@ int device_cu_count();
 // records carry another number and read as empty.  Without the caller's promise, under stream capture (a
 // captured launch sequence would replay one number) and for a new address or signature: 0 / 1 and *fill = true.
 unsigned int workspace_epoch(void *workspace, unsigned long long layout_sig, hipStream_t st, bool *fill);
+// A number no other call of this process has, and no other memory by more than chance (64 random bits to start from).
+unsigned long long call_nonce();
+bool stream_is_capturing(hipStream_t st);
 // The library no longer knows what this workspace holds (a call on it failed, or ran without a signature).
 void workspace_forget(void *workspace);
 

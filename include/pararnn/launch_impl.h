@@ -132,6 +132,49 @@ hipError_t Kernels<Cell, UT>::newton_fused(const TileCfg &cfg, const FusedArgs &
     }
 }
 
+template <class Cell, typename UT>
+hipError_t Kernels<Cell, UT>::newton_short(int c, int w, const ShortArgs &a, hipStream_t st)
+{
+    if constexpr (IsRaw<Cell>::value) {
+        return hipErrorInvalidValue;
+    } else {
+        const unsigned int grid = 8u * (unsigned int)((a.n_items + 7) / 8);
+        const size_t lds = w > 1 ? ((size_t)w * (Cell::S * Cell::S + Cell::S) << a.lps_log2) * sizeof(float) : 0;
+#define PARARNN_CASE(C)                                                                                           \
+    if constexpr (short_offered<Cell, C>(false)) {                                                                   \
+        if (c == C && w <= short_max_waves<Cell, C>()) {                                                          \
+            hipLaunchKernelGGL((newton_short_kernel<Cell, C, UT>), dim3(grid), dim3(kWave * w), lds, st, a);          \
+            return hipGetLastError();                                                                             \
+        }                                                                                                         \
+    }
+        PARARNN_CASE(4) PARARNN_CASE(8) PARARNN_CASE(16)
+#undef PARARNN_CASE
+        return hipErrorInvalidValue;
+    }
+}
+
+template <class Cell, typename UT>
+hipError_t Kernels<Cell, UT>::backward_short(int c, int w, const ShortArgs &a, hipStream_t st)
+{
+    if constexpr (IsRaw<Cell>::value) {
+        return hipErrorInvalidValue;
+    } else {
+        constexpr int SA = Cell::S * Cell::S + Cell::S, rows = SA > Cell::PR ? SA : Cell::PR;
+        const unsigned int grid = 8u * (unsigned int)((a.n_items + 7) / 8);
+        const size_t lds = w > 1 ? ((size_t)w * rows << a.lps_log2) * sizeof(float) : 0;
+#define PARARNN_CASE(C)                                                                                           \
+    if constexpr (short_offered<Cell, C>(true)) {                                                                   \
+        if (c == C && w <= short_max_waves<Cell, C>()) {                                                          \
+            hipLaunchKernelGGL((backward_short_kernel<Cell, C, UT>), dim3(grid), dim3(kWave * w), lds, st, a);          \
+            return hipGetLastError();                                                                             \
+        }                                                                                                         \
+    }
+        PARARNN_CASE(4) PARARNN_CASE(8) PARARNN_CASE(16)
+#undef PARARNN_CASE
+        return hipErrorInvalidValue;
+    }
+}
+
 // The LDS-staged variant of the backward kernel exists for bf16 storage, one channel per lane, one
 // segment per wave and steps per thread in multiples of 8 (one copy instruction moves 8 rows).
 template <class Cell, int VEC, int LL, int C, typename UT> constexpr bool backward_stage_offered()

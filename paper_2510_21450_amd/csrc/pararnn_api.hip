@@ -1,6 +1,8 @@
 // C ABI of the library (see include/pararnn.h) for the built-in cells; the
 // cell-generic host driver is driver.h.  No kernel code here.
+#include <atomic>
 #include <mutex>
+#include <random>
 #include <unordered_map>
 
 #include "dense.h"
@@ -35,14 +37,27 @@ unsigned long long ws_key(const void *workspace)
 }
 }  // namespace
 
+bool stream_is_capturing(hipStream_t st)
+{
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone;
+}
+
+unsigned long long call_nonce()
+{
+    static std::atomic<unsigned long long> next([] {
+        std::random_device rd;
+        return (unsigned long long)rd() << 32 | rd();
+    }());
+    return next.fetch_add(1, std::memory_order_relaxed);
+}
+
 unsigned int workspace_epoch(void *workspace, unsigned long long layout_sig, hipStream_t st, bool *fill)
 {
     *fill = true;
     const unsigned long long key = ws_key(workspace);
     std::lock_guard<std::mutex> lock(g_ws_mutex);
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    const bool capturing = hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone;
-    if (!settings().ws_reuse || capturing) {
+    if (!settings().ws_reuse || stream_is_capturing(st)) {
         g_ws_notes.erase(key);
         return 0u;
     }

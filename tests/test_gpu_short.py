@@ -1,0 +1,88 @@
+"""Solves and backward passes whose sequences fit one workgroup (include/pararnn/short_kernels.h), at the edges of
+their shapes: steps per thread, segments per wave, waves per workgroup, channel groups, the limits beyond which
+the kernels with carry records take over."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+from test_gpu_parity import problem, relerr, to_np      # noqa: E402
+from parity_util import well_posed_tol                   # noqa: E402
+
+SHAPES = [(1, 1, 1), (3, 4, 5), (2, 5, 64), (1, 64, 65), (2, 65, 3), (1, 127, 9), (2, 129, 33), (1, 512, 4), (1, 513, 6),
+          (2, 777, 17), (1, 1024, 5), (1, 1025, 3), (1, 2048, 2), (1, 2049, 2), (150, 9, 70), (70, 300, 260)]
+
+
+@pytest.mark.parametrize("cell", ["gru_diag", "lstm_diag", "paralstm_diag"])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_short_sequences(oracle_mod, as_stored, cell, shape):
+    import paper_2510_21450_amd as P
+    B, L, H = shape
+    dtype = torch.bfloat16 if (B + L + H) % 3 == 0 else torch.float32
+    bound = 1e-5 if dtype == torch.float32 else 2e-2
+    print(f"short {cell} {shape} {dtype}", flush=True)
+    params, u, h0, g = problem(cell, B, L, H, seed=41 + L, dtype=dtype)
+    pn, un, h0n, gn = to_np(params), to_np(u), to_np(h0), to_np(g)
+    tol, want = well_posed_tol(oracle_mod, cell, pn, un, h0n)
+    ref = oracle_mod.seq_unroll(cell, pn, un, h0n)
+    h, iters, _ = P.forward(cell, params, u, h0, tol=tol, max_iter=40)
+    torch.cuda.synchronize()
+    assert iters.cpu().tolist() == [want, 0]
+    assert relerr(to_np(h), ref) <= bound
+    # fixed counts, on both sides of what one fused block runs
+    for k in (2, 9):
+        h, iters, _ = P.forward(cell, params, u, h0, tol=-1.0, max_iter=k)
+        hk = oracle_mod.newton(cell, pn, un, h0n, tol=-1.0, max_iter=k)[0]
+        assert iters.cpu().tolist() == [k, 0] and relerr(to_np(h), hk) <= 2 * bound
+    hs = as_stored(ref, u)
+    got = P.backward(cell, params, u, h0, hs, g)
+    torch.cuda.synchronize()
+    for x, r in zip(got, oracle_mod.backward(cell, pn, un, h0n, to_np(hs), gn)):
+        assert relerr(to_np(x), r) <= bound
+    again = P.backward(cell, params, u, h0, hs, g)          # fixed order of summation
+    assert all(torch.equal(x, y) for x, y in zip(got, again))
+
+
+def test_short_verdicts(oracle_mod):
+    """Not converged, a NaN in one group of channels (its first iteration counts, whatever the others do), and
+    groups that stop at different iterations."""
+    import paper_2510_21450_amd as P
+    B, L, H = 3, 200, 150
+    params, u, h0, _ = problem("gru_diag", B, L, H, seed=77)
+    pn, un, h0n = to_np(params), to_np(u), to_np(h0)
+    _, iters, _ = P.forward("gru_diag", params, u, h0, tol=0.0, max_iter=3)
+    assert iters.cpu().tolist() == [3, 1]
+    bad = u.clone()
+    bad[1, 50, 0, 70] = float("nan")
+    _, iters, _ = P.forward("gru_diag", params, bad, h0, tol=1e-5, max_iter=20)
+    _, it, st, _ = oracle_mod.newton("gru_diag", pn, to_np(bad), h0n, tol=1e-5, max_iter=20)
+    assert iters.cpu().tolist() == [it, st] == [1, 5]
+    calm = u.clone()
+    calm[:, :, :, 64:] *= 1e-3                              # channels that need fewer iterations
+    tol, want = well_posed_tol(oracle_mod, "gru_diag", pn, to_np(calm), h0n)
+    h, iters, _ = P.forward("gru_diag", params, calm, h0, tol=tol, max_iter=20)
+    assert iters.cpu().tolist() == [want, 0]
+    assert relerr(to_np(h), oracle_mod.seq_unroll("gru_diag", pn, to_np(calm), h0n)) <= 1e-5
+
+
+def test_short_solve_in_a_graph(oracle_mod):
+    """A captured solve replays its verdicts' nonce: every replay clears them first."""
+    import paper_2510_21450_amd as P
+    B, L, H = 4, 100, 96
+    params, u, h0, _ = problem("lstm_diag", B, L, H, seed=78)
+    inputs = [u.clone(), u * 0.5, u * 1.5, torch.full_like(u, float("nan")), u * 0.1]
+    eager = [[t.clone() for t in P.forward("lstm_diag", params, x, h0, tol=1e-4, max_iter=30)[:2]] for x in inputs]
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        P.forward("lstm_diag", params, u, h0, tol=1e-4, max_iter=30)
+    torch.cuda.current_stream().wait_stream(side)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        h, iters, _ = P.forward("lstm_diag", params, u, h0, tol=1e-4, max_iter=30)
+    for x, (eh, ei) in zip(inputs, eager):
+        u.copy_(x)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert iters.cpu().tolist() == ei.cpu().tolist()
+        assert torch.equal(torch.nan_to_num(h), torch.nan_to_num(eh))
