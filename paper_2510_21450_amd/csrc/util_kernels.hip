@@ -84,6 +84,22 @@ __global__ __launch_bounds__(1024) void param_reduce_kernel(const float *part, f
     }
 }
 
+// The same sum where there are many outputs and few terms (the row ranges of a weight gradient): a thread owns four
+// outputs and runs through the terms.  With the kernel above 13 of 16 slices had nothing to add and there was a workgroup
+// of 1024 threads for every 64 outputs: 61 -> 14 us for 2.4e6 outputs of three terms.
+__global__ __launch_bounds__(256) void param_reduce_few_kernel(const float *part, float *out, int n_terms, int n_out4)
+{
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= n_out4) return;
+    const float4 *p = reinterpret_cast<const float4 *>(part) + i;
+    float4 s = p[0];
+    for (int t = 1; t < n_terms; ++t) {
+        const float4 x = p[(size_t)t * n_out4];
+        s.x += x.x; s.y += x.y; s.z += x.z; s.w += x.w;
+    }
+    reinterpret_cast<float4 *>(out)[i] = s;
+}
+
 }  // namespace pararnn
 
 namespace pararnn {
@@ -134,6 +150,12 @@ hipError_t launch_store_bf16(const float *src, void *dst, size_t n, const Ctrl *
 
 hipError_t launch_param_reduce(const float *part, float *out, int n_terms, int n_out, hipStream_t st)
 {
+    // few terms per output and enough outputs for a wave per SIMD
+    if (n_terms <= 16 && n_out >= (1 << 18) && n_out % 4 == 0 &&
+        (reinterpret_cast<uintptr_t>(part) | reinterpret_cast<uintptr_t>(out)) % 16 == 0) {
+        hipLaunchKernelGGL(param_reduce_few_kernel, dim3((n_out / 4 + 255) / 256), dim3(256), 0, st, part, out, n_terms, n_out / 4);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(param_reduce_kernel, dim3((n_out + 63) / 64), dim3(1024), 0, st, part, out, n_terms, n_out);
     return hipGetLastError();
 }
