@@ -1,5 +1,6 @@
-"""ctypes binding: one Python function per entry point of include/pararnn.h,
-same names without the prefix.  Argument marshalling only."""
+"""Python binding: one function per entry point of include/pararnn.h, same names without the prefix.
+Argument marshalling only: by the native module _host (csrc/host_binding.cpp) for the calls of a model's
+inner loop, by ctypes for the rest."""
 from __future__ import annotations
 
 import ctypes
@@ -20,6 +21,11 @@ if not os.path.exists(_LIB_PATH):
                       "(there is no CPU fallback)")
 
 _lib = ctypes.CDLL(_LIB_PATH)
+try:
+    from . import _host
+except ImportError as e:
+    raise ImportError(f"the native binding module beside {_LIB_PATH} is missing or unusable ({e}): build it with "
+                      "`python -m paper_2510_21450_amd.build`") from e
 for _name in ("pararnn_input_projection", "pararnn_residual_norm", "pararnn_set_dense_jacobian", "pararnn_device_info", "pararnn_set_dense_products", "pararnn_solve_plan", "pararnn_affine_scan_workspace_bytes"):
     if not hasattr(_lib, _name):
         raise ImportError(f"{_LIB_PATH} is older than this binding ({_name} is missing): rebuild it with "
@@ -47,8 +53,6 @@ _lib.pararnn_set_dense_products.argtypes = [_i]
 _lib.pararnn_set_fused_head.argtypes = [_i]
 _lib.pararnn_solve_plan.restype = _i
 _lib.pararnn_solve_plan.argtypes = [ctypes.c_float, _i, ctypes.POINTER(ctypes.c_int), _i]
-_lib.pararnn_forward.restype = _i
-_lib.pararnn_forward.argtypes = [_i, _i, _vp, _vp, _vp, _i, _i, _i, _f, _i, _vp, _vp, _vp, _vp, _sz, _vp]
 class _SolveOptions(ctypes.Structure):
     _fields_ = [("first_block", ctypes.c_int), ("fused", ctypes.c_int)]
 
@@ -62,8 +66,6 @@ _lib.pararnn_solve_plan_ex.restype = _i
 _lib.pararnn_solve_plan_ex.argtypes = [ctypes.c_float, _i, ctypes.POINTER(_SolveOptions), ctypes.POINTER(ctypes.c_int), _i]
 _lib.pararnn_forward_noalloc.restype = _i
 _lib.pararnn_forward_noalloc.argtypes = [_i, _i, _vp, _vp, _vp, _i, _i, _i, _f, _i, _vp, _vp, _vp, _vp]
-_lib.pararnn_backward.restype = _i
-_lib.pararnn_backward.argtypes = [_i, _i, _vp, _vp, _vp, _vp, _vp, _i, _i, _i, _vp, _vp, _vp, _vp, _sz, _vp]
 _lib.pararnn_dense_chunk_products.restype = _i
 _lib.pararnn_dense_chunk_products.argtypes = [_vp, _vp, _i, _i, _i, _vp, _vp, _sz, _vp]
 _lib.pararnn_affine_scan.restype = _i
@@ -72,8 +74,6 @@ _lib.pararnn_affine_scan_workspace_bytes.argtypes = [_i] * 5
 _lib.pararnn_affine_scan.argtypes = [_i, _i, _vp, _vp, _i, _i, _i, _vp, _vp, _sz, _vp]
 
 
-_FWD_ARGS = [_i, _vp, _vp, _vp, _i, _i, _i, _f, _i, _vp, _vp, _vp, _vp, _sz, _vp]
-_BWD_ARGS = [_i, _vp, _vp, _vp, _vp, _vp, _i, _i, _i, _vp, _vp, _vp, _vp, _sz, _vp]
 _RES_ARGS = [_i, _vp, _vp, _vp, _vp, _i, _i, _i, _vp, _vp]
 _lib.pararnn_residual_norm.restype = _i
 _lib.pararnn_residual_norm.argtypes = [_i] + _RES_ARGS
@@ -89,8 +89,7 @@ class _BuiltinCell:
         self.what = "pararnn"
         self.ws = lambda *a: _lib.pararnn_workspace_bytes(c, *a)
         self.ws_fused = lambda *a: _lib.pararnn_workspace_bytes_fused(c, *a)
-        self.fwd = lambda *a: _lib.pararnn_forward(c, *a)
-        self.bwd = lambda *a: _lib.pararnn_backward(c, *a)
+        self.host = _host.builtin_cell(c, self.what)
         self.res = lambda *a: _lib.pararnn_residual_norm(c, *a)
 
 
@@ -105,11 +104,12 @@ class UserCell:
         self._lib = lib = ctypes.CDLL(lib_path)
         f = lambda s: getattr(lib, f"{name}_{s}")
         self.G, self.S, self.param_rows = f("gates")(), f("state")(), f("param_rows")()
-        self.ws, self.ws_fused, self.fwd, self.bwd = f("workspace_bytes"), f("workspace_bytes_fused"), f("forward"), f("backward")
+        self.ws, self.ws_fused = f("workspace_bytes"), f("workspace_bytes_fused")
         self.ws.restype = self.ws_fused.restype = _sz
         self.ws.argtypes = self.ws_fused.argtypes = [_i] * 5
-        self.fwd.restype = self.bwd.restype = _i
-        self.fwd.argtypes, self.bwd.argtypes = _FWD_ARGS, _BWD_ARGS
+        address = lambda s: ctypes.cast(f(s), _vp).value
+        self.host = _host.library_cell(name, self.G, self.S, address("workspace_bytes"), address("workspace_bytes_fused"),
+                                       address("forward"), address("backward"))
         self.res = f("residual_norm")
         self.res.restype, self.res.argtypes = _i, _RES_ARGS
 
@@ -274,6 +274,11 @@ def _stream(stream):
     return s.cuda_stream
 
 
+def _raw_stream(stream):
+    """The stream's handle for the native module, which takes the current stream for None itself."""
+    return None if stream is None else stream.cuda_stream
+
+
 def _workspace(nbytes, device, workspace):
     if workspace is None:
         workspace = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
@@ -291,24 +296,7 @@ def forward(cell, params, u, h0=None, tol: float = 1e-6, max_iter: int = 64, tra
     Returns (h, iters, delta_trace): iters is a DEVICE int32[2] tensor
     {iterations, status} (no synchronisation happens here), delta_trace a
     device float[max_iter] tensor or None."""
-    G, S = cell_dims(cell)
-    B, L, Gu, H = u.shape
-    dt = u.dtype
-    _check(u, "u", dt, (B, L, G, H))
-    _check(params, "params", torch.float32)
-    if h0 is not None:
-        _check(h0, "h0", dt, (B, S, H))
-    h = torch.empty((B, L, S, H), dtype=dt, device=u.device) if out is None else out
-    _check(h, "h", dt, (B, L, S, H))
-    iters = torch.empty(2, dtype=torch.int32, device=u.device)
-    tr = torch.zeros(max(max_iter, 1), dtype=torch.float32, device=u.device) if trace else None
-    need = workspace_bytes_fused(cell, dt, B, L, H, max_iter) if tol < 0 else workspace_bytes(cell, dt, B, L, H, False)
-    ws = _workspace(need, u.device, workspace)
-    api = _api(cell)
-    code = api.fwd(DTYPES[dt], _ptr(params), _ptr(u), _ptr(h0), B, L, H, tol, max_iter,
-                   _ptr(h), _ptr(iters), _ptr(tr), _ptr(ws), ws.numel(), _stream(stream))
-    _raise(code, f"{api.what}_forward")
-    return h, iters, tr
+    return _host.forward(_api(cell).host, params, u, h0, tol, max_iter, trace, workspace, _raw_stream(stream), out)
 
 
 def forward_ex(cell, params, u, h0=None, tol: float = 1e-6, max_iter: int = 64, first_block: int = -1, fused: int = -1,
@@ -370,31 +358,8 @@ def forward_noalloc(cell, params, u, h0, tol, max_iter, out, iters, delta_trace=
 def backward(cell, params, u, h0, h, dL_dh, want_dh0: bool = True, workspace=None, stream=None, out=None):
     """pararnn_backward.  Returns (dL_du, dL_dparams, dL_dh0 or None); `out`
     may hold a preallocated (dL_du, dL_dparams, dL_dh0) triple."""
-    G, S = cell_dims(cell)
-    B, L, Gu, H = u.shape
-    dt = u.dtype
-    _check(u, "u", dt, (B, L, G, H))
-    _check(params, "params", torch.float32)
-    _check(h, "h", dt, (B, L, S, H))
-    _check(dL_dh, "dL_dh", dt, (B, L, S, H))
-    if h0 is not None:
-        _check(h0, "h0", dt, (B, S, H))
-    if out is not None:
-        du, dparams, dh0 = out
-        _check(du, "dL_du", dt, u.shape)
-        _check(dparams, "dL_dparams", torch.float32, params.shape)
-        if dh0 is not None:
-            _check(dh0, "dL_dh0", dt, (B, S, H))
-    else:
-        du = torch.empty_like(u)
-        dparams = torch.empty_like(params)
-        dh0 = torch.empty((B, S, H), dtype=dt, device=u.device) if want_dh0 else None
-    ws = _workspace(workspace_bytes(cell, dt, B, L, H, True), u.device, workspace)
-    api = _api(cell)
-    code = api.bwd(DTYPES[dt], _ptr(params), _ptr(u), _ptr(h0), _ptr(h), _ptr(dL_dh),
-                   B, L, H, _ptr(du), _ptr(dparams), _ptr(dh0), _ptr(ws), ws.numel(), _stream(stream))
-    _raise(code, f"{api.what}_backward")
-    return du, dparams, dh0
+    return _host.backward(_api(cell).host, params, u, h0, h, dL_dh, want_dh0, workspace, _raw_stream(stream),
+                          *(out if out is not None else (None, None, None)))
 
 
 def residual_norm(cell, params, u, h0, h, stream=None, out=None):
@@ -418,10 +383,6 @@ def residual_norm(cell, params, u, h0, h, stream=None, out=None):
 
 _lib.pararnn_input_projection_workspace_bytes.restype = _sz
 _lib.pararnn_input_projection_workspace_bytes.argtypes = [_i] * 7
-_lib.pararnn_input_projection.restype = _i
-_lib.pararnn_input_projection.argtypes = [_i, _vp, _vp, _vp, _i, _i, _i, _i, _i, _vp, _vp, _sz, _vp]
-_lib.pararnn_input_projection_backward.restype = _i
-_lib.pararnn_input_projection_backward.argtypes = [_i, _vp, _vp, _vp, _i, _i, _i, _i, _i, _vp, _vp, _vp, _vp, _sz, _vp]
 
 
 def input_projection_workspace_bytes(dtype, B: int, L: int, H: int, G: int, n_heads: int = 1, backward: bool = False) -> int:
@@ -431,39 +392,13 @@ def input_projection_workspace_bytes(dtype, B: int, L: int, H: int, G: int, n_he
 def input_projection(x, Wx, bias=None, n_heads: int = 1, workspace=None, stream=None, out=None):
     """pararnn_input_projection.  x [B][L][H], Wx fp32 [G][H][H / n_heads], bias fp32 [G][H] or None
     -> u [B][L][G][H] of x's dtype."""
-    B, L, H = x.shape
-    G = Wx.shape[0]
-    dt = x.dtype
-    _check(x, "x", dt, (B, L, H))
-    _check(Wx, "Wx", torch.float32, (G, H, H // n_heads))
-    if bias is not None:
-        _check(bias, "bias", torch.float32, (G, H))
-    u = torch.empty((B, L, G, H), dtype=dt, device=x.device) if out is None else out
-    _check(u, "u", dt, (B, L, G, H))
-    ws = _workspace(input_projection_workspace_bytes(dt, B, L, H, G, n_heads), x.device, workspace)
-    code = _lib.pararnn_input_projection(DTYPES[dt], _ptr(x), _ptr(Wx), _ptr(bias), B, L, H, G, n_heads, _ptr(u),
-                                         _ptr(ws), ws.numel(), _stream(stream))
-    _raise(code, "pararnn_input_projection")
-    return u
+    return _host.input_projection(x, Wx, bias, n_heads, workspace, _raw_stream(stream), out)
 
 
 def input_projection_backward(x, Wx, du, n_heads: int = 1, want_dx: bool = True, want_dw: bool = True,
                               want_dbias: bool = True, workspace=None, stream=None):
     """pararnn_input_projection_backward.  Returns (dx, dWx, dbias); entries not wanted are None."""
-    B, L, H = x.shape
-    G = Wx.shape[0]
-    dt = x.dtype
-    _check(x, "x", dt, (B, L, H))
-    _check(Wx, "Wx", torch.float32, (G, H, H // n_heads))
-    _check(du, "du", dt, (B, L, G, H))
-    dx = torch.empty_like(x) if want_dx else None
-    dW = torch.empty_like(Wx) if want_dw else None
-    db = torch.empty((G, H), dtype=torch.float32, device=x.device) if want_dbias else None
-    ws = _workspace(input_projection_workspace_bytes(dt, B, L, H, G, n_heads, True), x.device, workspace)
-    code = _lib.pararnn_input_projection_backward(DTYPES[dt], _ptr(x), _ptr(Wx), _ptr(du), B, L, H, G, n_heads,
-                                                  _ptr(dx), _ptr(dW), _ptr(db), _ptr(ws), ws.numel(), _stream(stream))
-    _raise(code, "pararnn_input_projection_backward")
-    return dx, dW, db
+    return _host.input_projection_backward(x, Wx, du, n_heads, want_dx, want_dw, want_dbias, workspace, _raw_stream(stream))
 
 
 def affine_scan(J, r, reverse: bool = False, workspace=None, stream=None):

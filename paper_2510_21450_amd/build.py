@@ -1,5 +1,7 @@
 """Builds libpararnn.so (gfx950) in-tree with hipcc.
 
+Beside it goes _host.so, the native half of the Python binding (host code only,
+compiled against the installed torch).
 Each .hip file is compiled to an object on its own (in parallel) and linked
 into paper_2510_21450_amd/libpararnn.so.  No GPU is needed to build.
 
@@ -30,6 +32,7 @@ FLAGS = ["--offload-arch=gfx950", f"-I{INCLUDE}", "-O3", "-std=c++17", "-fPIC", 
          "-Wno-sometimes-uninitialized", "-Wno-uninitialized"]
 
 
+HOST = os.path.join(PKG, "_host.so")
 USER_CELLS = os.path.join(PKG, "user_cells")
 
 
@@ -82,6 +85,35 @@ def build_cell(src: str, out: str | None = None, extra_flags=(), verbose: bool =
     return out
 
 
+def _host_command(out: str, link: bool):
+    """Host compilation of the native binding module (no device code) against the installed torch."""
+    import sysconfig
+    import torch
+    t = os.path.join(os.path.dirname(os.path.abspath(torch.__file__)))
+    inc = [INCLUDE, os.path.join(t, "include"), os.path.join(t, "include", "torch", "csrc", "api", "include"),
+           "/opt/rocm/include", sysconfig.get_paths()["include"]]
+    if not link:
+        return [HIPCC, "-x", "c++", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM", "-O2", "-std=c++17", "-fPIC", "-fvisibility=hidden",
+                *(f"-I{i}" for i in inc), "-c", os.path.join(CSRC, "host_binding.cpp"), "-o", out]
+    return [HIPCC, "-shared", "-fPIC", "-o", HOST, out, f"-L{PKG}", "-lpararnn", f"-L{os.path.join(t, 'lib')}", "-ltorch",
+            "-ltorch_cpu", "-ltorch_python", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN"]
+
+
+def _host_step(obj: str, link: bool) -> str:
+    r = subprocess.run(_host_command(obj, link), capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("building the native binding module failed:\n" + r.stderr)
+    return obj
+
+
+def build_host(obj: str | None = None, verbose: bool = False) -> str:
+    """The native binding module (_host.so beside the library).  `obj`: its object file, if there is one already."""
+    _host_step(obj or _host_step(os.path.join(OBJ, "host_binding.cpp.o"), False), True)
+    if verbose:
+        print("built", HOST)
+    return HOST
+
+
 def build_examples(jobs: int | None = None, verbose: bool = False):
     """The example cells under user_cells/ (libpararnn_<name>.so beside the library)."""
     srcs = sorted(glob.glob(os.path.join(USER_CELLS, "*.hip")))
@@ -90,15 +122,17 @@ def build_examples(jobs: int | None = None, verbose: bool = False):
 
 
 def build_all(jobs: int | None = None, verbose: bool = False):
-    """The library and the example cells; the cells' objects compile alongside the library's (they
+    """The library, the native binding module and the example cells; the cells' objects compile alongside the library's (they
     only need the library at link time)."""
     os.makedirs(OBJ, exist_ok=True)
     cells = sorted(glob.glob(os.path.join(USER_CELLS, "*.hip")))
     with cf.ThreadPoolExecutor(max_workers=jobs or min(8, os.cpu_count() or 1)) as ex:
         # the slowest translation units first
         cell_objs = [ex.submit(_compile, s, []) for s in reversed(cells)]
+        host = ex.submit(_host_step, os.path.join(OBJ, "host_binding.cpp.o"), False)
         lib = ex.submit(build, jobs, (), verbose)
         lib.result()
+        build_host(host.result(), verbose)
         objs = [f.result() for f in cell_objs][::-1]
     return [build_cell(s, verbose=verbose, obj=o) for s, o in zip(cells, objs)]
 
