@@ -187,51 +187,66 @@ inline Layout make_layout(const CellInfo &ci, int dtype, int B, int L, int H, bo
     return lo;
 }
 
-// Shape of the one-workgroup kernels for a problem (short_kernels.h): c steps per thread, 64 >> lps_log2 segments per
-// wave, w waves; n_items workgroups.  fixed: a solve of a fixed number of iterations.  False where the kernels with
-// carry records do better.
-struct ShortShape { int c, lps_log2, w, n_cg, n_items; };
+// Shape of the kernels of short_kernels.h for a problem: c steps per thread, 64 >> lps_log2 segments per wave, w waves;
+// n_items workgroups that walk their sequence in n_tiles tiles.  fixed: a solve of a fixed number of iterations.
+// False where the kernels with carry records do better.  Figures: us on MI355X, kernels with records / these.
+struct ShortShape { int c, lps_log2, w, n_cg, n_items, n_tiles; };
 inline bool short_shape(const CellInfo &ci, int dtype, int B, int L, int H, bool backward, bool fixed, ShortShape *out)
 {
-    const double n = (double)B * L * H, esz = dtype == PARARNN_BF16 ? 2.0 : 4.0;
-    // Steps per thread.  Below half a wave per SIMD at eight steps the chunk's own latency counts (4 x 250 x 100 GRU
-    // 10.9 -> 9.8 us with four).  Sixteen spread the wave and workgroup levels of an iteration over more cell
-    // evaluations and are what makes longer sequences fit; the adjoint scan passes those levels once.
-    int c = ci.S > 2 || n < 512.0 * 512.0 ? 4 : backward || L <= 512 ? 8 : 16;
-    if (c == 4 && ci.S <= 2 && L > 1024) c = backward ? 8 : 16;
-    // Waves per workgroup: four iterate fastest (two barriers in every iteration; workgroups of eight leave fewer of
-    // them on a compute unit); the single pass backward takes all there may be, for longer pieces of rows.
-    const int wmax = ci.S * c <= 8 ? 16 : 8, want = backward ? wmax : 4;
-    int ll = 1;
-    while (ll < 16 && c * ll * want < L) ll *= 2;
-    const int w = (L + c * ll - 1) / (c * ll);
-    if (w > wmax) return false;
-    // Long sequences mean 16-byte pieces of rows (four channels per group), for which the memory pipeline needs as
-    // many cycles as for whole lines: fine where latency bounds the other kernels too, not on large tensors.
-    if (backward) {
-        // GRU fp32 (us, record kernels / these): 64 steps x 32 x 4096 66 / 52; 250 x 16 x 1000 36 / 26 but x 32 x 4096
-        // 203 / 214; 500 x 16 x 1024 59 / 56; 1000 x 8 x 1536 87 / 122; 2000 x 2 x 1000 36 / 47; two-state cells
-        // 777 x 5 x 333 25 / 30
-        if (ci.S >= 2 && L > 512) return false;
-        const double bytes = n * esz * (2 * ci.G + 2 * ci.S);
-        const double most = L <= 128 ? 1e30 : L <= 256 ? 512e6 : L <= 512 ? 192e6 : L <= 1024 ? 96e6 : 32e6;
-        if (bytes > most) return false;
-    } else if (L > 1024) {
-        // 2000 x 8 x 1000: GRU fp32 156 / 137, bf16 160 / 133, two-state cells 264 / 379 (5 iterations) and 450 / 358
-        // (LSTM: 6; what wins there is that groups of channels stop on their own, which a fixed count does not:
-        // 1531 x 3 x 1001, three iterations, 81 / 118); 2048 x 8 x 2048: GRU fp32 264 / 279, bf16 287 / 242
-        if (ci.S >= 2 && fixed) return false;
-        const double most = ci.S >= 2 ? (ci.kind == PARARNN_LSTM_DIAG ? 64e6 : 16e6) : 68e6;
-        if (n * esz > most) return false;
+    const double n = (double)B * L * H, channels = (double)B * H, esz = dtype == PARARNN_BF16 ? 2.0 : 4.0;
+    const bool tiny = n < 512.0 * 512.0 && L <= 1024;
+    int c, lps, w;
+    if (backward || L <= 512 || ci.S > 2 || tiny || (ci.S == 1 && L <= 2048)) {
+        // ---- one tile.  Steps per thread: below half a wave per SIMD at eight of them the chunk's own latency counts (GRU
+        // 4 x 250 x 100: eight steps 10.9, four 9.8); sixteen spread the wave and workgroup levels of an iteration over
+        // more cell evaluations and are what makes longer sequences fit; the single pass backward has those levels once.
+        c = ci.S > 2 || tiny ? 4 : backward || L <= 512 ? 8 : 16;
+        // Four waves iterate fastest (two barriers in every iteration; workgroups of eight leave fewer of them on a
+        // compute unit); the single pass takes all there may be, for longer pieces of rows.
+        const int wmax = ci.S * c <= 8 ? 16 : 8, want = backward ? wmax : 4;
+        int ll = 1;
+        while (ll < 16 && c * ll * want < L) ll *= 2;
+        w = (L + c * ll - 1) / (c * ll);
+        if (w > wmax) return false;
+        lps = 6;
+        while ((64 >> lps) < ll) --lps;
+        // Long sequences mean short pieces of rows (four channels per group in the end), for which the memory pipeline
+        // needs as many cycles as for whole lines: fine where latency bounds the other kernels too, not on large tensors.
+        if (backward) {
+            // GRU fp32: 64 steps x 32 x 4096 66 / 52; 250 x 16 x 1000 36 / 26 but x 32 x 4096 203 / 214;
+            // 500 x 16 x 1024 59 / 56; 1000 x 8 x 1536 87 / 122; 2000 x 2 x 1000 36 / 47; two-state cells 777 x 5 x 333 25 / 30
+            if (ci.S >= 2 && L > 512) return false;
+            const double bytes = n * esz * (2 * ci.G + 2 * ci.S);
+            const double most = L <= 128 ? 1e30 : L <= 256 ? 512e6 : L <= 512 ? 192e6 : L <= 1024 ? 96e6 : 32e6;
+            if (bytes > most) return false;
+        } else if (L > 1024 && ci.S == 1) {
+            // GRU 2000 x 8 x 1000 fp32 156 / 137, bf16 160 / 133; 2048 x 8 x 2048 fp32 264 / 279, bf16 287 / 242.  A fixed
+            // count has no channels that stop on their own, which is most of the gain.
+            if (fixed || n * esz > 68e6) return false;
+        }
+    } else {
+        // ---- tiles.  What these kernels gain is that channels stop on their own and that nothing is cleared, published
+        // or launched for iterations that are not needed; what they lose is that a sequence is one chain.  Two-state
+        // cells (LSTM: six or seven iterations): 7261 x 27 x 818 4131 / 2301, 2048 x 8 x 2048 718 / 557, 43636 x 4 x 240
+        // 1261 / 930, 1531 x 3 x 1001 with three fixed iterations 83 / 73, but 39461 x 7 x 24 338 / 730.  Scalar cells, which
+        // take five nearly everywhere: bf16 4096 x 16 x 1024 573 / 480, 2720 x 2 x 950 88 / 73; fp32 4096 x 16 x 1024
+        // 487 / 506, 4063 x 20 x 565 380 / 406; 65536 x 4 x 4096 bf16 7602 / 8453 (in long sequences neighbouring groups
+        // drift apart and no longer share cache lines).
+        if (L > 2048 && channels < (ci.S == 1 ? 1500.0 : 900.0)) return false;
+        if (ci.S == 1 && (fixed || dtype != PARARNN_BF16 || L > 8192)) return false;
+        if (channels < 1500.0) { c = 16; lps = 2; w = 8; }               // few chains: all the waves there can be
+        else if (channels < (ci.S == 1 ? 3500.0 : 6000.0)) { c = ci.S == 1 || fixed ? 8 : 16; lps = 2; w = 4; }
+        else { c = 8; lps = 3; w = 4; }
+        const int most = (L + c * (64 >> lps) - 1) / (c * (64 >> lps));
+        if (w > most) w = most;
     }
-    const double row = (double)ci.G * H * esz;
-    if (row * ((double)c * ll * w + 1.0) >= 2147483647.0) return false;       // 32-bit offsets within a sequence
-    int lps = 6;
-    while ((64 >> lps) < ll) --lps;
+    const int T = c * (64 >> lps) * w;
+    if ((double)ci.G * H * esz * (T + 1.0) >= 2147483647.0) return false;     // 32-bit offsets within a tile
     out->c = c; out->lps_log2 = lps; out->w = w;
     out->n_cg = (H + (1 << lps) - 1) >> lps;
     if ((double)B * out->n_cg > 131072.0) return false;      // verdicts that workgroup 0 collects
     out->n_items = B * out->n_cg;
+    out->n_tiles = (L + T - 1) / T;
     return true;
 }
 // workspace of such a solve: the control block (not used) and the workgroups' verdicts
@@ -427,7 +442,7 @@ int forward_short(int dtype, const ShortShape &sh, const float *params, const vo
     char *ws = static_cast<char *>(workspace);
     ShortArgs a;
     memset(&a, 0, sizeof(a));
-    a.B = B; a.L = L; a.H = H; a.n_cg = sh.n_cg; a.lps_log2 = sh.lps_log2; a.n_items = sh.n_items;
+    a.B = B; a.L = L; a.H = H; a.n_cg = sh.n_cg; a.lps_log2 = sh.lps_log2; a.n_items = sh.n_items; a.n_tiles = sh.n_tiles;
     a.params = params; a.u = u; a.h0 = h0; a.h = h; a.tol = tol; a.max_iter = max_iter; a.iters_out = iters;
     a.spin_limit = settings().spin_limit;
     a.slots = reinterpret_cast<rec_t *>(ws + round256(sizeof(Ctrl)));
@@ -450,10 +465,6 @@ int forward_solve(const CellInfo &ci, int dtype, const float *params, const void
 {
     const size_t esz = dtype == PARARNN_BF16 ? 2 : 4;
     const int status0 = tol < 0.0f ? PARARNN_OK : PARARNN_NOT_CONVERGED;
-    ShortShape sh;
-    if (opts.fused_enabled && opts.fused_head > 0 && max_iter > 0 && !delta_trace && settings().tile[0] <= 0 &&
-        short_shape(ci, dtype, B, L, H, false, tol < 0.0f, &sh) && workspace_bytes >= short_workspace_bytes(sh))
-        return forward_short<Cell>(dtype, sh, params, u, h0, B, L, H, tol, max_iter, h, iters, workspace, st);
     int al = align_elems(esz, {u, h, h0});
     const int alp = align_elems(4, {params});
     if (alp < al) al = alp;
@@ -470,6 +481,10 @@ int forward_solve(const CellInfo &ci, int dtype, const float *params, const void
         }
     }
     if (n_fused == 0 && workspace_bytes < lo.total) return PARARNN_WORKSPACE_TOO_SMALL;
+    ShortShape sh;
+    if (opts.fused_enabled && opts.fused_head > 0 && max_iter > 0 && !delta_trace && settings().tile[0] <= 0 &&
+        short_shape(ci, dtype, B, L, H, false, tol < 0.0f, &sh) && workspace_bytes >= short_workspace_bytes(sh))
+        return forward_short<Cell>(dtype, sh, params, u, h0, B, L, H, tol, max_iter, h, iters, workspace, st);
     char *ws = static_cast<char *>(workspace);
     FwdArgs a;
     memset(&a, 0, sizeof(a));

@@ -139,15 +139,21 @@ hipError_t Kernels<Cell, UT>::newton_short(int c, int w, const ShortArgs &a, hip
         return hipErrorInvalidValue;
     } else {
         const unsigned int grid = 8u * (unsigned int)((a.n_items + 7) / 8);
-        const size_t lds = w > 1 ? ((size_t)w * (Cell::S * Cell::S + Cell::S) << a.lps_log2) * sizeof(float) : 0;
-#define PARARNN_CASE(C)                                                                                           \
-    if constexpr (short_offered<Cell, C>(false)) {                                                                   \
-        if (c == C && w <= short_max_waves<Cell, C>()) {                                                          \
-            hipLaunchKernelGGL((newton_short_kernel<Cell, C, UT>), dim3(grid), dim3(kWave * w), lds, st, a);          \
-            return hipGetLastError();                                                                             \
-        }                                                                                                         \
+        // the last tile starts inside the sequence (its descriptor ends with it), the tiles cover it, and the carries
+        // of several tiles cross the workgroup's barriers
+        const long long steps = (long long)c * (kWave >> a.lps_log2) * w;
+        if (a.n_tiles < 1 || (a.n_tiles - 1) * steps >= a.L || a.n_tiles * steps < a.L || (a.n_tiles > 1 && w < 2))
+            return hipErrorInvalidValue;
+        const size_t lds = w > 1 ? ((size_t)(w * (Cell::S * Cell::S + Cell::S) + (a.n_tiles > 1 ? 2 * kShortCarries * Cell::S : 0))
+                                    << a.lps_log2) * sizeof(float) : 0;
+#define PARARNN_CASE(C, MANY)                                                                                         \
+    if constexpr (short_offered<Cell, C>(MANY)) {                                                                     \
+        if (c == C && (a.n_tiles > 1 || (C > 8 && Cell::S > 1)) == MANY && w <= (MANY ? 8 : short_max_waves<Cell, C>())) { \
+            hipLaunchKernelGGL((newton_short_kernel<Cell, C, UT, MANY>), dim3(grid), dim3(kWave * w), lds, st, a);    \
+            return hipGetLastError();                                                                                 \
+        }                                                                                                             \
     }
-        PARARNN_CASE(4) PARARNN_CASE(8) PARARNN_CASE(16)
+        PARARNN_CASE(4, false) PARARNN_CASE(8, false) PARARNN_CASE(16, false) PARARNN_CASE(8, true) PARARNN_CASE(16, true)
 #undef PARARNN_CASE
         return hipErrorInvalidValue;
     }
@@ -160,16 +166,17 @@ hipError_t Kernels<Cell, UT>::backward_short(int c, int w, const ShortArgs &a, h
         return hipErrorInvalidValue;
     } else {
         constexpr int SA = Cell::S * Cell::S + Cell::S, rows = SA > Cell::PR ? SA : Cell::PR;
+        if ((long long)c * (kWave >> a.lps_log2) * w < a.L) return hipErrorInvalidValue;
         const unsigned int grid = 8u * (unsigned int)((a.n_items + 7) / 8);
         const size_t lds = w > 1 ? ((size_t)w * rows << a.lps_log2) * sizeof(float) : 0;
 #define PARARNN_CASE(C)                                                                                           \
-    if constexpr (short_offered<Cell, C>(true)) {                                                                   \
+    if constexpr (short_offered<Cell, C>(false)) {                                                                  \
         if (c == C && w <= short_max_waves<Cell, C>()) {                                                          \
             hipLaunchKernelGGL((backward_short_kernel<Cell, C, UT>), dim3(grid), dim3(kWave * w), lds, st, a);          \
             return hipGetLastError();                                                                             \
         }                                                                                                         \
     }
-        PARARNN_CASE(4) PARARNN_CASE(8) PARARNN_CASE(16)
+        PARARNN_CASE(4) PARARNN_CASE(8)
 #undef PARARNN_CASE
         return hipErrorInvalidValue;
     }

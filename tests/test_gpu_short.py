@@ -10,7 +10,8 @@ from test_gpu_parity import problem, relerr, to_np      # noqa: E402
 from parity_util import well_posed_tol                   # noqa: E402
 
 SHAPES = [(1, 1, 1), (3, 4, 5), (2, 5, 64), (1, 64, 65), (2, 65, 3), (1, 127, 9), (2, 129, 33), (1, 512, 4), (1, 513, 6),
-          (2, 777, 17), (1, 1024, 5), (1, 1025, 3), (1, 2048, 2), (1, 2049, 2), (150, 9, 70), (70, 300, 260)]
+          (2, 777, 17), (1, 1024, 5), (1, 1025, 3), (1, 2048, 2), (1, 2049, 2), (150, 9, 70), (20, 300, 260),
+          (1, 2060, 1504), (6, 520, 1001)]       # the last two: several tiles of different shapes for some cells
 
 
 @pytest.mark.parametrize("cell", ["gru_diag", "lstm_diag", "paralstm_diag"])
