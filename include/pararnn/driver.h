@@ -325,8 +325,8 @@ inline size_t diag_workspace_bytes_fused(const CellInfo &ci, int dtype, int B, i
 // tol >= 0: the solve is a sequence of launches, each checked by the stopping test on the
 // device: a fused block of n_fused iterations from the initial guess, then blocks of 1, 2,
 // 4, ... (at most n_fused) iterations from the iterate; a block of one iteration that is a
-// launch of its own is the per-iteration kernel.  With `tail` the blocks after the second share
-// ONE launch of the fused kernel, which returns at once when the tolerance was met before;
+// launch of its own is the per-iteration kernel.  With `tail` the blocks after the second (scalar
+// cells: the first) share ONE launch of the fused kernel, which returns at once when the tolerance was met before;
 // without it every block is a launch of its own.  Launches after the one that met the
 // tolerance return at once.
 template <class Cell>
@@ -360,12 +360,15 @@ int forward_diag(const CellInfo &ci, int dtype, const Layout &lo, FwdArgs &a, hi
     f.bnd = a.bnd;
     f.n_slots = n_fused; f.spin_limit = settings().spin_limit;
     const bool tail = settings().fused_tail != 0;
+    // Scalar cells need a second block so rarely that it is not worth a launch of its own, which finds nothing to do
+    // (5 us each); two-state cells do need it, and one iteration is what the per-iteration kernel does fastest.
+    const int tail_from = ci.S == 1 ? 1 : 2;
+    bool whole_h = n_fused > 0;            // every launch writes the output itself
     int done = 0, cur = 0;
     for (int launches = 0; done < max_iter; ++launches) {
         const int K = next_block_size(done, launches, max_iter, n_fused);
-        if (to_tol && n_fused > 0 && launches == 2 && tail) {
-            // everything after the second block in one launch that goes through the plan on the device (the
-            // second block is one iteration, which the per-iteration kernel does faster than a fused block)
+        if (to_tol && n_fused > 0 && launches == tail_from && tail) {
+            // everything that is left in one launch that goes through the plan on the device
             f.n_iters = K; f.k0 = done; f.epoch0 = f.g.epoch_base + (unsigned int)done; f.bnd_cur = cur; f.tail = 1; f.launch_no = launches;
             e = bf ? Kernels<Cell, unsigned short>::newton_fused(lo.cfg, f, st) : Kernels<Cell, float>::newton_fused(lo.cfg, f, st);
             if (e != hipSuccess) return e == hipErrorInvalidValue ? PARARNN_UNSUPPORTED : PARARNN_HIP_ERROR;
@@ -376,6 +379,7 @@ int forward_diag(const CellInfo &ci, int dtype, const Layout &lo, FwdArgs &a, hi
             e = bf ? Kernels<Cell, unsigned short>::newton_fused(lo.cfg, f, st) : Kernels<Cell, float>::newton_fused(lo.cfg, f, st);
         } else {
             a.k = done + 1; a.bnd_cur = cur;
+            whole_h = false;
             e = bf ? Kernels<Cell, unsigned short>::newton_iter(lo.cfg, a, done == 0, st)
                    : Kernels<Cell, float>::newton_iter(lo.cfg, a, done == 0, st);
         }
@@ -383,7 +387,7 @@ int forward_diag(const CellInfo &ci, int dtype, const Layout &lo, FwdArgs &a, hi
         done += K;
         cur ^= 1;
     }
-    if (bf && !(n_fused > 0 && !to_tol)) {
+    if (bf && !whole_h) {
         // rounds the fp32 iterate into the output; skipped on the device when a fused block
         // already wrote the final iterate
         e = launch_store_bf16(a.hit, h, (size_t)lo.g.B * lo.g.L * ci.S * lo.g.H, a.ctrl, st);
