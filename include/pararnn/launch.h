@@ -43,6 +43,14 @@ hipError_t launch_store_bf16(const float *src, void *dst, size_t n, const Ctrl *
 // n 32-bit words of zeros, written by a kernel (no memset node when a caller captures a graph)
 hipError_t launch_zero_words(unsigned int *dst, int n, hipStream_t st);
 hipError_t launch_param_reduce(const float *part, float *out, int n_terms, int n_out, hipStream_t st);
+// two such sums with the same number of terms in one launch; everything 16-byte aligned, counts in fours (the second may be 0)
+struct ReducePair {
+    const float *part[2];
+    float *out[2];
+    int n4[2];
+    int n_terms;
+};
+hipError_t launch_param_reduce_pair(const ReducePair &a, hipStream_t st);
 int device_cu_count();
 
 // Workspaces that are reused across calls (pararnn_set_workspace_reuse).  Returns the number this call adds

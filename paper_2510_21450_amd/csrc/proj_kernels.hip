@@ -204,6 +204,23 @@ struct GemmArgs {
     int draw;                      // tile numbers taken per draw (copy-to-LDS kernel)
 };
 
+// first tile number of an XCD: an eighth of the grid each
+__device__ __forceinline__ int xcd_first(const GemmArgs &a, int xcd)
+{
+    return (int)((long long)a.tiles_m * (a.tiles_n * a.n_batch) * xcd / 8);
+}
+
+// row block and (batch, column block) of tile number `no` in patch order
+__device__ __forceinline__ void patch_tile(int no, int tiles_m, int inner_n, int &mt, int &inner)
+{
+    const int pm = no / (8 * inner_n), rem = no - pm * 8 * inner_n;
+    const int hm = min(8, tiles_m - 8 * pm);                     // rows of this patch row
+    const int pn = rem / (8 * hm), rem2 = rem - pn * 8 * hm;
+    const int hn = min(8, inner_n - 8 * pn);                     // columns of this patch
+    mt = 8 * pm + rem2 / hn;
+    inner = 8 * pn + rem2 % hn;
+}
+
 // Persistent workgroups, each walking a list of output tiles; the (tile, k-step) pairs
 // of that list form one flat stream of steps, so that the loads of a tile's first steps
 // are in flight while the previous tile is still being multiplied.  Step t is multiplied
@@ -222,24 +239,14 @@ __global__ __launch_bounds__(256, 2) void proj_gemm_nt_kernel(const GemmArgs a)
     __shared__ int s_ring[8];
     const int xcd = blockIdx.x & 7;
     const int inner_n = a.tiles_n * a.n_batch;
-    // This XCD owns the row blocks [xcd * mx, (xcd + 1) * mx).  Its (row block, inner) grid is
-    // cut into patches of 8 x 8 tiles (smaller at the edges), numbered one after the other, and
-    // its workgroups draw numbers from a counter: whatever their relative speed they are inside
-    // one or two neighbouring patches at any time, whose 8 + 8 operand panels stay in that
-    // XCD's L2.
-    const int mx = (a.tiles_m + 7) / 8;
-    int my_rows = a.tiles_m - xcd * mx;            // row blocks of this XCD
-    if (my_rows > mx) my_rows = mx;
-    if (my_rows <= 0) return;
-    const int n_local = my_rows * inner_n;
-    auto decode = [&](int local, int &mt, int &inner) {
-        const int pm = local / (8 * inner_n), rem = local - pm * 8 * inner_n;
-        const int hm = min(8, my_rows - 8 * pm);                 // rows of this patch row
-        const int pn = rem / (8 * hm), rem2 = rem - pn * 8 * hm;
-        const int hn = min(8, inner_n - 8 * pn);                 // columns of this patch
-        mt = xcd * mx + 8 * pm + rem2 / hn;
-        inner = 8 * pn + rem2 % hn;
-    };
+    // The (row block, inner) grid is cut into patches of 8 x 8 tiles (smaller at the edges),
+    // numbered one after the other; every XCD has an eighth of these numbers (an eighth of the
+    // row blocks where there are many; whole row blocks per XCD left XCDs idle where there are
+    // few), and its workgroups draw them from a counter: whatever their relative speed they are
+    // inside one or two neighbouring patches at any time, whose 8 + 8 operand panels stay in
+    // that XCD's L2.
+    const int base = xcd_first(a, xcd), n_local = xcd_first(a, xcd + 1) - base;
+    auto decode = [&](int local, int &mt, int &inner) { patch_tile(base + local, a.tiles_m, inner_n, mt, inner); };
     const int nk = a.K / BK;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, wm = w >> 1, wn = w & 1;
     const int half = lane >> 5, l32 = lane & 31;
@@ -496,12 +503,8 @@ __global__ __launch_bounds__(512) void proj_gemm_nt_dma_kernel(const GemmArgs a)
     __shared__ int s_ring[8];
     const int xcd = blockIdx.x & 7;
     const int inner_n = a.tiles_n * a.n_batch;
-    // the XCD's (row block, inner) grid in patches of 8 x 8 tiles, as in proj_gemm_nt_kernel
-    const int mx = (a.tiles_m + 7) / 8;
-    int my_rows = a.tiles_m - xcd * mx;
-    if (my_rows > mx) my_rows = mx;
-    if (my_rows <= 0) return;
-    const int n_local = my_rows * inner_n;
+    // an eighth of the (row block, inner) grid's patches of 8 x 8 tiles, as in proj_gemm_nt_kernel
+    const int base = xcd_first(a, xcd), n_local = xcd_first(a, xcd + 1) - base;
     const int nk = a.K / BK;
     const int tid = threadIdx.x, lane = tid & 63, w = (int)uniform((unsigned int)tid >> 6), wm = w >> 2, wn = w & 3;
     const int half = lane >> 5, l32 = lane & 31;
@@ -516,11 +519,8 @@ __global__ __launch_bounds__(512) void proj_gemm_nt_dma_kernel(const GemmArgs a)
         int m0, n0;
     };
     auto tile_of = [&](int local) {
-        const int pm = local / (8 * inner_n), rem = local - pm * 8 * inner_n;
-        const int hm = min(8, my_rows - 8 * pm);
-        const int pn = rem / (8 * hm), rem2 = rem - pn * 8 * hm;
-        const int hn = min(8, inner_n - 8 * pn);
-        const int mt = xcd * mx + 8 * pm + rem2 / hn, inner = 8 * pn + rem2 % hn;
+        int mt, inner;
+        patch_tile(base + local, a.tiles_m, inner_n, mt, inner);
         const int nt = inner % a.tiles_n, z = inner / a.tiles_n;
         const int z0 = z % a.nz0, z1 = z / a.nz0;
         Tile t;
@@ -760,12 +760,8 @@ __global__ __launch_bounds__(512) void proj_gemm_nt_dma_f32_kernel(const GemmArg
     __shared__ int s_ring[8];
     const int xcd = blockIdx.x & 7;
     const int inner_n = a.tiles_n * a.n_batch;
-    // the XCD's (row block, inner) grid in patches of 8 x 8 tiles, as in proj_gemm_nt_kernel
-    const int mx = (a.tiles_m + 7) / 8;
-    int my_rows = a.tiles_m - xcd * mx;
-    if (my_rows > mx) my_rows = mx;
-    if (my_rows <= 0) return;
-    const int n_local = my_rows * inner_n;
+    // an eighth of the (row block, inner) grid's patches of 8 x 8 tiles, as in proj_gemm_nt_kernel
+    const int base = xcd_first(a, xcd), n_local = xcd_first(a, xcd + 1) - base;
     const int nk = a.K / BK;
     const int tid = threadIdx.x, lane = tid & 63, w = (int)uniform((unsigned int)tid >> 6), wm = w & 3, wn = w >> 2;
     const int half = lane >> 5, l32 = lane & 31;
@@ -781,11 +777,8 @@ __global__ __launch_bounds__(512) void proj_gemm_nt_dma_f32_kernel(const GemmArg
         int m0, n0;
     };
     auto tile_of = [&](int local) {
-        const int pm = local / (8 * inner_n), rem = local - pm * 8 * inner_n;
-        const int hm = min(8, my_rows - 8 * pm);
-        const int pn = rem / (8 * hm), rem2 = rem - pn * 8 * hm;
-        const int hn = min(8, inner_n - 8 * pn);
-        const int mt = xcd * mx + 8 * pm + rem2 / hn, inner = 8 * pn + rem2 % hn;
+        int mt, inner;
+        patch_tile(base + local, a.tiles_m, inner_n, mt, inner);
         const int nt = inner % a.tiles_n, z = inner / a.tiles_n;
         const int z0 = z % a.nz0, z1 = z / a.nz0;
         Tile t;
@@ -1394,26 +1387,42 @@ __global__ __launch_bounds__(512) void proj_dw_dma_kernel(const DwArgs a)
 }
 
 // ------------------------------------------------------------- weight copies
-// Wb = bf16(Wx), same layout [G][H][dh]
-__global__ __launch_bounds__(256) void proj_wb_kernel(const float *Wx, unsigned short *Wb, size_t n, int *tickets)
+// Wb = bf16(Wx), same layout [G][H][dh]; n4 fours
+__global__ __launch_bounds__(256) void proj_wb_kernel(const float *Wx, unsigned short *Wb, size_t n4, int *tickets)
 {
     if (blockIdx.x == 0 && threadIdx.x < 8) tickets[threadIdx.x] = 0;      // for the product that follows
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-        Wb[i] = f32_to_bf16(Wx[i]);
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += (size_t)gridDim.x * blockDim.x)
+        store4(Wb + 4 * i, reinterpret_cast<const f4v *>(Wx)[i]);
 }
 
-// Wt[head][j][g dh + i] = bf16(Wx[g][head dh + i][j]): the B operand of the dx product
+// Wt[head][j][g dh + i] = bf16(Wx[g][head dh + i][j]): the B operand of the dx product.  One workgroup per 64 x 64 block
+// of a head's matrix (dh is a multiple of 64), transposed through LDS so that memory is read and written in whole lines:
+// 21 (43) -> 6 (8) us for 4 (8) million weights; read element by element along a column, a line was fetched several times.
+constexpr int WT_PITCH = 36;             // dwords from one row of the LDS block to the next: 32 pairs and a pad of 16 bytes
 __global__ __launch_bounds__(256) void proj_wt_kernel(const float *Wx, unsigned short *Wt, int G, int H, int dh,
                                                       int *tickets)
 {
+    __shared__ __attribute__((aligned(16))) unsigned int s_t[64 * WT_PITCH];      // [j][pair of i], bf16
     if (blockIdx.x == 0 && threadIdx.x < 8) tickets[threadIdx.x] = 0;      // for the product that follows
-    const size_t n = (size_t)G * H * dh;
-    for (size_t o = (size_t)blockIdx.x * blockDim.x + threadIdx.x; o < n; o += (size_t)gridDim.x * blockDim.x) {
-        const int i = (int)(o % dh);
-        const int g = (int)((o / dh) % G);
-        const int j = (int)((o / ((size_t)dh * G)) % dh);
-        const int head = (int)(o / ((size_t)dh * G * dh));
-        Wt[o] = f32_to_bf16(Wx[((size_t)g * H + (size_t)head * dh + i) * dh + j]);
+    const int nb = dh / 64;
+    const int jb = blockIdx.x % nb, ib = (blockIdx.x / nb) % nb, gh = blockIdx.x / (nb * nb);
+    const int g = gh % G, head = gh / G;
+    const float *src = Wx + ((size_t)g * H + (size_t)head * dh + 64 * ib) * dh + 64 * jb;
+    const int c = threadIdx.x & 15, r = threadIdx.x >> 4;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int p = r + 16 * q;                                           // rows 2 p and 2 p + 1, columns 4 c .. 4 c + 3
+        const f4v v0 = *reinterpret_cast<const f4v *>(src + (size_t)(2 * p) * dh + 4 * c);
+        const f4v v1 = *reinterpret_cast<const f4v *>(src + (size_t)(2 * p + 1) * dh + 4 * c);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) s_t[(4 * c + k) * WT_PITCH + p] = pack2(v0[k], v1[k]);
+    }
+    __syncthreads();
+    unsigned short *dst = Wt + ((size_t)head * dh + 64 * jb) * ((size_t)G * dh) + (size_t)g * dh + 64 * ib;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int j = (threadIdx.x >> 3) + 32 * q, ch = threadIdx.x & 7;
+        *reinterpret_cast<u4v *>(dst + (size_t)j * ((size_t)G * dh) + 8 * ch) = *reinterpret_cast<const u4v *>(&s_t[j * WT_PITCH + 4 * ch]);
     }
 }
 
@@ -1429,6 +1438,9 @@ bool shapes_ok(int dtype, int B, int L, int H, int G, int n_heads)
     return rows < 2.0e9 && rows * G * H < 3.0e10;
 }
 
+// up to this many rows are one range: a second one would save four steps (5 us) and cost a launch that adds the two
+constexpr int dw_one_range = 8 * BK;
+
 // row ranges of the dWx reduction: enough workgroups to fill the device, whole 64-row steps
 void dw_split(int M, int base_tiles, int *S, int *rows_per_split)
 {
@@ -1438,6 +1450,7 @@ void dw_split(int M, int base_tiles, int *S, int *rows_per_split)
     int rps = (M + want - 1) / want;
     rps = (rps + BK - 1) / BK * BK;
     if (rps < 4 * BK) rps = 4 * BK;
+    if (M <= dw_one_range) rps = (M + BK - 1) / BK * BK;
     *rows_per_split = rps;
     *S = (M + rps - 1) / rps;
 }
@@ -1470,11 +1483,13 @@ void dw_dma_split(int M, int G, int H, int dh, int n_heads, int *S, int *rows_pe
 }
 
 // the copy-to-LDS kernel's 256-wide tiles against the 128-wide ones: taken where they cover dh with at most
-// half as much again of idle tile area
-bool dw_dma_shape_ok(int H, int G, int dh)
+// half as much again of idle tile area, and where the 128-wide ones are not all on the device at once in a single range
+// (256 rows: 16 -> 11 us)
+bool dw_dma_shape_ok(int M, int H, int G, int dh)
 {
     const double t2 = (double)((dh + dwd::BT - 1) / dwd::BT * dwd::BT), t1 = (double)((dh + BM - 1) / BM * BM);
-    return dh % 8 == 0 && H % 8 == 0 && (long long)G * H < (1 << 22) && t2 * t2 <= 1.5 * t1 * t1;
+    return dh % 8 == 0 && H % 8 == 0 && (long long)G * H < (1 << 22) && t2 * t2 <= 1.5 * t1 * t1 &&
+           !(M <= dw_one_range && (double)G * H / dh * (t1 / BM) * (t1 / BM) <= 2.0 * device_cu_count());
 }
 
 struct ProjLayout {
@@ -1498,7 +1513,7 @@ ProjLayout proj_layout(int B, int L, int H, int G, int n_heads, int backward)
     if (backward) {
         dw_split(B * L, lo.tiles * lo.tiles * G * n_heads, &lo.S, &lo.rows_per_split);
         // room for either kernel's partial sums, so that the size does not depend on proj_set_dma
-        if (dw_dma_shape_ok(H, G, dh)) {
+        if (dw_dma_shape_ok(B * L, H, G, dh)) {
             lo.tiles2 = (dh + dwd::BT - 1) / dwd::BT;
             dw_dma_split(B * L, G, H, dh, n_heads, &lo.S2, &lo.rows_per_split2);
         }
@@ -1523,18 +1538,29 @@ template <typename AT, typename CT> hipError_t launch_nt(GemmArgs &g, hipStream_
     return hipGetLastError();
 }
 
+// Few output tiles: with the 128-wide ones all of them run at once, two to a compute unit at most, and a step of a tile
+// takes half the time of a 256-wide one, which leaves three of four compute units idle (512 rows, dh = 512, four gates:
+// dx 50 -> 38 us in bf16, 69 -> 44 in fp32 storage).  Two to a unit cost bf16 tiles of a few steps what the size gains
+// (K = 768: 28 -> 30 us, K = 1024 and more: faster).
+bool nt_few_tiles(const GemmArgs &g, bool bf)
+{
+    const long long tiles = (long long)((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN) * g.n_batch;
+    const int cus = device_cu_count();
+    return tiles <= cus || (tiles <= 2 * cus && (!bf || g.K >= 1024));
+}
+
 // the copy-to-LDS kernel: bf16 storage, at least two 64-k steps per tile, k-segments in whole steps, row
 // offsets of a 256-row tile within 32 bits
 bool nt_dma_ok(const GemmArgs &g)
 {
-    return g.K >= 2 * dma::BK && g.K % dma::BK == 0 && g.kseg % dma::BK == 0 && g.N % 64 == 0 &&
+    return !nt_few_tiles(g, true) && g.K >= 2 * dma::BK && g.K % dma::BK == 0 && g.kseg % dma::BK == 0 && g.N % 64 == 0 &&
            g.lda < (1 << 22) && g.ldb < (1 << 22) && g.ldc < (1 << 22) && g.lda % 8 == 0 && g.ldb % 8 == 0 && g.ldc % 8 == 0;
 }
 
 // the same for fp32 A and C: 32-k steps
 bool nt_dma_f32_ok(const GemmArgs &g)
 {
-    return g.K >= 3 * dmaf::BK && g.K % dmaf::BK == 0 && g.kseg % dmaf::BK == 0 && g.N % 64 == 0 &&
+    return !nt_few_tiles(g, false) && g.K >= 3 * dmaf::BK && g.K % dmaf::BK == 0 && g.kseg % dmaf::BK == 0 && g.N % 64 == 0 &&
            g.lda < (1 << 22) && g.ldb < (1 << 22) && g.ldc < (1 << 22) && g.lda % 4 == 0 && g.ldb % 8 == 0 && g.ldc % 4 == 0;
 }
 
@@ -1602,7 +1628,7 @@ int proj_forward(int dtype, const void *x, const float *Wx, const float *bias, i
     unsigned short *Wb = reinterpret_cast<unsigned short *>(static_cast<char *>(workspace) + lo.off_w);
     const size_t nw = (size_t)G * H * dh;
     int *tickets = reinterpret_cast<int *>(static_cast<char *>(workspace) + lo.off_tickets);
-    hipLaunchKernelGGL(proj_wb_kernel, dim3(elementwise_blocks(nw)), dim3(256), 0, st, Wx, Wb, nw, tickets);
+    hipLaunchKernelGGL(proj_wb_kernel, dim3(elementwise_blocks(nw / 4)), dim3(256), 0, st, Wx, Wb, nw / 4, tickets);
     GemmArgs g;
     memset(&g, 0, sizeof(g));
     g.A = x; g.Bw = Wb; g.C = u; g.bias = bias; g.tickets = tickets;
@@ -1637,7 +1663,7 @@ int proj_backward(int dtype, const void *x, const float *Wx, const void *du, int
     if (dx) {
         unsigned short *Wt = reinterpret_cast<unsigned short *>(ws + lo.off_w);
         int *tickets = reinterpret_cast<int *>(ws + lo.off_tickets);
-        hipLaunchKernelGGL(proj_wt_kernel, dim3(elementwise_blocks(nw)), dim3(256), 0, st, Wx, Wt, G, H, dh, tickets);
+        hipLaunchKernelGGL(proj_wt_kernel, dim3((unsigned)(nw / 4096)), dim3(256), 0, st, Wx, Wt, G, H, dh, tickets);
         GemmArgs g;
         memset(&g, 0, sizeof(g));
         g.A = du; g.Bw = Wt; g.C = dx; g.bias = nullptr; g.tickets = tickets;
@@ -1673,8 +1699,13 @@ int proj_backward(int dtype, const void *x, const float *Wx, const void *du, int
         else hipLaunchKernelGGL(proj_dw_kernel<float>, dim3(blocks), dim3(256), 0, st, a);
         if (hipGetLastError() != hipSuccess) return PARARNN_HIP_ERROR;
         if (a.S > 1) {
-            if (launch_param_reduce(a.part, dWx, a.S, (int)nw, st) != hipSuccess) return PARARNN_HIP_ERROR;
-            if (dbias && launch_param_reduce(a.dbpart, dbias, a.S, G * H, st) != hipSuccess) return PARARNN_HIP_ERROR;
+            if (((uintptr_t)dWx | (uintptr_t)dbias) % 16 == 0) {
+                const ReducePair r = {{a.part, a.dbpart}, {dWx, dbias}, {(int)(nw / 4), dbias ? G * H / 4 : 0}, a.S};
+                if (launch_param_reduce_pair(r, st) != hipSuccess) return PARARNN_HIP_ERROR;
+            } else {
+                if (launch_param_reduce(a.part, dWx, a.S, (int)nw, st) != hipSuccess) return PARARNN_HIP_ERROR;
+                if (dbias && launch_param_reduce(a.dbpart, dbias, a.S, G * H, st) != hipSuccess) return PARARNN_HIP_ERROR;
+            }
         }
     }
     return PARARNN_OK;

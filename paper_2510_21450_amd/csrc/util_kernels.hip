@@ -84,20 +84,42 @@ __global__ __launch_bounds__(1024) void param_reduce_kernel(const float *part, f
     }
 }
 
-// The same sum where there are many outputs and few terms (the row ranges of a weight gradient): a thread owns four
-// outputs and runs through the terms.  With the kernel above 13 of 16 slices had nothing to add and there was a workgroup
-// of 1024 threads for every 64 outputs: 61 -> 14 us for 2.4e6 outputs of three terms.
-__global__ __launch_bounds__(256) void param_reduce_few_kernel(const float *part, float *out, int n_terms, int n_out4)
+// The same sums for the row ranges of a weight gradient (many outputs, at most 64 terms) and of the bias gradient with it,
+// in one launch: a thread owns four neighbouring outputs and every SL-th term of them, four terms in flight; the slices
+// are added through LDS in a fixed order.  With the kernel above 13 of 16 slices had nothing to add where there are three
+// terms, and there was a workgroup of 1024 threads for every 64 outputs: 61 -> 14 us for 2.4e6 outputs of three terms,
+// 29 -> 12 us for 0.8e6 outputs of 21; and the bias sums took a launch of their own (5 us).
+template <int SL>
+__global__ __launch_bounds__(256) void param_reduce_pair_kernel(const ReducePair a)
 {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= n_out4) return;
-    const float4 *p = reinterpret_cast<const float4 *>(part) + i;
-    float4 s = p[0];
-    for (int t = 1; t < n_terms; ++t) {
-        const float4 x = p[(size_t)t * n_out4];
-        s.x += x.x; s.y += x.y; s.z += x.z; s.w += x.w;
+    constexpr int N = 256 / SL;
+    __shared__ float4 s_sum[SL > 1 ? SL : 1][SL > 1 ? N : 1];
+    const int o = threadIdx.x % N, slice = threadIdx.x / N;
+    int i = blockIdx.x * N + o;
+    const bool second = i >= a.n4[0];
+    if (second) i -= a.n4[0];
+    const int n4 = a.n4[second];
+    const bool own = i < n4;
+    const float4 *p = reinterpret_cast<const float4 *>(a.part[second]) + i;
+    float4 s = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    auto add = [&](const float4 &x) { s.x += x.x; s.y += x.y; s.z += x.z; s.w += x.w; };
+    if (own) {
+        int t = slice;
+        for (; t + 3 * SL < a.n_terms; t += 4 * SL) {
+            const float4 x0 = p[(size_t)t * n4], x1 = p[(size_t)(t + SL) * n4], x2 = p[(size_t)(t + 2 * SL) * n4],
+                         x3 = p[(size_t)(t + 3 * SL) * n4];
+            add(x0); add(x1); add(x2); add(x3);
+        }
+        for (; t < a.n_terms; t += SL) add(p[(size_t)t * n4]);
     }
-    reinterpret_cast<float4 *>(out)[i] = s;
+    if constexpr (SL > 1) {
+        s_sum[slice][o] = s;
+        __syncthreads();
+        if (slice > 0) return;
+#pragma unroll
+        for (int k = 1; k < SL; ++k) add(s_sum[k][o]);
+    }
+    if (own) reinterpret_cast<float4 *>(a.out[second])[i] = s;
 }
 
 }  // namespace pararnn
@@ -150,13 +172,20 @@ hipError_t launch_store_bf16(const float *src, void *dst, size_t n, const Ctrl *
 
 hipError_t launch_param_reduce(const float *part, float *out, int n_terms, int n_out, hipStream_t st)
 {
-    // few terms per output and enough outputs for a wave per SIMD
-    if (n_terms <= 16 && n_out >= (1 << 18) && n_out % 4 == 0 &&
-        (reinterpret_cast<uintptr_t>(part) | reinterpret_cast<uintptr_t>(out)) % 16 == 0) {
-        hipLaunchKernelGGL(param_reduce_few_kernel, dim3((n_out / 4 + 255) / 256), dim3(256), 0, st, part, out, n_terms, n_out / 4);
-        return hipGetLastError();
-    }
     hipLaunchKernelGGL(param_reduce_kernel, dim3((n_out + 63) / 64), dim3(1024), 0, st, part, out, n_terms, n_out);
+    return hipGetLastError();
+}
+
+hipError_t launch_param_reduce_pair(const ReducePair &a, hipStream_t st)
+{
+    // slices until there is a wave for every SIMD, as far as there are terms
+    const int n4 = a.n4[0] + a.n4[1];
+    if (n4 >= (1 << 16) || a.n_terms < 8)
+        hipLaunchKernelGGL((param_reduce_pair_kernel<1>), dim3((n4 + 255) / 256), dim3(256), 0, st, a);
+    else if (n4 >= (1 << 14) || a.n_terms < 32)
+        hipLaunchKernelGGL((param_reduce_pair_kernel<4>), dim3((n4 + 63) / 64), dim3(256), 0, st, a);
+    else
+        hipLaunchKernelGGL((param_reduce_pair_kernel<16>), dim3((n4 + 15) / 16), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 

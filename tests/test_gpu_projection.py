@@ -184,6 +184,35 @@ def test_projection_weight_gradients_over_long_row_ranges(oracle_mod, shape):
     assert float((dW - dW2).abs().max()) <= 1e-5 * float(dW2.abs().max())
 
 
+# Either side of the choices between 128- and 256-wide tiles (dx in bf16 and fp32; the forward products have three or four
+# times as many tiles), no number of tiles a multiple of eight, ragged rows and columns; one row range (512) and two
+# (513) of the weight gradient, and as many ranges as there can be of few outputs.
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("shape", [(1, 512, 256, 3, 1), (3, 171, 256, 3, 1), (3, 640, 960, 4, 3), (1, 3969, 1024, 3, 8), (2, 4100, 1024, 4, 8),
+                                   (1, 20001, 128, 3, 2)])
+def test_projection_tile_choices(shape, dtype):
+    import paper_2510_21450_amd as P
+    print(f"projection tile choices {shape} {dtype}", flush=True)
+    B, L, H, G, heads = shape
+    dh = H // heads
+    x, Wx, bias, du = problem(shape, dtype, seed=5700 + L + H)
+    u = P.input_projection(x, Wx, bias, n_heads=heads)
+    dx, dW, db = P.input_projection_backward(x, Wx, du, n_heads=heads)
+    torch.cuda.synchronize()
+    tol = 2e-5 if dtype == torch.float32 else 1e-2
+    xr, dur, Wr = (torch.from_numpy(rounded(t)) for t in (x, du, Wx))
+    xr, dur, Wr = xr.reshape(B * L, heads, dh), dur.reshape(B * L, G, heads, dh), Wr.reshape(G, heads, dh, dh)
+    for k in range(heads):
+        ref_dx = 0.0
+        for g in range(G):
+            ref_u = xr[:, k] @ Wr[g, k].T + bias.reshape(G, heads, dh)[g, k].cpu().double()
+            assert relerr(f64(u).reshape(B * L, G, heads, dh)[:, g, k], ref_u) <= tol
+            assert relerr(f64(dW).reshape(G, heads, dh, dh)[g, k], dur[:, g, k].T @ xr[:, k]) <= 2e-5
+            ref_dx = ref_dx + dur[:, g, k] @ Wr[g, k]
+        assert relerr(f64(dx).reshape(B * L, heads, dh)[:, k], ref_dx) <= tol
+    assert relerr(f64(db), f64(du).sum((0, 1))) <= 2e-5          # column sums of du as stored
+
+
 def test_projection_refuses_what_it_cannot_do():
     import paper_2510_21450_amd as P
     x = torch.zeros(1, 4, 96, device="cuda")
