@@ -176,27 +176,30 @@ def projection_calls(run):
     return pf, pb, dh
 
 
+def block_iterations(w):
+    """Iterations of the launch whose rate is quoted: the first block of a solve; cells with two state values solve
+    in one launch at these sizes, which is timed over more iterations than any of these solves needs."""
+    from workloads import cell_dims
+    return min(FUSED_HEAD, w.max_iter) if cell_dims(w.cell)[1] == 1 else 8
+
+
 def kernel_figures(run, reps, counters):
     """Per-kernel timings of one workload (device events on the launch stream) and its roofline record."""
     P, torch, w, N = run.P, run.torch, run.w, run.N
     cnt = counters.get(run.name, {})
     out = {}
     if w.cell == "tanh_dense":
-        # one launch sequence per iteration: time per Newton iteration from fixed-count solves
-        m_lo, m_hi = 2, 10
-        for m in (m_lo, m_hi):
-            run.forward(tol=-1.0, max_iter=m)
-        t_lo = time_events(lambda: run.forward(tol=-1.0, max_iter=m_lo), reps)
-        t_hi = time_events(lambda: run.forward(tol=-1.0, max_iter=m_hi), reps)
-        t_iter_ms = (mean(t_hi) - mean(t_lo)) / (m_hi - m_lo)
-        # the scan composes one 64x64 Jacobian product (2 H^3 flop) per timestep
-        flops_iter = 2.0 * w.H ** 3 * w.B * w.L
+        # the solve is one launch that walks the steps in order, its iterations as a wavefront: bound by the
+        # latency of a step (a 64 x 64 matrix-vector product on registers, LDS exchange, barrier), not by a rate
+        t_fwd_ms = mean(time_events(lambda: run.forward(), reps))
         chunk = P.dense_chunk()
         n_c = (w.L + chunk - 1) // chunk
         flops_kernel = 2.0 * w.H ** 3 * w.B * max(0, n_c - 2) * (chunk - 1)
-        out.update({"t_iter_ms": t_iter_ms, "iter_tflops": flops_iter / (t_iter_ms * 1e-3) / 1e12})
-        out["iter_frac_mfma"] = out["iter_tflops"] / MFMA_F32_PEAK_TFLOPS
-        # the composition kernel alone, same launch as inside the solve, on Jacobian factors of the same
+        iters = int(run.iters.cpu()[0])
+        # per step and iteration W h and J delta, 2 H^2 each
+        ach_solve = 4.0 * w.H ** 2 * w.B * w.L * iters / (t_fwd_ms * 1e-3) / 1e12
+        out.update({"t_step_ns": t_fwd_ms * 1e6 / w.L, "solve_tflops": ach_solve})
+        # the composition kernel of the scan (long solves of few sequences; also an entry point), on Jacobian factors of the same
         # distribution (d = 1 - tanh^2 of the converged states)
         run.forward()
         dfac = (1.0 - run.h_out.view(w.B, w.L, w.H) ** 2).contiguous()
@@ -206,9 +209,11 @@ def kernel_figures(run, reps, counters):
         ach = flops_kernel / (t_k * 1e-3) / 1e12
         out["chunk_products_ms"] = t_k
         out["algorithmic_flops_per_launch"] = flops_kernel
-        out["roofline"] = {"bound": "mfma", "kernel": "dense_products_sweep_kernel (chunk products part)",
-                           "achieved": ach, "peak": MFMA_F32_PEAK_TFLOPS, "unit": "TFLOP/s",
-                           "frac": ach / MFMA_F32_PEAK_TFLOPS, "traffic": cnt.get("dominant", {}).get("traffic_bytes")}
+        out["chunk_products_tflops"] = ach
+        out["chunk_products_frac_mfma"] = ach / MFMA_F32_PEAK_TFLOPS
+        out["roofline"] = {"bound": "latency", "kernel": "dense_wavefront_kernel", "achieved": ach_solve,
+                           "peak": MFMA_F32_PEAK_TFLOPS, "unit": "TFLOP/s",
+                           "frac": ach_solve / MFMA_F32_PEAK_TFLOPS, "traffic": cnt.get("dominant", {}).get("traffic_bytes")}
         run.extra = (dfac, Aout)
         return out
     ab = ALGO_BYTES[run.name]
@@ -227,13 +232,15 @@ def kernel_figures(run, reps, counters):
     out.update({"t_iter_ms": t_iter_ms, "t_iter_min_ms": (min(t_hi) - min(t_lo)) / (m_hi - m_lo),
                 "iter_bytes_per_elt": ab["iter"], "iter_gbs": iter_gbs, "iter_frac_hbm": iter_gbs / HBM_PEAK_GBS,
                 "iter_traffic_bytes": cnt.get("iter", {}).get("traffic_bytes")})
-    # The dominant launch of a solve: its first fused block of FUSED_HEAD iterations from the initial
-    # guess (u read once, the iterate in registers, h written once).  Timed as the library runs it
+    # The dominant launch of a solve.  One state value: its first fused block of FUSED_HEAD iterations from the
+    # initial guess (u read once, the iterate in registers, h written once).  Timed as the library runs it
     # inside a solve: a tolerance that is met at once ends the solve after this launch, which still
     # performs all its iterations; the call also holds the reset of the control block and one
-    # launch that returns at once.
-    K0 = min(FUSED_HEAD, w.max_iter)
-    block = lambda: run.forward(tol=3.0e38, max_iter=K0 + 1)
+    # launch that returns at once.  Two state values (at these sizes): the one launch that walks every channel
+    # group's tiles, timed over a fixed count, because under a tolerance every group stops by itself.
+    K0 = block_iterations(w)
+    one_launch = K0 != min(FUSED_HEAD, w.max_iter)
+    block = (lambda: run.forward(tol=-1.0, max_iter=K0)) if one_launch else (lambda: run.forward(tol=3.0e38, max_iter=K0 + 1))
     block()
     t_blk = time_events(block, reps)
     t_block_ms = mean(t_blk)
@@ -258,7 +265,7 @@ def kernel_figures(run, reps, counters):
         out["block_issue_bound_frac"] = t_issue_ms / t_block_ms
     else:
         out["block_issue_bound_ms"] = out["block_issue_bound_frac"] = None
-    out["roofline"] = {"bound": "alu", "kernel": "newton_fused_kernel (first block of a solve)", "achieved": ach,
+    out["roofline"] = {"bound": "alu", "kernel": "newton_short_kernel (the whole solve)" if one_launch else "newton_fused_kernel (first block of a solve)", "achieved": ach,
                        "peak": VALU_F32_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": ach / VALU_F32_PEAK_TFLOPS,
                        "traffic": cnt.get("dominant", {}).get("traffic_bytes")}
     out["algorithmic_bytes_per_launch"] = ab["block"] * N
@@ -290,7 +297,7 @@ def measure(P, torch, name, steps, warmup, reps, counters, headline):
     if w.B * w.L * w.H < 1 << 16:
         # launch-latency bound: no roofline is claimed for it
         rec["roofline"] = None
-        rec["dominant_kernel"] = "newton_fused_kernel (launch latency: no roofline claimed)"
+        rec["dominant_kernel"] = "newton_short_kernel (launch latency: no roofline claimed)"
     else:
         rec.update(kernel_figures(run, reps, counters))
         rec["dominant_kernel"] = rec["roofline"]["kernel"]
@@ -301,9 +308,10 @@ def headline_extras(run, rec, reps, counters):
     """Figures beside the timed step, for the headline workload only."""
     P, torch, w, N = run.P, run.torch, run.w, run.N
     u, params, h0 = run.u, run.params, run.h0
-    # blocks of Newton iterations of the plan; the first two are launches of their own, the rest share one
+    # blocks of Newton iterations of the plan; the first (two state values: the first two) is a launch of its own, the
+    # rest share one.  Sequences that are walked by one workgroup per channel group take one launch for everything.
     rec["blocks"] = P.solve_plan(w.tol, w.max_iter) if w.cell != "tanh_dense" else None
-    rec["launches_per_solve"] = min(len(rec["blocks"]), 3) if rec["blocks"] is not None else None
+    rec["launches_per_solve"] = None if rec["blocks"] is None else min(len(rec["blocks"]), 2) if block_iterations(w) == FUSED_HEAD and w.L > 256 else 1
     if w.cell != "tanh_dense":
         # the same step under pararnn_set_workspace_reuse (the caller's promise that nothing else writes to the
         # two workspaces between calls: true for this loop): the carry records are not cleared again
@@ -400,9 +408,12 @@ def profile_pass(P, torch, name):
     if w.cell == "tanh_dense":
         kernel_figures(run, 3, {})
     else:
-        K0 = min(FUSED_HEAD, w.max_iter)
+        K0 = block_iterations(w)
         for _ in range(3):
-            run.forward(tol=3.0e38, max_iter=K0 + 1)
+            if K0 == min(FUSED_HEAD, w.max_iter):
+                run.forward(tol=3.0e38, max_iter=K0 + 1)
+            else:
+                run.forward(tol=-1.0, max_iter=K0)
         P.set_fused(False)
         for _ in range(3):
             run.forward(tol=-1.0, max_iter=3)

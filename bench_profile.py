@@ -91,11 +91,9 @@ def counter_rows(prefix):
 def classes(kind):
     """Launch classes of a workload: name -> (kernel-name pattern, which dispatches of it)."""
     if kind == "dense":
-        return {"dominant": (r"^dense_products_sweep_kernel<false", "work"),
-                "residual": (r"^dense_residual_kernel", "work"),
-                "carry": (r"^dense_carry_kernel", "work"),
-                "final_sweep": (r"^dense_final_sweep_kernel<false", "work")}
-    return {"dominant": (r"^newton_fused_kernel<", "longest"),          # first block of a solve
+        return {"dominant": (r"^dense_wavefront_kernel", "work"),           # the whole solve
+                "products": (r"^dense_products_sweep_kernel<false", "work")}
+    return {"dominant": (r"^newton_(fused|short)_kernel<", "longest"),  # first block of a solve, or all of it
             "iter": (r"^newton_iter_kernel<.*false>$", "work"),        # one iteration per launch, from the iterate
             "bwd": (r"^backward_kernel<", "work"),
             # the input projection in front of the solve (four heads; not part of the timed step)
@@ -182,7 +180,7 @@ def profile_config(cfg, outdir):
                 if "SQ_VALU_MFMA_BUSY_CYCLES" in rec[c] and "GRBM_GUI_ACTIVE" in rec[c]:
                     rec[c]["mfma_busy_frac"] = rec[c]["SQ_VALU_MFMA_BUSY_CYCLES"] / 1024.0 / (rec[c]["GRBM_GUI_ACTIVE"] / 8.0)
         if "dominant" in rec and "SQ_INSTS_VALU" in rec["dominant"]:
-            K0 = min(bench.FUSED_HEAD, w.max_iter)
+            K0 = bench.block_iterations(w)
             rec["dominant"]["valu_insts_per_elt_iter"] = rec["dominant"]["SQ_INSTS_VALU"] * 64.0 / (N * K0)
             rec["dominant"]["trans_insts_per_elt_iter"] = rec["dominant"]["SQ_INSTS_VALU_TRANS_F32"] * 64.0 / (N * K0)
     rec["calibration"] = {"copy_bytes_each_way": n_copy, "fetch_factor": f_fetch, "write_factor": f_write}
@@ -198,7 +196,7 @@ def profile_config(cfg, outdir):
     lines.append(f"Byte-counter calibration on the device copy of {int(n_copy)} bytes in the same run: "
                  f"bytes fetched = {f_fetch:.3f} x FETCH_SIZE KiB x 1024, bytes written = {f_write:.3f} x WRITE_SIZE KiB x 1024")
     lines.append("")
-    lines.append("Launch classes (dominant = first fused block of a solve / chunk products; averages per launch):")
+    lines.append("Launch classes (dominant = first block of a solve or the launch that is the whole solve; averages per launch):")
     for cname, r in rec.items():
         if cname == "calibration":
             continue

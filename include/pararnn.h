@@ -175,15 +175,18 @@ int pararnn_set_streaming(int mode);
  * iteration before the end of a launch, the returned h is the iterate at the
  * END of that launch -- the converged iterate refined by the Newton iterations
  * that were already in flight -- so it differs from the per-iteration path's h
- * by less than tol.  0 <= n_iters <= 8; 0 turns
+ * by less than tol.  Problems that one workgroup per channel group solves in a
+ * single launch (pararnn_set_fused(1), sizes chosen by the library) have no blocks:
+ * each group of channels returns the iterate that met the tolerance within it.
+ * 0 <= n_iters <= 8; 0 turns
  * it off; default 5.  Query workspace sizes after setting it (a workspace
  * that is too small for the record slots falls back to one launch per
  * iteration). */
 int pararnn_set_fused_head(int n_iters);
 
 /* Tuning / test hook (host, process-wide, not thread-safe; default 1): the blocks
- * of a solve to a tolerance that follow its second launch (the first fused
- * block, then one iteration of the per-iteration kernel) run in ONE more launch
+ * of a solve to a tolerance that follow its first launch (the first fused block;
+ * two-state and larger cells: its second, one iteration of the per-iteration kernel) run in ONE more launch
  * of the fused kernel, which walks the rest of the plan on the device (grid-wide
  * barriers between blocks; the grid is what the device holds at once, and a
  * barrier wait is bounded like the look-back waits: pararnn_set_spin_limit) and
@@ -218,7 +221,7 @@ int pararnn_set_workspace_reuse(int enable);
  * block_sizes[0 .. capacity) and returns the number of blocks (which may exceed
  * capacity), or -1 on invalid arguments.  The sizes add up to max_iter.  The
  * stopping test is evaluated for every iteration and acted on between blocks.
- * The first two blocks are launches of their own; the following ones share one
+ * The first block (two-state and larger cells: the first two) is a launch of its own; the following ones share one
  * launch (pararnn_set_fused_tail) or are launches of their own. */
 int pararnn_solve_plan(float tol, int max_iter, int *block_sizes, int capacity);
 
@@ -323,8 +326,8 @@ int pararnn_forward_noalloc(int cell, int dtype, const float *params, const void
  *   dL_dh0          out [B][S][H], or NULL
  *   workspace       DEVICE scratch of at least pararnn_workspace_bytes(.., 1)
  * Dense cell (H = 64, fp32): with mu_l = (1 - F_l^2) * lam_l the recurrence reads
- * mu_l = diag(1 - F_l^2) W^T mu_{l+1} + (1 - F_l^2) * g_l, which the forward scan
- * kernels run with W^T and the time axis reversed; dL_du = mu, dL_dparams =
+ * mu_l = diag(1 - F_l^2) W^T mu_{l+1} + (1 - F_l^2) * g_l, the forward recurrence
+ * with W^T and the time axis reversed; dL_du = mu, dL_dparams =
  * dL/dW = sum_{b,l} mu_l h_{l-1}^T, dL_dh0 = W^T mu_1.
  * Same return convention as pararnn_forward.
  */
@@ -453,9 +456,11 @@ int pararnn_set_dense_products(int mode);
 int pararnn_set_dense_jacobian(int mode);
 
 /*
- * Launch structure of the dense path's forward solves (host, process-wide, not
- * thread-safe; default 1).  An iteration has four phases (residual; chunk
- * products and chunk-local sweeps; carry; final sweep).
+ * Launch structure of the dense path's forward solves where the linear systems are
+ * solved by the chunked scan (host, process-wide, not thread-safe; default 1;
+ * solves by forward substitution, most sizes, are two launches in every mode).
+ * An iteration of the scan has four phases (residual; chunk products and
+ * chunk-local sweeps; carry; final sweep).
  *   1  the first six iterations are enqueued as one launch per phase; whatever is
  *      left of max_iter runs in ONE persistent launch whose phases are separated
  *      by grid-wide barriers and which returns at once when the solve has already
