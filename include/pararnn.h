@@ -215,6 +215,14 @@ int pararnn_set_fused_tail(int enable);
  * predecessor's: wrong results without an error. */
 int pararnn_set_workspace_reuse(int enable);
 
+/* The same promise for one workspace on the current device (thread-safe): from here until enable = 0 nothing but this
+ * library writes to it, and no two calls that use it run at the same time.  What it holds now may be anything: the first
+ * call clears its records.  enable = 0 has to come before the memory is freed or used otherwise. */
+int pararnn_workspace_keep(void *workspace, int enable);
+/* 1 if the library knows what this workspace holds, so that the next call of the same layout clears nothing; else 0
+ * (the last call kept no carry records there, failed, was captured into a graph, or there was no promise). */
+int pararnn_workspace_known(const void *workspace);
+
 /* The blocks of Newton iterations pararnn_forward runs for a solve with these
  * settings when the workspace is of the size pararnn_workspace_bytes reports
  * (host only, no device work): writes the number of iterations of each block to

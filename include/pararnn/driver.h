@@ -401,12 +401,14 @@ int backward_diag(const CellInfo &ci, int dtype, const Layout &lo, BwdArgs &a, h
 {
     bool fill = true;
     a.g.epoch_base = workspace_epoch(a.ctrl, layout_signature(1, ci, dtype, lo, 1), st, &fill);
-    hipError_t e = launch_reset(a.ctrl, a.rec, fill ? lo.n_rec : 0, nullptr, 0, st);
+    // Nothing to clear, no launch for it: the reduction at the end of the call before left the control block cleared.
+    hipError_t e = fill ? launch_reset(a.ctrl, a.rec, lo.n_rec, nullptr, 0, st) : hipSuccess;
     if (e != hipSuccess) return PARARNN_HIP_ERROR;
     e = dtype == PARARNN_BF16 ? Kernels<Cell, unsigned short>::backward(lo.cfg, a, st)
                               : Kernels<Cell, float>::backward(lo.cfg, a, st);
     if (e != hipSuccess) return e == hipErrorInvalidValue ? PARARNN_UNSUPPORTED : PARARNN_HIP_ERROR;
-    e = launch_param_reduce(a.part, dparams, lo.g.n_lt * lo.g.B, ci.PR * lo.g.H, st);
+    e = launch_param_reduce(a.part, dparams, lo.g.n_lt * lo.g.B, ci.PR * lo.g.H, st,
+                            a.g.epoch_base ? a.ctrl : nullptr);
     return e == hipSuccess ? PARARNN_OK : PARARNN_HIP_ERROR;
 }
 

@@ -42,7 +42,8 @@ hipError_t launch_reset(Ctrl *ctrl, unsigned long long *rec, size_t n_rec, int *
 hipError_t launch_store_bf16(const float *src, void *dst, size_t n, const Ctrl *ctrl, hipStream_t st);
 // n 32-bit words of zeros, written by a kernel (no memset node when a caller captures a graph)
 hipError_t launch_zero_words(unsigned int *dst, int n, hipStream_t st);
-hipError_t launch_param_reduce(const float *part, float *out, int n_terms, int n_out, hipStream_t st);
+hipError_t launch_param_reduce(const float *part, float *out, int n_terms, int n_out, hipStream_t st,
+                               Ctrl *ctrl = nullptr);
 // two such sums with the same number of terms in one launch; everything 16-byte aligned, counts in fours (the second may be 0)
 struct ReducePair {
     const float *part[2];

@@ -243,6 +243,12 @@ def set_workspace_reuse(enable: bool = False) -> None:
     _raise(_lib.pararnn_set_workspace_reuse(int(enable)), "pararnn_set_workspace_reuse")
 
 
+def release_workspaces() -> int:
+    """Give the workspaces that `forward`, `backward` and the autograd functions keep between calls (at most 16 and a
+    thirty-second of the memory per device) back to torch's allocator; returns their bytes."""
+    return _host.release_workspaces()
+
+
 def set_fused_tail(enable: bool = True) -> None:
     """pararnn_set_fused_tail: the blocks after a solve's first launch share one persistent launch (default)
     or are launches of their own."""

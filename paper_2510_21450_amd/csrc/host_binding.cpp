@@ -8,7 +8,12 @@
 #include <torch/csrc/utils/pybind.h>
 #include <torch/custom_class.h>
 
+#include <algorithm>
+#include <array>
+#include <map>
+#include <mutex>
 #include <string>
+#include <vector>
 
 #include "pararnn.h"
 
@@ -93,6 +98,131 @@ Tensor workspace_of(size_t bytes, const Tensor &like, const OptTensor &given)
 }
 
 struct Dims { int B, L, H; };
+
+// ------------------------------------------------------------------ kept workspaces
+// The carry records of a solve or a backward pass have to be cleared unless the library knows what they hold: 1.3 GB for
+// 2^30 timestep-channels (0.25 ms of a forward solve, 0.05 of a backward pass and, in small passes, a launch of 5 us).  So
+// the workspaces of the diagonal cells' calls are kept between calls, per device, stream and problem, under the library's
+// per-workspace promise.  A call takes one out while it enqueues its work, and the next one that gets it is behind it in
+// the same stream; calls of several threads find different ones.  Bounds per device: kMost workspaces and a thirty-second of
+// its memory, the least recently used go first.  Under stream capture, with a workspace or a stream of the caller's, for
+// small problems (0.5 us of host time to look would show there) and for kernels without records nothing is kept.
+using WsKey = std::array<int64_t, 8>;
+constexpr size_t kMost = 16;
+constexpr double kSmall = 1 << 20;       // timestep-channels; below, most calls take kernels without records and 10-20 us
+struct KeptWs { WsKey key; Tensor ws; };
+struct DevicePool {
+    std::vector<KeptWs> free;          // least recently used first
+    size_t bytes = 0, cap = 0;
+};
+std::mutex &pool_mutex()
+{
+    static std::mutex &m = *new std::mutex;
+    return m;
+}
+std::map<int, DevicePool> &pools()
+{
+    static std::map<int, DevicePool> &p = *new std::map<int, DevicePool>;     // never destroyed: the runtime may be gone by then
+    return p;
+}
+
+// Gives a kept workspace up; the device is the current one.  The library has to know before the memory goes.
+void give_up(Tensor &ws)
+{
+    pararnn_workspace_keep(ws.data_ptr(), 0);
+    ws.reset();
+}
+
+class Workspace {
+public:
+    Workspace(const Cell &c, bool back, int code, const Dims &d, int64_t fixed, size_t bytes, const Tensor &like,
+              const OptTensor &given, const c10::optional<int64_t> &stream)
+    {
+        if (has(given) || stream || (double)d.B * d.L * d.H < kSmall) { ws_ = workspace_of(bytes, like, given); return; }
+        const auto cur = c10::hip::getCurrentHIPStream();
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (cur.device_index() != like.get_device() || hipStreamIsCapturing(cur.stream(), &cap) != hipSuccess ||
+            cap != hipStreamCaptureStatusNone) {
+            ws_ = workspace_of(bytes, like, given);
+            return;
+        }
+        device_ = cur.device_index();
+        key_ = {reinterpret_cast<int64_t>(cur.stream()), c.number >= 0 ? c.number : reinterpret_cast<int64_t>(c.fwd_fn),
+                back ? -1 : fixed, code, d.B, d.L, d.H, (int64_t)bytes};
+        {
+            std::lock_guard<std::mutex> lock(pool_mutex());
+            DevicePool &p = pools()[device_];
+            for (size_t i = p.free.size(); i-- > 0;)
+                if (p.free[i].key == key_) {
+                    ws_ = std::move(p.free[i].ws);
+                    p.free.erase(p.free.begin() + (long)i);
+                    p.bytes -= bytes;
+                    kept_ = true;
+                    return;
+                }
+            if (p.cap == 0) {
+                size_t avail = 0, total = 0;
+                p.cap = hipMemGetInfo(&avail, &total) == hipSuccess ? total / 32 : 1;
+            }
+            if (bytes > p.cap) device_ = -1;
+        }
+        ws_ = workspace_of(bytes, like, given);
+        kept_ = device_ >= 0 && pararnn_workspace_keep(ws_.data_ptr(), 1) == PARARNN_OK;
+    }
+    Workspace(const Workspace &) = delete;
+    Workspace &operator=(const Workspace &) = delete;
+    // after a call that failed, or one without carry records
+    ~Workspace() { if (kept_) give_up(ws_); }
+
+    void *data() const { return ws_.data_ptr(); }
+    size_t size() const { return (size_t)ws_.numel(); }
+    // the call's work is enqueued
+    void done()
+    {
+        if (!kept_ || !pararnn_workspace_known(ws_.data_ptr())) return;
+        std::vector<KeptWs> old;
+        {
+            std::lock_guard<std::mutex> lock(pool_mutex());
+            DevicePool &p = pools()[device_];
+            p.bytes += (size_t)ws_.numel();
+            p.free.push_back({key_, std::move(ws_)});
+            kept_ = false;
+            while (p.free.size() > kMost || p.bytes > p.cap) {
+                p.bytes -= (size_t)p.free.front().ws.numel();
+                old.push_back(std::move(p.free.front()));
+                p.free.erase(p.free.begin());
+            }
+        }
+        for (KeptWs &k : old) give_up(k.ws);
+    }
+
+private:
+    Tensor ws_;
+    WsKey key_{};
+    int device_ = -1;
+    bool kept_ = false;
+};
+
+int64_t release_workspaces()
+{
+    std::map<int, std::vector<KeptWs>> all;
+    int64_t bytes = 0;
+    {
+        std::lock_guard<std::mutex> lock(pool_mutex());
+        for (auto &p : pools()) {
+            bytes += (int64_t)p.second.bytes;
+            p.second.bytes = 0;
+            all[p.first].swap(p.second.free);
+        }
+    }
+    for (auto &d : all) {
+        if (d.second.empty()) continue;
+        const c10::DeviceGuard guard(d.second.front().ws.device());
+        for (KeptWs &k : d.second) give_up(k.ws);
+    }
+    return bytes;
+}
+
 Dims dims4(const Tensor &u, const char *name)
 {
     if (u.dim() != 4) throw py::value_error(std::string(name) + " must have four dimensions");
@@ -116,16 +246,17 @@ Solve solve(const Cell &c, const Tensor &params, const Tensor &u, const OptTenso
     r.iters = at::empty({2}, u.options().dtype(at::kInt));
     if (trace) r.trace = at::zeros({max_iter > 1 ? max_iter : 1}, u.options().dtype(at::kFloat));
     const size_t need = tol < 0 ? c.ws_fused(code, d.B, d.L, d.H, (int)max_iter) : c.ws(code, d.B, d.L, d.H, 0);
-    const Tensor ws = workspace_of(need, u, workspace);
+    Workspace ws(c, false, code, d, tol < 0 ? max_iter : 0, need, u, workspace, stream);
     float *tr = trace ? static_cast<float *>(r.trace.data_ptr()) : nullptr;
     const float *p = static_cast<const float *>(params.data_ptr());
     int *it = static_cast<int *>(r.iters.data_ptr());
     const int rc = c.number >= 0
                        ? pararnn_forward(c.number, code, p, u.data_ptr(), ptr(h0), d.B, d.L, d.H, (float)tol, (int)max_iter,
-                                         r.h.data_ptr(), it, tr, ws.data_ptr(), (size_t)ws.numel(), stream_ptr(stream))
+                                         r.h.data_ptr(), it, tr, ws.data(), ws.size(), stream_ptr(stream))
                        : c.fwd_fn(code, p, u.data_ptr(), ptr(h0), d.B, d.L, d.H, (float)tol, (int)max_iter, r.h.data_ptr(), it,
-                                  tr, ws.data_ptr(), (size_t)ws.numel(), stream_ptr(stream));
+                                  tr, ws.data(), ws.size(), stream_ptr(stream));
     raise_if(rc, c.what + "_forward");
+    ws.done();
     return r;
 }
 
@@ -153,16 +284,17 @@ Grads adjoint(const Cell &c, const Tensor &params, const Tensor &u, const OptTen
         r.dparams = at::empty(params.sizes(), params.options());
         if (want_dh0) r.dh0 = at::empty({d.B, c.S, d.H}, u.options());
     }
-    const Tensor ws = workspace_of(c.ws(code, d.B, d.L, d.H, 1), u, workspace);
+    Workspace ws(c, true, code, d, 0, c.ws(code, d.B, d.L, d.H, 1), u, workspace, stream);
     const float *p = static_cast<const float *>(params.data_ptr());
     float *dp = static_cast<float *>(r.dparams.data_ptr());
     void *dh = r.dh0.defined() ? r.dh0.data_ptr() : nullptr;
     const int rc = c.number >= 0
                        ? pararnn_backward(c.number, code, p, u.data_ptr(), ptr(h0), h.data_ptr(), g.data_ptr(), d.B, d.L, d.H,
-                                          r.du.data_ptr(), dp, dh, ws.data_ptr(), (size_t)ws.numel(), stream_ptr(stream))
+                                          r.du.data_ptr(), dp, dh, ws.data(), ws.size(), stream_ptr(stream))
                        : c.bwd_fn(code, p, u.data_ptr(), ptr(h0), h.data_ptr(), g.data_ptr(), d.B, d.L, d.H, r.du.data_ptr(),
-                                  dp, dh, ws.data_ptr(), (size_t)ws.numel(), stream_ptr(stream));
+                                  dp, dh, ws.data(), ws.size(), stream_ptr(stream));
     raise_if(rc, c.what + "_backward");
+    ws.done();
     return r;
 }
 
@@ -368,6 +500,7 @@ PYBIND11_MODULE(_host, m)
         ProjGrads r = project_backward(x, Wx, du, n_heads, want_dx, want_dw, want_db, workspace, stream);
         return py::make_tuple(object_of(r.dx), object_of(r.dW), object_of(r.db));
     });
+    m.def("release_workspaces", &release_workspaces);
     m.def("rnn_apply", [](const CellPtr &c, const Tensor &params, const Tensor &u, const OptTensor &h0, double tol, int64_t max_iter) {
         variable_list r = Recurrence::apply(params, u, h0, c, tol, max_iter);
         return py::make_tuple(r[0], r[1]);

@@ -25,6 +25,7 @@ namespace {
 struct WorkspaceNote {
     unsigned long long sig;    // layout signature of the last call that used the workspace
     unsigned int number;       // that call's number (1 .. 2^20 - 1)
+    bool kept;                 // promised on its own (pararnn_workspace_keep)
 };
 std::mutex g_ws_mutex;
 std::unordered_map<unsigned long long, WorkspaceNote> g_ws_notes;      // by device and address
@@ -34,6 +35,15 @@ unsigned long long ws_key(const void *workspace)
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) dev = 0;
     return ((unsigned long long)(unsigned int)dev << 56) ^ (unsigned long long)(uintptr_t)workspace;
+}
+
+// drops what is known of the content; a promise for this workspace stands
+void forget_locked(unsigned long long key)
+{
+    const auto it = g_ws_notes.find(key);
+    if (it == g_ws_notes.end()) return;
+    if (it->second.kept) it->second.sig = 0;
+    else g_ws_notes.erase(it);
 }
 }  // namespace
 
@@ -57,8 +67,9 @@ unsigned int workspace_epoch(void *workspace, unsigned long long layout_sig, hip
     *fill = true;
     const unsigned long long key = ws_key(workspace);
     std::lock_guard<std::mutex> lock(g_ws_mutex);
-    if (!settings().ws_reuse || stream_is_capturing(st)) {
-        g_ws_notes.erase(key);
+    const auto it = g_ws_notes.find(key);
+    if ((!settings().ws_reuse && (it == g_ws_notes.end() || !it->second.kept)) || stream_is_capturing(st)) {
+        forget_locked(key);
         return 0u;
     }
     WorkspaceNote &n = g_ws_notes[key];                // a new note has sig 0, which no call has
@@ -76,7 +87,7 @@ void workspace_forget(void *workspace)
 {
     const unsigned long long key = ws_key(workspace);
     std::lock_guard<std::mutex> lock(g_ws_mutex);
-    g_ws_notes.erase(key);
+    forget_locked(key);
 }
 
 }  // namespace pararnn
@@ -231,6 +242,24 @@ int pararnn_set_workspace_reuse(int enable)
 {
     settings().ws_reuse = enable ? 1 : 0;
     return PARARNN_OK;
+}
+
+int pararnn_workspace_keep(void *workspace, int enable)
+{
+    if (!workspace) return PARARNN_INVALID_ARG;
+    const unsigned long long key = ws_key(workspace);
+    std::lock_guard<std::mutex> lock(g_ws_mutex);
+    if (enable) g_ws_notes[key] = {0, 0, true};
+    else g_ws_notes.erase(key);
+    return PARARNN_OK;
+}
+
+int pararnn_workspace_known(const void *workspace)
+{
+    const unsigned long long key = ws_key(workspace);
+    std::lock_guard<std::mutex> lock(g_ws_mutex);
+    const auto it = g_ws_notes.find(key);
+    return it != g_ws_notes.end() && it->second.sig != 0;
 }
 
 int pararnn_solve_plan(float tol, int max_iter, int *block_sizes, int capacity)

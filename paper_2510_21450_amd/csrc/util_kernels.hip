@@ -57,9 +57,12 @@ __global__ void store_bf16_tail_kernel(const float *src, unsigned short *dst, in
 // dL/dparams[i] = sum over the n_terms (tile, sequence) partials part[t][i].
 // A block owns 64 outputs; its 16 slices of 64 threads sum interleaved terms
 // with independent accumulators, then the slices are added in a fixed order,
-// so the result does not depend on scheduling.
-__global__ __launch_bounds__(1024) void param_reduce_kernel(const float *part, float *out, int n_terms, int n_out)
+// so the result does not depend on scheduling.  ctrl (or NULL): the control block of
+// the call, which the first block leaves cleared for the next one.
+__global__ __launch_bounds__(1024) void param_reduce_kernel(const float *part, float *out, int n_terms, int n_out,
+                                                            Ctrl *ctrl)
 {
+    if (ctrl && blockIdx.x == 0 && threadIdx.x < 64) reinterpret_cast<unsigned int *>(ctrl)[threadIdx.x] = 0u;
     __shared__ float s_sum[16][64];
     const int o = threadIdx.x & 63, slice = threadIdx.x >> 6;
     const int i = blockIdx.x * 64 + o;
@@ -170,9 +173,9 @@ hipError_t launch_store_bf16(const float *src, void *dst, size_t n, const Ctrl *
     return hipGetLastError();
 }
 
-hipError_t launch_param_reduce(const float *part, float *out, int n_terms, int n_out, hipStream_t st)
+hipError_t launch_param_reduce(const float *part, float *out, int n_terms, int n_out, hipStream_t st, Ctrl *ctrl)
 {
-    hipLaunchKernelGGL(param_reduce_kernel, dim3((n_out + 63) / 64), dim3(1024), 0, st, part, out, n_terms, n_out);
+    hipLaunchKernelGGL(param_reduce_kernel, dim3((n_out + 63) / 64), dim3(1024), 0, st, part, out, n_terms, n_out, ctrl);
     return hipGetLastError();
 }
 

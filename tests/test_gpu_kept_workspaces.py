@@ -1,0 +1,113 @@
+"""Workspaces kept between the calls of the Python entry points: carry records are not cleared for a call of the same
+problem, and a backward pass then needs no clearing launch.  The results have to be the bits of a call on a fresh workspace
+of the caller's, whatever ran before on the kept one, on every stream and from every thread."""
+import threading
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+GS = {"gru_diag": (3, 1, 6), "lstm_diag": (4, 2, 8)}
+
+
+def problem(cell, dtype, B, L, H, seed):
+    G, S, _ = GS[cell]
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    rand = lambda *s: torch.randn(*s, generator=gen, device="cuda")
+    params = (torch.rand(2, G, H, generator=gen, device="cuda") * 2 - 1) * 0.9
+    return params, rand(B, L, G, H).to(dtype), (0.1 * rand(B, S, H)).to(dtype), rand(B, L, S, H).to(dtype)
+
+
+def run(P, cell, p, fresh, fixed=False):
+    params, u, h0, g = p
+    B, L, _, H = u.shape
+    tol, n = (-1.0, 3) if fixed else (1e-5, 16)
+    ws = [None, None]
+    if fresh:
+        size = P.workspace_bytes_fused(cell, u.dtype, B, L, H, n) if fixed else P.workspace_bytes(cell, u.dtype, B, L, H)
+        ws = [torch.empty(s, dtype=torch.uint8, device="cuda").random_(0, 256)
+              for s in (size, P.workspace_bytes(cell, u.dtype, B, L, H, True))]
+    h, iters, _ = P.forward(cell, params, u, h0, tol=tol, max_iter=n, workspace=ws[0])
+    return (h, iters, *P.backward(cell, params, u, h0, h, g, workspace=ws[1]))
+
+
+def same(a, b):
+    return all(torch.equal(x, y) for x, y in zip(a, b))
+
+
+@pytest.mark.parametrize("cell,dtype,B,L,H", [
+    ("gru_diag", torch.float32, 2, 2100, 260),       # records in both directions
+    ("gru_diag", torch.bfloat16, 1, 8200, 136),      # above the one-workgroup walks of bf16
+    ("lstm_diag", torch.float32, 5, 777, 300),       # forward without records, backward with them
+    ("gru_diag", torch.float32, 2, 2047, 256),       # just below the size from which anything is kept
+])
+def test_repeated_calls_give_the_bits_of_fresh_workspaces(cell, dtype, B, L, H):
+    import paper_2510_21450_amd as P
+    P.release_workspaces()
+    ps = [problem(cell, dtype, B, L, H, s) for s in range(3)]
+    want = [run(P, cell, p, True) for p in ps]
+    want_fixed = run(P, cell, ps[0], True, fixed=True)
+    assert P.release_workspaces() == 0               # a caller's workspace is not kept
+    for rep in range(3):
+        for k, p in enumerate(ps):
+            assert same(run(P, cell, p, False), want[k]), (rep, k)
+        assert same(run(P, cell, ps[0], False, fixed=True), want_fixed), rep
+    assert (P.release_workspaces() > 0) == (B * L * H >= 1 << 20)
+    assert same(run(P, cell, ps[1], False), want[1])
+
+
+def test_streams_and_threads_do_not_share_a_workspace_in_use():
+    import paper_2510_21450_amd as P
+    cell = "gru_diag"
+    ps = [problem(cell, torch.float32, 2, 2100, 260, s) for s in range(4)]
+    want = [run(P, cell, p, True) for p in ps]
+    torch.cuda.synchronize()
+    shared, bad = torch.cuda.Stream(), []
+
+    def work(k):
+        with torch.cuda.stream(shared if k < 2 else torch.cuda.Stream()):
+            got = [run(P, cell, ps[k], False) for _ in range(4)]
+            torch.cuda.current_stream().synchronize()
+        bad.extend(k for g in got if not same(g, want[k]))
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert not bad
+
+
+def test_many_problems_stay_within_the_bound():
+    import paper_2510_21450_amd as P
+    P.release_workspaces()
+    cell, most = "gru_diag", 0
+    for L in range(2100, 2120):
+        p = problem(cell, torch.float32, 2, L, 256, L)
+        assert same(run(P, cell, p, False), run(P, cell, p, True)), L
+        most = max(most, P.workspace_bytes(cell, torch.float32, 2, L, 256), P.workspace_bytes(cell, torch.float32, 2, L, 256, True))
+    assert 0 < P.release_workspaces() <= 16 * most
+
+
+def test_a_captured_call_keeps_nothing():
+    """A graph's workspace belongs to the graph: eager calls between the replays use others."""
+    import paper_2510_21450_amd as P
+    cell = "gru_diag"
+    ps = [problem(cell, torch.float32, 2, 2100, 260, s) for s in range(2)]
+    want = [run(P, cell, p, True) for p in ps]
+    torch.cuda.synchronize()
+    P.release_workspaces()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        got = run(P, cell, ps[0], False)
+    assert P.release_workspaces() == 0
+    for rep in range(3):
+        for t in got:
+            t.zero_()
+        eager = run(P, cell, ps[1], False)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert same(got, want[0]) and same(eager, want[1]), rep
