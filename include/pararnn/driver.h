@@ -241,7 +241,8 @@ inline bool short_shape(const CellInfo &ci, int dtype, int B, int L, int H, bool
         if (w > most) w = most;
     }
     const int T = c * (64 >> lps) * w;
-    if ((double)ci.G * H * esz * (T + 1.0) >= 2147483647.0) return false;     // 32-bit offsets within a tile
+    // 32-bit offsets within a tile, of u and of the states, whichever rows are wider
+    if ((double)(ci.G > ci.S ? ci.G : ci.S) * H * esz * (T + 1.0) >= 2147483647.0) return false;
     out->c = c; out->lps_log2 = lps; out->w = w;
     out->n_cg = (H + (1 << lps) - 1) >> lps;
     if ((double)B * out->n_cg > 131072.0) return false;      // verdicts that workgroup 0 collects

@@ -1,0 +1,52 @@
+"""The choice between the kernels that keep a channel group in one workgroup (include/pararnn/short_kernels.h) and those
+with carry records, on the host: a small program compiled against the driver's own header prints what is taken."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PKG = os.path.join(ROOT, "paper_2510_21450_amd")
+#: G, S, parameter rows, number of the built-in cell (-1: a cell that is not built in)
+GRU, LSTM, PARALSTM, ROT = (3, 1, 6, 0), (4, 2, 8, 1), (3, 2, 8, 4), (2, 2, 2, -1)
+F32, BF16 = 0, 1
+
+
+@pytest.fixture(scope="module")
+def choose(tmp_path_factory):
+    if not os.path.exists(os.path.join(PKG, "libpararnn.so")):
+        from paper_2510_21450_amd import build
+        build.build()
+    exe = tmp_path_factory.mktemp("probe") / "short_probe"
+    cmd = ["/opt/rocm/bin/hipcc", "--offload-arch=gfx950", "-O1", "-std=c++17", "-Xclang", "-target-feature", "-Xclang",
+           "-packed-fp32-ops", f"-I{os.path.join(ROOT, 'include')}", os.path.join(ROOT, "tests", "host_probe", "short_probe.hip"),
+           f"-L{PKG}", "-lpararnn", f"-Wl,-rpath,{PKG}", "-o", str(exe)]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+
+    def run(problems):
+        """problems: (cell, dtype, B, L, H, backward, fixed); per problem (c, lps_log2, w, workgroups, tiles) or None."""
+        text = "\n".join(" ".join(str(int(x)) for x in (*p[0], *p[1:])) for p in problems)
+        out = subprocess.run([str(exe)], input=text, capture_output=True, text=True, check=True).stdout
+        shapes = [tuple(int(x) for x in line.split()) for line in out.splitlines()]
+        assert len(shapes) == len(problems)
+        return [s if s[0] else None for s in shapes]
+    return run
+
+
+def test_offsets_within_a_tile_fit_32_bits(choose):
+    """Rows of u and of the states, whichever is wider: a cell with more state values than gates too."""
+    cells = [(g, s, 4, -1) for g in (1, 2, 3, 8) for s in (1, 2, 3, 4)]
+    ps = [(c, dt, 1, L, H, back, fixed) for c in cells for dt in (F32, BF16) for L in (1, 16, 64, 100, 300, 512, 2000)
+          for H in (1 << 18, 1 << 19, 1 << 20, 1 << 21, 1 << 22) for back in (0, 1) for fixed in (0, 3)]
+    taken = 0
+    for p, s in zip(ps, choose(ps)):
+        if s is None:
+            continue
+        taken += 1
+        (g, S, _, _), dt, _, L, H = p[:5]
+        c, lps, w, _, tiles = s
+        T = c * (64 >> lps) * w
+        assert tiles * T >= L
+        assert (T + 1) * max(g, S) * H * (2 if dt == BF16 else 4) < 2 ** 31, (p, s)
+    assert taken > 0
