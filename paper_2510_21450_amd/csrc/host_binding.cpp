@@ -451,6 +451,13 @@ struct Layer : torch::autograd::Function<Layer> {
     }
 };
 
+// Runs a call into the library without the interpreter lock: it may allocate, and wait for a place in a full launch queue.
+template <class F> auto unlocked(F &&f)
+{
+    const py::gil_scoped_release unlock;
+    return f();
+}
+
 py::object object_of(const Tensor &t) { return t.defined() ? py::cast(t) : py::none(); }
 
 }  // namespace
@@ -479,7 +486,7 @@ PYBIND11_MODULE(_host, m)
     });
     m.def("forward", [](const CellPtr &c, const Tensor &params, const Tensor &u, const OptTensor &h0, double tol, int64_t max_iter,
                         bool trace, const OptTensor &workspace, const c10::optional<int64_t> &stream, const OptTensor &out) {
-        Solve s = solve(*c, params, u, h0, tol, max_iter, trace, workspace, stream, out);
+        Solve s = unlocked([&] { return solve(*c, params, u, h0, tol, max_iter, trace, workspace, stream, out); });
         return py::make_tuple(s.h, s.iters, object_of(s.trace));
     });
     m.def("backward", [](const CellPtr &c, const Tensor &params, const Tensor &u, const OptTensor &h0, const Tensor &h, const Tensor &g,
@@ -487,30 +494,30 @@ PYBIND11_MODULE(_host, m)
                          const OptTensor &dparams, const OptTensor &dh0) {
         Grads given;
         if (has(du)) given = {*du, or_none(dparams), or_none(dh0)};
-        Grads r = adjoint(*c, params, u, h0, h, g, want_dh0, workspace, stream, has(du) ? &given : nullptr);
+        Grads r = unlocked([&] { return adjoint(*c, params, u, h0, h, g, want_dh0, workspace, stream, has(du) ? &given : nullptr); });
         return py::make_tuple(r.du, r.dparams, object_of(r.dh0));
     });
     m.def("input_projection", [](const Tensor &x, const Tensor &Wx, const OptTensor &bias, int64_t n_heads, const OptTensor &workspace,
                                  const c10::optional<int64_t> &stream, const OptTensor &out) {
-        return project(x, Wx, bias, n_heads, workspace, stream, out);
+        return unlocked([&] { return project(x, Wx, bias, n_heads, workspace, stream, out); });
     });
     m.def("input_projection_backward", [](const Tensor &x, const Tensor &Wx, const Tensor &du, int64_t n_heads, bool want_dx,
                                           bool want_dw, bool want_db, const OptTensor &workspace,
                                           const c10::optional<int64_t> &stream) {
-        ProjGrads r = project_backward(x, Wx, du, n_heads, want_dx, want_dw, want_db, workspace, stream);
+        ProjGrads r = unlocked([&] { return project_backward(x, Wx, du, n_heads, want_dx, want_dw, want_db, workspace, stream); });
         return py::make_tuple(object_of(r.dx), object_of(r.dW), object_of(r.db));
     });
-    m.def("release_workspaces", &release_workspaces);
+    m.def("release_workspaces", &release_workspaces, py::call_guard<py::gil_scoped_release>());
     m.def("rnn_apply", [](const CellPtr &c, const Tensor &params, const Tensor &u, const OptTensor &h0, double tol, int64_t max_iter) {
-        variable_list r = Recurrence::apply(params, u, h0, c, tol, max_iter);
+        variable_list r = unlocked([&] { return Recurrence::apply(params, u, h0, c, tol, max_iter); });
         return py::make_tuple(r[0], r[1]);
     });
     m.def("input_projection_apply", [](const Tensor &x, const Tensor &Wx, const OptTensor &bias, int64_t n_heads) {
-        return Projection::apply(x, Wx, bias, n_heads)[0];
+        return unlocked([&] { return Projection::apply(x, Wx, bias, n_heads)[0]; });
     });
     m.def("rnn_layer", [](const CellPtr &c, const Tensor &x, const Tensor &Wx, const OptTensor &bias, const Tensor &params,
                           const OptTensor &h0, int64_t n_heads, double tol, int64_t max_iter) {
-        variable_list r = Layer::apply(x, Wx, bias, params, h0, c, n_heads, tol, max_iter);
+        variable_list r = unlocked([&] { return Layer::apply(x, Wx, bias, params, h0, c, n_heads, tol, max_iter); });
         return py::make_tuple(r[0], r[1]);
     });
 }
