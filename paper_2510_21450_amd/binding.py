@@ -245,7 +245,8 @@ def set_workspace_reuse(enable: bool = False) -> None:
 
 def release_workspaces() -> int:
     """Give the workspaces that `forward`, `backward` and the autograd functions keep between calls (at most 16 and a
-    thirty-second of the memory per device) back to torch's allocator; returns their bytes."""
+    thirty-second of the memory per device) back to torch's allocator; returns their bytes.  The allocator gets them back by
+    itself before it takes more memory from the device."""
     return _host.release_workspaces()
 
 

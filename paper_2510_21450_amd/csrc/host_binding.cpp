@@ -3,6 +3,7 @@
 // device about 10 us; checks, allocations and ctypes marshalling in Python took 15 us of host time on top of the call.
 // No arithmetic here, and no device code: everything runs in the kernels behind pararnn.h.
 #include <ATen/ATen.h>
+#include <c10/hip/HIPCachingAllocator.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/custom_function.h>
 #include <torch/csrc/utils/pybind.h>
@@ -105,8 +106,9 @@ struct Dims { int B, L, H; };
 // the workspaces of the diagonal cells' calls are kept between calls, per device, stream and problem, under the library's
 // per-workspace promise.  A call takes one out while it enqueues its work, and the next one that gets it is behind it in
 // the same stream; calls of several threads find different ones.  Bounds per device: kMost workspaces and a thirty-second of
-// its memory, the least recently used go first.  Under stream capture, with a workspace or a stream of the caller's, for
-// small problems (0.5 us of host time to look would show there) and for kernels without records nothing is kept.
+// its memory, the least recently used go first, and all of them when torch's allocator runs short (GiveBack).  Under stream
+// capture, with a workspace or a stream of the caller's, for small problems (0.5 us of host time to look would show there)
+// and for kernels without records nothing is kept.
 using WsKey = std::array<int64_t, 8>;
 constexpr size_t kMost = 16;
 constexpr double kSmall = 1 << 20;       // timestep-channels; below, most calls take kernels without records and 10-20 us
@@ -203,25 +205,59 @@ private:
     bool kept_ = false;
 };
 
-int64_t release_workspaces()
+// Gives up what is kept on the current device; returns its bytes.
+int64_t release_on_device(int device)
 {
-    std::map<int, std::vector<KeptWs>> all;
+    std::vector<KeptWs> old;
     int64_t bytes = 0;
     {
         std::lock_guard<std::mutex> lock(pool_mutex());
-        for (auto &p : pools()) {
-            bytes += (int64_t)p.second.bytes;
-            p.second.bytes = 0;
-            all[p.first].swap(p.second.free);
-        }
+        const auto p = pools().find(device);
+        if (p == pools().end()) return 0;
+        bytes = (int64_t)p->second.bytes;
+        p->second.bytes = 0;
+        old.swap(p->second.free);
     }
-    for (auto &d : all) {
-        if (d.second.empty()) continue;
-        const c10::DeviceGuard guard(d.second.front().ws.device());
-        for (KeptWs &k : d.second) give_up(k.ws);
+    for (KeptWs &k : old) give_up(k.ws);
+    return bytes;
+}
+
+int64_t release_workspaces()
+{
+    std::vector<int> devices;
+    {
+        std::lock_guard<std::mutex> lock(pool_mutex());
+        for (auto &p : pools()) devices.push_back(p.first);
+    }
+    int64_t bytes = 0;
+    for (int d : devices) {
+        const c10::DeviceGuard guard(c10::Device(c10::DeviceType::CUDA, (c10::DeviceIndex)d));
+        bytes += release_on_device(d);
     }
     return bytes;
 }
+
+// torch's allocator asks before it takes more memory from the device, and so before an allocation fails; it does not say
+// how much it needs.  While seven eighths of what it may have are free it gets nothing (a program that has yet to
+// allocate its tensors would lose what is kept again and again), below that everything kept on the device it allocates
+// on: the current one, and no other, whose allocator may be locked by a thread that waits for this one.  That allocator's
+// lock is held here and taken again by what is freed, which it allows; the pool's own lock is never held while memory is
+// allocated or freed.
+struct GiveBack : c10::FreeMemoryCallback {
+    bool Execute() override
+    {
+        int device = -1;
+        size_t avail = 0, total = 0;
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(c10::hip::getCurrentHIPStream().stream(), &cap) != hipSuccess || cap != hipStreamCaptureStatusNone)
+            return false;
+        if (hipGetDevice(&device) != hipSuccess || hipMemGetInfo(&avail, &total) != hipSuccess) return false;
+        namespace alloc = c10::hip::HIPCachingAllocator;
+        const double most = 0.125 * (double)total, mine = (double)alloc::getDeviceStats(device).reserved_bytes[0].current;
+        if ((double)(total - avail) < most && mine < most * alloc::getMemoryFraction(device)) return false;
+        return release_on_device(device) > 0;
+    }
+};
 
 Dims dims4(const Tensor &u, const char *name)
 {
@@ -461,6 +497,10 @@ template <class F> auto unlocked(F &&f)
 py::object object_of(const Tensor &t) { return t.defined() ? py::cast(t) : py::none(); }
 
 }  // namespace
+
+namespace c10 {
+C10_REGISTER_CLASS(FreeHipMemoryCallbacksRegistry, pararnn_kept_workspaces, GiveBack)
+}
 
 PYBIND11_MODULE(_host, m)
 {

@@ -111,3 +111,23 @@ def test_a_captured_call_keeps_nothing():
         graph.replay()
         torch.cuda.synchronize()
         assert same(got, want[0]) and same(eager, want[1]), rep
+
+
+def test_kept_workspaces_go_back_before_an_allocation_fails():
+    import paper_2510_21450_amd as P
+    P.release_workspaces()
+    torch.cuda.empty_cache()
+    p = problem("gru_diag", torch.float32, 8, 4000, 512, 1)
+    want = run(P, "gru_diag", p, False)
+    again = run(P, "gru_diag", p, False)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()                         # what is left of the allocator's memory is in use, or kept
+    kept = max(P.workspace_bytes("gru_diag", torch.float32, 8, 4000, 512, b) for b in (False, True))
+    total = torch.cuda.get_device_properties(0).total_memory
+    try:
+        torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + kept // 2) / total)
+        more = torch.empty(kept, dtype=torch.uint8, device="cuda")
+        assert P.release_workspaces() == 0 and more.numel() == kept
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert same(again, want) and same(run(P, "gru_diag", p, False), want)
