@@ -223,6 +223,15 @@ int pararnn_workspace_keep(void *workspace, int enable);
  * (the last call kept no carry records there, failed, was captured into a graph, or there was no promise). */
 int pararnn_workspace_known(const void *workspace);
 
+/* A kept workspace in two parts, for callers that keep many: only its front (control block and carry records) can be made
+ * use of again.  pararnn_workspace_parts returns the bytes of the front for pararnn_forward (backward = 0; n_iters > 0:
+ * with tol < 0 and max_iter = n_iters) or pararnn_backward (backward = 1) and writes to *rest_bytes what a call needs
+ * besides; 0 on invalid arguments and for the dense cell, whose workspaces hold nothing of the kind.
+ * pararnn_workspace_rest names the memory (256-byte aligned, device) that the next call which is handed the front as its
+ * workspace takes for the rest; the name is used up by that call.  INVALID_ARG without a promise for the front. */
+size_t pararnn_workspace_parts(int cell, int dtype, int B, int L, int H, int backward, int n_iters, size_t *rest_bytes);
+int pararnn_workspace_rest(void *workspace, void *rest, size_t rest_bytes);
+
 /* The blocks of Newton iterations pararnn_forward runs for a solve with these
  * settings when the workspace is of the size pararnn_workspace_bytes reports
  * (host only, no device work): writes the number of iterations of each block to

@@ -309,6 +309,27 @@ inline size_t diag_workspace_bytes(const CellInfo &ci, int dtype, int B, int L, 
     return need;
 }
 
+// The front of such a workspace that a call with the same layout can make use of again (control block, carry records);
+// n_iters > 0: of a fixed-count solve.  *rest: what the call needs behind it, which nothing reads afterwards.
+inline size_t diag_workspace_parts(const CellInfo &ci, int dtype, int B, int L, int H, bool backward, int n_iters, size_t *rest)
+{
+    const SolveOpts s = default_opts();
+    const int slots = backward || !s.fused_enabled ? 0 : n_iters > 0 ? (n_iters <= kMaxFused ? n_iters : 0) : s.fused_head;
+    size_t front = 0;
+    *rest = 0;
+    for (int al = 1; al <= 4; al *= 2) {
+        for (int fused = 0; fused <= (slots > 0 ? 1 : 0); ++fused) {
+            const Layout lo = make_layout(ci, dtype, B, L, H, backward, al, fused != 0, fused ? slots : 1);
+            if (lo.off_bnd > front) front = lo.off_bnd;
+            if (lo.total - lo.off_bnd > *rest) *rest = lo.total - lo.off_bnd;
+        }
+    }
+    ShortShape sh;
+    if (!backward && short_shape(ci, dtype, B, L, H, false, n_iters > 0, &sh) && short_workspace_bytes(sh) > front)
+        front = short_workspace_bytes(sh);
+    return front;
+}
+
 // Workspace size of a fixed-count solve of n_iters iterations in one launch.
 inline size_t diag_workspace_bytes_fused(const CellInfo &ci, int dtype, int B, int L, int H, int n_iters)
 {
@@ -338,7 +359,8 @@ int forward_diag(const CellInfo &ci, int dtype, const Layout &lo, FwdArgs &a, hi
     const bool bf = dtype == PARARNN_BF16;
     const bool to_tol = a.tol >= 0.0f;
     hipError_t e;
-    a.hit = bf ? reinterpret_cast<float *>(ws + lo.off_iter) : static_cast<float *>(h);
+    // the fp32 iterate lies behind the boundary rows
+    a.hit = bf ? reinterpret_cast<float *>(reinterpret_cast<char *>(a.bnd) + (lo.off_iter - lo.off_bnd)) : static_cast<float *>(h);
     const int slots = n_fused > 0 ? n_fused : 1;
     bool fill = true;
     if (max_iter <= kMaxIterWithReuse) a.g.epoch_base = workspace_epoch(ws, layout_signature(0, ci, dtype, lo, slots), st, &fill);
@@ -477,17 +499,23 @@ int forward_solve(const CellInfo &ci, int dtype, const float *params, const void
     if (alp < al) al = alp;
     // Fused launches need one carry-record slot per iteration they run; they are used when the
     // workspace holds those.
-    Layout lo = make_layout(ci, dtype, B, L, H, false, al);
-    int n_fused = 0;
-    const int want = fused_slots_wanted(tol, max_iter, opts);
-    if (want > 0) {
-        const Layout lf = make_layout(ci, dtype, B, L, H, false, al, true, want);
-        if (workspace_bytes >= (tol < 0.0f ? lf.off_bnd : lf.total)) {
-            lo = lf;
-            n_fused = want;
-        }
+    Layout lo = make_layout(ci, dtype, B, L, H, false, al), lf;
+    int n_fused = fused_slots_wanted(tol, max_iter, opts);
+    size_t need = lo.total;
+    if (n_fused > 0) {
+        lf = make_layout(ci, dtype, B, L, H, false, al, true, n_fused);
+        need = tol < 0.0f ? lf.off_bnd : lf.total;
     }
-    if (n_fused == 0 && workspace_bytes < lo.total) return PARARNN_WORKSPACE_TOO_SMALL;
+    WorkspaceRest rest = {nullptr, 0};
+    if (workspace_bytes < need) {
+        rest = workspace_rest(workspace);
+        auto fits = [&](const Layout &l, size_t whole) {
+            return rest.ptr ? workspace_bytes >= l.off_bnd && rest.bytes >= whole - l.off_bnd : workspace_bytes >= whole;
+        };
+        if (n_fused > 0 && !fits(lf, need)) n_fused = 0;
+        if (n_fused == 0 && !fits(lo, lo.total)) return PARARNN_WORKSPACE_TOO_SMALL;
+    }
+    if (n_fused > 0) lo = lf;
     ShortShape sh;
     if (opts.fused_enabled && opts.fused_head > 0 && max_iter > 0 && !delta_trace && settings().tile[0] <= 0 &&
         short_shape(ci, dtype, B, L, H, false, tol < 0.0f, &sh) && workspace_bytes >= short_workspace_bytes(sh))
@@ -497,7 +525,7 @@ int forward_solve(const CellInfo &ci, int dtype, const float *params, const void
     memset(&a, 0, sizeof(a));
     a.g = lo.g;
     a.params = params; a.u = u; a.h0 = h0; a.jac = nullptr;
-    a.bnd = reinterpret_cast<float *>(ws + lo.off_bnd);
+    a.bnd = reinterpret_cast<float *>(rest.ptr ? rest.ptr : ws + lo.off_bnd);
     a.rec = reinterpret_cast<unsigned long long *>(ws + lo.off_rec);
     a.ctrl = reinterpret_cast<Ctrl *>(ws);
     a.iters_out = iters; a.trace = delta_trace;
@@ -554,14 +582,17 @@ int backward_pass(const CellInfo &ci, int dtype, const float *params, const void
     const int alp = align_elems(4, {params, dL_dparams});
     if (alp < al) al = alp;
     const Layout lo = make_layout(ci, dtype, B, L, H, true, al);
-    if (workspace_bytes < lo.total) return PARARNN_WORKSPACE_TOO_SMALL;
+    const WorkspaceRest rest = workspace_bytes < lo.total ? workspace_rest(workspace) : WorkspaceRest{nullptr, 0};
+    if (workspace_bytes < lo.total && !(rest.ptr && workspace_bytes >= lo.off_bnd && rest.bytes >= lo.total - lo.off_bnd))
+        return PARARNN_WORKSPACE_TOO_SMALL;
+    char *part = rest.ptr ? rest.ptr + (lo.off_part - lo.off_bnd) : static_cast<char *>(workspace) + lo.off_part;
     ShortShape sh;
     if (settings().tile[0] <= 0 && short_shape(ci, dtype, B, L, H, true, false, &sh)) {
         ShortArgs a;
         memset(&a, 0, sizeof(a));
         a.B = B; a.L = L; a.H = H; a.n_cg = sh.n_cg; a.lps_log2 = sh.lps_log2; a.n_items = sh.n_items;
         a.params = params; a.u = u; a.h0 = h0; a.hs = h; a.gl = dL_dh; a.du = dL_du; a.dh0 = dL_dh0;
-        a.part = B > 1 ? static_cast<float *>(workspace) : dL_dparams;   // a single sequence's sums are the gradient
+        a.part = B > 1 ? reinterpret_cast<float *>(part) : dL_dparams;   // a single sequence's sums are the gradient
         workspace_forget(workspace);
         hipError_t e = dtype == PARARNN_BF16 ? Kernels<Cell, unsigned short>::backward_short(sh.c, sh.w, a, st)
                                              : Kernels<Cell, float>::backward_short(sh.c, sh.w, a, st);
@@ -574,7 +605,7 @@ int backward_pass(const CellInfo &ci, int dtype, const float *params, const void
     a.g = lo.g;
     a.params = params; a.u = u; a.h0 = h0; a.h = h; a.gl = dL_dh; a.jac = nullptr;
     a.du = dL_du; a.dh0 = dL_dh0;
-    a.part = reinterpret_cast<float *>(ws + lo.off_part);
+    a.part = reinterpret_cast<float *>(part);
     a.rec = reinterpret_cast<unsigned long long *>(ws + lo.off_rec);
     a.ctrl = reinterpret_cast<Ctrl *>(ws);
     // rows that the kernel may copy straight into LDS, 16 bytes per lane: bf16 rows that start on 16-byte

@@ -63,6 +63,9 @@ unsigned int workspace_epoch(void *workspace, unsigned long long layout_sig, hip
 // A number no other call of this process has, and no other memory by more than chance (64 random bits to start from).
 unsigned long long call_nonce();
 bool stream_is_capturing(hipStream_t st);
+// Memory of its own for the regions behind the carry records (pararnn_workspace_rest), for the call that asks first; else {NULL, 0}.
+struct WorkspaceRest { char *ptr; size_t bytes; };
+WorkspaceRest workspace_rest(void *workspace);
 // The library no longer knows what this workspace holds (a call on it failed, or ran without a signature).
 void workspace_forget(void *workspace);
 

@@ -39,6 +39,7 @@
  *     int    name_gates(void), name_state(void), name_param_rows(void);
  *     size_t name_workspace_bytes(int dtype, int B, int L, int H, int backward);
  *     size_t name_workspace_bytes_fused(int dtype, int B, int L, int H, int n_iters);
+ *     size_t name_workspace_parts(int dtype, int B, int L, int H, int backward, int n_iters, size_t *rest_bytes);
  *     int    name_forward(int dtype, params, u, h0, B, L, H, tol, max_iter, h, iters, delta_trace,
  *                         workspace, workspace_bytes, hip_stream);
  *     int    name_backward(int dtype, params, u, h0, h, dL_dh, B, L, H, dL_du, dL_dparams, dL_dh0,
@@ -116,6 +117,12 @@ template <class Impl> struct UserCell {
         const pararnn::CellInfo ci = {Impl::G, Impl::S, Impl::P, -1};                                             \
         if ((dtype != PARARNN_F32 && dtype != PARARNN_BF16) || !pararnn::dims_ok(B, L, H)) return 0;              \
         return pararnn::diag_workspace_bytes_fused(ci, dtype, B, L, H, n_iters);                                  \
+    }                                                                                                             \
+    size_t name##_workspace_parts(int dtype, int B, int L, int H, int backward, int n_iters, size_t *rest_bytes)  \
+    {                                                                                                             \
+        const pararnn::CellInfo ci = {Impl::G, Impl::S, Impl::P, -1};                                             \
+        if ((dtype != PARARNN_F32 && dtype != PARARNN_BF16) || !pararnn::dims_ok(B, L, H) || !rest_bytes) return 0;  \
+        return pararnn::diag_workspace_parts(ci, dtype, B, L, H, backward != 0, n_iters, rest_bytes);             \
     }                                                                                                             \
     int name##_forward(int dtype, const float *params, const void *u, const void *h0, int B, int L, int H,        \
                        float tol, int max_iter, void *h, int *iters, float *delta_trace, void *workspace,         \

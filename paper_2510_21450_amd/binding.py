@@ -108,8 +108,9 @@ class UserCell:
         self.ws.restype = self.ws_fused.restype = _sz
         self.ws.argtypes = self.ws_fused.argtypes = [_i] * 5
         address = lambda s: ctypes.cast(f(s), _vp).value
+        parts = address("workspace_parts") if hasattr(lib, f"{name}_workspace_parts") else 0
         self.host = _host.library_cell(name, self.G, self.S, address("workspace_bytes"), address("workspace_bytes_fused"),
-                                       address("forward"), address("backward"))
+                                       address("forward"), address("backward"), parts)
         self.res = f("residual_norm")
         self.res.restype, self.res.argtypes = _i, _RES_ARGS
 
@@ -244,7 +245,7 @@ def set_workspace_reuse(enable: bool = False) -> None:
 
 
 def release_workspaces() -> int:
-    """Give the workspaces that `forward`, `backward` and the autograd functions keep between calls (at most 16 and a
+    """Give what `forward`, `backward` and the autograd functions keep of their workspaces between calls (at most 16 and a
     thirty-second of the memory per device) back to torch's allocator; returns their bytes.  The allocator gets them back by
     itself before it takes more memory from the device."""
     return _host.release_workspaces()

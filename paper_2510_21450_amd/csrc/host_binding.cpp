@@ -32,9 +32,11 @@ struct Cell : torch::CustomClassHolder {
                         void *, size_t, void *);
     using Bwd = int (*)(int, const float *, const void *, const void *, const void *, const void *, int, int, int, void *,
                         float *, void *, void *, size_t, void *);
+    using Parts = size_t (*)(int, int, int, int, int, int, size_t *);
     int number = -1, G = 0, S = 0;
     std::string what;
     Ws ws_fn = nullptr, ws_fused_fn = nullptr;
+    Parts parts_fn = nullptr;      // not in a library built before there was one
     Fwd fwd_fn = nullptr;
     Bwd bwd_fn = nullptr;
 
@@ -45,6 +47,11 @@ struct Cell : torch::CustomClassHolder {
     size_t ws_fused(int dt, int B, int L, int H, int n) const
     {
         return number >= 0 ? pararnn_workspace_bytes_fused(number, dt, B, L, H, n) : ws_fused_fn(dt, B, L, H, n);
+    }
+    size_t parts(int dt, int B, int L, int H, int back, int n, size_t *rest) const
+    {
+        if (number >= 0) return pararnn_workspace_parts(number, dt, B, L, H, back, n, rest);
+        return parts_fn ? parts_fn(dt, B, L, H, back, n, rest) : 0;
     }
 };
 using CellPtr = c10::intrusive_ptr<Cell>;
@@ -103,10 +110,12 @@ struct Dims { int B, L, H; };
 // ------------------------------------------------------------------ kept workspaces
 // The carry records of a solve or a backward pass have to be cleared unless the library knows what they hold: 1.3 GB for
 // 2^30 timestep-channels (0.25 ms of a forward solve, 0.05 of a backward pass and, in small passes, a launch of 5 us).  So
-// the workspaces of the diagonal cells' calls are kept between calls, per device, stream and problem, under the library's
-// per-workspace promise.  A call takes one out while it enqueues its work, and the next one that gets it is behind it in
-// the same stream; calls of several threads find different ones.  Bounds per device: kMost workspaces and a thirty-second of
-// its memory, the least recently used go first, and all of them when torch's allocator runs short (GiveBack).  Under stream
+// the fronts of the workspaces (control block and records) of the diagonal cells' calls are kept between calls, per device,
+// stream and problem, under the library's per-workspace promise; what nothing reads after the call (boundary rows, the fp32
+// iterate of bf16 storage, sums of parameter gradients: three quarters of a bf16 solve's workspace) is allocated for each
+// call as before.  A call takes a front out while it enqueues its work, and the next one that gets it is behind it in the
+// same stream; calls of several threads find different ones.  Bounds per device: kMost fronts and a thirty-second of its
+// memory, the least recently used go first, and all of them when torch's allocator runs short (GiveBack).  Under stream
 // capture, with a workspace or a stream of the caller's, for small problems (0.5 us of host time to look would show there)
 // and for kernels without records nothing is kept.
 using WsKey = std::array<int64_t, 8>;
@@ -137,39 +146,19 @@ void give_up(Tensor &ws)
 
 class Workspace {
 public:
-    Workspace(const Cell &c, bool back, int code, const Dims &d, int64_t fixed, size_t bytes, const Tensor &like,
+    // n_iters: of a fixed-count solve, else 0; bytes: of a whole workspace
+    Workspace(const Cell &c, bool back, int code, const Dims &d, int64_t n_iters, size_t bytes, const Tensor &like,
               const OptTensor &given, const c10::optional<int64_t> &stream)
     {
-        if (has(given) || stream || (double)d.B * d.L * d.H < kSmall) { ws_ = workspace_of(bytes, like, given); return; }
-        const auto cur = c10::hip::getCurrentHIPStream();
-        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-        if (cur.device_index() != like.get_device() || hipStreamIsCapturing(cur.stream(), &cap) != hipSuccess ||
-            cap != hipStreamCaptureStatusNone) {
-            ws_ = workspace_of(bytes, like, given);
-            return;
+        size_t rest = 0;
+        const size_t front = has(given) || stream ? 0 : look(c, back, code, d, n_iters, like, &rest);
+        if (device_ < 0) { ws_ = workspace_of(bytes, like, given); return; }
+        if (!kept_) {
+            ws_ = workspace_of(front, like, {});
+            kept_ = pararnn_workspace_keep(ws_.data_ptr(), 1) == PARARNN_OK;
         }
-        device_ = cur.device_index();
-        key_ = {reinterpret_cast<int64_t>(cur.stream()), c.number >= 0 ? c.number : reinterpret_cast<int64_t>(c.fwd_fn),
-                back ? -1 : fixed, code, d.B, d.L, d.H, (int64_t)bytes};
-        {
-            std::lock_guard<std::mutex> lock(pool_mutex());
-            DevicePool &p = pools()[device_];
-            for (size_t i = p.free.size(); i-- > 0;)
-                if (p.free[i].key == key_) {
-                    ws_ = std::move(p.free[i].ws);
-                    p.free.erase(p.free.begin() + (long)i);
-                    p.bytes -= bytes;
-                    kept_ = true;
-                    return;
-                }
-            if (p.cap == 0) {
-                size_t avail = 0, total = 0;
-                p.cap = hipMemGetInfo(&avail, &total) == hipSuccess ? total / 32 : 1;
-            }
-            if (bytes > p.cap) device_ = -1;
-        }
-        ws_ = workspace_of(bytes, like, given);
-        kept_ = device_ >= 0 && pararnn_workspace_keep(ws_.data_ptr(), 1) == PARARNN_OK;
+        rest_ = workspace_of(rest, like, {});
+        pararnn_workspace_rest(ws_.data_ptr(), rest_.data_ptr(), (size_t)rest_.numel());
     }
     Workspace(const Workspace &) = delete;
     Workspace &operator=(const Workspace &) = delete;
@@ -199,7 +188,39 @@ public:
     }
 
 private:
-    Tensor ws_;
+    // Whether this call's front is one to keep (device_), and a kept one if there is one (ws_, kept_).  Returns its size.
+    size_t look(const Cell &c, bool back, int code, const Dims &d, int64_t n_iters, const Tensor &like, size_t *rest)
+    {
+        if ((double)d.B * d.L * d.H < kSmall) return 0;
+        const auto cur = c10::hip::getCurrentHIPStream();
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (cur.device_index() != like.get_device() || hipStreamIsCapturing(cur.stream(), &cap) != hipSuccess ||
+            cap != hipStreamCaptureStatusNone)
+            return 0;
+        const size_t front = c.parts(code, d.B, d.L, d.H, back, (int)n_iters, rest);
+        if (front == 0) return 0;
+        key_ = {reinterpret_cast<int64_t>(cur.stream()), c.number >= 0 ? c.number : reinterpret_cast<int64_t>(c.fwd_fn),
+                back ? -1 : n_iters, code, d.B, d.L, d.H, (int64_t)front};
+        std::lock_guard<std::mutex> lock(pool_mutex());
+        DevicePool &p = pools()[cur.device_index()];
+        if (p.cap == 0) {
+            size_t avail = 0, total = 0;
+            p.cap = hipMemGetInfo(&avail, &total) == hipSuccess ? total / 32 : 1;
+        }
+        if (front > p.cap) return 0;
+        device_ = cur.device_index();
+        for (size_t i = p.free.size(); i-- > 0;)
+            if (p.free[i].key == key_) {
+                ws_ = std::move(p.free[i].ws);
+                p.free.erase(p.free.begin() + (long)i);
+                p.bytes -= (size_t)ws_.numel();
+                kept_ = true;
+                break;
+            }
+        return front;
+    }
+
+    Tensor ws_, rest_;
     WsKey key_{};
     int device_ = -1;
     bool kept_ = false;
@@ -513,7 +534,7 @@ PYBIND11_MODULE(_host, m)
         c->what = std::move(what);
         return c;
     });
-    m.def("library_cell", [](std::string what, int G, int S, size_t ws, size_t ws_fused, size_t fwd, size_t bwd) {
+    m.def("library_cell", [](std::string what, int G, int S, size_t ws, size_t ws_fused, size_t fwd, size_t bwd, size_t parts) {
         auto c = c10::make_intrusive<Cell>();
         c->G = G;
         c->S = S;
@@ -522,8 +543,9 @@ PYBIND11_MODULE(_host, m)
         c->ws_fused_fn = reinterpret_cast<Cell::Ws>(ws_fused);
         c->fwd_fn = reinterpret_cast<Cell::Fwd>(fwd);
         c->bwd_fn = reinterpret_cast<Cell::Bwd>(bwd);
+        c->parts_fn = reinterpret_cast<Cell::Parts>(parts);
         return c;
-    });
+    }, py::arg("what"), py::arg("G"), py::arg("S"), py::arg("ws"), py::arg("ws_fused"), py::arg("fwd"), py::arg("bwd"), py::arg("parts") = 0);
     m.def("forward", [](const CellPtr &c, const Tensor &params, const Tensor &u, const OptTensor &h0, double tol, int64_t max_iter,
                         bool trace, const OptTensor &workspace, const c10::optional<int64_t> &stream, const OptTensor &out) {
         Solve s = unlocked([&] { return solve(*c, params, u, h0, tol, max_iter, trace, workspace, stream, out); });

@@ -4,6 +4,7 @@
 #include <mutex>
 #include <random>
 #include <unordered_map>
+#include <utility>
 
 #include "dense.h"
 #include "cells.h"
@@ -26,6 +27,7 @@ struct WorkspaceNote {
     unsigned long long sig;    // layout signature of the last call that used the workspace
     unsigned int number;       // that call's number (1 .. 2^20 - 1)
     bool kept;                 // promised on its own (pararnn_workspace_keep)
+    WorkspaceRest rest;        // for the next call (pararnn_workspace_rest)
 };
 std::mutex g_ws_mutex;
 std::unordered_map<unsigned long long, WorkspaceNote> g_ws_notes;      // by device and address
@@ -42,7 +44,7 @@ void forget_locked(unsigned long long key)
 {
     const auto it = g_ws_notes.find(key);
     if (it == g_ws_notes.end()) return;
-    if (it->second.kept) it->second.sig = 0;
+    if (it->second.kept) it->second = {0, 0, true, {nullptr, 0}};
     else g_ws_notes.erase(it);
 }
 }  // namespace
@@ -73,6 +75,7 @@ unsigned int workspace_epoch(void *workspace, unsigned long long layout_sig, hip
         return 0u;
     }
     WorkspaceNote &n = g_ws_notes[key];                // a new note has sig 0, which no call has
+    n.rest = {nullptr, 0};
     if (n.sig == layout_sig && n.number >= 1u && n.number < (1u << 20) - 1u) {
         ++n.number;
         *fill = false;
@@ -81,6 +84,16 @@ unsigned int workspace_epoch(void *workspace, unsigned long long layout_sig, hip
         n.number = 1u;
     }
     return n.number << 10;
+}
+
+WorkspaceRest workspace_rest(void *workspace)
+{
+    WorkspaceRest r = {nullptr, 0};
+    const unsigned long long key = ws_key(workspace);
+    std::lock_guard<std::mutex> lock(g_ws_mutex);
+    const auto it = g_ws_notes.find(key);
+    if (it != g_ws_notes.end()) std::swap(r, it->second.rest);
+    return r;
 }
 
 void workspace_forget(void *workspace)
@@ -207,6 +220,14 @@ size_t pararnn_workspace_bytes_fused(int cell, int dtype, int B, int L, int H, i
     return diag_workspace_bytes_fused(ci, dtype, B, L, H, n_iters);
 }
 
+size_t pararnn_workspace_parts(int cell, int dtype, int B, int L, int H, int backward, int n_iters, size_t *rest_bytes)
+{
+    CellInfo ci;
+    if (!cell_info(cell, &ci) || (dtype != PARARNN_F32 && dtype != PARARNN_BF16) || !dims_ok(B, L, H) || !rest_bytes) return 0;
+    if (cell == PARARNN_TANH_DENSE) return 0;
+    return diag_workspace_parts(ci, dtype, B, L, H, backward != 0, n_iters, rest_bytes);
+}
+
 int pararnn_set_spin_limit(unsigned int polls)
 {
     settings().spin_limit = polls ? polls : kSpinLimit;
@@ -249,8 +270,19 @@ int pararnn_workspace_keep(void *workspace, int enable)
     if (!workspace) return PARARNN_INVALID_ARG;
     const unsigned long long key = ws_key(workspace);
     std::lock_guard<std::mutex> lock(g_ws_mutex);
-    if (enable) g_ws_notes[key] = {0, 0, true};
+    if (enable) g_ws_notes[key] = {0, 0, true, {nullptr, 0}};
     else g_ws_notes.erase(key);
+    return PARARNN_OK;
+}
+
+int pararnn_workspace_rest(void *workspace, void *rest, size_t rest_bytes)
+{
+    if (!workspace || !rest || !aligned(rest, 256)) return PARARNN_INVALID_ARG;
+    const unsigned long long key = ws_key(workspace);
+    std::lock_guard<std::mutex> lock(g_ws_mutex);
+    const auto it = g_ws_notes.find(key);
+    if (it == g_ws_notes.end() || !it->second.kept) return PARARNN_INVALID_ARG;
+    it->second.rest = {static_cast<char *>(rest), rest_bytes};
     return PARARNN_OK;
 }
 

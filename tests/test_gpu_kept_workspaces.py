@@ -131,3 +131,16 @@ def test_kept_workspaces_go_back_before_an_allocation_fails():
     finally:
         torch.cuda.set_per_process_memory_fraction(1.0)
     assert same(again, want) and same(run(P, "gru_diag", p, False), want)
+
+
+def test_only_control_block_and_records_are_kept():
+    """Not the fp32 iterate of bf16 storage (4 bytes per state value), nor the sums of parameter gradients."""
+    import paper_2510_21450_amd as P
+    cell, B, L, H = "gru_diag", 2, 9000, 512
+    P.release_workspaces()
+    p = problem(cell, torch.bfloat16, B, L, H, 3)
+    want = run(P, cell, p, True)
+    for rep in range(2):
+        assert same(run(P, cell, p, False), want), rep
+    records = 3 * 8 * B * -(-H // 64) * 64 * (5 * -(-L // 96) + -(-L // 64))        # A, b, inclusive value; 5 + 1 sets
+    assert 0 < P.release_workspaces() <= records + 4096

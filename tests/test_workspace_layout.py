@@ -80,3 +80,19 @@ def test_two_segment_bf16_tile_at_config_5_geometry(probe):
     r = probe(3, 1, 6, 1, 4, 65536, 4096, False, (1, 2, 12, 4), 5)
     assert (r["n_groups"], r["n_lt"], r["CW"], r["T"]) == (512, 683, 32, 96)
     assert r["n_rec"] == 512 * 683 * 3 * 32 and r["n_rec"] * 5 * 8 == 1342832640
+
+
+@pytest.mark.parametrize("cell,dtype,B,L,H", [(0, 0, 16, 4096, 1024), (0, 1, 4, 65536, 4096), (1, 1, 8, 2048, 2048), (4, 0, 3, 50, 7)])
+@pytest.mark.parametrize("back,n", [(0, 0), (0, 3), (0, 9), (1, 0)])
+def test_the_two_parts_make_up_a_workspace(cell, dtype, B, L, H, back, n):
+    import ctypes
+    lib = ctypes.CDLL(os.path.join(PKG, "libpararnn.so"))
+    lib.pararnn_workspace_parts.restype = lib.pararnn_workspace_bytes.restype = lib.pararnn_workspace_bytes_fused.restype = ctypes.c_size_t
+    rest = ctypes.c_size_t(0)
+    front = lib.pararnn_workspace_parts(cell, dtype, B, L, H, back, n, ctypes.byref(rest))
+    whole = lib.pararnn_workspace_bytes_fused(cell, dtype, B, L, H, n) if n else lib.pararnn_workspace_bytes(cell, dtype, B, L, H, back)
+    assert front % 256 == 0 and front > 0 and rest.value % 256 == 0
+    assert front <= whole and (n > 0 or front + rest.value >= whole)
+    # the dense cell has none, and memory for the rest needs a promise for the front
+    assert lib.pararnn_workspace_parts(2, 0, 4, 100, 64, 0, 0, ctypes.byref(rest)) == 0
+    assert lib.pararnn_workspace_rest(ctypes.c_void_p(4096), ctypes.c_void_p(8192), ctypes.c_size_t(256)) == 2
