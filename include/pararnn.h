@@ -175,11 +175,13 @@ int pararnn_set_streaming(int mode);
  * iteration before the end of a launch, the returned h is the iterate at the
  * END of that launch -- the converged iterate refined by the Newton iterations
  * that were already in flight -- so it differs from the per-iteration path's h
- * by less than tol.  Problems that one workgroup per channel group solves in a
- * single launch (pararnn_set_fused(1), sizes chosen by the library) have no blocks:
- * each group of channels returns the iterate that met the tolerance within it.
- * 0 <= n_iters <= 8; 0 turns
- * it off; default 5.  Query workspace sizes after setting it (a workspace
+ * by less than tol.  With the default of 5, problems of sizes the library
+ * chooses have no blocks (unless pararnn_set_fused(0)): one workgroup per channel
+ * group solves them in a single launch, and each group of channels returns the
+ * iterate that met the tolerance within it, where channels that a group walks in
+ * several pieces along L may have merged the last updates that cross from one
+ * piece into the next, none larger than tol / 8.  0 <= n_iters <= 8; 0 turns it
+ * off; default 5.  Query workspace sizes after setting it (a workspace
  * that is too small for the record slots falls back to one launch per
  * iteration). */
 int pararnn_set_fused_head(int n_iters);
@@ -239,7 +241,9 @@ int pararnn_workspace_rest(void *workspace, void *rest, size_t rest_bytes);
  * capacity), or -1 on invalid arguments.  The sizes add up to max_iter.  The
  * stopping test is evaluated for every iteration and acted on between blocks.
  * The first block (two-state and larger cells: the first two) is a launch of its own; the following ones share one
- * launch (pararnn_set_fused_tail) or are launches of their own. */
+ * launch (pararnn_set_fused_tail) or are launches of their own.  Problems that the library solves without blocks
+ * (pararnn_set_fused_head; the plan does not know their sizes) are one launch in which every group of channels ends
+ * after its own number of iterations, at most max_iter. */
 int pararnn_solve_plan(float tol, int max_iter, int *block_sizes, int capacity);
 
 /*
@@ -286,7 +290,8 @@ int pararnn_forward(int cell, int dtype, const float *params, const void *u, con
  *                regime of three iterations (Sec. 2.1, App. A) is first_block = 3:
  *                the returned h is then the iterate of the third iteration when
  *                the tolerance is met there, and a solve that needs more goes on
- *                in further launches.
+ *                in further launches.  With 1..8 every problem runs the blocks of
+ *                pararnn_solve_plan_ex.
  *   fused        -1 the library's setting, 0 never run more than one iteration
  *                per launch (as pararnn_set_fused(0)), 1 allow it.
  * options = NULL means all defaults: the call is then pararnn_forward.  Fields

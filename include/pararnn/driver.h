@@ -40,11 +40,13 @@ Settings &settings();
 struct SolveOpts {
     int fused_enabled;     // launches that run several Newton iterations are allowed
     int fused_head;        // iterations in the first launch of a solve to a tolerance (0 = none)
+    bool blocks;           // the caller has chosen fused_head: a solve to a tolerance runs the blocks that follow from it
 };
+constexpr int kFusedHead = 5;      // the library's own choice
 inline SolveOpts default_opts()
 {
     const Settings &s = settings();
-    return {s.fused_enabled, s.fused_head};
+    return {s.fused_enabled, s.fused_head, s.fused_head != kFusedHead};
 }
 
 inline size_t round256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -517,7 +519,7 @@ int forward_solve(const CellInfo &ci, int dtype, const float *params, const void
     }
     if (n_fused > 0) lo = lf;
     ShortShape sh;
-    if (opts.fused_enabled && opts.fused_head > 0 && max_iter > 0 && !delta_trace && settings().tile[0] <= 0 &&
+    if (opts.fused_enabled && opts.fused_head > 0 && !(opts.blocks && tol >= 0.0f) && max_iter > 0 && !delta_trace && settings().tile[0] <= 0 &&
         short_shape(ci, dtype, B, L, H, false, tol < 0.0f, &sh) && workspace_bytes >= short_workspace_bytes(sh))
         return forward_short<Cell>(dtype, sh, params, u, h0, B, L, H, tol, max_iter, h, iters, workspace, st);
     char *ws = static_cast<char *>(workspace);

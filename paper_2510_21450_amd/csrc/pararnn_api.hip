@@ -17,7 +17,7 @@ namespace pararnn {
 
 Settings &settings()
 {
-    static Settings s = {1, 5, {-1, 0, 0, 0}, kSpinLimit, 1, 1, 0, 0};
+    static Settings s = {1, kFusedHead, {-1, 0, 0, 0}, kSpinLimit, 1, 1, 0, 0};
     return s;
 }
 
@@ -324,7 +324,10 @@ bool solve_opts(const pararnn_solve_options_t *o, SolveOpts *out)
     *out = default_opts();
     if (!o) return true;
     if (o->first_block < -1 || o->first_block > kMaxFused || o->fused < -1 || o->fused > 1) return false;
-    if (o->first_block >= 0) out->fused_head = o->first_block;
+    if (o->first_block >= 0) {
+        out->fused_head = o->first_block;
+        out->blocks = true;
+    }
     if (o->fused >= 0) out->fused_enabled = o->fused;
     return true;
 }

@@ -87,3 +87,26 @@ def test_short_solve_in_a_graph(oracle_mod):
         torch.cuda.synchronize()
         assert iters.cpu().tolist() == ei.cpu().tolist()
         assert torch.equal(torch.nan_to_num(h), torch.nan_to_num(eh))
+
+
+@pytest.mark.parametrize("cell", ["gru_diag", "lstm_diag"])
+@pytest.mark.parametrize("shape", [(2, 50, 40), (4, 700, 260)])       # one tile, several (two-state cells)
+def test_a_chosen_first_block_is_run_to_its_end(oracle_mod, cell, shape):
+    """A caller who asks for a first block of n iterations gets at least iterate n, also where the library would solve
+    the problem without blocks and stop each group of channels at the tolerance."""
+    import paper_2510_21450_amd as P
+    B, L, H = shape
+    params, u, h0, _ = problem(cell, B, L, H, seed=80)
+    pn, un, h0n = to_np(params), to_np(u), to_np(h0)
+    h1 = oracle_mod.newton(cell, pn, un, h0n, tol=-1.0, max_iter=1)[0]
+    h3 = oracle_mod.newton(cell, pn, un, h0n, tol=-1.0, max_iter=3)[0]
+    assert relerr(h1, h3) > 1e-3                            # the two can be told apart
+    tol = 100.0                                             # met in the first iteration
+    got = [P.forward_ex(cell, params, u, h0, tol=tol, max_iter=20, first_block=3)[:2]]
+    try:
+        P.set_fused_head(3)
+        got.append(P.forward(cell, params, u, h0, tol=tol, max_iter=20)[:2])
+    finally:
+        P.set_fused_head(5)
+    for h, iters in got:
+        assert iters.cpu().tolist() == [1, 0] and relerr(to_np(h), h3) <= 2e-5
