@@ -4,6 +4,7 @@
 // Used by the C ABI of the built-in cells and by libraries that add a cell of
 // their own (pararnn_cell.h).  No kernel code here.
 #pragma once
+#include <math.h>
 #include <stdint.h>
 #include <stdio.h>
 #include <stdlib.h>
@@ -258,6 +259,17 @@ inline size_t short_workspace_bytes(const ShortShape &sh)
     return round256(sizeof(Ctrl)) + round256((size_t)sh.n_items * 2 * sizeof(rec_t));
 }
 
+// Polls (half a microsecond at least) after which workgroup 0 gives up waiting for the verdicts.  It waits for all
+// workgroups of the solve, so beside the limit of one wait the work there is counts: the iterations of all tiles, as often as
+// the 256 compute units take workgroups in turn (one at a time is the least they hold), 10 us each at most.  A limit of
+// 2^21 polls, the default, covers 2^15 of them three times.
+inline unsigned int short_wait_limit(unsigned int limit, const ShortShape &sh, int max_iter)
+{
+    const double steps = (double)sh.n_tiles * max_iter * ((sh.n_items + 255) / 256);
+    const double polls = (double)limit * ceil(steps < 1.0 ? 1.0 : steps / 32768.0);
+    return polls < 4294967295.0 ? (unsigned int)polls : 0xffffffffu;
+}
+
 inline bool dims_ok(int B, int L, int H)
 {
     if (B < 1 || L < 1 || H < 1) return false;
@@ -475,7 +487,7 @@ int forward_short(int dtype, const ShortShape &sh, const float *params, const vo
     memset(&a, 0, sizeof(a));
     a.B = B; a.L = L; a.H = H; a.n_cg = sh.n_cg; a.lps_log2 = sh.lps_log2; a.n_items = sh.n_items; a.n_tiles = sh.n_tiles;
     a.params = params; a.u = u; a.h0 = h0; a.h = h; a.tol = tol; a.max_iter = max_iter; a.iters_out = iters;
-    a.spin_limit = settings().spin_limit;
+    a.spin_limit = short_wait_limit(settings().spin_limit, sh, max_iter);
     a.slots = reinterpret_cast<rec_t *>(ws + round256(sizeof(Ctrl)));
     a.nonce = call_nonce();
     workspace_forget(workspace);

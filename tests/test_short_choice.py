@@ -25,7 +25,8 @@ def choose(tmp_path_factory):
     assert r.returncode == 0, r.stderr[-2000:]
 
     def run(problems):
-        """problems: (cell, dtype, B, L, H, backward, fixed); per problem (c, lps_log2, w, workgroups, tiles) or None."""
+        """problems: (cell, dtype, B, L, H, backward, fixed); per problem (c, lps_log2, w, workgroups, tiles, polls)
+        or None."""
         text = "\n".join(" ".join(str(int(x)) for x in (*p[0], *p[1:])) for p in problems)
         out = subprocess.run([str(exe)], input=text, capture_output=True, text=True, check=True).stdout
         shapes = [tuple(int(x) for x in line.split()) for line in out.splitlines()]
@@ -45,8 +46,27 @@ def test_offsets_within_a_tile_fit_32_bits(choose):
             continue
         taken += 1
         (g, S, _, _), dt, _, L, H = p[:5]
-        c, lps, w, _, tiles = s
+        c, lps, w, _, tiles, _ = s
         T = c * (64 >> lps) * w
         assert tiles * T >= L
         assert (T + 1) * max(g, S) * H * (2 if dt == BF16 else 4) < 2 ** 31, (p, s)
     assert taken > 0
+
+
+def test_the_wait_for_the_verdicts_covers_the_work(choose):
+    """At half a microsecond per poll, three times what all the workgroups take at ten per tile and iteration with one
+    workgroup on each of 256 compute units; the plain limit where that is little."""
+    ps = [(c, F32, B, L, H, 0, fixed) for c in (GRU, LSTM, ROT) for B, L, H in ((1, 64, 8), (16, 64, 2048), (64, 200, 4096),
+                                                                              (8, 2048, 2048), (16, 30000, 1024))
+          for fixed in (0, 3, 1000, 100000)]
+    seen = set()
+    for p, s in zip(ps, choose(ps)):
+        if s is None:
+            continue
+        _, _, _, items, tiles, polls = s
+        us = 10.0 * tiles * (p[6] or 64) * -(-items // 256)
+        assert polls == 2 ** 32 - 1 or 0.5 * polls >= 3 * us, (p, s)
+        if us < 300e3:
+            assert polls == 2 ** 21, (p, s)
+        seen.add(polls == 2 ** 21)
+    assert seen == {True, False}
