@@ -483,7 +483,8 @@ int pararnn_set_dense_jacobian(int mode);
 /*
  * Launch structure of the dense path's forward solves where the linear systems are
  * solved by the chunked scan (host, process-wide, not thread-safe; default 1;
- * solves by forward substitution, most sizes, are two launches in every mode).
+ * solves by forward substitution, most sizes unless
+ * pararnn_set_dense_substitution(0), are two launches in every mode).
  * An iteration of the scan has four phases (residual; chunk products and
  * chunk-local sweeps; carry; final sweep).
  *   1  the first six iterations are enqueued as one launch per phase; whatever is
@@ -500,6 +501,14 @@ int pararnn_set_dense_jacobian(int mode);
  * PARARNN_INVALID_ARG.
  */
 int pararnn_set_dense_tail(int mode);
+
+/*
+ * Test / tuning hook (host, process-wide, not thread-safe; default 1): enable = 0
+ * makes the dense path solve every linear system, of forward solves and of
+ * pararnn_backward, by the chunked scan, also where forward substitution is
+ * faster (most sizes).  Results agree to fp32 rounding.
+ */
+int pararnn_set_dense_substitution(int enable);
 
 #ifdef __cplusplus
 }

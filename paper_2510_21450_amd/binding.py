@@ -163,6 +163,12 @@ def set_dense_tail(mode: int = 1) -> None:
     _raise(_lib.pararnn_set_dense_tail(int(mode)), "pararnn_set_dense_tail")
 
 
+def set_dense_substitution(enable: bool = True) -> None:
+    """pararnn_set_dense_substitution: solve linear systems by forward substitution where it is faster (default), or
+    always by the chunked scan."""
+    _raise(_lib.pararnn_set_dense_substitution(int(enable)), "pararnn_set_dense_substitution")
+
+
 def dense_chunk() -> int:
     return _lib.pararnn_dense_chunk()
 

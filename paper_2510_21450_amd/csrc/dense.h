@@ -30,6 +30,8 @@ int dense_set_jacobian(int mode);
 // Launch structure of forward solves: 1 launches per phase for the first iterations, one persistent launch for the
 // rest (default); 0 launches per phase throughout; 2 the persistent launch from the first iteration.
 int dense_set_one_launch(int mode);
+// Forward substitution where it is faster (default), or the chunked scan for every linear system.
+int dense_set_substitution(int enable);
 int dense_chunk_products(const float *W, const float *d, int B, int L, int H, float *A, void *ctrl_scratch,
                          hipStream_t st);
 

@@ -734,6 +734,7 @@ int g_dense_products = 0;
 int g_dense_jacobian = 0;       // 0: the full Jacobian (Newton), 1: its diagonal (quasi-Newton)
 int g_dense_one_launch = 1;     // 1: the first kDenseHead iterations as launches per phase, the rest in one persistent
                                 // launch; 0: launches per phase throughout; 2: the persistent launch from the start
+int g_dense_substitution = 1;   // 0: every linear system is solved by the chunked scan
 constexpr int kDenseHead = 6;
 
 
@@ -1398,6 +1399,7 @@ __global__ __launch_bounds__(320) void dense_adjoint_kernel(const DenseArgs a, f
 // them, backward beyond 650 steps of a single one.
 bool wavefront_pays(int B, int L, bool backward)
 {
+    if (!g_dense_substitution) return false;
     const double rows = (double)B * L;
     const double products = (rows * 3.94 > 67e3 ? rows * 3.94 : 67e3) + 17.0 * L + 27e3;
     const double rounds = (B + 511) / 512;              // two workgroups share a compute unit
@@ -1508,6 +1510,12 @@ int dense_set_one_launch(int mode)
 {
     if (mode < 0 || mode > 2) return PARARNN_INVALID_ARG;
     g_dense_one_launch = mode;
+    return PARARNN_OK;
+}
+
+int dense_set_substitution(int enable)
+{
+    g_dense_substitution = enable ? 1 : 0;
     return PARARNN_OK;
 }
 

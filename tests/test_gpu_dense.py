@@ -25,9 +25,18 @@ def f64(t):
     return None if t is None else t.detach().to("cpu", torch.float64).numpy()
 
 
+@pytest.fixture(params=["chosen", "scan"])
+def linear_solve(request):
+    """How the linear systems are solved: as the library chooses (substitution at these sizes), or by the chunked scan."""
+    import paper_2510_21450_amd as P
+    P.set_dense_substitution(request.param == "chosen")
+    yield request.param
+    P.set_dense_substitution(True)
+
+
 @pytest.mark.parametrize("shape", [(1, 1), (1, 16), (2, 17), (3, 50), (33, 100), (5, 257), (64, 32)])
 @pytest.mark.parametrize("with_h0", [False, True])
-def test_dense_small(oracle_mod, shape, with_h0):
+def test_dense_small(oracle_mod, linear_solve, shape, with_h0):
     import paper_2510_21450_amd as P
     B, L = shape
     H = 64
@@ -95,7 +104,7 @@ def test_dense_unsupported_shapes_are_refused():
         P.forward("tanh_dense", W, u, None)
 
 
-def test_config_c4_full_size(oracle_mod):
+def test_config_c4_full_size(oracle_mod, linear_solve):
     """Benchmark configuration 4: B=64, L=1024, H=64, max_iter 32, forward."""
     import paper_2510_21450_amd as P
     w = CONFIGS["C4"]
@@ -122,7 +131,7 @@ def test_config_c4_full_size(oracle_mod):
 
 @pytest.mark.parametrize("shape", [(1, 1), (1, 16), (2, 17), (3, 50), (33, 100), (5, 257), (64, 33)])
 @pytest.mark.parametrize("with_h0", [False, True])
-def test_dense_backward_small(oracle_mod, as_stored, shape, with_h0):
+def test_dense_backward_small(oracle_mod, as_stored, linear_solve, shape, with_h0):
     """Eq. (6) for the dense cell: the reverse scan with W^T on the matrix cores,
     dL/du, dL/dW and dL/dh0 against the oracle's reverse sweep, both at the oracle's states."""
     import paper_2510_21450_amd as P
@@ -146,7 +155,7 @@ def test_dense_backward_small(oracle_mod, as_stored, shape, with_h0):
     assert none is None and torch.equal(du, du2) and torch.equal(dW, dW2)
 
 
-def test_dense_backward_config_c4(oracle_mod, as_stored):
+def test_dense_backward_config_c4(oracle_mod, as_stored, linear_solve):
     """Backward at config 4's size (B=64, L=1024), compared on whole sequences
     (the oracle handles a subset of the batch; dL/dW is checked for that subset
     by running the library on it alone)."""
@@ -329,7 +338,7 @@ def test_dense_quasi_newton_config_c4(oracle_mod, jacobian_mode):
 
 
 @pytest.mark.parametrize("mode", [0, 1])
-def test_dense_iteration_control_edge_cases(oracle_mod, jacobian_mode, mode):
+def test_dense_iteration_control_edge_cases(oracle_mod, jacobian_mode, linear_solve, mode):
     """The dense cell under both Jacobian modes: max_iter = 0 gives the initial guess, tol = 0 runs
     to max_iter with NOT_CONVERGED, L = 1 needs one solve with a zero update, a NaN in the input
     ends the solve with NONFINITE after its first iteration: statuses and counts as the oracle's."""
@@ -365,8 +374,17 @@ def tail_mode():
     P.set_dense_tail(1)
 
 
+@pytest.fixture
+def scan_only():
+    """The chunked scan, whose launch plans these are, also at sizes that go by substitution otherwise."""
+    import paper_2510_21450_amd as P
+    P.set_dense_substitution(False)
+    yield
+    P.set_dense_substitution(True)
+
+
 @pytest.mark.parametrize("shape", [(3, 50), (33, 100), (5, 257)])
-def test_dense_launch_plans_agree(oracle_mod, tail_mode, shape):
+def test_dense_launch_plans_agree(oracle_mod, tail_mode, scan_only, shape):
     """The same solve as launches per phase throughout (0), as six iterations of launches per phase and
     one persistent launch for the rest (1, the default), and as one persistent launch from the start
     (2): bit-identical states, the same iteration count, status and trace -- for a solve to a tolerance,
@@ -407,7 +425,7 @@ def test_dense_launch_plans_agree(oracle_mod, tail_mode, shape):
     assert relerr(f64(h), oracle_mod.seq_unroll("tanh_dense", Wn, un, h0n)) <= 1e-5
 
 
-def test_dense_persistent_launch_gives_up_after_a_bounded_wait(tail_mode):
+def test_dense_persistent_launch_gives_up_after_a_bounded_wait(tail_mode, scan_only):
     """The grid-wide barriers of the persistent launch wait a bounded number of polls.  With the limit
     forced to one poll a workgroup that is not the last to arrive gives up: every workgroup still
     exits, the status says INTERNAL (or the solve went through), and the next call works."""
@@ -456,7 +474,7 @@ def test_dense_substitution_iterates(oracle_mod, shape):
 @pytest.mark.parametrize("shape", [(2, 2700), (1, 2560), (1, 700)])
 def test_dense_long_sequences(oracle_mod, tail_mode, as_stored, shape):
     """Few long sequences, on both sides of the line between substitution and chunk products: states,
-    counts and gradients against the oracle under every launch plan."""
+    counts and gradients against the oracle under every launch plan, which the sizes beyond the line go by."""
     import paper_2510_21450_amd as P
     B, L = shape
     H = 64
