@@ -191,72 +191,200 @@ inline Layout make_layout(const CellInfo &ci, int dtype, int B, int L, int H, bo
 }
 
 // Shape of the kernels of short_kernels.h for a problem: c steps per thread, 64 >> lps_log2 segments per wave, w waves;
-// n_items workgroups that walk their sequence in n_tiles tiles.  fixed: a solve of a fixed number of iterations.
-// False where the kernels with carry records do better.  Figures: us on MI355X, kernels with records / these.
+// n_items workgroups that walk their sequence in n_tiles tiles.
 struct ShortShape { int c, lps_log2, w, n_cg, n_items, n_tiles; };
-inline bool short_shape(const CellInfo &ci, int dtype, int B, int L, int H, bool backward, bool fixed, ShortShape *out)
+
+// What a forward solve takes with the kernels that have carry records and with these, in us.  With records the time follows
+// the number of timestep-channels, and tiles of one channel group wait for each other: few groups cost more per
+// timestep-channel.  Without, the workgroups of a solve go through the device in rounds, as many at a time as the kernel's
+// registers allow; a round is the whole sequence, tile by tile, and the time of a tile depends on how many waves share a
+// SIMD.  So just above a full round the solve takes up to twice as long (two-state cell, bf16, 16000 steps, best shapes:
+// 1024 channels 0.83 of the time with records, 1100 channels 1.16, 2048 0.82, 2100 1.10), and a shape is chosen that fills
+// its last one.
+// The constants are a least-squares fit to 1100 problems on MI355X, each with every shape and with records (scalar and 2x2
+// cells, fp32 and bf16, to a tolerance and with three fixed iterations, 200 to 50000 steps of 300 to 131072 channels): 5-6 %
+// root mean square of either side.  Of 1560 problems 4 take more than 3 % longer this way than with records (worst 7 %), of
+// 400 random ones the fit has not seen 3 (worst 13 %: a single fixed iteration); lines drawn by size had left 247 and 35 (worst
+// 2.2 times).  The mean time is 5 % lower, by shapes that fill their last round.
+struct ShortCost {
+    float step, step_gate;            // per million timestep-channels and iteration: a part, and one for each gate
+    float rec_more, rec_tol, rec_fixed;   // with records: iterations' worth of loads and stores; launches, to a tolerance and fixed
+    float rec_tile, rec_narrow;       // a tile of the sequence and iteration; log2 of how far the groups are from 512
+    float more, start;                // without: the same two
+    struct { float one, wave; } tile[2][2];   // [8, 16 steps][one tile, several]: of a tile, and for each wave on its SIMD
+    float piece[4];                   // rows in pieces of 4, 8, 16, 32 channels
+    float wide;                       // workgroups of more than four waves, for pieces of four channels (wider ones: less)
+    float uneven;                     // five to seven waves take the places of eight and less of the arithmetic
+    float last, drift[2], bf16, few;  // a last round after two; doubling of the tiles (fp32, bf16); bf16; few workgroups
+    float overlap[2];                 // each of up to four rounds, one tile and several: workgroups do not end at once
+};
+constexpr ShortCost kCostScalar = {0.0f, 0.263f, 3.14f, 27.7f, 20.7f, 0.0171f, 0.0637f, 3.56f, 5.59f,
+                                   {{{0.411f, 0.557f}, {0.595f, 0.504f}}, {{0.664f, 1.077f}, {0.716f, 1.184f}}},
+                                   {1.0f, 0.917f, 0.887f, 0.878f}, 0.272f, 0.705f, 0.799f, {0.0161f, 0.0066f}, 0.968f, 0.166f,
+                                   {0.0333f, 0.0215f}};
+constexpr ShortCost kCostBlock2 = {0.512f, 0.456f, 0.847f, 33.4f, 24.0f, 0.0196f, 0.0728f, 2.36f, 5.97f,
+                                   {{{0.299f, 0.448f}, {0.519f, 0.363f}}, {{0.623f, 0.764f}, {0.623f, 0.764f}}},
+                                   {1.0f, 0.918f, 0.879f, 0.846f}, 0.283f, 0.561f, 0.906f, {0.0144f, 0.0097f}, 0.981f, 0.140f,
+                                   {0.0333f, 0.0f}};
+constexpr int kShortUnits = 256;      // compute units
+constexpr int kShortIters = 5;        // iterations of a solve to a tolerance: what the cells take nearly everywhere
+
+// n_iters: of a solve of a fixed count, 0 = to a tolerance
+inline float records_us(const ShortCost &k, const CellInfo &ci, int dtype, int B, int L, int H, int n_iters)
 {
-    const double n = (double)B * L * H, channels = (double)B * H, esz = dtype == PARARNN_BF16 ? 2.0 : 4.0;
-    const bool tiny = n < 512.0 * 512.0 && L <= 1024;
-    int c, lps, w;
-    if (backward || L <= 512 || ci.S > 2 || tiny || (ci.S == 1 && L <= 2048)) {
-        // ---- one tile.  Steps per thread: below half a wave per SIMD at eight of them the chunk's own latency counts (GRU
-        // 4 x 250 x 100: eight steps 10.9, four 9.8); sixteen spread the wave and workgroup levels of an iteration over
-        // more cell evaluations and are what makes longer sequences fit; the single pass backward has those levels once.
-        c = ci.S > 2 || tiny ? 4 : backward || L <= 512 ? 8 : 16;
-        // Four waves iterate fastest (two barriers in every iteration; workgroups of eight leave fewer of them on a
-        // compute unit); the single pass takes all there may be, for longer pieces of rows.
-        const int wmax = ci.S * c <= 8 ? 16 : 8, want = backward ? wmax : 4;
-        int ll = 1;
-        while (ll < 16 && c * ll * want < L) ll *= 2;
-        w = (L + c * ll - 1) / (c * ll);
-        if (w > wmax) return false;
-        lps = 6;
-        while ((64 >> lps) < ll) --lps;
-        // Long sequences mean short pieces of rows (four channels per group in the end), for which the memory pipeline
-        // needs as many cycles as for whole lines: fine where latency bounds the other kernels too, not on large tensors.
-        if (backward) {
-            // GRU fp32: 64 steps x 32 x 4096 66 / 52; 250 x 16 x 1000 36 / 26 but x 32 x 4096 203 / 214;
-            // 500 x 16 x 1024 59 / 56; 1000 x 8 x 1536 87 / 122; 2000 x 2 x 1000 36 / 47; two-state cells 777 x 5 x 333 25 / 30
-            if (ci.S >= 2 && L > 512) return false;
-            const double bytes = n * esz * (2 * ci.G + 2 * ci.S);
-            const double most = L <= 128 ? 1e30 : L <= 256 ? 512e6 : L <= 512 ? 192e6 : L <= 1024 ? 96e6 : 32e6;
-            if (bytes > most) return false;
-        } else if (L > 1024 && ci.S == 1) {
-            // GRU 2000 x 8 x 1000 fp32 156 / 137, bf16 160 / 133; 2048 x 8 x 2048 fp32 264 / 279, bf16 287 / 242.  A fixed
-            // count has no channels that stop on their own, which is most of the gain.
-            if (fixed || n * esz > 68e6) return false;
-        }
-    } else {
-        // ---- tiles.  What these kernels gain is that channels stop on their own and that nothing is cleared, published
-        // or launched for iterations that are not needed; what they lose is that a sequence is one chain.  Two-state
-        // cells (LSTM: six or seven iterations): 7261 x 27 x 818 4131 / 2301, 2048 x 8 x 2048 718 / 557, 43636 x 4 x 240
-        // 1261 / 930, 1531 x 3 x 1001 with three fixed iterations 83 / 73, but 39461 x 7 x 24 338 / 730.  Scalar cells, which
-        // take five nearly everywhere: bf16 4096 x 16 x 1024 573 / 480, 2720 x 2 x 950 88 / 73; fp32 4096 x 16 x 1024
-        // 487 / 506, 4063 x 20 x 565 380 / 406; 65536 x 4 x 4096 bf16 7602 / 8453 (in long sequences neighbouring groups
-        // drift apart and no longer share cache lines).
-        if (L > 2048 && channels < (ci.S == 1 ? 1500.0 : 900.0)) return false;
-        if (ci.S == 1 && (fixed || dtype != PARARNN_BF16 || L > 8192)) return false;
-        if (channels < 1500.0) { c = 16; lps = 2; w = 8; }               // few chains: all the waves there can be
-        else if (channels < (ci.S == 1 ? 3500.0 : 6000.0)) { c = ci.S == 1 || fixed ? 8 : 16; lps = 2; w = 4; }
-        else { c = 8; lps = 3; w = 4; }
-        const int most = (L + c * (64 >> lps) - 1) / (c * (64 >> lps));
-        if (w > most) w = most;
-    }
-    const int T = c * (64 >> lps) * w;
+    const int width = H <= 8 ? 8 : H <= 32 ? 32 : 64, T = H <= 8 ? 64 : H <= 32 ? 128 : ci.S == 1 ? 96 : 64;   // the fused blocks' tile
+    const float groups = (float)B * (float)((H + width - 1) / width), n_lt = (float)((L + T - 1) / T);
+    const float n = groups * (float)width * n_lt * (float)T * 1e-6f;
+    // a fixed count beyond the fused blocks is one launch per iteration, at the rate of the memory
+    if (n_iters > kMaxFused)
+        return (float)n_iters * (6.0f + n * ((float)ci.G * (dtype == PARARNN_BF16 ? 2.0f : 4.0f) + 8.0f * (float)ci.S) / 5.4f);
+    const float its = (float)(n_iters ? n_iters : kShortIters);
+    float step = (k.step + k.step_gate * (float)ci.G) * (its + k.rec_more), fixed = n_iters ? k.rec_fixed : k.rec_tol;
+    // the LSTM's sixth iteration is a launch of its own, which reads and writes the iterate, and there are channels that
+    // take a seventh
+    if (ci.kind == PARARNN_LSTM_DIAG && !n_iters) { step *= 1.45f; fixed += 8.7f; }
+    const float narrow = groups < 512.0f ? log2f(512.0f / groups) : 0.0f;
+    return fixed + step * n * (1.0f + k.rec_narrow * narrow) + k.rec_tile * its * n_lt;
+}
+inline float short_us(const ShortCost &k, const CellInfo &ci, int dtype, const ShortShape &sh, int n_iters)
+{
+    const bool many = sh.n_tiles > 1, bf = dtype == PARARNN_BF16;
+    // waves of a workgroup on one SIMD; a workgroup of five takes two on each, as one of eight does
+    const float waves = sh.w <= 4 ? 0.25f * (float)sh.w : (float)((sh.w + 3) / 4);
+    int per_unit = (int)((float)short_min_waves(ci.S, sh.c, many || (sh.c > 8 && ci.S > 1)) / waves);
+    if (per_unit < 1) per_unit = 1;
+    const int full = sh.n_items / (kShortUnits * per_unit), left = sh.n_items - full * kShortUnits * per_unit;
+    const auto &t = k.tile[sh.c > 8][many];
+    auto round = [&](int per) {
+        float on = waves * (float)per;
+        if (sh.w > 4 && sh.w < 8) on *= 1.0f - k.uneven * (1.0f - 0.125f * (float)sh.w);
+        return t.one + t.wave * on;
+    };
+    float rounds = (float)full * round(per_unit);
+    if (left) rounds += round((left + kShortUnits - 1) / kShortUnits) * (full > 1 ? k.last : 1.0f);
+    rounds *= 1.0f - k.overlap[many] * (float)(full < 4 ? full : 4);
+    if (sh.w > 4) rounds *= 1.0f + k.wide / (float)(sh.lps_log2 - 1);
+    rounds *= k.piece[sh.lps_log2 < 5 ? sh.lps_log2 - 2 : 3] * (1.0f + k.drift[bf] * log2f((float)sh.n_tiles)) * (bf ? k.bf16 : 1.0f);
+    if (sh.n_items < kShortUnits) rounds *= 1.0f - k.few * (1.0f - (float)sh.n_items / (float)kShortUnits);
+    const float its = (float)(n_iters ? n_iters : kShortIters);
+    return k.start + (k.step + k.step_gate * (float)ci.G) * (its + k.more) * (float)sh.n_tiles * rounds;
+}
+
+// Completes a shape (c, lps_log2, w); false where it is outside the kernels' bounds.
+inline bool short_complete(const CellInfo &ci, int dtype, int B, int L, int H, ShortShape *sh)
+{
+    const int T = sh->c * (64 >> sh->lps_log2) * sh->w;
     // 32-bit offsets within a tile, of u and of the states, whichever rows are wider
+    const double esz = dtype == PARARNN_BF16 ? 2.0 : 4.0;
     if ((double)(ci.G > ci.S ? ci.G : ci.S) * H * esz * (T + 1.0) >= 2147483647.0) return false;
-    out->c = c; out->lps_log2 = lps; out->w = w;
-    out->n_cg = (H + (1 << lps) - 1) >> lps;
-    if ((double)B * out->n_cg > 131072.0) return false;      // verdicts that workgroup 0 collects
-    out->n_items = B * out->n_cg;
-    out->n_tiles = (L + T - 1) / T;
+    sh->n_cg = (H + (1 << sh->lps_log2) - 1) >> sh->lps_log2;
+    if ((double)B * sh->n_cg > 131072.0) return false;       // verdicts that workgroup 0 collects
+    sh->n_items = B * sh->n_cg;
+    sh->n_tiles = (L + T - 1) / T;
     return true;
 }
-// workspace of such a solve: the control block (not used) and the workgroups' verdicts
-inline size_t short_workspace_bytes(const ShortShape &sh)
+
+// One tile: the fewest segments per wave with which `want` waves hold the sequence, as few waves as that takes.
+inline bool short_one_tile(int L, int c, int want, int most, ShortShape *sh)
 {
-    return round256(sizeof(Ctrl)) + round256((size_t)sh.n_items * 2 * sizeof(rec_t));
+    int ll = 1;
+    while (ll < 16 && c * ll * want < L) ll *= 2;
+    sh->c = c;
+    sh->w = (L + c * ll - 1) / (c * ll);
+    sh->lps_log2 = 6;
+    while ((64 >> sh->lps_log2) < ll) --sh->lps_log2;
+    return sh->w <= most;
+}
+
+// The shape of a forward solve, or false where the kernels with carry records do better.  n_iters: 0 = to a tolerance.
+inline bool short_forward_shape(const CellInfo &ci, int dtype, int B, int L, int H, int n_iters, ShortShape *out)
+{
+    const bool tiny = (double)B * L * H < 512.0 * 512.0 && L <= 1024;
+    const ShortCost &k = ci.S == 1 ? kCostScalar : kCostBlock2;
+    // the fit has counts of three; two or twelve are estimated from it
+    const float better = n_iters == 0 || (n_iters >= 3 && n_iters <= 5) ? 0.97f : 0.85f;
+    ShortShape sh;
+    if (tiny || L <= 512 || ci.S > 2) {
+        // One tile.  Steps per thread: below half a wave per SIMD at eight of them the chunk's own latency counts (GRU
+        // 4 x 250 x 100: eight steps 10.9 us, four 9.8), blocks of 3x3 and larger spill beyond four.  Four waves iterate
+        // fastest: two barriers in every iteration, and workgroups of eight leave fewer of them on a compute unit.
+        const int c = ci.S > 2 || tiny ? 4 : 8;
+        if (!short_one_tile(L, c, 4, ci.S * c <= 8 ? 16 : 8, &sh) || !short_complete(ci, dtype, B, L, H, &sh)) return false;
+        *out = sh;
+        if (ci.S > 2) {
+            // 3x3 / 4x4 cells, times / times with records: up to 256 steps 0.3-0.98 to a tolerance; three fixed iterations 64
+            // steps 0.5-1.0, 128 steps of 1024 workgroups 0.8-0.9, of 2048 1.0-1.1, 256 steps of 1024 0.8-0.94, of 2000
+            // 1.0-1.27.  Beyond, with five to eight waves, of which a unit holds one workgroup: 256 of them 0.4-0.75, 512 0.8-1.0
+            // and fixed 1.2-1.4, 1000 1.0-1.2 and 1.4-1.75.
+            if (L > 256) return sh.n_items <= kShortUnits * (n_iters ? 1 : 2);
+            return L <= 64 || n_iters == 0 || n_iters > kMaxFused || sh.n_items <= 4 * kShortUnits;
+        }
+        // below 160 steps the kernels with records are nowhere faster (131072 channels: 0.87-0.93 of their time)
+        return tiny || L < 160 || short_us(k, ci, dtype, sh, n_iters) < better * records_us(k, ci, dtype, B, L, H, n_iters);
+    }
+    // what long sequences of scalar cells lose by their groups drifting apart in time (they no longer share the cache lines
+    // of a row) is fitted up to 16384 steps: 65536 x 4 x 4096 in bf16 took 8453 us against 7602 with records
+    if (ci.S == 1 && L > 16384) return false;
+    float best = better * records_us(k, ci, dtype, B, L, H, n_iters);
+    bool found = false;
+    for (int c = 8; c <= 16; c += 8)
+        for (int lps = 2; lps <= 5; ++lps)
+            for (int w = 4; w <= 8; w += 4) {
+                const int row = c * (64 >> lps), most = (L + row - 1) / row;
+                sh.c = c; sh.lps_log2 = lps; sh.w = w < most ? w : most;
+                if (!short_complete(ci, dtype, B, L, H, &sh)) continue;
+                const float us = short_us(k, ci, dtype, sh, n_iters);
+                if (us < best) { best = us; *out = sh; found = true; }
+            }
+    return found;
+}
+
+// The shape of a backward pass: one pass over one tile.  It takes all the waves there may be, for longer pieces of rows; two-state
+// cells of 65 to 192 steps take four where a round of the device does not hold all groups, because a unit holds three
+// such workgroups and one of five to eight waves (LSTM bf16 192 x 16 x 2048: 0.72 of the time with records, with six waves
+// 0.95; 192 x 4 x 1024: 0.56 and 0.53).  Long sequences mean short pieces (four channels per group in the end), for which the
+// memory pipeline needs as many cycles as for whole lines: fine where latency bounds the other kernels too, not on large
+// tensors.  Bounds on the bytes of a pass, where the two are level: times / times with records,
+//   scalar   128 steps fp32 131072 channels 1.13-1.27, 65536 0.98; 256: fp32 32768 0.97-1.03, bf16 65536 1.0, 131072 1.2; 512:
+//            fp32 16384 0.93, bf16 32768 1.1; 1024: fp32 1332 1.0, bf16 8000 0.94; 1500: bf16 1024 0.73, 1332 1.33
+//   2x2      96 steps fp32 65536 0.7-0.9, 131072 0.9-1.1; 160: fp32 32768 0.65-0.8, 65536 0.85-1.2; 192: fp32 16384 0.75-0.87,
+//            32768 0.77-1.07; 256: fp32 16384 0.82-0.99, 32768 0.84 (two gates) to 1.32, bf16 32768 0.8-1.0, 65536 0.92 (two
+//            gates) to 1.31; 320-384: one round of the device, 2048 channels, 0.6-0.9; two 0.98-1.18; 448-512: two 0.9-1.0,
+//            four 0.92-1.07; two gates: two rounds 0.8-0.95, four 0.8-1.1
+//   3x3, 4x4 32 steps 0.6-1.08; up to 256 steps one round (a workgroup on each unit) 0.6-0.75, two 0.75-1.03, four 1.0-1.4; 320-512
+//            one round 0.6-0.85, two 1.07-1.4
+inline bool short_backward_shape(const CellInfo &ci, int dtype, int B, int L, int H, ShortShape *out)
+{
+    const double n = (double)B * L * H, bytes = n * (dtype == PARARNN_BF16 ? 2.0 : 4.0) * (2 * ci.G + 2 * ci.S);
+    const int c = ci.S > 2 || (n < 512.0 * 512.0 && L <= 1024) ? 4 : 8, most = ci.S * c <= 8 ? 16 : 8;
+    if (!short_one_tile(L, c, most, most, out) || !short_complete(ci, dtype, B, L, H, out)) return false;
+    const int per_gate = ci.G <= 2 ? 2 : 1;
+    if (ci.S == 2 && c == 8 && L > 64 && L <= 192 && out->n_items > kShortUnits * per_gate &&
+        (!short_one_tile(L, c, 4, most, out) || !short_complete(ci, dtype, B, L, H, out)))
+        return false;
+    if (ci.S == 1)
+        return L <= 64 || (L <= 1536 && bytes <= (L <= 256 ? 400e6 : L <= 512 ? 192e6 : L <= 1024 ? 96e6 : 32e6) &&
+                           (L <= 1024 || out->n_items <= kShortUnits));
+    if (L > 512) return false;
+    if (ci.S > 2) return L <= 32 || out->n_items <= kShortUnits * (L <= 256 ? 2 : 1);
+    if (L <= 256) return L <= 64 || bytes <= (L <= 96 ? 420e6 : L <= 160 ? 340e6 : L <= 192 ? 250e6 : 280e6);
+    return bytes <= 192e6 && (c == 4 || out->n_items <= kShortUnits * per_gate * (L > 384 || per_gate > 1 ? 2 : 1));
+}
+
+inline bool short_shape(const CellInfo &ci, int dtype, int B, int L, int H, bool backward, int n_iters, ShortShape *out)
+{
+    return backward ? short_backward_shape(ci, dtype, B, L, H, out) : short_forward_shape(ci, dtype, B, L, H, n_iters, out);
+}
+// workspace of such a solve: the control block (not used) and the workgroups' verdicts
+inline size_t short_workspace_bytes(size_t n_items)
+{
+    return round256(sizeof(Ctrl)) + round256(n_items * 2 * sizeof(rec_t));
+}
+// ... of whatever shape and number of iterations: four channels are the smallest group
+inline size_t short_workspace_most(int B, int H)
+{
+    const size_t n = (size_t)B * (((size_t)H + 3) / 4);
+    return short_workspace_bytes(n < 131072 ? n : 131072);
 }
 
 // Polls (half a microsecond at least) after which workgroup 0 gives up waiting for the verdicts.  It waits for all
@@ -317,9 +445,7 @@ inline size_t diag_workspace_bytes(const CellInfo &ci, int dtype, int B, int L, 
             if (lf.total > need) need = lf.total;
         }
     }
-    ShortShape sh;
-    if (!backward && short_shape(ci, dtype, B, L, H, false, false, &sh) && short_workspace_bytes(sh) > need)
-        need = short_workspace_bytes(sh);
+    if (!backward && short_workspace_most(B, H) > need) need = short_workspace_most(B, H);
     return need;
 }
 
@@ -338,9 +464,7 @@ inline size_t diag_workspace_parts(const CellInfo &ci, int dtype, int B, int L, 
             if (lo.total - lo.off_bnd > *rest) *rest = lo.total - lo.off_bnd;
         }
     }
-    ShortShape sh;
-    if (!backward && short_shape(ci, dtype, B, L, H, false, n_iters > 0, &sh) && short_workspace_bytes(sh) > front)
-        front = short_workspace_bytes(sh);
+    if (!backward && short_workspace_most(B, H) > front) front = short_workspace_most(B, H);
     return front;
 }
 
@@ -532,7 +656,8 @@ int forward_solve(const CellInfo &ci, int dtype, const float *params, const void
     if (n_fused > 0) lo = lf;
     ShortShape sh;
     if (opts.fused_enabled && opts.fused_head > 0 && !(opts.blocks && tol >= 0.0f) && max_iter > 0 && !delta_trace && settings().tile[0] <= 0 &&
-        short_shape(ci, dtype, B, L, H, false, tol < 0.0f, &sh) && workspace_bytes >= short_workspace_bytes(sh))
+        short_shape(ci, dtype, B, L, H, false, tol < 0.0f ? max_iter : 0, &sh) &&
+        workspace_bytes >= short_workspace_bytes((size_t)sh.n_items))
         return forward_short<Cell>(dtype, sh, params, u, h0, B, L, H, tol, max_iter, h, iters, workspace, st);
     char *ws = static_cast<char *>(workspace);
     FwdArgs a;
@@ -601,7 +726,7 @@ int backward_pass(const CellInfo &ci, int dtype, const float *params, const void
         return PARARNN_WORKSPACE_TOO_SMALL;
     char *part = rest.ptr ? rest.ptr + (lo.off_part - lo.off_bnd) : static_cast<char *>(workspace) + lo.off_part;
     ShortShape sh;
-    if (settings().tile[0] <= 0 && short_shape(ci, dtype, B, L, H, true, false, &sh)) {
+    if (settings().tile[0] <= 0 && short_shape(ci, dtype, B, L, H, true, 0, &sh)) {
         ShortArgs a;
         memset(&a, 0, sizeof(a));
         a.B = B; a.L = L; a.H = H; a.n_cg = sh.n_cg; a.lps_log2 = sh.lps_log2; a.n_items = sh.n_items;

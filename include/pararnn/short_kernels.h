@@ -55,9 +55,9 @@ constexpr int kShortCarries = 16;
 template <class Cell, int C> constexpr int short_max_waves() { return Cell::S * C <= 8 ? 16 : 8; }
 // Waves per SIMD the register allocation must leave room for.  Sixteen steps of a scalar cell come out one register above
 // the four-wave limit by themselves, and a workgroup of eight waves then has its compute unit to itself (2 x).
-template <class Cell, int C, bool MANY = false> constexpr int short_min_waves()
+constexpr int short_min_waves(int S, int C, bool many)
 {
-    return Cell::S == 1 ? (C <= 8 ? (MANY ? 5 : 6) : 4) : Cell::S == 2 ? (C <= 4 ? 4 : C == 8 ? 3 : 2) : 2;
+    return S == 1 ? (C <= 8 ? (many ? 5 : 6) : 4) : S == 2 ? (C <= 4 ? 4 : C == 8 ? 3 : 2) : 2;
 }
 // Shapes that are compiled (the choice: short_shape in driver.h): a single tile with four and eight steps per thread
 // and, for scalar cells, sixteen; several tiles with eight and sixteen; blocks of 3x3 and larger spill beyond four.
@@ -150,7 +150,7 @@ __device__ __forceinline__ void short_report(unsigned int v, int max_iter, int *
 
 // MANY: more than one tile (at most eight waves)
 template <class Cell, int C, typename UT, bool MANY>
-__global__ __launch_bounds__((kWave * (MANY ? 8 : short_max_waves<Cell, C>()))) __attribute__((amdgpu_waves_per_eu(short_min_waves<Cell, C, MANY>()))) void newton_short_kernel(const ShortArgs a)
+__global__ __launch_bounds__((kWave * (MANY ? 8 : short_max_waves<Cell, C>()))) __attribute__((amdgpu_waves_per_eu(short_min_waves(Cell::S, C, MANY)))) void newton_short_kernel(const ShortArgs a)
 {
     constexpr int S = Cell::S, G = Cell::G, SS = S * S, PR = Cell::PR;
     extern __shared__ float s_agg[];                   // [W][SS + S][CW] wave aggregates; several tiles: [2][kShortCarries][S][CW] carries
@@ -401,7 +401,7 @@ __global__ __launch_bounds__((kWave * (MANY ? 8 : short_max_waves<Cell, C>()))) 
 
 // The adjoint scan and the gradients (Eq. (6)), formulas and variables as in backward_kernel.
 template <class Cell, int C, typename UT>
-__global__ __launch_bounds__((kWave * short_max_waves<Cell, C>())) __attribute__((amdgpu_waves_per_eu(short_min_waves<Cell, C>()))) void backward_short_kernel(const ShortArgs a)
+__global__ __launch_bounds__((kWave * short_max_waves<Cell, C>())) __attribute__((amdgpu_waves_per_eu(short_min_waves(Cell::S, C, false)))) void backward_short_kernel(const ShortArgs a)
 {
     constexpr int S = Cell::S, G = Cell::G, SS = S * S, PR = Cell::PR, NC = Cell::NC;
     extern __shared__ float s_agg[];                   // [W][max(SS + S, PR)][CW]

@@ -14,7 +14,7 @@ int main()
     while (scanf("%d %d %d %d %d %d %d %d %d %d", &G, &S, &PR, &kind, &dtype, &B, &L, &H, &backward, &fixed) == 10) {
         const CellInfo ci = {G, S, PR, kind};
         ShortShape sh = {};
-        if (!short_shape(ci, dtype, B, L, H, backward != 0, fixed != 0, &sh)) sh = ShortShape{};
+        if (!short_shape(ci, dtype, B, L, H, backward != 0, fixed, &sh)) sh = ShortShape{};
         const unsigned int polls = sh.c ? short_wait_limit(kSpinLimit, sh, fixed ? fixed : 64) : 0;
         printf("%d %d %d %d %d %u\n", sh.c, sh.lps_log2, sh.w, sh.n_items, sh.n_tiles, polls);
     }

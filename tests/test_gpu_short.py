@@ -110,3 +110,48 @@ def test_a_chosen_first_block_is_run_to_its_end(oracle_mod, cell, shape):
         P.set_fused_head(5)
     for h, iters in got:
         assert iters.cpu().tolist() == [1, 0] and relerr(to_np(h), h3) <= 2e-5
+
+
+@pytest.mark.parametrize("cell", ["gru_diag", "lstm_diag", "paralstm_diag"])
+@pytest.mark.parametrize("shape", [(1, 530, 8189), (1, 520, 16381), (1, 1100, 2047), (1, 1500, 4093), (2, 1030, 1101), (1, 4097, 258)])
+def test_walks_of_every_width(oracle_mod, cell, shape):
+    """Groups of 4 to 32 channels, four and eight waves, the last group and the last tile incomplete: every iterate and the
+    solution of sampled channels (they are independent), and the count of the kernels with carry records."""
+    import paper_2510_21450_amd as P
+    B, L, H = shape
+    dtype = torch.bfloat16 if (L + H) % 2 else torch.float32
+    bound = 1e-5 if dtype == torch.float32 else 2e-2
+    print(f"walk {cell} {shape} {dtype}", flush=True)
+    params, u, h0, _ = problem(cell, B, L, H, seed=90 + L, dtype=dtype)
+    pick = sorted({0, 1, 3, 4, 31, 32, 63, 64, H // 2, H - 33, H - 5, H - 4, H - 3, H - 2, H - 1})
+    take = lambda t: to_np(t)[..., pick]
+    pn, un, h0n = take(params), take(u), take(h0)
+    for k in (2, 3, 7):
+        h, iters, _ = P.forward(cell, params, u, h0, tol=-1.0, max_iter=k)
+        assert iters.cpu().tolist() == [k, 0]
+        assert relerr(take(h), oracle_mod.newton(cell, pn, un, h0n, tol=-1.0, max_iter=k)[0]) <= 2 * bound, k
+    h, iters, _ = P.forward(cell, params, u, h0, tol=1e-4, max_iter=40)
+    assert relerr(take(h), oracle_mod.seq_unroll(cell, pn, un, h0n)) <= bound
+    _, with_records, _ = P.forward(cell, params, u, h0, tol=1e-4, max_iter=40, trace=True)
+    assert iters.cpu().tolist() == with_records.cpu().tolist()
+
+
+@pytest.mark.parametrize("cell", ["lstm_diag", "paralstm_diag"])
+@pytest.mark.parametrize("shape", [(1, 66, 8203), (2, 128, 2061), (1, 129, 4113), (3, 192, 1397)])
+def test_backward_of_four_waves(oracle_mod, as_stored, cell, shape):
+    """Two-state cells of 65 to 192 steps with more channel groups than the device has units: at both ends of that range,
+    last group and last wave incomplete."""
+    import paper_2510_21450_amd as P
+    B, L, H = shape
+    dtype = torch.bfloat16 if L % 2 else torch.float32
+    bound = 1e-5 if dtype == torch.float32 else 2e-2
+    print(f"backward {cell} {shape} {dtype}", flush=True)
+    params, u, h0, g = problem(cell, B, L, H, seed=140 + L, dtype=dtype)
+    pick = sorted({0, 1, 15, 16, 31, 32, H // 2, H - 17, H - 16, H - 2, H - 1})
+    take = lambda t: to_np(t)[..., pick]
+    pn, un, h0n, gn = take(params), take(u), take(h0), take(g)
+    hs = P.forward(cell, params, u, h0, tol=1e-4, max_iter=40)[0]
+    hs[..., pick] = as_stored(oracle_mod.seq_unroll(cell, pn, un, h0n), u)
+    got = P.backward(cell, params, u, h0, hs, g)
+    for x, r in zip(got, oracle_mod.backward(cell, pn, un, h0n, take(hs), gn)):
+        assert relerr(take(x), r) <= bound

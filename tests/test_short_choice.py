@@ -8,7 +8,7 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PKG = os.path.join(ROOT, "paper_2510_21450_amd")
 #: G, S, parameter rows, number of the built-in cell (-1: a cell that is not built in)
-GRU, LSTM, PARALSTM, ROT = (3, 1, 6, 0), (4, 2, 8, 1), (3, 2, 8, 4), (2, 2, 2, -1)
+GRU, LSTM, PARALSTM, ROT, TRI = (3, 1, 6, 0), (4, 2, 8, 1), (3, 2, 8, 4), (2, 2, 2, -1), (3, 3, 12, -1)
 F32, BF16 = 0, 1
 
 
@@ -70,3 +70,28 @@ def test_the_wait_for_the_verdicts_covers_the_work(choose):
             assert polls == 2 ** 21, (p, s)
         seen.add(polls == 2 ** 21)
     assert seen == {True, False}
+
+
+# us on MI355X with carry records / without, of the best shape (forward: iterations of a fixed count, 0 = to a tolerance)
+MEASURED = [
+    (ROT, F32, 4, 50000, 275, 0, 779, 1134), (ROT, BF16, 4, 50000, 275, 0, 835, 1103), (ROT, BF16, 8, 2000, 256, 0, 85, 50),
+    (PARALSTM, F32, 4, 16000, 525, 0, 575, 825), (PARALSTM, BF16, 8, 1000, 1000, 0, 149, 118), (PARALSTM, F32, 4, 2000, 225, 0, 69, 43),
+    (LSTM, F32, 8, 4000, 1000, 0, 752, 554), (LSTM, BF16, 8, 50000, 1000, 0, 9715, 6497), (LSTM, F32, 8, 4000, 1000, 3, 352, 397),
+    (LSTM, BF16, 4, 600, 225, 3, 33, 19), (GRU, F32, 8, 8000, 1000, 0, 495, 565), (GRU, F32, 8, 1500, 512, 0, 79, 59),
+    (GRU, BF16, 4, 65536, 4096, 0, 7602, 8453), (GRU, BF16, 8, 1000, 1000, 0, 94, 64), (TRI, F32, 8, 320, 1000, 3, 62, 132),
+]
+
+
+MEASURED_BACKWARD = [
+    (LSTM, BF16, 16, 384, 1024, 57, 75), (LSTM, BF16, 16, 192, 2048, 65, 47), (PARALSTM, BF16, 16, 512, 1024, 61, 76),
+    (ROT, F32, 32, 128, 4096, 110, 127), (ROT, F32, 4, 512, 1024, 21, 20), (GRU, F32, 32, 128, 4096, 108, 123),
+    (GRU, BF16, 4, 1500, 333, 24, 32), (GRU, BF16, 1, 1500, 1024, 25, 18), (TRI, BF16, 8, 320, 1000, 35, 71),
+    (TRI, F32, 4, 128, 1000, 19, 11),
+]
+
+
+def test_the_faster_kernels_are_taken(choose):
+    for m, s in zip(MEASURED, choose([(m[0], m[1], m[2], m[3], m[4], 0, m[5]) for m in MEASURED])):
+        assert (s is None) == (m[6] < m[7]), (m, s)
+    for m, s in zip(MEASURED_BACKWARD, choose([(*m[:5], 1, 0) for m in MEASURED_BACKWARD])):
+        assert (s is None) == (m[5] < m[6]), (m, s)
