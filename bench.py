@@ -177,10 +177,18 @@ def projection_calls(run):
 
 
 def block_iterations(w):
-    """Iterations of the launch whose rate is quoted: the first block of a solve; cells with two state values solve
-    in one launch at these sizes, which is timed over more iterations than any of these solves needs."""
-    from workloads import cell_dims
-    return min(FUSED_HEAD, w.max_iter) if cell_dims(w.cell)[1] == 1 else 8
+    """Iterations of the launch whose rate is quoted: the first block of a solve; a solve that is one launch
+    without blocks is timed over more iterations than any of these workloads needs."""
+    return 8 if without_blocks(w) else min(FUSED_HEAD, w.max_iter)
+
+
+def without_blocks(w):
+    """Whether the library solves the workload in one launch, one workgroup per group of channels."""
+    import torch
+    import paper_2510_21450_amd as P
+    if w.cell == "tanh_dense":
+        return False
+    return P.solve_without_blocks(w.cell, torch.bfloat16 if w.dtype == "bf16" else torch.float32, w.B, w.L, w.H, w.tol, w.max_iter)
 
 
 def kernel_figures(run, reps, counters):
@@ -236,11 +244,11 @@ def kernel_figures(run, reps, counters):
     # initial guess (u read once, the iterate in registers, h written once).  Timed as the library runs it
     # inside a solve: a tolerance that is met at once ends the solve after this launch, which still
     # performs all its iterations; the call also holds the reset of the control block and one
-    # launch that returns at once.  Two state values (at these sizes): the one launch that walks every channel
-    # group's tiles, timed over a fixed count, because under a tolerance every group stops by itself.
+    # launch that returns at once.  A solve without blocks is the one launch that walks every channel group's
+    # tiles, timed with a tolerance of zero, which no group meets: with its own every group stops by itself.
     K0 = block_iterations(w)
-    one_launch = K0 != min(FUSED_HEAD, w.max_iter)
-    block = (lambda: run.forward(tol=-1.0, max_iter=K0)) if one_launch else (lambda: run.forward(tol=3.0e38, max_iter=K0 + 1))
+    one_launch = without_blocks(w)
+    block = (lambda: run.forward(tol=0.0, max_iter=K0)) if one_launch else (lambda: run.forward(tol=3.0e38, max_iter=K0 + 1))
     block()
     t_blk = time_events(block, reps)
     t_block_ms = mean(t_blk)
@@ -311,7 +319,7 @@ def headline_extras(run, rec, reps, counters):
     # blocks of Newton iterations of the plan; the first (two state values: the first two) is a launch of its own, the
     # rest share one.  Sequences that are walked by one workgroup per channel group take one launch for everything.
     rec["blocks"] = P.solve_plan(w.tol, w.max_iter) if w.cell != "tanh_dense" else None
-    rec["launches_per_solve"] = None if rec["blocks"] is None else min(len(rec["blocks"]), 2) if block_iterations(w) == FUSED_HEAD and w.L > 256 else 1
+    rec["launches_per_solve"] = None if rec["blocks"] is None else 1 if without_blocks(w) else min(len(rec["blocks"]), 2 if run.S == 1 else 3)
     if w.cell != "tanh_dense":
         # the same step under pararnn_set_workspace_reuse (the caller's promise that nothing else writes to the
         # two workspaces between calls: true for this loop): the carry records are not cleared again
@@ -410,10 +418,10 @@ def profile_pass(P, torch, name):
     else:
         K0 = block_iterations(w)
         for _ in range(3):
-            if K0 == min(FUSED_HEAD, w.max_iter):
-                run.forward(tol=3.0e38, max_iter=K0 + 1)
+            if without_blocks(w):
+                run.forward(tol=0.0, max_iter=K0)
             else:
-                run.forward(tol=-1.0, max_iter=K0)
+                run.forward(tol=3.0e38, max_iter=K0 + 1)
         P.set_fused(False)
         for _ in range(3):
             run.forward(tol=-1.0, max_iter=3)

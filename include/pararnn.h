@@ -179,7 +179,7 @@ int pararnn_set_streaming(int mode);
  * END of that launch -- the converged iterate refined by the Newton iterations
  * that were already in flight -- so it differs from the per-iteration path's h
  * by less than tol.  With the default of 5, problems of sizes the library
- * chooses have no blocks (unless pararnn_set_fused(0)): one workgroup per channel
+ * chooses (pararnn_solve_without_blocks) have no blocks: one workgroup per channel
  * group solves them in a single launch, and each group of channels returns the
  * iterate that met the tolerance within it, where channels that a group walks in
  * several pieces along L may have merged the last updates that cross from one
@@ -245,9 +245,14 @@ int pararnn_workspace_rest(void *workspace, void *rest, size_t rest_bytes);
  * stopping test is evaluated for every iteration and acted on between blocks.
  * The first block (two-state and larger cells: the first two) is a launch of its own; the following ones share one
  * launch (pararnn_set_fused_tail) or are launches of their own.  Problems that the library solves without blocks
- * (pararnn_set_fused_head; the plan does not know their sizes) are one launch in which every group of channels ends
- * after its own number of iterations, at most max_iter. */
+ * (pararnn_solve_without_blocks; the plan does not know their sizes) are one launch in which every group of channels
+ * ends after its own number of iterations, at most max_iter. */
 int pararnn_solve_plan(float tol, int max_iter, int *block_sizes, int capacity);
+
+/* 1 if pararnn_forward without delta_trace solves this problem, with the library's present settings, in one launch
+ * without blocks (one workgroup per group of channels), 0 if it runs the blocks of pararnn_solve_plan, -1 on
+ * invalid arguments (host only; 0 for the dense cell). */
+int pararnn_solve_without_blocks(int cell, int dtype, int B, int L, int H, float tol, int max_iter);
 
 /*
  * Forward: solve Eq. (2) by Newton iterations (Alg. 1a).

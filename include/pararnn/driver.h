@@ -624,6 +624,14 @@ int forward_short(int dtype, const ShortShape &sh, const float *params, const vo
     return e == hipSuccess ? PARARNN_OK : PARARNN_HIP_ERROR;
 }
 
+// Whether a solve without a trace is one launch without blocks, given the workspace for it.
+inline bool without_blocks(const CellInfo &ci, int dtype, int B, int L, int H, float tol, int max_iter, const SolveOpts &opts,
+                           ShortShape *sh)
+{
+    return opts.fused_enabled && opts.fused_head > 0 && !(opts.blocks && tol >= 0.0f) && max_iter > 0 && settings().tile[0] <= 0 &&
+           short_shape(ci, dtype, B, L, H, false, tol < 0.0f ? max_iter : 0, sh);
+}
+
 // A forward solve with checked arguments: layout, then the launches.
 template <class Cell>
 int forward_solve(const CellInfo &ci, int dtype, const float *params, const void *u, const void *h0, int B, int L,
@@ -655,8 +663,7 @@ int forward_solve(const CellInfo &ci, int dtype, const float *params, const void
     }
     if (n_fused > 0) lo = lf;
     ShortShape sh;
-    if (opts.fused_enabled && opts.fused_head > 0 && !(opts.blocks && tol >= 0.0f) && max_iter > 0 && !delta_trace && settings().tile[0] <= 0 &&
-        short_shape(ci, dtype, B, L, H, false, tol < 0.0f ? max_iter : 0, &sh) &&
+    if (!delta_trace && without_blocks(ci, dtype, B, L, H, tol, max_iter, opts, &sh) &&
         workspace_bytes >= short_workspace_bytes((size_t)sh.n_items))
         return forward_short<Cell>(dtype, sh, params, u, h0, B, L, H, tol, max_iter, h, iters, workspace, st);
     char *ws = static_cast<char *>(workspace);

@@ -238,6 +238,15 @@ def solve_plan(tol: float, max_iter: int):
     return [buf[i] for i in range(n)]
 
 
+def solve_without_blocks(cell, dtype, B: int, L: int, H: int, tol: float, max_iter: int) -> bool:
+    """pararnn_solve_without_blocks (built-in cells): whether `forward` solves this problem in one launch without the blocks
+    of `solve_plan`."""
+    r = _lib.pararnn_solve_without_blocks(CELLS[cell], DTYPES[dtype], B, L, H, ctypes.c_float(tol), int(max_iter))
+    if r < 0:
+        raise ValueError("pararnn_solve_without_blocks: invalid arguments")
+    return bool(r)
+
+
 def set_streaming(mode: int = 0) -> None:
     """pararnn_set_streaming: streamed tile accesses of the memory-bound kernels chosen by size (0, default),
     never (1) or always (2)."""

@@ -307,6 +307,15 @@ int pararnn_solve_plan(float tol, int max_iter, int *block_sizes, int capacity)
     return launches;
 }
 
+int pararnn_solve_without_blocks(int cell, int dtype, int B, int L, int H, float tol, int max_iter)
+{
+    CellInfo ci;
+    ShortShape sh;
+    if (!cell_info(cell, &ci) || (dtype != PARARNN_F32 && dtype != PARARNN_BF16) || !dims_ok(B, L, H) || max_iter < 0 || tol != tol)
+        return -1;
+    return cell != PARARNN_TANH_DENSE && without_blocks(ci, dtype, B, L, H, tol, max_iter, default_opts(), &sh) ? 1 : 0;
+}
+
 int pararnn_set_fused_head(int n_iters)
 {
     if (n_iters < 0 || n_iters > kMaxFused) return PARARNN_INVALID_ARG;

@@ -378,3 +378,19 @@ def test_user_cell_builds_from_the_public_headers_alone(tmp_path):
     text = open(src).read() + open(os.path.join(ROOT, "include", "pararnn_cell.h")).read() \
         + open(os.path.join(ROOT, "include", "pararnn_nonlin.h")).read()
     assert "csrc" not in text and "../" not in text.replace("../pararnn.h", "")
+
+
+def test_solve_without_blocks_follows_the_settings(lib):
+    f = lib.pararnn_solve_without_blocks
+    f.argtypes = [ctypes.c_int] * 5 + [ctypes.c_float, ctypes.c_int]
+    small, large = (0, 0, 2, 50, 40), (0, 0, 16, 4096, 1024)
+    assert f(*small, 1e-5, 20) == 1 and f(*small, -1.0, 3) == 1 and f(*large, 1e-5, 20) == 0
+    assert f(*small, 1e-5, 0) == 0 and f(2, 0, 2, 50, 64, 1e-5, 20) == 0
+    assert f(9, 0, 2, 50, 40, 1e-5, 20) == -1 and f(*small, float("nan"), 20) == -1 and f(0, 0, 0, 50, 40, 1e-5, 20) == -1
+    lib.pararnn_set_fused_head(3)                  # a chosen first block is run
+    assert f(*small, 1e-5, 20) == 0 and f(*small, -1.0, 3) == 1
+    lib.pararnn_set_fused_head(5)
+    lib.pararnn_set_fused(0)
+    assert f(*small, 1e-5, 20) == 0
+    lib.pararnn_set_fused(1)
+    assert f(*small, 1e-5, 20) == 1
