@@ -431,12 +431,29 @@ def profile_pass(P, torch, name):
             for _ in range(3):
                 pf()
                 pb()
+    print(json.dumps({"profile_pass": name, "copy_bytes_each_way": calibration_copy(torch), "N": run.N, "version": P.version()}))
+
+
+def calibration_copy(torch):
+    """A plain device copy of known size (bytes each way), the reference for the hardware byte counters."""
     src = torch.empty(1 << 26, dtype=torch.float32, device="cuda").normal_()
     dst = torch.empty_like(src)
     for _ in range(3):
         dst.copy_(src)          # 256 MiB read, 256 MiB written
     torch.cuda.synchronize()
-    print(json.dumps({"profile_pass": name, "copy_bytes_each_way": src.numel() * 4, "N": run.N, "version": P.version()}))
+    return src.numel() * 4
+
+
+def profile_case(P, torch, name):
+    """The same for one case of perf/cases.py: a few of its passes, and the copy."""
+    from perf import cases
+    case = next(c for c in cases.listed() if c["name"] == name)
+    state = cases.prepare(case, 1)
+    for _ in range(8):
+        cases.run(state)
+    torch.cuda.synchronize()
+    print(json.dumps({"profile_pass": name, "copy_bytes_each_way": calibration_copy(torch), "work": cases.work(case),
+                      "passes": 8, "case": case, "version": P.version()}))
 
 
 def main():
@@ -449,6 +466,7 @@ def main():
     ap.add_argument("--only", action="store_true", help="measure the headline workload only")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--profile-pass", action="store_true", help="short run of --config for rocprofv3 (bench_profile.py)")
+    ap.add_argument("--case", help="with --profile-pass: a case of perf/cases.py instead of --config")
     args = ap.parse_args()
     if args.gpus != 1:
         sys.exit("bench.py: this build runs on ONE GPU only (no sharding or collectives are part of it); "
@@ -460,7 +478,10 @@ def main():
     torch.cuda.set_device(0)
     P.set_fused_head(FUSED_HEAD)
     if args.profile_pass:
-        profile_pass(P, torch, args.config)
+        if args.case:
+            profile_case(P, torch, args.case)
+        else:
+            profile_pass(P, torch, args.config)
         return
     counters, why = load_counters(P.version())
     if why:

@@ -21,7 +21,8 @@ fetches n and writes n, so the factor of each counter is n over what it read.
 Raw rocprofv3 output goes to an untracked scratch folder (RAW_OUT below), with a second copy of the summaries
 and of counters.json.  Run on the machine with the GPU, from the repository root:
 
-    python3 bench_profile.py C5 C2 C3 C4
+    python3 bench_profile.py C2 C3 C4
+    python3 bench_profile.py gru-layer-train user-cell-train     # cases of perf/cases.py: every kernel of a pass, profiles/case_<name>.txt
 """
 import collections
 import csv
@@ -44,7 +45,10 @@ ISSUE_COUNTERS = {
             "SQ_VALU_MFMA_BUSY_CYCLES SQ_LDS_BANK_CONFLICT GRBM_GUI_ACTIVE",
     "dense": "SQ_VALU_MFMA_BUSY_CYCLES SQ_BUSY_CYCLES SQ_INSTS_VALU_MFMA_MOPS_F32 SQ_WAVES GRBM_GUI_ACTIVE",
 }
-PASS_TIMEOUT_S = 170
+PASS_TIMEOUT_S = 60                 # a good pass takes a few seconds
+# Not run under counters: a FETCH_SIZE pass of this workload made no progress after the runtime's initialisation and was killed,
+# where its kernel-trace pass and every pass of the other workloads ended within seconds.  The cause is not known.
+NOT_UNDER_COUNTERS = ("C5", "gru-long-train")
 
 
 def short(name):
@@ -53,12 +57,12 @@ def short(name):
     return name[:96]
 
 
-def run_pass(cfg, tag, rocprof_args, outdir):
+def run_pass(cfg, tag, rocprof_args, outdir, what="--config"):
     """One rocprofv3 pass of bench.py's profile run; returns the path prefix of its CSV files."""
     d = os.path.join(outdir, tag)
     os.makedirs(d, exist_ok=True)
     cmd = ["rocprofv3", *rocprof_args, "--output-format", "csv", "-d", d, "-o", tag, "--",
-           "python3", os.path.join(ROOT, "bench.py"), "--config", cfg, "--profile-pass"]
+           "python3", os.path.join(ROOT, "bench.py"), what, cfg, "--profile-pass"]
     env = dict(os.environ, TMPDIR="/tmp", PYTHONPATH=ROOT)
     print(f"[profile] {cfg} {tag}: {' '.join(cmd)}", flush=True)
     t0 = time.time()
@@ -69,7 +73,7 @@ def run_pass(cfg, tag, rocprof_args, outdir):
     if r.returncode != 0:
         tail = open(os.path.join(d, "run.log")).read()[-1500:]
         raise SystemExit(f"pass {tag} of {cfg} failed (exit {r.returncode}); nothing further is run\n{tail}")
-    return os.path.join(d, tag), " ".join(cmd[:cmd.index("--") + 1] + ["python3", "bench.py", "--config", cfg, "--profile-pass"])
+    return os.path.join(d, tag), " ".join(cmd[:cmd.index("--") + 1] + ["python3", "bench.py", what, cfg, "--profile-pass"])
 
 
 def durations(prefix):
@@ -116,6 +120,54 @@ def mean(v):
     return sum(v) / len(v) if v else None
 
 
+def calibration(meta, fetch, write):
+    """Bytes of the device copy, and the factors of the two byte counters on it (its largest dispatches)."""
+    def reading(rows, counter):
+        vals = [x for k, cs in rows.items() if "copyBuffer" in k for x, dd in cs[counter] if dd >= 20.0]
+        return mean([v for v in vals if v >= 0.9 * max(vals)]) * 1024.0
+    n = float(meta["copy_bytes_each_way"])
+    return n, n / reading(fetch, "FETCH_SIZE"), n / reading(write, "WRITE_SIZE")
+
+
+def profile_case(name, outdir):
+    """Every kernel of one pass of a case of perf/cases.py: time, bytes, busy fractions."""
+    d = os.path.join(outdir, name)
+    passes = [("kt", ["--kernel-trace", "--stats"]), ("fetch", ["--pmc", "FETCH_SIZE"]), ("write", ["--pmc", "WRITE_SIZE"]),
+              ("issue", ["--pmc", *ISSUE_COUNTERS["diag"].split()])]
+    prefix, cmds = {}, []
+    for tag, how in passes:
+        prefix[tag], cmd = run_pass(name, tag, how, d, "--case")
+        cmds.append(cmd.replace(d + "/", "OUT/"))
+    meta = [json.loads(l) for l in open(os.path.join(d, "kt", "run.log")) if l.startswith("{")][-1]
+    dur = durations(prefix["kt"])
+    fetch, write, issue = counter_rows(prefix["fetch"]), counter_rows(prefix["write"]), counter_rows(prefix["issue"])
+    _, f_fetch, f_write = calibration(meta, fetch, write)
+    n = meta["passes"]
+    lines = [f"Case {name} of perf/cases.py: {json.dumps(meta['case'])}",
+             f"Library version {meta['version']}, kernel-source hash {bench.source_hash()}",
+             f"Bytes a pass cannot do without: {meta['work']['bytes'] / 1e6:.1f} MB",
+             "Commands (cwd /tmp, TMPDIR=/tmp, PYTHONPATH=<repository>; separate passes of the same command), written by "
+             f"`python3 bench_profile.py {name}`:", *("  " + c for c in cmds), "",
+             f"Kernels of a pass ({n} passes on one state; calibration: {f_fetch:.3f} x FETCH_SIZE, {f_write:.3f} x WRITE_SIZE)"]
+    med = lambda v: sorted(v)[len(v) // 2]
+    for k, v in sorted(dur.items(), key=lambda kv: -sum(kv[1])):
+        if len(v) % n or re.search(r"at::|elementwise|distribution|copyBuffer|fillBuffer", k):
+            continue
+        us = med(v)
+        rd = med([x for x, _ in fetch[k]["FETCH_SIZE"]]) * 1024.0 * f_fetch
+        wr = med([x for x, _ in write[k]["WRITE_SIZE"]]) * 1024.0 * f_write
+        c = {m: med([x for x, _ in vals]) for m, vals in issue[k].items()}
+        cyc = c["GRBM_GUI_ACTIVE"] / 8.0           # summed over the XCDs; 1024 SIMDs
+        lines.append(f"  {k}")
+        lines.append(f"      {len(v) // n} per pass, {us:.1f} us (min {min(v):.1f}); read {rd / 1e6:.1f} MB, written {wr / 1e6:.1f} MB, "
+                     f"{(rd + wr) / us / 1e3:.0f} GB/s; {c['SQ_WAVES']:.0f} waves, vector ALUs busy "
+                     f"{4.0 * c['SQ_ACTIVE_INST_VALU'] / 1024.0 / cyc:.2f}, matrix pipes {c['SQ_VALU_MFMA_BUSY_CYCLES'] / 1024.0 / cyc:.2f}, "
+                     f"LDS conflict cycles {c['SQ_LDS_BANK_CONFLICT'] / 256.0 / cyc:.2f} per unit")
+    for path in (os.path.join(ROOT, "profiles", f"case_{name}.txt"), os.path.join(outdir, f"case_{name}.txt")):
+        open(path, "w").write("\n".join(lines) + "\n")
+        print(f"[profile] wrote {path}", flush=True)
+
+
 def profile_config(cfg, outdir):
     from workloads import ALL_CONFIGS
     w = ALL_CONFIGS[cfg]
@@ -129,12 +181,7 @@ def profile_config(cfg, outdir):
     dur, fetch, write, issue = durations(kt), counter_rows(fe), counter_rows(wr), counter_rows(ex)
 
     # calibration: the device copy of known size (the largest copy kernel dispatches)
-    def copy_reading(rows, counter):
-        vals = [x for k, cs in rows.items() if "copyBuffer" in k for x, dd in cs[counter] if dd >= 20.0]
-        top = max(vals)
-        return mean([v for v in vals if v >= 0.9 * top]) * 1024.0
-    n_copy = float(meta["copy_bytes_each_way"])
-    f_fetch, f_write = n_copy / copy_reading(fetch, "FETCH_SIZE"), n_copy / copy_reading(write, "WRITE_SIZE")
+    n_copy, f_fetch, f_write = calibration(meta, fetch, write)
 
     rec, lines = {}, []
     for cname, (pat, how) in classes(kind).items():
@@ -238,8 +285,16 @@ def profile_config(cfg, outdir):
 
 
 def main():
-    cfgs = sys.argv[1:] or ["C5", "C2", "C3", "C4"]
+    cfgs = sys.argv[1:] or ["C2", "C3", "C4"]
+    for c in cfgs:
+        if c in NOT_UNDER_COUNTERS:
+            raise SystemExit(f"{c} is not run under counters (see NOT_UNDER_COUNTERS)")
     outdir = RAW_OUT
+    for name in [c for c in cfgs if c not in PROFILE_NAMES]:
+        profile_case(name, outdir)
+    cfgs = [c for c in cfgs if c in PROFILE_NAMES]
+    if not cfgs:
+        return
     import ctypes
     lib = ctypes.CDLL(os.path.join(ROOT, "paper_2510_21450_amd", "libpararnn.so"))
     path = bench.COUNTERS_JSON

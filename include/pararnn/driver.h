@@ -232,7 +232,8 @@ constexpr int kShortIters = 5;        // iterations of a solve to a tolerance: w
 // n_iters: of a solve of a fixed count, 0 = to a tolerance
 inline float records_us(const ShortCost &k, const CellInfo &ci, int dtype, int B, int L, int H, int n_iters)
 {
-    const int width = H <= 8 ? 8 : H <= 32 ? 32 : 64, T = H <= 8 ? 64 : H <= 32 ? 128 : ci.S == 1 ? 96 : 64;   // the fused blocks' tile
+    // the fused blocks' tile
+    const int width = H <= 8 ? 8 : H <= 32 ? 32 : 64, T = H <= 8 ? 64 : H <= 32 ? 128 : ci.S == 1 ? 96 : 64;
     const float groups = (float)B * (float)((H + width - 1) / width), n_lt = (float)((L + T - 1) / T);
     const float n = groups * (float)width * n_lt * (float)T * 1e-6f;
     // a fixed count beyond the fused blocks is one launch per iteration, at the rate of the memory
@@ -264,7 +265,8 @@ inline float short_us(const ShortCost &k, const CellInfo &ci, int dtype, const S
     if (left) rounds += round((left + kShortUnits - 1) / kShortUnits) * (full > 1 ? k.last : 1.0f);
     rounds *= 1.0f - k.overlap[many] * (float)(full < 4 ? full : 4);
     if (sh.w > 4) rounds *= 1.0f + k.wide / (float)(sh.lps_log2 - 1);
-    rounds *= k.piece[sh.lps_log2 < 5 ? sh.lps_log2 - 2 : 3] * (1.0f + k.drift[bf] * log2f((float)sh.n_tiles)) * (bf ? k.bf16 : 1.0f);
+    rounds *= k.piece[sh.lps_log2 < 5 ? sh.lps_log2 - 2 : 3] * (bf ? k.bf16 : 1.0f);
+    rounds *= 1.0f + k.drift[bf] * log2f((float)sh.n_tiles);
     if (sh.n_items < kShortUnits) rounds *= 1.0f - k.few * (1.0f - (float)sh.n_items / (float)kShortUnits);
     const float its = (float)(n_iters ? n_iters : kShortIters);
     return k.start + (k.step + k.step_gate * (float)ci.G) * (its + k.more) * (float)sh.n_tiles * rounds;
