@@ -157,7 +157,12 @@ public:
             ws_ = workspace_of(front, like, {});
             kept_ = pararnn_workspace_keep(ws_.data_ptr(), 1) == PARARNN_OK;
         }
-        rest_ = workspace_of(rest, like, {});
+        try {
+            rest_ = workspace_of(rest, like, {});
+        } catch (...) {
+            if (kept_) give_up(ws_);         // no destructor runs for an object that was not constructed
+            throw;
+        }
         pararnn_workspace_rest(ws_.data_ptr(), rest_.data_ptr(), (size_t)rest_.numel());
     }
     Workspace(const Workspace &) = delete;

@@ -1,6 +1,7 @@
 """Workspaces kept between the calls of the Python entry points: carry records are not cleared for a call of the same
 problem, and a backward pass then needs no clearing launch.  The results have to be the bits of a call on a fresh workspace
 of the caller's, whatever ran before on the kept one, on every stream and from every thread."""
+import ctypes
 import threading
 
 import pytest
@@ -35,6 +36,13 @@ def run(P, cell, p, fresh, fixed=False):
 
 def same(a, b):
     return all(torch.equal(x, y) for x, y in zip(a, b))
+
+
+def front_bytes(P, dtype, B, L, H, back):
+    """What is kept of a GRU call's workspace, and what the call takes besides."""
+    parts = ctypes.CDLL(P.lib_path()).pararnn_workspace_parts
+    parts.restype, rest = ctypes.c_size_t, ctypes.c_size_t(0)
+    return parts(0, dtype, B, L, H, back, 0, ctypes.byref(rest)), rest.value
 
 
 @pytest.mark.parametrize("cell,dtype,B,L,H", [
@@ -144,3 +152,32 @@ def test_only_control_block_and_records_are_kept():
         assert same(run(P, cell, p, False), want), rep
     records = 3 * 8 * B * -(-H // 64) * 64 * (5 * -(-L // 96) + -(-L // 64))        # A, b, inclusive value; 5 + 1 sets
     assert 0 < P.release_workspaces() <= records + 4096
+
+
+def test_a_call_that_cannot_allocate_forgets_the_workspace_it_took():
+    """The kept front goes back to torch's allocator with the failed call, so the library may no longer trust what is there."""
+    import paper_2510_21450_amd as P
+    lib = ctypes.CDLL(P.lib_path())
+    cell, B, L, H = "gru_diag", 4, 9000, 1024
+    P.release_workspaces()
+    on_host = [t.cpu() for t in problem(cell, torch.bfloat16, B, L, H, 5)]
+    torch.cuda.empty_cache()
+    params, u, h0, out = (t.cuda() for t in on_host)         # memory of exactly their size: none left over in the allocator
+    solve = lambda: P.forward(cell, params, u, h0, tol=1e-5, max_iter=16, out=out)[0].clone()
+    rest = front_bytes(P, 1, B, L, H, 0)[1]
+    known = lambda at: lib.pararnn_workspace_known(ctypes.c_void_p(at))
+    want = solve()
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    mine = [b["address"] for s in torch.cuda.memory_snapshot() for b in s["blocks"]
+            if b["state"] == "active_allocated" and known(b["address"])]
+    assert len(mine) == 1
+    total = torch.cuda.get_device_properties(0).total_memory
+    try:
+        torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + rest // 2) / total)
+        with pytest.raises(torch.OutOfMemoryError):
+            solve()
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert not known(mine[0]) and P.release_workspaces() == 0
+    assert torch.equal(solve(), want)
