@@ -115,7 +115,7 @@ struct Dims { int B, L, H; };
 // iterate of bf16 storage, sums of parameter gradients: three quarters of a bf16 solve's workspace) is allocated for each
 // call as before.  A call takes a front out while it enqueues its work, and the next one that gets it is behind it in the
 // same stream; calls of several threads find different ones.  Bounds per device: kMost fronts and a thirty-second of its
-// memory, the least recently used go first, and all of them when torch's allocator runs short (GiveBack).  Under stream
+// memory, the least recently used go first, and all of them when torch's allocator would take more memory (GiveBack).  Under stream
 // capture, with a workspace or a stream of the caller's, for small problems (0.5 us of host time to look would show there)
 // and for kernels without records nothing is kept.
 using WsKey = std::array<int64_t, 8>;
@@ -137,6 +137,17 @@ std::map<int, DevicePool> &pools()
     return p;
 }
 
+// Part of a workspace, allocated while its size is known to GiveBack.
+thread_local size_t t_allocating = 0;
+Tensor own_memory(size_t bytes, const Tensor &like)
+{
+    struct Note {
+        explicit Note(size_t n) { t_allocating = n; }
+        ~Note() { t_allocating = 0; }
+    } note(bytes);
+    return workspace_of(bytes, like, {});
+}
+
 // Gives a kept workspace up; the device is the current one.  The library has to know before the memory goes.
 void give_up(Tensor &ws)
 {
@@ -154,11 +165,11 @@ public:
         const size_t front = has(given) || stream ? 0 : look(c, back, code, d, n_iters, like, &rest);
         if (device_ < 0) { ws_ = workspace_of(bytes, like, given); return; }
         if (!kept_) {
-            ws_ = workspace_of(front, like, {});
+            ws_ = own_memory(front, like);
             kept_ = pararnn_workspace_keep(ws_.data_ptr(), 1) == PARARNN_OK;
         }
         try {
-            rest_ = workspace_of(rest, like, {});
+            rest_ = own_memory(rest, like);
         } catch (...) {
             if (kept_) give_up(ws_);         // no destructor runs for an object that was not constructed
             throw;
@@ -264,23 +275,26 @@ int64_t release_workspaces()
 }
 
 // torch's allocator asks before it takes more memory from the device, and so before an allocation fails; it does not say
-// how much it needs.  While seven eighths of what it may have are free it gets nothing (a program that has yet to
-// allocate its tensors would lose what is kept again and again), below that everything kept on the device it allocates
-// on: the current one, and no other, whose allocator may be locked by a thread that waits for this one.  That allocator's
-// lock is held here and taken again by what is freed, which it allows; the pool's own lock is never held while memory is
-// allocated or freed.
+// how much it needs.  It gets everything kept on the device it allocates on: the current one, and no other, whose allocator
+// may be locked by a thread that waits for this one.  Only a workspace of this thread's own call does not push out the kept
+// ones while there is memory for both: forward and backward pass of one training step would otherwise take turns with the
+// same memory for good.  The allocator's lock is held here and taken again by what is freed, which it allows; the pool's own
+// lock is never held while memory is allocated or freed.
 struct GiveBack : c10::FreeMemoryCallback {
     bool Execute() override
     {
         int device = -1;
-        size_t avail = 0, total = 0;
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(c10::hip::getCurrentHIPStream().stream(), &cap) != hipSuccess || cap != hipStreamCaptureStatusNone)
             return false;
-        if (hipGetDevice(&device) != hipSuccess || hipMemGetInfo(&avail, &total) != hipSuccess) return false;
-        namespace alloc = c10::hip::HIPCachingAllocator;
-        const double most = 0.125 * (double)total, mine = (double)alloc::getDeviceStats(device).reserved_bytes[0].current;
-        if ((double)(total - avail) < most && mine < most * alloc::getMemoryFraction(device)) return false;
+        if (hipGetDevice(&device) != hipSuccess) return false;
+        size_t avail = 0, total = 0;
+        if (t_allocating > 0 && hipMemGetInfo(&avail, &total) == hipSuccess) {
+            namespace alloc = c10::hip::HIPCachingAllocator;
+            const double need = (double)t_allocating + (32 << 20);        // the allocator rounds up
+            const double mine = (double)alloc::getDeviceStats(device).reserved_bytes[0].current;
+            if (need <= (double)avail && mine + need <= (double)total * alloc::getMemoryFraction(device)) return false;
+        }
         return release_on_device(device) > 0;
     }
 };

@@ -121,7 +121,9 @@ def test_a_captured_call_keeps_nothing():
         assert same(got, want[0]) and same(eager, want[1]), rep
 
 
-def test_kept_workspaces_go_back_before_an_allocation_fails():
+@pytest.mark.parametrize("most", ["half of what is kept", "ten times what is in use"])
+def test_kept_workspaces_go_back_before_an_allocation_fails(most):
+    """Of a few more bytes, and of a single tensor as large as nearly everything there is."""
     import paper_2510_21450_amd as P
     P.release_workspaces()
     torch.cuda.empty_cache()
@@ -133,9 +135,12 @@ def test_kept_workspaces_go_back_before_an_allocation_fails():
     kept = max(P.workspace_bytes("gru_diag", torch.float32, 8, 4000, 512, b) for b in (False, True))
     total = torch.cuda.get_device_properties(0).total_memory
     try:
-        torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + kept // 2) / total)
-        more = torch.empty(kept, dtype=torch.uint8, device="cuda")
-        assert P.release_workspaces() == 0 and more.numel() == kept
+        used = torch.cuda.memory_reserved()
+        allowed = 10 * used if most.startswith("ten") else used + kept // 2
+        torch.cuda.set_per_process_memory_fraction(allowed / total)
+        more = torch.empty(allowed - used + kept // 2, dtype=torch.uint8, device="cuda")
+        assert P.release_workspaces() == 0
+        del more
     finally:
         torch.cuda.set_per_process_memory_fraction(1.0)
     assert same(again, want) and same(run(P, "gru_diag", p, False), want)
@@ -181,3 +186,19 @@ def test_a_call_that_cannot_allocate_forgets_the_workspace_it_took():
         torch.cuda.set_per_process_memory_fraction(1.0)
     assert not known(mine[0]) and P.release_workspaces() == 0
     assert torch.equal(solve(), want)
+
+
+def test_a_program_that_fills_memory_keeps_its_workspaces():
+    """A workspace that is allocated does not push out the ones that are kept while there is memory for both."""
+    import paper_2510_21450_amd as P
+    cell, B, L, H = "gru_diag", 8, 16000, 512
+    p = problem(cell, torch.float32, B, L, H, 6)
+    P.release_workspaces()
+    torch.cuda.empty_cache()
+    ballast = torch.empty(torch.cuda.get_device_properties(0).total_memory // 5, dtype=torch.uint8, device="cuda")
+    first = run(P, cell, p, False)
+    for _ in range(5):
+        last = run(P, cell, p, False)
+    both = sum(front_bytes(P, 0, B, L, H, back)[0] for back in (0, 1))
+    assert P.release_workspaces() >= both > 0 and ballast.numel() > 0
+    assert same(last, first)
