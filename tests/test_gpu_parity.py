@@ -490,8 +490,10 @@ def test_bf16_stores_round_to_nearest_even_on_ties(P, oracle_mod):
         want = torch.from_numpy(ref).to(torch.bfloat16)
         # the cases really are ties: the exact result is not a bf16 value in the first two patterns
         assert not np.array_equal(want.double().numpy(), ref)
-        paths = {"fused block epilogue": dict(tol=1e-6, max_iter=8),
-                 "fixed-count fused launch": dict(tol=-1.0, max_iter=3),
+        paths = {"one workgroup": dict(tol=1e-6, max_iter=8),
+                 "one workgroup, fixed count": dict(tol=-1.0, max_iter=3),
+                 "fused block epilogue": dict(tol=1e-6, max_iter=8, trace=True),         # a trace takes the kernels with records
+                 "fixed-count fused launch": dict(tol=-1.0, max_iter=3, trace=True),
                  "initial guess + rounding pass": dict(tol=1e-6, max_iter=0)}
         for name, kw in paths.items():
             print(f"bf16 ties H={H}: {name}", flush=True)
@@ -511,14 +513,22 @@ def test_bf16_stores_round_to_nearest_even_on_ties(P, oracle_mod):
         u2 = torch.zeros(B, 2, 1, H, dtype=torch.bfloat16, device="cuda")
         hs = torch.zeros(B, 2, 1, H, dtype=torch.bfloat16, device="cuda")
         g = torch.stack([first, one]).view(1, 2, 1, H).expand(B, 2, 1, H).contiguous().cuda()
-        print(f"bf16 ties H={H}: backward", flush=True)
-        du, dp, dh0 = P.backward(cell, params, u2, None, hs, g)
-        torch.cuda.synchronize()
+        got = []
+        for tile in (None, (1, 1, 8, 8)):                  # one workgroup; a given tile takes the kernel with records
+            print(f"bf16 ties H={H}: backward, tile {tile}", flush=True)
+            try:
+                if tile:
+                    P.set_tile(*tile)
+                got.append(P.backward(cell, params, u2, None, hs, g))
+                torch.cuda.synchronize()
+            finally:
+                P.set_tile(0)
         rdu, rdp, rdh0 = oracle_mod.backward(cell, to_np(params), to_np(u2), None, to_np(hs), to_np(g))
         want_du, want_dh0 = torch.from_numpy(rdu).to(torch.bfloat16), torch.from_numpy(rdh0).to(torch.bfloat16)
         assert not np.array_equal(want_du.double().numpy(), rdu)
-        assert torch.equal(du.cpu().view(torch.int16), want_du.view(torch.int16)), H
-        assert torch.equal(dh0.cpu().view(torch.int16), want_dh0.view(torch.int16)), H
+        for tile, (du, dp, dh0) in enumerate(got):
+            assert torch.equal(du.cpu().view(torch.int16), want_du.view(torch.int16)), (H, tile)
+            assert torch.equal(dh0.cpu().view(torch.int16), want_dh0.view(torch.int16)), (H, tile)
 
 
 @pytest.mark.parametrize("cell", ["gru_diag", "lstm_diag", "paralstm_diag"])
@@ -526,9 +536,10 @@ def test_backward_inputs_staged_through_lds(P, oracle_mod, as_stored, cell):
     """bf16 storage: the backward kernel copies the rows of a tile straight from memory into LDS one
     tile ahead (interior tiles; edge tiles and the first tile of a sequence load through registers).
     Same arithmetic either way: bit-identical outputs with the staging switched off, and both within
-    the bf16 bound of the oracle.  Shapes with ragged tiles in L and H, and L below one tile."""
+    the bf16 bound of the oracle.  Shapes with ragged tiles in L and H, and L below one tile (scalar cells up to 1536
+    steps and two-state cells up to 512 go by the one-workgroup kernel, which stages nothing, unless a tile is given)."""
     for (B, L, H), tile in (((2, 1100, 200), None), ((3, 700, 64), None), ((2, 50, 72), None), ((1, 2100, 136), (1, 1, 8, 16)),
-                            ((2, 900, 128), (1, 1, 16, 4))):
+                            ((2, 900, 128), (1, 1, 16, 4)), ((2, 1700, 200), None), ((3, 1600, 64), None), ((2, 50, 72), (1, 1, 8, 16))):
         print(f"staged backward {cell} B={B} L={L} H={H} tile={tile}", flush=True)
         params, u, h0, g = problem(cell, B, L, H, seed=900 + L, dtype=torch.bfloat16)
         pn, un, h0n, gn = to_np(params), to_np(u), to_np(h0), to_np(g)
@@ -558,7 +569,7 @@ def test_streamed_tile_accesses_give_the_same_bits(P, oracle_mod, as_stored, cel
     interior tiles' accesses marked as streamed (mode 2; what large problems get by themselves) against
     plain accesses (mode 1).  Only the cache policy differs: same bits, iteration count and trace; the
     plain result is checked against the oracle."""
-    B, L, H = 2, 1100, 200
+    B, L, H = 2, 1700, 200                      # above the backward passes in one workgroup
     params, u, h0, g = problem(cell, B, L, H, seed=4242, dtype=dtype)
     pn, un, h0n = to_np(params), to_np(u), to_np(h0)
     fwd, bwd = [], []

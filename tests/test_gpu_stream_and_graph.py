@@ -23,9 +23,11 @@ def relerr(got, ref):
     return float(np.max(np.abs(got - ref)) / max(np.max(np.abs(ref)), 1e-30))
 
 
-def test_forward_and_backward_replay_from_a_graph(oracle_mod):
+@pytest.mark.parametrize("L", [600, 2100])        # one workgroup per channel group; carry records in both directions
+def test_forward_and_backward_replay_from_a_graph(oracle_mod, L):
     import paper_2510_21450_amd as P
-    w = CONFIGS["C2"].scaled(B=2, L=600, H=192)
+    w = CONFIGS["C2"].scaled(B=2, L=L, H=192)
+    assert P.solve_without_blocks(w.cell, torch.float32, w.B, w.L, w.H, w.tol, 16) == (L == 600)
     G, S = cell_dims(w.cell)
     d = make_inputs(w, device="cuda")
     params, u, g = d["params"], d["u"], d["g"]

@@ -82,7 +82,8 @@ def test_reuse_under_graph_capture_clears_every_time():
     """A captured launch sequence replays one call number, so calls that are being captured clear their
     records: replays with changing inputs give the eager results."""
     import paper_2510_21450_amd as P
-    w = CONFIGS["C2"].scaled(B=2, L=900, H=192)
+    w = CONFIGS["C2"].scaled(B=2, L=2100, H=192)            # carry records in both directions
+    assert not P.solve_without_blocks(w.cell, torch.float32, w.B, w.L, w.H, w.tol, 16)
     G, S = cell_dims(w.cell)
     d = make_inputs(w, device="cuda")
     params, u, g = d["params"], d["u"].clone(), d["g"]
@@ -129,6 +130,7 @@ def test_reuse_on_the_library_own_scratch():
     G, S = cell_dims(cell)
 
     def solve(B, L, H, seed, scale):
+        assert not P.solve_without_blocks(cell, torch.float32, B, L, H, 1e-5, 24)       # a solve with carry records
         params = torch.zeros(2, G, H, device="cuda")
         params[0] = uniform_sym(seed, 2, (G, H), 0.9, device="cuda")
         u = normal(seed, 1, (B, L, G, H), device="cuda") * scale
@@ -145,8 +147,8 @@ def test_reuse_on_the_library_own_scratch():
         assert iters.cpu().tolist() == it_ref.cpu().tolist() and torch.equal(h, h_ref)
 
     try:
-        for B, L, H, seed, scale in ((2, 1200, 128, 71, 1.0), (2, 1200, 128, 71, 1.0), (2, 1200, 128, 72, 1.3),
-                                     (1, 500, 64, 73, 1.0), (2, 1200, 128, 71, 0.7)):
+        for B, L, H, seed, scale in ((2, 2100, 128, 71, 1.0), (2, 2100, 128, 71, 1.0), (2, 2100, 128, 72, 1.3),
+                                     (1, 2100, 64, 73, 1.0), (2, 2100, 128, 71, 0.7)):
             print(f"noalloc with reuse B={B} L={L} H={H} seed={seed} scale={scale}", flush=True)
             solve(B, L, H, seed, scale)
     finally:
