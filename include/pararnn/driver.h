@@ -241,8 +241,11 @@ inline float records_us(const ShortCost &k, const CellInfo &ci, int dtype, int B
         return (float)n_iters * (6.0f + n * ((float)ci.G * (dtype == PARARNN_BF16 ? 2.0f : 4.0f) + 8.0f * (float)ci.S) / 5.4f);
     const float its = (float)(n_iters ? n_iters : kShortIters);
     float step = (k.step + k.step_gate * (float)ci.G) * (its + k.rec_more), fixed = n_iters ? k.rec_fixed : k.rec_tol;
-    // the LSTM's sixth iteration is a launch of its own, which reads and writes the iterate, and there are channels that
-    // take a seventh
+    // The LSTM's sixth iteration is a launch of its own, which reads and writes the iterate, and there are channels that
+    // take a seventh: 1.45 of the time of five, or twice it, where a walk takes 1.05.  Six or seven is what the
+    // benchmark's weights (up to 0.9, forget bias 1) take; they are not known here.  With weights up to 0.5 or without the
+    // bias it is five, and where the two are close records would be faster, by up to 1.46 (1024 channels x 50000 fp32: 882 us
+    // against 1284; with six iterations 1233 against 1302; 4200 x 50000 3237 against 4407, with seven 6916 against 4982).
     if (ci.kind == PARARNN_LSTM_DIAG && !n_iters) { step *= 1.45f; fixed += 8.7f; }
     const float narrow = groups < 512.0f ? log2f(512.0f / groups) : 0.0f;
     return fixed + step * n * (1.0f + k.rec_narrow * narrow) + k.rec_tile * its * n_lt;
