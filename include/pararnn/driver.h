@@ -204,8 +204,10 @@ struct ShortShape { int c, lps_log2, w, n_cg, n_items, n_tiles; };
 // The constants are a least-squares fit to 1100 problems on MI355X, each with every shape and with records (scalar and 2x2
 // cells, fp32 and bf16, to a tolerance and with three fixed iterations, 200 to 50000 steps of 300 to 131072 channels): 5-6 %
 // root mean square of either side.  Of 1560 problems 4 take more than 3 % longer this way than with records (worst 7 %), of
-// 400 random ones the fit has not seen 3 (worst 13 %: a single fixed iteration); lines drawn by size had left 247 and 35 (worst
-// 2.2 times).  The mean time is 5 % lower, by shapes that fill their last round.
+// 920 random ones the fit has not seen 9 (worst 1.3 times: a fixed count of eight); lines drawn by size had left 247 and 127
+// (worst 2.3 times).  On 520 of the random ones, timed with every shape, the time is 2.9 % above the fastest on the mean, where
+// those lines were 9.5 % above; 24 of them are more than 3 % slower than by the lines (worst 1.54: a single fixed iteration).
+// A fit to those 520 themselves does no better on the half it has not seen.
 struct ShortCost {
     float step, step_gate;            // per million timestep-channels and iteration: a part, and one for each gate
     float rec_more, rec_tol, rec_fixed;   // with records: iterations' worth of loads and stores; launches, to a tolerance and fixed
@@ -301,6 +303,15 @@ inline bool short_one_tile(int L, int c, int want, int most, ShortShape *sh)
     return sh->w <= most;
 }
 
+// Channels that the kernels with records work on for each one there is: their groups are 8, 32 or 64 wide, and the time of a
+// narrow H is that of a full group (3x3 cells fp32, 478 steps x 52 x 19, 260 workgroups, three iterations: 0.66 of it).
+inline double records_padding(const CellInfo &ci, int dtype, int H, bool backward)
+{
+    const TileCfg cfg = choose_tile(ci, dtype, backward, H, 1, !backward);
+    const int width = cfg.vec * (64 / cfg.ll);
+    return (double)((H + width - 1) / width) * width / (double)H;
+}
+
 // The shape of a forward solve, or false where the kernels with carry records do better.  n_iters: 0 = to a tolerance.
 inline bool short_forward_shape(const CellInfo &ci, int dtype, int B, int L, int H, int n_iters, ShortShape *out)
 {
@@ -317,12 +328,16 @@ inline bool short_forward_shape(const CellInfo &ci, int dtype, int B, int L, int
         if (!short_one_tile(L, c, 4, ci.S * c <= 8 ? 16 : 8, &sh) || !short_complete(ci, dtype, B, L, H, &sh)) return false;
         *out = sh;
         if (ci.S > 2) {
-            // 3x3 / 4x4 cells, times / times with records: up to 256 steps 0.3-0.98 to a tolerance; three fixed iterations 64
-            // steps 0.5-1.0, 128 steps of 1024 workgroups 0.8-0.9, of 2048 1.0-1.1, 256 steps of 1024 0.8-0.94, of 2000
-            // 1.0-1.27.  Beyond, with five to eight waves, of which a unit holds one workgroup: 256 of them 0.4-0.75, 512 0.8-1.0
-            // and fixed 1.2-1.4, 1000 1.0-1.2 and 1.4-1.75.
-            if (L > 256) return sh.n_items <= kShortUnits * (n_iters ? 1 : 2);
-            return L <= 64 || n_iters == 0 || n_iters > kMaxFused || sh.n_items <= 4 * kShortUnits;
+            // 3x3 / 4x4 cells, times / times with records.  To a tolerance up to 256 steps 0.3-0.98.  Three fixed iterations: 40-64
+            // steps 0.47-0.96, 3x3 72-128 steps of 2000 workgroups 0.84-0.94, of 4000 0.9-1.02, 192-256 of 1000 0.72-0.81, of 2000
+            // 0.97-1.03; 4x4 72-256 of 1000 0.85-1.02, of 2000 0.96-1.3.  Eight: 72-256 of 500 0.6-0.78, of 1000 0.84-1.24.  More than
+            // eight are a launch each with records: up to 256 steps 0.18-0.82, 320-500 of 2000 0.83-1.03, of 4000 0.91-1.22.
+            // Beyond 256 steps, with five to eight waves, of which a unit holds one workgroup: 256 of them 0.4-0.8, 500 to a
+            // tolerance 0.8-1.0 and fixed 1.2-1.5, 1000 1.0-1.2 and 1.4-2.0.
+            const double units = kShortUnits * records_padding(ci, dtype, H, false);
+            if (n_iters > kMaxFused) return L <= 256 || sh.n_items <= 8 * units;
+            if (L > 256) return sh.n_items <= units * (n_iters ? 1 : 2);
+            return L <= 64 || n_iters == 0 || sh.n_items <= units * (n_iters > 5 ? 3 : ci.S > 3 ? 4 : L <= 128 ? 12 : 6);
         }
         // below 160 steps the kernels with records are nowhere faster (131072 channels: 0.87-0.93 of their time)
         return tiny || L < 160 || short_us(k, ci, dtype, sh, n_iters) < better * records_us(k, ci, dtype, B, L, H, n_iters);
@@ -351,29 +366,31 @@ inline bool short_forward_shape(const CellInfo &ci, int dtype, int B, int L, int
 // memory pipeline needs as many cycles as for whole lines: fine where latency bounds the other kernels too, not on large
 // tensors.  Bounds on the bytes of a pass, where the two are level: times / times with records,
 //   scalar   128 steps fp32 131072 channels 1.13-1.27, 65536 0.98; 256: fp32 32768 0.97-1.03, bf16 65536 1.0, 131072 1.2; 512:
-//            fp32 16384 0.93, bf16 32768 1.1; 1024: fp32 1332 1.0, bf16 8000 0.94; 1500: bf16 1024 0.73, 1332 1.33
+//            fp32 16384 0.93, bf16 32768 1.1; 1024: fp32 1332 1.0, bf16 8000 0.94; 1500: bf16 1024 0.73, 1332 1.33; 1537-2048: up
+//            to 64 workgroups 0.66-0.96, 128 0.82-1.22, 250 0.72-1.32
 //   2x2      96 steps fp32 65536 0.7-0.9, 131072 0.9-1.1; 160: fp32 32768 0.65-0.8, 65536 0.85-1.2; 192: fp32 16384 0.75-0.87,
 //            32768 0.77-1.07; 256: fp32 16384 0.82-0.99, 32768 0.84 (two gates) to 1.32, bf16 32768 0.8-1.0, 65536 0.92 (two
 //            gates) to 1.31; 320-384: one round of the device, 2048 channels, 0.6-0.9; two 0.98-1.18; 448-512: two 0.9-1.0,
 //            four 0.92-1.07; two gates: two rounds 0.8-0.95, four 0.8-1.1
-//   3x3, 4x4 32 steps 0.6-1.08; up to 256 steps one round (a workgroup on each unit) 0.6-0.75, two 0.75-1.03, four 1.0-1.4; 320-512
-//            one round 0.6-0.85, two 1.07-1.4
+//   3x3, 4x4 up to 64 steps 1000 workgroups 0.84-0.96, 4000 1.05; 72-128 500 0.68-0.88, 1000 0.89-1.16, 2000 0.97-1.3; 192-256
+//            500 0.86-0.95, 1000 1.1-1.3; 320-512 one round (a workgroup on each unit) 0.6-0.85, two 0.99-1.4
 inline bool short_backward_shape(const CellInfo &ci, int dtype, int B, int L, int H, ShortShape *out)
 {
     const double n = (double)B * L * H, bytes = n * (dtype == PARARNN_BF16 ? 2.0 : 4.0) * (2 * ci.G + 2 * ci.S);
     const int c = ci.S > 2 || (n < 512.0 * 512.0 && L <= 1024) ? 4 : 8, most = ci.S * c <= 8 ? 16 : 8;
     if (!short_one_tile(L, c, most, most, out) || !short_complete(ci, dtype, B, L, H, out)) return false;
     const int per_gate = ci.G <= 2 ? 2 : 1;
+    const double units = kShortUnits * records_padding(ci, dtype, H, true);
     if (ci.S == 2 && c == 8 && L > 64 && L <= 192 && out->n_items > kShortUnits * per_gate &&
         (!short_one_tile(L, c, 4, most, out) || !short_complete(ci, dtype, B, L, H, out)))
         return false;
     if (ci.S == 1)
-        return L <= 64 || (L <= 1536 && bytes <= (L <= 256 ? 400e6 : L <= 512 ? 192e6 : L <= 1024 ? 96e6 : 32e6) &&
-                           (L <= 1024 || out->n_items <= kShortUnits));
+        return L <= 64 || (bytes <= (L <= 256 ? 400e6 : L <= 512 ? 192e6 : L <= 1024 ? 96e6 : 32e6) &&
+                           (L <= 1024 || out->n_items <= units * (L <= 1536 ? 1.0 : 0.25)));
     if (L > 512) return false;
-    if (ci.S > 2) return L <= 32 || out->n_items <= kShortUnits * (L <= 256 ? 2 : 1);
+    if (ci.S > 2) return L <= 32 || out->n_items <= units * (L <= 64 ? 8 : L <= 128 ? 3 : L <= 256 ? 2 : 1);
     if (L <= 256) return L <= 64 || bytes <= (L <= 96 ? 420e6 : L <= 160 ? 340e6 : L <= 192 ? 250e6 : 280e6);
-    return bytes <= 192e6 && (c == 4 || out->n_items <= kShortUnits * per_gate * (L > 384 || per_gate > 1 ? 2 : 1));
+    return bytes <= 192e6 && (c == 4 || out->n_items <= units * per_gate * (L > 384 || per_gate > 1 ? 2 : 1));
 }
 
 inline bool short_shape(const CellInfo &ci, int dtype, int B, int L, int H, bool backward, int n_iters, ShortShape *out)

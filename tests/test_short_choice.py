@@ -79,6 +79,8 @@ MEASURED = [
     (LSTM, F32, 8, 4000, 1000, 0, 752, 554), (LSTM, BF16, 8, 50000, 1000, 0, 9715, 6497), (LSTM, F32, 8, 4000, 1000, 3, 352, 397),
     (LSTM, BF16, 4, 600, 225, 3, 33, 19), (GRU, F32, 8, 8000, 1000, 0, 495, 565), (GRU, F32, 8, 1500, 512, 0, 79, 59),
     (GRU, BF16, 4, 65536, 4096, 0, 7602, 8453), (GRU, BF16, 8, 1000, 1000, 0, 94, 64), (TRI, F32, 8, 320, 1000, 3, 62, 132),
+    (TRI, F32, 47, 274, 26, 12, 279, 99), (TRI, F32, 19, 72, 627, 3, 43, 32),
+    (TRI, BF16, 52, 478, 19, 3, 54, 36),
 ]
 
 
@@ -86,7 +88,8 @@ MEASURED_BACKWARD = [
     (LSTM, BF16, 16, 384, 1024, 57, 75), (LSTM, BF16, 16, 192, 2048, 65, 47), (PARALSTM, BF16, 16, 512, 1024, 61, 76),
     (ROT, F32, 32, 128, 4096, 110, 127), (ROT, F32, 4, 512, 1024, 21, 20), (GRU, F32, 32, 128, 4096, 108, 123),
     (GRU, BF16, 4, 1500, 333, 24, 32), (GRU, BF16, 1, 1500, 1024, 25, 18), (TRI, BF16, 8, 320, 1000, 35, 71),
-    (TRI, F32, 4, 128, 1000, 19, 11),
+    (TRI, F32, 4, 128, 1000, 19, 11), (TRI, BF16, 24, 104, 421, 28, 23), (TRI, BF16, 49, 60, 455, 28, 23), (GRU, F32, 1, 1931, 50, 19, 15),
+    (GRU, BF16, 35, 1997, 9, 30, 16), (TRI, BF16, 38, 416, 29, 27, 20), (TRI, BF16, 20, 423, 65, 28, 22),
 ]
 
 
