@@ -63,3 +63,40 @@ def test_other_threads_run_during_a_call(slow, entry):
     flags[1].value = 1
     t.join()
     assert not failed
+
+
+@pytest.mark.parametrize("anomaly", [False, True])
+def test_python_hooks_run_inside_the_calls(anomaly):
+    """What calls back into Python from inside (hooks of saved tensors, the stack that anomaly mode records) takes the lock
+    itself: same results with and without them, also while another thread keeps the interpreter busy."""
+    import paper_2510_21450_amd as P
+    B, L, H = 2, 60, 64
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    rand = lambda *s: torch.randn(*s, generator=gen, device="cuda")
+    x, Wx, bias, params, g = rand(B, L, H), rand(3, H, H) / 8, rand(3, H), 0.3 * rand(2, 3, H), rand(B, L, 1, H)
+
+    def grads():
+        leaves = [t.clone().requires_grad_() for t in (x, Wx, bias, params)]
+        u = P.input_projection_apply(leaves[0], leaves[1], leaves[2], n_heads=1)
+        h = P.rnn_apply("gru_diag", leaves[3], u, None, tol=1e-5, max_iter=30)[0]
+        y = P.rnn_layer("gru_diag", *leaves, n_heads=1, tol=1e-5, max_iter=30)[0]
+        ((h + y) * g).sum().backward()
+        return [h.detach(), y.detach(), *(t.grad for t in leaves)]
+
+    want, packed, stop = grads(), [], threading.Event()
+
+    def spin():
+        while not stop.is_set():
+            sum(range(1000))
+
+    other = threading.Thread(target=spin)
+    other.start()
+    try:
+        with torch.autograd.set_detect_anomaly(anomaly), \
+                torch.autograd.graph.saved_tensors_hooks(lambda t: packed.append(t.shape) or t.cpu(), lambda t: t.cuda()):
+            got = grads()
+    finally:
+        stop.set()
+        other.join()
+    assert len(packed) >= 8 and all(torch.equal(a, b) for a, b in zip(got, want))
