@@ -26,7 +26,7 @@ struct CellInfo { int G, S, PR, kind; };
 struct Settings {
     int fused_enabled;     // launches that run several Newton iterations are allowed
     int fused_head;        // iterations in the first launch of a solve to a tolerance (0 = none)
-    int tile[4];           // tile-shape override {vec, ll, c, w}; vec = 0 none, -1 not yet read from the environment
+    int tile[4];           // tile-shape override {vec, ll, c, w}; vec = 0 none
     unsigned int spin_limit;   // polls of one predecessor before a tile gives up (pararnn_set_spin_limit)
     int stage_enabled;         // kernels that copy their inputs straight into LDS are allowed (pararnn_set_staging)
     int fused_tail;            // the blocks after a solve's first launch share one persistent launch (pararnn_set_fused_tail)
@@ -118,15 +118,7 @@ inline TileCfg choose_tile(const CellInfo &ci, int dtype, bool backward, int H, 
         else if (bf) cfg = {1, 1, 8, 8};                 // 64 channels x 64 steps
         else cfg = {1, 1, 8, 16};                        // 64 channels x 128 steps (3-4 % faster than 32 x 256 on config 2)
     }
-    int *ov = settings().tile;
-    if (ov[0] == -1) {
-        ov[0] = 0;
-        const char *e = getenv("PARARNN_TILE");
-        int v, l, c, w;
-        if (e && sscanf(e, "%d,%d,%d,%d", &v, &l, &c, &w) == 4) {
-            ov[0] = v; ov[1] = l; ov[2] = c; ov[3] = w;
-        }
-    }
+    const int *ov = settings().tile;
     if (ov[0] > 0 && ov[0] <= vmax) {
         cfg.vec = ov[0]; cfg.ll = ov[1]; cfg.c = ov[2]; cfg.w = ov[3];
     }

@@ -17,7 +17,15 @@ namespace pararnn {
 
 Settings &settings()
 {
-    static Settings s = {1, kFusedHead, {-1, 0, 0, 0}, kSpinLimit, 1, 1, 0, 0};
+    static Settings s = [] {            // once, whichever thread comes first
+        Settings r = {1, kFusedHead, {0, 0, 0, 0}, kSpinLimit, 1, 1, 0, 0};
+        const char *e = getenv("PARARNN_TILE");
+        int v, l, c, w;
+        if (e && sscanf(e, "%d,%d,%d,%d", &v, &l, &c, &w) == 4) {
+            r.tile[0] = v; r.tile[1] = l; r.tile[2] = c; r.tile[3] = w;
+        }
+        return r;
+    }();
     return s;
 }
 

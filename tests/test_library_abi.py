@@ -5,6 +5,8 @@ that happens before any device work) behaves as the header says."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -394,3 +396,14 @@ def test_solve_without_blocks_follows_the_settings(lib):
     assert f(*small, 1e-5, 20) == 0
     lib.pararnn_set_fused(1)
     assert f(*small, 1e-5, 20) == 1
+
+
+def test_a_tile_from_the_environment_counts_from_the_first_call():
+    """Read before anything depends on it, by whichever thread comes first."""
+    code = ("import ctypes\n"
+            f"f = ctypes.CDLL({os.path.join(ROOT, 'paper_2510_21450_amd', 'libpararnn.so')!r}).pararnn_solve_without_blocks\n"
+            "f.argtypes = [ctypes.c_int] * 5 + [ctypes.c_float, ctypes.c_int]\n"
+            "print(f(0, 0, 2, 50, 40, 1e-5, 20))\n")
+    for tile, want in (("1,2,8,8", "0"), ("", "1"), ("0,0,0,0", "1")):
+        r = subprocess.run([sys.executable, "-c", code], env=dict(os.environ, PARARNN_TILE=tile), capture_output=True, text=True)
+        assert r.returncode == 0 and r.stdout.strip() == want, (tile, r.stdout, r.stderr)
