@@ -214,6 +214,40 @@ template <bool FOLD> __device__ __forceinline__ float gate_in(float w, float wq,
     else return fmaf(w, h, u + b);
 }
 
+// The part of a cell evaluation that holds its transcendental instructions (v_exp_f32, v_rcp_f32), for kernels whose waves
+// do little else: gates_begin in front of it, gates_end behind it with its results.  In between the wave has priority 1,
+// outside 0.  A SIMD runs plain instructions (fma, mul, add; not min, max, shifts, DPP, or with a scalar operand) of two
+// waves side by side, four cycles for the pair, and a transcendental one for eight cycles on its own.  Left to the
+// default order, the plain instructions next to another wave's transcendental ones go alone.  The GRU's mix, 26 plain and
+// 6 transcendental, in a loop of its own, ns per evaluation and SIMD: four waves 64.6 -> 45.5, two 71.1 -> 46, eight
+// 63.0 -> 44.4 (the plain ones alone 26, the others 20; the whole evaluation at priority 1, 50).  A single wave gains nothing.
+// The compiler moves arithmetic freely across a bare s_setprio: what passes through the marks is what keeps the two
+// parts apart.  gates_begin takes operands that every transcendental instruction depends on and that are in registers
+// of their own anyway (the weights); gates_done, after the part outside, ties that to its place.
+template <int N> __device__ __forceinline__ void gates_tie(float *x)
+{
+#pragma unroll
+    for (int e = 0; e < N; ++e) asm volatile("" : "+v"(x[e]));
+}
+template <int N> __device__ __forceinline__ void gates_begin(float *x)
+{
+    gates_tie<N - 1>(x);
+    asm volatile("s_setprio 1" : "+v"(x[N - 1]));
+}
+template <int N> __device__ __forceinline__ void gates_end(float *x)
+{
+    gates_tie<N - 1>(x);
+    asm volatile("s_setprio 0" : "+v"(x[N - 1]));
+}
+template <int N> __device__ __forceinline__ void gates_done(const float *x)
+{
+#pragma unroll
+    for (int e = 0; e < N; ++e) asm volatile("" ::"v"(x[e]));
+}
+
+// Running maximum of |x|, two values an instruction; a NaN stays (as its bits, which are above those of infinity).
+__device__ __forceinline__ void abs_max(float &m, float x, float y) { asm("v_maximum3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(x), "v"(y)); }
+
 // Workgroup barrier that orders LDS accesses only: global loads and stores
 // issued before it stay in flight (a full __syncthreads() waits for them).
 __device__ __forceinline__ void lds_barrier()

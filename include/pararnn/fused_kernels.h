@@ -361,10 +361,12 @@ void newton_fused_kernel(const FusedArgs a)
                                 for (int s = 0; s < S; ++s) hp[s] = i == 0 ? hprev[s][v] : ho[i - 1][s][v];
 #pragma unroll
                                 for (int q = 0; q < G; ++q) ug[q] = uu[i][q][v];
-                                Cell::template fwd<true>(p[v], hp, ug, F, J, pq[v]);
+                                eval_step<Cell>(p[v], pq[v], hp, ug, F, J);
 #pragma unroll
                                 for (int s = 0; s < S; ++s) r[s] = F[s] - ho[i][s][v];
                                 push_step<S>(J, r, accA[v], accB[v]);
+                                gates_done<SS>(accA[v]);
+                                gates_done<S>(accB[v]);
                             }
                         }
 #pragma unroll
@@ -592,6 +594,7 @@ void newton_fused_kernel(const FusedArgs a)
                 unsigned int wmax_bits = 0u;
                 auto back_substitute = [&](auto gd) {
                     constexpr bool kG = decltype(gd)::value;
+                    float m = 0.0f, last = 0.0f;
 #pragma unroll
                     for (int v = 0; v < VEC; ++v) {
                         // the delta that enters this wave's first step: its prefix applied to the tile's carry
@@ -611,11 +614,16 @@ void newton_fused_kernel(const FusedArgs a)
 #pragma unroll
                             for (int s = 0; s < S; ++s) {
                                 ho[i][s][v] += d[s];
-                                if (!kG || (ch_ok && l0 + i < g.L))
-                                    wmax_bits = max(wmax_bits, __float_as_uint(d[s]) & 0x7fffffffu);
+                                if constexpr (kG) {
+                                    if (ch_ok && l0 + i < g.L) wmax_bits = max(wmax_bits, __float_as_uint(d[s]) & 0x7fffffffu);
+                                } else {
+                                    if ((i * S + s) & 1) abs_max(m, last, d[s]);      // C is even
+                                    last = d[s];
+                                }
                             }
                         }
                     }
+                    if constexpr (!kG) wmax_bits = __float_as_uint(m) & 0x7fffffffu;
                 };
                 if constexpr (kMode == 2) {
                     if (full_tile) back_substitute(std::false_type{});

@@ -250,10 +250,12 @@ __global__ __launch_bounds__((kWave * (MANY ? 8 : short_max_waves<Cell, C>()))) 
                 float J[SS], r[S], hp[S], F[S];
 #pragma unroll
                 for (int s = 0; s < S; ++s) hp[s] = i == 0 ? hprev[s] : ho[i > 0 ? i - 1 : 0][s];
-                Cell::template fwd<true>(p, hp, uu[i], F, J, pq);
+                eval_step<Cell>(p, pq, hp, uu[i], F, J);
 #pragma unroll
                 for (int s = 0; s < S; ++s) r[s] = F[s] - ho[i][s];
                 push_step<S>(J, r, accA, accB);
+                gates_done<SS>(accA);
+                gates_done<S>(accB);
 #pragma unroll
                 for (int e = 0; e < SS; ++e) PA[i][e] = accA[e];
 #pragma unroll
@@ -305,15 +307,22 @@ __global__ __launch_bounds__((kWave * (MANY ? 8 : short_max_waves<Cell, C>()))) 
 #pragma unroll
             for (int s = 0; s < S; ++s) hprev[s] += din[s];
             auto substitute = [&](auto guard) {
+                float m = 0.0f, last = 0.0f;
 #pragma unroll
                 for (int i = 0; i < C; ++i) {
                     affine<S>(PA[i], din, qb[i], d);
 #pragma unroll
                     for (int s = 0; s < S; ++s) {
                         ho[i][s] += d[s];
-                        if (!decltype(guard)::value || i < n_valid) wmax_bits = max(wmax_bits, __float_as_uint(d[s]) & 0x7fffffffu);
+                        if constexpr (decltype(guard)::value) {
+                            if (i < n_valid) wmax_bits = max(wmax_bits, __float_as_uint(d[s]) & 0x7fffffffu);
+                        } else {
+                            if ((i * S + s) & 1) abs_max(m, last, d[s]);
+                            last = d[s];
+                        }
                     }
                 }
+                if constexpr (!decltype(guard)::value) wmax_bits = __float_as_uint(m) & 0x7fffffffu;
             };
             if (all_valid) substitute(std::false_type{});
             else substitute(std::true_type{});

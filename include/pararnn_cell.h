@@ -78,6 +78,20 @@ template <class Impl> struct UserCell {
     {
         Impl::step(p, hp, u, F);
     }
+    static constexpr int NM = S + S * S;               // state and Jacobian: nothing is known about what either needs
+    __device__ __forceinline__ static void begin(float *p, float *) { gates_begin<PR>(p); }
+    template <bool FOLD>
+    __device__ __forceinline__ static void mid(const float *p, const float *, const float *hp, const float *u, float *m)
+    {
+        Impl::step_and_jacobian(p, hp, u, m, m + S);
+    }
+    __device__ __forceinline__ static void jac(const float *, const float *, const float *m, float *F, float *J)
+    {
+#pragma unroll
+        for (int s = 0; s < S; ++s) F[s] = m[s];
+#pragma unroll
+        for (int e = 0; e < S * S; ++e) J[e] = m[S + e];
+    }
     template <bool FOLD = false>
     __device__ __forceinline__ static void fwd(const float *p, const float *hp, const float *u, float *F, float *J,
                                                const float * = nullptr)

@@ -5,9 +5,12 @@
 // values), u[] the G pre-activations.  J is row-major S x S with
 // J[p*S+q] = d(out_p)/d(in_q).
 //
-// step<true> / fwd<true> are the folded forms: u[] then holds fold_u()'s output
+// step<true> / mid<true> are the folded forms: u[] then holds fold_u()'s output
 // (the gate inputs u + b scaled for the exp2-based nonlinearities) and q[] the
 // PQ scaled weights from fold_params(); p[] is still needed for the Jacobian.
+//
+// An evaluation with its Jacobian is mid() (the NM values that need exponentials and reciprocals), then jac(); begin()
+// marks the start of the former (gates_begin in common.h, eval_step in scan_kernels.h).  fwd() is the two in one.
 //
 // Backward (Sec. 2, Eq. (6)): bwd_prep returns J and NC coefficients from which
 // bwd_emit maps the incoming adjoint lam (dL/d state_l) to dL/du_l and adds this
@@ -68,21 +71,32 @@ struct GruDiag {
         J = fmaf(p[1], kr, J);
     }
 
+    static constexpr int NM = 4;                       // z, r, r h, c
+    __device__ __forceinline__ static void begin(float *, float *q) { gates_begin<PQ>(q); }
+    template <bool FOLD>
+    __device__ __forceinline__ static void mid(const float *p, const float *q, const float *hp, const float *u, float *m)
+    {
+        gates<FOLD>(p, q, hp[0], u, m[0], m[1], m[2], m[3]);
+    }
     // The forward pass needs F and J only: J = (1-z) + a_z k_z + a_c k_c (r + a_r r h (1-r)), which
     // skips k_r as a value of its own (one instruction fewer per evaluation than coefs).
-    template <bool FOLD = false>
-    __device__ __forceinline__ static void fwd(const float *p, const float *hp, const float *u, float *F, float *J,
-                                               const float *q = nullptr)
+    __device__ __forceinline__ static void jac(const float *p, const float *hp, const float *m, float *F, float *J)
     {
-        float z, r, rh, c;
-        const float h = hp[0];
-        gates<FOLD>(p, q, h, u, z, r, rh, c);
+        const float h = hp[0], z = m[0], r = m[1], rh = m[2], c = m[3];
         const float cmh = c - h, omz = 1.0f - z;
         F[0] = fmaf(z, cmh, h);
         const float kz = cmh * (z * omz);
         const float ackc = p[2] * (z * fmaf(-c, c, 1.0f));
         const float t = fmaf(p[1], rh * (1.0f - r), r);
         J[0] = fmaf(ackc, t, fmaf(p[0], kz, omz));
+    }
+    template <bool FOLD = false>
+    __device__ __forceinline__ static void fwd(const float *p, const float *hp, const float *u, float *F, float *J,
+                                               const float *q = nullptr)
+    {
+        float m[NM];
+        mid<FOLD>(p, q, hp, u, m);
+        jac(p, hp, m, F, J);
     }
 
     __device__ __forceinline__ static void bwd_prep(const float *p, const float *hp, const float *u,
@@ -143,18 +157,21 @@ struct LstmDiag {
         F[1] = o * fast_tanh(F[0]);
     }
 
+    static constexpr int NM = 6;                       // i, f, o, g, c', tanh(c')
+    __device__ __forceinline__ static void begin(float *, float *q) { gates_begin<PQ>(q); }
+    template <bool FOLD>
+    __device__ __forceinline__ static void mid(const float *p, const float *q, const float *hp, const float *u, float *m)
+    {
+        gates<FOLD>(p, q, hp[1], u, m[0], m[1], m[2], m[3]);
+        m[4] = fmaf(m[1], hp[0], m[0] * m[3]);
+        m[5] = fast_tanh(m[4]);
+    }
     // k[0..3] = d c'/d u_{i,f,g-slot order i,f,o,g} with k[2] = d h'/d u_o,
     // k[4] = o (1 - tanh(c')^2) = d h'/d c', k[5] = h.
-    template <bool FOLD>
-    __device__ __forceinline__ static void coefs(const float *p, const float *q, const float *hp, const float *u,
-                                                 float *F, float *J, float *k)
+    __device__ __forceinline__ static void coefs(const float *p, const float *hp, const float *m, float *F, float *J, float *k)
     {
-        const float c = hp[0], h = hp[1];
-        float i, f, o, g;
-        gates<FOLD>(p, q, h, u, i, f, o, g);
-        const float cn = fmaf(f, c, i * g);
-        const float t = fast_tanh(cn);
-        F[0] = cn;
+        const float c = hp[0], h = hp[1], i = m[0], f = m[1], o = m[2], g = m[3], t = m[5];
+        F[0] = m[4];
         F[1] = o * t;
         k[0] = g * (i * (1.0f - i));
         k[1] = c * (f * (1.0f - f));
@@ -168,20 +185,26 @@ struct LstmDiag {
         J[2] = k[4] * f;
         J[3] = fmaf(k[2], p[2], k[4] * jch);
     }
-
+    __device__ __forceinline__ static void jac(const float *p, const float *hp, const float *m, float *F, float *J)
+    {
+        float k[NC];
+        coefs(p, hp, m, F, J, k);
+    }
     template <bool FOLD = false>
     __device__ __forceinline__ static void fwd(const float *p, const float *hp, const float *u, float *F, float *J,
                                                const float *q = nullptr)
     {
-        float k[NC];
-        coefs<FOLD>(p, q, hp, u, F, J, k);
+        float m[NM];
+        mid<FOLD>(p, q, hp, u, m);
+        jac(p, hp, m, F, J);
     }
 
     __device__ __forceinline__ static void bwd_prep(const float *p, const float *hp, const float *u,
                                                     float *J, float *k)
     {
-        float F[2];
-        coefs<false>(p, nullptr, hp, u, F, J, k);
+        float F[2], m[NM];
+        mid<false>(p, nullptr, hp, u, m);
+        coefs(p, hp, m, F, J, k);
     }
 
     __device__ __forceinline__ static void bwd_emit(const float *k, const float *lam, float *du, float *acc)
@@ -250,19 +273,22 @@ struct ParaLstmDiag {
         F[1] = o * fast_tanh(cn);
     }
 
+    static constexpr int NM = 5;                       // f, z, o, c', tanh(c')
+    __device__ __forceinline__ static void begin(float *, float *q) { gates_begin<3>(q); }
+    template <bool FOLD>
+    __device__ __forceinline__ static void mid(const float *p, const float *q, const float *hp, const float *u, float *m)
+    {
+        gates_fz<FOLD>(p, q, hp[0], hp[1], u, m[0], m[1]);
+        m[3] = fmaf(m[0], hp[0] - m[1], m[1]);
+        m[2] = gate_o<FOLD>(p, q, m[3], hp[1], u);
+        m[4] = fast_tanh(m[3]);
+    }
     // k[0] = d c'/d u_f = (c - z) f(1-f), k[1] = d c'/d u_z = (1-f)(1-z^2),
     // k[2] = d h'/d u_o = t o(1-o), k[3] = o (1-t^2), k[4] = c_o, k[5] = h, k[6] = c, k[7] = c'.
-    template <bool FOLD>
-    __device__ __forceinline__ static void coefs(const float *p, const float *q, const float *hp, const float *u,
-                                                 float *F, float *J, float *k)
+    __device__ __forceinline__ static void coefs(const float *p, const float *hp, const float *m, float *F, float *J, float *k)
     {
-        const float c = hp[0], h = hp[1];
-        float f, z;
-        gates_fz<FOLD>(p, q, c, h, u, f, z);
+        const float c = hp[0], h = hp[1], f = m[0], z = m[1], o = m[2], cn = m[3], t = m[4];
         const float cmz = c - z;
-        const float cn = fmaf(f, cmz, z);
-        const float o = gate_o<FOLD>(p, q, cn, h, u);
-        const float t = fast_tanh(cn);
         F[0] = cn;
         F[1] = o * t;
         k[0] = cmz * (f * (1.0f - f));
@@ -281,20 +307,26 @@ struct ParaLstmDiag {
         J[2] = hc * jcc;
         J[3] = fmaf(k[2], p[2], hc * jch);
     }
-
+    __device__ __forceinline__ static void jac(const float *p, const float *hp, const float *m, float *F, float *J)
+    {
+        float k[NC];
+        coefs(p, hp, m, F, J, k);
+    }
     template <bool FOLD = false>
     __device__ __forceinline__ static void fwd(const float *p, const float *hp, const float *u, float *F, float *J,
                                                const float *q = nullptr)
     {
-        float k[NC];
-        coefs<FOLD>(p, q, hp, u, F, J, k);
+        float m[NM];
+        mid<FOLD>(p, q, hp, u, m);
+        jac(p, hp, m, F, J);
     }
 
     __device__ __forceinline__ static void bwd_prep(const float *p, const float *hp, const float *u,
                                                     float *J, float *k)
     {
-        float F[2];
-        coefs<false>(p, nullptr, hp, u, F, J, k);
+        float F[2], m[NM];
+        mid<false>(p, nullptr, hp, u, m);
+        coefs(p, hp, m, F, J, k);
     }
 
     __device__ __forceinline__ static void bwd_emit(const float *k, const float *lam, float *du, float *acc)
@@ -328,6 +360,18 @@ struct LinearDiag {
                                                 const float * = nullptr)
     {
         F[0] = fmaf(p[0], hp[0], FOLD ? u[0] : u[0] + p[1]);
+    }
+    static constexpr int NM = 1;
+    __device__ __forceinline__ static void begin(float *, float *) {}
+    template <bool FOLD>
+    __device__ __forceinline__ static void mid(const float *p, const float *q, const float *hp, const float *u, float *m)
+    {
+        step<FOLD>(p, hp, u, m, q);
+    }
+    __device__ __forceinline__ static void jac(const float *p, const float *, const float *m, float *F, float *J)
+    {
+        F[0] = m[0];
+        J[0] = p[0];
     }
     template <bool FOLD = false>
     __device__ __forceinline__ static void fwd(const float *p, const float *hp, const float *u, float *F, float *J,
