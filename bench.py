@@ -183,7 +183,7 @@ def block_iterations(w):
 
 
 def without_blocks(w):
-    """Whether the library solves the workload in one launch, one workgroup per group of channels."""
+    """Whether the library solves the workload in one launch, one workgroup or wave per group of channels."""
     import torch
     import paper_2510_21450_amd as P
     if w.cell == "tanh_dense":
@@ -273,7 +273,7 @@ def kernel_figures(run, reps, counters):
         out["block_issue_bound_frac"] = t_issue_ms / t_block_ms
     else:
         out["block_issue_bound_ms"] = out["block_issue_bound_frac"] = None
-    out["roofline"] = {"bound": "alu", "kernel": "newton_short_kernel (the whole solve)" if one_launch else "newton_fused_kernel (first block of a solve)", "achieved": ach,
+    out["roofline"] = {"bound": "alu", "kernel": "newton_walk_kernel or newton_short_kernel (the whole solve)" if one_launch else "newton_fused_kernel (first block of a solve)", "achieved": ach,
                        "peak": VALU_F32_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": ach / VALU_F32_PEAK_TFLOPS,
                        "traffic": cnt.get("dominant", {}).get("traffic_bytes")}
     out["algorithmic_bytes_per_launch"] = ab["block"] * N

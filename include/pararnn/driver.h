@@ -184,7 +184,8 @@ inline Layout make_layout(const CellInfo &ci, int dtype, int B, int L, int H, bo
 
 // Shape of the kernels of short_kernels.h for a problem: c steps per thread, 64 >> lps_log2 segments per wave, w waves;
 // n_items workgroups that walk their sequence in n_tiles tiles.
-struct ShortShape { int c, lps_log2, w, n_cg, n_items, n_tiles; };
+// `walk`: of those of walk_kernels.h, where the group of a workgroup is w times as wide.
+struct ShortShape { int c, lps_log2, w, n_cg, n_items, n_tiles; bool walk = false; };
 
 // What a forward solve takes with the kernels that have carry records and with these, in us.  With records the time follows
 // the number of timestep-channels, and tiles of one channel group wait for each other: few groups cost more per
@@ -389,6 +390,84 @@ inline bool short_shape(const CellInfo &ci, int dtype, int B, int L, int H, bool
 {
     return backward ? short_backward_shape(ci, dtype, B, L, H, out) : short_forward_shape(ci, dtype, B, L, H, n_iters, out);
 }
+// What a forward solve takes where waves walk sequences on their own (walk_kernels.h), in us: rounds of the device as above,
+// with the copies and stores of the tiles beside them.  Rows shorter than a cache line (128 bytes) cost a request each, and what
+// neighbouring workgroups share of a line comes in again once these have drifted apart, the more the longer the sequence.  The
+// constants are a fit to 3400 measurements (scalar and 2x2 cells, fp32 and bf16, to a tolerance and with three fixed
+// iterations, 200 to 65536 steps of 1024 to 131072 channels, every shape): 5-7 % root mean square.  On those 600 problems the
+// shape it takes is 3.0 % (scalar) and 1.8 % (2x2) above the fastest one on the mean (worst 1.3 times); against the kernels
+// with records and the one-workgroup ones the walk takes 0.65 to 0.95 of the time from 3000 channels on.
+struct WalkCost {
+    int c, w, waves;                  // steps per thread, waves, workgroups on a unit by registers
+    float start, one, more_each;      // launch; a tile's iteration: a part, and one for each workgroup on the unit
+    float tol_iters, more;            // iterations of a solve to a tolerance; loads, guess and stores as iterations
+    float last, bf16, level, few;     // a last round after others; bf16; doubling of the channels; few workgroups
+    float bytes, shared, apart;       // TB/s; what the other bytes of a line cost, at once and for each doubling of 1000 steps
+};
+constexpr WalkCost kWalkScalar[2] = {
+    {8, 4, 5, 6.55f, 0.766f, 0.3614f, 4.25f, 0.744f, 0.981f, 1.014f, 0.0533f, 0.0f, 4.89f, 0.088f, 0.0417f},
+    {12, 8, 2, 7.12f, 0.877f, 1.2527f, 4.17f, 1.106f, 0.974f, 0.963f, 0.0574f, 0.044f, 5.24f, 0.169f, 0.0246f}};
+constexpr WalkCost kWalkBlock2[2] = {
+    {8, 4, 3, 7.16f, 1.204f, 0.7797f, 4.73f, 0.751f, 0.947f, 0.990f, 0.0584f, 0.066f, 4.62f, 0.110f, 0.0291f},
+    {16, 4, 2, 7.06f, 2.236f, 1.3244f, 4.99f, 1.025f, 1.003f, 0.900f, 0.0549f, 0.103f, 2.86f, 0.077f, 0.0026f}};
+
+// wide: copies of 16 bytes
+inline float walk_us(const WalkCost &k, const CellInfo &ci, int dtype, bool wide, int L, const ShortShape &sh, double n, int n_iters)
+{
+    const int esz = dtype == PARARNN_BF16 ? 2 : 4, lds_esz = wide ? esz : 4;
+    const size_t lds = (size_t)k.c * ci.G * 64 * k.w * lds_esz + ((size_t)k.w * kShortCarries * ci.S << sh.lps_log2) * 4 + 64;
+    int per_unit = (int)((size_t)163840 / (lds > 1 ? lds : 1));
+    if (per_unit > k.waves) per_unit = k.waves;
+    if (per_unit < 1) return 1e30f;
+    const int full = sh.n_items / (kShortUnits * per_unit), left = sh.n_items - full * kShortUnits * per_unit;
+    auto round = [&](int on) { return k.one + k.more_each * (float)on; };
+    float rounds = (float)full * round(per_unit);
+    if (left) rounds += round((left + kShortUnits - 1) / kShortUnits) * (full > 0 ? k.last : 1.0f);
+    // the fit is of cells with three gates and one state value, and four and two
+    const ShortCost &c = ci.S == 1 ? kCostScalar : kCostBlock2;
+    const float work = (c.step + c.step_gate * (float)ci.G) / (c.step + c.step_gate * (ci.S == 1 ? 3.0f : 4.0f));
+    const float its = n_iters ? (float)n_iters : k.tol_iters;
+    float t = work * (its + k.more) * (float)sh.n_tiles * rounds * (1.0f - k.level * (float)sh.lps_log2);
+    if (esz == 2) t *= k.bf16;
+    if (sh.n_items < kShortUnits) t *= 1.0f - k.few * (1.0f - (float)sh.n_items / (float)kShortUnits);
+    const int row = (k.w << sh.lps_log2) * esz;
+    const float shared = row < 128 ? 128.0f / (float)row - 1.0f : 0.0f;
+    const float m = (float)(n * esz * (ci.G + ci.S)) / (k.bytes * 1e6f) *
+                    (1.0f + shared * (k.shared + (L > 1000 ? k.apart * log2f(0.001f * (float)L) : 0.0f)));
+    return k.start + cbrtf(t * t * t + m * m * m);
+}
+
+// The shape of a forward solve by walk_kernels.h, or false where the other kernels do better: the one-workgroup ones in the
+// shape `other`, with records where that is NULL.  n_iters: 0 = to a tolerance.
+inline bool walk_forward_shape(const CellInfo &ci, int dtype, int B, int L, int H, int n_iters, const ShortShape *other, ShortShape *out)
+{
+    // Fewer waves than there are SIMDs, or a solve of a few launches' time: the others are faster everywhere, and the estimates
+    // below take a microsecond that such a solve does not have.
+    if (ci.S > 2 || ci.G < ci.S || (double)B * H < 1024.0 || (double)B * L * H < 524288.0) return false;
+    const ShortCost &c = ci.S == 1 ? kCostScalar : kCostBlock2;
+    const int esz = dtype == PARARNN_BF16 ? 2 : 4;
+    const bool wide = (size_t)H * esz % 16 == 0;
+    // the estimates of the others are of earlier kernels: the present ones take 0.94 and 0.9 of them
+    const float better = n_iters == 0 || (n_iters >= 3 && n_iters <= 5) ? 0.97f : 0.85f;
+    float best = better * (other ? 0.94f * short_us(c, ci, dtype, *other, n_iters) : 0.9f * records_us(c, ci, dtype, B, L, H, n_iters));
+    bool found = false;
+    for (const WalkCost &k : ci.S == 1 ? kWalkScalar : kWalkBlock2)
+        for (int cwl = 0; cwl <= 4; ++cwl) {
+            ShortShape sh;
+            const int width = k.w << cwl, T = k.c * (64 >> cwl);
+            if (wide && width * esz < 16) continue;
+            if ((double)ci.G * H * esz * (T + 1.0) >= 2147483647.0) continue;      // 32-bit offsets within a tile
+            sh.c = k.c; sh.lps_log2 = cwl; sh.w = k.w; sh.walk = true;
+            sh.n_cg = (H + width - 1) / width;
+            if ((double)B * sh.n_cg > 131072.0) continue;
+            sh.n_items = B * sh.n_cg;
+            sh.n_tiles = (L + T - 1) / T;
+            const float us = walk_us(k, ci, dtype, wide, L, sh, (double)B * L * H, n_iters);
+            if (us < best) { best = us; *out = sh; found = true; }
+        }
+    return found;
+}
+
 // workspace of such a solve: the control block (not used) and the workgroups' verdicts
 inline size_t short_workspace_bytes(size_t n_items)
 {
@@ -628,22 +707,46 @@ int forward_short(int dtype, const ShortShape &sh, const float *params, const vo
     a.spin_limit = short_wait_limit(settings().spin_limit, sh, max_iter);
     a.slots = reinterpret_cast<rec_t *>(ws + round256(sizeof(Ctrl)));
     a.nonce = call_nonce();
-    workspace_forget(workspace);
+    if (sh.walk) {
+        // Nothing here needs what an earlier call left or leaves what a later one could use, but the large problems that are
+        // walked keep their workspaces as those with records do: the block that the caller allocates is as large.
+        unsigned long long sig = 1469598103934665603ull;
+        for (long long x : {2LL, (long long)dtype, (long long)B, (long long)L, (long long)H, (long long)sh.c, (long long)sh.lps_log2, (long long)sh.w})
+            sig = (sig ^ (unsigned long long)x) * 1099511628211ull;
+        bool fill;
+        workspace_epoch(workspace, sig, st, &fill);
+    } else {
+        workspace_forget(workspace);
+    }
     // a captured launch replays its nonce: the verdicts are cleared in front of it
     if (sh.n_items > 1 && stream_is_capturing(st) &&
         launch_reset(reinterpret_cast<Ctrl *>(ws), a.slots, (size_t)sh.n_items * 2, nullptr, 0, st) != hipSuccess)
         return PARARNN_HIP_ERROR;
-    const hipError_t e = dtype == PARARNN_BF16 ? Kernels<Cell, unsigned short>::newton_short(sh.c, sh.w, a, st)
-                                               : Kernels<Cell, float>::newton_short(sh.c, sh.w, a, st);
-    return e == hipSuccess ? PARARNN_OK : PARARNN_HIP_ERROR;
+    const size_t esz = dtype == PARARNN_BF16 ? 2 : 4;
+    const bool wide = (size_t)H * esz % 16 == 0 && aligned(u, 16) && aligned(h, 16);
+    hipError_t e;
+    if (sh.walk)
+        e = dtype == PARARNN_BF16 ? Kernels<Cell, unsigned short>::newton_walk(sh.c, sh.w, wide, a, st)
+                                  : Kernels<Cell, float>::newton_walk(sh.c, sh.w, wide, a, st);
+    else
+        e = dtype == PARARNN_BF16 ? Kernels<Cell, unsigned short>::newton_short(sh.c, sh.w, a, st)
+                                  : Kernels<Cell, float>::newton_short(sh.c, sh.w, a, st);
+    if (e == hipSuccess) return PARARNN_OK;
+    workspace_forget(workspace);
+    return PARARNN_HIP_ERROR;
 }
 
 // Whether a solve without a trace is one launch without blocks, given the workspace for it.
 inline bool without_blocks(const CellInfo &ci, int dtype, int B, int L, int H, float tol, int max_iter, const SolveOpts &opts,
                            ShortShape *sh)
 {
-    return opts.fused_enabled && opts.fused_head > 0 && !(opts.blocks && tol >= 0.0f) && max_iter > 0 && settings().tile[0] <= 0 &&
-           short_shape(ci, dtype, B, L, H, false, tol < 0.0f ? max_iter : 0, sh);
+    if (!opts.fused_enabled || opts.fused_head <= 0 || (opts.blocks && tol >= 0.0f) || max_iter < 1 || settings().tile[0] > 0) return false;
+    const int n_iters = tol < 0.0f ? max_iter : 0;
+    ShortShape other;
+    const bool one_workgroup = short_shape(ci, dtype, B, L, H, false, n_iters, &other);
+    if (walk_forward_shape(ci, dtype, B, L, H, n_iters, one_workgroup ? &other : nullptr, sh)) return true;
+    *sh = other;
+    return one_workgroup;
 }
 
 // A forward solve with checked arguments: layout, then the launches.

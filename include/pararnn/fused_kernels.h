@@ -350,7 +350,7 @@ void newton_fused_kernel(const FusedArgs a)
                     for (int s = 0; s < S; ++s) accB[v][s] = 0.0f;
                 }
                 auto thread_level = [&](auto gd) {
-                    constexpr bool kG = decltype(gd)::value;
+                    constexpr bool kG = decltype(gd)::value, kMark = LL < 8;     // eight channels wide: few waves
 #pragma unroll
                     for (int i = 0; i < C; ++i) {
                         if (!kG || l0 + i < g.L) {
@@ -361,12 +361,14 @@ void newton_fused_kernel(const FusedArgs a)
                                 for (int s = 0; s < S; ++s) hp[s] = i == 0 ? hprev[s][v] : ho[i - 1][s][v];
 #pragma unroll
                                 for (int q = 0; q < G; ++q) ug[q] = uu[i][q][v];
-                                eval_step<Cell>(p[v], pq[v], hp, ug, F, J);
+                                eval_step<Cell, kMark>(p[v], pq[v], hp, ug, F, J);
 #pragma unroll
                                 for (int s = 0; s < S; ++s) r[s] = F[s] - ho[i][s][v];
                                 push_step<S>(J, r, accA[v], accB[v]);
-                                gates_done<SS>(accA[v]);
-                                gates_done<S>(accB[v]);
+                                if constexpr (kMark) {
+                                    gates_done<SS>(accA[v]);
+                                    gates_done<S>(accB[v]);
+                                }
                             }
                         }
 #pragma unroll

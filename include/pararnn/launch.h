@@ -3,6 +3,7 @@
 #pragma once
 #include "fused_kernels.h"
 #include "short_kernels.h"
+#include "walk_kernels.h"
 
 namespace pararnn {
 
@@ -33,6 +34,8 @@ template <class Cell, typename UT> struct Kernels {
     static hipError_t newton_fused(const TileCfg &cfg, const FusedArgs &a, hipStream_t st);
     // sequences that fit one workgroup of w waves, c steps per thread (short_kernels.h)
     static hipError_t newton_short(int c, int w, const ShortArgs &a, hipStream_t st);
+    // sequences walked by a wave each (walk_kernels.h); `wide`: rows and tensors are aligned to 16 bytes
+    static hipError_t newton_walk(int c, int w, bool wide, const ShortArgs &a, hipStream_t st);
     static hipError_t backward_short(int c, int w, const ShortArgs &a, hipStream_t st);
 };
 

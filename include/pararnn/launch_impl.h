@@ -160,6 +160,34 @@ hipError_t Kernels<Cell, UT>::newton_short(int c, int w, const ShortArgs &a, hip
 }
 
 template <class Cell, typename UT>
+hipError_t Kernels<Cell, UT>::newton_walk(int c, int w, bool wide, const ShortArgs &a, hipStream_t st)
+{
+    if constexpr (IsRaw<Cell>::value) {
+        return hipErrorInvalidValue;
+    } else {
+        const unsigned int grid = 8u * (unsigned int)((a.n_items + 7) / 8);
+        // the last tile starts inside the sequence, the tiles cover it
+        const long long steps = (long long)c * (kWave >> a.lps_log2);
+        if (a.n_tiles < 1 || (a.n_tiles - 1) * steps >= a.L || a.n_tiles * steps < a.L) return hipErrorInvalidValue;
+#define PARARNN_CASE(C, W, CWL, WIDE)                                                                                 \
+    if constexpr (walk_offered<Cell, C, W, CWL, UT, WIDE>()) {                                                        \
+        if (c == C && w == W && a.lps_log2 == CWL && wide == WIDE) {                                                  \
+            hipLaunchKernelGGL((newton_walk_kernel<Cell, C, W, CWL, UT, WIDE>), dim3(grid), dim3(kWave * W), 0, st, a); \
+            return hipGetLastError();                                                                                 \
+        }                                                                                                             \
+    }
+#define PARARNN_WIDTHS(C, W)                                                                                          \
+    PARARNN_CASE(C, W, 0, true) PARARNN_CASE(C, W, 1, true) PARARNN_CASE(C, W, 2, true) PARARNN_CASE(C, W, 3, true)   \
+    PARARNN_CASE(C, W, 4, true) PARARNN_CASE(C, W, 0, false) PARARNN_CASE(C, W, 1, false) PARARNN_CASE(C, W, 2, false) \
+    PARARNN_CASE(C, W, 3, false) PARARNN_CASE(C, W, 4, false)
+        PARARNN_WIDTHS(8, 4) PARARNN_WIDTHS(12, 8) PARARNN_WIDTHS(16, 4)
+#undef PARARNN_WIDTHS
+#undef PARARNN_CASE
+        return hipErrorInvalidValue;
+    }
+}
+
+template <class Cell, typename UT>
 hipError_t Kernels<Cell, UT>::backward_short(int c, int w, const ShortArgs &a, hipStream_t st)
 {
     if constexpr (IsRaw<Cell>::value) {

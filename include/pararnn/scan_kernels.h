@@ -204,13 +204,14 @@ __device__ __forceinline__ void push_step(const float *J, const float *r, float 
 // F and J of a step, for the kernels that iterate in registers: the part with the transcendental instructions first, at
 // raised priority (gates_begin).  Two steps at a time, whose chains of exponential and reciprocal could fill each other's
 // waits, gain 9 % in a loop of their own and lose 3 % in the kernels (forward and backward of 16 x 4096 x 1024 fp32: 814 us, 793 with one).
-template <class Cell>
+// MARK = false for shapes whose waves have a SIMD to themselves: nothing to gain, and the marks cost 2-4 %.
+template <class Cell, bool MARK = true>
 __device__ __forceinline__ void eval_step(float *p, float *pq, const float *hp, const float *u, float *F, float *J)
 {
     float m[Cell::NM];
-    Cell::begin(p, pq);
+    if constexpr (MARK) Cell::begin(p, pq);
     Cell::template mid<true>(p, pq, hp, u, m);
-    gates_end<Cell::NM>(m);
+    if constexpr (MARK) gates_end<Cell::NM>(m);
     Cell::jac(p, hp, m, F, J);
 }
 

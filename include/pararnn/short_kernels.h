@@ -148,11 +148,69 @@ __device__ __forceinline__ void short_report(unsigned int v, int max_iter, int *
     iters_out[1] = status;
 }
 
+// The verdict of the whole solve from those of its workgroups: v of workgroup `item`, of W waves; s_max is scratch for them.
+__device__ __forceinline__ void short_collect(const ShortArgs &a, int item, unsigned int v, int W, unsigned int *s_max)
+{
+    const int lane = threadIdx.x & 63, w = (int)(threadIdx.x >> 6);
+    if (a.n_items == 1) {
+        if (threadIdx.x == 0) short_report(v, a.max_iter, a.iters_out);
+    } else {
+        const unsigned int hi = (unsigned int)(a.nonce >> 32), lo = (unsigned int)a.nonce;
+        if (item > 0) {
+            if (threadIdx.x == 0) {
+                __hip_atomic_store(a.slots + 2 * (size_t)item, ((rec_t)hi << 32) | v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(a.slots + 2 * (size_t)item + 1, ((rec_t)lo << 32) | v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            return;
+        }
+        // workgroup 0 waits for the others, which wait for nothing; eight verdicts per trip to memory
+        constexpr int kBatch = 8;
+        for (int i0 = 1 + (int)threadIdx.x; i0 < a.n_items; i0 += kBatch * (int)blockDim.x) {
+            unsigned int polls = 0;
+            for (;;) {
+                rec_t w0[kBatch], w1[kBatch];
+#pragma unroll
+                for (int j = 0; j < kBatch; ++j) {
+                    const int i = min(i0 + j * (int)blockDim.x, a.n_items - 1);
+                    w0[j] = rec_load(a.slots + 2 * (size_t)i);
+                    w1[j] = rec_load(a.slots + 2 * (size_t)i + 1);
+                }
+                bool all = true;
+                unsigned int vb = 0u;
+#pragma unroll
+                for (int j = 0; j < kBatch; ++j) {
+                    all = all && (unsigned int)(w0[j] >> 32) == hi && (unsigned int)(w1[j] >> 32) == lo &&
+                          (unsigned int)w0[j] == (unsigned int)w1[j];
+                    vb = max(vb, (unsigned int)w0[j]);
+                }
+                if (all) { v = max(v, vb); break; }
+                if (++polls >= a.spin_limit) { v = 0xffffffffu; break; }
+                // A workgroup that polls without a pause takes its compute unit from the one beside it, which is what it
+                // waits for: it ended at 547 us where the others had by 428 (GRU fp32 4096 x 16 x 1024, five iterations).
+                // Pauses of up to a fortieth of the time waited.
+                if (polls < 16) __builtin_amdgcn_s_sleep(1);
+                else if (polls < 64) __builtin_amdgcn_s_sleep(4);
+                else if (polls < 128) __builtin_amdgcn_s_sleep(16);
+                else __builtin_amdgcn_s_sleep(64);
+            }
+        }
+        __syncthreads();                               // s_max is free again
+        v = wave_max_u32(v);
+        if (lane == 0) s_max[w] = v;
+        __syncthreads();
+        if (w == 0) {
+            v = wave_max_u32(s_max[lane < W ? lane : 0]);
+            if (lane == 0) short_report(v, a.max_iter, a.iters_out);
+        }
+    }
+}
+
 // MANY: more than one tile (at most eight waves)
 template <class Cell, int C, typename UT, bool MANY>
 __global__ __launch_bounds__((kWave * (MANY ? 8 : short_max_waves<Cell, C>()))) __attribute__((amdgpu_waves_per_eu(short_min_waves(Cell::S, C, MANY)))) void newton_short_kernel(const ShortArgs a)
 {
     constexpr int S = Cell::S, G = Cell::G, SS = S * S, PR = Cell::PR;
+    constexpr bool kMark = C > 4 || S > 2;             // scalar and 2x2 cells: four steps are for problems of a few waves
     extern __shared__ float s_agg[];                   // [W][SS + S][CW] wave aggregates; several tiles: [2][kShortCarries][S][CW] carries
     __shared__ unsigned int s_max[16];
     const int item = short_item(a.n_items);
@@ -250,12 +308,14 @@ __global__ __launch_bounds__((kWave * (MANY ? 8 : short_max_waves<Cell, C>()))) 
                 float J[SS], r[S], hp[S], F[S];
 #pragma unroll
                 for (int s = 0; s < S; ++s) hp[s] = i == 0 ? hprev[s] : ho[i > 0 ? i - 1 : 0][s];
-                eval_step<Cell>(p, pq, hp, uu[i], F, J);
+                eval_step<Cell, kMark>(p, pq, hp, uu[i], F, J);
 #pragma unroll
                 for (int s = 0; s < S; ++s) r[s] = F[s] - ho[i][s];
                 push_step<S>(J, r, accA, accB);
-                gates_done<SS>(accA);
-                gates_done<S>(accB);
+                if constexpr (kMark) {
+                    gates_done<SS>(accA);
+                    gates_done<S>(accB);
+                }
 #pragma unroll
                 for (int e = 0; e < SS; ++e) PA[i][e] = accA[e];
 #pragma unroll
@@ -360,52 +420,7 @@ __global__ __launch_bounds__((kWave * (MANY ? 8 : short_max_waves<Cell, C>()))) 
         if (k_before == k && k > 1 && mk <= 0.125f * a.tol) k_final = k - 1;
     }
 
-    // ---- the verdict of the whole solve
-    if (a.n_items == 1) {
-        if (threadIdx.x == 0) short_report(v, a.max_iter, a.iters_out);
-    } else {
-        const unsigned int hi = (unsigned int)(a.nonce >> 32), lo = (unsigned int)a.nonce;
-        if (item > 0) {
-            if (threadIdx.x == 0) {
-                __hip_atomic_store(a.slots + 2 * (size_t)item, ((rec_t)hi << 32) | v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(a.slots + 2 * (size_t)item + 1, ((rec_t)lo << 32) | v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-            return;
-        }
-        // workgroup 0 waits for the others, which wait for nothing; eight verdicts per trip to memory
-        constexpr int kBatch = 8;
-        for (int i0 = 1 + (int)threadIdx.x; i0 < a.n_items; i0 += kBatch * (int)blockDim.x) {
-            unsigned int polls = 0;
-            for (;;) {
-                rec_t w0[kBatch], w1[kBatch];
-#pragma unroll
-                for (int j = 0; j < kBatch; ++j) {
-                    const int i = min(i0 + j * (int)blockDim.x, a.n_items - 1);
-                    w0[j] = rec_load(a.slots + 2 * (size_t)i);
-                    w1[j] = rec_load(a.slots + 2 * (size_t)i + 1);
-                }
-                bool all = true;
-                unsigned int vb = 0u;
-#pragma unroll
-                for (int j = 0; j < kBatch; ++j) {
-                    all = all && (unsigned int)(w0[j] >> 32) == hi && (unsigned int)(w1[j] >> 32) == lo &&
-                          (unsigned int)w0[j] == (unsigned int)w1[j];
-                    vb = max(vb, (unsigned int)w0[j]);
-                }
-                if (all) { v = max(v, vb); break; }
-                if (++polls >= a.spin_limit) { v = 0xffffffffu; break; }
-                __builtin_amdgcn_s_sleep(1);
-            }
-        }
-        __syncthreads();                               // s_max is free again
-        v = wave_max_u32(v);
-        if (lane == 0) s_max[w] = v;
-        __syncthreads();
-        if (w == 0) {
-            v = wave_max_u32(s_max[lane < W ? lane : 0]);
-            if (lane == 0) short_report(v, a.max_iter, a.iters_out);
-        }
-    }
+    short_collect(a, item, v, W, s_max);
 }
 
 // The adjoint scan and the gradients (Eq. (6)), formulas and variables as in backward_kernel.
