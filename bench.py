@@ -188,7 +188,8 @@ def without_blocks(w):
     import paper_2510_21450_amd as P
     if w.cell == "tanh_dense":
         return False
-    return P.solve_without_blocks(w.cell, torch.bfloat16 if w.dtype == "bf16" else torch.float32, w.B, w.L, w.H, w.tol, w.max_iter)
+    problem = (w.cell, torch.bfloat16 if w.dtype == "bf16" else torch.float32, w.B, w.L, w.H, w.tol, w.max_iter)
+    return P.solve_without_blocks(*problem) or P.solve_walked(*problem)
 
 
 def kernel_figures(run, reps, counters):

@@ -179,8 +179,8 @@ int pararnn_set_streaming(int mode);
  * END of that launch -- the converged iterate refined by the Newton iterations
  * that were already in flight -- so it differs from the per-iteration path's h
  * by less than tol.  With the default of 5, problems of sizes the library
- * chooses (pararnn_solve_without_blocks) have no blocks: one workgroup or wave per
- * channel group solves them in a single launch, and each group of channels returns the
+ * chooses (pararnn_solve_without_blocks, pararnn_solve_walked) have no blocks: one workgroup
+ * or wave per channel group solves them in a single launch, and each group of channels returns the
  * iterate that met the tolerance within it, where channels that a group walks in
  * several pieces along L may have merged the last updates that cross from one
  * piece into the next, none larger than tol / 8.  0 <= n_iters <= 8; 0 turns it
@@ -245,14 +245,17 @@ int pararnn_workspace_rest(void *workspace, void *rest, size_t rest_bytes);
  * stopping test is evaluated for every iteration and acted on between blocks.
  * The first block (two-state and larger cells: the first two) is a launch of its own; the following ones share one
  * launch (pararnn_set_fused_tail) or are launches of their own.  Problems that the library solves without blocks
- * (pararnn_solve_without_blocks; the plan does not know their sizes) are one launch in which every group of channels
+ * (pararnn_solve_without_blocks, pararnn_solve_walked; the plan does not know their sizes) are one launch in which every group of channels
  * ends after its own number of iterations, at most max_iter. */
 int pararnn_solve_plan(float tol, int max_iter, int *block_sizes, int capacity);
 
 /* 1 if pararnn_forward without delta_trace solves this problem, with the library's present settings, in one launch
- * without blocks (one workgroup or wave per group of channels), 0 if it runs the blocks of pararnn_solve_plan, -1 on
- * invalid arguments (host only; 0 for the dense cell). */
+ * without blocks, one workgroup per group of channels, 0 if it runs the blocks of pararnn_solve_plan or walks the sequences
+ * (pararnn_solve_walked), -1 on invalid arguments (host only; 0 for the dense cell). */
 int pararnn_solve_without_blocks(int cell, int dtype, int B, int L, int H, float tol, int max_iter);
+/* The same for solves without blocks in which every wave walks the sequences of a group of channels on its own: 1 or 0, -1 on
+ * invalid arguments. */
+int pararnn_solve_walked(int cell, int dtype, int B, int L, int H, float tol, int max_iter);
 
 /*
  * Forward: solve Eq. (2) by Newton iterations (Alg. 1a).

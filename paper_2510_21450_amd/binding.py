@@ -240,10 +240,19 @@ def solve_plan(tol: float, max_iter: int):
 
 def solve_without_blocks(cell, dtype, B: int, L: int, H: int, tol: float, max_iter: int) -> bool:
     """pararnn_solve_without_blocks (built-in cells): whether `forward` solves this problem in one launch without the blocks
-    of `solve_plan`."""
+    of `solve_plan`, one workgroup per group of channels."""
     r = _lib.pararnn_solve_without_blocks(CELLS[cell], DTYPES[dtype], B, L, H, ctypes.c_float(tol), int(max_iter))
     if r < 0:
         raise ValueError("pararnn_solve_without_blocks: invalid arguments")
+    return bool(r)
+
+
+def solve_walked(cell, dtype, B: int, L: int, H: int, tol: float, max_iter: int) -> bool:
+    """pararnn_solve_walked (built-in cells): whether `forward` solves this problem in one launch without the blocks of
+    `solve_plan`, every wave walking the sequences of a group of channels."""
+    r = _lib.pararnn_solve_walked(CELLS[cell], DTYPES[dtype], B, L, H, ctypes.c_float(tol), int(max_iter))
+    if r < 0:
+        raise ValueError("pararnn_solve_walked: invalid arguments")
     return bool(r)
 
 

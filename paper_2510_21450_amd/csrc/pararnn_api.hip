@@ -315,13 +315,27 @@ int pararnn_solve_plan(float tol, int max_iter, int *block_sizes, int capacity)
     return launches;
 }
 
-int pararnn_solve_without_blocks(int cell, int dtype, int B, int L, int H, float tol, int max_iter)
+// 0 blocks, 1 one workgroup per channel group, 2 waves that walk, -1 invalid arguments
+static int solve_route(int cell, int dtype, int B, int L, int H, float tol, int max_iter)
 {
     CellInfo ci;
     ShortShape sh;
     if (!cell_info(cell, &ci) || (dtype != PARARNN_F32 && dtype != PARARNN_BF16) || !dims_ok(B, L, H) || max_iter < 0 || tol != tol)
         return -1;
-    return cell != PARARNN_TANH_DENSE && without_blocks(ci, dtype, B, L, H, tol, max_iter, default_opts(), &sh) ? 1 : 0;
+    if (cell == PARARNN_TANH_DENSE || !without_blocks(ci, dtype, B, L, H, tol, max_iter, default_opts(), &sh)) return 0;
+    return sh.walk ? 2 : 1;
+}
+
+int pararnn_solve_without_blocks(int cell, int dtype, int B, int L, int H, float tol, int max_iter)
+{
+    const int r = solve_route(cell, dtype, B, L, H, tol, max_iter);
+    return r == 2 ? 0 : r;
+}
+
+int pararnn_solve_walked(int cell, int dtype, int B, int L, int H, float tol, int max_iter)
+{
+    const int r = solve_route(cell, dtype, B, L, H, tol, max_iter);
+    return r < 0 ? r : r == 2 ? 1 : 0;
 }
 
 int pararnn_set_fused_head(int n_iters)
