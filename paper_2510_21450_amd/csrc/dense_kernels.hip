@@ -3,7 +3,8 @@
 //
 // The linear solve of a Newton iteration is block bi-diagonal.  Two ways through it (wavefront_pays chooses):
 // forward substitution, all iterations of a block at once as a wavefront (dense_wavefront_kernel,
-// dense_adjoint_kernel: latency-bound, one workgroup per sequence, whole solves in two launches), and the chunked scan:
+// dense_adjoint_kernel: latency-bound, one workgroup per sequence, whole solves in two launches; sequences fewer than the
+// compute units are cut into stretches that run side by side, DenseStretch), and the chunked scan:
 //
 // One Newton iteration (Alg. 1a) is four launches (chunk_products and the local sweep share one):
 //   residual  F_l = tanh(W h_{l-1} + u_l), d_l = 1 - F_l^2, r_l = F_l - h_l   (Eq. (3))
@@ -1126,148 +1127,275 @@ template <int N> __device__ __forceinline__ f4v *ring_slot(float (*ring)[N], int
     return reinterpret_cast<f4v *>(&ring[(t + (lane >> 4)) & (kRing - 1)][at + 4 * (lane & 15)]);
 }
 
-// One workgroup per sequence.  A sequence whose own update meets the tolerance at the end of a block is done:
-// the blocks after it are run by the sequences that are not.  gm[k-1]: max |delta| of iteration k over the
-// sequences that ran it.  The last workgroup to finish reports the first iteration whose maximum met the tolerance.
+// Stretches of a sequence.  The chain of L steps is what bounds a substitution, and most of the device has nothing to do
+// meanwhile.  So a sequence is cut into n stretches that run side by side.  What enters a stretch is the update of its
+// last step before, delta of every iteration, and nothing else (y and h come from it and the rows): a stretch starts
+// kWarm steps early from delta = 0, and by its own first step a recurrence that contracts has forgotten that.  Whether it
+// has is looked at: every stretch leaves the updates it reached at the step before its own first one, and at its last;
+// where the two that belong together differ by more than kWarmTol (eight units of the last place of a state of 1), in
+// any iteration and row, the sequence is solved again from its first step, as a whole.  Where they agree the
+// states are those of one chain but for a rounding at a few steps.  The benchmark's W (0.8 N(0, 1/64)) agrees to 2e-7
+// after 24-26 steps with u ~ N(0, 1), 52-64 with u a tenth to a third of that; 1.2 N(0, 1/64) after 50-61.
+constexpr int kWarm = 64;
+constexpr int kWarmLeast = 32;        // steps of a stretch at least: shorter ones would be half warm-up and more
+constexpr float kWarmTol = 4.8e-7f;
+
+struct DenseStretch {
+    int n, len;                       // stretches of a sequence (1: none, the whole sequence at once), steps of each but the last
+    float *h0it;                      // initial guess, where the result does not take its place
+    float *y;                         // y of the iterate that the stretches leave behind
+    float *edge;                      // [B][n][2][kWaveIters][64] updates at the step before the first one and at the last one
+    unsigned int *top;                // [B][n][kWaveIters] max |delta|
+};
+
+// Where a block of iterations reads and leaves its rows, and which: steps from `first` on are run, `start` to `end` count.
+struct WaveRows {
+    const float *h_in, *y_in;         // of the sequence
+    float *h_out, *y_out;
+    int first, start, end;
+};
+
+constexpr int kWavePer = 3 * DH + 16, kWaveRec = kWaveIters * kWavePer + 2 * DH;
+struct WaveLds {
+    __attribute__((aligned(16))) float x[2][DH * kWaveIters];        // delta, in the order of wave_products
+    __attribute__((aligned(16))) float rec[kRing][kWaveRec];
+    unsigned int m[kWaveIters];
+};
+
+// A block of K iterations over the rows q of sequence b, by a whole workgroup; wr: W as wave_products wants it.
+// s.m[i]: max |delta| of iteration i.  EDGE: the updates that DenseStretch::edge holds go to `edge`.
 //
-// Record of step t: for iteration i (0 ..) at timestep l = t - i three rows from float kPer i on: h_l and y_{l-1} of the
+// Record of step t: for iteration i (0 ..) at timestep l = first + t - i three rows from float kWavePer i on: h_l and y_{l-1} of the
 // iterate before (left there by iteration i - 1 in step t - 1, by the mover for i = 0), and kTanhScale * u_l.  The
 // sixteen floats behind them put the four iterations of a wave's access into four different quarters of the banks.
 // Steps before an iteration's first timestep find zeros there, which give delta = 0.
-__global__ __launch_bounds__(320) void dense_wavefront_kernel(const DenseArgs a, unsigned int *gm)
+template <bool EDGE>
+__device__ __forceinline__ void wavefront_block(const DenseArgs &a, int b, int K, const WaveRows &q, const float (&wr)[16], WaveLds &s,
+                                                float *edge)
 {
-    constexpr int kPer = 3 * DH + 16, kRec = kWaveIters * kPer + 2 * DH;
-    __shared__ __attribute__((aligned(16))) float s_x[2][DH * kWaveIters];   // delta, in the order of wave_products
-    __shared__ __attribute__((aligned(16))) float s_rec[kRing][kRec];
-    __shared__ unsigned int s_m[kWaveIters];
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int b = blockIdx.x, L = a.L;
-    const unsigned int seq_bytes = (unsigned int)L * (DH * 4u);
-    const int it = lane >> 4, r = lane & 15, row = 16 * (w & 3) + r;  // this lane: iteration `it` of a block, one row
-    float wr[16];
+    const int it = lane >> 4, r = lane & 15, row = 16 * (w & 3) + r;  // this lane: iteration `it` of the block, one row
+    const int xw = 64 * (w & 3) + 16 * (r >> 2) + 4 * it + (r & 3);  // where this lane's delta goes
+    const int L = q.end - q.first, lead = q.start - q.first;         // steps, of which the first do not count
+    const int n_groups = (L + K - 1 + kWaveGroup - 1) / kWaveGroup;
+    if (threadIdx.x < DH * kWaveIters) s.x[0][threadIdx.x] = 0.0f;
+    if (threadIdx.x < kWaveIters) s.m[threadIdx.x] = 0u;
+    if (w == 4) {
+        const unsigned int seq_bytes = (unsigned int)a.L * (DH * 4u);
+        const buf_rsrc ru = seq_rsrc(a.u + (size_t)b * a.L * DH, seq_bytes), rh = seq_rsrc(q.h_in, seq_bytes), ry = seq_rsrc(q.y_in, seq_bytes);
+        // results: the rows that count, y those before them
+        const int y0 = q.start > 0 ? q.start - 1 : 0;
+        const buf_rsrc oh = seq_rsrc(q.h_out + (size_t)q.start * DH, (unsigned int)(q.end - q.start) * (DH * 4u)),
+                       oy = seq_rsrc(q.y_out + (size_t)y0 * DH, (unsigned int)(q.end - 1 - y0) * (DH * 4u));
+        f4v xh[2], xy[2], xu[2];
+        auto same = [&](int t) { return q.first + t; };
+        auto before = [&](int t) { return q.first + t - 1; };
+        auto bring = [&](int t) {
+            rows_load(rh, xh, lane, t, same);
+            rows_load(ry, xy, lane, t, before);
+            rows_load(ru, xu, lane, t, same);
+        };
+        auto put = [&](int t) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                *ring_slot(s.rec, 0, lane, t + 4 * j) = xh[j];
+                *ring_slot(s.rec, DH, lane, t + 4 * j) = xy[j];
+#pragma unroll
+                for (int i = 0; i < kWaveIters; ++i) *ring_slot(s.rec, kWavePer * i + 2 * DH, lane, t + 4 * j + i) = xu[j] * kTanhScale;
+            }
+        };
+        auto take = [&](int t) {                           // what iteration K - 1 left in the records t .. t + 7
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                xh[j] = *ring_slot(s.rec, kWavePer * K, lane, t + 4 * j);
+                xy[j] = *ring_slot(s.rec, kWavePer * K + DH, lane, t + 4 * j);
+            }
+            rows_store(oh, xh, lane, t - K, [&](int l) { return l - lead; });
+            rows_store(oy, xy, lane, t - K, [&](int l) { return q.first + l - 1 - y0; });
+        };
+#pragma unroll
+        for (int i = 1; i < kWaveIters; ++i)
+            for (int t = 0; t < i; ++t) s.rec[t][kWavePer * i + 2 * DH + lane] = 0.0f;
+        bring(0);
+        put(0);
+        // y in front of the sequence's first row: W h0, the same for every iteration
+        if (q.first == 0) s.rec[0][DH + lane] = a.h0 ? a.r[(size_t)b * DH + lane] : 0.0f;
+        lds_barrier();
+        for (int g = 0; g < n_groups; ++g) {
+            const int t0 = g * kWaveGroup;
+            lds_barrier();
+            if (g > 0) take(t0 - kWaveGroup + 1);          // records t0 - 7 .. t0: complete with the first step of this group
+            bring(t0 + kWaveGroup);
+#pragma unroll 1
+            for (int i = 1; i < kWaveGroup - 2; ++i) lds_barrier();
+            put(t0 + kWaveGroup);                          // the group's last step reads the first of these records
+            lds_barrier();
+            lds_barrier();
+        }
+        lds_barrier();
+        take((n_groups - 1) * kWaveGroup + 1);
+    } else {
+        float mymax = 0.0f, h_in, y_in, us;
+        float *my_edge = EDGE ? edge + it * DH + row : nullptr;
+        // what this lane's iteration leaves for the next one in record `rec`, and what it finds there itself
+        auto hand_on = [&](float *record, float hn, float yn) {
+            float *rec = record + kWavePer * it + row;
+            rec[kWavePer] = hn;
+            rec[kWavePer + DH] = yn;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the reader is in this wave
+            __builtin_amdgcn_wave_barrier();
+            h_in = rec[0];
+            y_in = rec[DH];
+            us = rec[2 * DH];
+        };
+        // kind 0: all timesteps count; 1: some do not, or it is one whose update is handed out; 2: none counts
+        auto step = [&](auto kind, int kB, float *next_rec, int t) {
+            constexpr int kKind = decltype(kind)::value;
+            const f4v xv = *reinterpret_cast<const f4v *>(&s.x[kB][4 * lane]);
+            __builtin_amdgcn_sched_barrier(0);
+            const float F = tanh_scaled(y_in, us), d = fmaf(-F, F, 1.0f), res = F - h_in;
+            __builtin_amdgcn_sched_barrier(0);
+            const f4v p = wave_products(xv, wr);
+            const float z = swap16_add(swap32_add(p[0], p[2]), swap32_add(p[1], p[3]));
+            const float delta = fmaf(d, z, res);
+            s.x[kB ^ 1][xw] = delta;
+            __builtin_amdgcn_sched_barrier(0);
+            hand_on(next_rec, fmaf(d, z, F), y_in + z);
+            if constexpr (kKind == 1) {                    // past the end too; a NaN has reached the last one
+                const int l = t - it;
+                if (l >= lead && l < L) mymax = nanmax(mymax, fabsf(delta));
+                if constexpr (EDGE) {
+                    if (l == lead - 1) my_edge[0] = delta;
+                    if (l == L - 1) my_edge[kWaveIters * DH] = delta;
+                }
+            } else if constexpr (kKind == 0) {
+                mymax = fmaxf(mymax, fabsf(delta));
+            }
+            // delta is written; the (at least three) LDS instructions of hand_on may be on their way still
+            asm volatile("s_waitcnt lgkmcnt(3)\n\ts_barrier" ::: "memory");
+        };
+        lds_barrier();
+        hand_on(s.rec[0], 0.0f, 0.0f);
+        for (int g = 0; g < n_groups; ++g) {
+            const int t0 = g * kWaveGroup;
+            float *rec = s.rec[t0 & (kRing - 1)], *rec_next = s.rec[(t0 + kWaveGroup) & (kRing - 1)];
+            auto group = [&](auto kind) {
+#pragma unroll
+                for (int i = 0; i < kWaveGroup; ++i) step(kind, i & 1, i + 1 < kWaveGroup ? rec + kWaveRec * (i + 1) : rec_next, t0 + i);
+            };
+            if (t0 + kWaveGroup < L && (lead == 0 || t0 >= lead + kWaveIters - 1)) {
+                group(std::integral_constant<int, 0>{});
+            } else {
+                if constexpr (EDGE) {
+                    if (t0 + kWaveGroup < lead && t0 + kWaveGroup < L) { group(std::integral_constant<int, 2>{}); continue; }
+                }
+                group(std::integral_constant<int, 1>{});
+            }
+        }
+        lds_barrier();
+        if (it < K) atomicMax(&s.m[it], __float_as_uint(mymax) & 0x7fffffffu);
+    }
+}
+
+// W of this lane as wave_products wants it
+__device__ __forceinline__ void load_w_wave(const float *W, float (&wr)[16])
+{
+    const int lane = threadIdx.x & 63, row = 16 * ((int)(threadIdx.x >> 6) & 3) + (lane & 15);
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
-        const f4v t = *reinterpret_cast<const f4v *>(a.W + row * DH + 16 * it + 4 * m);
+        const f4v t = *reinterpret_cast<const f4v *>(W + row * DH + 16 * (lane >> 4) + 4 * m);
 #pragma unroll
         for (int v = 0; v < 4; ++v) wr[4 * m + v] = t[v];
     }
-    const int xw = 64 * (w & 3) + 16 * (r >> 2) + 4 * it + (r & 3);  // where this lane's delta goes
+}
 
-    for (int k0 = 0; k0 < a.max_iter; k0 += kWaveIters) {
-        const int K = min(kWaveIters, a.max_iter - k0);
-        const int n_groups = (L + K - 1 + kWaveGroup - 1) / kWaveGroup;
-        if (threadIdx.x < DH * kWaveIters) s_x[0][threadIdx.x] = 0.0f;
-        if (threadIdx.x < kWaveIters) s_m[threadIdx.x] = 0u;
-        if (w == 4) {
-            const buf_rsrc ru = seq_rsrc(a.u + (size_t)b * L * DH, seq_bytes), rh = seq_rsrc(a.h + (size_t)b * L * DH, seq_bytes),
-                           ry = seq_rsrc(a.d + (size_t)b * L * DH, seq_bytes);
-            f4v xh[2], xy[2], xu[2];
-            auto same = [](int t) { return t; };
-            auto before = [](int t) { return t - 1; };
-            auto bring = [&](int t) {
-                rows_load(rh, xh, lane, t, same);
-                rows_load(ry, xy, lane, t, before);
-                rows_load(ru, xu, lane, t, same);
-            };
-            auto put = [&](int t) {
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    *ring_slot(s_rec, 0, lane, t + 4 * j) = xh[j];
-                    *ring_slot(s_rec, DH, lane, t + 4 * j) = xy[j];
-#pragma unroll
-                    for (int i = 0; i < kWaveIters; ++i) *ring_slot(s_rec, kPer * i + 2 * DH, lane, t + 4 * j + i) = xu[j] * kTanhScale;
-                }
-            };
-            auto take = [&](int t) {                       // what iteration K - 1 left in the records t .. t + 7
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    xh[j] = *ring_slot(s_rec, kPer * K, lane, t + 4 * j);
-                    xy[j] = *ring_slot(s_rec, kPer * K + DH, lane, t + 4 * j);
-                }
-                rows_store(rh, xh, lane, t - K, same);
-                rows_store(ry, xy, lane, t - K, before);
-            };
-#pragma unroll
-            for (int i = 1; i < kWaveIters; ++i)
-                for (int t = 0; t < i; ++t) s_rec[t][kPer * i + 2 * DH + lane] = 0.0f;
-            bring(0);
-            put(0);
-            // y in front of the first row: W h0, the same for every iteration
-            s_rec[0][DH + lane] = a.h0 ? a.r[(size_t)b * DH + lane] : 0.0f;
-            lds_barrier();
-            for (int g = 0; g < n_groups; ++g) {
-                const int t0 = g * kWaveGroup;
-                lds_barrier();
-                if (g > 0) take(t0 - kWaveGroup + 1);      // records t0 - 7 .. t0: complete with the first step of this group
-                bring(t0 + kWaveGroup);
-#pragma unroll 1
-                for (int i = 1; i < kWaveGroup - 2; ++i) lds_barrier();
-                put(t0 + kWaveGroup);                      // the group's last step reads the first of these records
-                lds_barrier();
-                lds_barrier();
-            }
-            lds_barrier();
-            take((n_groups - 1) * kWaveGroup + 1);
-        } else {
-            float mymax = 0.0f, h_in, y_in, us;
-            // what this lane's iteration leaves for the next one in record `rec`, and what it finds there itself
-            auto hand_on = [&](float *record, float hn, float yn) {
-                float *rec = record + kPer * it + row;
-                rec[kPer] = hn;
-                rec[kPer + DH] = yn;
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the reader is in this wave
-                __builtin_amdgcn_wave_barrier();
-                h_in = rec[0];
-                y_in = rec[DH];
-                us = rec[2 * DH];
-            };
-            auto step = [&](auto tail, int kB, float *next_rec, int t) {
-                const f4v xv = *reinterpret_cast<const f4v *>(&s_x[kB][4 * lane]);
-                __builtin_amdgcn_sched_barrier(0);
-                const float F = tanh_scaled(y_in, us), d = fmaf(-F, F, 1.0f), res = F - h_in;
-                __builtin_amdgcn_sched_barrier(0);
-                const f4v p = wave_products(xv, wr);
-                const float z = swap16_add(swap32_add(p[0], p[2]), swap32_add(p[1], p[3]));
-                const float delta = fmaf(d, z, res);
-                s_x[kB ^ 1][xw] = delta;
-                __builtin_amdgcn_sched_barrier(0);
-                hand_on(next_rec, fmaf(d, z, F), y_in + z);
-                if constexpr (decltype(tail)::value) {     // timesteps past the end do not count; a NaN has reached the last one
-                    if (t - it < L) mymax = nanmax(mymax, fabsf(delta));
-                } else {
-                    mymax = fmaxf(mymax, fabsf(delta));
-                }
-                // delta is written; the (at least three) LDS instructions of hand_on may be on their way still
-                asm volatile("s_waitcnt lgkmcnt(3)\n\ts_barrier" ::: "memory");
-            };
-            lds_barrier();
-            hand_on(s_rec[0], 0.0f, 0.0f);
-            for (int g = 0; g < n_groups; ++g) {
-                const int t0 = g * kWaveGroup;
-                float *rec = s_rec[t0 & (kRing - 1)], *rec_next = s_rec[(t0 + kWaveGroup) & (kRing - 1)];
-                if (t0 + kWaveGroup < L) {
-#pragma unroll
-                    for (int i = 0; i < kWaveGroup; ++i)
-                        step(std::false_type(), i & 1, i + 1 < kWaveGroup ? rec + kRec * (i + 1) : rec_next, t0 + i);
-                } else {
-#pragma unroll
-                    for (int i = 0; i < kWaveGroup; ++i)
-                        step(std::true_type(), i & 1, i + 1 < kWaveGroup ? rec + kRec * (i + 1) : rec_next, t0 + i);
-                }
-            }
-            lds_barrier();
-            if (it < K) atomicMax(&s_m[it], __float_as_uint(mymax) & 0x7fffffffu);
-        }
-        __threadfence();                                   // the next block reads the rows that this one wrote
-        __syncthreads();
+// The first block of iterations, one workgroup per stretch of a sequence.
+__global__ __launch_bounds__(320) void dense_stretch_kernel(const DenseArgs a, const DenseStretch c)
+{
+    __shared__ WaveLds s;
+    const int b = (int)blockIdx.x / c.n, j = (int)blockIdx.x - b * c.n, K = min(kWaveIters, a.max_iter);
+    const size_t seq = (size_t)b * a.L * DH;
+    float wr[16];
+    load_w_wave(a.W, wr);
+    const int start = j * c.len;
+    const WaveRows q = {c.h0it + seq, a.d + seq, a.h + seq, c.y + seq, max(start - kWarm, 0), start, min(start + c.len, a.L)};
+    wavefront_block<true>(a, b, K, q, wr, s, c.edge + (size_t)blockIdx.x * 2 * kWaveIters * DH);
+    __syncthreads();
+    if (threadIdx.x < kWaveIters) c.top[(size_t)blockIdx.x * kWaveIters + threadIdx.x] = s.m[threadIdx.x];
+}
+
+// One workgroup per sequence.  A sequence whose own update meets the tolerance at the end of a block is done:
+// the blocks after it are run by the sequences that are not.  gm[k-1]: max |delta| of iteration k over the
+// sequences that ran it.  The last workgroup to finish reports the first iteration whose maximum met the tolerance.
+// After dense_stretch_kernel it goes on behind the first block, or starts from the beginning where that has to be.
+__global__ __launch_bounds__(320) void dense_wavefront_kernel(const DenseArgs a, unsigned int *gm, const DenseStretch c)
+{
+    __shared__ WaveLds s;
+    const int b = blockIdx.x;
+    const size_t seq = (size_t)b * a.L * DH;
+    float *y = a.d;
+    const float *h_first = a.h;
+    auto ended = [&](int K) {                              // the maxima in s.m are of a whole block
         bool met = false;
         for (int i = 0; i < K; ++i) {
-            const float mk = __uint_as_float(s_m[i]);
+            const float mk = __uint_as_float(s.m[i]);
             met = met || !(mk - mk == 0.0f) || (i == K - 1 && a.tol >= 0.0f && mk <= a.tol);
         }
-        if ((int)threadIdx.x < K) atomicMax(&gm[k0 + threadIdx.x], s_m[threadIdx.x]);
+        return met;
+    };
+    int k0 = 0;
+    if (c.n > 1) {
+        const int K = min(kWaveIters, a.max_iter);
+        if (threadIdx.x < kWaveIters) s.m[threadIdx.x] = 0u;
         __syncthreads();
-        if (met) break;
+        const unsigned int *top = c.top + (size_t)b * c.n * kWaveIters;
+        for (int i = threadIdx.x; i < c.n * kWaveIters; i += (int)blockDim.x) atomicMax(&s.m[i & (kWaveIters - 1)], top[i]);
+        // quads of updates: the ones at the last step of stretch j, and the ones that j + 1 started from
+        constexpr int kQuads = kWaveIters * DH / 4, kBatch = 4;
+        const f4v *edge = reinterpret_cast<const f4v *>(c.edge) + (size_t)b * c.n * 2 * kQuads;
+        const int n_quads = (c.n - 1) * kQuads;
+        int apart = 0;
+        for (int i0 = threadIdx.x; i0 < n_quads; i0 += kBatch * (int)blockDim.x) {
+            f4v there[kBatch], here[kBatch];
+#pragma unroll
+            for (int j = 0; j < kBatch; ++j) {
+                const int i = min(i0 + j * (int)blockDim.x, n_quads - 1);
+                const f4v *at = edge + (size_t)(i / kQuads) * 2 * kQuads + i % kQuads;
+                there[j] = at[kQuads];
+                here[j] = at[2 * kQuads];
+            }
+#pragma unroll
+            for (int j = 0; j < kBatch; ++j) {
+                if (min(i0 + j * (int)blockDim.x, n_quads - 1) % kQuads >= K * DH / 4) continue;
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (!(fabsf(there[j][v] - here[j][v]) <= kWarmTol)) apart = 1;
+            }
+        }
+        // the same for the whole workgroup, which the compiler is told: buffers chosen by it are scalars
+        if (__builtin_amdgcn_readfirstlane(__syncthreads_or(apart))) {
+            h_first = c.h0it;
+        } else {
+            if ((int)threadIdx.x < K) atomicMax(&gm[threadIdx.x], s.m[threadIdx.x]);
+            y = c.y;
+            k0 = __builtin_amdgcn_readfirstlane(ended(K) ? a.max_iter : K);
+        }
+        __syncthreads();
+    }
+    if (k0 < a.max_iter) {
+        float wr[16];
+        load_w_wave(a.W, wr);
+        for (; k0 < a.max_iter; k0 += kWaveIters) {
+            const int K = min(kWaveIters, a.max_iter - k0);
+            const WaveRows q = {(k0 == 0 ? h_first : a.h) + seq, y + seq, a.h + seq, y + seq, 0, 0, a.L};
+            wavefront_block<false>(a, b, K, q, wr, s, nullptr);
+            __threadfence();                               // the next block reads the rows that this one wrote
+            __syncthreads();
+            const bool met = ended(K);
+            if ((int)threadIdx.x < K) atomicMax(&gm[k0 + threadIdx.x], s.m[threadIdx.x]);
+            __syncthreads();
+            if (met) break;
+        }
     }
     if (threadIdx.x == 0) {
         __threadfence();
@@ -1292,21 +1420,42 @@ __global__ __launch_bounds__(320) void dense_wavefront_kernel(const DenseArgs a,
 // sums, which two lane-row swaps complete.  mu reaches the FMAs one value per lane, broadcast inside the lane row by
 // the instruction itself (as 16-byte reads of all terms it cost 16 LDS transactions of 1 KB per step: 164 ns a step).  A fifth wave moves rows as in the forward kernel.  Ends with
 // dL/dh0 = W^T mu_1.
-__global__ __launch_bounds__(320) void dense_adjoint_kernel(const DenseArgs a, float *dh0)
+//
+// STRETCH: one workgroup per stretch of a sequence (DenseStretch: here from the last row down; what enters is one mu), which
+// starts kWarm rows early from mu = 0 and leaves mu at the row behind its own last one in `edge`.  Otherwise one workgroup
+// per sequence; after the stretches it does nothing where these agree, relative to the largest of the 64 values, and runs
+// the whole sequence where they do not.
+template <bool STRETCH>
+__global__ __launch_bounds__(320) void dense_adjoint_kernel(const DenseArgs a, float *dh0, const DenseStretch c)
 {
-    // step t of the recurrence is row L - 1 - t; its record holds d and d g, and mu is in the slot of the same number
+    // step t of the recurrence is row last - t; its record holds d and d g, and mu is in the slot of the same number
     __shared__ __attribute__((aligned(16))) float s_rec[kRing][2 * DH], s_mu[kRing][DH];
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int q = lane >> 4, row = 16 * (w & 3) + (lane & 15), b = blockIdx.x, L = a.L;
-    const unsigned int seq_bytes = (unsigned int)L * (DH * 4u);
-    auto rev = [L](int t) { return L - 1 - t; };
+    const int q = lane >> 4, row = 16 * (w & 3) + (lane & 15);
+    const int b = STRETCH ? (int)blockIdx.x / c.n : (int)blockIdx.x, j = STRETCH ? (int)blockIdx.x - b * c.n : 0;
+    const unsigned int seq_bytes = (unsigned int)a.L * (DH * 4u);
+    // rows start .. end - 1 are this workgroup's, the ones from `last` down are run
+    const int start = STRETCH ? j * c.len : 0, end = STRETCH ? min(start + c.len, a.L) : a.L;
+    const int last = STRETCH ? min(end + kWarm, a.L) - 1 : a.L - 1, L = last + 1 - start, lead = last + 1 - end;
+    if constexpr (!STRETCH) {
+        if (c.n > 1) {
+            int apart = 0;
+            for (int e = 1 + w; e < c.n; e += 5) {         // a wave looks at the 64 values between two stretches
+                const float there = a.du[((size_t)b * a.L + (size_t)e * c.len) * DH + lane], here = c.edge[((size_t)b * c.n + e - 1) * DH + lane];
+                const float top = __uint_as_float(wave_max_u32(__float_as_uint(there) & 0x7fffffffu));
+                if (!(fabsf(there - here) <= kWarmTol * top)) apart = 1;
+            }
+            if (!__syncthreads_or(apart)) return;
+        }
+    }
+    auto rev = [last](int t) { return last - t; };
     float wr[16];                                          // W^T[row][16 q ..]
 #pragma unroll
     for (int i = 0; i < 16; ++i) wr[i] = a.W[(16 * q + i) * DH + row];
     const int n_groups = (L + kWaveGroup - 1) / kWaveGroup;
     if (w == 4) {
-        const buf_rsrc rd = seq_rsrc(a.d + (size_t)b * L * DH, seq_bytes), rg = seq_rsrc(a.g + (size_t)b * L * DH, seq_bytes),
-                       ro = seq_rsrc(a.du + (size_t)b * L * DH, seq_bytes);
+        const buf_rsrc rd = seq_rsrc(a.d + (size_t)b * a.L * DH, seq_bytes), rg = seq_rsrc(a.g + (size_t)b * a.L * DH, seq_bytes),
+                       ro = seq_rsrc(a.du + (size_t)b * a.L * DH, (unsigned int)end * (DH * 4u));   // rows behind the own ones are not stored
         f4v xd[2], xg[2], xm[2];
         auto bring = [&](int t) { rows_load(rd, xd, lane, t, rev); rows_load(rg, xg, lane, t, rev); };
         auto put = [&](int t) {
@@ -1319,7 +1468,7 @@ __global__ __launch_bounds__(320) void dense_adjoint_kernel(const DenseArgs a, f
         auto take = [&](int t) {
 #pragma unroll
             for (int j = 0; j < 2; ++j) xm[j] = *ring_slot(s_mu, 0, lane, t + 4 * j);
-            rows_store(ro, xm, lane, t, rev);
+            rows_store(ro, xm, lane, t, [&](int k) { return k < L ? last - k : -1; });
         };
         bring(0);
         put(0);
@@ -1374,7 +1523,11 @@ __global__ __launch_bounds__(320) void dense_adjoint_kernel(const DenseArgs a, f
         const float *rec = s_rec[s0], *rec_next = s_rec[s1];
 #pragma unroll
         for (int i = 0; i < kWaveGroup; ++i) {
-            mus[i * DH + row] = fmaf(d, sum(x), dg);       // the four lane groups store the same value
+            const float mu = fmaf(d, sum(x), dg);
+            mus[i * DH + row] = mu;                        // the four lane groups store the same value
+            if constexpr (STRETCH) {
+                if (g * kWaveGroup + i == lead - 1 && q == 0) c.edge[(size_t)blockIdx.x * DH + row] = mu;
+            }
             __builtin_amdgcn_sched_barrier(0);
             const float *nr = i + 1 < kWaveGroup ? rec + 2 * (i + 1) * DH : rec_next;
             d = nr[row];
@@ -1384,26 +1537,44 @@ __global__ __launch_bounds__(320) void dense_adjoint_kernel(const DenseArgs a, f
             x = mus[i * DH + lane];
         }
     }
-    if (dh0) {
+    if (dh0 && start == 0) {
         const float s = sum(s_mu[(L - 1) & (kRing - 1)][lane]);
         if (q == 0) dh0[(size_t)b * DH + row] = s;
     }
 }
 
+// Stretches of a substitution: one for each compute unit, and none where that saves less than a quarter of the steps.  Two
+// workgroups on a unit, 512 stretches, take 590 ns a step instead of 225 (64 sequences of 1024 steps: 108 us with 256, 136 with 512).
+DenseStretch dense_stretches(int B, int L)
+{
+    DenseStretch c;
+    memset(&c, 0, sizeof(c));
+    c.n = 1; c.len = L;
+    const int most = 256 / B;
+    if (most < 2) return c;
+    const int len = (L + most - 1) / most > kWarmLeast ? (L + most - 1) / most : kWarmLeast;
+    if (len >= L || 4 * (len + kWarm + kWaveIters) > 3 * L) return c;
+    c.n = (L + len - 1) / len; c.len = len;
+    return c;
+}
+
 // Substitution or chunk products?  Nanoseconds, measured on config 4's shape and on 1 to 16 sequences of 500 to 2000
 // steps: a forward substitution step takes 225, an adjoint one 160, whatever the number of sequences while
-// each has a compute unit (config 4: 1.26 ms with chunk products, 0.24 with substitution; 6 sequences of 523 steps:
-// 0.44 and 0.13 ms); an iteration with chunk products takes 3.94 per row but at least 67 us (the chain of one
+// each has a compute unit; an iteration with chunk products takes 3.94 per row but at least 67 us (the chain of one
 // chunk), 17 per step for the carry and 25-30 us for the sweeps, and four iterations are what a solve
-// needs.  Substitution wins but for few long sequences: forward beyond 2500 steps for fewer than ten of
-// them, backward beyond 650 steps of a single one.
+// needs.  Stretches run side by side, so their chain is what counts, and two launches (64 x 1024 forward: 1.26 ms with chunk
+// products, 244 us by substitution, 107 in stretches; backward 201 and 96; 16 x 1000 backward 145 with chunk products).  Where
+// they come to nothing, because the recurrence does not contract, the whole chain is to be gone through after all: it
+// may take twice as long as chunk products, not more.
 bool wavefront_pays(int B, int L, bool backward)
 {
     if (!g_dense_substitution) return false;
-    const double rows = (double)B * L;
-    const double products = (rows * 3.94 > 67e3 ? rows * 3.94 : 67e3) + 17.0 * L + 27e3;
-    const double rounds = (B + 511) / 512;              // two workgroups share a compute unit
-    return backward ? 160.0 * L * rounds < products : 225.0 * L * rounds < 4.0 * products;
+    const double rows = (double)B * L, step = backward ? 160.0 : 225.0;
+    const double products = ((rows * 3.94 > 67e3 ? rows * 3.94 : 67e3) + 17.0 * L + 27e3) * (backward ? 1.0 : 4.0);
+    const double chain = step * L * (double)((B + 511) / 512);              // two workgroups share a compute unit
+    const DenseStretch c = dense_stretches(B, L);
+    if (c.n > 1) return step * (c.len + kWarm + kWaveIters) + 10e3 < products && chain < 2.0 * products;
+    return chain < products;
 }
 
 // ------------------------------------------------------------ backward extras
@@ -1601,7 +1772,11 @@ int dense_backward(int dtype, const float *W, const void *u, const void *h0, con
         const size_t items = ((size_t)B * L + 15) / 16, most = (size_t)device_cu_count() * 8;
         a.W = W;
         hipLaunchKernelGGL(dense_residual_kernel, dim3((unsigned)(items < most ? items : most)), dim3(256), 0, st, a, 5);
-        hipLaunchKernelGGL(dense_adjoint_kernel, dim3(B), dim3(320), 0, st, a, static_cast<float *>(dh0));
+        DenseStretch c = dense_stretches(B, L);
+        // what the stretches leave lies where the chunk products would: 256 bytes of each, and they take 16 KB per 16 steps
+        c.edge = a.Ac;
+        if (c.n > 1) hipLaunchKernelGGL(dense_adjoint_kernel<true>, dim3(B * c.n), dim3(320), 0, st, a, static_cast<float *>(dh0), c);
+        hipLaunchKernelGGL(dense_adjoint_kernel<false>, dim3(B), dim3(320), 0, st, a, static_cast<float *>(dh0), c);
         return dense_weight_gradient(a, part, dW, st);
     }
     if (launch_reset(a.ctrl, nullptr, 0, nullptr, 0, st) != hipSuccess) return PARARNN_HIP_ERROR;
@@ -1701,8 +1876,23 @@ int dense_forward(int dtype, const float *W, const void *u, const void *h0, int 
     // the maxima of the iterations lie where the chunk products would (at least 4096 words)
     if (g_dense_products == 0 && max_iter > 0 && max_iter <= DH * DH && wavefront_pays(B, L, false)) {
         unsigned int *gm = reinterpret_cast<unsigned int *>(ws + lo.off_A);
-        hipLaunchKernelGGL(dense_guess_kernel, dim3(res_blocks), dim3(256), 0, st, a, gm, max_iter);
-        hipLaunchKernelGGL(dense_wavefront_kernel, dim3(B), dim3(320), 0, st, a, gm);
+        DenseStretch c = dense_stretches(B, L);
+        DenseArgs guess = a;
+        if (c.n > 1) {
+            // behind the maxima: two more sets of rows and what the stretches leave, 2.06 KB for each of at least 32 steps;
+            // chunk products would take 1 KB per step
+            const size_t rows = (size_t)B * L * DH;
+            float *more = reinterpret_cast<float *>(gm) + DH * DH;
+            c.h0it = more;
+            c.y = c.h0it + rows;
+            c.edge = c.y + rows;
+            c.top = reinterpret_cast<unsigned int *>(c.edge + (size_t)B * c.n * 2 * kWaveIters * DH);
+            if (reinterpret_cast<char *>(c.top + (size_t)B * c.n * kWaveIters) > ws + lo.off_b) { c.n = 1; c.len = L; }
+            else guess.h = c.h0it;
+        }
+        hipLaunchKernelGGL(dense_guess_kernel, dim3(res_blocks), dim3(256), 0, st, guess, gm, max_iter);
+        if (c.n > 1) hipLaunchKernelGGL(dense_stretch_kernel, dim3(B * c.n), dim3(320), 0, st, a, c);
+        hipLaunchKernelGGL(dense_wavefront_kernel, dim3(B), dim3(320), 0, st, a, gm, c);
         return hipGetLastError() == hipSuccess ? PARARNN_OK : PARARNN_HIP_ERROR;
     }
     if (launch_reset(a.ctrl, nullptr, 0, iters, status0, st) != hipSuccess) return PARARNN_HIP_ERROR;

@@ -1,0 +1,104 @@
+"""The dense cell's substitution in stretches that run side by side: against the chain of a whole sequence, which a batch of more
+sequences than half the compute units takes, and against the oracle; recurrences that contract, that do not, and both in
+one batch."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+H = 64
+
+
+def problem(B, L, gain, scale, seed, h0=True):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    rand = lambda *s: torch.randn(*s, generator=gen, device="cuda")
+    W = rand(H, H) * (gain / 8)
+    return W, rand(B, L, 1, H) * scale, rand(B, 1, H) * 0.1 if h0 else None, rand(B, L, 1, H)
+
+
+def whole(t, B):
+    """The same sequences over and over, in a batch that is not cut up."""
+    return None if t is None else t.repeat(-(-140 // B), *[1] * (t.dim() - 1))
+
+
+# stretches of 32 steps and longer, shorter and longer than what a stretch starts early, the last one short
+@pytest.mark.parametrize("B,L", [(1, 137), (3, 161), (2, 523), (1, 2050), (7, 400), (16, 1000), (60, 701), (100, 450), (128, 513)])
+def test_stretches_that_contract(oracle_mod, B, L):
+    import paper_2510_21450_amd as P
+    W, u, h0, g = problem(B, L, 0.8, 1.0, L, h0=L % 2 == 1)
+    print(f"stretches B={B} L={L}", flush=True)
+    for tol, n in ((1e-3, 32), (-1.0, 1), (-1.0, 3), (-1.0, 6)):
+        h, it, trace = P.forward("tanh_dense", W, u, h0, tol=tol, max_iter=n, trace=True)
+        H_, it_, trace_ = P.forward("tanh_dense", W, whole(u, B), whole(h0, B), tol=tol, max_iter=n, trace=True)
+        assert it.tolist() == it_.tolist()
+        # a rounding of the updates where stretches meet, forgotten again: eight units of the last place of a state of 1
+        assert (h - H_[:B]).abs().max() <= 1e-6, (tol, n)
+        k = it.tolist()[0]
+        assert np.allclose(trace[:k].cpu(), trace_[:k].cpu(), rtol=1e-4, atol=1e-6)
+    np_ = lambda t: None if t is None else t[:2].double().cpu().numpy()
+    h = P.forward("tanh_dense", W, u, h0, tol=1e-3, max_iter=32)[0]
+    ref = oracle_mod.seq_unroll("tanh_dense", W.double().cpu().numpy(), np_(u), np_(h0))
+    assert np.max(np.abs(np_(h) - ref)) <= 1e-5 * np.max(np.abs(ref))
+    got = P.backward("tanh_dense", W, u, h0, h, g, want_dh0=True)
+    want = P.backward("tanh_dense", W, whole(u, B), whole(h0, B), whole(h, B), whole(g, B), want_dh0=True)
+    assert (got[0] - want[0][:B]).abs().max() <= 1e-6 * want[0].abs().max()
+    if h0 is not None:
+        assert (got[2] - want[2][:B]).abs().max() <= 1e-6 * want[2].abs().max()
+
+
+@pytest.mark.parametrize("B,L", [(2, 300), (5, 523), (40, 600)])
+def test_stretches_that_do_not(B, L):
+    """The bits of the chain of a whole sequence; with u at 0.1 and 1.2 N(0, 1/64) nothing is forgotten, at 1 it is."""
+    import paper_2510_21450_amd as P
+    W, u, h0, g = problem(B, L, 1.2, 1.0, 5 * L)
+    u[::2] *= 0.1
+    for tol, n in ((1e-3, 8), (-1.0, 2), (-1.0, 5)):
+        h, it, _ = P.forward("tanh_dense", W, u, h0, tol=tol, max_iter=n)
+        H_, it_, _ = P.forward("tanh_dense", W, whole(u, B), whole(h0, B), tol=tol, max_iter=n)
+        assert it.tolist() == it_.tolist()
+        assert torch.equal(torch.nan_to_num(h[::2]), torch.nan_to_num(H_[:B:2]))
+        assert (torch.nan_to_num(h[1::2]) - torch.nan_to_num(H_[1:B:2])).abs().max() <= 1e-5
+    # d = 1 - h^2 near 1 and W expanding: neither does mu
+    h = torch.zeros_like(h)
+    got = P.backward("tanh_dense", W, torch.zeros_like(u), None, h, g)
+    want = P.backward("tanh_dense", W, whole(torch.zeros_like(u), B), None, whole(h, B), whole(g, B))
+    assert torch.equal(torch.nan_to_num(got[0]), torch.nan_to_num(want[0][:B]))
+
+
+def test_a_nan_ends_the_solve_in_its_iteration():
+    import paper_2510_21450_amd as P
+    B, L = 3, 400
+    W, u, h0, _ = problem(B, L, 0.8, 1.0, 9)
+    for at in (0, 40, 130, 399):
+        bad = u.clone()
+        bad[1, at, 0, 7] = float("nan")
+        h, it, _ = P.forward("tanh_dense", W, bad, h0, tol=1e-3, max_iter=9)
+        H_, it_, _ = P.forward("tanh_dense", W, whole(bad, B), whole(h0, B), tol=1e-3, max_iter=9)
+        assert it.tolist() == it_.tolist() and it.tolist()[1] == 5
+        assert (h[0] - H_[0]).abs().max() <= 1e-6
+
+
+def test_stretches_in_a_graph():
+    import paper_2510_21450_amd as P
+    W, u, h0, g = problem(4, 300, 0.8, 1.0, 10)
+    inputs = [u.clone(), u * 0.5, u * 0.01, u * 1.5]
+    solve = lambda: P.forward("tanh_dense", W, u, h0, tol=1e-3, max_iter=16)[:2]
+    eager = []
+    for x in inputs:
+        u.copy_(x)
+        eager.append([t.clone() for t in solve()])
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        solve()
+    torch.cuda.current_stream().wait_stream(side)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        h, it = solve()
+    for x, (eh, ei) in zip(inputs, eager):
+        u.copy_(x)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(h, eh) and torch.equal(it, ei)
