@@ -28,6 +28,7 @@
 
 #include <stdint.h>
 #include <string.h>
+#include <math.h>
 
 namespace pararnn {
 
@@ -35,6 +36,7 @@ namespace {
 
 typedef float f16v __attribute__((ext_vector_type(16)));
 typedef float f4v __attribute__((ext_vector_type(4)));
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f2v __attribute__((ext_vector_type(2)));
 typedef __bf16 bf2v __attribute__((ext_vector_type(2)));
 typedef __bf16 bf8v __attribute__((ext_vector_type(8)));
@@ -78,6 +80,17 @@ __device__ __forceinline__ void store4(float *p, const f4v &v) { *reinterpret_ca
 __device__ __forceinline__ void store4(unsigned short *p, const f4v &v)
 {
     *reinterpret_cast<uint2 *>(p) = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
+}
+
+__device__ __forceinline__ void store4(__attribute__((address_space(3))) float *p, const f4v &v)
+{
+    *(__attribute__((address_space(3))) f4v *)p = v;
+}
+__device__ __forceinline__ void store4(__attribute__((address_space(3))) unsigned short *p, const f4v &v)
+{
+    typedef unsigned int u2v __attribute__((ext_vector_type(2)));
+    const u2v r = {pack2(v[0], v[1]), pack2(v[2], v[3])};
+    *(__attribute__((address_space(3))) u2v *)p = r;
 }
 
 __device__ __forceinline__ int acc_row(int v, int half) { return 8 * (v >> 2) + 4 * half + (v & 3); }
@@ -996,6 +1009,222 @@ __global__ __launch_bounds__(512) void proj_gemm_nt_dma_f32_kernel(const GemmArg
 }
 
 
+// ------------------------------- forward product of narrow heads: the weights stay in registers
+// u = W x + bias where a head is at most 256 wide (K = N = d_h = 64 KB).  The tiles of the kernels above then last four steps of
+// 64 k or fewer: the first loads and the store of an output tile weigh as much as its products.  Here a workgroup keeps
+// the d_h x d_h weights of one gate of one head in registers (a wave 64 of the output channels, 32 KB registers a lane) and
+// rows of x stream past: a step is R rows, whole rows of the head, copied straight into LDS two or three steps ahead; a wave
+// multiplies 32 of them by its weights and stores 32 x 64 outputs.  Bound by memory: 65536 rows, H = 1024, three gates in four
+// heads of 256 in bf16 185 -> 138 us (3.9 TB/s), eight heads of 64 at H = 512 162 -> 43 (6.2 TB/s, x and u fit the last
+// level of cache in part), 6993 rows of four heads of 192 with four gates in fp32 48 -> 28.
+//
+//   waves    MG row groups x KB column groups; R = 32 MG so that a stage is about 32 KB
+//   LDS      NS stages; 16-byte chunk c of row r lies at c ^ (r & 7 ^ r / 8 & 1), in the low three bits: a copy instruction reads
+//            whole lines, and eight rows of a fragment read cover all banks
+//   waits    as above: operations of a wave complete in order.  A step issues N copies (for the step NS - 1 ahead, with nothing
+//            to read past the end) and then N stores, so the number that may be outstanding at a step's one wait is known.
+//   XCDs     a job is one head's share of the rows, on one XCD: its workgroups take the G gates of the same rows, and the
+//            rows in turn, so that x comes from memory once; an XCD with several jobs runs them side by side.
+template <typename AT, int KB> struct RowsShape {
+    static constexpr int E = sizeof(AT), K = 64 * KB;
+    static constexpr int MG = E == 2 ? (KB == 1 ? 8 : KB == 2 ? 4 : 2) : (KB == 1 ? 4 : KB == 4 ? 1 : 2);
+    static constexpr int WAVES = MG * KB, R = 32 * MG, ROW = K * E, STAGE = R * ROW;
+    static constexpr int NS = STAGE > 40 * 1024 ? 3 : 4;
+    static constexpr int N = STAGE / 1024 / WAVES;          // copies of a wave per step; its stores: as many
+    static_assert(N * 1024 * WAVES == STAGE && N == 2 * E && NS * STAGE + WAVES * 2048 <= 160 * 1024, "");
+};
+
+struct RowsArgs {
+    const void *x;         // [M][H]
+    const float *Wx;       // [G][H][dh]
+    const float *bias;     // [G][H] or NULL
+    void *u;               // [M][G][H]
+    int M, H, G, heads;
+    int parts;             // shares of the rows
+    int abreast, J;        // jobs an XCD runs side by side; workgroups of a job's gate
+};
+
+template <typename AT, int KB, bool BIAS>
+__global__ __launch_bounds__((64 * RowsShape<AT, KB>::WAVES)) void proj_rows_kernel(const RowsArgs a)
+{
+    typedef RowsShape<AT, KB> S;
+    constexpr int E = S::E, K = S::K, R = S::R, ROW = S::ROW, NS = S::NS, N = S::N;
+    __shared__ __attribute__((aligned(16))) unsigned char s_op[NS][S::STAGE];
+    __shared__ __attribute__((aligned(16))) unsigned char s_epi[S::WAVES][2048];
+    const int xcd = blockIdx.x & 7, wg = blockIdx.x >> 3, gate = wg % a.G, lane_job = wg / a.G % a.abreast, turn = wg / a.G / a.abreast;
+    if (turn >= a.J) return;
+    const int tid = threadIdx.x, lane = tid & 63, w = (int)uniform((unsigned int)tid >> 6), wm = w / KB, wn = w % KB;
+    const int half = lane >> 5, l32 = lane & 31;
+    const unsigned int lds_op = lds_address(&s_op[0][0]), lds_epi = lds_address(&s_epi[w][0]);
+    const long long ldx = (long long)a.H * E, ldu = (long long)a.G * a.H * E;      // bytes
+    // where this lane's 16 bytes of each copy come from, within a step
+    unsigned int va[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        const int byte = (w * N + j) * 1024 + lane * 16, row = byte / ROW, c = byte % ROW / 16;
+        va[j] = (unsigned int)row * (unsigned int)ldx + (unsigned int)(c ^ dma_swz(row)) * 16u;
+    }
+    // and this lane's pieces of the fragments: a row's position bits are those of its row within a block of 32
+    unsigned int fo[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int c = E == 2 ? 2 * q + half : 4 * (q >> 1) + 2 * half + (q & 1);   // bf16: round q of four; fp32: piece q % 2 of round q / 2
+        fo[q] = (unsigned int)(32 * wm + l32) * ROW + (unsigned int)(c ^ dma_swz(l32)) * 16u;
+    }
+    const int steps = (a.M + R - 1) / R, jobs = a.heads * a.parts;
+    for (int job = xcd + 8 * lane_job; job < jobs; job += 8 * a.abreast) {
+        const int head = job % a.heads, part = job / a.heads;
+        const int s0 = (int)((long long)steps * part / a.parts), s1 = (int)((long long)steps * (part + 1) / a.parts);
+        const int count = s1 - s0 > turn ? (s1 - s0 - turn + a.J - 1) / a.J : 0;   // steps s0 + turn + i J
+        if (count == 0) continue;
+        const unsigned long long x0 = (unsigned long long)a.x + (unsigned long long)head * ROW;
+        auto issue = [&](int i, int stage) {
+            const long long row = (long long)(s0 + turn + (long long)i * a.J) * R, left = a.M - row;
+            const unsigned long long p = x0 + (unsigned long long)(row * ldx);
+            // rows past the last one lie beyond the descriptor and arrive as zeros
+            const unsigned int n = i < count ? (unsigned int)((min(left, (long long)R) - 1) * ldx + ROW) : 0u;
+            const u4v rs = {uniform((unsigned int)p), uniform((unsigned int)(p >> 32) & 0xffffu), uniform(n), 0x27000u};
+#pragma unroll
+            for (int j = 0; j < N; ++j)
+                copy_to_lds_16(lds_op + (unsigned int)stage * S::STAGE + (unsigned int)(w * N + j) * 1024u, rs, va[j], 0u);
+        };
+        // The weights come through the stages, as they are (fp32), 32 of every wave's 64 channels at a time or all of them
+        // where they fit, in the same order of chunks: read from memory by the lanes that keep them they took 15 us at d_h = 256.
+        const int o0 = gate * a.H + head * K + 64 * wn;                            // this wave's first output channel
+        bf8v wf[2][4 * KB];
+        f4v bias4[2][4];
+#pragma unroll
+        for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if constexpr (BIAS) bias4[ni][q] = *reinterpret_cast<const f4u *>(a.bias + o0 + 32 * ni + 8 * q + 4 * half);
+        {
+            constexpr int WB = 32 * KB * K * 4, PER = WB / 1024 / S::WAVES, AT_ONCE = 2 * WB <= NS * S::STAGE ? 2 : 1;
+            static_assert(PER * 1024 * S::WAVES == WB && WB <= NS * S::STAGE, "");
+            const unsigned long long p = (unsigned long long)(a.Wx + (size_t)(gate * a.H + head * K) * K);
+            const u4v rs = {uniform((unsigned int)p), uniform((unsigned int)(p >> 32) & 0xffffu), (unsigned int)(K * K * 4), 0x27000u};
+#pragma unroll
+            for (int n0 = 0; n0 < 2; n0 += AT_ONCE) {
+#pragma unroll
+                for (int ni = n0; ni < n0 + AT_ONCE; ++ni)
+#pragma unroll
+                    for (int j = 0; j < PER; ++j) {
+                        const int byte = (w * PER + j) * 1024 + lane * 16, row = byte / (4 * K), c = byte % (4 * K) / 16;
+                        copy_to_lds_16(lds_op + (unsigned int)((ni - n0) * WB + (w * PER + j) * 1024), rs,
+                                       (unsigned int)((row / 32 * 64 + 32 * ni + row % 32) * (4 * K) + (c ^ dma_swz(row)) * 16), 0u);
+                    }
+                asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+                for (int ni = n0; ni < n0 + AT_ONCE; ++ni)
+#pragma unroll
+                    for (int kb = 0; kb < 4 * KB; ++kb) {
+                        const unsigned char *q = &s_op[0][0] + (ni - n0) * WB + (32 * wn + l32) * (4 * K) + kb / 2 * 128;
+                        const int c = 4 * (kb & 1) + 2 * half;
+                        Raw8f r;
+                        r.lo = *reinterpret_cast<const f4v *>(q + (c ^ dma_swz(l32)) * 16);
+                        r.hi = *reinterpret_cast<const f4v *>(q + ((c + 1) ^ dma_swz(l32)) * 16);
+                        wf[ni][kb] = __builtin_bit_cast(bf8v, to_bf16x8(r));
+                    }
+#pragma unroll
+                for (int ni = n0; ni < n0 + AT_ONCE; ++ni)
+#pragma unroll
+                    for (int kb = 0; kb < 4 * KB; ++kb) asm volatile("" : "+v"(wf[ni][kb]));    // read before what follows overwrites it
+                asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            }
+            if constexpr (BIAS) {
+#pragma unroll
+                for (int q = 0; q < 8; ++q) asm volatile("" : "+v"(bias4[q / 4][q % 4]));       // and waited for here, not in the loop
+            }
+        }
+        // acc = (W rows)(x rows)^T: a lane owns row l32 of x and, per four registers, four consecutive channels
+#pragma unroll
+        for (int i = 0; i < NS - 1; ++i) issue(i, i);
+        int stage = 0, behind = 0;
+        for (int i = 0; i < count; ++i) {
+            // the copies of this step have landed: behind them at most those of the steps after it, and stores
+            asm volatile("" : "+s"(behind));                                       // (no copy of the loop for each of the first steps)
+            if (behind >= NS - 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N * (2 * NS - 3)) : "memory");
+            else if (behind == 0) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N * (NS - 2)) : "memory");
+            else if (behind == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N * (NS - 1)) : "memory");
+            else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N * NS) : "memory");
+            ++behind;
+            // everybody's have, and everybody has read the stage before it
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            issue(i + NS - 1, stage == 0 ? NS - 1 : stage - 1);
+            const unsigned char *op = &s_op[stage][0];
+            f16v acc[2];
+#pragma unroll
+            for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[ni][v] = 0.0f;
+            // the fragments of the next 32 k are read while those of the last are multiplied
+            bf8v fa[2][2];
+            auto read = [&](int g, bf8v(&f)[2]) {
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    if constexpr (E == 2) {
+                        f[q] = *reinterpret_cast<const bf8v *>(op + fo[2 * (g & 1) + q] + (g >> 1) * 128);
+                    } else {
+                        Raw8f r;
+                        r.lo = *reinterpret_cast<const f4v *>(op + fo[2 * q] + g * 128);
+                        r.hi = *reinterpret_cast<const f4v *>(op + fo[2 * q + 1] + g * 128);
+                        f[q] = __builtin_bit_cast(bf8v, to_bf16x8(r));
+                    }
+                }
+            };
+            read(0, fa[0]);
+#pragma unroll
+            for (int g = 0; g < 2 * KB; ++g) {
+                if (g + 1 < 2 * KB) read(g + 1, fa[(g + 1) & 1]);
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+#pragma unroll
+                    for (int ni = 0; ni < 2; ++ni)
+                        acc[ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[ni][2 * g + q], fa[g & 1][q], acc[ni], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            // 2 KB of output rows at a time through this wave's patch of LDS, so that a store instruction writes whole lines;
+            // 16-byte chunk c of patch row r sits at c ^ (r % 8).  Rows past the end are dropped by the descriptor.
+            const long long row = (long long)(s0 + turn + (long long)i * a.J) * R + 32 * wm, left = a.M - row;
+            unsigned char *dst = static_cast<unsigned char *>(a.u) + row * ldu + (long long)o0 * E;
+            const buf_rsrc rc = __builtin_amdgcn_make_buffer_rsrc(dst, 0, left > 0 ? (int)((min(left, 32ll) - 1) * ldu + 64 * E) : 0, 0x27000);
+            constexpr int PR = 32 / E, CH = 4 * E;                                 // rows of the patch, chunks of a row
+            const int pr = l32 % PR, r0 = lane / CH;                               // patch row of this lane's outputs, and of its pieces to store
+            unsigned int wr = lds_epi + (unsigned int)(pr * (64 * E) + (E == 2 ? 8 * half : 0)), wx = (unsigned int)((pr & 7) ^ (E == 4 ? half : 0)) * 16u;
+            unsigned int rd = lds_epi + (unsigned int)(r0 * (64 * E)), rx = (unsigned int)((lane % CH) * 16), off = (unsigned int)r0 * (unsigned int)ldu + rx;
+            asm volatile("" : "+v"(wr), "+v"(wx), "+v"(rd), "+v"(rx), "+v"(off));  // worked out here: there is no room to keep what follows from them
+#pragma unroll
+            for (int ph = 0; ph < 32 / PR; ++ph) {
+                if (l32 / PR == ph) {
+#pragma unroll
+                    for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            f4v o = {acc[ni][4 * q], acc[ni][4 * q + 1], acc[ni][4 * q + 2], acc[ni][4 * q + 3]};
+                            if constexpr (BIAS) o += bias4[ni][q];
+                            const unsigned int c = E == 2 ? 4 * ni + q : 8 * ni + 2 * q;
+                            store4((__attribute__((address_space(3))) AT *)(unsigned long long)(wr + ((c * 16u) ^ wx)), o);
+                        }
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int it = 0; it < 2; ++it) {
+                    const unsigned int sw = (unsigned int)((r0 + it * (PR / 2)) & 7) * 16u;
+                    const u4v v = *(const __attribute__((address_space(3))) u4v *)(unsigned long long)(rd + it * (PR / 2) * (64 * E) + (rx ^ sw));
+                    __builtin_amdgcn_raw_buffer_store_b128(v, rc, off + (unsigned int)(PR * ph + it * (PR / 2)) * (unsigned int)ldu, 0, 0);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+            }
+            stage = stage + 1 == NS ? 0 : stage + 1;
+        }
+        // nothing of this job is in flight when the next one fills the stages
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    }
+}
+
+
 // --------------------------------------------------- dWx and dbias (TN product)
 struct DwArgs {
     const void *du;        // [M][G][H], storage type AT
@@ -1595,6 +1824,47 @@ hipError_t launch_nt_dma(GemmArgs &g, hipStream_t st)
     return hipGetLastError();
 }
 
+// The forward product with the weights in registers: every head of at most 256 channels, which is what a wave's registers hold
+// (64 x 256 weights in 128 of them).  Also with few rows, where the launch that rounds W falls away: 604 problems of 1 to
+// 60001 rows, 1 to 16 heads and 1 to 4 gates in both types take 1.8 times less on the geometric mean than with the kernels above, none
+// more.  Row offsets of a step within 32 bits.
+template <typename AT, int KB> hipError_t launch_rows_kb(const RowsArgs &a, int blocks, hipStream_t st)
+{
+    constexpr int T = 64 * RowsShape<AT, KB>::WAVES;
+    if (a.bias) hipLaunchKernelGGL((proj_rows_kernel<AT, KB, true>), dim3((unsigned)blocks), dim3(T), 0, st, a);
+    else hipLaunchKernelGGL((proj_rows_kernel<AT, KB, false>), dim3((unsigned)blocks), dim3(T), 0, st, a);
+    return hipGetLastError();
+}
+template <typename AT> hipError_t launch_rows(const RowsArgs &a, int kb, int blocks, hipStream_t st)
+{
+    switch (kb) {
+        case 1: return launch_rows_kb<AT, 1>(a, blocks, st);
+        case 2: return launch_rows_kb<AT, 2>(a, blocks, st);
+        case 3: return launch_rows_kb<AT, 3>(a, blocks, st);
+        default: return launch_rows_kb<AT, 4>(a, blocks, st);
+    }
+}
+bool rows_shape(int M, int H, int G, int n_heads, bool bf, RowsArgs *a, int *blocks)
+{
+    const int dh = H / n_heads, slots = device_cu_count() / 8;
+    if (!g_proj_dma || dh % 64 || dh > 256 || slots < G || (long long)G * H >= (1 << 22)) return false;
+    a->M = M; a->H = H; a->G = G; a->heads = n_heads;
+    // every XCD gets the same number of jobs; side by side as many of them as take the least time, a job's weights at
+    // about two steps (with three heads one after the other, 300 rows took 22 us instead of 16)
+    a->parts = 8;
+    for (int h = n_heads; h % 2 == 0 && a->parts > 1; h /= 2) a->parts /= 2;
+    const int jobs = n_heads * a->parts / 8;
+    const double steps = (double)M / a->parts / (bf ? (dh <= 128 ? 16384 / dh : 64) : (dh == 64 ? 128 : dh == 256 ? 32 : 64));
+    double best = 0.0;
+    for (int n = 1; n <= jobs && n * G <= slots; ++n) {
+        const int J = slots / (n * G);
+        const double t = (double)((jobs + n - 1) / n) * (2.0 + ceil(steps / J));
+        if (n == 1 || t < best) { best = t; a->abreast = n; a->J = J; }
+    }
+    *blocks = 8 * slots;
+    return true;
+}
+
 int elementwise_blocks(size_t n)
 {
     size_t blocks = (n + 255) / 256;
@@ -1625,6 +1895,13 @@ int proj_forward(int dtype, const void *x, const float *Wx, const float *bias, i
     if (((uintptr_t)x | (uintptr_t)Wx | (uintptr_t)u | (uintptr_t)workspace) % 16) return PARARNN_UNSUPPORTED;
     const ProjLayout lo = proj_layout(B, L, H, G, n_heads, 0);
     if (workspace_bytes < lo.total) return PARARNN_WORKSPACE_TOO_SMALL;
+    RowsArgs r;
+    int blocks;
+    if (rows_shape(B * L, H, G, n_heads, dtype == PARARNN_BF16, &r, &blocks)) {
+        r.x = x; r.Wx = Wx; r.bias = bias; r.u = u;
+        const hipError_t e = dtype == PARARNN_BF16 ? launch_rows<unsigned short>(r, dh / 64, blocks, st) : launch_rows<float>(r, dh / 64, blocks, st);
+        return e == hipSuccess ? PARARNN_OK : PARARNN_HIP_ERROR;
+    }
     unsigned short *Wb = reinterpret_cast<unsigned short *>(static_cast<char *>(workspace) + lo.off_w);
     const size_t nw = (size_t)G * H * dh;
     int *tickets = reinterpret_cast<int *>(static_cast<char *>(workspace) + lo.off_tickets);
