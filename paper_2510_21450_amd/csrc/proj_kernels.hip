@@ -1615,6 +1615,237 @@ __global__ __launch_bounds__(512) void proj_dw_dma_kernel(const DwArgs a)
     }
 }
 
+// ------------------------------- dWx and dbias of narrow heads: a whole gate of a head per workgroup
+// The same sums for heads of at most 256 channels (d_h = 64 KB): a workgroup holds all d_h x d_h sums of one gate of one head over a
+// range of rows, so that du is read once and x once per gate, and no part of a tile lies idle.  Rows go to LDS as they
+// are, NS steps deep.  A wave owns IB x JB blocks of 32 x 32 sums; MS waves share a part and take the 16-row slices of a
+// step in turn, their sums are added at the end.
+//
+//   bf16     columns come out of the stage by transposing reads, as above; chunk c of row r lies at c ^ DwRows::swz(r): within
+//            128 bytes where a row is an odd number of those, for dw_swz does not fit it
+//   fp32     a lane reads its channel of eight rows, 32 neighbouring channels at a time, and rounds them
+//   dbias    is added up from the fragments of du (unrounded in fp32; eight rows before they join the sum); the waves that share a part's du blocks take one each
+//   bound    by memory, and where ranges are many by their sums: three gates, 65536 x 512 in heads of 64, bf16: 110 -> 55 us (4.9 TB/s);
+//            40000 x 512 in heads of 128, four gates: 67 -> 41; fp32: 16000 x 1024 in heads of 256 117 -> 100, 6993 x 768 in
+//            heads of 192, four gates: 57 -> 35, of which the sums of 16 ranges, written and added, are half
+template <typename AT, int KB> struct DwRows {
+    static constexpr int E = sizeof(AT), K = 64 * KB, ROW = K * E;
+    static constexpr int MS = KB == 1 ? (E == 2 ? 8 : 4) : KB == 2 ? 2 : 1;
+    static constexpr int IB = KB >= 3 ? KB : 2, JB = 2, WI = 2 * KB / IB, WJ = KB, WAVES = MS * WI * WJ;
+    static constexpr int R = E == 2 ? (KB == 1 ? 128 : KB == 2 ? 64 : 32) : (KB == 1 ? 64 : KB == 4 ? 16 : 32);
+    static constexpr int OP = R * ROW, STAGE = 2 * OP, NS = STAGE > 40 * 1024 ? 3 : 4;
+    static constexpr int N = OP / 1024 / WAVES;             // copies of each operand of a wave per step
+    static constexpr int SLICES = R / 16 / MS;              // of a wave per step
+    static constexpr int DB = (IB + WJ - 1) / WJ;           // du blocks of which a wave adds up the rows
+    static_assert(N * 1024 * WAVES == OP && SLICES >= 1 && (MS == 1 || WAVES * 16384 <= NS * STAGE), "");
+    static __device__ __forceinline__ int swz(int row) { return E == 4 ? 0 : (KB & 1) ? 2 * (row & 3) : dw_swz(row); }
+};
+
+template <typename AT, int KB> __global__ __launch_bounds__((64 * DwRows<AT, KB>::WAVES)) void proj_dw_rows_kernel(const DwArgs a)
+{
+    typedef DwRows<AT, KB> S;
+    constexpr int E = S::E, K = S::K, R = S::R, ROW = S::ROW, NS = S::NS, N = S::N, IB = S::IB, JB = S::JB, MS = S::MS, DB = S::DB;
+    __shared__ __attribute__((aligned(16))) unsigned char s_op[NS * S::STAGE];
+    __shared__ float s_db[MS][K];
+    // numbered as above: the gates of a (head, range) on one XCD at a time
+    int id = (int)(blockIdx.x & 7) * a.per_xcd + (int)(blockIdx.x >> 3);
+    if (id >= a.n_blocks) return;
+    const int g = id % a.G; id /= a.G;
+    const int head = id % a.heads;
+    const int s = id / a.heads;
+    const int m_begin = s * a.rows_per_split;
+    const int rows = min(a.M, m_begin + a.rows_per_split) - m_begin;
+    if (rows <= 0) return;
+    const int nk = (rows + R - 1) / R;
+    const int tid = threadIdx.x, lane = tid & 63, w = (int)uniform((unsigned int)tid >> 6);
+    const int ms = w % MS, part = w / MS, wi = part % S::WI, wj = part / S::WI;
+    const int half = lane >> 5, l32 = lane & 31;
+    const unsigned int lds_op = lds_address(s_op);
+
+    // ---- the copying side
+    const long long ld_du = (long long)a.G * a.H * E, ld_x = (long long)a.H * E;
+    unsigned long long p_du = (unsigned long long)a.du + (unsigned long long)(m_begin * ld_du + ((long long)g * a.H + head * K) * E);
+    unsigned long long p_x = (unsigned long long)a.x + (unsigned long long)(m_begin * ld_x + (long long)head * ROW);
+    int left = rows;
+    unsigned int va[N], vb[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        const int byte = (w * N + j) * 1024 + lane * 16, row = byte / ROW, c = (byte % ROW / 16) ^ S::swz(row);
+        va[j] = (unsigned int)row * (unsigned int)ld_du + (unsigned int)c * 16u;
+        vb[j] = (unsigned int)row * (unsigned int)ld_x + (unsigned int)c * 16u;
+    }
+    auto issue = [&](int stage) {
+        // rows past the end of the range lie beyond the descriptors: the copy writes zeros for them
+        const int n = min(left, R);
+        const u4v ra = {uniform((unsigned int)p_du), uniform((unsigned int)(p_du >> 32) & 0xffffu), uniform(n > 0 ? (unsigned int)((n - 1) * ld_du + ROW) : 0u), 0x27000u};
+        const u4v rb = {uniform((unsigned int)p_x), uniform((unsigned int)(p_x >> 32) & 0xffffu), uniform(n > 0 ? (unsigned int)((n - 1) * ld_x + ROW) : 0u), 0x27000u};
+        const unsigned int dst = lds_op + (unsigned int)stage * S::STAGE + (unsigned int)(w * N) * 1024u;
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            copy_to_lds_16(dst + (unsigned int)j * 1024u, ra, va[j], 0u);
+            copy_to_lds_16(dst + S::OP + (unsigned int)j * 1024u, rb, vb[j], 0u);
+        }
+        p_du += (unsigned long long)(R * ld_du);
+        p_x += (unsigned long long)(R * ld_x);
+        left -= R;
+    };
+
+    // ---- the multiplying side
+    const int rr = (lane & 15) >> 2, mask = S::swz(rr);
+    const unsigned int in_block = (unsigned int)((2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ (mask & 3));
+    const lds_char_ptr lds_zero = (lds_char_ptr)s_op - lds_op;                     // LDS address 0, as a pointer
+    auto place = [&](int block) {                                                  // of this lane's first element of a 32-channel block, in a slice
+        if constexpr (E == 2) return (unsigned int)(8 * half + rr) * ROW + (unsigned int)(lane & 1) * 8u + (((unsigned int)(4 * block) ^ (unsigned int)(mask & 12)) + in_block) * 16u;
+        else return (unsigned int)(8 * half) * ROW + (unsigned int)(32 * block + l32) * 4u;
+    };
+    unsigned int o_du[IB], o_x[JB];
+#pragma unroll
+    for (int i = 0; i < IB; ++i) o_du[i] = lds_op + place(IB * wi + i);
+#pragma unroll
+    for (int j = 0; j < JB; ++j) o_x[j] = lds_op + S::OP + place(JB * wj + j);
+    float sdb[DB];
+#pragma unroll
+    for (int d = 0; d < DB; ++d) sdb[d] = 0.0f;
+    auto read8 = [&](unsigned int addr, float *sum) {
+        bf8v f;
+        if constexpr (E == 2) {
+            const s4v q0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4v_ptr)(lds_zero + addr));
+            const s4v q1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4v_ptr)(lds_zero + addr + 4u * ROW));
+            f = __builtin_bit_cast(bf8v, __builtin_shufflevector(q0, q1, 0, 1, 2, 3, 4, 5, 6, 7));
+            if (sum) *sum += (((float)f[0] + (float)f[1]) + ((float)f[2] + (float)f[3])) + (((float)f[4] + (float)f[5]) + ((float)f[6] + (float)f[7]));
+        } else {
+            Raw8f r;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) (q < 4 ? r.lo : r.hi)[q & 3] = *(const __attribute__((address_space(3))) float *)(lds_zero + addr + (unsigned int)q * ROW);
+            if (sum) *sum += ((r.lo[0] + r.lo[1]) + (r.lo[2] + r.lo[3])) + ((r.hi[0] + r.hi[1]) + (r.hi[2] + r.hi[3]));
+            f = __builtin_bit_cast(bf8v, to_bf16x8(r));
+        }
+        return f;
+    };
+    const bool do_db = a.dbpart != nullptr;
+    f16v acc[JB][IB];
+#pragma unroll
+    for (int j = 0; j < JB; ++j)
+#pragma unroll
+        for (int i = 0; i < IB; ++i)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[j][i][v] = 0.0f;
+    // Sums of 512 rows of a wave at a time, added up: a range here is up to four times as long as with the smaller tiles, and one
+    // chain of roundings over it would be less exact.  Heads of 256 have no registers for it; their ranges are no longer.
+    constexpr bool TWO = KB < 4;
+    f16v sum[TWO ? JB : 1][TWO ? IB : 1];
+    if constexpr (TWO) {
+#pragma unroll
+        for (int j = 0; j < JB; ++j)
+#pragma unroll
+            for (int i = 0; i < IB; ++i) sum[j][i] = acc[j][i];
+    }
+    auto add_up = [&]() {
+        if constexpr (TWO) {
+#pragma unroll
+            for (int j = 0; j < JB; ++j)
+#pragma unroll
+                for (int i = 0; i < IB; ++i)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        sum[j][i][v] += acc[j][i][v];
+                        acc[j][i][v] = 0.0f;
+                    }
+        }
+    };
+
+#pragma unroll
+    for (int q = 0; q < NS - 1; ++q) issue(q);
+    int stage = 0;
+    for (int T = 0; T < nk; ++T) {
+        // own copies of this step have landed, behind them only those of the steps after it; after the barrier everybody's, and everybody
+        // has read the stage before it
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * N * (NS - 2)) : "memory");
+        issue(stage == 0 ? NS - 1 : stage - 1);
+#pragma unroll
+        for (int sl = 0; sl < S::SLICES; ++sl) {
+            const unsigned int at = (unsigned int)stage * S::STAGE + (unsigned int)(sl * MS + ms) * (16u * ROW);
+            bf8v fd[IB], fx[JB];
+#pragma unroll
+            for (int j = 0; j < JB; ++j) fx[j] = read8(o_x[j] + at, nullptr);
+#pragma unroll
+            for (int i = 0; i < IB; ++i) fd[i] = read8(o_du[i] + at, nullptr);
+#pragma unroll
+            for (int i = 0; i < IB; ++i)
+#pragma unroll
+                for (int j = 0; j < JB; ++j) acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fx[j], fd[i], acc[j][i], 0, 0, 0);
+            if (do_db) {
+#pragma unroll
+                for (int i = 0; i < IB; ++i)
+                    if (i % S::WJ == wj || S::WJ == 1) (void)read8(o_du[i] + at, &sdb[i / S::WJ]);
+            }
+        }
+        if (TWO && (T + 1) % (32 / S::SLICES) == 0) add_up();
+        stage = stage + 1 == NS ? 0 : stage + 1;
+    }
+    // nothing is on its way into the stages any more
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if constexpr (TWO) {
+        add_up();
+#pragma unroll
+        for (int j = 0; j < JB; ++j)
+#pragma unroll
+            for (int i = 0; i < IB; ++i) acc[j][i] = sum[j][i];
+    }
+
+    float *out = a.part + (((long long)s * a.G + g) * a.H + (long long)head * K) * K;
+    auto put = [&](int i, int j, int q, const f4v &o) {
+        const int row = 32 * (IB * wi + i) + l32, col = 32 * (JB * wj + j) + 8 * q + 4 * half;
+        *reinterpret_cast<f4v *>(out + (long long)row * K + col) = o;
+    };
+    if constexpr (MS > 1) {
+        // the sums of the waves that share a part, [part][wave][four of its 64 registers][lane]; each wave adds up a share
+        static_assert(IB * JB == 4, "");
+        f4v *mine = reinterpret_cast<f4v *>(s_op) + (part * MS + ms) * (16 * 64) + lane;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            const f16v &v = acc[q / 4 % JB][q / 4 / JB];
+            const f4v o = {v[4 * (q % 4)], v[4 * (q % 4) + 1], v[4 * (q % 4) + 2], v[4 * (q % 4) + 3]};
+            mine[q * 64] = o;
+        }
+        __syncthreads();
+        const f4v *all = reinterpret_cast<const f4v *>(s_op) + part * MS * (16 * 64) + lane;
+#pragma unroll
+        for (int k = 0; k < 16 / MS; ++k) {
+            const int q = ms * (16 / MS) + k;
+            f4v o = all[q * 64];
+#pragma unroll
+            for (int r = 1; r < MS; ++r) o += all[(r * 16 + q) * 64];
+            put(q / 4 / JB, q / 4 % JB, q % 4, o);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < IB; ++i)
+#pragma unroll
+            for (int j = 0; j < JB; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const f4v o = {acc[j][i][4 * q], acc[j][i][4 * q + 1], acc[j][i][4 * q + 2], acc[j][i][4 * q + 3]};
+                    put(i, j, q, o);
+                }
+    }
+    if (do_db) {
+#pragma unroll
+        for (int d = 0; d < DB; ++d) {
+            const float t = sdb[d] + __shfl_xor(sdb[d], 32);
+            const int i = d * S::WJ + (S::WJ == 1 ? 0 : wj);
+            if (half == 0 && i < IB) s_db[ms][32 * (IB * wi + i) + l32] = t;
+        }
+        __syncthreads();
+        for (int c = tid; c < K; c += 64 * S::WAVES) {
+            float t = 0.0f;
+#pragma unroll
+            for (int r = 0; r < MS; ++r) t += s_db[r][c];
+            a.dbpart[((long long)s * a.G + g) * a.H + (long long)head * K + c] = t;
+        }
+    }
+}
+
 // ------------------------------------------------------------- weight copies
 // Wb = bf16(Wx), same layout [G][H][dh]; n4 fours
 __global__ __launch_bounds__(256) void proj_wb_kernel(const float *Wx, unsigned short *Wb, size_t n4, int *tickets)
@@ -1721,13 +1952,46 @@ bool dw_dma_shape_ok(int M, int H, int G, int dh)
            !(M <= dw_one_range && (double)G * H / dh * (t1 / BM) * (t1 / BM) <= 2.0 * device_cu_count());
 }
 
+// The narrow-head kernel against the tiles of 128 and 256.  Up to 512 rows the tiles are one range and need no second launch
+// (9 us against 10-26).  bf16: at least level from 600 rows on, up to 2.4 times faster, but for heads of 256, where the 256-wide tiles do the
+// same.  fp32: more sums have to be written and added, for a range is all of a compute unit's work, and that pays
+// with enough rows: by gates x heads x rows, heads of 128 and 192 24000 0.9-1.05 times as fast, 48000 1.1-1.2, a million
+// 1.6; of 256, 96000 0.94, 128000 to a million 1.1-1.2; of 64, level at 600 rows; one or two gates in all never.
+bool dw_rows_shape_ok(int M, int H, int G, int dh, bool bf)
+{
+    if (dh % 64 || dh > 256 || M <= dw_one_range || (long long)G * H >= (1 << 22)) return false;
+    if (bf) return dh < 256;
+    const int units = G * (H / dh);
+    return dh == 64 || (units >= 3 && (double)units * M >= (dh == 256 ? 120000.0 : 40000.0));
+}
+
+// The ranges of the narrow-head kernel, one workgroup per compute unit: estimated as above, with 23 GB/s of rows per workgroup.
+void dw_rows_split(int M, int G, int H, int dh, int n_heads, bool bf, int least, int *S, int *rows_per_split)
+{
+    const int cus = device_cu_count() > 0 ? device_cu_count() : 256;
+    const int R = bf ? (dh == 64 ? 128 : dh == 128 ? 64 : 32) : (dh == 64 ? 64 : dh == 256 ? 16 : 32);
+    const int units = G * n_heads;
+    const double nw = (double)G * H * dh, row_us = 2.0 * dh * (bf ? 2 : 4) / 23e3;
+    double best_us = 0.0;
+    if (dh < 256) least = 1;                            // (heads of 256: no longer ranges than the smaller tiles have)
+    for (int s = least; s <= 96; ++s) {
+        int rps = (M + s - 1) / s;
+        rps = (rps + R - 1) / R * R;
+        const int ranges = (M + rps - 1) / rps;
+        const long long rounds = ((long long)units * ranges + cus - 1) / cus;
+        const double us = (double)rounds * (rps * row_us + 6.0) + (ranges > 1 ? 3.0 + (double)ranges * nw * 8.0 / 4.0e6 : 0.0);
+        if (s == least || us < best_us) { best_us = us; *rows_per_split = rps; *S = ranges; }
+    }
+}
+
 struct ProjLayout {
     size_t off_tickets, off_w, off_part, off_db, total;
     int S, rows_per_split, tiles;
+    int S3, rows_per_split3;               // the narrow-head dWx kernel's ranges (S3 = 0: not offered)
     int S2, rows_per_split2, tiles2;       // the copy-to-LDS dWx kernel's ranges and 256-wide tiles (S2 = 0: not offered)
 };
 
-ProjLayout proj_layout(int B, int L, int H, int G, int n_heads, int backward)
+ProjLayout proj_layout(int dtype, int B, int L, int H, int G, int n_heads, int backward)
 {
     ProjLayout lo;
     const int dh = H / n_heads;
@@ -1738,6 +2002,7 @@ ProjLayout proj_layout(int B, int L, int H, int G, int n_heads, int backward)
     lo.tiles = (dh + BM - 1) / BM;
     lo.S = 0; lo.rows_per_split = 0;
     lo.S2 = 0; lo.rows_per_split2 = 0; lo.tiles2 = 0;
+    lo.S3 = 0; lo.rows_per_split3 = 0;
     lo.off_part = lo.off_db = off;
     if (backward) {
         dw_split(B * L, lo.tiles * lo.tiles * G * n_heads, &lo.S, &lo.rows_per_split);
@@ -1746,7 +2011,9 @@ ProjLayout proj_layout(int B, int L, int H, int G, int n_heads, int backward)
             lo.tiles2 = (dh + dwd::BT - 1) / dwd::BT;
             dw_dma_split(B * L, G, H, dh, n_heads, &lo.S2, &lo.rows_per_split2);
         }
-        const size_t s_max = (size_t)(lo.S > lo.S2 ? lo.S : lo.S2);
+        if (dw_rows_shape_ok(B * L, H, G, dh, dtype == PARARNN_BF16)) dw_rows_split(B * L, G, H, dh, n_heads, dtype == PARARNN_BF16, lo.S, &lo.S3, &lo.rows_per_split3);
+        size_t s_max = (size_t)(lo.S > lo.S2 ? lo.S : lo.S2);
+        if ((size_t)lo.S3 > s_max) s_max = (size_t)lo.S3;
         lo.off_part = off; off += r256(s_max * nw * sizeof(float));
         lo.off_db = off;   off += r256(s_max * G * H * sizeof(float));
     }
@@ -1865,6 +2132,20 @@ bool rows_shape(int M, int H, int G, int n_heads, bool bf, RowsArgs *a, int *blo
     return true;
 }
 
+template <typename AT> hipError_t launch_dw_rows(const DwArgs &a, int kb, int blocks, hipStream_t st)
+{
+#define PARARNN_DW_ROWS(KB) hipLaunchKernelGGL((proj_dw_rows_kernel<AT, KB>), dim3((unsigned)blocks), dim3((64 * DwRows<AT, KB>::WAVES)), 0, st, a)
+    switch (kb) {
+        case 1: PARARNN_DW_ROWS(1); break;
+        case 2: PARARNN_DW_ROWS(2); break;
+        case 3: PARARNN_DW_ROWS(3); break;
+        default:
+            if constexpr (sizeof(AT) == 4) PARARNN_DW_ROWS(4);
+    }
+#undef PARARNN_DW_ROWS
+    return hipGetLastError();
+}
+
 int elementwise_blocks(size_t n)
 {
     size_t blocks = (n + 255) / 256;
@@ -1883,7 +2164,7 @@ int proj_set_dma(int on)
 size_t proj_workspace_bytes(int dtype, int B, int L, int H, int G, int n_heads, int backward)
 {
     if (!shapes_ok(dtype, B, L, H, G, n_heads) || (H / n_heads) % BK) return 0;
-    return proj_layout(B, L, H, G, n_heads, backward).total;
+    return proj_layout(dtype, B, L, H, G, n_heads, backward).total;
 }
 
 int proj_forward(int dtype, const void *x, const float *Wx, const float *bias, int B, int L, int H, int G,
@@ -1893,7 +2174,7 @@ int proj_forward(int dtype, const void *x, const float *Wx, const float *bias, i
     const int dh = H / n_heads;
     if (dh % BK) return PARARNN_UNSUPPORTED;
     if (((uintptr_t)x | (uintptr_t)Wx | (uintptr_t)u | (uintptr_t)workspace) % 16) return PARARNN_UNSUPPORTED;
-    const ProjLayout lo = proj_layout(B, L, H, G, n_heads, 0);
+    const ProjLayout lo = proj_layout(dtype, B, L, H, G, n_heads, 0);
     if (workspace_bytes < lo.total) return PARARNN_WORKSPACE_TOO_SMALL;
     RowsArgs r;
     int blocks;
@@ -1931,7 +2212,7 @@ int proj_backward(int dtype, const void *x, const float *Wx, const void *du, int
     const int dh = H / n_heads;
     if (dh % BK) return PARARNN_UNSUPPORTED;
     if (((uintptr_t)x | (uintptr_t)Wx | (uintptr_t)du | (uintptr_t)dx | (uintptr_t)workspace) % 16) return PARARNN_UNSUPPORTED;
-    const ProjLayout lo = proj_layout(B, L, H, G, n_heads, 1);
+    const ProjLayout lo = proj_layout(dtype, B, L, H, G, n_heads, 1);
     if (workspace_bytes < lo.total) return PARARNN_WORKSPACE_TOO_SMALL;
     char *ws = static_cast<char *>(workspace);
     const size_t nw = (size_t)G * H * dh;
@@ -1961,17 +2242,20 @@ int proj_backward(int dtype, const void *x, const float *Wx, const void *du, int
         a.dbpart = dbias ? reinterpret_cast<float *>(ws + lo.off_db) : nullptr;
         a.M = B * L; a.H = H; a.G = G; a.heads = n_heads; a.dh = dh;
         const bool copy_kernel = bf && g_proj_dma && lo.S2 > 0;
-        a.S = copy_kernel ? lo.S2 : lo.S;
+        const bool rows_kernel = g_proj_dma && lo.S3 > 0;
+        a.S = rows_kernel ? lo.S3 : copy_kernel ? lo.S2 : lo.S;
         if (a.S == 1) {                                 // one range: its sums are the results
             a.part = dWx;
             if (dbias) a.dbpart = dbias;
         }
-        a.rows_per_split = copy_kernel ? lo.rows_per_split2 : lo.rows_per_split;
-        a.tiles = copy_kernel ? lo.tiles2 : lo.tiles;
+        a.rows_per_split = rows_kernel ? lo.rows_per_split3 : copy_kernel ? lo.rows_per_split2 : lo.rows_per_split;
+        a.tiles = rows_kernel ? 1 : copy_kernel ? lo.tiles2 : lo.tiles;
         a.n_blocks = a.tiles * a.tiles * n_heads * G * a.S;
         a.per_xcd = (a.n_blocks + 7) / 8;
         const int blocks = 8 * a.per_xcd;
-        if (copy_kernel) hipLaunchKernelGGL(proj_dw_dma_kernel, dim3(blocks), dim3(512), 0, st, a);
+        if (rows_kernel) {
+            if ((bf ? launch_dw_rows<unsigned short>(a, dh / 64, blocks, st) : launch_dw_rows<float>(a, dh / 64, blocks, st)) != hipSuccess) return PARARNN_HIP_ERROR;
+        } else if (copy_kernel) hipLaunchKernelGGL(proj_dw_dma_kernel, dim3(blocks), dim3(512), 0, st, a);
         else if (bf) hipLaunchKernelGGL(proj_dw_kernel<unsigned short>, dim3(blocks), dim3(256), 0, st, a);
         else hipLaunchKernelGGL(proj_dw_kernel<float>, dim3(blocks), dim3(256), 0, st, a);
         if (hipGetLastError() != hipSuccess) return PARARNN_HIP_ERROR;
