@@ -1040,9 +1040,49 @@ struct RowsArgs {
     const float *bias;     // [G][H] or NULL
     void *u;               // [M][G][H]
     int M, H, G, heads;
-    int parts;             // shares of the rows
+    int log_parts;         // 2^log_parts shares of the rows
     int abreast, J;        // jobs an XCD runs side by side; workgroups of a job's gate
 };
+
+// 32 rows x 32 NI outputs of a wave to memory, rows and channels from `dst` on, `left` rows of them: 2 KB of rows at a time through
+// the wave's patch of LDS, so that a store instruction writes pieces of rows that are as long as can be.  16-byte chunk c of patch
+// row r sits at c ^ r in the low bits.  Rows past the end are dropped by the descriptor; always NI E stores.
+template <typename AT, int NI, bool BIAS>
+__device__ __forceinline__ void rows_out(const f16v (&acc)[NI], const f4v (&bias4)[NI][4], unsigned int lds_epi, unsigned char *dst,
+                                         long long ldu, long long left, int lane)
+{
+    constexpr int E = sizeof(AT), PW = 32 * NI * E, PR = 2048 / PW, CH = PW / 16, SW = CH < 8 ? CH - 1 : 7;
+    const int l32 = lane & 31, half = lane >> 5;
+    const buf_rsrc rc = __builtin_amdgcn_make_buffer_rsrc(dst, 0, left > 0 ? (int)((min(left, 32ll) - 1) * ldu + PW) : 0, 0x27000);
+    const int pr = l32 % PR, r0 = lane / CH;                               // patch row of this lane's outputs, and of its pieces to store
+    unsigned int wr = lds_epi + (unsigned int)(pr * PW + (E == 2 ? 8 * half : 0)), wx = (unsigned int)((pr & SW) ^ (E == 4 ? half : 0)) * 16u;
+    unsigned int rd = lds_epi + (unsigned int)(r0 * PW), rx = (unsigned int)((lane % CH) * 16), off = (unsigned int)r0 * (unsigned int)ldu + rx;
+    asm volatile("" : "+v"(wr), "+v"(wx), "+v"(rd), "+v"(rx), "+v"(off));  // worked out here: there is no room to keep what follows from them
+#pragma unroll
+    for (int ph = 0; ph < 32 / PR; ++ph) {
+        if (l32 / PR == ph) {
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    f4v o = {acc[ni][4 * q], acc[ni][4 * q + 1], acc[ni][4 * q + 2], acc[ni][4 * q + 3]};
+                    if constexpr (BIAS) o += bias4[ni][q];
+                    const unsigned int c = E == 2 ? 4 * ni + q : 8 * ni + 2 * q;
+                    store4((__attribute__((address_space(3))) AT *)(unsigned long long)(wr + ((c * 16u) ^ wx)), o);
+                }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int it = 0; it < 2; ++it) {
+            const unsigned int sw = (unsigned int)((r0 + it * (PR / 2)) & SW) * 16u;
+            const u4v v = *(const __attribute__((address_space(3))) u4v *)(unsigned long long)(rd + it * (PR / 2) * PW + (rx ^ sw));
+            __builtin_amdgcn_raw_buffer_store_b128(v, rc, off + (unsigned int)(PR * ph + it * (PR / 2)) * (unsigned int)ldu, 0, 0);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+}
 
 template <typename AT, int KB, bool BIAS>
 __global__ __launch_bounds__((64 * RowsShape<AT, KB>::WAVES)) void proj_rows_kernel(const RowsArgs a)
@@ -1071,10 +1111,10 @@ __global__ __launch_bounds__((64 * RowsShape<AT, KB>::WAVES)) void proj_rows_ker
         const int c = E == 2 ? 2 * q + half : 4 * (q >> 1) + 2 * half + (q & 1);   // bf16: round q of four; fp32: piece q % 2 of round q / 2
         fo[q] = (unsigned int)(32 * wm + l32) * ROW + (unsigned int)(c ^ dma_swz(l32)) * 16u;
     }
-    const int steps = (a.M + R - 1) / R, jobs = a.heads * a.parts;
+    const int steps = (a.M + R - 1) / R, jobs = a.heads << a.log_parts;
     for (int job = xcd + 8 * lane_job; job < jobs; job += 8 * a.abreast) {
         const int head = job % a.heads, part = job / a.heads;
-        const int s0 = (int)((long long)steps * part / a.parts), s1 = (int)((long long)steps * (part + 1) / a.parts);
+        const int s0 = (int)((long long)steps * part >> a.log_parts), s1 = (int)((long long)steps * (part + 1) >> a.log_parts);
         const int count = s1 - s0 > turn ? (s1 - s0 - turn + a.J - 1) / a.J : 0;   // steps s0 + turn + i J
         if (count == 0) continue;
         const unsigned long long x0 = (unsigned long long)a.x + (unsigned long long)head * ROW;
@@ -1183,40 +1223,8 @@ __global__ __launch_bounds__((64 * RowsShape<AT, KB>::WAVES)) void proj_rows_ker
                         acc[ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[ni][2 * g + q], fa[g & 1][q], acc[ni], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            // 2 KB of output rows at a time through this wave's patch of LDS, so that a store instruction writes whole lines;
-            // 16-byte chunk c of patch row r sits at c ^ (r % 8).  Rows past the end are dropped by the descriptor.
-            const long long row = (long long)(s0 + turn + (long long)i * a.J) * R + 32 * wm, left = a.M - row;
-            unsigned char *dst = static_cast<unsigned char *>(a.u) + row * ldu + (long long)o0 * E;
-            const buf_rsrc rc = __builtin_amdgcn_make_buffer_rsrc(dst, 0, left > 0 ? (int)((min(left, 32ll) - 1) * ldu + 64 * E) : 0, 0x27000);
-            constexpr int PR = 32 / E, CH = 4 * E;                                 // rows of the patch, chunks of a row
-            const int pr = l32 % PR, r0 = lane / CH;                               // patch row of this lane's outputs, and of its pieces to store
-            unsigned int wr = lds_epi + (unsigned int)(pr * (64 * E) + (E == 2 ? 8 * half : 0)), wx = (unsigned int)((pr & 7) ^ (E == 4 ? half : 0)) * 16u;
-            unsigned int rd = lds_epi + (unsigned int)(r0 * (64 * E)), rx = (unsigned int)((lane % CH) * 16), off = (unsigned int)r0 * (unsigned int)ldu + rx;
-            asm volatile("" : "+v"(wr), "+v"(wx), "+v"(rd), "+v"(rx), "+v"(off));  // worked out here: there is no room to keep what follows from them
-#pragma unroll
-            for (int ph = 0; ph < 32 / PR; ++ph) {
-                if (l32 / PR == ph) {
-#pragma unroll
-                    for (int ni = 0; ni < 2; ++ni)
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            f4v o = {acc[ni][4 * q], acc[ni][4 * q + 1], acc[ni][4 * q + 2], acc[ni][4 * q + 3]};
-                            if constexpr (BIAS) o += bias4[ni][q];
-                            const unsigned int c = E == 2 ? 4 * ni + q : 8 * ni + 2 * q;
-                            store4((__attribute__((address_space(3))) AT *)(unsigned long long)(wr + ((c * 16u) ^ wx)), o);
-                        }
-                }
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                for (int it = 0; it < 2; ++it) {
-                    const unsigned int sw = (unsigned int)((r0 + it * (PR / 2)) & 7) * 16u;
-                    const u4v v = *(const __attribute__((address_space(3))) u4v *)(unsigned long long)(rd + it * (PR / 2) * (64 * E) + (rx ^ sw));
-                    __builtin_amdgcn_raw_buffer_store_b128(v, rc, off + (unsigned int)(PR * ph + it * (PR / 2)) * (unsigned int)ldu, 0, 0);
-                }
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-            }
+            const long long row = (long long)(s0 + turn + (long long)i * a.J) * R + 32 * wm;
+            rows_out<AT, 2, BIAS>(acc, bias4, lds_epi, static_cast<unsigned char *>(a.u) + row * ldu + (long long)o0 * E, ldu, a.M - row, lane);
             stage = stage + 1 == NS ? 0 : stage + 1;
         }
         // nothing of this job is in flight when the next one fills the stages
@@ -1224,6 +1232,188 @@ __global__ __launch_bounds__((64 * RowsShape<AT, KB>::WAVES)) void proj_rows_ker
     }
 }
 
+
+// ------------------------------- dx of narrow heads: the weights of all gates of a head stay in registers
+// dx = sum over the gates of du_g W_g for heads of at most 256 channels, the same way: a workgroup keeps a head's G d_h x d_h
+// weights (a wave 32 of the input channels j, 64 at d_h = 64), a step is R rows of one gate's du, and G steps add up to 32
+// rows x channels of a row block per wave and turn.  Bound by memory: three gates, 65536 x 512 in heads of 64, bf16 73 -> 45 us
+// (6.0 TB/s, in part from the last level of cache), 20000 x 768 in heads of 192 44 -> 28, 65536 x 1024 in heads of 256 142 -> 132;
+// fp32: 32768 x 1024 in heads of 256 130 -> 113, four gates of 6993 x 768 in heads of 192 35 -> 31.
+//
+//   W        arrives as fp32 rows i through two halves of the stages; a lane picks its column j of eight rows
+//   waits    copies as above; the stores come with every G-th step: which of them lie between is known by the gate, but for
+//            the first rows, which have none before them
+template <typename AT, int KB, int G> struct DxShape {
+    static constexpr int E = sizeof(AT), K = 64 * KB, ROW = K * E;
+    static constexpr int NI = KB == 1 ? 2 : 1, NG = 2 * KB / NI;            // 32-channel blocks of a wave, groups of them
+    static constexpr int MG = KB == 1 ? 16 / E : KB == 2 ? 2 : 1, RB = E == 2 && KB > 1 && KB * G < 12 ? 2 : 1;      // (192 registers of weights leave room for one row block)
+    static constexpr int WAVES = MG * NG, R = 32 * MG * RB, STAGE = R * ROW, NS = STAGE <= 16384 ? 8 : STAGE < 32768 && E == 4 ? 6 : 4;
+    static constexpr int N = STAGE / 1024 / WAVES, STORES = RB * NI * E;
+    static constexpr int RW = NS * STAGE / 2 / (4 * K) < K ? NS * STAGE / 2 / (4 * K) : K;      // rows of W in half of the stages
+    static constexpr int PER = RW * K * 4 / 1024 / WAVES;
+    static_assert(N * 1024 * WAVES == STAGE && PER * 1024 * WAVES == RW * K * 4 && K % RW == 0 && RW % 16 == 0, "");
+};
+
+struct DxArgs {
+    const void *du;        // [M][G][H]
+    const float *Wx;       // [G][H][dh]
+    void *dx;              // [M][H]
+    int M, H, heads;
+    int log_parts, abreast, J;
+};
+
+template <typename AT, int KB, int G>
+__global__ __launch_bounds__((64 * DxShape<AT, KB, G>::WAVES)) void proj_dx_rows_kernel(const DxArgs a)
+{
+    typedef DxShape<AT, KB, G> S;
+    constexpr int E = S::E, K = S::K, R = S::R, ROW = S::ROW, NS = S::NS, N = S::N, NI = S::NI, RB = S::RB;
+    __shared__ __attribute__((aligned(128))) unsigned char s_op[NS * S::STAGE];
+    __shared__ __attribute__((aligned(16))) unsigned char s_epi[S::WAVES][2048];
+    const int xcd = blockIdx.x & 7, wg = blockIdx.x >> 3, lane_job = wg % a.abreast, turn = wg / a.abreast;
+    if (turn >= a.J) return;
+    const int tid = threadIdx.x, lane = tid & 63, w = (int)uniform((unsigned int)tid >> 6), wm = w / S::NG, wn = w % S::NG;
+    const int half = lane >> 5, l32 = lane & 31;
+    const unsigned int lds_op = lds_address(s_op), lds_epi = lds_address(&s_epi[w][0]);
+    const long long ldu = (long long)G * a.H * E, ldx = (long long)a.H * E;        // bytes
+    unsigned int va[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        const int byte = (w * N + j) * 1024 + lane * 16, row = byte / ROW, c = byte % ROW / 16;
+        va[j] = (unsigned int)row * (unsigned int)ldu + (unsigned int)(c ^ dma_swz(row)) * 16u;
+    }
+    // of this lane's first fragment; the others of 128 bytes of a row are at this address with two of its bits changed
+    const unsigned int fo = lds_op + (unsigned int)(32 * RB * wm + l32) * ROW + (unsigned int)(((E == 2 ? 1 : 2) * half) ^ dma_swz(l32)) * 16u;
+    const int steps = (a.M + R - 1) / R, jobs = a.heads << a.log_parts;
+    for (int job = xcd + 8 * lane_job; job < jobs; job += 8 * a.abreast) {
+        const int head = job % a.heads, part = job / a.heads;
+        const int s0 = (int)((long long)steps * part >> a.log_parts), s1 = (int)((long long)steps * (part + 1) >> a.log_parts);
+        const int count = s1 - s0 > turn ? (s1 - s0 - turn + a.J - 1) / a.J : 0;   // row blocks s0 + turn + i J
+        if (count == 0) continue;
+
+        bf8v wf[NI][G][4 * KB];
+        {
+            constexpr int PER_GATE = K / S::RW, ROUNDS = G * PER_GATE;
+            auto fetch = [&](int r) {
+                const unsigned long long p = (unsigned long long)(a.Wx + ((size_t)(r / PER_GATE) * a.H + (size_t)head * K + (size_t)(r % PER_GATE) * S::RW) * K);
+                const u4v rs = {uniform((unsigned int)p), uniform((unsigned int)(p >> 32) & 0xffffu), (unsigned int)(S::RW * K * 4), 0x27000u};
+#pragma unroll
+                for (int j = 0; j < S::PER; ++j) {
+                    const unsigned int at = (unsigned int)((w * S::PER + j) * 1024);
+                    copy_to_lds_16(lds_op + (unsigned int)((r & 1) * (NS * S::STAGE / 2)) + at, rs, (unsigned int)lane * 16u, at);
+                }
+            };
+            fetch(0);
+            if (ROUNDS > 1) fetch(1);
+#pragma unroll
+            for (int r = 0; r < ROUNDS; ++r) {
+                if (r + 1 < ROUNDS) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(S::PER) : "memory");
+                else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+                unsigned int w0 = lds_op + (unsigned int)((r & 1) * (NS * S::STAGE / 2) + (8 * half * K + 32 * NI * wn + l32) * 4);
+                asm volatile("" : "+v"(w0));                                       // what is added is part of the instructions
+#pragma unroll
+                for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+                    for (int k = 0; k < S::RW / 16; ++k) {
+                        const __attribute__((address_space(3))) float *q = (const __attribute__((address_space(3))) float *)(unsigned long long)w0 + 16 * k * K + 32 * ni;
+                        const u4v v = {pack2(q[0], q[K]), pack2(q[2 * K], q[3 * K]), pack2(q[4 * K], q[5 * K]), pack2(q[6 * K], q[7 * K])};
+                        bf8v f = __builtin_bit_cast(bf8v, v);
+                        asm volatile("" : "+v"(f));                                // read before what follows overwrites it
+                        wf[ni][r / PER_GATE][r % PER_GATE * (S::RW / 16) + k] = f;
+                        if (KB * G >= 12 && k % 2 == 1) asm volatile("" ::: "memory");      // registers for two fragments at a time
+                    }
+                asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+                if (r + 2 < ROUNDS) fetch(r + 2);
+            }
+        }
+
+        const unsigned long long u0 = (unsigned long long)a.du + (unsigned long long)head * ROW;
+        // step t: gate t % G of row block t / G
+        int ci = 0, cg = 0;                                                        // of the next copies
+        auto issue = [&](int stage) {
+            const long long row = (long long)(s0 + turn + (long long)ci * a.J) * R, left = a.M - row;
+            const unsigned long long p = u0 + (unsigned long long)(row * ldu + (long long)cg * ldx);
+            const unsigned int n = ci < count ? (unsigned int)((min(left, (long long)R) - 1) * ldu + ROW) : 0u;
+            const u4v rs = {uniform((unsigned int)p), uniform((unsigned int)(p >> 32) & 0xffffu), uniform(n), 0x27000u};
+#pragma unroll
+            for (int j = 0; j < N; ++j)
+                copy_to_lds_16(lds_op + (unsigned int)stage * S::STAGE + (unsigned int)(w * N + j) * 1024u, rs, va[j], 0u);
+            if (++cg == G) {
+                cg = 0;
+                ++ci;
+            }
+        };
+#pragma unroll
+        for (int q = 0; q < NS - 1; ++q) issue(q);
+        int stage = 0, before = 0;                                                 // row blocks stored before this one
+        f16v acc[RB][NI];
+        for (int i = 0; i < count; ++i) {
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) acc[rb][ni][v] = 0.0f;
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                // the copies of this step have landed: behind them those of NS - 2 steps, and the stores at the ends of row blocks
+                // among the NS - 1 steps before
+                constexpr int COPIES = N * (NS - 2);
+                constexpr int STORES = S::STORES;
+                const int ends = g < NS - 1 ? (NS - 2 - g) / G + 1 : 0;
+                if (ends > 0) {
+                    asm volatile("" : "+s"(before));                               // (no copy of the loop for the first row blocks)
+                    if (before < ends) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(COPIES) : "memory");
+                    else if (ends == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(COPIES + STORES) : "memory");
+                    else if (ends == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(COPIES + 2 * STORES) : "memory");
+                    else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(COPIES + 3 * STORES) : "memory");
+                } else {
+                    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(COPIES) : "memory");
+                }
+                asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+                issue(stage == 0 ? NS - 1 : stage - 1);
+                // fragments are read two ahead of their products
+                const unsigned int op = fo + (unsigned int)stage * S::STAGE;
+                bf8v fa[3][RB];
+                auto read = [&](int kb, bf8v(&f)[RB]) {
+                    unsigned int at = op ^ (E == 2 ? 32u * (kb & 3) : 64u * (kb & 1));
+                    if (KB * G >= 12) asm volatile("" : "+v"(at));                 // not kept for the next 128 bytes
+#pragma unroll
+                    for (int rb = 0; rb < RB; ++rb) {
+                        if constexpr (E == 2) {
+                            f[rb] = *(const __attribute__((address_space(3))) bf8v *)(unsigned long long)(at + (kb >> 2) * 128 + rb * (32 * ROW));
+                        } else {
+                            Raw8f r;
+                            r.lo = *(const __attribute__((address_space(3))) f4v *)(unsigned long long)(at + (kb >> 1) * 128 + rb * (32 * ROW));
+                            r.hi = *(const __attribute__((address_space(3))) f4v *)(unsigned long long)((at ^ 16u) + (kb >> 1) * 128 + rb * (32 * ROW));
+                            f[rb] = __builtin_bit_cast(bf8v, to_bf16x8(r));
+                        }
+                    }
+                };
+                read(0, fa[0]);
+                read(1, fa[1]);
+#pragma unroll
+                for (int kb = 0; kb < 4 * KB; ++kb) {
+                    if (kb + 2 < 4 * KB) read(kb + 2, fa[(kb + 2) % 3]);
+#pragma unroll
+                    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                        for (int ni = 0; ni < NI; ++ni)
+                            acc[rb][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[ni][g][kb], fa[kb % 3][rb], acc[rb][ni], 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                stage = stage + 1 == NS ? 0 : stage + 1;
+            }
+            const f4v none[NI][4] = {};
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) {
+                const long long row = (long long)(s0 + turn + (long long)i * a.J) * R + 32 * (RB * wm + rb);
+                rows_out<AT, NI, false>(acc[rb], none, lds_epi, static_cast<unsigned char *>(a.dx) + row * ldx + (long long)(head * K + 32 * NI * wn) * E, ldx, a.M - row, lane);
+            }
+            ++before;
+        }
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    }
+}
 
 // --------------------------------------------------- dWx and dbias (TN product)
 struct DwArgs {
@@ -2111,23 +2301,58 @@ template <typename AT> hipError_t launch_rows(const RowsArgs &a, int kb, int blo
         default: return launch_rows_kb<AT, 4>(a, blocks, st);
     }
 }
+// Jobs: every XCD gets the same number of them; side by side as many as take the least time, a job's weights at about two steps
+// of R rows (with three heads one after the other, 300 rows took 22 us instead of 16).  `each`: workgroups that take the same rows.
+void rows_jobs(int M, int n_heads, int each, int R, int slots, int *log_parts, int *abreast, int *J)
+{
+    *log_parts = 3;
+    for (int h = n_heads; h % 2 == 0 && *log_parts > 0; h /= 2) --*log_parts;
+    const int jobs = (n_heads << *log_parts) / 8;
+    const double steps = (double)M / (1 << *log_parts) / R;
+    double best = 0.0;
+    for (int n = 1; n <= jobs && n * each <= slots; ++n) {
+        const int j = slots / (n * each);
+        const double t = (double)((jobs + n - 1) / n) * (2.0 + ceil(steps / j));
+        if (n == 1 || t < best) { best = t; *abreast = n; *J = j; }
+    }
+}
 bool rows_shape(int M, int H, int G, int n_heads, bool bf, RowsArgs *a, int *blocks)
 {
     const int dh = H / n_heads, slots = device_cu_count() / 8;
     if (!g_proj_dma || dh % 64 || dh > 256 || slots < G || (long long)G * H >= (1 << 22)) return false;
     a->M = M; a->H = H; a->G = G; a->heads = n_heads;
-    // every XCD gets the same number of jobs; side by side as many of them as take the least time, a job's weights at
-    // about two steps (with three heads one after the other, 300 rows took 22 us instead of 16)
-    a->parts = 8;
-    for (int h = n_heads; h % 2 == 0 && a->parts > 1; h /= 2) a->parts /= 2;
-    const int jobs = n_heads * a->parts / 8;
-    const double steps = (double)M / a->parts / (bf ? (dh <= 128 ? 16384 / dh : 64) : (dh == 64 ? 128 : dh == 256 ? 32 : 64));
-    double best = 0.0;
-    for (int n = 1; n <= jobs && n * G <= slots; ++n) {
-        const int J = slots / (n * G);
-        const double t = (double)((jobs + n - 1) / n) * (2.0 + ceil(steps / J));
-        if (n == 1 || t < best) { best = t; a->abreast = n; a->J = J; }
+    rows_jobs(M, n_heads, G, bf ? (dh <= 128 ? 16384 / dh : 64) : (dh == 64 ? 128 : dh == 256 ? 32 : 64), slots, &a->log_parts, &a->abreast, &a->J);
+    *blocks = 8 * slots;
+    return true;
+}
+
+// dx with the weights in registers: three and four gates of heads of at most 256 channels, as far as the weights fit (192 of a
+// lane's registers: not four gates of 256).  792 problems of 1 to 60001 rows and 3 to 48 gates x heads, both types: 1.6 times less on the
+// geometric mean than with the kernels above.  Heads of 256 take 10 us to load their weights, which 60001 x 256 or 16000 x 1024
+// rows and channels (du and dx lie in the last level of cache and the tiles run at 3.5 TB/s) do not give back: 0.86-0.98
+// in bf16, 0.93-1.16 in fp32; half of that 1.06-1.28, twice as many 1.09-1.26.
+template <typename AT> hipError_t launch_dx_rows(const DxArgs &a, int G, int kb, int blocks, hipStream_t st)
+{
+#define PARARNN_DX_ROWS(KB, G) hipLaunchKernelGGL((proj_dx_rows_kernel<AT, KB, G>), dim3((unsigned)blocks), dim3((64 * DxShape<AT, KB, G>::WAVES)), 0, st, a)
+    switch (8 * kb + G) {
+        case 8 + 3: PARARNN_DX_ROWS(1, 3); break;
+        case 8 + 4: PARARNN_DX_ROWS(1, 4); break;
+        case 16 + 3: PARARNN_DX_ROWS(2, 3); break;
+        case 16 + 4: PARARNN_DX_ROWS(2, 4); break;
+        case 24 + 3: PARARNN_DX_ROWS(3, 3); break;
+        case 24 + 4: PARARNN_DX_ROWS(3, 4); break;
+        default: PARARNN_DX_ROWS(4, 3);
     }
+#undef PARARNN_DX_ROWS
+    return hipGetLastError();
+}
+bool dx_rows_shape(int M, int H, int G, int n_heads, bool bf, DxArgs *a, int *blocks)
+{
+    const int dh = H / n_heads, slots = device_cu_count() / 8;
+    if (!g_proj_dma || dh % 64 || dh > 256 || (G != 3 && G != 4) || (dh == 256 && G == 4) || slots < 1 || (long long)G * H >= (1 << 22)) return false;
+    if (dh == 256 && (double)M * H > 10e6 && (double)M * H < 24e6) return false;
+    a->M = M; a->H = H; a->heads = n_heads;
+    rows_jobs(M, n_heads, 1, bf ? (dh <= 128 ? 16384 / dh : dh * G < 768 ? 64 : 32) : dh == 64 ? 128 : dh == 128 ? 64 : 32, slots, &a->log_parts, &a->abreast, &a->J);
     *blocks = 8 * slots;
     return true;
 }
@@ -2218,7 +2443,12 @@ int proj_backward(int dtype, const void *x, const float *Wx, const void *du, int
     const size_t nw = (size_t)G * H * dh;
     const bool bf = dtype == PARARNN_BF16;
     hipError_t e = hipSuccess;
-    if (dx) {
+    DxArgs r;
+    int blocks;
+    if (dx && dx_rows_shape(B * L, H, G, n_heads, bf, &r, &blocks)) {
+        r.du = du; r.Wx = Wx; r.dx = dx;
+        if ((bf ? launch_dx_rows<unsigned short>(r, G, dh / 64, blocks, st) : launch_dx_rows<float>(r, G, dh / 64, blocks, st)) != hipSuccess) return PARARNN_HIP_ERROR;
+    } else if (dx) {
         unsigned short *Wt = reinterpret_cast<unsigned short *>(ws + lo.off_w);
         int *tickets = reinterpret_cast<int *>(ws + lo.off_tickets);
         hipLaunchKernelGGL(proj_wt_kernel, dim3((unsigned)(nw / 4096)), dim3(256), 0, st, Wx, Wt, G, H, dh, tickets);
@@ -2252,7 +2482,7 @@ int proj_backward(int dtype, const void *x, const float *Wx, const void *du, int
         a.tiles = rows_kernel ? 1 : copy_kernel ? lo.tiles2 : lo.tiles;
         a.n_blocks = a.tiles * a.tiles * n_heads * G * a.S;
         a.per_xcd = (a.n_blocks + 7) / 8;
-        const int blocks = 8 * a.per_xcd;
+        blocks = 8 * a.per_xcd;
         if (rows_kernel) {
             if ((bf ? launch_dw_rows<unsigned short>(a, dh / 64, blocks, st) : launch_dw_rows<float>(a, dh / 64, blocks, st)) != hipSuccess) return PARARNN_HIP_ERROR;
         } else if (copy_kernel) hipLaunchKernelGGL(proj_dw_dma_kernel, dim3(blocks), dim3(512), 0, st, a);
