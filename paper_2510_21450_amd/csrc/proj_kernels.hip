@@ -1237,7 +1237,7 @@ __global__ __launch_bounds__((64 * RowsShape<AT, KB>::WAVES)) void proj_rows_ker
 // dx = sum over the gates of du_g W_g for heads of at most 256 channels, the same way: a workgroup keeps a head's G d_h x d_h
 // weights (a wave 32 of the input channels j, 64 at d_h = 64), a step is R rows of one gate's du, and G steps add up to 32
 // rows x channels of a row block per wave and turn.  Bound by memory: three gates, 65536 x 512 in heads of 64, bf16 73 -> 45 us
-// (6.0 TB/s, in part from the last level of cache), 20000 x 768 in heads of 192 44 -> 28, 65536 x 1024 in heads of 256 142 -> 132;
+// (6.0 TB/s, in part from the last level of cache), 20000 x 768 in heads of 192 44 -> 27;
 // fp32: 32768 x 1024 in heads of 256 130 -> 113, four gates of 6993 x 768 in heads of 192 35 -> 31.
 //
 //   W        arrives as fp32 rows i through two halves of the stages; a lane picks its column j of eight rows
@@ -2330,7 +2330,9 @@ bool rows_shape(int M, int H, int G, int n_heads, bool bf, RowsArgs *a, int *blo
 // lane's registers: not four gates of 256).  792 problems of 1 to 60001 rows and 3 to 48 gates x heads, both types: 1.6 times less on the
 // geometric mean than with the kernels above.  Heads of 256 take 10 us to load their weights, which 60001 x 256 or 16000 x 1024
 // rows and channels (du and dx lie in the last level of cache and the tiles run at 3.5 TB/s) do not give back: 0.86-0.98
-// in bf16, 0.93-1.16 in fp32; half of that 1.06-1.28, twice as many 1.09-1.26.
+// in bf16, 0.93-1.16 in fp32; half of that 1.06-1.28.  Larger ones are faster by themselves (65536 x 1024 in bf16 142 -> 125 us),
+// in fp32 1.1-1.2 times; in bf16 a training step gained 1 % on one device and lost 3 % on another, whose other kernels
+// slowed down (the forward solve after it 366 -> 403 us): the tiles stay there.
 template <typename AT> hipError_t launch_dx_rows(const DxArgs &a, int G, int kb, int blocks, hipStream_t st)
 {
 #define PARARNN_DX_ROWS(KB, G) hipLaunchKernelGGL((proj_dx_rows_kernel<AT, KB, G>), dim3((unsigned)blocks), dim3((64 * DxShape<AT, KB, G>::WAVES)), 0, st, a)
@@ -2350,7 +2352,7 @@ bool dx_rows_shape(int M, int H, int G, int n_heads, bool bf, DxArgs *a, int *bl
 {
     const int dh = H / n_heads, slots = device_cu_count() / 8;
     if (!g_proj_dma || dh % 64 || dh > 256 || (G != 3 && G != 4) || (dh == 256 && G == 4) || slots < 1 || (long long)G * H >= (1 << 22)) return false;
-    if (dh == 256 && (double)M * H > 10e6 && (double)M * H < 24e6) return false;
+    if (dh == 256 && (double)M * H > 10e6 && (bf || (double)M * H < 24e6)) return false;
     a->M = M; a->H = H; a->heads = n_heads;
     rows_jobs(M, n_heads, 1, bf ? (dh <= 128 ? 16384 / dh : dh * G < 768 ? 64 : 32) : dh == 64 ? 128 : dh == 128 ? 64 : 32, slots, &a->log_parts, &a->abreast, &a->J);
     *blocks = 8 * slots;
