@@ -111,7 +111,7 @@ inline TileCfg choose_tile(const CellInfo &ci, int dtype, bool backward, int H, 
         if (lstm) cfg = {1, 1, 8, 16};                   // 64 channels x 128 steps
         else if (bf) cfg = {1, 1, 16, 8};                // 64 channels x 128 steps (3 % faster than two channels per lane on config 5)
         else cfg = {1, 1, 8, 16};                        // 64 channels x 128 steps
-    } else {
+    } else {                                             // (backward_tile below goes by B and L as well)
         if (ci.kind == PARARNN_PARALSTM_DIAG) cfg = {1, 1, 12, 8};   // 64 channels x 96 steps
         else if (lstm && !bf) cfg = {1, 2, 8, 8};        // 32 channels x 128 steps (3 % faster than 64 x 128 on config 3)
         else if (lstm) cfg = {1, 1, 16, 8};              // 64 channels x 128 steps
@@ -123,6 +123,42 @@ inline TileCfg choose_tile(const CellInfo &ci, int dtype, bool backward, int H, 
         cfg.vec = ov[0]; cfg.ll = ov[1]; cfg.c = ov[2]; cfg.w = ov[3];
     }
     return cfg;
+}
+
+// The tile of a backward pass of a scalar or 2x2 cell with carry records, by sweeps over 300 to 60000 steps of 2048 to 65792
+// channels in all (times / times of choose_tile's shape with its rows staged whenever they can be).  Rows of whole lines
+// (64 channels, bf16) are worth staging once the tensors are far larger than the last-level cache; before that, and for
+// other rows, plain loads are faster (GRU 8 x 1000 x 1536 0.85, 32 x 700 x 2056 0.71).
+//   scalar   bf16: 64 channels x 64 steps; of few channels, or of up to 8192 with long sequences, x 128 (2 x 1536 x 1024 0.67, 2 x 32768 x
+//            2048 staged 0.88)
+//   2x2      two gates: 64 x 64 in four waves (bf16 8 x 700 x 1536 0.87, fp32 8 x 4096 x 1536 0.87); of few channels eight waves
+//            in bf16 (2 x 1001 x 1024 0.64), 32 x 128 in fp32
+//   more     bf16 LSTM: x 128 staged from 1.8e7 elements on (8 x 2048 x 2048 260 -> 206 us), before that x 96 and, with 8192
+//   gates    channels or more, x 32 (16 x 300 x 2048 0.86); rows of other lengths 0.8-0.9 with the same.  ParaLSTM: x 96, or x 64
+//            staged (16 x 2048 x 2048 0.91).  fp32: x 96 instead of 32 x 128 (0.81-0.98), x 32 for many channels up to 2048
+//            steps (8 x 2048 x 1536 0.90)
+inline TileCfg backward_tile(const CellInfo &ci, int dtype, int B, int L, int H, const TileCfg &table)
+{
+    if (ci.S > 2 || H <= 32 || settings().tile[0] > 0) return table;
+    const bool bf = dtype == PARARNN_BF16, whole = H % 64 == 0;
+    const double channels = (double)B * H, n = channels * L;
+    const TileCfg x32 = {1, 1, 4, 8}, x64 = {1, 1, 8, 8}, x96 = {1, 1, 12, 8}, x128 = {1, 1, 16, 8}, x128w = {1, 1, 8, 16}, x64n = {1, 1, 16, 4};
+    if (ci.S == 1) return !bf ? table : channels < 4096 || (channels <= 8192 && L >= 4096) ? x128w : x64;
+    if (ci.G <= 2) return channels >= 6000 ? x64n : bf ? x128 : table;
+    if (ci.kind == PARARNN_PARALSTM_DIAG) {
+        if (!bf || channels < 8192) return x96;
+        return whole ? (n >= 1.6e7 ? x64 : x96) : channels >= 32768 ? x32 : x96;
+    }
+    if (!bf) return channels < 1024 ? table : channels >= 12288 && L <= 2048 ? x32 : x96;
+    if (whole && n >= 1.8e7) return x128;
+    return channels >= (whole ? 8192 : 32768) ? x32 : x96;
+}
+// ... and whether its rows are staged
+inline bool backward_staged(const CellInfo &ci, int B, int L, int H)
+{
+    const double n = (double)B * L * H;
+    if (ci.S > 2) return true;
+    return H % 64 == 0 && n >= (ci.S == 1 ? 4e7 : ci.G <= 2 ? 3e7 : 0.0);
 }
 
 struct Layout {
@@ -159,6 +195,7 @@ inline Layout make_layout(const CellInfo &ci, int dtype, int B, int L, int H, bo
 {
     Layout lo;
     lo.cfg = force ? *force : choose_tile(ci, dtype, backward, H, align_elems, fused);
+    if (backward && !force) lo.cfg = backward_tile(ci, dtype, B, L, H, lo.cfg);
     const int CW = (kWave / lo.cfg.ll) * lo.cfg.vec, T = lo.cfg.c * lo.cfg.ll * lo.cfg.w;
     ScanGeom &g = lo.g;
     g.B = B; g.L = L; g.H = H; g.T = T;
@@ -874,7 +911,8 @@ int backward_pass(const CellInfo &ci, int dtype, const float *params, const void
     // rows that the kernel may copy straight into LDS, 16 bytes per lane: bf16 rows that start on 16-byte
     // boundaries, and row offsets that stay inside the 32-bit range of a buffer instruction
     a.stage = settings().stage_enabled && dtype == PARARNN_BF16 && H % 8 == 0 && aligned(u, 16) && aligned(h, 16) &&
-              aligned(dL_dh, 16) && (double)H * 2.0 * (16.0 * ci.G) < 4.0e9;
+              aligned(dL_dh, 16) && (double)H * 2.0 * (16.0 * ci.G) < 4.0e9 &&
+              (settings().tile[0] > 0 || backward_staged(ci, B, L, H));
     a.stream = dtype == PARARNN_BF16 ? backward_stream((size_t)B * L * H * 2 * (2 * ci.G + 2 * ci.S)) : 0;
     const int rc = backward_diag<Cell>(ci, dtype, lo, a, st, dL_dparams);
     if (rc != PARARNN_OK) workspace_forget(workspace);
