@@ -220,7 +220,7 @@ def kernel_figures(run, reps, counters):
         out["algorithmic_flops_per_launch"] = flops_kernel
         out["chunk_products_tflops"] = ach
         out["chunk_products_frac_mfma"] = ach / MFMA_F32_PEAK_TFLOPS
-        out["roofline"] = {"bound": "latency", "kernel": "dense_wavefront_kernel", "achieved": ach_solve,
+        out["roofline"] = {"bound": "latency", "kernel": "dense_stretch_kernel", "achieved": ach_solve,
                            "peak": MFMA_F32_PEAK_TFLOPS, "unit": "TFLOP/s",
                            "frac": ach_solve / MFMA_F32_PEAK_TFLOPS, "traffic": cnt.get("dominant", {}).get("traffic_bytes")}
         run.extra = (dfac, Aout)

@@ -95,15 +95,15 @@ def counter_rows(prefix):
 def classes(kind):
     """Launch classes of a workload: name -> (kernel-name pattern, which dispatches of it)."""
     if kind == "dense":
-        return {"dominant": (r"^dense_wavefront_kernel", "work"),           # the whole solve
+        return {"dominant": (r"^dense_(stretch|wavefront)_kernel", "work"), # all the steps of a solve
                 "products": (r"^dense_products_sweep_kernel<false", "work")}
-    return {"dominant": (r"^newton_(fused|short)_kernel<", "longest"),  # first block of a solve, or all of it
+    return {"dominant": (r"^newton_(fused|short|walk)_kernel<", "longest"),  # first block of a solve, or all of it
             "iter": (r"^newton_iter_kernel<.*false>$", "work"),        # one iteration per launch, from the iterate
             "bwd": (r"^backward_kernel<", "work"),
             # the input projection in front of the solve (four heads; not part of the timed step)
-            "proj_fwd": (r"^proj_gemm_nt(_dma(_f32)?)?_kernel<.*true>", "work"),
-            "proj_dx": (r"^proj_gemm_nt(_dma(_f32)?)?_kernel<.*false>", "work"),
-            "proj_dw": (r"^proj_dw_(dma_)?kernel", "work")}
+            "proj_fwd": (r"^proj_(rows_kernel<|gemm_nt(_dma(_f32)?)?_kernel<.*true>)", "work"),
+            "proj_dx": (r"^proj_(dx_rows_kernel<|gemm_nt(_dma(_f32)?)?_kernel<.*false>)", "work"),
+            "proj_dw": (r"^proj_dw_(dma_|rows_)?kernel", "work")}
 
 
 def pick(values, how):
