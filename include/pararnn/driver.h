@@ -453,9 +453,10 @@ inline float walk_us(const WalkCost &k, const CellInfo &ci, int dtype, bool wide
 {
     const int esz = dtype == PARARNN_BF16 ? 2 : 4, lds_esz = wide ? esz : 4;
     const size_t lds = (size_t)k.c * ci.G * 64 * k.w * lds_esz + ((size_t)k.w * kShortCarries * ci.S << sh.lps_log2) * 4 + 64;
-    int per_unit = (int)((size_t)163840 / (lds > 1 ? lds : 1));
+    // tensors off 16 bytes are copied a dword per element: the kernel for them has to fit too (walk_offered)
+    if ((size_t)k.c * ci.G * 64 * k.w * 4 + ((size_t)k.w * kShortCarries * ci.S << sh.lps_log2) * 4 > 163840 - 256) return 1e30f;
+    int per_unit = (int)(163840 / lds);
     if (per_unit > k.waves) per_unit = k.waves;
-    if (per_unit < 1) return 1e30f;
     const int full = sh.n_items / (kShortUnits * per_unit), left = sh.n_items - full * kShortUnits * per_unit;
     auto round = [&](int on) { return k.one + k.more_each * (float)on; };
     float rounds = (float)full * round(per_unit);

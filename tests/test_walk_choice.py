@@ -64,6 +64,19 @@ def test_bounds_of_a_walk(choose):
     assert taken > 100
 
 
+def test_room_for_tensors_at_odd_addresses(choose):
+    """The choice goes by sizes only; tensors that do not start at 16 bytes are copied a dword per element, whatever the
+    type, and the kernel for them has to be one that fits LDS."""
+    ps = [((g, s, 4, -1), dt, B, L, H, fixed) for g in range(1, 25) for s in (1, 2) for dt in (F32, BF16) for B in (1, 16)
+          for L in (100, 2000) for H in (1024, 8192, 32768) for fixed in (0, 3)]
+    taken = 0
+    for p, (kind, c, lps, w, *_) in zip(ps, choose(ps)):
+        if kind == WALK:
+            taken += 1
+            assert c * p[0][0] * 64 * w * 4 + (w * 16 * p[0][1] << lps) * 4 <= 160 * 1024 - 256, p
+    assert taken > 100
+
+
 def test_the_sizes_that_are_tested_take_every_shape(choose):
     for cell, cs in ((GRU, ((8, 4), (12, 8))), (LSTM, ((8, 4), (16, 4)))):
         seen = set()
