@@ -1132,10 +1132,13 @@ template <int N> __device__ __forceinline__ f4v *ring_slot(float (*ring)[N], int
 // last step before, delta of every iteration, and nothing else (y and h come from it and the rows): a stretch starts
 // kWarm steps early from delta = 0, and by its own first step a recurrence that contracts has forgotten that.  Whether it
 // has is looked at: every stretch leaves the updates it reached at the step before its own first one, and at its last;
-// where the two that belong together differ by more than kWarmTol (eight units of the last place of a state of 1), in
-// any iteration and row, the sequence is solved again from its first step, as a whole.  Where they agree the
-// states are those of one chain but for a rounding at a few steps.  The benchmark's W (0.8 N(0, 1/64)) agrees to 2e-7
+// where the two that belong together differ by more than kWarmTol (eight units of the last place) times the largest of the 64
+// states at that step, at most 1, or by more than the tolerance of the solve, in any iteration and row, the sequence is solved
+// again from its first step, as a whole.  Where they agree the states are those of one chain but for a rounding at a few
+// steps.  The benchmark's W (0.8 N(0, 1/64)) agrees to 2e-7
 // after 24-26 steps with u ~ N(0, 1), 52-64 with u a tenth to a third of that; 1.2 N(0, 1/64) after 50-61.
+// Small states seldom agree even where all is forgotten: tanh and with it an update from the second iteration on
+// has an absolute error of 6e-8.  Nor do any to a tolerance below kWarmTol: such solves have no stretches.
 constexpr int kWarm = 64;
 constexpr int kWarmLeast = 32;        // steps of a stretch at least: shorter ones would be half warm-up and more
 constexpr float kWarmTol = 4.8e-7f;
@@ -1350,26 +1353,35 @@ __global__ __launch_bounds__(320) void dense_wavefront_kernel(const DenseArgs a,
         __syncthreads();
         const unsigned int *top = c.top + (size_t)b * c.n * kWaveIters;
         for (int i = threadIdx.x; i < c.n * kWaveIters; i += (int)blockDim.x) atomicMax(&s.m[i & (kWaveIters - 1)], top[i]);
-        // quads of updates: the ones at the last step of stretch j, and the ones that j + 1 started from
+        // A wave looks at the updates between two stretches, a quad a lane: the ones at the last step of stretch e, the ones that e + 1
+        // started from, and the states that both belong to.
         constexpr int kQuads = kWaveIters * DH / 4, kBatch = 4;
+        static_assert(kQuads == 64, "a quad per lane");
+        const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
         const f4v *edge = reinterpret_cast<const f4v *>(c.edge) + (size_t)b * c.n * 2 * kQuads;
-        const int n_quads = (c.n - 1) * kQuads;
+        const f4v *state = reinterpret_cast<const f4v *>(a.h + seq);
         int apart = 0;
-        for (int i0 = threadIdx.x; i0 < n_quads; i0 += kBatch * (int)blockDim.x) {
-            f4v there[kBatch], here[kBatch];
+        for (int e0 = w; e0 < c.n - 1; e0 += kBatch * 5) {
+            f4v there[kBatch], here[kBatch], hq[kBatch];
 #pragma unroll
             for (int j = 0; j < kBatch; ++j) {
-                const int i = min(i0 + j * (int)blockDim.x, n_quads - 1);
-                const f4v *at = edge + (size_t)(i / kQuads) * 2 * kQuads + i % kQuads;
+                const int e = min(e0 + 5 * j, c.n - 2);
+                const f4v *at = edge + (size_t)e * 2 * kQuads + lane;
                 there[j] = at[kQuads];
                 here[j] = at[2 * kQuads];
+                hq[j] = state[(size_t)((e + 1) * c.len - 1) * (DH / 4) + (lane & 15)];
             }
 #pragma unroll
             for (int j = 0; j < kBatch; ++j) {
-                if (min(i0 + j * (int)blockDim.x, n_quads - 1) % kQuads >= K * DH / 4) continue;
+                unsigned int top = 0u;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) top = max(top, __float_as_uint(hq[j][v]) & 0x7fffffffu);
+                float bound = kWarmTol * fminf(__uint_as_float(wave_max_u32(top)), 1.0f);
+                if (a.tol >= 0.0f) bound = fminf(bound, a.tol);
+                if (lane >= K * (DH / 4)) continue;
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
-                    if (!(fabsf(there[j][v] - here[j][v]) <= kWarmTol)) apart = 1;
+                    if (!(fabsf(there[j][v] - here[j][v]) <= bound)) apart = 1;
             }
         }
         // the same for the whole workgroup, which the compiler is told: buffers chosen by it are scalars
@@ -1877,6 +1889,7 @@ int dense_forward(int dtype, const float *W, const void *u, const void *h0, int 
     if (g_dense_products == 0 && max_iter > 0 && max_iter <= DH * DH && wavefront_pays(B, L, false)) {
         unsigned int *gm = reinterpret_cast<unsigned int *>(ws + lo.off_A);
         DenseStretch c = dense_stretches(B, L);
+        if (tol >= 0.0f && tol < kWarmTol) { c.n = 1; c.len = L; }
         DenseArgs guess = a;
         if (c.n > 1) {
             // behind the maxima: two more sets of rows and what the stretches leave, 2.06 KB for each of at least 32 steps;

@@ -102,3 +102,38 @@ def test_stretches_in_a_graph():
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(h, eh) and torch.equal(it, ei)
+
+
+# W that forgets slowly or not at all (orthogonal times rho) and the benchmark's, states from 1 down to where tanh's own error of
+# 6e-8 is all there is
+@pytest.mark.parametrize("rho", [0.0, 0.8, 0.9, 0.95, 1.0])
+@pytest.mark.parametrize("scale", [1.0, 0.1, 1e-2, 1e-3, 1e-5, 1e-6])
+def test_small_states_are_those_of_one_chain(rho, scale):
+    """Where stretches are taken, what enters one is wrong by at most eight units of the last place of the states there, whatever
+    their size, and W does not make it larger for long (orthogonal ones times rho at most 1 never do): twice that for
+    what several stretches add up.  One rounding of tanh that turns over costs a quantum of 6e-8; states that are not
+    large against that agree bit for bit or are solved as a whole."""
+    import paper_2510_21450_amd as P
+    for B, L in ((1, 512), (6, 523), (16, 1000)):
+        W, u, _, _ = problem(B, L, 0.8, scale, 3 * L, h0=False)
+        if rho:
+            W = (torch.linalg.qr(W.double().cpu())[0] * rho).float().contiguous().cuda()
+        for tol, n in ((-1.0, 1), (-1.0, 4), (1e-3, 32)):
+            h, it, _ = P.forward("tanh_dense", W, u, None, tol=tol, max_iter=n)
+            H_, it_, _ = P.forward("tanh_dense", W, whole(u, B), None, tol=tol, max_iter=n)
+            assert it.tolist() == it_.tolist()
+            top = float(H_[:B].abs().max())
+            err = float((h - H_[:B]).abs().max())
+            assert err <= 2 * 4.8e-7 * top, (B, L, tol, n, err, top)
+
+
+def test_tight_tolerances_are_met_where_stretches_meet():
+    """To a tolerance below what two histories of one step agree to, the bits are those of one chain."""
+    import paper_2510_21450_amd as P
+    for B, L in ((1, 512), (6, 523)):
+        for gain in (0.5, 0.8, 0.95):
+            W, u, h0, _ = problem(B, L, gain, 1.0, 4 * L)
+            for tol in (0.0, 1e-8, 1e-7):
+                h, it, _ = P.forward("tanh_dense", W, u, h0, tol=tol, max_iter=8)
+                H_, it_, _ = P.forward("tanh_dense", W, whole(u, B), whole(h0, B), tol=tol, max_iter=8)
+                assert it.tolist() == it_.tolist() and torch.equal(h, H_[:B])
