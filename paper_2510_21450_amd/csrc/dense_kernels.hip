@@ -1133,15 +1133,17 @@ template <int N> __device__ __forceinline__ f4v *ring_slot(float (*ring)[N], int
 // kWarm steps early from delta = 0, and by its own first step a recurrence that contracts has forgotten that.  Whether it
 // has is looked at: every stretch leaves the updates it reached at the step before its own first one, and at its last;
 // where the two that belong together differ by more than kWarmTol (eight units of the last place) times the largest of the 64
-// states at that step, at most 1, or by more than the tolerance of the solve, in any iteration and row, the sequence is solved
-// again from its first step, as a whole.  Where they agree the states are those of one chain but for a rounding at a few
-// steps.  The benchmark's W (0.8 N(0, 1/64)) agrees to 2e-7
+// states at that step, at most 1, or by more than the tolerance of the solve, in any iteration and row, the stretch and all
+// behind it are solved again as one chain, from the updates that the stretch before it ended with: kWarm steps and a launch
+// more than one chain from the first step on.  Where they agree the states are those of one chain but for a rounding at a
+// few steps.  The benchmark's W (0.8 N(0, 1/64)) agrees to 2e-7
 // after 24-26 steps with u ~ N(0, 1), 52-64 with u a tenth to a third of that; 1.2 N(0, 1/64) after 50-61.
 // Small states seldom agree even where all is forgotten: tanh and with it an update from the second iteration on
 // has an absolute error of 6e-8.  Nor do any to a tolerance below kWarmTol: such solves have no stretches.
 constexpr int kWarm = 64;
 constexpr int kWarmLeast = 32;        // steps of a stretch at least: shorter ones would be half warm-up and more
 constexpr float kWarmTol = 4.8e-7f;
+constexpr int kStretches = 256;       // of all sequences at most: one for each compute unit
 
 struct DenseStretch {
     int n, len;                       // stretches of a sequence (1: none, the whole sequence at once), steps of each but the last
@@ -1166,12 +1168,14 @@ struct WaveLds {
 };
 
 // A block of K iterations over the rows q of sequence b, by a whole workgroup; wr: W as wave_products wants it.
-// s.m[i]: max |delta| of iteration i.  EDGE: the updates that DenseStretch::edge holds go to `edge`.
+// s.m[i]: max |delta| of iteration i.  EDGE: the updates that DenseStretch::edge holds go to `edge`; otherwise they may be
+// what enters at the first row, the updates of the step before it (NULL: zero).
 //
 // Record of step t: for iteration i (0 ..) at timestep l = first + t - i three rows from float kWavePer i on: h_l and y_{l-1} of the
 // iterate before (left there by iteration i - 1 in step t - 1, by the mover for i = 0), and kTanhScale * u_l.  The
 // sixteen floats behind them put the four iterations of a wave's access into four different quarters of the banks.
-// Steps before an iteration's first timestep find zeros there, which give delta = 0.
+// Steps before an iteration's first timestep find zeros there, which give delta = 0; the last of them, at the timestep before
+// the first one, is where what enters takes its place.
 template <bool EDGE>
 __device__ __forceinline__ void wavefront_block(const DenseArgs &a, int b, int K, const WaveRows &q, const float (&wr)[16], WaveLds &s,
                                                 float *edge)
@@ -1181,7 +1185,8 @@ __device__ __forceinline__ void wavefront_block(const DenseArgs &a, int b, int K
     const int xw = 64 * (w & 3) + 16 * (r >> 2) + 4 * it + (r & 3);  // where this lane's delta goes
     const int L = q.end - q.first, lead = q.start - q.first;         // steps, of which the first do not count
     const int n_groups = (L + K - 1 + kWaveGroup - 1) / kWaveGroup;
-    if (threadIdx.x < DH * kWaveIters) s.x[0][threadIdx.x] = 0.0f;
+    const bool enters = !EDGE && edge;
+    if (w < 4) s.x[0][xw] = enters && it == 0 ? edge[row] : 0.0f;
     if (threadIdx.x < kWaveIters) s.m[threadIdx.x] = 0u;
     if (w == 4) {
         const unsigned int seq_bytes = (unsigned int)a.L * (DH * 4u);
@@ -1240,6 +1245,7 @@ __device__ __forceinline__ void wavefront_block(const DenseArgs &a, int b, int K
     } else {
         float mymax = 0.0f, h_in, y_in, us;
         float *my_edge = EDGE ? edge + it * DH + row : nullptr;
+        const float first_delta = enters ? edge[it * DH + row] : 0.0f;
         // what this lane's iteration leaves for the next one in record `rec`, and what it finds there itself
         auto hand_on = [&](float *record, float hn, float yn) {
             float *rec = record + kWavePer * it + row;
@@ -1251,7 +1257,8 @@ __device__ __forceinline__ void wavefront_block(const DenseArgs &a, int b, int K
             y_in = rec[DH];
             us = rec[2 * DH];
         };
-        // kind 0: all timesteps count; 1: some do not, or it is one whose update is handed out; 2: none counts
+        // kind 0: all timesteps count; 1: some do not, or it is one whose update is handed out; 2: none counts; 3: those before the
+        // first one do not, and what enters is taken over
         auto step = [&](auto kind, int kB, float *next_rec, int t) {
             constexpr int kKind = decltype(kind)::value;
             const f4v xv = *reinterpret_cast<const f4v *>(&s.x[kB][4 * lane]);
@@ -1260,11 +1267,14 @@ __device__ __forceinline__ void wavefront_block(const DenseArgs &a, int b, int K
             __builtin_amdgcn_sched_barrier(0);
             const f4v p = wave_products(xv, wr);
             const float z = swap16_add(swap32_add(p[0], p[2]), swap32_add(p[1], p[3]));
-            const float delta = fmaf(d, z, res);
+            float delta = fmaf(d, z, res);
+            if constexpr (kKind == 3) {
+                if (t - it == -1) delta = first_delta;
+            }
             s.x[kB ^ 1][xw] = delta;
             __builtin_amdgcn_sched_barrier(0);
             hand_on(next_rec, fmaf(d, z, F), y_in + z);
-            if constexpr (kKind == 1) {                    // past the end too; a NaN has reached the last one
+            if constexpr (kKind == 1 || kKind == 3) {      // past the end too; a NaN has reached the last one
                 const int l = t - it;
                 if (l >= lead && l < L) mymax = nanmax(mymax, fabsf(delta));
                 if constexpr (EDGE) {
@@ -1286,6 +1296,9 @@ __device__ __forceinline__ void wavefront_block(const DenseArgs &a, int b, int K
 #pragma unroll
                 for (int i = 0; i < kWaveGroup; ++i) step(kind, i & 1, i + 1 < kWaveGroup ? rec + kWaveRec * (i + 1) : rec_next, t0 + i);
             };
+            if constexpr (!EDGE) {
+                if (g == 0 && enters) { group(std::integral_constant<int, 3>{}); continue; }
+            }
             if (t0 + kWaveGroup < L && (lead == 0 || t0 >= lead + kWaveIters - 1)) {
                 group(std::integral_constant<int, 0>{});
             } else {
@@ -1330,14 +1343,14 @@ __global__ __launch_bounds__(320) void dense_stretch_kernel(const DenseArgs a, c
 // One workgroup per sequence.  A sequence whose own update meets the tolerance at the end of a block is done:
 // the blocks after it are run by the sequences that are not.  gm[k-1]: max |delta| of iteration k over the
 // sequences that ran it.  The last workgroup to finish reports the first iteration whose maximum met the tolerance.
-// After dense_stretch_kernel it goes on behind the first block, or starts from the beginning where that has to be.
+// After dense_stretch_kernel it goes on behind the first block, or solves that again from the first border on where the updates
+// differ.
 __global__ __launch_bounds__(320) void dense_wavefront_kernel(const DenseArgs a, unsigned int *gm, const DenseStretch c)
 {
     __shared__ WaveLds s;
+    __shared__ int s_held;
     const int b = blockIdx.x;
     const size_t seq = (size_t)b * a.L * DH;
-    float *y = a.d;
-    const float *h_first = a.h;
     auto ended = [&](int K) {                              // the maxima in s.m are of a whole block
         bool met = false;
         for (int i = 0; i < K; ++i) {
@@ -1346,13 +1359,18 @@ __global__ __launch_bounds__(320) void dense_wavefront_kernel(const DenseArgs a,
         }
         return met;
     };
-    int k0 = 0;
+    constexpr int kTops = (kStretches * kWaveIters + 319) / 320;
+    unsigned int top[kTops];                               // of stretch (threadIdx.x + 320 j) / kWaveIters
+    int held = 0;                                          // stretches that are as they have to be
     if (c.n > 1) {
-        const int K = min(kWaveIters, a.max_iter);
+        if (threadIdx.x == 0) s_held = c.n;
         if (threadIdx.x < kWaveIters) s.m[threadIdx.x] = 0u;
-        __syncthreads();
-        const unsigned int *top = c.top + (size_t)b * c.n * kWaveIters;
-        for (int i = threadIdx.x; i < c.n * kWaveIters; i += (int)blockDim.x) atomicMax(&s.m[i & (kWaveIters - 1)], top[i]);
+#pragma unroll
+        for (int j = 0; j < kTops; ++j) {
+            const int i = (int)threadIdx.x + 320 * j;
+            top[j] = i < c.n * kWaveIters ? c.top[(size_t)b * c.n * kWaveIters + i] : 0u;
+        }
+        lds_barrier();                                     // the loads stay on their way
         // A wave looks at the updates between two stretches, a quad a lane: the ones at the last step of stretch e, the ones that e + 1
         // started from, and the states that both belong to.
         constexpr int kQuads = kWaveIters * DH / 4, kBatch = 4;
@@ -1360,7 +1378,7 @@ __global__ __launch_bounds__(320) void dense_wavefront_kernel(const DenseArgs a,
         const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
         const f4v *edge = reinterpret_cast<const f4v *>(c.edge) + (size_t)b * c.n * 2 * kQuads;
         const f4v *state = reinterpret_cast<const f4v *>(a.h + seq);
-        int apart = 0;
+        const int K = min(kWaveIters, a.max_iter);
         for (int e0 = w; e0 < c.n - 1; e0 += kBatch * 5) {
             f4v there[kBatch], here[kBatch], hq[kBatch];
 #pragma unroll
@@ -1373,41 +1391,45 @@ __global__ __launch_bounds__(320) void dense_wavefront_kernel(const DenseArgs a,
             }
 #pragma unroll
             for (int j = 0; j < kBatch; ++j) {
-                unsigned int top = 0u;
+                unsigned int large = 0u;
 #pragma unroll
-                for (int v = 0; v < 4; ++v) top = max(top, __float_as_uint(hq[j][v]) & 0x7fffffffu);
-                float bound = kWarmTol * fminf(__uint_as_float(wave_max_u32(top)), 1.0f);
+                for (int v = 0; v < 4; ++v) large = max(large, __float_as_uint(hq[j][v]) & 0x7fffffffu);
+                float bound = kWarmTol * fminf(__uint_as_float(wave_max_u32(large)), 1.0f);
                 if (a.tol >= 0.0f) bound = fminf(bound, a.tol);
                 if (lane >= K * (DH / 4)) continue;
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
-                    if (!(fabsf(there[j][v] - here[j][v]) <= bound)) apart = 1;
+                    if (!(fabsf(there[j][v] - here[j][v]) <= bound)) atomicMin(&s_held, min(e0 + 5 * j, c.n - 2) + 1);
             }
         }
-        // the same for the whole workgroup, which the compiler is told: buffers chosen by it are scalars
-        if (__builtin_amdgcn_readfirstlane(__syncthreads_or(apart))) {
-            h_first = c.h0it;
-        } else {
-            if ((int)threadIdx.x < K) atomicMax(&gm[threadIdx.x], s.m[threadIdx.x]);
-            y = c.y;
-            k0 = __builtin_amdgcn_readfirstlane(ended(K) ? a.max_iter : K);
-        }
         __syncthreads();
+        held = __builtin_amdgcn_readfirstlane(s_held);     // the same for the whole workgroup: buffers chosen by it are scalars
     }
-    if (k0 < a.max_iter) {
-        float wr[16];
-        load_w_wave(a.W, wr);
-        for (; k0 < a.max_iter; k0 += kWaveIters) {
-            const int K = min(kWaveIters, a.max_iter - k0);
-            const WaveRows q = {(k0 == 0 ? h_first : a.h) + seq, y + seq, a.h + seq, y + seq, 0, 0, a.L};
-            wavefront_block<false>(a, b, K, q, wr, s, nullptr);
+    float *y = c.n > 1 ? c.y : a.d;
+    for (int k0 = 0; k0 < a.max_iter; k0 += kWaveIters) {
+        const int K = min(kWaveIters, a.max_iter - k0);
+        if (k0 > 0 || held < c.n) {
+            const bool cut = k0 == 0 && c.n > 1;           // the rest of the first block
+            const int first = cut ? held * c.len : 0;
+            const WaveRows q = {(cut ? c.h0it : a.h) + seq, (cut ? a.d : y) + seq, a.h + seq, y + seq, first, first, a.L};
+            float wr[16];
+            load_w_wave(a.W, wr);
+            wavefront_block<false>(a, b, K, q, wr, s, cut ? c.edge + ((size_t)(b * c.n + held - 1) * 2 + 1) * kWaveIters * DH : nullptr);
             __threadfence();                               // the next block reads the rows that this one wrote
             __syncthreads();
-            const bool met = ended(K);
-            if ((int)threadIdx.x < K) atomicMax(&gm[k0 + threadIdx.x], s.m[threadIdx.x]);
-            __syncthreads();
-            if (met) break;
         }
+        if (k0 == 0 && held > 0) {
+#pragma unroll
+            for (int j = 0; j < kTops; ++j) {
+                const int i = (int)threadIdx.x + 320 * j;
+                if (i < held * kWaveIters) atomicMax(&s.m[i & (kWaveIters - 1)], top[j]);
+            }
+            __syncthreads();
+        }
+        const bool met = ended(K);
+        if ((int)threadIdx.x < K) atomicMax(&gm[k0 + threadIdx.x], s.m[threadIdx.x]);
+        __syncthreads();
+        if (met) break;
     }
     if (threadIdx.x == 0) {
         __threadfence();
@@ -1436,7 +1458,7 @@ __global__ __launch_bounds__(320) void dense_wavefront_kernel(const DenseArgs a,
 // STRETCH: one workgroup per stretch of a sequence (DenseStretch: here from the last row down; what enters is one mu), which
 // starts kWarm rows early from mu = 0 and leaves mu at the row behind its own last one in `edge`.  Otherwise one workgroup
 // per sequence; after the stretches it does nothing where these agree, relative to the largest of the 64 values, and runs
-// the whole sequence where they do not.
+// on from the last border where they do not.
 template <bool STRETCH>
 __global__ __launch_bounds__(320) void dense_adjoint_kernel(const DenseArgs a, float *dh0, const DenseStretch c)
 {
@@ -1446,20 +1468,28 @@ __global__ __launch_bounds__(320) void dense_adjoint_kernel(const DenseArgs a, f
     const int q = lane >> 4, row = 16 * (w & 3) + (lane & 15);
     const int b = STRETCH ? (int)blockIdx.x / c.n : (int)blockIdx.x, j = STRETCH ? (int)blockIdx.x - b * c.n : 0;
     const unsigned int seq_bytes = (unsigned int)a.L * (DH * 4u);
-    // rows start .. end - 1 are this workgroup's, the ones from `last` down are run
-    const int start = STRETCH ? j * c.len : 0, end = STRETCH ? min(start + c.len, a.L) : a.L;
-    const int last = STRETCH ? min(end + kWarm, a.L) - 1 : a.L - 1, L = last + 1 - start, lead = last + 1 - end;
+    // rows start .. end - 1 are this workgroup's, the ones from `last` down are run, with `x` entering at that one
+    const int start = STRETCH ? j * c.len : 0;
+    int end = STRETCH ? min(start + c.len, a.L) : a.L;
+    float x = 0.0f;
     if constexpr (!STRETCH) {
         if (c.n > 1) {
-            int apart = 0;
+            __shared__ int s_apart;
+            if (threadIdx.x == 0) s_apart = 0;
+            __syncthreads();
             for (int e = 1 + w; e < c.n; e += 5) {         // a wave looks at the 64 values between two stretches
                 const float there = a.du[((size_t)b * a.L + (size_t)e * c.len) * DH + lane], here = c.edge[((size_t)b * c.n + e - 1) * DH + lane];
                 const float top = __uint_as_float(wave_max_u32(__float_as_uint(there) & 0x7fffffffu));
-                if (!(fabsf(there - here) <= kWarmTol * top)) apart = 1;
+                if (!(fabsf(there - here) <= kWarmTol * top)) atomicMax(&s_apart, e);
             }
-            if (!__syncthreads_or(apart)) return;
+            __syncthreads();
+            const int e = __builtin_amdgcn_readfirstlane(s_apart);
+            if (e == 0) return;
+            end = e * c.len;
+            x = a.du[((size_t)b * a.L + end) * DH + lane];
         }
     }
+    const int last = STRETCH ? min(end + kWarm, a.L) - 1 : end - 1, L = last + 1 - start, lead = last + 1 - end;
     auto rev = [last](int t) { return last - t; };
     float wr[16];                                          // W^T[row][16 q ..]
 #pragma unroll
@@ -1528,7 +1558,7 @@ __global__ __launch_bounds__(320) void dense_adjoint_kernel(const DenseArgs a, f
         return swap16_add(t, t);
     };
     lds_barrier();
-    float d = s_rec[0][row], dg = s_rec[0][DH + row], x = 0.0f;
+    float d = s_rec[0][row], dg = s_rec[0][DH + row];
     for (int g = 0; g < n_groups; ++g) {
         const int s0 = (g * kWaveGroup) & (kRing - 1), s1 = (s0 + kWaveGroup) & (kRing - 1);
         float *mus = s_mu[s0];
@@ -1562,7 +1592,7 @@ DenseStretch dense_stretches(int B, int L)
     DenseStretch c;
     memset(&c, 0, sizeof(c));
     c.n = 1; c.len = L;
-    const int most = 256 / B;
+    const int most = kStretches / B;
     if (most < 2) return c;
     const int len = (L + most - 1) / most > kWarmLeast ? (L + most - 1) / most : kWarmLeast;
     if (len >= L || 4 * (len + kWarm + kWaveIters) > 3 * L) return c;

@@ -137,3 +137,35 @@ def test_tight_tolerances_are_met_where_stretches_meet():
                 h, it, _ = P.forward("tanh_dense", W, u, h0, tol=tol, max_iter=8)
                 H_, it_, _ = P.forward("tanh_dense", W, whole(u, B), whole(h0, B), tol=tol, max_iter=8)
                 assert it.tolist() == it_.tolist() and torch.equal(h, H_[:B])
+
+
+@pytest.mark.parametrize("B,L", [(1, 301), (3, 523), (60, 701)])
+def test_stretches_are_repaired_from_where_they_differ(B, L):
+    """Large u, with which 0.95 x orthogonal W forgets, and small u, with which it does not, in this order and in the other: stretches
+    at the front hold and the ones behind them are run again, or the first ones differ.  States: what enters a stretch, twice 4.8e-7 as
+    above, and where u is large the roundings of tanh, 2^-24 a step in each of the two chains, of which 0.95 adds up 1 / (1 - 0.95)."""
+    import paper_2510_21450_amd as P
+    W, u, h0, g = problem(B, L, 0.8, 1.0, 6 * L)
+    W = (torch.linalg.qr(W.double().cpu())[0] * 0.95).float().contiguous().cuda()
+    for order in (0, 1):
+        v = u.clone()
+        (v[:, :L // 2] if order else v[:, L // 2:]).mul_(0.02)
+        for tol, n in ((1e-3, 32), (-1.0, 1), (-1.0, 3), (-1.0, 6)):
+            h, it, trace = P.forward("tanh_dense", W, v, h0, tol=tol, max_iter=n, trace=True)
+            H_, it_, trace_ = P.forward("tanh_dense", W, whole(v, B), whole(h0, B), tol=tol, max_iter=n, trace=True)
+            assert it.tolist() == it_.tolist()
+            assert float((h - H_[:B]).abs().max()) <= 2 * 4.8e-7 + 2 * 2.0 ** -24 / (1 - 0.95), (order, tol, n)
+            k = it.tolist()[0]
+            assert np.allclose(trace[:k].cpu(), trace_[:k].cpu(), rtol=1e-4, atol=1e-6)
+    # a loss that looks at part of the steps: nothing to start a stretch from where it does not
+    h = P.forward("tanh_dense", W, u, h0, tol=1e-3, max_iter=32)[0]
+    for seen in (slice(L - 1, L), slice(2 * L // 3, L), slice(0, L // 3)):
+        part = torch.zeros_like(g)
+        part[:, seen] = g[:, seen]
+        du, dW, dh0 = P.backward("tanh_dense", W, u, h0, h, part, want_dh0=True)
+        du_, dW_, dh0_ = P.backward("tanh_dense", W, whole(u, B), whole(h0, B), whole(h, B), whole(part, B), want_dh0=True)
+        if seen.start == L - 1:
+            assert torch.equal(du, du_[:B]) and torch.equal(dh0, dh0_[:B])
+        # relative to the largest of 64 values where it enters, and |W^T D| <= 0.95
+        assert float((du - du_[:B]).abs().max()) <= 1e-6 * float(du_.abs().max())
+        assert float((dh0 - dh0_[:B]).abs().max()) <= 1e-6 * float(du_.abs().max())
