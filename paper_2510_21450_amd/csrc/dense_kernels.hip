@@ -1,7 +1,7 @@
 // Dense-Jacobian path: h' = tanh(W h + u), J_l = diag(1 - F_l^2) W (the generic
 // dense case of Sec. 2.1), H = 64, fp32.
 //
-// The linear solve of a Newton iteration is block bi-diagonal.  Two ways through it (wavefront_pays chooses):
+// The linear solve of a Newton iteration is block bi-diagonal.  Two ways through it (wavefront_plan chooses):
 // forward substitution, all iterations of a block at once as a wavefront (dense_wavefront_kernel,
 // dense_adjoint_kernel: latency-bound, one workgroup per sequence, whole solves in two launches; sequences fewer than the
 // compute units are cut into stretches that run side by side, DenseStretch), and the chunked scan:
@@ -999,7 +999,7 @@ int newton_grid(int prod)
 // takes four cycles to issue, 1.8 ns), so the four waves touch no memory and compute no addresses: a fifth brings the
 // rows of u, h and y in, sixteen bytes per lane, and takes the results out, by way of a ring of records in LDS, one
 // per step, in which each iteration finds its inputs and leaves its results where the next one looks for them.
-// Measured: see the rule at wavefront_pays().
+// Measured: see the rule at wavefront_plan().
 constexpr int kWaveIters = 4;
 constexpr int kWaveGroup = 8;         // steps per group: the mover wave brings in and takes out the rows of a group at a time
 constexpr int kRing = 16;             // steps a ring in LDS holds: the group in use and the one that is ready
@@ -1585,9 +1585,25 @@ __global__ __launch_bounds__(320) void dense_adjoint_kernel(const DenseArgs a, f
     }
 }
 
-// Stretches of a substitution: one for each compute unit, and none where that saves less than a quarter of the steps.  Two
-// workgroups on a unit, 512 stretches, take 590 ns a step instead of 225 (64 sequences of 1024 steps: 108 us with 256, 136 with 512).
-DenseStretch dense_stretches(int B, int L)
+// Substitution or chunk products, and in how many stretches?  Nanoseconds, measured on config 4's shape and on 1 to 16
+// sequences of 500 to 2000 steps: a forward substitution step takes 225, an adjoint one 160, whatever the number of sequences
+// while each has a compute unit; an iteration with chunk products takes 3.94 per row but at least 67 us (the chain of one
+// chunk), 17 per step for the carry and 25-30 us for the sweeps, and four iterations are what a solve needs.
+//
+// Stretches: one for each compute unit.  Two workgroups on a unit, 512 stretches, take 590 ns a step instead of 225 (64
+// sequences of 1024 steps: 108 us with 256, 136 with 512).  Whether a recurrence forgets within kWarm steps is known only
+// afterwards, so they are a bet: won, the chain is that of one stretch; lost, all of it and the warm-up.  It is taken where it
+// loses at most half of what it gains.  us, without stretches / won / lost (W orthogonal, u a tenth):
+//
+//            forward              backward
+//   1 x 200   53 /  37 /  64       47 / 32 /  55     not taken
+//   1 x 300   74 /  37 /  85       62 / 33 /  71
+//   6 x 523  121 /  38 / 134       98 / 35 / 108
+//   16 x 600 142 /  46 / 163      115 / 44 / 129
+//   64 x 272  80 /  53 / 105       70 / 51 /  88     not taken
+//   64 x 1024 242 / 97 / 273      200 / 96 / 223
+//   16 x 1000 227 / 52 / 246      145 / 49 / 191     backward not taken: chunk products
+DenseStretch dense_stretches(int B, int L, double step, double products)
 {
     DenseStretch c;
     memset(&c, 0, sizeof(c));
@@ -1595,28 +1611,23 @@ DenseStretch dense_stretches(int B, int L)
     const int most = kStretches / B;
     if (most < 2) return c;
     const int len = (L + most - 1) / most > kWarmLeast ? (L + most - 1) / most : kWarmLeast;
-    if (len >= L || 4 * (len + kWarm + kWaveIters) > 3 * L) return c;
+    if (len >= L) return c;
+    const double chain = step * L, without = chain < products ? chain : products;
+    const double warm = step * (kWarm + kWaveIters) + 3e3;                 // and the second launch
+    if (chain + warm - without > 0.5 * (without - step * len - warm)) return c;
     c.n = (L + len - 1) / len; c.len = len;
     return c;
 }
 
-// Substitution or chunk products?  Nanoseconds, measured on config 4's shape and on 1 to 16 sequences of 500 to 2000
-// steps: a forward substitution step takes 225, an adjoint one 160, whatever the number of sequences while
-// each has a compute unit; an iteration with chunk products takes 3.94 per row but at least 67 us (the chain of one
-// chunk), 17 per step for the carry and 25-30 us for the sweeps, and four iterations are what a solve
-// needs.  Stretches run side by side, so their chain is what counts, and two launches (64 x 1024 forward: 1.26 ms with chunk
-// products, 244 us by substitution, 107 in stretches; backward 201 and 96; 16 x 1000 backward 145 with chunk products).  Where
-// they come to nothing, because the recurrence does not contract, the whole chain is to be gone through after all: it
-// may take twice as long as chunk products, not more.
-bool wavefront_pays(int B, int L, bool backward)
+// The stretches of a solve by substitution; n = 0 where chunk products are faster.
+DenseStretch wavefront_plan(int B, int L, bool backward)
 {
-    if (!g_dense_substitution) return false;
     const double rows = (double)B * L, step = backward ? 160.0 : 225.0;
     const double products = ((rows * 3.94 > 67e3 ? rows * 3.94 : 67e3) + 17.0 * L + 27e3) * (backward ? 1.0 : 4.0);
+    DenseStretch c = dense_stretches(B, L, step, products);
     const double chain = step * L * (double)((B + 511) / 512);              // two workgroups share a compute unit
-    const DenseStretch c = dense_stretches(B, L);
-    if (c.n > 1) return step * (c.len + kWarm + kWaveIters) + 10e3 < products && chain < 2.0 * products;
-    return chain < products;
+    if (!g_dense_substitution || (c.n == 1 && chain >= products)) c.n = 0;
+    return c;
 }
 
 // ------------------------------------------------------------ backward extras
@@ -1810,11 +1821,11 @@ int dense_backward(int dtype, const float *W, const void *u, const void *h0, con
     a.ctrl = reinterpret_cast<Ctrl *>(ws);
     a.g = static_cast<const float *>(g); a.du = static_cast<float *>(du);
     a.B = B; a.L = L; a.n_c = lo.n_c;
-    if (wavefront_pays(B, L, true)) {
+    DenseStretch c = wavefront_plan(B, L, true);
+    if (c.n > 0) {
         const size_t items = ((size_t)B * L + 15) / 16, most = (size_t)device_cu_count() * 8;
         a.W = W;
         hipLaunchKernelGGL(dense_residual_kernel, dim3((unsigned)(items < most ? items : most)), dim3(256), 0, st, a, 5);
-        DenseStretch c = dense_stretches(B, L);
         // what the stretches leave lies where the chunk products would: 256 bytes of each, and they take 16 KB per 16 steps
         c.edge = a.Ac;
         if (c.n > 1) hipLaunchKernelGGL(dense_adjoint_kernel<true>, dim3(B * c.n), dim3(320), 0, st, a, static_cast<float *>(dh0), c);
@@ -1916,9 +1927,9 @@ int dense_forward(int dtype, const float *W, const void *u, const void *h0, int 
         return hipGetLastError() == hipSuccess ? PARARNN_OK : PARARNN_HIP_ERROR;
     }
     // the maxima of the iterations lie where the chunk products would (at least 4096 words)
-    if (g_dense_products == 0 && max_iter > 0 && max_iter <= DH * DH && wavefront_pays(B, L, false)) {
+    DenseStretch c = wavefront_plan(B, L, false);
+    if (g_dense_products == 0 && max_iter > 0 && max_iter <= DH * DH && c.n > 0) {
         unsigned int *gm = reinterpret_cast<unsigned int *>(ws + lo.off_A);
-        DenseStretch c = dense_stretches(B, L);
         if (tol >= 0.0f && tol < kWarmTol) { c.n = 1; c.len = L; }
         DenseArgs guess = a;
         if (c.n > 1) {
