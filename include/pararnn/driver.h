@@ -137,9 +137,8 @@ inline TileCfg choose_tile(const CellInfo &ci, int dtype, bool backward, int H, 
 //   gates    channels or more, x 32 (16 x 300 x 2048 0.86); rows of other lengths 0.8-0.9 with the same.  ParaLSTM: x 96, or x 64
 //            staged (16 x 2048 x 2048 0.91).  fp32: x 96 instead of 32 x 128 (0.81-0.98), x 32 for many channels up to 2048
 //            steps (8 x 2048 x 1536 0.90)
-inline TileCfg backward_tile(const CellInfo &ci, int dtype, int B, int L, int H, const TileCfg &table)
+inline TileCfg backward_tile_by_size(const CellInfo &ci, int dtype, int B, int L, int H, const TileCfg &table)
 {
-    if (ci.S > 2 || H <= 32 || settings().tile[0] > 0) return table;
     const bool bf = dtype == PARARNN_BF16, whole = H % 64 == 0;
     const double channels = (double)B * H, n = channels * L;
     const TileCfg x32 = {1, 1, 4, 8}, x64 = {1, 1, 8, 8}, x96 = {1, 1, 12, 8}, x128 = {1, 1, 16, 8}, x128w = {1, 1, 8, 16}, x64n = {1, 1, 16, 4};
@@ -152,6 +151,19 @@ inline TileCfg backward_tile(const CellInfo &ci, int dtype, int B, int L, int H,
     if (!bf) return channels < 1024 ? table : channels >= 12288 && L <= 2048 ? x32 : x96;
     if (whole && n >= 1.8e7) return x128;
     return channels >= (whole ? 8192 : 32768) ? x32 : x96;
+}
+// ... as far as a workgroup's sums for the parameter rows leave room for it: shapes beyond 64 KB of LDS are not built
+// (backward_fits_lds in launch_impl.h).
+inline bool backward_tile_fits(const CellInfo &ci, const TileCfg &t)
+{
+    const size_t rows = (size_t)(ci.S * ci.S + ci.S > ci.PR ? ci.S * ci.S + ci.S : ci.PR);
+    return (t.w * rows + ci.S) * (size_t)(64 / t.ll) * t.vec * sizeof(float) + 16 <= 65536;
+}
+inline TileCfg backward_tile(const CellInfo &ci, int dtype, int B, int L, int H, const TileCfg &table)
+{
+    if (ci.S > 2 || H <= 32 || settings().tile[0] > 0) return table;
+    const TileCfg t = backward_tile_by_size(ci, dtype, B, L, H, table);
+    return backward_tile_fits(ci, t) ? t : table;
 }
 // ... and whether its rows are staged
 inline bool backward_staged(const CellInfo &ci, int B, int L, int H)

@@ -29,7 +29,7 @@ template <class Cell, int VEC, int LL, int W> constexpr bool forward_fits_lds()
     return (size_t)(W * (SS + S) + 4 * S) * (kWave / LL) * VEC * sizeof(float) + 4 * W + 64 <= 65536;
 }
 
-// static LDS of the backward kernel must stay within 64 KiB
+// static LDS of the backward kernel must stay within 64 KiB (backward_tile_fits in driver.h is the same on the host)
 template <class Cell, int VEC, int LL, int W> constexpr bool backward_fits_lds()
 {
     constexpr int S = Cell::S, SS = S * S, PRX = Cell::PR > 0 ? Cell::PR : 1;

@@ -1,0 +1,50 @@
+"""The tile of a backward pass with carry records (include/pararnn/driver.h), on the host: a small program compiled against the
+driver's own header prints what is taken."""
+import os
+import re
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PKG = os.path.join(ROOT, "paper_2510_21450_amd")
+F32, BF16 = 0, 1
+
+
+@pytest.fixture(scope="module")
+def tiles(tmp_path_factory):
+    if not os.path.exists(os.path.join(PKG, "libpararnn.so")):
+        from paper_2510_21450_amd import build
+        build.build()
+    exe = tmp_path_factory.mktemp("probe") / "tile_probe"
+    cmd = ["/opt/rocm/bin/hipcc", "--offload-arch=gfx950", "-O1", "-std=c++17", "-Xclang", "-target-feature", "-Xclang",
+           "-packed-fp32-ops", f"-I{os.path.join(ROOT, 'include')}", os.path.join(ROOT, "tests", "host_probe", "tile_probe.hip"),
+           f"-L{PKG}", "-lpararnn", f"-Wl,-rpath,{PKG}", "-o", str(exe)]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+
+    def run(problems):
+        """problems: (G, S, PR, kind, dtype, B, L, H); per problem the table's shape, the one taken, staged rows."""
+        text = "\n".join(" ".join(str(int(x)) for x in p) for p in problems)
+        out = subprocess.run([str(exe)], input=text, capture_output=True, text=True, check=True).stdout
+        rows = [[int(x) for x in line.split()] for line in out.splitlines()]
+        assert len(rows) == len(problems)
+        return [(tuple(r[:4]), tuple(r[4:8]), bool(r[8])) for r in rows]
+    return run
+
+
+def test_a_shape_that_is_taken_is_built(tiles):
+    """However many parameter rows a cell has: of the list that is compiled, and within 64 KB of LDS wherever the table's shape is."""
+    text = open(os.path.join(ROOT, "include", "pararnn", "launch.h")).read()
+    built = {tuple(int(x) for x in m) for m in re.findall(r"X\((\d+), (\d+), (\d+), (\d+)\)", text[text.index("define PARARNN_SHAPES"):])}
+    fits = lambda S, P, t: (t[3] * max(S * S + S, P) + S) * (64 // t[1]) * t[0] * 4 + 16 <= 65536
+    ps = [(G, S, P, -1, dt, B, L, H) for G in (1, 2, 3, 4) for S in (1, 2) for P in range(1, 65) for dt in (F32, BF16) for B in (1, 8)
+          for L in (700, 4096) for H in (64, 1001, 1024, 2048, 6144)]
+    other = 0
+    for p, (table, taken, _) in zip(ps, tiles(ps)):
+        S, P = p[1], p[2]
+        assert taken in built, (p, taken)
+        if fits(S, P, table):
+            assert fits(S, P, taken), (p, table, taken)
+        other += taken != table
+    assert other > 1000
