@@ -505,9 +505,10 @@ Layout scan_layout(int kind, int reverse, int B, int L, int H, int al)
 {
     const int S = kind + 1;
     const CellInfo ci = {S, S, 0, -1};
-    if (S <= 2) return make_layout(ci, PARARNN_F32, B, L, H, reverse != 0, al);
-    // 3x3 and 4x4 blocks keep 12 / 20 floats per step in registers: four steps per thread
-    const TileCfg cfg = H <= 8 ? TileCfg{1, 8, 4, 2} : TileCfg{1, 1, 4, 8};
+    // 3x3 and 4x4 blocks keep 12 / 20 floats per step in registers: four steps per thread.  Smaller ones take the table's shape: the
+    // backward passes' rule by sizes (backward_tile) is of cells that evaluate gates; the reverse scan of 2x2 blocks takes
+    // 58 us instead of 50 with its shape (4 x 1000 x 2048).
+    const TileCfg cfg = S <= 2 ? choose_tile(ci, PARARNN_F32, reverse != 0, H, al) : H <= 8 ? TileCfg{1, 8, 4, 2} : TileCfg{1, 1, 4, 8};
     return make_layout(ci, PARARNN_F32, B, L, H, reverse != 0, al, false, 1, &cfg);
 }
 

@@ -96,3 +96,12 @@ def test_the_two_parts_make_up_a_workspace(cell, dtype, B, L, H, back, n):
     # the dense cell has none, and memory for the rest needs a promise for the front
     assert lib.pararnn_workspace_parts(2, 0, 4, 100, 64, 0, 0, ctypes.byref(rest)) == 0
     assert lib.pararnn_workspace_rest(ctypes.c_void_p(4096), ctypes.c_void_p(8192), ctypes.c_size_t(256)) == 2
+
+
+@pytest.mark.parametrize("B,L,H", [(4, 1000, 2048), (16, 2048, 1024), (3, 777, 100)])
+def test_the_reverse_scan_alone_keeps_its_shape(probe, B, L, H):
+    """2x2 blocks: 32 channels x 128 steps, whatever shape a cell's backward pass takes at these sizes."""
+    import ctypes
+    lib = ctypes.CDLL(os.path.join(PKG, "libpararnn.so"))
+    lib.pararnn_affine_scan_workspace_bytes.restype = ctypes.c_size_t
+    assert lib.pararnn_affine_scan_workspace_bytes(1, 1, B, L, H) == probe(2, 2, 0, 0, B, L, H, True, (1, 2, 8, 8))["total"]
