@@ -165,11 +165,12 @@ inline TileCfg backward_tile(const CellInfo &ci, int dtype, int B, int L, int H,
     const TileCfg t = backward_tile_by_size(ci, dtype, B, L, H, table);
     return backward_tile_fits(ci, t) ? t : table;
 }
-// ... and whether its rows are staged
+// ... and whether its rows are staged.  3x3 blocks: one workgroup of 64 x 64 steps on a compute unit then, for its rows take 99 KB of
+// LDS; tri_tanh staged / plain: 2e6 to 4e6 elements 1.05-1.27, 8e6 0.98-1.06, 1.2e7 0.95-1.0, 6e7 0.85-0.89.
 inline bool backward_staged(const CellInfo &ci, int B, int L, int H)
 {
     const double n = (double)B * L * H;
-    if (ci.S > 2) return true;
+    if (ci.S > 2) return H % 64 == 0 && n >= 1.2e7;
     return H % 64 == 0 && n >= (ci.S == 1 ? 4e7 : ci.G <= 2 ? 3e7 : 0.0);
 }
 

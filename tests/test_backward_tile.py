@@ -48,3 +48,13 @@ def test_a_shape_that_is_taken_is_built(tiles):
             assert fits(S, P, taken), (p, table, taken)
         other += taken != table
     assert other > 1000
+
+
+# 3x3 blocks (tri_tanh, bf16), us on MI355X with staged rows / without
+STAGED = [(16, 1000, 64, 30.7, 23.9), (4, 500, 1024, 33.8, 27.5), (4, 4096, 192, 45.2, 42.6), (1, 4096, 1536, 68.0, 66.0),
+          (16, 500, 1536, 114.3, 120.1), (4, 4096, 1024, 144.9, 151.9), (16, 1000, 4096, 512.5, 582.1)]
+
+
+def test_rows_of_3x3_blocks_are_staged_where_that_is_faster(tiles):
+    for m, (_, _, staged) in zip(STAGED, tiles([(3, 3, 9, -1, BF16, *m[:3]) for m in STAGED])):
+        assert staged == (m[3] < m[4]), m

@@ -38,3 +38,26 @@ def test_tiles_agree(cell, dtype, B, L, H):
     # fp32: sums of the same terms in another order, 2e-6 of the largest; bf16 outputs: one unit of the last place more
     for x, y, bits in zip(got, want, (dtype == torch.bfloat16, False, dtype == torch.bfloat16)):
         assert (x.float() - y.float()).abs().max() <= (2.0 ** -8 if bits else 2e-6) * y.float().abs().max()
+
+
+# 3x3 blocks: rows that are staged, the last tile short, and rows that are not for their number and for their length
+@pytest.mark.parametrize("B,L,H,staged", [(16, 501, 1536, True), (3, 2051, 2048, True), (4, 500, 1024, False), (16, 700, 1544, False)])
+def test_3x3_blocks_staged_and_not(B, L, H, staged):
+    import paper_2510_21450_amd as P
+    c = P.example_cell("tri_tanh")
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(L)
+    rand = lambda *s: torch.randn(*s, generator=gen, device="cuda")
+    p = (2 * torch.rand(c.param_rows, H, generator=gen, device="cuda") - 1) * 0.3
+    u, g, h0 = rand(B, L, c.G, H).bfloat16(), rand(B, L, 3, H).bfloat16(), rand(B, 3, H).bfloat16()
+    h = (rand(B, L, 3, H) * 0.5).bfloat16()
+    got = P.backward(c, p, u, h0, h, g, want_dh0=True)
+    try:
+        P.set_staging(False)
+        want = P.backward(c, p, u, h0, h, g, want_dh0=True)
+    finally:
+        P.set_staging(True)
+    # the same tile and order of operations: products and sums may be contracted differently in the two kernels
+    for x, y, bits in zip(got, want, (True, False, True)):
+        assert (x.float() - y.float()).abs().max() <= (2.0 ** -8 if bits else 2e-6) * y.float().abs().max()
+        assert staged or torch.equal(x, y)
