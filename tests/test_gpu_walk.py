@@ -5,24 +5,22 @@ import torch
 pytestmark = pytest.mark.gpu
 
 from test_gpu_parity import problem, relerr, to_np      # noqa: E402
-from test_walk_choice import SIZES                       # noqa: E402
+from test_gpu_user_cells import ORACLE_NAME, problem as user_problem      # noqa: E402
+from test_walk_choice import SIZES, USER_SIZES           # noqa: E402
 
 
 def sampled(H):
     return sorted({c for c in (0, 1, 3, 4, 15, 16, 31, 32, 63, 64, H // 2, H - 17, H - 5, H - 4, H - 2, H - 1) if 0 <= c < H})
 
 
-@pytest.mark.parametrize("cell", ["gru_diag", "lstm_diag", "paralstm_diag"])
-@pytest.mark.parametrize("shape", SIZES)
-def test_walk(oracle_mod, cell, shape):
+def check(oracle_mod, cell, oracle_name, make, B, L, H):
     """Every iterate and the solution of sampled channels (they are independent), and states and count against the kernels with
     carry records; tensors at odd addresses, with and without h0."""
     import paper_2510_21450_amd as P
-    B, L, H = shape
     for dtype in (torch.float32, torch.bfloat16):
         bound = 1e-5 if dtype == torch.float32 else 2e-2
-        print(f"walk {cell} {shape} {dtype}", flush=True)
-        params, u, h0, _ = problem(cell, B, L, H, seed=170 + L, dtype=dtype)
+        print(f"walk {oracle_name} {B}x{L}x{H} {dtype}", flush=True)
+        params, u, h0, _ = make(cell, B, L, H, seed=170 + L, dtype=dtype)
         if (L + H + (dtype == torch.float32)) % 2:
             h0 = None
         pick = sampled(H)
@@ -31,15 +29,29 @@ def test_walk(oracle_mod, cell, shape):
         for k in (2, 20):                                # 20: more iterations than carries are kept for one by one
             h, iters, _ = P.forward(cell, params, u, h0, tol=-1.0, max_iter=k)
             assert iters.cpu().tolist() == [k, 0]
-            assert relerr(take(h), oracle_mod.newton(cell, pn, un, h0n, tol=-1.0, max_iter=k)[0]) <= 2 * bound, k
+            assert relerr(take(h), oracle_mod.newton(oracle_name, pn, un, h0n, tol=-1.0, max_iter=k)[0]) <= 2 * bound, k
         h, iters, _ = P.forward(cell, params, u, h0, tol=1e-4, max_iter=40)
-        assert relerr(take(h), oracle_mod.seq_unroll(cell, pn, un, h0n)) <= bound
+        assert relerr(take(h), oracle_mod.seq_unroll(oracle_name, pn, un, h0n)) <= bound
         other, with_records, _ = P.forward(cell, params, u, h0, tol=1e-4, max_iter=40, trace=True)
         assert iters.cpu().tolist() == with_records.cpu().tolist()
         assert relerr(to_np(h), to_np(other)) <= bound
         shifted = torch.empty(u.numel() + 1, dtype=dtype, device="cuda")[1:].view(u.shape).copy_(u)
         again = P.forward(cell, params, shifted, h0, tol=1e-4, max_iter=40)[0]
         assert torch.equal(again, h)                     # the same values by other copies
+
+
+@pytest.mark.parametrize("cell", ["gru_diag", "lstm_diag", "paralstm_diag"])
+@pytest.mark.parametrize("shape", SIZES)
+def test_walk(oracle_mod, cell, shape):
+    check(oracle_mod, cell, cell, problem, *shape)
+
+
+@pytest.mark.parametrize("name", ["gru_softsign", "rot_tanh"])
+@pytest.mark.parametrize("shape", USER_SIZES)
+def test_walk_of_a_users_cell(oracle_mod, name, shape):
+    """Instantiations of their own: nothing folded, the marks around the whole cell, two gates."""
+    import paper_2510_21450_amd as P
+    check(oracle_mod, P.example_cell(name), ORACLE_NAME[name], user_problem, *shape)
 
 
 @pytest.mark.parametrize("cell", ["gru_diag", "lstm_diag"])

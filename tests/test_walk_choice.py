@@ -17,6 +17,9 @@ RECORDS, WORKGROUP, WALK = 0, 1, 2
 SIZES = [(3, 1025, 343), (1, 1025, 1024), (2, 200, 1500), (1, 200, 3001), (16, 97, 344), (3, 97, 3001), (16, 64, 515), (1, 64, 10000),
          (16, 64, 3001), (3, 513, 343), (2, 513, 700), (2, 257, 2047), (1, 257, 4096), (16, 129, 1001), (8, 129, 2048), (3, 129, 10000),
          (3, 1531, 512), (8, 200, 1001), (1, 200, 8192), (3, 64, 10000), (2, 769, 1000), (1, 2305, 1024), (4, 300, 8192), (8, 480, 4090), (8, 97, 2047)]
+#: ... and those at which cells from libraries of their own are run, walked in both types
+USER_SIZES = [(3, 1025, 343), (16, 64, 515), (3, 97, 3001), (16, 129, 1001), (3, 1531, 512), (8, 200, 1001), (1, 200, 8192), (8, 480, 4090), (8, 97, 2047),
+              (8, 1000, 1536)]
 
 
 @pytest.fixture(scope="module")
@@ -100,3 +103,13 @@ def test_the_faster_kernels_are_taken(choose):
     for m, s in zip(MEASURED, choose([m[:6] for m in MEASURED])):
         assert (s[0] == WALK) == (m[7] < m[6]), (m, s)
     assert all(s[0] != WALK for s in choose([(TRI, F32, 16, 2000, 1024, 0), (GRU, F32, 1, 64, 8, 0), (GRU, BF16, 32, 1, 1024, 0)]))
+
+
+def test_cells_of_a_users_own_are_walked_where_they_are_tested(choose):
+    for cell in ((3, 1, 6, -1), ROT):
+        seen = set()
+        for dt in (F32, BF16):
+            for s in choose([(cell, dt, *size, 0) for size in USER_SIZES]):
+                assert s[0] == WALK
+                seen.add((s[1], s[2]))
+        assert len(seen) >= 5, seen
