@@ -796,7 +796,7 @@ inline bool without_blocks(const CellInfo &ci, int dtype, int B, int L, int H, f
     ShortShape other;
     const bool one_workgroup = short_shape(ci, dtype, B, L, H, false, n_iters, &other);
     if (walk_forward_shape(ci, dtype, B, L, H, n_iters, one_workgroup ? &other : nullptr, sh)) return true;
-    *sh = other;
+    if (one_workgroup) *sh = other;
     return one_workgroup;
 }
 

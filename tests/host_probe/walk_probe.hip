@@ -14,9 +14,16 @@ int main()
     while (scanf("%d %d %d %d %d %d %d %d %d", &G, &S, &PR, &kind, &dtype, &B, &L, &H, &fixed) == 9) {
         const CellInfo ci = {G, S, PR, kind};
         const SolveOpts opts = {1, kFusedHead, false};
-        ShortShape sh = {};
+        const ShortShape none = {-1, -1, -1, -1, -1, -1};
+        ShortShape sh = none;
         const bool found = without_blocks(ci, dtype, B, L, H, fixed ? -1.0f : 1e-5f, fixed ? fixed : 64, opts, &sh);
-        if (!found) sh = ShortShape{};
+        if (!found) {
+            if (sh.c != none.c || sh.lps_log2 != none.lps_log2 || sh.w != none.w || sh.n_items != none.n_items) {
+                fprintf(stderr, "a shape without a choice\n");
+                return 1;
+            }
+            sh = ShortShape{};
+        }
         printf("%d %d %d %d %d %d %u\n", found ? sh.walk ? 2 : 1 : 0, sh.c, sh.lps_log2, sh.w, sh.n_items, sh.n_tiles,
                found ? short_wait_limit(kSpinLimit, sh, fixed ? fixed : 64) : 0);
     }
