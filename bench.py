@@ -183,13 +183,13 @@ def block_iterations(w):
 
 
 def without_blocks(w):
-    """Whether the library solves the workload in one launch, one workgroup or wave per group of channels."""
+    """The kernel that solves the workload in one launch, one workgroup or wave per group of channels; None if it runs blocks."""
     import torch
     import paper_2510_21450_amd as P
     if w.cell == "tanh_dense":
-        return False
+        return None
     problem = (w.cell, torch.bfloat16 if w.dtype == "bf16" else torch.float32, w.B, w.L, w.H, w.tol, w.max_iter)
-    return P.solve_without_blocks(*problem) or P.solve_walked(*problem)
+    return "newton_walk_kernel" if P.solve_walked(*problem) else "newton_short_kernel" if P.solve_without_blocks(*problem) else None
 
 
 def kernel_figures(run, reps, counters):
@@ -274,7 +274,7 @@ def kernel_figures(run, reps, counters):
         out["block_issue_bound_frac"] = t_issue_ms / t_block_ms
     else:
         out["block_issue_bound_ms"] = out["block_issue_bound_frac"] = None
-    out["roofline"] = {"bound": "alu", "kernel": "newton_walk_kernel or newton_short_kernel (the whole solve)" if one_launch else "newton_fused_kernel (first block of a solve)", "achieved": ach,
+    out["roofline"] = {"bound": "alu", "kernel": f"{one_launch} (the whole solve, {K0} iterations)" if one_launch else f"newton_fused_kernel (first block of a solve, {K0} iterations)", "achieved": ach,
                        "peak": VALU_F32_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": ach / VALU_F32_PEAK_TFLOPS,
                        "traffic": cnt.get("dominant", {}).get("traffic_bytes")}
     out["algorithmic_bytes_per_launch"] = ab["block"] * N
