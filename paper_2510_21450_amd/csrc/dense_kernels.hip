@@ -1173,15 +1173,16 @@ struct WaveLds {
 };
 
 // A block of K iterations over the rows q of sequence b, by a whole workgroup; wr: W as wave_products wants it.
-// s.m[i]: max |delta| of iteration i.  EDGE: the updates that DenseStretch::edge holds go to `edge`; otherwise they may be
-// what enters at the first row, the updates of the step before it (NULL: zero).
+// s.m[i]: max |delta| of iteration i.  KIND: kStretch leaves the updates that DenseStretch::edge holds in `edge`; kRest may find there
+// what enters at the first row, the updates of the step before it (NULL: zero); kWhole starts from zero.
 //
 // Record of step t: for iteration i (0 ..) at timestep l = first + t - i three rows from float kWavePer i on: h_l and y_{l-1} of the
 // iterate before (left there by iteration i - 1 in step t - 1, by the mover for i = 0), and kTanhScale * u_l.  The
 // sixteen floats behind them put the four iterations of a wave's access into four different quarters of the banks.
 // Steps before an iteration's first timestep find zeros there, which give delta = 0; the last of them, at the timestep before
 // the first one, is where what enters takes its place.
-template <bool EDGE>
+enum { kWhole, kStretch, kRest };
+template <int KIND>
 __device__ __forceinline__ void wavefront_block(const DenseArgs &a, int b, int K, const WaveRows &q, const float (&wr)[16], WaveLds &s,
                                                 float *edge)
 {
@@ -1190,7 +1191,8 @@ __device__ __forceinline__ void wavefront_block(const DenseArgs &a, int b, int K
     const int xw = 64 * (w & 3) + 16 * (r >> 2) + 4 * it + (r & 3);  // where this lane's delta goes
     const int L = q.end - q.first, lead = q.start - q.first;         // steps, of which the first do not count
     const int n_groups = (L + K - 1 + kWaveGroup - 1) / kWaveGroup;
-    const bool enters = !EDGE && edge;
+    constexpr bool EDGE = KIND == kStretch;
+    const bool enters = KIND == kRest && edge;
     if (w < 4) s.x[0][xw] = enters && it == 0 ? edge[row] : 0.0f;
     if (threadIdx.x < kWaveIters) s.m[threadIdx.x] = 0u;
     if (w == 4) {
@@ -1294,16 +1296,19 @@ __device__ __forceinline__ void wavefront_block(const DenseArgs &a, int b, int K
         };
         lds_barrier();
         hand_on(s.rec[0], 0.0f, 0.0f);
-        for (int g = 0; g < n_groups; ++g) {
+        int g = 0;
+        if (enters) {
+#pragma unroll
+            for (int i = 0; i < kWaveGroup; ++i) step(std::integral_constant<int, 3>{}, i & 1, s.rec[i + 1], i);
+            g = 1;
+        }
+        for (; g < n_groups; ++g) {
             const int t0 = g * kWaveGroup;
             float *rec = s.rec[t0 & (kRing - 1)], *rec_next = s.rec[(t0 + kWaveGroup) & (kRing - 1)];
             auto group = [&](auto kind) {
 #pragma unroll
                 for (int i = 0; i < kWaveGroup; ++i) step(kind, i & 1, i + 1 < kWaveGroup ? rec + kWaveRec * (i + 1) : rec_next, t0 + i);
             };
-            if constexpr (!EDGE) {
-                if (g == 0 && enters) { group(std::integral_constant<int, 3>{}); continue; }
-            }
             if (t0 + kWaveGroup < L && (lead == 0 || t0 >= lead + kWaveIters - 1)) {
                 group(std::integral_constant<int, 0>{});
             } else {
@@ -1340,7 +1345,7 @@ __global__ __launch_bounds__(320) void dense_stretch_kernel(const DenseArgs a, c
     load_w_wave(a.W, wr);
     const int start = j * c.len;
     const WaveRows q = {c.h0it + seq, a.d + seq, a.h + seq, c.y + seq, max(start - kWarm, 0), start, min(start + c.len, a.L)};
-    wavefront_block<true>(a, b, K, q, wr, s, c.edge + (size_t)blockIdx.x * 2 * kWaveIters * DH);
+    wavefront_block<kStretch>(a, b, K, q, wr, s, c.edge + (size_t)blockIdx.x * 2 * kWaveIters * DH);
     __syncthreads();
     if (threadIdx.x < kWaveIters) c.top[(size_t)blockIdx.x * kWaveIters + threadIdx.x] = s.m[threadIdx.x];
 }
@@ -1349,7 +1354,8 @@ __global__ __launch_bounds__(320) void dense_stretch_kernel(const DenseArgs a, c
 // the blocks after it are run by the sequences that are not.  gm[k-1]: max |delta| of iteration k over the
 // sequences that ran it.  The last workgroup to finish reports the first iteration whose maximum met the tolerance.
 // After dense_stretch_kernel it goes on behind the first block, or solves that again from the first border on where the updates
-// differ.
+// differ.  CUT: there were stretches.
+template <bool CUT>
 __global__ __launch_bounds__(320) void dense_wavefront_kernel(const DenseArgs a, unsigned int *gm, const DenseStretch c)
 {
     __shared__ WaveLds s;
@@ -1367,7 +1373,7 @@ __global__ __launch_bounds__(320) void dense_wavefront_kernel(const DenseArgs a,
     constexpr int kTops = (kStretches * kWaveIters + 319) / 320;
     unsigned int top[kTops];                               // of stretch (threadIdx.x + 320 j) / kWaveIters
     int held = 0;                                          // stretches that are as they have to be
-    if (c.n > 1) {
+    if constexpr (CUT) {
         if (threadIdx.x == 0) s_held = c.n;
         if (threadIdx.x < kWaveIters) s.m[threadIdx.x] = 0u;
 #pragma unroll
@@ -1410,20 +1416,21 @@ __global__ __launch_bounds__(320) void dense_wavefront_kernel(const DenseArgs a,
         __syncthreads();
         held = __builtin_amdgcn_readfirstlane(s_held);     // the same for the whole workgroup: buffers chosen by it are scalars
     }
-    float *y = c.n > 1 ? c.y : a.d;
+    float wr[16];
+    if (!CUT || held < c.n) load_w_wave(a.W, wr);
+    float *y = CUT ? c.y : a.d;
     for (int k0 = 0; k0 < a.max_iter; k0 += kWaveIters) {
         const int K = min(kWaveIters, a.max_iter - k0);
-        if (k0 > 0 || held < c.n) {
-            const bool cut = k0 == 0 && c.n > 1;           // the rest of the first block
-            const int first = cut ? held * c.len : 0;
-            const WaveRows q = {(cut ? c.h0it : a.h) + seq, (cut ? a.d : y) + seq, a.h + seq, y + seq, first, first, a.L};
-            float wr[16];
-            load_w_wave(a.W, wr);
-            wavefront_block<false>(a, b, K, q, wr, s, cut ? c.edge + ((size_t)(b * c.n + held - 1) * 2 + 1) * kWaveIters * DH : nullptr);
+        if (!CUT || k0 > 0 || held < c.n) {
+            const bool rest = CUT && k0 == 0;              // of the first block
+            const int first = rest ? held * c.len : 0;
+            const WaveRows q = {(rest ? c.h0it : a.h) + seq, (rest ? a.d : y) + seq, a.h + seq, y + seq, first, first, a.L};
+            if (CUT && k0 == kWaveIters && held == c.n) load_w_wave(a.W, wr);
+            wavefront_block<CUT ? kRest : kWhole>(a, b, K, q, wr, s, rest ? c.edge + ((size_t)(b * c.n + held - 1) * 2 + 1) * kWaveIters * DH : nullptr);
             __threadfence();                               // the next block reads the rows that this one wrote
             __syncthreads();
         }
-        if (k0 == 0 && held > 0) {
+        if (CUT && k0 == 0) {
 #pragma unroll
             for (int j = 0; j < kTops; ++j) {
                 const int i = (int)threadIdx.x + 320 * j;
@@ -1950,8 +1957,12 @@ int dense_forward(int dtype, const float *W, const void *u, const void *h0, int 
             else guess.h = c.h0it;
         }
         hipLaunchKernelGGL(dense_guess_kernel, dim3(res_blocks), dim3(256), 0, st, guess, gm, max_iter);
-        if (c.n > 1) hipLaunchKernelGGL(dense_stretch_kernel, dim3(B * c.n), dim3(320), 0, st, a, c);
-        hipLaunchKernelGGL(dense_wavefront_kernel, dim3(B), dim3(320), 0, st, a, gm, c);
+        if (c.n > 1) {
+            hipLaunchKernelGGL(dense_stretch_kernel, dim3(B * c.n), dim3(320), 0, st, a, c);
+            hipLaunchKernelGGL(dense_wavefront_kernel<true>, dim3(B), dim3(320), 0, st, a, gm, c);
+        } else {
+            hipLaunchKernelGGL(dense_wavefront_kernel<false>, dim3(B), dim3(320), 0, st, a, gm, c);
+        }
         return hipGetLastError() == hipSuccess ? PARARNN_OK : PARARNN_HIP_ERROR;
     }
     if (launch_reset(a.ctrl, nullptr, 0, iters, status0, st) != hipSuccess) return PARARNN_HIP_ERROR;
