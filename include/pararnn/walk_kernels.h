@@ -285,6 +285,7 @@ __global__ __launch_bounds__(kWave * W) __attribute__((amdgpu_waves_per_eu(walk_
     }
     Cell::fold_params(p, pq);
 
+    const unsigned int tol_bits = __float_as_uint(fabsf(a.tol)), eighth_bits = __float_as_uint(0.125f * fabsf(a.tol));
     unsigned int v = 0u;                               // this wave's verdict
     int k_before = 0, k_final = 0;                     // iterations of the tile before; the first with a final boundary
     float ho[C][S], guess_end[S];                      // guess_end: the initial guess of the last step of the tile before
@@ -345,7 +346,10 @@ __global__ __launch_bounds__(kWave * W) __attribute__((amdgpu_waves_per_eu(walk_
         const int n_valid = ch_ok ? min(max(a.L - l0, 0), C) : 0;      // steps of this lane inside the tensor
         const bool all_valid = __all(n_valid == C);
         int k = 0, k_met = 1;                          // k_met: the first iteration after which every update met the tolerance
-        float mk = 0.0f;
+        // The largest update only takes part in comparisons, which every lane makes for itself: the bits of a value that is not
+        // negative are in its order, those of a NaN above them all.
+        bool finite = true, over = false;
+        unsigned int wmax_bits = 0u;
         while (k < a.max_iter) {
             ++k;
             float dt[S];                               // what enters the tile
@@ -360,9 +364,6 @@ __global__ __launch_bounds__(kWave * W) __attribute__((amdgpu_waves_per_eu(walk_
             }
             // ---- thread level
             float PA[C][SS], qb[C][S], accA[SS], accB[S];
-            set_identity<S>(accA);
-#pragma unroll
-            for (int s = 0; s < S; ++s) accB[s] = 0.0f;
 #pragma unroll
             for (int i = 0; i < C; ++i) {
                 float J[SS], r[S], hp[S], F[S];
@@ -371,7 +372,14 @@ __global__ __launch_bounds__(kWave * W) __attribute__((amdgpu_waves_per_eu(walk_
                 eval_step<Cell>(p, pq, hp, uu[i], F, J);
 #pragma unroll
                 for (int s = 0; s < S; ++s) r[s] = F[s] - ho[i][s];
-                push_step<S>(J, r, accA, accB);
+                if (i == 0) {
+#pragma unroll
+                    for (int e = 0; e < SS; ++e) accA[e] = J[e];
+#pragma unroll
+                    for (int s = 0; s < S; ++s) accB[s] = r[s];
+                } else {
+                    push_step<S>(J, r, accA, accB);
+                }
                 gates_done<SS>(accA);
                 gates_done<S>(accB);
 #pragma unroll
@@ -386,7 +394,7 @@ __global__ __launch_bounds__(kWave * W) __attribute__((amdgpu_waves_per_eu(walk_
 #pragma unroll
             for (int s = 0; s < S; ++s) din[s] = walk_shift(cwl, me.seg, x[s], dt[s]);
             // ---- back-substitution
-            unsigned int wmax_bits = 0u;
+            wmax_bits = 0u;
             float d[S];
             auto substitute = [&](auto guard) {
                 float m = 0.0f, last = 0.0f;
@@ -417,18 +425,19 @@ __global__ __launch_bounds__(kWave * W) __attribute__((amdgpu_waves_per_eu(walk_
                 for (int s = 0; s < S; ++s) c[s << cwl] = k > kShortCarries ? c[s << cwl] + d[s] : d[s];
             }
             // ---- the stopping test of this group of channels
-            mk = __uint_as_float(wave_max_u32(wmax_bits));
-            if (!(mk - mk == 0.0f)) break;
+            finite = !__any(wmax_bits >= 0x7f800000u);
+            if (!finite) break;
             if (a.tol >= 0.0f) {
-                if (mk > a.tol) k_met = k + 1;
+                over = __any(wmax_bits > tol_bits);
+                if (over) k_met = k + 1;
                 else if (k >= k_final) break;
             }
         }
-        if (!(mk - mk == 0.0f)) v = max(v, short_verdict(kStNonFinite, k));
-        else if (a.tol >= 0.0f && mk > a.tol) v = max(v, short_verdict(kStNotConverged, k));
+        if (!finite) v = max(v, short_verdict(kStNonFinite, k));
+        else if (over) v = max(v, short_verdict(kStNotConverged, k));
         else v = max(v, short_verdict(kStOk, a.tol >= 0.0f ? k_met : k));
         k_before = k_final = min(k, kShortCarries);
-        if (k_before == k && k > 1 && mk <= 0.125f * a.tol) k_final = k - 1;
+        if (k_before == k && k > 1 && finite && a.tol >= 0.0f && !__any(wmax_bits > eighth_bits)) k_final = k - 1;
     }
     {
         leave_h(ho);                                   // nobody reads u any more since the tile's barriers

@@ -29,7 +29,7 @@ namespace pararnn {
 
 struct NlSigmoid {
     __device__ __forceinline__ static float f(float x) { return fast_sigmoid(x); }
-    __device__ __forceinline__ static float d(float, float y) { return y * (1.0f - y); }
+    __device__ __forceinline__ static float d(float, float y) { return fmaf(-y, y, y); }
 };
 struct NlTanh {
     __device__ __forceinline__ static float f(float x) { return fast_tanh(x); }
@@ -86,8 +86,15 @@ template <class NU, class NR, class NS> struct GruDiagNl {
     __device__ __forceinline__ static void step_and_jacobian(const float *p, const float *hp, const float *u,
                                                              float *F, float *J)
     {
-        float kz, kr, kc, rh;
-        coefs(p, hp[0], u, F[0], J[0], kz, kr, kc, rh);
+        const float h = hp[0];
+        const float xz = fmaf(p[0], h, u[0] + p[3]), xr = fmaf(p[1], h, u[1] + p[4]);
+        const float z = NU::f(xz), r = NR::f(xr);
+        const float xc = fmaf(p[2], r * h, u[2] + p[5]);
+        const float c = NS::f(xc);
+        const float cmh = c - h;
+        F[0] = fmaf(z, cmh, h);
+        const float t = fmaf(p[1], h * NR::d(xr, r), r);          // r + a_r h NR'(.): k_r is not needed by itself
+        J[0] = fmaf(p[2] * (z * NS::d(xc, c)), t, fmaf(p[0], cmh * NU::d(xz, z), 1.0f - z));
     }
 
     // k = (k_z, k_r, k_c, h, r h): the last two are d(pre-activation)/d(a_*)

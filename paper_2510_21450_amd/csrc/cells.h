@@ -11,6 +11,10 @@
 //
 // An evaluation with its Jacobian is mid() (the NM values that need exponentials and reciprocals), then jac(); begin()
 // marks the start of the former (gates_begin in common.h, eval_step in scan_kernels.h).  fwd() is the two in one.
+// The forward solves are bound by the vector instructions of an evaluation, so jac() forms J alone with as few as there
+// are, and the backward pass, which is bound by memory and needs the derivatives one by one, has its own formulas (us of a
+// training step, shared formulas -> own ones and the first step of a chunk without a product with the identity: GRU fp32
+// 16 x 4096 x 1024 750 -> 737, LSTM fp32 8 x 2048 x 2048 693 -> 651, GRU bf16 4 x 65536 x 4096 8954 -> 8595).
 //
 // Backward (Sec. 2, Eq. (6)): bwd_prep returns J and NC coefficients from which
 // bwd_emit maps the incoming adjoint lam (dL/d state_l) to dL/du_l and adds this
@@ -78,17 +82,17 @@ struct GruDiag {
     {
         gates<FOLD>(p, q, hp[0], u, m[0], m[1], m[2], m[3]);
     }
-    // The forward pass needs F and J only: J = (1-z) + a_z k_z + a_c k_c (r + a_r r h (1-r)), which
-    // skips k_r as a value of its own (one instruction fewer per evaluation than coefs).
+    // The forward pass needs F and J only: J = (1-z) (1 + a_z z (c-h)) + a_c k_c (r + a_r r h (1-r)), with x (1-x) as x - x x
+    // in one instruction: eleven of them where the coefficients of the backward pass take fifteen.
     __device__ __forceinline__ static void jac(const float *p, const float *hp, const float *m, float *F, float *J)
     {
         const float h = hp[0], z = m[0], r = m[1], rh = m[2], c = m[3];
-        const float cmh = c - h, omz = 1.0f - z;
+        const float cmh = c - h;
         F[0] = fmaf(z, cmh, h);
-        const float kz = cmh * (z * omz);
+        const float jz = fmaf(p[0], z * cmh, 1.0f);
         const float ackc = p[2] * (z * fmaf(-c, c, 1.0f));
-        const float t = fmaf(p[1], rh * (1.0f - r), r);
-        J[0] = fmaf(ackc, t, fmaf(p[0], kz, omz));
+        const float t = fmaf(p[1], fmaf(-rh, r, rh), r);
+        J[0] = fmaf(ackc, t, fmaf(-z, jz, jz));
     }
     template <bool FOLD = false>
     __device__ __forceinline__ static void fwd(const float *p, const float *hp, const float *u, float *F, float *J,
@@ -157,13 +161,14 @@ struct LstmDiag {
         F[1] = o * fast_tanh(F[0]);
     }
 
-    static constexpr int NM = 6;                       // i, f, o, g, c', tanh(c')
+    static constexpr int NM = 7;                       // i, f, o, g, c', tanh(c'), i g
     __device__ __forceinline__ static void begin(float *, float *q) { gates_begin<PQ>(q); }
     template <bool FOLD>
     __device__ __forceinline__ static void mid(const float *p, const float *q, const float *hp, const float *u, float *m)
     {
         gates<FOLD>(p, q, hp[1], u, m[0], m[1], m[2], m[3]);
-        m[4] = fmaf(m[1], hp[0], m[0] * m[3]);
+        m[6] = m[0] * m[3];
+        m[4] = fmaf(m[1], hp[0], m[6]);
         m[5] = fast_tanh(m[4]);
     }
     // k[0..3] = d c'/d u_{i,f,g-slot order i,f,o,g} with k[2] = d h'/d u_o,
@@ -185,10 +190,20 @@ struct LstmDiag {
         J[2] = k[4] * f;
         J[3] = fmaf(k[2], p[2], k[4] * jch);
     }
+    // The forward pass needs J alone, to the absolute error of the gates: products that the state's formula has anyway
+    // (i g, o tanh(c')) lead to the derivatives in one instruction each, thirteen in all where coefs() takes twenty.
     __device__ __forceinline__ static void jac(const float *p, const float *hp, const float *m, float *F, float *J)
     {
-        float k[NC];
-        coefs(p, hp, m, F, J, k);
+        const float c = hp[0], i = m[0], f = m[1], o = m[2], g = m[3], t = m[5], ig = m[6];
+        F[0] = m[4];
+        F[1] = o * t;
+        const float ki = fmaf(-ig, i, ig), kf = c * fmaf(-f, f, f), ko = fmaf(-F[1], o, F[1]);
+        const float kg = fmaf(-ig, g, i), kc = fmaf(-F[1], t, o);
+        const float jch = fmaf(ki, p[0], fmaf(kf, p[1], kg * p[3]));
+        J[0] = f;
+        J[1] = jch;
+        J[2] = kc * f;
+        J[3] = fmaf(ko, p[2], kc * jch);
     }
     template <bool FOLD = false>
     __device__ __forceinline__ static void fwd(const float *p, const float *hp, const float *u, float *F, float *J,
@@ -273,13 +288,14 @@ struct ParaLstmDiag {
         F[1] = o * fast_tanh(cn);
     }
 
-    static constexpr int NM = 5;                       // f, z, o, c', tanh(c')
+    static constexpr int NM = 6;                       // f, z, o, c', tanh(c'), c - z
     __device__ __forceinline__ static void begin(float *, float *q) { gates_begin<3>(q); }
     template <bool FOLD>
     __device__ __forceinline__ static void mid(const float *p, const float *q, const float *hp, const float *u, float *m)
     {
         gates_fz<FOLD>(p, q, hp[0], hp[1], u, m[0], m[1]);
-        m[3] = fmaf(m[0], hp[0] - m[1], m[1]);
+        m[5] = hp[0] - m[1];
+        m[3] = fmaf(m[0], m[5], m[1]);
         m[2] = gate_o<FOLD>(p, q, m[3], hp[1], u);
         m[4] = fast_tanh(m[3]);
     }
@@ -307,10 +323,19 @@ struct ParaLstmDiag {
         J[2] = hc * jcc;
         J[3] = fmaf(k[2], p[2], hc * jch);
     }
-    __device__ __forceinline__ static void jac(const float *p, const float *hp, const float *m, float *F, float *J)
+    // The forward pass needs J alone: as in LstmDiag.
+    __device__ __forceinline__ static void jac(const float *p, const float *, const float *m, float *F, float *J)
     {
-        float k[NC];
-        coefs(p, hp, m, F, J, k);
+        const float f = m[0], z = m[1], o = m[2], t = m[4], fcz = m[0] * m[5], omz2 = fmaf(-z, z, 1.0f);
+        F[0] = m[3];
+        F[1] = o * t;
+        const float kf = fmaf(-fcz, f, fcz), kz = fmaf(-f, omz2, omz2), ko = fmaf(-F[1], o, F[1]), kc = fmaf(-F[1], t, o);
+        const float jcc = fmaf(kf, p[3], f), jch = fmaf(kf, p[0], kz * p[1]);
+        const float hc = fmaf(ko, p[4], kc);          // d h'/d c' including the peephole of o
+        J[0] = jcc;
+        J[1] = jch;
+        J[2] = hc * jcc;
+        J[3] = fmaf(ko, p[2], hc * jch);
     }
     template <bool FOLD = false>
     __device__ __forceinline__ static void fwd(const float *p, const float *hp, const float *u, float *F, float *J,
