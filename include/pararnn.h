@@ -158,13 +158,13 @@ int pararnn_set_fused(int enable);
 int pararnn_set_staging(int enable);
 
 /* Test / tuning hook (host, process-wide; default 0).  The kernels that run at
- * the speed of the memory (one Newton iteration per launch; the backward pass
- * for bf16 storage) can mark their tile accesses as streamed, which keeps
+ * the speed of the memory (one Newton iteration per launch; the backward pass)
+ * can mark their tile accesses as streamed, which keeps
  * them out of the way of what the device's memory-side cache holds from the
  * launch before.  mode 0: chosen per call from the sizes of the tensors (u is
  * streamed once u and the fp32 iterate together exceed that cache, the iterate
- * and the backward pass's tensors once they exceed twice its size); 1: never;
- * 2: always.  The results are the same bits in every mode.  Returns
+ * once it exceeds twice its size, the backward pass's tensors from one and a
+ * half times its size on, where rows are whole cache lines); 1: never; 2: always.  The results are the same bits in every mode.  Returns
  * PARARNN_INVALID_ARG for another mode. */
 int pararnn_set_streaming(int mode);
 

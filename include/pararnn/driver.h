@@ -66,14 +66,19 @@ inline int forward_stream_level(size_t u_bytes, size_t iterate_bytes)
     if (iterate_bytes > 2 * kMemCacheBytes) return 2;
     return u_bytes + iterate_bytes > kMemCacheBytes ? 1 : 0;
 }
-// The backward kernel for bf16 storage reads and writes every byte once: streamed when its tensors
-// together exceed twice the cache (4 % on 17 GB).  The fp32 kernels gain nothing either way (measured).
-inline int backward_stream(size_t bytes)
+// The backward kernel reads and writes every byte once.  Marked as streams its tensors stay out of each other's way, and out
+// of the way of what the pass before left in the cache (u and h of the last steps, where this one begins).  Pays from one
+// and a half times the cache on; below that the next reader of dL/du finds it in the cache.  Only rows of whole cache
+// lines: a line that two channel groups share leaves the L2 before the second one asks.  Not in tiles of twelve steps a
+// thread (ParaLSTM in fp32).  us of the pass, plain / streamed: fp32 16 x 2048 x 1024 GRU 212 / 192, LSTM 294 / 270, rot_tanh 223 / 200,
+// ParaLSTM 284 / 289 (7 x 3000 x 1536 259 / 270); bf16 16 x 2048 x 1024 LSTM 223 / 212, rot_tanh 146 / 135; 384 MB GRU fp32 87 / 79, LSTM
+// bf16 126 / 119; 256 MB rot_tanh bf16 78 / 81; 192 MB GRU bf16 57 / 61; rows of 1500 channels (16 x 2000) GRU fp32 371 / 412, bf16 232 / 298.
+inline int backward_stream(size_t bytes, bool pays)
 {
     const int mode = settings().streaming;
     if (mode == 1) return 0;
     if (mode == 2) return 1;
-    return bytes > 2 * kMemCacheBytes ? 1 : 0;
+    return pays && 2 * bytes >= 3 * kMemCacheBytes ? 1 : 0;
 }
 
 // Tile shape for a problem.  The table is the result of sweeps on MI355X over
@@ -927,7 +932,8 @@ int backward_pass(const CellInfo &ci, int dtype, const float *params, const void
     a.stage = settings().stage_enabled && dtype == PARARNN_BF16 && H % 8 == 0 && aligned(u, 16) && aligned(h, 16) &&
               aligned(dL_dh, 16) && (double)H * 2.0 * (16.0 * ci.G) < 4.0e9 &&
               (settings().tile[0] > 0 || backward_staged(ci, B, L, H));
-    a.stream = dtype == PARARNN_BF16 ? backward_stream((size_t)B * L * H * 2 * (2 * ci.G + 2 * ci.S)) : 0;
+    a.stream = backward_stream((size_t)B * L * H * esz * (2 * ci.G + 2 * ci.S),
+                               lo.cfg.c != 12 && H * esz % 128 == 0 && aligned(u, 128) && aligned(h, 128) && aligned(dL_dh, 128) && aligned(dL_du, 128));
     const int rc = backward_diag<Cell>(ci, dtype, lo, a, st, dL_dparams);
     if (rc != PARARNN_OK) workspace_forget(workspace);
     return rc;

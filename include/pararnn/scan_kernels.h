@@ -94,7 +94,7 @@ struct BwdArgs {
     unsigned long long *rec;
     Ctrl *ctrl;
     int stage;           // the tensors allow the LDS-staged kernel variant (16-byte aligned rows)
-    int stream;          // bf16 storage: interior tiles read and write their rows as streams
+    int stream;          // interior tiles read and write their rows as streams
 };
 
 // ------------------------------------------------------------ small matrix ops
@@ -1135,8 +1135,9 @@ __global__ __launch_bounds__(kWave *W) void backward_kernel(const BwdArgs a)
         RawU uur[kRaw ? 1 : C][kRaw ? 1 : G], hpr[C][S], ggr[C][S];
         RawF jrr[kRaw ? C : 1][kRaw ? SS : 1];
         const bool full_tile = (lt + 1) * T <= g.L && (cg + 1) * CW <= g.H;
-        auto load_inputs = [&](auto guard) {
+        auto load_inputs = [&](auto guard, auto stream) {
             constexpr bool kGuard = decltype(guard)::value;
+            constexpr int kAux = decltype(stream)::value ? kAuxStream : kAuxNone;
 #pragma unroll
             for (int i = 0; i < C; ++i) {
                 const int l = l0 + i;
@@ -1144,21 +1145,21 @@ __global__ __launch_bounds__(kWave *W) void backward_kernel(const BwdArgs a)
                 if constexpr (!kRaw) {
 #pragma unroll
                     for (int q = 0; q < G; ++q) {
-                        if constexpr (!kGuard) uur[i][q] = buf_load<UT, VEC>(ru, vu, (unsigned int)(i * G + q) * Hn * (unsigned int)sizeof(UT));
+                        if constexpr (!kGuard) uur[i][q] = buf_load<UT, VEC, kAux>(ru, vu, (unsigned int)(i * G + q) * Hn * (unsigned int)sizeof(UT));
                         else if (ok) uur[i][q] = load_raw<UT, VEC>(u + ((seq + l) * G + q) * g.H + ch);
                         else uur[i][q] = zero_raw<UT, VEC>();
                     }
                 }
 #pragma unroll
                 for (int s = 0; s < S; ++s) {
-                    if constexpr (!kGuard) ggr[i][s] = buf_load<UT, VEC>(rg, vh, (unsigned int)(i * S + s) * Hn * (unsigned int)sizeof(UT));
+                    if constexpr (!kGuard) ggr[i][s] = buf_load<UT, VEC, kAux>(rg, vh, (unsigned int)(i * S + s) * Hn * (unsigned int)sizeof(UT));
                     else if (ok) ggr[i][s] = load_raw<UT, VEC>(gl + ((seq + l) * S + s) * g.H + ch);
                     else ggr[i][s] = zero_raw<UT, VEC>();
                     hpr[i][s] = zero_raw<UT, VEC>();
                     if constexpr (!kRaw) {
                         if (ok) {
                             if (i > 0 || l > 0) {        // only a chunk's first step can be l = 0
-                                if constexpr (!kGuard) hpr[i][s] = buf_load<UT, VEC>(rh1, vh, (unsigned int)(i * S + s) * Hn * (unsigned int)sizeof(UT));
+                                if constexpr (!kGuard) hpr[i][s] = buf_load<UT, VEC, kAux>(rh1, vh, (unsigned int)(i * S + s) * Hn * (unsigned int)sizeof(UT));
                                 else hpr[i][s] = load_raw<UT, VEC>(hres + ((seq + l - 1) * S + s) * g.H + ch);
                             } else if (a.h0) {
                                 hpr[i][s] = load_raw<UT, VEC>(static_cast<const UT *>(a.h0) + ((size_t)b * S + s) * g.H + ch);
@@ -1257,8 +1258,8 @@ __global__ __launch_bounds__(kWave *W) void backward_kernel(const BwdArgs a)
                 thread_level(std::true_type{});
                 __builtin_amdgcn_s_waitcnt(0);       // every row has been read before it is overwritten
             } else {
-                if (full_tile) load_inputs(std::false_type{});
-                else load_inputs(std::true_type{});
+                if (full_tile) load_inputs(std::false_type{}, std::false_type{});
+                else load_inputs(std::true_type{}, std::false_type{});
                 thread_level(std::false_type{});
                 __builtin_amdgcn_s_waitcnt(0);
             }
@@ -1268,8 +1269,9 @@ __global__ __launch_bounds__(kWave *W) void backward_kernel(const BwdArgs a)
             if (next_staged) stage_tile(t_next);
             if (t_next < (unsigned int)g.n_tiles) load_params((int)(t_next % (unsigned int)g.n_groups) % g.n_cg, pn);
         } else {
-            if (full_tile) load_inputs(std::false_type{});
-            else load_inputs(std::true_type{});
+            if (full_tile && !kRaw && a.stream) load_inputs(std::false_type{}, std::bool_constant<!kRaw>{});
+            else if (full_tile) load_inputs(std::false_type{}, std::false_type{});
+            else load_inputs(std::true_type{}, std::false_type{});
             thread_level(std::false_type{});
         }
         // chunk aggregate before the wave-level scan overwrites it (nu at the chunk's first step)
@@ -1434,7 +1436,7 @@ __global__ __launch_bounds__(kWave *W) void backward_kernel(const BwdArgs a)
 #pragma unroll
             for (int s = 0; s < S; ++s) nu0[s][v] = n0[s];
         }
-        if (STAGE && full_tile && a.stream) {
+        if (!kRaw && full_tile && a.stream) {
 #pragma unroll
             for (int i = 0; i < C; ++i)
 #pragma unroll
