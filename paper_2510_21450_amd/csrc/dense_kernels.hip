@@ -987,8 +987,8 @@ int newton_grid(int prod)
 // A step is the product z = W [delta of the four iterations], 64 x 64 x 4, on v_mfma_f32_4x4x1_16b_f32, and
 //     F = tanh(y + u_l), d = 1 - F^2, delta = (F - h) + d z;   h += delta;   y_next = y + z
 // for every row and iteration, with y = W h_{l-1} and h = h_l of the iterate before.  y advances by z = W delta as
-// h does by delta, so W is applied to nothing but the updates; y of the first iterate of a block comes from
-// dense_guess_kernel, later blocks continue from the y their predecessor left behind.
+// h does by delta, so W is applied to nothing but the updates and the initial guess, whose rows four more waves have ready
+// group by group (guess_rows); later blocks continue from the y their predecessor left behind.
 // What bounds a step is latency (LDS read, products, sum, LDS write, barrier), so it has one exchange: wave w owns
 // rows 16 w .. 16 w + 15 and all of k.  The instruction's 16 blocks are four groups of four; a group covers the
 // wave's 16 rows (4 columns of the B operand in each block: W) and one quarter of k, and the A operand (the four
@@ -997,7 +997,7 @@ int newton_grid(int prod)
 // one iteration, and what an iteration hands to the next (h, y) moves up sixteen lanes within the wave.
 // F and d are formed while the delta of the step before is on its way.  With one wave per SIMD every instruction counts (a vector instruction
 // takes four cycles to issue, 1.8 ns), so the four waves touch no memory and compute no addresses: a fifth brings the
-// rows of u, h and y in, sixteen bytes per lane, and takes the results out, by way of a ring of records in LDS, one
+// rows of u (and, after the first block, h and y) in, sixteen bytes per lane, and takes the results out, by way of a ring of records in LDS, one
 // per step, in which each iteration finds its inputs and leaves its results where the next one looks for them.
 // Measured: see the rule at wavefront_plan().
 constexpr int kWaveIters = 4;
@@ -1011,7 +1011,7 @@ __device__ __forceinline__ float tanh_scaled(float y, float us)
     return fmaf(-2.0f, __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(fmaf(kTanhScale, y, us))), 1.0f);
 }
 
-// The first iterate and its y = W h, for every row at once: the initial guess
+// The first iterate and its y = W h, for every row at once, for sequences that are not cut: the initial guess
 // h_l = tanh(W h0 + u_l) (App. A), written here; W h0 itself goes to a.r, one row per sequence.  Also clears the control block and the n_gm maxima.
 __global__ __launch_bounds__(256) void dense_guess_kernel(const DenseArgs a, unsigned int *gm, int n_gm)
 {
@@ -1069,6 +1069,16 @@ __global__ __launch_bounds__(256) void dense_guess_kernel(const DenseArgs a, uns
         if (ok) *reinterpret_cast<f4v *>(a.d + row * DH + chn) = acc0 + acc1;
     }
 }
+
+// Waves of a workgroup: four for the chain, one that moves rows and, where the launch has them, four helpers, which make
+// ahead of the chain what does not wait for it: the rows of the initial guess and their W h, or the row factors of the
+// backward pass.  Without helpers that is a launch in front (dense_guess_kernel, dense_residual_kernel), which reads u and
+// writes one or two more sets of rows.  us, with the launch / with helpers: forward 64 x 1024 97 / 87.5, 16 x 600 45.6 / 40.6, backward
+// 64 x 1024 97 / 82, 256 x 256 83 / 70.  Forward solves that are not cut keep the launch (64 x 64 30 / 33, 256 x 256 109 / 110), and so
+// do backward passes of more sequences than units, where a unit's second workgroup has no room for so many waves (300 x 200 73 / 95).
+constexpr int kChain = 4, kMover = 4, kHelpers = 5, kWaves = 9;
+constexpr int kHelperUnits = 256;     // compute units
+constexpr int wave_threads(bool help) { return (help ? kWaves : kHelpers) * kWave; }
 
 // z of this lane's row from the exchanged vectors xv (lane 4 (4 s + m) + i, component g: row 16 s + 4 m + g of
 // column i) and wr[4 m + g] = W[16 w + lane % 16][16 (lane / 16) + 4 m + g], as four partial sums over k:
@@ -1152,16 +1162,14 @@ constexpr int kStretches = 256;       // of all sequences at most: one for each 
 
 struct DenseStretch {
     int n, len;                       // stretches of a sequence (1: none, the whole sequence at once), steps of each but the last
-    float *h0it;                      // initial guess, where the result does not take its place
-    float *y;                         // y of the iterate that the stretches leave behind
     float *edge;                      // [B][n][2][kWaveIters][64] updates at the step before the first one and at the last one
     unsigned int *top;                // [B][n][kWaveIters] max |delta|
 };
 
-// Where a block of iterations reads and leaves its rows, and which: steps from `first` on are run, `start` to `end` count.
+// The rows of a sequence that a block of iterations runs and leaves, and which: steps from `first` on are run, `start` to
+// `end` count.
 struct WaveRows {
-    const float *h_in, *y_in;         // of the sequence
-    float *h_out, *y_out;
+    float *h, *y;                     // of the sequence
     int first, start, end;
 };
 
@@ -1169,10 +1177,126 @@ constexpr int kWavePer = 3 * DH + 16, kWaveRec = kWaveIters * kWavePer + 2 * DH;
 struct WaveLds {
     __attribute__((aligned(16))) float x[2][DH * kWaveIters];        // delta, in the order of wave_products
     __attribute__((aligned(16))) float rec[kRing][kWaveRec];
+    f4v guess[DH / 4][16];                                           // rows of the initial guess, [channels 4 c ..][row % 16]
     unsigned int m[kWaveIters];
 };
 
-// A block of K iterations over the rows q of sequence b, by a whole workgroup; wr: W as wave_products wants it.
+// W x for the 16 columns of a wave of helpers, rows 16 hw .. + 15, as sixteen products of four terms each in two sums: the
+// MFMAs [from, to) of them.  One in a step of the chain, first thing behind its barrier, where the waves of the chain wait
+// for LDS: in the way of the chain's own products (or, in the backward pass, of its vector instructions) they cost a step 40 ns.
+struct HelperSums { f4v acc0, acc1; };
+__device__ __forceinline__ void helper_products(int from, int to, const float (&wa)[4][4], const f4v (&x)[4], HelperSums &s)
+{
+#pragma unroll
+    for (int m = 0; m < 16; ++m) {
+        if (m < from || m >= to) continue;
+        const int ww = (m & 1) + (m >= 8 ? 2 : 0), v = m >> 1 & 3;
+        f4v &acc = m & 1 ? s.acc1 : s.acc0;
+        if (m < 2) acc = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[ww][v], x[ww][v], acc, 0, 0, 0);
+    }
+}
+__device__ __forceinline__ void helper_barrier()
+{
+    __builtin_amdgcn_sched_barrier(0);
+    lds_barrier_keep_vmem();
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// The sixteen MFMAs of two groups spread over sixteen steps less the two in which their operands are exchanged; `slot` counts
+// from the first of those.
+__device__ __forceinline__ void helper_products_at(int slot, const float (&wa)[4][4], const f4v (&x)[4], HelperSums &s)
+{
+    helper_products(slot < 10 ? slot - 2 : 2 * slot - 12, slot < 10 ? slot - 1 : 2 * slot - 10 < 16 ? 2 * slot - 10 : 16, wa, x, s);
+}
+
+// The initial guess h_l = tanh(W h0 + u_l) (App. A) and y_{l-1} = W h_{l-1} of it for the rows of a block's groups, by the
+// four helping waves: wave hw has channels 16 hw .. + 15 of both, lane (n = lane % 16, g = lane / 16) channels 16 hw + 4 g ..
+// + 3 of row n.  Two groups at a time, rows t - 1 .. t + 14 for those from t on, made while the two before the last one run;
+// the first two in front of the chain, the next two during the first group.
+__device__ __forceinline__ void guess_rows(const DenseArgs &a, int b, const WaveRows &q, WaveLds &s, int n_groups)
+{
+    const int lane = threadIdx.x & 63, hw = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) - kHelpers;
+    const int n = lane & 15, g = lane >> 4, chn = 16 * hw + 4 * g;
+    const buf_rsrc ru = seq_rsrc(a.u + (size_t)b * a.L * DH, (unsigned int)a.L * (DH * 4u));
+    auto load_u = [&](int t, int i) {                      // of row t - 1 + i; outside the sequence zero
+        return __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(ru, (unsigned int)(q.first + t - 1 + i) * (DH * 4u) + 4u * chn, 0, 0));
+    };
+    f4v uv = load_u(0, n), un = load_u(2 * kWaveGroup, n);
+    float wa[4][4];
+    load_w_operand16(a.W, hw, n, g, wa);
+    f4v c0 = {0.0f, 0.0f, 0.0f, 0.0f}, hv = c0, x[4];      // c0: W h0
+    HelperSums y;
+    if (a.h0) {
+#pragma unroll
+        for (int ww = 0; ww < 4; ++ww) x[ww] = *reinterpret_cast<const f4v *>(a.h0 + (size_t)b * DH + 16 * ww + 4 * g);
+        hv = *reinterpret_cast<const f4v *>(a.h0 + (size_t)b * DH + chn);
+        helper_products(0, 16, wa, x, y);
+        c0 = y.acc0 + y.acc1;
+    }
+    if (q.first == 0 && n == 0) *reinterpret_cast<f4v *>(a.r + (size_t)b * DH + chn) = c0;   // later blocks need it
+    auto guess = [&]() {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) hv[v] = tanh_scaled(c0[v], kTanhScale * uv[v]);
+    };
+    auto fetch = [&]() {
+#pragma unroll
+        for (int ww = 0; ww < 4; ++ww) x[ww] = s.guess[4 * ww + g][n];
+    };
+    auto row_of = [&](int t) { return &s.rec[t & (kRing - 1)][chn]; };
+
+    if (q.first + n > 0) guess();                          // else h0, in front of the sequence's first row
+    s.guess[4 * hw + g][n] = hv;
+    if (n > 0) *reinterpret_cast<f4v *>(row_of(n - 1)) = hv;
+    helper_barrier();
+    fetch();
+    helper_products(0, 16, wa, x, y);
+    *reinterpret_cast<f4v *>(row_of(n) + DH) = y.acc0 + y.acc1;
+    helper_barrier();
+    auto start = [&](int t) {                              // rows t - 1 .. t + 14; the ones after those are asked for
+        uv = un;
+        guess();
+        s.guess[4 * hw + g][n] = hv;
+        un = load_u(t + 2 * kWaveGroup, n);
+        helper_barrier();
+        fetch();
+        helper_barrier();
+    };
+    f4v h_ready = hv, y_ready = c0;
+    auto leave = [&](int t) {
+        *reinterpret_cast<f4v *>(row_of(t - 1 + n)) = h_ready;
+        *reinterpret_cast<f4v *>(row_of(t + n) + DH) = y_ready;
+    };
+    start(2 * kWaveGroup);
+#pragma unroll
+    for (int j = 0; j < kWaveGroup - 2; ++j) {
+        helper_products(3 * j, 3 * j + 3, wa, x, y);
+        helper_barrier();
+    }
+    for (int i = 1; i < n_groups; i += 2) {
+        const int t = (i + 1) * kWaveGroup;                // of the two groups behind this one
+        h_ready = hv;
+        y_ready = y.acc0 + y.acc1;
+        if (n < kWaveGroup) leave(t);
+        start(t + 2 * kWaveGroup);
+#pragma unroll
+        for (int j = 2; j < kWaveGroup; ++j) {
+            helper_products_at(j, wa, x, y);
+            helper_barrier();
+        }
+        if (i + 1 == n_groups) break;
+        if (n >= kWaveGroup) leave(t);
+#pragma unroll
+        for (int j = kWaveGroup; j < 2 * kWaveGroup; ++j) {
+            helper_products_at(j, wa, x, y);
+            helper_barrier();
+        }
+    }
+    helper_barrier();
+}
+
+// A block of K iterations over the rows q of sequence b, by a whole workgroup; wr: W as wave_products wants it.  HELP: there
+// are helpers; GUESS: they make the iterate that the block starts from, the initial guess, which is otherwise read from its rows.
 // s.m[i]: max |delta| of iteration i.  KIND: kStretch leaves the updates that DenseStretch::edge holds in `edge`; kRest may find there
 // what enters at the first row, the updates of the step before it (NULL: zero); kWhole starts from zero.
 //
@@ -1182,7 +1306,7 @@ struct WaveLds {
 // Steps before an iteration's first timestep find zeros there, which give delta = 0; the last of them, at the timestep before
 // the first one, is where what enters takes its place.
 enum { kWhole, kStretch, kRest };
-template <int KIND>
+template <int KIND, bool HELP, bool GUESS>
 __device__ __forceinline__ void wavefront_block(const DenseArgs &a, int b, int K, const WaveRows &q, const float (&wr)[16], WaveLds &s,
                                                 float *edge)
 {
@@ -1193,28 +1317,36 @@ __device__ __forceinline__ void wavefront_block(const DenseArgs &a, int b, int K
     const int n_groups = (L + K - 1 + kWaveGroup - 1) / kWaveGroup;
     constexpr bool EDGE = KIND == kStretch;
     const bool enters = KIND == kRest && edge;
-    if (w < 4) s.x[0][xw] = enters && it == 0 ? edge[row] : 0.0f;
+    if (w < kChain) s.x[0][xw] = enters && it == 0 ? edge[row] : 0.0f;
     if (threadIdx.x < kWaveIters) s.m[threadIdx.x] = 0u;
-    if (w == 4) {
+    if (HELP && w >= kHelpers) {
+        if constexpr (GUESS) guess_rows(a, b, q, s, n_groups);
+        else
+            for (int i = 0; i < kWaveGroup * n_groups + 2; ++i) lds_barrier();
+    } else if (w == kMover) {
         const unsigned int seq_bytes = (unsigned int)a.L * (DH * 4u);
-        const buf_rsrc ru = seq_rsrc(a.u + (size_t)b * a.L * DH, seq_bytes), rh = seq_rsrc(q.h_in, seq_bytes), ry = seq_rsrc(q.y_in, seq_bytes);
+        const buf_rsrc ru = seq_rsrc(a.u + (size_t)b * a.L * DH, seq_bytes), rh = seq_rsrc(q.h, seq_bytes), ry = seq_rsrc(q.y, seq_bytes);
         // results: the rows that count, y those before them
         const int y0 = q.start > 0 ? q.start - 1 : 0;
-        const buf_rsrc oh = seq_rsrc(q.h_out + (size_t)q.start * DH, (unsigned int)(q.end - q.start) * (DH * 4u)),
-                       oy = seq_rsrc(q.y_out + (size_t)y0 * DH, (unsigned int)(q.end - 1 - y0) * (DH * 4u));
+        const buf_rsrc oh = seq_rsrc(q.h + (size_t)q.start * DH, (unsigned int)(q.end - q.start) * (DH * 4u)),
+                       oy = seq_rsrc(q.y + (size_t)y0 * DH, (unsigned int)(q.end - 1 - y0) * (DH * 4u));
         f4v xh[2], xy[2], xu[2];
         auto same = [&](int t) { return q.first + t; };
         auto before = [&](int t) { return q.first + t - 1; };
         auto bring = [&](int t) {
-            rows_load(rh, xh, lane, t, same);
-            rows_load(ry, xy, lane, t, before);
+            if constexpr (!GUESS) {
+                rows_load(rh, xh, lane, t, same);
+                rows_load(ry, xy, lane, t, before);
+            }
             rows_load(ru, xu, lane, t, same);
         };
         auto put = [&](int t) {
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                *ring_slot(s.rec, 0, lane, t + 4 * j) = xh[j];
-                *ring_slot(s.rec, DH, lane, t + 4 * j) = xy[j];
+                if constexpr (!GUESS) {
+                    *ring_slot(s.rec, 0, lane, t + 4 * j) = xh[j];
+                    *ring_slot(s.rec, DH, lane, t + 4 * j) = xy[j];
+                }
 #pragma unroll
                 for (int i = 0; i < kWaveIters; ++i) *ring_slot(s.rec, kWavePer * i + 2 * DH, lane, t + 4 * j + i) = xu[j] * kTanhScale;
             }
@@ -1234,7 +1366,8 @@ __device__ __forceinline__ void wavefront_block(const DenseArgs &a, int b, int K
         bring(0);
         put(0);
         // y in front of the sequence's first row: W h0, the same for every iteration
-        if (q.first == 0) s.rec[0][DH + lane] = a.h0 ? a.r[(size_t)b * DH + lane] : 0.0f;
+        if (!GUESS && q.first == 0) s.rec[0][DH + lane] = a.h0 ? a.r[(size_t)b * DH + lane] : 0.0f;
+        if constexpr (GUESS) lds_barrier();
         lds_barrier();
         for (int g = 0; g < n_groups; ++g) {
             const int t0 = g * kWaveGroup;
@@ -1294,7 +1427,9 @@ __device__ __forceinline__ void wavefront_block(const DenseArgs &a, int b, int K
             // delta is written; the (at least three) LDS instructions of hand_on may be on their way still
             asm volatile("s_waitcnt lgkmcnt(3)\n\ts_barrier" ::: "memory");
         };
+        if constexpr (GUESS) lds_barrier();
         lds_barrier();
+        __builtin_amdgcn_s_setprio(3);
         hand_on(s.rec[0], 0.0f, 0.0f);
         int g = 0;
         if (enters) {
@@ -1318,6 +1453,7 @@ __device__ __forceinline__ void wavefront_block(const DenseArgs &a, int b, int K
                 group(std::integral_constant<int, 1>{});
             }
         }
+        __builtin_amdgcn_s_setprio(0);
         lds_barrier();
         if (it < K) atomicMax(&s.m[it], __float_as_uint(mymax) & 0x7fffffffu);
     }
@@ -1335,17 +1471,21 @@ __device__ __forceinline__ void load_w_wave(const float *W, float (&wr)[16])
     }
 }
 
-// The first block of iterations, one workgroup per stretch of a sequence.
-__global__ __launch_bounds__(320) void dense_stretch_kernel(const DenseArgs a, const DenseStretch c)
+// The first block of iterations, one workgroup per stretch of a sequence.  Also clears the control block and the maxima gm.
+__global__ __launch_bounds__(wave_threads(true)) void dense_stretch_kernel(const DenseArgs a, unsigned int *gm, const DenseStretch c)
 {
     __shared__ WaveLds s;
+    if (blockIdx.x == 0) {
+        if (threadIdx.x < 64) reinterpret_cast<unsigned int *>(a.ctrl)[threadIdx.x] = 0u;
+        for (int i = threadIdx.x; i < a.max_iter; i += wave_threads(true)) gm[i] = 0u;
+    }
     const int b = (int)blockIdx.x / c.n, j = (int)blockIdx.x - b * c.n, K = min(kWaveIters, a.max_iter);
     const size_t seq = (size_t)b * a.L * DH;
     float wr[16];
     load_w_wave(a.W, wr);
     const int start = j * c.len;
-    const WaveRows q = {c.h0it + seq, a.d + seq, a.h + seq, c.y + seq, max(start - kWarm, 0), start, min(start + c.len, a.L)};
-    wavefront_block<kStretch>(a, b, K, q, wr, s, c.edge + (size_t)blockIdx.x * 2 * kWaveIters * DH);
+    const WaveRows q = {a.h + seq, a.d + seq, max(start - kWarm, 0), start, min(start + c.len, a.L)};
+    wavefront_block<kStretch, true, true>(a, b, K, q, wr, s, c.edge + (size_t)blockIdx.x * 2 * kWaveIters * DH);
     __syncthreads();
     if (threadIdx.x < kWaveIters) c.top[(size_t)blockIdx.x * kWaveIters + threadIdx.x] = s.m[threadIdx.x];
 }
@@ -1356,7 +1496,7 @@ __global__ __launch_bounds__(320) void dense_stretch_kernel(const DenseArgs a, c
 // After dense_stretch_kernel it goes on behind the first block, or solves that again from the first border on where the updates
 // differ.  CUT: there were stretches.
 template <bool CUT>
-__global__ __launch_bounds__(320) void dense_wavefront_kernel(const DenseArgs a, unsigned int *gm, const DenseStretch c)
+__global__ __launch_bounds__(wave_threads(CUT)) void dense_wavefront_kernel(const DenseArgs a, unsigned int *gm, const DenseStretch c)
 {
     __shared__ WaveLds s;
     __shared__ int s_held;
@@ -1370,15 +1510,15 @@ __global__ __launch_bounds__(320) void dense_wavefront_kernel(const DenseArgs a,
         }
         return met;
     };
-    constexpr int kTops = (kStretches * kWaveIters + 319) / 320;
-    unsigned int top[kTops];                               // of stretch (threadIdx.x + 320 j) / kWaveIters
+    constexpr int kThreads = wave_threads(CUT), kTops = (kStretches * kWaveIters + kThreads - 1) / kThreads;
+    unsigned int top[kTops];                               // of stretch (threadIdx.x + kThreads j) / kWaveIters
     int held = 0;                                          // stretches that are as they have to be
     if constexpr (CUT) {
         if (threadIdx.x == 0) s_held = c.n;
         if (threadIdx.x < kWaveIters) s.m[threadIdx.x] = 0u;
 #pragma unroll
         for (int j = 0; j < kTops; ++j) {
-            const int i = (int)threadIdx.x + 320 * j;
+            const int i = (int)threadIdx.x + kThreads * j;
             top[j] = i < c.n * kWaveIters ? c.top[(size_t)b * c.n * kWaveIters + i] : 0u;
         }
         lds_barrier();                                     // the loads stay on their way
@@ -1390,11 +1530,11 @@ __global__ __launch_bounds__(320) void dense_wavefront_kernel(const DenseArgs a,
         const f4v *edge = reinterpret_cast<const f4v *>(c.edge) + (size_t)b * c.n * 2 * kQuads;
         const f4v *state = reinterpret_cast<const f4v *>(a.h + seq);
         const int K = min(kWaveIters, a.max_iter);
-        for (int e0 = w; e0 < c.n - 1; e0 += kBatch * 5) {
+        for (int e0 = w; e0 < c.n - 1; e0 += kBatch * kWaves) {
             f4v there[kBatch], here[kBatch], hq[kBatch];
 #pragma unroll
             for (int j = 0; j < kBatch; ++j) {
-                const int e = min(e0 + 5 * j, c.n - 2);
+                const int e = min(e0 + kWaves * j, c.n - 2);
                 const f4v *at = edge + (size_t)e * 2 * kQuads + lane;
                 there[j] = at[kQuads];
                 here[j] = at[2 * kQuads];
@@ -1410,7 +1550,7 @@ __global__ __launch_bounds__(320) void dense_wavefront_kernel(const DenseArgs a,
                 if (lane >= K * (DH / 4)) continue;
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
-                    if (!(fabsf(there[j][v] - here[j][v]) <= bound)) atomicMin(&s_held, min(e0 + 5 * j, c.n - 2) + 1);
+                    if (!(fabsf(there[j][v] - here[j][v]) <= bound)) atomicMin(&s_held, min(e0 + kWaves * j, c.n - 2) + 1);
             }
         }
         __syncthreads();
@@ -1418,22 +1558,23 @@ __global__ __launch_bounds__(320) void dense_wavefront_kernel(const DenseArgs a,
     }
     float wr[16];
     if (!CUT || held < c.n) load_w_wave(a.W, wr);
-    float *y = CUT ? c.y : a.d;
     for (int k0 = 0; k0 < a.max_iter; k0 += kWaveIters) {
         const int K = min(kWaveIters, a.max_iter - k0);
         if (!CUT || k0 > 0 || held < c.n) {
             const bool rest = CUT && k0 == 0;              // of the first block
             const int first = rest ? held * c.len : 0;
-            const WaveRows q = {(rest ? c.h0it : a.h) + seq, (rest ? a.d : y) + seq, a.h + seq, y + seq, first, first, a.L};
+            const WaveRows q = {a.h + seq, a.d + seq, first, first, a.L};
             if (CUT && k0 == kWaveIters && held == c.n) load_w_wave(a.W, wr);
-            wavefront_block<CUT ? kRest : kWhole>(a, b, K, q, wr, s, rest ? c.edge + ((size_t)(b * c.n + held - 1) * 2 + 1) * kWaveIters * DH : nullptr);
+            float *enters = rest ? c.edge + ((size_t)(b * c.n + held - 1) * 2 + 1) * kWaveIters * DH : nullptr;
+            if (CUT && k0 == 0) wavefront_block<kRest, CUT, CUT>(a, b, K, q, wr, s, enters);
+            else wavefront_block<kWhole, CUT, false>(a, b, K, q, wr, s, nullptr);
             __threadfence();                               // the next block reads the rows that this one wrote
             __syncthreads();
         }
         if (CUT && k0 == 0) {
 #pragma unroll
             for (int j = 0; j < kTops; ++j) {
-                const int i = (int)threadIdx.x + 320 * j;
+                const int i = (int)threadIdx.x + kThreads * j;
                 if (i < held * kWaveIters) atomicMax(&s.m[i & (kWaveIters - 1)], top[j]);
             }
             __syncthreads();
@@ -1460,7 +1601,8 @@ __global__ __launch_bounds__(320) void dense_wavefront_kernel(const DenseArgs a,
     }
 }
 
-// Backward by substitution: mu_l = d_l (W^T mu_{l+1} + g_l), one workgroup per sequence; row factors d in a.d.
+// Backward by substitution: mu_l = d_l (W^T mu_{l+1} + g_l), one workgroup per sequence.  The row factors
+// d_l = 1 - tanh^2(W h_{l-1} + u_l) at the given states are the helpers' work (HELP) or in a.d.
 // A single column leaves the matrix instruction's other three idle, and sixteen vector FMAs per lane (68 cycles)
 // are quicker than sixteen of it (150): wave w owns rows 16 w .. + 15, lane group q the terms 16 q .. + 15 of their
 // sums, which two lane-row swaps complete.  mu reaches the FMAs one value per lane, broadcast inside the lane row by
@@ -1471,8 +1613,8 @@ __global__ __launch_bounds__(320) void dense_wavefront_kernel(const DenseArgs a,
 // starts kWarm rows early from mu = 0 and leaves mu at the row behind its own last one in `edge`.  Otherwise one workgroup
 // per sequence; after the stretches it does nothing where these agree, relative to the largest of the 64 values, and runs
 // on from the last border where they do not.
-template <bool STRETCH>
-__global__ __launch_bounds__(320) void dense_adjoint_kernel(const DenseArgs a, float *dh0, const DenseStretch c)
+template <bool STRETCH, bool HELP>
+__global__ __launch_bounds__(wave_threads(HELP)) void dense_adjoint_kernel(const DenseArgs a, float *dh0, const DenseStretch c)
 {
     // step t of the recurrence is row last - t; its record holds d and d g, and mu is in the slot of the same number
     __shared__ __attribute__((aligned(16))) float s_rec[kRing][2 * DH], s_mu[kRing][DH];
@@ -1489,7 +1631,7 @@ __global__ __launch_bounds__(320) void dense_adjoint_kernel(const DenseArgs a, f
             __shared__ int s_apart;
             if (threadIdx.x == 0) s_apart = 0;
             __syncthreads();
-            for (int e = 1 + w; e < c.n; e += 5) {         // a wave looks at the 64 values between two stretches
+            for (int e = 1 + w; e < c.n; e += wave_threads(HELP) / kWave) {   // a wave looks at the 64 values between two stretches
                 const float there = a.du[((size_t)b * a.L + (size_t)e * c.len) * DH + lane], here = c.edge[((size_t)b * c.n + e - 1) * DH + lane];
                 const float top = __uint_as_float(wave_max_u32(__float_as_uint(there) & 0x7fffffffu));
                 if (!(fabsf(there - here) <= kWarmTol * top)) atomicMax(&s_apart, e);
@@ -1507,16 +1649,101 @@ __global__ __launch_bounds__(320) void dense_adjoint_kernel(const DenseArgs a, f
 #pragma unroll
     for (int i = 0; i < 16; ++i) wr[i] = a.W[(16 * q + i) * DH + row];
     const int n_groups = (L + kWaveGroup - 1) / kWaveGroup;
-    if (w == 4) {
+    if (HELP && w >= kHelpers) {
+        // lane (n = lane % 16, g = lane / 16) has channels 16 hw + 4 g .. + 3 of step n of two groups
+        const int hw = w - kHelpers, n = lane & 15, g = lane >> 4, chn = 16 * hw + 4 * g;
+        const buf_rsrc ru = seq_rsrc(a.u + (size_t)b * a.L * DH, seq_bytes), rh = seq_rsrc(a.h + (size_t)b * a.L * DH, seq_bytes),
+                       rg = seq_rsrc(a.g + (size_t)b * a.L * DH, seq_bytes);
+        float wa[4][4];
+        load_w_operand16(a.W, hw, n, g, wa);
+        auto load = [](buf_rsrc r, int row, int channel) {      // rows outside the sequence read zero
+            return __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(r, (unsigned int)row * (DH * 4u) + 4u * channel, 0, 0));
+        };
+        f4v xh[4], xu, xg, nh[4], nu, ng;                  // of the steps that are worked on, and of those after them
+        HelperSums y;
+        auto bring = [&](int t) {
+            const int l = rev(t);
+            nu = load(ru, l, chn);
+            ng = load(rg, l, chn);
+#pragma unroll
+            for (int ww = 0; ww < 4; ++ww) nh[ww] = load(rh, l - 1, 16 * ww + 4 * g);
+            if (l == 0 && a.h0) {
+#pragma unroll
+                for (int ww = 0; ww < 4; ++ww) nh[ww] = *reinterpret_cast<const f4v *>(a.h0 + (size_t)b * DH + 16 * ww + 4 * g);
+            }
+        };
+        auto next = [&]() {
+            xu = nu; xg = ng;
+#pragma unroll
+            for (int ww = 0; ww < 4; ++ww) xh[ww] = nh[ww];
+        };
+        f4v d, dg;
+        auto finish = [&]() {
+            const f4v p = y.acc0 + y.acc1 + xu;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float F = fast_tanh(p[v]);
+                d[v] = fmaf(-F, F, 1.0f);
+            }
+            dg = d * xg;
+        };
+        auto put = [&](int t) {                            // the last readers of these records are done
+            float *rec = s_rec[t & (kRing - 1)];
+            *reinterpret_cast<f4v *>(rec + chn) = d;
+            *reinterpret_cast<f4v *>(rec + DH + chn) = dg;
+        };
+        // as guess_rows: two groups of steps at a time
+        bring(n);
+        next();
+        bring(2 * kWaveGroup + n);
+        helper_products(0, 16, wa, xh, y);
+        finish();
+        put(n);
+        helper_barrier();
+        next();
+        bring(4 * kWaveGroup + n);
+#pragma unroll
+        for (int j = 0; j < kWaveGroup; ++j) {
+            helper_products(2 * j, 2 * j + 2, wa, xh, y);
+            helper_barrier();
+        }
+        for (int i = 1; i < n_groups; i += 2) {
+            const int t = (i + 1) * kWaveGroup;            // of the two groups behind this one
+            finish();
+            if (n < kWaveGroup) put(t + n);
+            next();
+            helper_barrier();
+            bring(t + 4 * kWaveGroup + n);
+            helper_barrier();
+#pragma unroll
+            for (int j = 2; j < kWaveGroup; ++j) {
+                helper_products_at(j, wa, xh, y);
+                helper_barrier();
+            }
+            if (i + 1 == n_groups) break;
+            if (n >= kWaveGroup) put(t + n);
+#pragma unroll
+            for (int j = kWaveGroup; j < 2 * kWaveGroup; ++j) {
+                helper_products_at(j, wa, xh, y);
+                helper_barrier();
+            }
+        }
+        return;
+    }
+    if (w == kMover) {
         const buf_rsrc rd = seq_rsrc(a.d + (size_t)b * a.L * DH, seq_bytes), rg = seq_rsrc(a.g + (size_t)b * a.L * DH, seq_bytes),
                        ro = seq_rsrc(a.du + (size_t)b * a.L * DH, (unsigned int)end * (DH * 4u));   // rows behind the own ones are not stored
         f4v xd[2], xg[2], xm[2];
-        auto bring = [&](int t) { rows_load(rd, xd, lane, t, rev); rows_load(rg, xg, lane, t, rev); };
+        auto bring = [&](int t) {
+            if constexpr (!HELP) { rows_load(rd, xd, lane, t, rev); rows_load(rg, xg, lane, t, rev); }
+        };
         auto put = [&](int t) {
+            if constexpr (!HELP) {
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                *ring_slot(s_rec, 0, lane, t + 4 * j) = xd[j];
-                *ring_slot(s_rec, DH, lane, t + 4 * j) = xd[j] * xg[j];
+                for (int j = 0; j < 2; ++j) {
+                    *ring_slot(s_rec, 0, lane, t + 4 * j) = xd[j];
+                    *ring_slot(s_rec, DH, lane, t + 4 * j) = xd[j] * xg[j];
+                }
             }
         };
         auto take = [&](int t) {
@@ -1570,6 +1797,7 @@ __global__ __launch_bounds__(320) void dense_adjoint_kernel(const DenseArgs a, f
         return swap16_add(t, t);
     };
     lds_barrier();
+    __builtin_amdgcn_s_setprio(3);
     float d = s_rec[0][row], dg = s_rec[0][DH + row];
     for (int g = 0; g < n_groups; ++g) {
         const int s0 = (g * kWaveGroup) & (kRing - 1), s1 = (s0 + kWaveGroup) & (kRing - 1);
@@ -1609,12 +1837,12 @@ __global__ __launch_bounds__(320) void dense_adjoint_kernel(const DenseArgs a, f
 //
 //            forward              backward
 //   1 x 200   53 /  37 /  64       47 / 32 /  55     not taken
-//   1 x 300   74 /  37 /  85       62 / 33 /  71
-//   6 x 523  121 /  38 / 134       98 / 35 / 108
-//   16 x 600 142 /  46 / 163      115 / 44 / 129
-//   64 x 272  80 /  53 / 105       70 / 51 /  88     not taken
-//   64 x 1024 242 / 97 / 273      200 / 96 / 223
-//   16 x 1000 227 / 52 / 246      145 / 49 / 191     backward not taken: chunk products
+//   1 x 300   74 /  36 /  85       62 / 30 /  71
+//   6 x 523  121 /  36 / 134       98 / 32 / 108
+//   16 x 600 142 /  40 / 160      115 / 36 / 128
+//   64 x 272  80 /  53 / 105       67 / 51 /  88     not taken
+//   64 x 1024 242 / 88 / 268      200 / 82 / 215
+//   16 x 1000 227 / 45 / 242      144 / 49 / 191     backward not taken: chunk products
 DenseStretch dense_stretches(int B, int L, double step, double products)
 {
     DenseStretch c;
@@ -1835,13 +2063,17 @@ int dense_backward(int dtype, const float *W, const void *u, const void *h0, con
     a.B = B; a.L = L; a.n_c = lo.n_c;
     DenseStretch c = wavefront_plan(B, L, true);
     if (c.n > 0) {
-        const size_t items = ((size_t)B * L + 15) / 16, most = (size_t)device_cu_count() * 8;
         a.W = W;
-        hipLaunchKernelGGL(dense_residual_kernel, dim3((unsigned)(items < most ? items : most)), dim3(256), 0, st, a, 5);
         // what the stretches leave lies where the chunk products would: 256 bytes of each, and they take 16 KB per 16 steps
         c.edge = a.Ac;
-        if (c.n > 1) hipLaunchKernelGGL(dense_adjoint_kernel<true>, dim3(B * c.n), dim3(320), 0, st, a, static_cast<float *>(dh0), c);
-        hipLaunchKernelGGL(dense_adjoint_kernel<false>, dim3(B), dim3(320), 0, st, a, static_cast<float *>(dh0), c);
+        if (B > kHelperUnits) {
+            const size_t items = ((size_t)B * L + 15) / 16, most = (size_t)device_cu_count() * 8;
+            hipLaunchKernelGGL(dense_residual_kernel, dim3((unsigned)(items < most ? items : most)), dim3(256), 0, st, a, 5);
+            hipLaunchKernelGGL((dense_adjoint_kernel<false, false>), dim3(B), dim3(wave_threads(false)), 0, st, a, static_cast<float *>(dh0), c);
+        } else {
+            if (c.n > 1) hipLaunchKernelGGL((dense_adjoint_kernel<true, true>), dim3(B * c.n), dim3(wave_threads(true)), 0, st, a, static_cast<float *>(dh0), c);
+            hipLaunchKernelGGL((dense_adjoint_kernel<false, true>), dim3(B), dim3(wave_threads(true)), 0, st, a, static_cast<float *>(dh0), c);
+        }
         return dense_weight_gradient(a, part, dW, st);
     }
     if (launch_reset(a.ctrl, nullptr, 0, nullptr, 0, st) != hipSuccess) return PARARNN_HIP_ERROR;
@@ -1943,25 +2175,18 @@ int dense_forward(int dtype, const float *W, const void *u, const void *h0, int 
     if (g_dense_products == 0 && max_iter > 0 && max_iter <= DH * DH && c.n > 0) {
         unsigned int *gm = reinterpret_cast<unsigned int *>(ws + lo.off_A);
         if (tol >= 0.0f && tol < kWarmTol) { c.n = 1; c.len = L; }
-        DenseArgs guess = a;
         if (c.n > 1) {
-            // behind the maxima: two more sets of rows and what the stretches leave, 2.06 KB for each of at least 32 steps;
-            // chunk products would take 1 KB per step
-            const size_t rows = (size_t)B * L * DH;
-            float *more = reinterpret_cast<float *>(gm) + DH * DH;
-            c.h0it = more;
-            c.y = c.h0it + rows;
-            c.edge = c.y + rows;
+            // behind the maxima what the stretches leave, 2.06 KB for each of at least 32 steps; chunk products would take 1 KB per step
+            c.edge = reinterpret_cast<float *>(gm) + DH * DH;
             c.top = reinterpret_cast<unsigned int *>(c.edge + (size_t)B * c.n * 2 * kWaveIters * DH);
             if (reinterpret_cast<char *>(c.top + (size_t)B * c.n * kWaveIters) > ws + lo.off_b) { c.n = 1; c.len = L; }
-            else guess.h = c.h0it;
         }
-        hipLaunchKernelGGL(dense_guess_kernel, dim3(res_blocks), dim3(256), 0, st, guess, gm, max_iter);
         if (c.n > 1) {
-            hipLaunchKernelGGL(dense_stretch_kernel, dim3(B * c.n), dim3(320), 0, st, a, c);
-            hipLaunchKernelGGL(dense_wavefront_kernel<true>, dim3(B), dim3(320), 0, st, a, gm, c);
+            hipLaunchKernelGGL(dense_stretch_kernel, dim3(B * c.n), dim3(wave_threads(true)), 0, st, a, gm, c);
+            hipLaunchKernelGGL(dense_wavefront_kernel<true>, dim3(B), dim3(wave_threads(true)), 0, st, a, gm, c);
         } else {
-            hipLaunchKernelGGL(dense_wavefront_kernel<false>, dim3(B), dim3(320), 0, st, a, gm, c);
+            hipLaunchKernelGGL(dense_guess_kernel, dim3(res_blocks), dim3(256), 0, st, a, gm, max_iter);
+            hipLaunchKernelGGL(dense_wavefront_kernel<false>, dim3(B), dim3(wave_threads(false)), 0, st, a, gm, c);
         }
         return hipGetLastError() == hipSuccess ? PARARNN_OK : PARARNN_HIP_ERROR;
     }

@@ -169,3 +169,23 @@ def test_stretches_are_repaired_from_where_they_differ(B, L):
         # relative to the largest of 64 values where it enters, and |W^T D| <= 0.95
         assert float((du - du_[:B]).abs().max()) <= 1e-6 * float(du_.abs().max())
         assert float((dh0 - dh0_[:B]).abs().max()) <= 1e-6 * float(du_.abs().max())
+
+
+@pytest.mark.parametrize("L", [1, 7, 8, 9, 16, 17, 25, 40, 301, 311, 312, 313, 328])
+def test_rows_that_helpers_make_ahead_of_the_chain(L):
+    """The initial guess and the row factors, made two groups of eight steps at a time, for chains that end anywhere in
+    them: against a batch that has both from launches of their own.  The bound of the other tests here: a rounding of the
+    updates where stretches meet; the row factors differ by a unit of the last place."""
+    import paper_2510_21450_amd as P
+    B = 3
+    W, u, h0, g = problem(B, L, 0.8, 1.0, 7 * L + 1, h0=L % 2 == 1)
+    many = lambda t: None if t is None else t.repeat(90, *[1] * (t.dim() - 1))
+    for n in (2, 4, 5):
+        h, _, _ = P.forward("tanh_dense", W, u, h0, tol=-1.0, max_iter=n)
+        H_, _, _ = P.forward("tanh_dense", W, many(u), many(h0), tol=-1.0, max_iter=n)
+        assert (h - H_[:B]).abs().max() <= 1e-6, n
+    got = P.backward("tanh_dense", W, u, h0, h, g, want_dh0=True)
+    want = P.backward("tanh_dense", W, many(u), many(h0), many(h), many(g), want_dh0=True)
+    assert (got[0] - want[0][:B]).abs().max() <= 1e-6 * want[0].abs().max()
+    if h0 is not None:
+        assert (got[2] - want[2][:B]).abs().max() <= 1e-6 * want[2].abs().max()
