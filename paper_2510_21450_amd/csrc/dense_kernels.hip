@@ -1124,13 +1124,17 @@ template <class F> __device__ __forceinline__ void rows_load(buf_rsrc r, f4v (&x
         x[j] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(
                    r, (unsigned int)row_of(t + 4 * j + (lane >> 4)) * (DH * 4u) + 16u * (lane & 15), 0, 0));
 }
-template <class F> __device__ __forceinline__ void rows_store(buf_rsrc r, const f4v (&x)[2], int lane, int t, F row_of)
+// THROUGH: to memory, past the L2, for other workgroups of the launch.
+constexpr int kThrough = 16;              // cache policy of such a buffer store: device scope
+template <bool THROUGH, class F> __device__ __forceinline__ void rows_store(buf_rsrc r, const f4v (&x)[2], int lane, int t, F row_of)
 {
 #pragma unroll
     for (int j = 0; j < 2; ++j)
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4v, x[j]), r,
-                                               (unsigned int)row_of(t + 4 * j + (lane >> 4)) * (DH * 4u) + 16u * (lane & 15), 0, 0);
+                                               (unsigned int)row_of(t + 4 * j + (lane >> 4)) * (DH * 4u) + 16u * (lane & 15), 0, THROUGH ? kThrough : 0);
 }
+__device__ __forceinline__ void store_through(float *p, float x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void store_through(unsigned int *p, unsigned int x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 // The same rows in a ring of kRing records of N floats each: the row at float `at` of the records of steps t .. t + 3.
 template <int N> __device__ __forceinline__ f4v *ring_slot(float (*ring)[N], int at, int lane, int t)
 {
@@ -1144,7 +1148,7 @@ template <int N> __device__ __forceinline__ f4v *ring_slot(float (*ring)[N], int
 // has is looked at: every stretch leaves the updates it reached at the step before its own first one, and at its last;
 // where the two that belong together differ by more than kWarmTol (eight units of the last place; ten from the second iteration on) times the largest of the 64
 // states at that step, at most 1, or by more than the tolerance of the solve, in any iteration and row, the stretch and all
-// behind it are solved again as one chain, from the updates that the stretch before it ended with: kWarm steps and a launch
+// behind it are solved again as one chain, from the updates that the stretch before it ended with: kWarm steps
 // more than one chain from the first step on.  Where they agree the states are those of one chain but for a rounding at a
 // few steps.  The benchmark's W (0.8 N(0, 1/64)) agrees to 2e-7
 // after 24-26 steps with u ~ N(0, 1), 52-64 with u a tenth to a third of that; 1.2 N(0, 1/64) after 50-61.
@@ -1164,7 +1168,46 @@ struct DenseStretch {
     int n, len;                       // stretches of a sequence (1: none, the whole sequence at once), steps of each but the last
     float *edge;                      // [B][n][2][kWaveIters][64] updates at the step before the first one and at the last one
     unsigned int *top;                // [B][n][kWaveIters] max |delta|
+    unsigned long long *flag;         // [B][n] the call's nonce, once what a stretch leaves is in memory
+    unsigned long long nonce;
+    unsigned int spin_limit;          // polls of a flag before its reader gives up
 };
+
+// The workgroup of a sequence's last stretch looks at the borders when all stretches have ended, in the same launch.  It waits
+// for workgroups before its own only, which wait for nobody but such ones: workgroups start in their order, so every wait ends on
+// whatever part of the device the launch gets.  A flag is the nonce of the call: nothing has to be cleared in front, but in a
+// captured launch, which replays its nonce.  Whatever others may read goes to memory past the L2 as it is stored: a fence in front
+// of the flag writes the L2 back, once for each workgroup, 1.2 us one after the other (40 us for 32 of them on each L2).
+// As a launch of its own the look took 6.2 us forward and 4.5 backward.  us of a call, with that launch / in one: forward
+// 64 x 1024 87.5 / 84.8, backward (with the terms of dL/dW) 82 / 70, training step 6 x 523 68.5 / 62.7.
+__device__ __forceinline__ void stretch_leaves(const DenseStretch &c)
+{
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // this wave's stores; behind the barrier, every wave's
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(c.flag + blockIdx.x, c.nonce, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// What the unit's L1 and the L2 hold of memory that others, or other waves of the workgroup, have written is dropped: once for
+// a workgroup, as every fence of a launch waits its turn (in every wave of 64 workgroups: 13 us more).
+__device__ __forceinline__ void own_rows_fresh()
+{
+    if (threadIdx.x < kWave) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    __syncthreads();
+}
+// By all threads of the workgroup of sequence b's last stretch: false where a wait ran out.  Workgroup 0 is waited for too.
+__device__ __forceinline__ bool stretches_left(const DenseStretch &c, int b)
+{
+    int there = 1;
+    if ((int)threadIdx.x < c.n) {
+        const unsigned long long *f = c.flag + (threadIdx.x == 0 ? 0 : b * c.n + (int)threadIdx.x - 1);
+        for (unsigned int polls = 0; __hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != c.nonce;) {
+            if (++polls >= c.spin_limit) { there = 0; break; }
+            __builtin_amdgcn_s_sleep(1);
+        }
+    }
+    there = __syncthreads_and(there);
+    own_rows_fresh();
+    return there != 0;
+}
 
 // The rows of a sequence that a block of iterations runs and leaves, and which: steps from `first` on are run, `start` to
 // `end` count.
@@ -1234,7 +1277,10 @@ __device__ __forceinline__ void guess_rows(const DenseArgs &a, int b, const Wave
         helper_products(0, 16, wa, x, y);
         c0 = y.acc0 + y.acc1;
     }
-    if (q.first == 0 && n == 0) *reinterpret_cast<f4v *>(a.r + (size_t)b * DH + chn) = c0;   // later blocks need it
+    if (q.first == 0 && n == 0) {                          // later blocks need it
+#pragma unroll
+        for (int v = 0; v < 4; ++v) store_through(a.r + (size_t)b * DH + chn + v, c0[v]);
+    }
     auto guess = [&]() {
 #pragma unroll
         for (int v = 0; v < 4; ++v) hv[v] = tanh_scaled(c0[v], kTanhScale * uv[v]);
@@ -1357,8 +1403,8 @@ __device__ __forceinline__ void wavefront_block(const DenseArgs &a, int b, int K
                 xh[j] = *ring_slot(s.rec, kWavePer * K, lane, t + 4 * j);
                 xy[j] = *ring_slot(s.rec, kWavePer * K + DH, lane, t + 4 * j);
             }
-            rows_store(oh, xh, lane, t - K, [&](int l) { return l - lead; });
-            rows_store(oy, xy, lane, t - K, [&](int l) { return q.first + l - 1 - y0; });
+            rows_store<EDGE>(oh, xh, lane, t - K, [&](int l) { return l - lead; });
+            rows_store<EDGE>(oy, xy, lane, t - K, [&](int l) { return q.first + l - 1 - y0; });
         };
 #pragma unroll
         for (int i = 1; i < kWaveIters; ++i)
@@ -1372,8 +1418,10 @@ __device__ __forceinline__ void wavefront_block(const DenseArgs &a, int b, int K
         for (int g = 0; g < n_groups; ++g) {
             const int t0 = g * kWaveGroup;
             lds_barrier();
+            // a load is waited for behind the stores in front of it: those of rows that go to memory come after
+            if constexpr (GUESS) bring(t0 + kWaveGroup);
             if (g > 0) take(t0 - kWaveGroup + 1);          // records t0 - 7 .. t0: complete with the first step of this group
-            bring(t0 + kWaveGroup);
+            if constexpr (!GUESS) bring(t0 + kWaveGroup);
 #pragma unroll 1
             for (int i = 1; i < kWaveGroup - 2; ++i) lds_barrier();
             put(t0 + kWaveGroup);                          // the group's last step reads the first of these records
@@ -1418,8 +1466,8 @@ __device__ __forceinline__ void wavefront_block(const DenseArgs &a, int b, int K
                 const int l = t - it;
                 if (l >= lead && l < L) mymax = nanmax(mymax, fabsf(delta));
                 if constexpr (EDGE) {
-                    if (l == lead - 1) my_edge[0] = delta;
-                    if (l == L - 1) my_edge[kWaveIters * DH] = delta;
+                    if (l == lead - 1) store_through(my_edge, delta);
+                    if (l == L - 1) store_through(my_edge + kWaveIters * DH, delta);
                 }
             } else if constexpr (kKind == 0) {
                 mymax = fmaxf(mymax, fabsf(delta));
@@ -1471,36 +1519,15 @@ __device__ __forceinline__ void load_w_wave(const float *W, float (&wr)[16])
     }
 }
 
-// The first block of iterations, one workgroup per stretch of a sequence.  Also clears the control block and the maxima gm.
-__global__ __launch_bounds__(wave_threads(true)) void dense_stretch_kernel(const DenseArgs a, unsigned int *gm, const DenseStretch c)
-{
-    __shared__ WaveLds s;
-    if (blockIdx.x == 0) {
-        if (threadIdx.x < 64) reinterpret_cast<unsigned int *>(a.ctrl)[threadIdx.x] = 0u;
-        for (int i = threadIdx.x; i < a.max_iter; i += wave_threads(true)) gm[i] = 0u;
-    }
-    const int b = (int)blockIdx.x / c.n, j = (int)blockIdx.x - b * c.n, K = min(kWaveIters, a.max_iter);
-    const size_t seq = (size_t)b * a.L * DH;
-    float wr[16];
-    load_w_wave(a.W, wr);
-    const int start = j * c.len;
-    const WaveRows q = {a.h + seq, a.d + seq, max(start - kWarm, 0), start, min(start + c.len, a.L)};
-    wavefront_block<kStretch, true, true>(a, b, K, q, wr, s, c.edge + (size_t)blockIdx.x * 2 * kWaveIters * DH);
-    __syncthreads();
-    if (threadIdx.x < kWaveIters) c.top[(size_t)blockIdx.x * kWaveIters + threadIdx.x] = s.m[threadIdx.x];
-}
-
-// One workgroup per sequence.  A sequence whose own update meets the tolerance at the end of a block is done:
+// The solve of sequence b by a workgroup.  A sequence whose own update meets the tolerance at the end of a block is done:
 // the blocks after it are run by the sequences that are not.  gm[k-1]: max |delta| of iteration k over the
 // sequences that ran it.  The last workgroup to finish reports the first iteration whose maximum met the tolerance.
-// After dense_stretch_kernel it goes on behind the first block, or solves that again from the first border on where the updates
-// differ.  CUT: there were stretches.
+// CUT: there were stretches; it goes on behind the first block, or solves that again from the first border on where the
+// updates differ.
 template <bool CUT>
-__global__ __launch_bounds__(wave_threads(CUT)) void dense_wavefront_kernel(const DenseArgs a, unsigned int *gm, const DenseStretch c)
+__device__ __forceinline__ void wavefront_sequence(const DenseArgs &a, unsigned int *gm, const DenseStretch &c, int b, WaveLds &s)
 {
-    __shared__ WaveLds s;
     __shared__ int s_held;
-    const int b = blockIdx.x;
     const size_t seq = (size_t)b * a.L * DH;
     auto ended = [&](int K) {                              // the maxima in s.m are of a whole block
         bool met = false;
@@ -1568,8 +1595,9 @@ __global__ __launch_bounds__(wave_threads(CUT)) void dense_wavefront_kernel(cons
             float *enters = rest ? c.edge + ((size_t)(b * c.n + held - 1) * 2 + 1) * kWaveIters * DH : nullptr;
             if (CUT && k0 == 0) wavefront_block<kRest, CUT, CUT>(a, b, K, q, wr, s, enters);
             else wavefront_block<kWhole, CUT, false>(a, b, K, q, wr, s, nullptr);
-            __threadfence();                               // the next block reads the rows that this one wrote
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the next block reads the rows that this one wrote
             __syncthreads();
+            own_rows_fresh();
         }
         if (CUT && k0 == 0) {
 #pragma unroll
@@ -1585,9 +1613,8 @@ __global__ __launch_bounds__(wave_threads(CUT)) void dense_wavefront_kernel(cons
         if (met) break;
     }
     if (threadIdx.x == 0) {
-        __threadfence();
-        if (atomicAdd(&a.ctrl->done, 1u) == gridDim.x - 1) {
-            __threadfence();
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the maxima, which are this wave's
+        if (atomicAdd(&a.ctrl->done, 1u) == (unsigned int)a.B - 1) {
             int status = a.tol < 0.0f ? kStOk : kStNotConverged, k = 1;
             for (; k <= a.max_iter; ++k) {
                 const float mk = __uint_as_float(__hip_atomic_load(&gm[k - 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
@@ -1601,6 +1628,44 @@ __global__ __launch_bounds__(wave_threads(CUT)) void dense_wavefront_kernel(cons
     }
 }
 
+// One workgroup per sequence, which is not cut.
+__global__ __launch_bounds__(wave_threads(false)) void dense_wavefront_kernel(const DenseArgs a, unsigned int *gm)
+{
+    __shared__ WaveLds s;
+    const DenseStretch c = {};
+    wavefront_sequence<false>(a, gm, c, (int)blockIdx.x, s);
+}
+
+// One workgroup per stretch of a sequence for the first block of iterations; the last one's goes on with the sequence.
+// Also clears the control block and the maxima gm.
+__global__ __launch_bounds__(wave_threads(true)) void dense_stretch_kernel(const DenseArgs a, unsigned int *gm, const DenseStretch c)
+{
+    __shared__ WaveLds s;
+    if (blockIdx.x == 0) {
+        if (threadIdx.x < 64) store_through(reinterpret_cast<unsigned int *>(a.ctrl) + threadIdx.x, 0u);
+        for (int i = threadIdx.x; i < a.max_iter; i += wave_threads(true)) store_through(gm + i, 0u);
+    }
+    const int b = (int)blockIdx.x / c.n, j = (int)blockIdx.x - b * c.n, K = min(kWaveIters, a.max_iter);
+    const size_t seq = (size_t)b * a.L * DH;
+    {
+        float wr[16];
+        load_w_wave(a.W, wr);
+        const int start = j * c.len;
+        const WaveRows q = {a.h + seq, a.d + seq, max(start - kWarm, 0), start, min(start + c.len, a.L)};
+        wavefront_block<kStretch, true, true>(a, b, K, q, wr, s, c.edge + (size_t)blockIdx.x * 2 * kWaveIters * DH);
+    }
+    __syncthreads();
+    if (threadIdx.x < kWaveIters) store_through(c.top + (size_t)blockIdx.x * kWaveIters + threadIdx.x, s.m[threadIdx.x]);
+    stretch_leaves(c);
+    if (j != c.n - 1) return;
+    if (stretches_left(c, b)) {
+        wavefront_sequence<true>(a, gm, c, b, s);
+    } else if (threadIdx.x == 0) {
+        a.iters_out[0] = a.max_iter;
+        a.iters_out[1] = kStInternal;
+    }
+}
+
 // Backward by substitution: mu_l = d_l (W^T mu_{l+1} + g_l), one workgroup per sequence.  The row factors
 // d_l = 1 - tanh^2(W h_{l-1} + u_l) at the given states are the helpers' work (HELP) or in a.d.
 // A single column leaves the matrix instruction's other three idle, and sixteen vector FMAs per lane (68 cycles)
@@ -1610,39 +1675,20 @@ __global__ __launch_bounds__(wave_threads(CUT)) void dense_wavefront_kernel(cons
 // dL/dh0 = W^T mu_1.
 //
 // STRETCH: one workgroup per stretch of a sequence (DenseStretch: here from the last row down; what enters is one mu), which
-// starts kWarm rows early from mu = 0 and leaves mu at the row behind its own last one in `edge`.  Otherwise one workgroup
-// per sequence; after the stretches it does nothing where these agree, relative to the largest of the 64 values, and runs
-// on from the last border where they do not.
-template <bool STRETCH, bool HELP>
-__global__ __launch_bounds__(wave_threads(HELP)) void dense_adjoint_kernel(const DenseArgs a, float *dh0, const DenseStretch c)
-{
+// starts kWarm rows early from mu = 0 and leaves mu at the row behind its own last one in `edge`.  Otherwise a whole sequence, or
+// what is run again behind the last border at which its stretches differ: rows 0 .. end - 1, with `x` entering.
+struct AdjointLds {
     // step t of the recurrence is row last - t; its record holds d and d g, and mu is in the slot of the same number
-    __shared__ __attribute__((aligned(16))) float s_rec[kRing][2 * DH], s_mu[kRing][DH];
+    __attribute__((aligned(16))) float rec[kRing][2 * DH], mu[kRing][DH];
+};
+template <bool STRETCH, bool HELP>
+__device__ __forceinline__ void adjoint_chain(const DenseArgs &a, float *dh0, int b, int start, int end, float x, float *edge, AdjointLds &lds)
+{
+    auto &s_rec = lds.rec;
+    auto &s_mu = lds.mu;
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int q = lane >> 4, row = 16 * (w & 3) + (lane & 15);
-    const int b = STRETCH ? (int)blockIdx.x / c.n : (int)blockIdx.x, j = STRETCH ? (int)blockIdx.x - b * c.n : 0;
     const unsigned int seq_bytes = (unsigned int)a.L * (DH * 4u);
-    // rows start .. end - 1 are this workgroup's, the ones from `last` down are run, with `x` entering at that one
-    const int start = STRETCH ? j * c.len : 0;
-    int end = STRETCH ? min(start + c.len, a.L) : a.L;
-    float x = 0.0f;
-    if constexpr (!STRETCH) {
-        if (c.n > 1) {
-            __shared__ int s_apart;
-            if (threadIdx.x == 0) s_apart = 0;
-            __syncthreads();
-            for (int e = 1 + w; e < c.n; e += wave_threads(HELP) / kWave) {   // a wave looks at the 64 values between two stretches
-                const float there = a.du[((size_t)b * a.L + (size_t)e * c.len) * DH + lane], here = c.edge[((size_t)b * c.n + e - 1) * DH + lane];
-                const float top = __uint_as_float(wave_max_u32(__float_as_uint(there) & 0x7fffffffu));
-                if (!(fabsf(there - here) <= kWarmTol * top)) atomicMax(&s_apart, e);
-            }
-            __syncthreads();
-            const int e = __builtin_amdgcn_readfirstlane(s_apart);
-            if (e == 0) return;
-            end = e * c.len;
-            x = a.du[((size_t)b * a.L + end) * DH + lane];
-        }
-    }
     const int last = STRETCH ? min(end + kWarm, a.L) - 1 : end - 1, L = last + 1 - start, lead = last + 1 - end;
     auto rev = [last](int t) { return last - t; };
     float wr[16];                                          // W^T[row][16 q ..]
@@ -1749,7 +1795,7 @@ __global__ __launch_bounds__(wave_threads(HELP)) void dense_adjoint_kernel(const
         auto take = [&](int t) {
 #pragma unroll
             for (int j = 0; j < 2; ++j) xm[j] = *ring_slot(s_mu, 0, lane, t + 4 * j);
-            rows_store(ro, xm, lane, t, [&](int k) { return k < L ? last - k : -1; });
+            rows_store<STRETCH>(ro, xm, lane, t, [&](int k) { return k < L ? last - k : -1; });
         };
         bring(0);
         put(0);
@@ -1808,7 +1854,7 @@ __global__ __launch_bounds__(wave_threads(HELP)) void dense_adjoint_kernel(const
             const float mu = fmaf(d, sum(x), dg);
             mus[i * DH + row] = mu;                        // the four lane groups store the same value
             if constexpr (STRETCH) {
-                if (g * kWaveGroup + i == lead - 1 && q == 0) c.edge[(size_t)blockIdx.x * DH + row] = mu;
+                if (g * kWaveGroup + i == lead - 1 && q == 0) store_through(edge + row, mu);
             }
             __builtin_amdgcn_sched_barrier(0);
             const float *nr = i + 1 < kWaveGroup ? rec + 2 * (i + 1) * DH : rec_next;
@@ -1821,8 +1867,110 @@ __global__ __launch_bounds__(wave_threads(HELP)) void dense_adjoint_kernel(const
     }
     if (dh0 && start == 0) {
         const float s = sum(s_mu[(L - 1) & (kRing - 1)][lane]);
-        if (q == 0) dh0[(size_t)b * DH + row] = s;
+        if (q == 0) store_through(dh0 + (size_t)b * DH + row, s);
     }
+}
+
+// The terms that rows first .. end - 1 of sequence b add to dL/dW = sum mu_l h_{l-1}^T, in sums of `piece` rows (a multiple of 64, or all
+// of them), each a matrix of `out`.  By eight waves: each has a quarter of the matrix and every other batch of 32 rows, two at a
+// time on v_mfma_f32_32x32x2_f32; the rows of a batch travel while the one before is multiplied.  In the launch of the
+// stretches, where mu is at hand; as one of its own it took 6.6 us of a step of 6 x 523.
+__device__ __forceinline__ void stretch_weight_gradient(const DenseArgs &a, int b, int first, int end, int piece, float (&s_half)[4][16][kWave], float *out)
+{
+    constexpr int kPairs = 16, kSums = 4;                  // sums of a wave: in one, 128 rows of 256 added up one by one, 1.5 to 2 times the error
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int n = lane & 31, half = lane >> 5, mt = w & 1, nt = w >> 1 & 1, part = w >> 2;
+    // rows past the end, and the one in front of the sequence, read zero
+    const buf_rsrc rm = seq_rsrc(a.du + (size_t)b * a.L * DH, (unsigned int)end * (DH * 4u)),
+                   rh = seq_rsrc(a.h + (size_t)b * a.L * DH, (unsigned int)(end - 1) * (DH * 4u));
+    float m[kPairs], h[kPairs], mn[kPairs], hn[kPairs];
+    auto bring = [&](int r) {
+#pragma unroll
+        for (int i = 0; i < kPairs; ++i) {
+            const unsigned int at = (unsigned int)(r + 2 * i + half) * (DH * 4u) + 4u * n;
+            mn[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rm, at + 128u * mt, 0, 0));
+            hn[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rh, at - DH * 4u + 128u * nt, 0, 0));
+        }
+        if (r == 0 && half == 0 && a.h0) hn[0] = a.h0[(size_t)b * DH + 32 * nt + n];
+    };
+    int r = first + 2 * kPairs * part;
+    if (w < 8) bring(r);
+    for (int p = first; p < end; p += piece, out += DH * DH) {
+        f16v Qs[kSums], Q;
+#pragma unroll
+        for (int k = 0; k < kSums; ++k)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) Qs[k][v] = 0.0f;
+        if (w < 8) {
+            for (const int stop = min(p + piece, end); r < stop; r += 4 * kPairs) {
+#pragma unroll
+                for (int i = 0; i < kPairs; ++i) { m[i] = mn[i]; h[i] = hn[i]; }
+                bring(r + 4 * kPairs);
+#pragma unroll
+                for (int i = 0; i < kPairs; ++i) Qs[i % kSums] = __builtin_amdgcn_mfma_f32_32x32x2f32(m[i], h[i], Qs[i % kSums], 0, 0, 0);
+            }
+            Q = (Qs[0] + Qs[1]) + (Qs[2] + Qs[3]);
+            if (part == 1) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) s_half[w & 3][v][lane] = Q[v];
+            }
+        }
+        lds_barrier();
+        if (w < 4) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) store_through(out + (32 * mt + mfma_row(v, half)) * DH + 32 * nt + n, Q[v] + s_half[w][v][lane]);
+        }
+        lds_barrier();
+    }
+}
+
+// One workgroup per sequence, which is not cut.
+template <bool HELP>
+__global__ __launch_bounds__(wave_threads(HELP)) void dense_adjoint_kernel(const DenseArgs a, float *dh0)
+{
+    __shared__ AdjointLds s;
+    adjoint_chain<false, HELP>(a, dh0, (int)blockIdx.x, 0, a.L, 0.0f, nullptr, s);
+}
+
+// One workgroup per stretch; the one of a sequence's last stretch looks at the borders, where two mu may differ relative to the
+// largest of the 64 values there, and runs on from the last one at which they do.  part: a matrix of terms of dL/dW per stretch.
+// Those of rows that are run again are added up anew, in pieces of kAgain rows at least; the other ones are zero.
+constexpr int kAgain = 256;
+__global__ __launch_bounds__(wave_threads(true)) void dense_adjoint_stretch_kernel(const DenseArgs a, float *dh0, const DenseStretch c, float *part)
+{
+    __shared__ AdjointLds s;
+    __shared__ float s_half[4][16][kWave];
+    __shared__ int s_apart;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int b = (int)blockIdx.x / c.n, j = (int)blockIdx.x - b * c.n;
+    const int start = j * c.len, end = min(start + c.len, a.L);
+    float *mine = part + (size_t)b * c.n * DH * DH;        // of this sequence
+    auto written = [] {                                    // mu of these rows, for every wave
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+    };
+    if (threadIdx.x == 0) s_apart = 0;
+    adjoint_chain<true, true>(a, dh0, b, start, end, 0.0f, c.edge + (size_t)blockIdx.x * DH, s);
+    written();
+    stretch_weight_gradient(a, b, start, end, c.len, s_half, mine + (size_t)j * DH * DH);
+    stretch_leaves(c);
+    if (j != c.n - 1) return;
+    const bool left = stretches_left(c, b);
+    for (int e = 1 + w; e < c.n; e += kWaves) {            // a wave looks at the 64 values between two stretches
+        const float there = a.du[((size_t)b * a.L + (size_t)e * c.len) * DH + lane], here = c.edge[((size_t)b * c.n + e - 1) * DH + lane];
+        const float top = __uint_as_float(wave_max_u32(__float_as_uint(there) & 0x7fffffffu));
+        if (!(fabsf(there - here) <= kWarmTol * top)) atomicMax(&s_apart, e);
+    }
+    __syncthreads();
+    const int e = left ? __builtin_amdgcn_readfirstlane(s_apart) : c.n;      // a wait that ran out: the whole sequence
+    if (e == 0) return;
+    const int rows = min(e * c.len, a.L);
+    adjoint_chain<false, true>(a, dh0, b, 0, rows, e < c.n ? a.du[((size_t)b * a.L + rows) * DH + lane] : 0.0f, nullptr, s);
+    written();
+    own_rows_fresh();
+    const int piece = max((c.len + 63) & ~63, kAgain), n_pieces = (rows + piece - 1) / piece;
+    stretch_weight_gradient(a, b, 0, rows, piece, s_half, mine);
+    for (int k = n_pieces * DH * DH + threadIdx.x; k < e * DH * DH; k += wave_threads(true)) store_through(mine + k, 0.0f);
 }
 
 // Substitution or chunk products, and in how many stretches?  Nanoseconds, measured on config 4's shape and on 1 to 16
@@ -1837,12 +1985,14 @@ __global__ __launch_bounds__(wave_threads(HELP)) void dense_adjoint_kernel(const
 //
 //            forward              backward
 //   1 x 200   53 /  37 /  64       47 / 32 /  55     not taken
-//   1 x 300   74 /  36 /  85       62 / 30 /  71
-//   6 x 523  121 /  36 / 134       98 / 32 / 108
-//   16 x 600 142 /  40 / 160      115 / 36 / 128
+//   1 x 300   74 /  35 /  82       62 / 26 /  74
+//   6 x 523  121 /  36 / 132       98 / 28 / 120
+//   16 x 600 142 /  40 / 158      115 / 31 / 141
 //   64 x 272  80 /  53 / 105       67 / 51 /  88     not taken
-//   64 x 1024 242 / 88 / 268      200 / 82 / 215
-//   16 x 1000 227 / 45 / 242      144 / 49 / 191     backward not taken: chunk products
+//   64 x 1024 242 / 91 / 259      200 / 70 / 224
+//   16 x 1000 227 / 44 / 238      144 / 49 / 191     backward not taken: chunk products
+//
+// Lost, a backward pass also adds the terms of dL/dW up again, in one workgroup of a sequence (20 ns a row).
 DenseStretch dense_stretches(int B, int L, double step, double products)
 {
     DenseStretch c;
@@ -1853,10 +2003,18 @@ DenseStretch dense_stretches(int B, int L, double step, double products)
     const int len = (L + most - 1) / most > kWarmLeast ? (L + most - 1) / most : kWarmLeast;
     if (len >= L) return c;
     const double chain = step * L, without = chain < products ? chain : products;
-    const double warm = step * (kWarm + kWaveIters) + 3e3;                 // and the second launch
+    const double warm = step * (kWarm + kWaveIters) + 3e3;                 // and the look at the borders
     if (chain + warm - without > 0.5 * (without - step * len - warm)) return c;
     c.n = (L + len - 1) / len; c.len = len;
     return c;
+}
+
+// What the workgroups of stretches say to each other with; c.flag is where its words are.
+bool stretch_flags(DenseStretch &c, int B, Ctrl *ctrl, hipStream_t st)
+{
+    c.nonce = call_nonce();
+    c.spin_limit = settings().spin_limit;
+    return !stream_is_capturing(st) || launch_reset(ctrl, c.flag, (size_t)B * c.n, nullptr, 0, st) == hipSuccess;
 }
 
 // The stretches of a solve by substitution; n = 0 where chunk products are faster.
@@ -2064,15 +2222,21 @@ int dense_backward(int dtype, const float *W, const void *u, const void *h0, con
     DenseStretch c = wavefront_plan(B, L, true);
     if (c.n > 0) {
         a.W = W;
-        // what the stretches leave lies where the chunk products would: 256 bytes of each, and they take 16 KB per 16 steps
+        // what the stretches leave lies where the chunk products would: 264 bytes of each, and they take 16 KB per 16 steps
         c.edge = a.Ac;
         if (B > kHelperUnits) {
             const size_t items = ((size_t)B * L + 15) / 16, most = (size_t)device_cu_count() * 8;
             hipLaunchKernelGGL(dense_residual_kernel, dim3((unsigned)(items < most ? items : most)), dim3(256), 0, st, a, 5);
-            hipLaunchKernelGGL((dense_adjoint_kernel<false, false>), dim3(B), dim3(wave_threads(false)), 0, st, a, static_cast<float *>(dh0), c);
+            hipLaunchKernelGGL(dense_adjoint_kernel<false>, dim3(B), dim3(wave_threads(false)), 0, st, a, static_cast<float *>(dh0));
+        } else if (c.n > 1) {
+            // at most one matrix of terms per stretch, of which there are no more than waves that would share the rows
+            c.flag = reinterpret_cast<unsigned long long *>(c.edge + (size_t)B * c.n * DH);
+            if (B * c.n > dw_waves(B, L) || !stretch_flags(c, B, a.ctrl, st)) return PARARNN_HIP_ERROR;
+            hipLaunchKernelGGL(dense_adjoint_stretch_kernel, dim3(B * c.n), dim3(wave_threads(true)), 0, st, a, static_cast<float *>(dh0), c, part);
+            if (hipGetLastError() != hipSuccess) return PARARNN_HIP_ERROR;
+            return launch_param_reduce(part, dW, B * c.n, DH * DH, st) == hipSuccess ? PARARNN_OK : PARARNN_HIP_ERROR;
         } else {
-            if (c.n > 1) hipLaunchKernelGGL((dense_adjoint_kernel<true, true>), dim3(B * c.n), dim3(wave_threads(true)), 0, st, a, static_cast<float *>(dh0), c);
-            hipLaunchKernelGGL((dense_adjoint_kernel<false, true>), dim3(B), dim3(wave_threads(true)), 0, st, a, static_cast<float *>(dh0), c);
+            hipLaunchKernelGGL(dense_adjoint_kernel<true>, dim3(B), dim3(wave_threads(true)), 0, st, a, static_cast<float *>(dh0));
         }
         return dense_weight_gradient(a, part, dW, st);
     }
@@ -2176,17 +2340,18 @@ int dense_forward(int dtype, const float *W, const void *u, const void *h0, int 
         unsigned int *gm = reinterpret_cast<unsigned int *>(ws + lo.off_A);
         if (tol >= 0.0f && tol < kWarmTol) { c.n = 1; c.len = L; }
         if (c.n > 1) {
-            // behind the maxima what the stretches leave, 2.06 KB for each of at least 32 steps; chunk products would take 1 KB per step
+            // behind the maxima what the stretches leave, 2.07 KB for each of at least 32 steps; chunk products would take 1 KB per step
             c.edge = reinterpret_cast<float *>(gm) + DH * DH;
-            c.top = reinterpret_cast<unsigned int *>(c.edge + (size_t)B * c.n * 2 * kWaveIters * DH);
+            c.flag = reinterpret_cast<unsigned long long *>(c.edge + (size_t)B * c.n * 2 * kWaveIters * DH);
+            c.top = reinterpret_cast<unsigned int *>(c.flag + (size_t)B * c.n);
             if (reinterpret_cast<char *>(c.top + (size_t)B * c.n * kWaveIters) > ws + lo.off_b) { c.n = 1; c.len = L; }
         }
         if (c.n > 1) {
+            if (!stretch_flags(c, B, a.ctrl, st)) return PARARNN_HIP_ERROR;
             hipLaunchKernelGGL(dense_stretch_kernel, dim3(B * c.n), dim3(wave_threads(true)), 0, st, a, gm, c);
-            hipLaunchKernelGGL(dense_wavefront_kernel<true>, dim3(B), dim3(wave_threads(true)), 0, st, a, gm, c);
         } else {
             hipLaunchKernelGGL(dense_guess_kernel, dim3(res_blocks), dim3(256), 0, st, a, gm, max_iter);
-            hipLaunchKernelGGL(dense_wavefront_kernel<false>, dim3(B), dim3(wave_threads(false)), 0, st, a, gm, c);
+            hipLaunchKernelGGL(dense_wavefront_kernel, dim3(B), dim3(wave_threads(false)), 0, st, a, gm);
         }
         return hipGetLastError() == hipSuccess ? PARARNN_OK : PARARNN_HIP_ERROR;
     }

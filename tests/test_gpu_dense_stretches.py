@@ -189,3 +189,74 @@ def test_rows_that_helpers_make_ahead_of_the_chain(L):
     assert (got[0] - want[0][:B]).abs().max() <= 1e-6 * want[0].abs().max()
     if h0 is not None:
         assert (got[2] - want[2][:B]).abs().max() <= 1e-6 * want[2].abs().max()
+
+
+# stretches of 32 steps and more (at most 256 of all sequences), whole and short last ones; a gradient on the last step only, where
+# stretches are run again behind the last border, on all steps, and on the first half
+@pytest.mark.parametrize("B,L", [(1, 320), (1, 321), (3, 352), (2, 383), (16, 577), (60, 701), (64, 1024)])
+def test_weight_gradient_of_stretches(B, L):
+    """dL/dW against the sum in 64 bits over the same dL/du and states.  A sum of n rows in 32 bits, added up in runs of at most 32 and
+    then as partial sums: 2^-24 per addition of the largest partial sum, sqrt(additions) of them."""
+    import paper_2510_21450_amd as P
+    W, u, h0, g = problem(B, L, 0.8, 1.0, L + B, h0=L % 2 == 1)
+    h = P.forward("tanh_dense", W, u, h0, tol=1e-3, max_iter=32)[0]
+    front = torch.zeros(B, 1, H, device="cuda") if h0 is None else h0
+    before = torch.cat([front, h[:, :-1, 0]], 1).double().reshape(-1, H)
+    for seen in (slice(0, L), slice(L - 1, L), slice(0, L // 2)):
+        part = torch.zeros_like(g)
+        part[:, seen] = g[:, seen]
+        print(f"dW B={B} L={L} {seen}", flush=True)
+        du, dW, _ = P.backward("tanh_dense", W, u, h0, h, part)
+        mu = du.double().reshape(-1, H)
+        want, size = mu.T @ before, mu.abs().T @ before.abs()
+        bound = 2.0 ** -24 * (32 + (B * L / 32) ** 0.5) * size
+        assert bool(((dW.double().reshape(H, H) - want).abs() <= bound + 1e-30).all())
+
+
+def test_backward_of_stretches_in_a_graph():
+    import paper_2510_21450_amd as P
+    W, u, h0, g = problem(5, 400, 0.8, 1.0, 12)
+    h = P.forward("tanh_dense", W, u, h0, tol=1e-3, max_iter=16)[0]
+    last = torch.zeros_like(g)
+    last[:, -1] = g[:, -1]
+    grads = [g.clone(), last, g * 0.5, g.flip(0).contiguous()]
+    back = lambda: P.backward("tanh_dense", W, u, h0, h, g)
+    eager = []
+    for x in grads:
+        g.copy_(x)
+        eager.append([t.clone() for t in back()])
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        back()
+    torch.cuda.current_stream().wait_stream(side)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = back()
+    for x, want in zip(grads + grads, eager + eager):
+        g.copy_(x)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(out, want))
+        assert torch.equal(back()[0], want[0])
+
+
+def test_waits_for_stretches_are_bounded():
+    """With one poll the workgroup of a last stretch gives up on the others: the launch ends, the solve says so (or went through),
+    and the next call with the default limit is right."""
+    import paper_2510_21450_amd as P
+    W, u, h0, g = problem(6, 523, 0.8, 1.0, 13)
+    seen = set()
+    try:
+        P.set_spin_limit(1)
+        for _ in range(3):
+            h, it, _ = P.forward("tanh_dense", W, u, h0, tol=1e-3, max_iter=32)
+            P.backward("tanh_dense", W, u, h0, torch.zeros_like(h), g)
+            torch.cuda.synchronize()
+            seen.add(P.status_string(int(it.cpu()[1])))
+    finally:
+        P.set_spin_limit(0)
+    assert seen <= {"OK", "INTERNAL"}, seen
+    h, it, _ = P.forward("tanh_dense", W, u, h0, tol=1e-3, max_iter=32)
+    H_, it_, _ = P.forward("tanh_dense", W, whole(u, 6), whole(h0, 6), tol=1e-3, max_iter=32)
+    assert it.tolist() == it_.tolist() and (h - H_[:6]).abs().max() <= 1e-6
