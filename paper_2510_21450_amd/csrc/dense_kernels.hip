@@ -4,7 +4,7 @@
 // The linear solve of a Newton iteration is block bi-diagonal.  Two ways through it (wavefront_plan chooses):
 // forward substitution, all iterations of a block at once as a wavefront (dense_wavefront_kernel,
 // dense_adjoint_kernel: latency-bound, one workgroup per sequence, whole solves in two launches; sequences fewer than the
-// compute units are cut into stretches that run side by side, DenseStretch), and the chunked scan:
+// compute units are cut into stretches that run side by side, in one launch, DenseStretch), and the chunked scan:
 //
 // One Newton iteration (Alg. 1a) is four launches (chunk_products and the local sweep share one):
 //   residual  F_l = tanh(W h_{l-1} + u_l), d_l = 1 - F_l^2, r_l = F_l - h_l   (Eq. (3))

@@ -201,16 +201,16 @@ def test_weight_gradient_of_stretches(B, L):
     W, u, h0, g = problem(B, L, 0.8, 1.0, L + B, h0=L % 2 == 1)
     h = P.forward("tanh_dense", W, u, h0, tol=1e-3, max_iter=32)[0]
     front = torch.zeros(B, 1, H, device="cuda") if h0 is None else h0
-    before = torch.cat([front, h[:, :-1, 0]], 1).double().reshape(-1, H)
+    before = torch.cat([front, h[:, :-1, 0]], 1).double().reshape(-1, H).cpu()      # a product on the device leaves a workspace in torch's allocator
     for seen in (slice(0, L), slice(L - 1, L), slice(0, L // 2)):
         part = torch.zeros_like(g)
         part[:, seen] = g[:, seen]
         print(f"dW B={B} L={L} {seen}", flush=True)
         du, dW, _ = P.backward("tanh_dense", W, u, h0, h, part)
-        mu = du.double().reshape(-1, H)
+        mu = du.double().reshape(-1, H).cpu()
         want, size = mu.T @ before, mu.abs().T @ before.abs()
         bound = 2.0 ** -24 * (32 + (B * L / 32) ** 0.5) * size
-        assert bool(((dW.double().reshape(H, H) - want).abs() <= bound + 1e-30).all())
+        assert bool(((dW.double().reshape(H, H).cpu() - want).abs() <= bound + 1e-30).all())
 
 
 def test_backward_of_stretches_in_a_graph():
