@@ -1171,7 +1171,25 @@ struct DenseStretch {
     unsigned long long *flag;         // [B][n] the call's nonce, once what a stretch leaves is in memory
     unsigned long long nonce;
     unsigned int spin_limit;          // polls of a flag before its reader gives up
+    unsigned long long *count;        // [B] tag + how many of a sequence's stretches have left what they leave
+    unsigned long long tag;           // of the call; the bits below kCountBits are zero
 };
+
+// The stretch of a sequence that is the last to end looks at its borders, in the same launch: nobody waits for another workgroup, so
+// nothing rests on the order in which they start.  The count of a sequence begins wherever the workspace stood: every workgroup
+// puts the call's tag there when it starts, if nobody has (whoever of several comes second finds the word changed, and it is
+// changed by this call only), and adds one when all it leaves is in memory.  The one that finds the others there clears the word
+// for a replay of the launch, which has the same tag.
+constexpr int kCountBits = 9;
+static_assert(kStretches < 1 << kCountBits, "a count of all stretches");
+__device__ __forceinline__ void stretch_enters(const DenseStretch &c, int b)
+{
+    if (threadIdx.x == 0) {
+        unsigned long long *word = c.count + b;
+        const unsigned long long old = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (old >> kCountBits != c.tag >> kCountBits) atomicCAS(word, old, c.tag);
+    }
+}
 
 // The workgroup of a sequence's last stretch looks at the borders when all stretches have ended, in the same launch.  It waits
 // for workgroups before its own only, which wait for nobody but such ones: workgroups start in their order, so every wait ends on
@@ -1207,6 +1225,23 @@ __device__ __forceinline__ bool stretches_left(const DenseStretch &c, int b)
     there = __syncthreads_and(there);
     own_rows_fresh();
     return there != 0;
+}
+
+// By all threads of a workgroup: true in the last stretch of sequence b to get here, which then finds what the others left.
+__device__ __forceinline__ bool stretch_is_last(const DenseStretch &c, int b)
+{
+    __shared__ int s_last;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // this wave's stores; behind the barrier, every wave's
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned long long *word = c.count + b;
+        s_last = (int)(atomicAdd(word, 1ull) & ((1u << kCountBits) - 1)) == c.n - 1;
+        if (s_last) __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (!s_last) return false;
+    own_rows_fresh();
+    return true;
 }
 
 // The rows of a sequence that a block of iterations runs and leaves, and which: steps from `first` on are run, `start` to
@@ -1932,7 +1967,7 @@ __global__ __launch_bounds__(wave_threads(HELP)) void dense_adjoint_kernel(const
     adjoint_chain<false, HELP>(a, dh0, (int)blockIdx.x, 0, a.L, 0.0f, nullptr, s);
 }
 
-// One workgroup per stretch; the one of a sequence's last stretch looks at the borders, where two mu may differ relative to the
+// One workgroup per stretch; the last one of a sequence to end looks at the borders, where two mu may differ relative to the
 // largest of the 64 values there, and runs on from the last one at which they do.  part: a matrix of terms of dL/dW per stretch.
 // Those of rows that are run again are added up anew, in pieces of kAgain rows at least; the other ones are zero.
 constexpr int kAgain = 256;
@@ -1950,22 +1985,20 @@ __global__ __launch_bounds__(wave_threads(true)) void dense_adjoint_stretch_kern
         __syncthreads();
     };
     if (threadIdx.x == 0) s_apart = 0;
+    stretch_enters(c, b);
     adjoint_chain<true, true>(a, dh0, b, start, end, 0.0f, c.edge + (size_t)blockIdx.x * DH, s);
     written();
     stretch_weight_gradient(a, b, start, end, c.len, s_half, mine + (size_t)j * DH * DH);
-    stretch_leaves(c);
-    if (j != c.n - 1) return;
-    const bool left = stretches_left(c, b);
+    if (!stretch_is_last(c, b)) return;
     for (int e = 1 + w; e < c.n; e += kWaves) {            // a wave looks at the 64 values between two stretches
         const float there = a.du[((size_t)b * a.L + (size_t)e * c.len) * DH + lane], here = c.edge[((size_t)b * c.n + e - 1) * DH + lane];
         const float top = __uint_as_float(wave_max_u32(__float_as_uint(there) & 0x7fffffffu));
         if (!(fabsf(there - here) <= kWarmTol * top)) atomicMax(&s_apart, e);
     }
     __syncthreads();
-    const int e = left ? __builtin_amdgcn_readfirstlane(s_apart) : c.n;      // a wait that ran out: the whole sequence
+    const int e = __builtin_amdgcn_readfirstlane(s_apart), rows = e * c.len;
     if (e == 0) return;
-    const int rows = min(e * c.len, a.L);
-    adjoint_chain<false, true>(a, dh0, b, 0, rows, e < c.n ? a.du[((size_t)b * a.L + rows) * DH + lane] : 0.0f, nullptr, s);
+    adjoint_chain<false, true>(a, dh0, b, 0, rows, a.du[((size_t)b * a.L + rows) * DH + lane], nullptr, s);
     written();
     own_rows_fresh();
     const int piece = max((c.len + 63) & ~63, kAgain), n_pieces = (rows + piece - 1) / piece;
@@ -2222,7 +2255,7 @@ int dense_backward(int dtype, const float *W, const void *u, const void *h0, con
     DenseStretch c = wavefront_plan(B, L, true);
     if (c.n > 0) {
         a.W = W;
-        // what the stretches leave lies where the chunk products would: 264 bytes of each, and they take 16 KB per 16 steps
+        // what the stretches leave lies where the chunk products would: 256 bytes of each and 8 of a sequence, and they take 16 KB per 16 steps
         c.edge = a.Ac;
         if (B > kHelperUnits) {
             const size_t items = ((size_t)B * L + 15) / 16, most = (size_t)device_cu_count() * 8;
@@ -2230,8 +2263,9 @@ int dense_backward(int dtype, const float *W, const void *u, const void *h0, con
             hipLaunchKernelGGL(dense_adjoint_kernel<false>, dim3(B), dim3(wave_threads(false)), 0, st, a, static_cast<float *>(dh0));
         } else if (c.n > 1) {
             // at most one matrix of terms per stretch, of which there are no more than waves that would share the rows
-            c.flag = reinterpret_cast<unsigned long long *>(c.edge + (size_t)B * c.n * DH);
-            if (B * c.n > dw_waves(B, L) || !stretch_flags(c, B, a.ctrl, st)) return PARARNN_HIP_ERROR;
+            c.count = reinterpret_cast<unsigned long long *>(c.edge + (size_t)B * c.n * DH);
+            c.tag = call_nonce() << kCountBits;
+            if (B * c.n > dw_waves(B, L)) return PARARNN_HIP_ERROR;
             hipLaunchKernelGGL(dense_adjoint_stretch_kernel, dim3(B * c.n), dim3(wave_threads(true)), 0, st, a, static_cast<float *>(dh0), c, part);
             if (hipGetLastError() != hipSuccess) return PARARNN_HIP_ERROR;
             return launch_param_reduce(part, dW, B * c.n, DH * DH, st) == hipSuccess ? PARARNN_OK : PARARNN_HIP_ERROR;

@@ -241,6 +241,26 @@ def test_backward_of_stretches_in_a_graph():
         assert torch.equal(back()[0], want[0])
 
 
+@pytest.mark.parametrize("B,L", [(1, 320), (6, 523), (64, 1024)])
+def test_a_poll_limit_changes_no_gradient(B, L):
+    """A backward pass of stretches has no status: what it returns may not depend on how long anybody waits.  Bits of a pass
+    with the default limit, where stretches hold and where they are run again."""
+    import paper_2510_21450_amd as P
+    W, u, h0, g = problem(B, L, 0.8, 1.0, 14 * L)
+    h = P.forward("tanh_dense", W, u, h0, tol=1e-3, max_iter=32)[0]
+    last = torch.zeros_like(g)
+    last[:, -1] = g[:, -1]
+    for part in (g, last):
+        want = P.backward("tanh_dense", W, u, h0, h, part, want_dh0=True)
+        try:
+            P.set_spin_limit(1)
+            for _ in range(3):
+                got = P.backward("tanh_dense", W, u, h0, h, part, want_dh0=True)
+                assert all(torch.equal(x, y) for x, y in zip(got, want))
+        finally:
+            P.set_spin_limit(0)
+
+
 def test_waits_for_stretches_are_bounded():
     """With one poll the workgroup of a last stretch gives up on the others: the launch ends, the solve says so (or went through),
     and the next call with the default limit is right."""
