@@ -136,8 +136,7 @@ size_t pararnn_workspace_bytes_fused(int cell, int dtype, int B, int L, int H, i
  * two million, i.e. seconds).  A tile that gives up uses a zero carry, the call's
  * device status becomes PARARNN_INTERNAL and every wave still exits: with a tiny
  * limit this path can be exercised without any wait that does not end.  It bounds
- * the grid-wide barriers of the one-launch tails too, the wait of a solve of the dense cell for the other stretches of a
- * sequence, and, times the work there is
+ * the grid-wide barriers of the one-launch tails too, and, times the work there is
  * to wait for (one more limit per 32768 iterations of a tile), the wait of a solve
  * without blocks for the verdicts of its channel groups. */
 int pararnn_set_spin_limit(unsigned int polls);

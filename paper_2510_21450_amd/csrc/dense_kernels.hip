@@ -1168,41 +1168,39 @@ struct DenseStretch {
     int n, len;                       // stretches of a sequence (1: none, the whole sequence at once), steps of each but the last
     float *edge;                      // [B][n][2][kWaveIters][64] updates at the step before the first one and at the last one
     unsigned int *top;                // [B][n][kWaveIters] max |delta|
-    unsigned long long *flag;         // [B][n] the call's nonce, once what a stretch leaves is in memory
-    unsigned long long nonce;
-    unsigned int spin_limit;          // polls of a flag before its reader gives up
-    unsigned long long *count;        // [B] tag + how many of a sequence's stretches have left what they leave
+    unsigned int *seen;               // [B][seen_words] how many iterations a sequence ran, and from word kWaveIters on max |delta| of each
+    unsigned long long *count;        // [B + 1] tag + how many of a sequence's stretches have left what they leave; the last one of the sequences
     unsigned long long tag;           // of the call; the bits below kCountBits are zero
 };
+__host__ __device__ constexpr int seen_words(int max_iter) { return (kWaveIters + max_iter + 31) / 32 * 32; }       // whole lines
 
-// The stretch of a sequence that is the last to end looks at its borders, in the same launch: nobody waits for another workgroup, so
-// nothing rests on the order in which they start.  The count of a sequence begins wherever the workspace stood: every workgroup
-// puts the call's tag there when it starts, if nobody has (whoever of several comes second finds the word changed, and it is
-// changed by this call only), and adds one when all it leaves is in memory.  The one that finds the others there clears the word
-// for a replay of the launch, which has the same tag.
-constexpr int kCountBits = 9;
-static_assert(kStretches < 1 << kCountBits, "a count of all stretches");
-__device__ __forceinline__ void stretch_enters(const DenseStretch &c, int b)
-{
-    if (threadIdx.x == 0) {
-        unsigned long long *word = c.count + b;
-        const unsigned long long old = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (old >> kCountBits != c.tag >> kCountBits) atomicCAS(word, old, c.tag);
-    }
-}
-
-// The workgroup of a sequence's last stretch looks at the borders when all stretches have ended, in the same launch.  It waits
-// for workgroups before its own only, which wait for nobody but such ones: workgroups start in their order, so every wait ends on
-// whatever part of the device the launch gets.  A flag is the nonce of the call: nothing has to be cleared in front, but in a
-// captured launch, which replays its nonce.  Whatever others may read goes to memory past the L2 as it is stored: a fence in front
-// of the flag writes the L2 back, once for each workgroup, 1.2 us one after the other (40 us for 32 of them on each L2).
+// The stretch of a sequence that is the last to end looks at its borders, in the same launch, and goes on with the sequence: nobody
+// waits for another workgroup, so nothing rests on the order in which they start.  A count begins wherever the workspace stood:
+// every workgroup puts the call's tag there when it starts, if nobody has (whoever of several comes second finds the word changed,
+// and only this call changes it), and adds one when all it leaves is in memory.  The one that finds the others there clears the
+// word for a replay of the launch, which has the same tag.
+// Whatever others may read goes to memory past the L2 as it is stored: a fence in front of the count writes the L2 back, once for
+// each workgroup, 1.2 us one after the other (40 us for 32 of them on each L2).
 // As a launch of its own the look took 6.2 us forward and 4.5 backward.  us of a call, with that launch / in one: forward
 // 64 x 1024 87.5 / 84.8, backward (with the terms of dL/dW) 82 / 70, training step 6 x 523 68.5 / 62.7.
-__device__ __forceinline__ void stretch_leaves(const DenseStretch &c)
+constexpr int kCountBits = 9, kCountApart = 16;           // words: a line each (next to each other 16 x 600 took 1 us more)
+static_assert(kStretches < 1 << kCountBits, "a count of all stretches");
+__device__ __forceinline__ unsigned long long count_read(const DenseStretch &c, int which)
 {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // this wave's stores; behind the barrier, every wave's
-    __syncthreads();
-    if (threadIdx.x == 0) __hip_atomic_store(c.flag + blockIdx.x, c.nonce, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return __hip_atomic_load(c.count + which * kCountApart, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void count_enters(const DenseStretch &c, int which, unsigned long long old)
+{
+    if (old >> kCountBits != c.tag >> kCountBits) atomicCAS(c.count + which * kCountApart, old, c.tag);
+}
+// One more of `all`; true for the last one, which clears the word when nothing waits for its stores.
+__device__ __forceinline__ bool count_is_last(const DenseStretch &c, int which, int all)
+{
+    return (int)(atomicAdd(c.count + which * kCountApart, 1ull) & ((1u << kCountBits) - 1)) == all - 1;
+}
+__device__ __forceinline__ void count_clear(const DenseStretch &c, int which)
+{
+    __hip_atomic_store(c.count + which * kCountApart, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // What the unit's L1 and the L2 hold of memory that others, or other waves of the workgroup, have written is dropped: once for
 // a workgroup, as every fence of a launch waits its turn (in every wave of 64 workgroups: 13 us more).
@@ -1211,36 +1209,17 @@ __device__ __forceinline__ void own_rows_fresh()
     if (threadIdx.x < kWave) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     __syncthreads();
 }
-// By all threads of the workgroup of sequence b's last stretch: false where a wait ran out.  Workgroup 0 is waited for too.
-__device__ __forceinline__ bool stretches_left(const DenseStretch &c, int b)
-{
-    int there = 1;
-    if ((int)threadIdx.x < c.n) {
-        const unsigned long long *f = c.flag + (threadIdx.x == 0 ? 0 : b * c.n + (int)threadIdx.x - 1);
-        for (unsigned int polls = 0; __hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != c.nonce;) {
-            if (++polls >= c.spin_limit) { there = 0; break; }
-            __builtin_amdgcn_s_sleep(1);
-        }
-    }
-    there = __syncthreads_and(there);
-    own_rows_fresh();
-    return there != 0;
-}
-
 // By all threads of a workgroup: true in the last stretch of sequence b to get here, which then finds what the others left.
 __device__ __forceinline__ bool stretch_is_last(const DenseStretch &c, int b)
 {
     __shared__ int s_last;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // this wave's stores; behind the barrier, every wave's
     __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned long long *word = c.count + b;
-        s_last = (int)(atomicAdd(word, 1ull) & ((1u << kCountBits) - 1)) == c.n - 1;
-        if (s_last) __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    if (threadIdx.x == 0) s_last = count_is_last(c, b, c.n);
     __syncthreads();
     if (!s_last) return false;
     own_rows_fresh();
+    if (threadIdx.x == kWave * (kWaves - 1)) count_clear(c, b);
     return true;
 }
 
@@ -1554,10 +1533,48 @@ __device__ __forceinline__ void load_w_wave(const float *W, float (&wr)[16])
     }
 }
 
+// By one wave of the workgroup that is through with a sequence: the last of them reports the first iteration whose maximum over the
+// sequences that ran it met the tolerance.  A lane has two sequences at most, and a block of their iterations at a time.
+__device__ __forceinline__ void stretches_report(const DenseArgs &a, const DenseStretch &c)
+{
+    static_assert(kStretches / 2 <= 2 * kWave, "at least two stretches of a sequence");
+    const int lane = threadIdx.x & 63;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // this sequence's words, which are this wave's
+    int last = 0;
+    if (lane == 0) last = count_is_last(c, a.B, a.B);
+    if (!__builtin_amdgcn_readfirstlane(last)) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    int status = a.tol < 0.0f ? kStOk : kStNotConverged, k = 0;
+    for (bool ended = false; k < a.max_iter && !ended;) {
+        u4v top = {0u, 0u, 0u, 0u};
+        for (int b = lane; b < a.B; b += kWave) {
+            const unsigned int *row = c.seen + (size_t)b * seen_words(a.max_iter);
+            const u4v m = *reinterpret_cast<const u4v *>(row + kWaveIters + k);
+            const int ran = (int)row[0] - k;
+#pragma unroll
+            for (int i = 0; i < kWaveIters; ++i) top[i] = max(top[i], i < ran ? m[i] : 0u);
+        }
+#pragma unroll
+        for (int i = 0; i < kWaveIters; ++i) {
+            if (k == a.max_iter || ended) continue;
+            const float mk = __uint_as_float(wave_max_u32(top[i]));
+            if (a.trace && lane == 0) a.trace[k] = mk;
+            ++k;
+            if (!(mk - mk == 0.0f)) { status = kStNonFinite; ended = true; }
+            else if (a.tol >= 0.0f && mk <= a.tol) { status = kStOk; ended = true; }
+        }
+    }
+    if (lane == 0) {
+        a.iters_out[0] = k;
+        a.iters_out[1] = status;
+        count_clear(c, a.B);
+    }
+}
+
 // The solve of sequence b by a workgroup.  A sequence whose own update meets the tolerance at the end of a block is done:
 // the blocks after it are run by the sequences that are not.  gm[k-1]: max |delta| of iteration k over the
 // sequences that ran it.  The last workgroup to finish reports the first iteration whose maximum met the tolerance.
-// CUT: there were stretches; it goes on behind the first block, or solves that again from the first border on where the
+// CUT: there were stretches, and the maxima are in `seen`; it goes on behind the first block, or solves that again from the first border on where the
 // updates differ.
 template <bool CUT>
 __device__ __forceinline__ void wavefront_sequence(const DenseArgs &a, unsigned int *gm, const DenseStretch &c, int b, WaveLds &s)
@@ -1618,6 +1635,7 @@ __device__ __forceinline__ void wavefront_sequence(const DenseArgs &a, unsigned 
         __syncthreads();
         held = __builtin_amdgcn_readfirstlane(s_held);     // the same for the whole workgroup: buffers chosen by it are scalars
     }
+    unsigned int *seen = CUT ? c.seen + (size_t)b * seen_words(a.max_iter) : nullptr;
     float wr[16];
     if (!CUT || held < c.n) load_w_wave(a.W, wr);
     for (int k0 = 0; k0 < a.max_iter; k0 += kWaveIters) {
@@ -1643,11 +1661,17 @@ __device__ __forceinline__ void wavefront_sequence(const DenseArgs &a, unsigned 
             __syncthreads();
         }
         const bool met = ended(K);
-        if ((int)threadIdx.x < K) atomicMax(&gm[k0 + threadIdx.x], s.m[threadIdx.x]);
+        if ((int)threadIdx.x < K) {
+            if constexpr (CUT) store_through(seen + kWaveIters + k0 + threadIdx.x, s.m[threadIdx.x]);
+            else atomicMax(&gm[k0 + threadIdx.x], s.m[threadIdx.x]);
+        }
+        if (CUT && threadIdx.x == 0) store_through(seen, (unsigned int)(k0 + K));
         __syncthreads();
         if (met) break;
     }
-    if (threadIdx.x == 0) {
+    if constexpr (CUT) {
+        if (threadIdx.x < kWave) stretches_report(a, c);
+    } else if (threadIdx.x == 0) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the maxima, which are this wave's
         if (atomicAdd(&a.ctrl->done, 1u) == (unsigned int)a.B - 1) {
             int status = a.tol < 0.0f ? kStOk : kStNotConverged, k = 1;
@@ -1671,34 +1695,29 @@ __global__ __launch_bounds__(wave_threads(false)) void dense_wavefront_kernel(co
     wavefront_sequence<false>(a, gm, c, (int)blockIdx.x, s);
 }
 
-// One workgroup per stretch of a sequence for the first block of iterations; the last one's goes on with the sequence.
-// Also clears the control block and the maxima gm.
-__global__ __launch_bounds__(wave_threads(true)) void dense_stretch_kernel(const DenseArgs a, unsigned int *gm, const DenseStretch c)
+// One workgroup per stretch of a sequence for the first block of iterations; the last one of a sequence to end goes on with it.
+__global__ __launch_bounds__(wave_threads(true)) void dense_stretch_kernel(const DenseArgs a, const DenseStretch c)
 {
     __shared__ WaveLds s;
-    if (blockIdx.x == 0) {
-        if (threadIdx.x < 64) store_through(reinterpret_cast<unsigned int *>(a.ctrl) + threadIdx.x, 0u);
-        for (int i = threadIdx.x; i < a.max_iter; i += wave_threads(true)) store_through(gm + i, 0u);
-    }
     const int b = (int)blockIdx.x / c.n, j = (int)blockIdx.x - b * c.n, K = min(kWaveIters, a.max_iter);
     const size_t seq = (size_t)b * a.L * DH;
     {
+        // the count of the sequences by one workgroup of each: all of them at one word took 2 us of 64 x 1024
+        const bool counts = threadIdx.x < (j == 0 ? 2 : 1);
+        const int which = threadIdx.x == 0 ? b : a.B;
+        unsigned long long old = 0;
+        if (counts) old = count_read(c, which);
         float wr[16];
         load_w_wave(a.W, wr);
+        __builtin_amdgcn_sched_barrier(0);                 // all of it on its way before anything is waited for
+        if (counts) count_enters(c, which, old);
         const int start = j * c.len;
         const WaveRows q = {a.h + seq, a.d + seq, max(start - kWarm, 0), start, min(start + c.len, a.L)};
         wavefront_block<kStretch, true, true>(a, b, K, q, wr, s, c.edge + (size_t)blockIdx.x * 2 * kWaveIters * DH);
     }
     __syncthreads();
     if (threadIdx.x < kWaveIters) store_through(c.top + (size_t)blockIdx.x * kWaveIters + threadIdx.x, s.m[threadIdx.x]);
-    stretch_leaves(c);
-    if (j != c.n - 1) return;
-    if (stretches_left(c, b)) {
-        wavefront_sequence<true>(a, gm, c, b, s);
-    } else if (threadIdx.x == 0) {
-        a.iters_out[0] = a.max_iter;
-        a.iters_out[1] = kStInternal;
-    }
+    if (stretch_is_last(c, b)) wavefront_sequence<true>(a, nullptr, c, b, s);
 }
 
 // Backward by substitution: mu_l = d_l (W^T mu_{l+1} + g_l), one workgroup per sequence.  The row factors
@@ -1985,7 +2004,7 @@ __global__ __launch_bounds__(wave_threads(true)) void dense_adjoint_stretch_kern
         __syncthreads();
     };
     if (threadIdx.x == 0) s_apart = 0;
-    stretch_enters(c, b);
+    if (threadIdx.x == 0) count_enters(c, b, count_read(c, b));
     adjoint_chain<true, true>(a, dh0, b, start, end, 0.0f, c.edge + (size_t)blockIdx.x * DH, s);
     written();
     stretch_weight_gradient(a, b, start, end, c.len, s_half, mine + (size_t)j * DH * DH);
@@ -2040,14 +2059,6 @@ DenseStretch dense_stretches(int B, int L, double step, double products)
     if (chain + warm - without > 0.5 * (without - step * len - warm)) return c;
     c.n = (L + len - 1) / len; c.len = len;
     return c;
-}
-
-// What the workgroups of stretches say to each other with; c.flag is where its words are.
-bool stretch_flags(DenseStretch &c, int B, Ctrl *ctrl, hipStream_t st)
-{
-    c.nonce = call_nonce();
-    c.spin_limit = settings().spin_limit;
-    return !stream_is_capturing(st) || launch_reset(ctrl, c.flag, (size_t)B * c.n, nullptr, 0, st) == hipSuccess;
 }
 
 // The stretches of a solve by substitution; n = 0 where chunk products are faster.
@@ -2255,7 +2266,7 @@ int dense_backward(int dtype, const float *W, const void *u, const void *h0, con
     DenseStretch c = wavefront_plan(B, L, true);
     if (c.n > 0) {
         a.W = W;
-        // what the stretches leave lies where the chunk products would: 256 bytes of each and 8 of a sequence, and they take 16 KB per 16 steps
+        // what the stretches leave lies where the chunk products would: 256 bytes of each and 128 of a sequence, and they take 16 KB per 16 steps
         c.edge = a.Ac;
         if (B > kHelperUnits) {
             const size_t items = ((size_t)B * L + 15) / 16, most = (size_t)device_cu_count() * 8;
@@ -2374,15 +2385,16 @@ int dense_forward(int dtype, const float *W, const void *u, const void *h0, int 
         unsigned int *gm = reinterpret_cast<unsigned int *>(ws + lo.off_A);
         if (tol >= 0.0f && tol < kWarmTol) { c.n = 1; c.len = L; }
         if (c.n > 1) {
-            // behind the maxima what the stretches leave, 2.07 KB for each of at least 32 steps; chunk products would take 1 KB per step
-            c.edge = reinterpret_cast<float *>(gm) + DH * DH;
-            c.flag = reinterpret_cast<unsigned long long *>(c.edge + (size_t)B * c.n * 2 * kWaveIters * DH);
-            c.top = reinterpret_cast<unsigned int *>(c.flag + (size_t)B * c.n);
+            // 2.06 KB of each stretch of at least 32 steps and a word of each iteration; chunk products would take 1 KB per step
+            c.edge = reinterpret_cast<float *>(gm);
+            c.seen = reinterpret_cast<unsigned int *>(c.edge + (size_t)B * c.n * 2 * kWaveIters * DH);
+            c.count = reinterpret_cast<unsigned long long *>(c.seen + (size_t)B * seen_words(max_iter));
+            c.tag = call_nonce() << kCountBits;
+            c.top = reinterpret_cast<unsigned int *>(c.count + (size_t)(B + 1) * kCountApart);
             if (reinterpret_cast<char *>(c.top + (size_t)B * c.n * kWaveIters) > ws + lo.off_b) { c.n = 1; c.len = L; }
         }
         if (c.n > 1) {
-            if (!stretch_flags(c, B, a.ctrl, st)) return PARARNN_HIP_ERROR;
-            hipLaunchKernelGGL(dense_stretch_kernel, dim3(B * c.n), dim3(wave_threads(true)), 0, st, a, gm, c);
+            hipLaunchKernelGGL(dense_stretch_kernel, dim3(B * c.n), dim3(wave_threads(true)), 0, st, a, c);
         } else {
             hipLaunchKernelGGL(dense_guess_kernel, dim3(res_blocks), dim3(256), 0, st, a, gm, max_iter);
             hipLaunchKernelGGL(dense_wavefront_kernel, dim3(B), dim3(wave_threads(false)), 0, st, a, gm);

@@ -242,11 +242,22 @@ def test_backward_of_stretches_in_a_graph():
 
 
 @pytest.mark.parametrize("B,L", [(1, 320), (6, 523), (64, 1024)])
-def test_a_poll_limit_changes_no_gradient(B, L):
-    """A backward pass of stretches has no status: what it returns may not depend on how long anybody waits.  Bits of a pass
-    with the default limit, where stretches hold and where they are run again."""
+def test_a_poll_limit_changes_nothing(B, L):
+    """Stretches wait for nobody: with one poll allowed the bits of the default limit, and status OK, where stretches hold and where
+    they are run again.  (A backward pass has no status that could say otherwise.)"""
     import paper_2510_21450_amd as P
     W, u, h0, g = problem(B, L, 0.8, 1.0, 14 * L)
+    slow = (torch.linalg.qr(W.double().cpu())[0] * 0.95).float().contiguous().cuda()
+    for V, x in ((W, u), (slow, u * 0.02)):
+        want = P.forward("tanh_dense", V, x, h0, tol=1e-3, max_iter=32)
+        assert P.status_string(int(want[1].cpu()[1])) == "OK"
+        try:
+            P.set_spin_limit(1)
+            for _ in range(3):
+                got = P.forward("tanh_dense", V, x, h0, tol=1e-3, max_iter=32)
+                assert torch.equal(got[0], want[0]) and got[1].tolist() == want[1].tolist()
+        finally:
+            P.set_spin_limit(0)
     h = P.forward("tanh_dense", W, u, h0, tol=1e-3, max_iter=32)[0]
     last = torch.zeros_like(g)
     last[:, -1] = g[:, -1]
@@ -261,22 +272,24 @@ def test_a_poll_limit_changes_no_gradient(B, L):
             P.set_spin_limit(0)
 
 
-def test_waits_for_stretches_are_bounded():
-    """With one poll the workgroup of a last stretch gives up on the others: the launch ends, the solve says so (or went through),
-    and the next call with the default limit is right."""
+def test_training_steps_on_two_streams():
+    """Launches of stretches side by side, each a third or all of the device: the bits of one after the other."""
     import paper_2510_21450_amd as P
-    W, u, h0, g = problem(6, 523, 0.8, 1.0, 13)
-    seen = set()
-    try:
-        P.set_spin_limit(1)
-        for _ in range(3):
-            h, it, _ = P.forward("tanh_dense", W, u, h0, tol=1e-3, max_iter=32)
-            P.backward("tanh_dense", W, u, h0, torch.zeros_like(h), g)
-            torch.cuda.synchronize()
-            seen.add(P.status_string(int(it.cpu()[1])))
-    finally:
-        P.set_spin_limit(0)
-    assert seen <= {"OK", "INTERNAL"}, seen
-    h, it, _ = P.forward("tanh_dense", W, u, h0, tol=1e-3, max_iter=32)
-    H_, it_, _ = P.forward("tanh_dense", W, whole(u, 6), whole(h0, 6), tol=1e-3, max_iter=32)
-    assert it.tolist() == it_.tolist() and (h - H_[:6]).abs().max() <= 1e-6
+    work = [problem(B, L, 0.8, 1.0, B + L) for B, L in ((64, 1024), (6, 523), (85, 700), (1, 2050))]
+
+    def step(p):
+        h, it, _ = P.forward("tanh_dense", p[0], p[1], p[2], tol=1e-3, max_iter=32)
+        return (h, it) + tuple(P.backward("tanh_dense", p[0], p[1], p[2], h, p[3], want_dh0=True))
+
+    want = [step(p) for p in work]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    got = []
+    for turn in range(6):
+        for k, st in enumerate(streams):
+            i = (turn + 2 * k + k * (turn // 2)) % len(work)
+            with torch.cuda.stream(st):
+                got.append((i, step(work[i])))
+    torch.cuda.synchronize()
+    for i, out in got:
+        assert all(torch.equal(x, y) for x, y in zip(out, want[i])), i
