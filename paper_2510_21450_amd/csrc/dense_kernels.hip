@@ -34,6 +34,7 @@
 #include "pararnn.h"
 #include "pararnn/common.h"
 #include "dense.h"
+#include "dense_plan.h"
 #include "pararnn/driver.h"
 #include "pararnn/launch.h"
 
@@ -1000,7 +1001,6 @@ int newton_grid(int prod)
 // rows of u (and, after the first block, h and y) in, sixteen bytes per lane, and takes the results out, by way of a ring of records in LDS, one
 // per step, in which each iteration finds its inputs and leaves its results where the next one looks for them.
 // Measured: see the rule at wavefront_plan().
-constexpr int kWaveIters = 4;
 constexpr int kWaveGroup = 8;         // steps per group: the mover wave brings in and takes out the rows of a group at a time
 constexpr int kRing = 16;             // steps a ring in LDS holds: the group in use and the one that is ready
 
@@ -1154,18 +1154,16 @@ template <int N> __device__ __forceinline__ f4v *ring_slot(float (*ring)[N], int
 // after 24-26 steps with u ~ N(0, 1), 52-64 with u a tenth to a third of that; 1.2 N(0, 1/64) after 50-61.
 // Small states seldom agree even where all is forgotten: tanh and with it an update from the second iteration on
 // has an absolute error of 6e-8.  Nor do any to a tolerance below kWarmTol: such solves have no stretches.
-constexpr int kWarm = 64;
-constexpr int kWarmLeast = 32;        // steps of a stretch at least: shorter ones would be half warm-up and more
+// (kWarm, the least length of a stretch and their number: dense_plan.h)
 constexpr float kWarmTol = 4.8e-7f;
 // From the second iteration on two histories that have forgotten everything still turn roundings of tanh over: up to 4.9e-7
 // at 2880 borders of the benchmark's W (3.6e-7 in the first iteration, which is linear); one batch of 64 x 1024 in twenty and one of
 // 16 x 600 in ten had a border above 4.8e-7, none of a hundred one above 6e-7.  What those iterations have not forgotten is
 // less than in the first one, as their updates are.
 constexpr float kWarmTolLater = 6e-7f;
-constexpr int kStretches = 256;       // of all sequences at most: one for each compute unit
 
 struct DenseStretch {
-    int n, len;                       // stretches of a sequence (1: none, the whole sequence at once), steps of each but the last
+    int n, len;                       // as in DensePlan
     float *edge;                      // [B][n][2][kWaveIters][64] updates at the step before the first one and at the last one
     unsigned int *top;                // [B][n][kWaveIters] max |delta|
     unsigned int *seen;               // [B][seen_words] how many iterations a sequence ran, and from word kWaveIters on max |delta| of each
@@ -2025,50 +2023,12 @@ __global__ __launch_bounds__(wave_threads(true)) void dense_adjoint_stretch_kern
     for (int k = n_pieces * DH * DH + threadIdx.x; k < e * DH * DH; k += wave_threads(true)) store_through(mine + k, 0.0f);
 }
 
-// Substitution or chunk products, and in how many stretches?  Nanoseconds, measured on config 4's shape and on 1 to 16
-// sequences of 500 to 2000 steps: a forward substitution step takes 225, an adjoint one 160, whatever the number of sequences
-// while each has a compute unit; an iteration with chunk products takes 3.94 per row but at least 67 us (the chain of one
-// chunk), 17 per step for the carry and 25-30 us for the sweeps, and four iterations are what a solve needs.
-//
-// Stretches: one for each compute unit.  Two workgroups on a unit, 512 stretches, take 590 ns a step instead of 225 (64
-// sequences of 1024 steps: 108 us with 256, 136 with 512).  Whether a recurrence forgets within kWarm steps is known only
-// afterwards, so they are a bet: won, the chain is that of one stretch; lost, all of it and the warm-up.  It is taken where it
-// loses at most half of what it gains.  us, without stretches / won / lost (W orthogonal, u a tenth):
-//
-//            forward              backward
-//   1 x 200   53 /  37 /  64       47 / 32 /  55     not taken
-//   1 x 300   74 /  35 /  82       62 / 26 /  74
-//   6 x 523  121 /  36 / 132       98 / 28 / 120
-//   16 x 600 142 /  40 / 158      115 / 31 / 141
-//   64 x 272  80 /  53 / 105       67 / 51 /  88     not taken
-//   64 x 1024 242 / 91 / 259      200 / 70 / 224
-//   16 x 1000 227 / 44 / 238      144 / 49 / 191     backward not taken: chunk products
-//
-// Lost, a backward pass also adds the terms of dL/dW up again, in one workgroup of a sequence (20 ns a row).
-DenseStretch dense_stretches(int B, int L, double step, double products)
+DenseStretch planned(int B, int L, bool backward)
 {
+    const DensePlan p = g_dense_substitution ? wavefront_plan(B, L, backward) : DensePlan{0, 0};
     DenseStretch c;
     memset(&c, 0, sizeof(c));
-    c.n = 1; c.len = L;
-    const int most = kStretches / B;
-    if (most < 2) return c;
-    const int len = (L + most - 1) / most > kWarmLeast ? (L + most - 1) / most : kWarmLeast;
-    if (len >= L) return c;
-    const double chain = step * L, without = chain < products ? chain : products;
-    const double warm = step * (kWarm + kWaveIters) + 3e3;                 // and the look at the borders
-    if (chain + warm - without > 0.5 * (without - step * len - warm)) return c;
-    c.n = (L + len - 1) / len; c.len = len;
-    return c;
-}
-
-// The stretches of a solve by substitution; n = 0 where chunk products are faster.
-DenseStretch wavefront_plan(int B, int L, bool backward)
-{
-    const double rows = (double)B * L, step = backward ? 160.0 : 225.0;
-    const double products = ((rows * 3.94 > 67e3 ? rows * 3.94 : 67e3) + 17.0 * L + 27e3) * (backward ? 1.0 : 4.0);
-    DenseStretch c = dense_stretches(B, L, step, products);
-    const double chain = step * L * (double)((B + 511) / 512);              // two workgroups share a compute unit
-    if (!g_dense_substitution || (c.n == 1 && chain >= products)) c.n = 0;
+    c.n = p.n; c.len = p.len;
     return c;
 }
 
@@ -2263,7 +2223,7 @@ int dense_backward(int dtype, const float *W, const void *u, const void *h0, con
     a.ctrl = reinterpret_cast<Ctrl *>(ws);
     a.g = static_cast<const float *>(g); a.du = static_cast<float *>(du);
     a.B = B; a.L = L; a.n_c = lo.n_c;
-    DenseStretch c = wavefront_plan(B, L, true);
+    DenseStretch c = planned(B, L, true);
     if (c.n > 0) {
         a.W = W;
         // what the stretches leave lies where the chunk products would: 256 bytes of each and 128 of a sequence, and they take 16 KB per 16 steps
@@ -2380,7 +2340,7 @@ int dense_forward(int dtype, const float *W, const void *u, const void *h0, int 
         return hipGetLastError() == hipSuccess ? PARARNN_OK : PARARNN_HIP_ERROR;
     }
     // the maxima of the iterations lie where the chunk products would (at least 4096 words)
-    DenseStretch c = wavefront_plan(B, L, false);
+    DenseStretch c = planned(B, L, false);
     if (g_dense_products == 0 && max_iter > 0 && max_iter <= DH * DH && c.n > 0) {
         unsigned int *gm = reinterpret_cast<unsigned int *>(ws + lo.off_A);
         if (tol >= 0.0f && tol < kWarmTol) { c.n = 1; c.len = L; }

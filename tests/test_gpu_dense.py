@@ -497,3 +497,40 @@ def test_dense_long_sequences(oracle_mod, tail_mode, as_stored, shape):
     torch.cuda.synchronize()
     rdu, rdW, rdh0 = oracle_mod.backward("tanh_dense", Wn, un, h0n, f64(hs), f64(g))
     assert relerr(f64(du), rdu) <= 1e-5 and relerr(f64(dW), rdW) <= 1e-5 and relerr(f64(dh0), rdh0) <= 1e-5
+
+
+def test_a_sequence_of_more_than_4_gb():
+    """2^24 rows of 256 bytes and five more: rows beyond what 32 bits address are solved and given gradients like the others.  Stretches of
+    the result against the recurrences in 64 bits, from the state (or mu) that the stretch begins with."""
+    import paper_2510_21450_amd as P
+    H, L = 64, (1 << 24) + 5
+    gen = torch.Generator(device="cuda").manual_seed(77)
+    W = torch.randn(H, H, generator=gen, device="cuda") * (0.8 / 8)
+    u = torch.randn(1, L, 1, H, generator=gen, device="cuda")
+    print(f"dense L={L}", flush=True)
+    h, iters, _ = P.forward("tanh_dense", W, u, None, tol=1e-4, max_iter=16)
+    assert iters.tolist()[1] == 0
+    Wn = f64(W)
+    at = (1, 1 << 20, (1 << 24) - 40, L - 30)               # the last two across and behind the line
+    for s in at:
+        hn, un = f64(h[0, s - 1:s + 30, 0]), f64(u[0, s:s + 30, 0])
+        x = hn[0]
+        for i in range(len(un)):
+            x = np.tanh(Wn @ x + un[i])
+            assert relerr(hn[i + 1], x) <= 1e-5, (s, i)
+    g = torch.randn(1, L, 1, H, generator=gen, device="cuda")
+    du, dW, _ = P.backward("tanh_dense", W, u, None, h, g)
+    for s in at:
+        dn, hn, gn = f64(du[0, s:s + 31, 0]), f64(h[0, s:s + 31, 0]), f64(g[0, s:s + 31, 0])
+        mu = np.zeros(H) if s + 31 > L else dn[-1]
+        for i in reversed(range(len(dn) - (s + 31 <= L))):
+            mu = (1 - hn[i] ** 2) * (Wn.T @ mu + gn[i])
+            assert relerr(dn[i], mu) <= 1e-5, (s, i)
+    # sums of 2^24 terms of either sign in 32 bits, in partial sums of at most 2^14: relative to the sum of their sizes
+    n, want, size = 1 << 20, 0.0, 0.0
+    for i in range(0, L - 1, n):
+        m, x = du[0, i + 1:i + 1 + n, 0].double().cpu(), h[0, i:min(i + n, L - 1), 0].double().cpu()
+        want, size = want + m.T @ x, size + m.abs().T @ x.abs()
+    assert bool(((dW.double().cpu().reshape(H, H) - want).abs() <= 2.0 ** -24 * (1 << 7) * 2 * size).all())
+    del u, h, g, du
+    torch.cuda.empty_cache()
