@@ -70,9 +70,14 @@ inline int forward_stream_level(size_t u_bytes, size_t iterate_bytes)
 // of the way of what the pass before left in the cache (u and h of the last steps, where this one begins).  Pays from one
 // and a half times the cache on; below that the next reader of dL/du finds it in the cache.  Only rows of whole cache
 // lines: a line that two channel groups share leaves the L2 before the second one asks.  Not in tiles of twelve steps a
-// thread (ParaLSTM in fp32).  us of the pass, plain / streamed: fp32 16 x 2048 x 1024 GRU 212 / 192, LSTM 294 / 270, rot_tanh 223 / 200,
-// ParaLSTM 284 / 289 (7 x 3000 x 1536 259 / 270); bf16 16 x 2048 x 1024 LSTM 223 / 212, rot_tanh 146 / 135; 384 MB GRU fp32 87 / 79, LSTM
-// bf16 126 / 119; 256 MB rot_tanh bf16 78 / 81; 192 MB GRU bf16 57 / 61; rows of 1500 channels (16 x 2000) GRU fp32 371 / 412, bf16 232 / 298.
+// thread, whatever the cell (backward_tile_by_size: fp32 LSTM but for many channels of short sequences, ParaLSTM in fp32 and, of few
+// channels, in bf16), which lose up to 5 % or stay level.  us of the pass, plain / streamed:
+//   twelve steps  fp32 LSTM 16 x 4096 x 1024 612 / 643, 16 x 2049 x 1024 325 / 329, 8 x 4096 x 2048 604 / 607, 4 x 2048 x 2048 157 / 164;
+//                 ParaLSTM 16 x 4096 x 1024 526 / 549, 7 x 3000 x 1536 262 / 271, bf16 4 x 8192 x 1024 212 / 214
+//   others        fp32 16 x 2048 x 1024 GRU 212 / 192, LSTM 294 / 270, rot_tanh 223 / 200; bf16 16 x 2048 x 1024 LSTM 223 / 212, rot_tanh 146 /
+//                 135, ParaLSTM 205 / 198
+//   sizes         384 MB GRU fp32 87 / 79, LSTM bf16 126 / 119; 256 MB rot_tanh bf16 78 / 81; 192 MB GRU bf16 57 / 61
+//   lines         rows of 1500 channels (16 x 2000) GRU fp32 371 / 412, bf16 232 / 298
 inline int backward_stream(size_t bytes, bool pays)
 {
     const int mode = settings().streaming;
