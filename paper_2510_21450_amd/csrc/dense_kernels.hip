@@ -1729,13 +1729,21 @@ __global__ __launch_bounds__(wave_threads(true)) void dense_stretch_kernel(const
 // STRETCH: one workgroup per stretch of a sequence (DenseStretch: here from the last row down; what enters is one mu), which
 // starts kWarm rows early from mu = 0 and leaves mu at the row behind its own last one in `edge`.  Otherwise a whole sequence, or
 // what is run again behind the last border at which its stretches differ: rows 0 .. end - 1, with `x` entering.
+//
+// The helpers of a stretch leave the row factors in a.d, for a sequence that is run again.  GRADIENT: then they add up the terms of
+// dL/dW of these rows instead, a group of steps behind the chain, each those of sixteen rows of the matrix, four rows of mu and h at
+// a time on v_mfma_f32_16x16x4_f32, in sums of sixteen rows and a sum of those; `dw`: the matrix, and n_dw - 1 more behind it that the
+// mover clears.  us of a pass whose sequences are run again, with row factors made anew and the terms added up behind the chain /
+// so: 6 x 523 117 / 102, 16 x 600 137 / 120, 64 x 1024 218 / 197.
 struct AdjointLds {
     // step t of the recurrence is row last - t; its record holds d and d g, and mu is in the slot of the same number
     __attribute__((aligned(16))) float rec[kRing][2 * DH], mu[kRing][DH];
 };
-template <bool STRETCH, bool HELP>
-__device__ __forceinline__ void adjoint_chain(const DenseArgs &a, float *dh0, int b, int start, int end, float x, float *edge, AdjointLds &lds)
+template <bool STRETCH, bool HELP, bool GRADIENT = false>
+__device__ __forceinline__ void adjoint_chain(const DenseArgs &a, float *dh0, int b, int start, int end, float x, float *edge, AdjointLds &lds,
+                                              float *dw = nullptr, int n_dw = 0)
 {
+    static_assert(!GRADIENT || !HELP, "the helpers' work instead");
     auto &s_rec = lds.rec;
     auto &s_mu = lds.mu;
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -1785,10 +1793,14 @@ __device__ __forceinline__ void adjoint_chain(const DenseArgs &a, float *dh0, in
             }
             dg = d * xg;
         };
+        // own rows: those behind them are another stretch's, steps past the last one come out in front
+        const buf_rsrc rd = seq_rsrc(a.d + ((size_t)b * a.L + start) * DH, (unsigned int)(end - start) * (DH * 4u));
         auto put = [&](int t) {                            // the last readers of these records are done
             float *rec = s_rec[t & (kRing - 1)];
             *reinterpret_cast<f4v *>(rec + chn) = d;
             *reinterpret_cast<f4v *>(rec + DH + chn) = dg;
+            if constexpr (STRETCH)
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4v, d), rd, (unsigned int)(rev(t) - start) * (DH * 4u) + 4u * chn, 0, kThrough);
         };
         // as guess_rows: two groups of steps at a time
         bring(n);
@@ -1828,6 +1840,66 @@ __device__ __forceinline__ void adjoint_chain(const DenseArgs &a, float *dh0, in
         }
         return;
     }
+    if (GRADIENT && w >= kHelpers) {
+        // Terms of dL/dW of group k: lane (n, g) has step 8 k + 4 i + g, channel 16 hw + n of mu and 16 j + n of h, in register 4 i + j.
+        const int hw = w - kHelpers, n = lane & 15, g = lane >> 4;
+        const buf_rsrc rh = seq_rsrc(a.h + (size_t)b * a.L * DH, seq_bytes);
+        float mu[2], h[8], h_next[8];
+        const f4v zero = {0.0f, 0.0f, 0.0f, 0.0f};
+        f4v acc[8] = {zero, zero, zero, zero, zero, zero, zero, zero}, sum[4] = {zero, zero, zero, zero}, lost[4] = {zero, zero, zero, zero};
+        auto bring = [&](int k) {                          // rows outside the sequence read zero
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int l = rev(k * kWaveGroup + 4 * i + g);
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    h_next[4 * i + j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rh, (unsigned int)(l - 1) * (DH * 4u) + 4u * (16 * j + n), 0, 0));
+                if (l == 0 && a.h0) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) h_next[4 * i + j] = a.h0[(size_t)b * DH + 16 * j + n];
+                }
+            }
+        };
+        auto take = [&](int k) {                           // mu of the group is complete; steps past the last one have none
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int t = k * kWaveGroup + 4 * i + g;
+                mu[i] = t < L ? s_mu[t & (kRing - 1)][16 * hw + n] : 0.0f;
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) h[i] = h_next[i];
+        };
+        auto multiply = [&](int i) { acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(mu[i >> 2], h[i], acc[i], 0, 0, 0); };
+        auto add = [&](int j) {                            // compensated: plain, the sums of 512 rows had a tenth more error than a tree of them
+            const f4v y = acc[j] + acc[j + 4] - lost[j], s = sum[j] + y;
+            lost[j] = (s - sum[j]) - y;
+            sum[j] = s;
+            acc[j] = acc[j + 4] = zero;
+        };
+        bring(0);
+        helper_barrier();
+        for (int k = 0; k < n_groups; ++k) {               // the terms of a group while the next one runs
+#pragma unroll
+            for (int j = 0; j < kWaveGroup; ++j) {
+                if (k > 0) {
+                    if (j == 0) { take(k - 1); bring(k); }
+                    if (j < 4 && (k & 3) == 1) add(j);     // of 32 rows
+                    multiply(j);
+                }
+                helper_barrier();
+            }
+        }
+        take(n_groups - 1);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) multiply(j);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            add(j);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) dw[(16 * hw + 4 * g + v) * DH + 16 * j + n] = sum[j][v];
+        }
+        return;
+    }
     if (w == kMover) {
         const buf_rsrc rd = seq_rsrc(a.d + (size_t)b * a.L * DH, seq_bytes), rg = seq_rsrc(a.g + (size_t)b * a.L * DH, seq_bytes),
                        ro = seq_rsrc(a.du + (size_t)b * a.L * DH, (unsigned int)end * (DH * 4u));   // rows behind the own ones are not stored
@@ -1849,6 +1921,10 @@ __device__ __forceinline__ void adjoint_chain(const DenseArgs &a, float *dh0, in
             for (int j = 0; j < 2; ++j) xm[j] = *ring_slot(s_mu, 0, lane, t + 4 * j);
             rows_store<STRETCH>(ro, xm, lane, t, [&](int k) { return k < L ? last - k : -1; });
         };
+        int k = DH * DH / 4 + lane;                        // quads to be cleared: up to four a lane and group, of 32 rows or more a matrix
+        auto clear = [&]() {
+            for (int i = 0; i < 4 && k < n_dw * (DH * DH / 4); ++i, k += kWave) reinterpret_cast<f4v *>(dw)[k] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+        };
         bring(0);
         put(0);
         lds_barrier();
@@ -1856,6 +1932,7 @@ __device__ __forceinline__ void adjoint_chain(const DenseArgs &a, float *dh0, in
             const int t0 = g * kWaveGroup;
             bring(t0 + kWaveGroup);
             if (g > 0) take(t0 - kWaveGroup);
+            if constexpr (GRADIENT) clear();
 #pragma unroll 1
             for (int i = 0; i < kWaveGroup - 2; ++i) lds_barrier();
             put(t0 + kWaveGroup);                          // the group's last step reads the first of these records
@@ -1923,11 +2000,10 @@ __device__ __forceinline__ void adjoint_chain(const DenseArgs &a, float *dh0, in
     }
 }
 
-// The terms that rows first .. end - 1 of sequence b add to dL/dW = sum mu_l h_{l-1}^T, in sums of `piece` rows (a multiple of 64, or all
-// of them), each a matrix of `out`.  By eight waves: each has a quarter of the matrix and every other batch of 32 rows, two at a
-// time on v_mfma_f32_32x32x2_f32; the rows of a batch travel while the one before is multiplied.  In the launch of the
-// stretches, where mu is at hand; as one of its own it took 6.6 us of a step of 6 x 523.
-__device__ __forceinline__ void stretch_weight_gradient(const DenseArgs &a, int b, int first, int end, int piece, float (&s_half)[4][16][kWave], float *out)
+// The terms that rows first .. end - 1 of sequence b add to dL/dW = sum mu_l h_{l-1}^T, a matrix.  By eight waves: each has a quarter of
+// it and every other batch of 32 rows, two at a time on v_mfma_f32_32x32x2_f32; the rows of a batch travel while the one before
+// is multiplied.  In the launch of the stretches, where mu is at hand; as one of its own it took 6.6 us of a step of 6 x 523.
+__device__ __forceinline__ void stretch_weight_gradient(const DenseArgs &a, int b, int first, int end, float (&s_half)[4][16][kWave], float *out)
 {
     constexpr int kPairs = 16, kSums = 4;                  // sums of a wave: in one, 128 rows of 256 added up one by one, 1.5 to 2 times the error
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -1945,34 +2021,31 @@ __device__ __forceinline__ void stretch_weight_gradient(const DenseArgs &a, int 
         }
         if (r == 0 && half == 0 && a.h0) hn[0] = a.h0[(size_t)b * DH + 32 * nt + n];
     };
-    int r = first + 2 * kPairs * part;
-    if (w < 8) bring(r);
-    for (int p = first; p < end; p += piece, out += DH * DH) {
-        f16v Qs[kSums], Q;
+    f16v Qs[kSums], Q;
+    if (w < 8) {
+        int r = first + 2 * kPairs * part;
+        bring(r);
 #pragma unroll
         for (int k = 0; k < kSums; ++k)
 #pragma unroll
             for (int v = 0; v < 16; ++v) Qs[k][v] = 0.0f;
-        if (w < 8) {
-            for (const int stop = min(p + piece, end); r < stop; r += 4 * kPairs) {
+        for (; r < end; r += 4 * kPairs) {
 #pragma unroll
-                for (int i = 0; i < kPairs; ++i) { m[i] = mn[i]; h[i] = hn[i]; }
-                bring(r + 4 * kPairs);
+            for (int i = 0; i < kPairs; ++i) { m[i] = mn[i]; h[i] = hn[i]; }
+            bring(r + 4 * kPairs);
 #pragma unroll
-                for (int i = 0; i < kPairs; ++i) Qs[i % kSums] = __builtin_amdgcn_mfma_f32_32x32x2f32(m[i], h[i], Qs[i % kSums], 0, 0, 0);
-            }
-            Q = (Qs[0] + Qs[1]) + (Qs[2] + Qs[3]);
-            if (part == 1) {
-#pragma unroll
-                for (int v = 0; v < 16; ++v) s_half[w & 3][v][lane] = Q[v];
-            }
+            for (int i = 0; i < kPairs; ++i) Qs[i % kSums] = __builtin_amdgcn_mfma_f32_32x32x2f32(m[i], h[i], Qs[i % kSums], 0, 0, 0);
         }
-        lds_barrier();
-        if (w < 4) {
+        Q = (Qs[0] + Qs[1]) + (Qs[2] + Qs[3]);
+        if (part == 1) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) store_through(out + (32 * mt + mfma_row(v, half)) * DH + 32 * nt + n, Q[v] + s_half[w][v][lane]);
+            for (int v = 0; v < 16; ++v) s_half[w & 3][v][lane] = Q[v];
         }
-        lds_barrier();
+    }
+    lds_barrier();
+    if (w < 4) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) store_through(out + (32 * mt + mfma_row(v, half)) * DH + 32 * nt + n, Q[v] + s_half[w][v][lane]);
     }
 }
 
@@ -1986,8 +2059,7 @@ __global__ __launch_bounds__(wave_threads(HELP)) void dense_adjoint_kernel(const
 
 // One workgroup per stretch; the last one of a sequence to end looks at the borders, where two mu may differ relative to the
 // largest of the 64 values there, and runs on from the last one at which they do.  part: a matrix of terms of dL/dW per stretch.
-// Those of rows that are run again are added up anew, in pieces of kAgain rows at least; the other ones are zero.
-constexpr int kAgain = 256;
+// Those of rows that are run again are added up anew, in the first one; the other ones are zero.
 __global__ __launch_bounds__(wave_threads(true)) void dense_adjoint_stretch_kernel(const DenseArgs a, float *dh0, const DenseStretch c, float *part)
 {
     __shared__ AdjointLds s;
@@ -2005,7 +2077,7 @@ __global__ __launch_bounds__(wave_threads(true)) void dense_adjoint_stretch_kern
     if (threadIdx.x == 0) count_enters(c, b, count_read(c, b));
     adjoint_chain<true, true>(a, dh0, b, start, end, 0.0f, c.edge + (size_t)blockIdx.x * DH, s);
     written();
-    stretch_weight_gradient(a, b, start, end, c.len, s_half, mine + (size_t)j * DH * DH);
+    stretch_weight_gradient(a, b, start, end, s_half, mine + (size_t)j * DH * DH);
     if (!stretch_is_last(c, b)) return;
     for (int e = 1 + w; e < c.n; e += kWaves) {            // a wave looks at the 64 values between two stretches
         const float there = a.du[((size_t)b * a.L + (size_t)e * c.len) * DH + lane], here = c.edge[((size_t)b * c.n + e - 1) * DH + lane];
@@ -2015,12 +2087,7 @@ __global__ __launch_bounds__(wave_threads(true)) void dense_adjoint_stretch_kern
     __syncthreads();
     const int e = __builtin_amdgcn_readfirstlane(s_apart), rows = e * c.len;
     if (e == 0) return;
-    adjoint_chain<false, true>(a, dh0, b, 0, rows, a.du[((size_t)b * a.L + rows) * DH + lane], nullptr, s);
-    written();
-    own_rows_fresh();
-    const int piece = max((c.len + 63) & ~63, kAgain), n_pieces = (rows + piece - 1) / piece;
-    stretch_weight_gradient(a, b, 0, rows, piece, s_half, mine);
-    for (int k = n_pieces * DH * DH + threadIdx.x; k < e * DH * DH; k += wave_threads(true)) store_through(mine + k, 0.0f);
+    adjoint_chain<false, false, true>(a, dh0, b, 0, rows, a.du[((size_t)b * a.L + rows) * DH + lane], nullptr, s, mine, e);
 }
 
 DenseStretch planned(int B, int L, bool backward)

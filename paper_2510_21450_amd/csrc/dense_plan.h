@@ -26,15 +26,15 @@ struct DensePlan { int n, len; };
 // loses at most half of what it gains.  us, without stretches / won / lost (W orthogonal, u a tenth):
 //
 //            forward              backward
-//   1 x 200   53 /  37 /  64       47 / 32 /  55     not taken
-//   1 x 300   74 /  35 /  82       62 / 26 /  74
-//   6 x 523  121 /  36 / 132       98 / 28 / 120
-//   16 x 600 142 /  40 / 158      115 / 31 / 141
-//   64 x 272  80 /  53 / 105       67 / 51 /  88     not taken
-//   64 x 1024 242 / 91 / 259      200 / 70 / 224
-//   16 x 1000 227 / 44 / 238      144 / 49 / 191     backward not taken: chunk products
-//
-// Lost, a backward pass also adds the terms of dL/dW up again, in one workgroup of a sequence (20 ns a row).
+//   1 x 200   53 /  34 /  62       43 / 25 /  48     not taken
+//   1 x 300   73 /  35 /  83       61 / 26 /  64
+//   6 x 523  122 /  35 / 133      100 / 27 / 102
+//   16 x 600 143 /  37 / 157      116 / 30 / 120
+//   64 x 272  75 /  43 /  93       66 / 36 /  72     not taken
+//   64 x 400 106 /  50 / 122       87 / 41 /  94
+//   64 x 1024 244 / 85 / 262      194 / 69 / 197
+//   16 x 1000 231 / 43 / 240      144 / 34 / 182     backward not taken: chunk products
+// (those not taken measured without the rule)
 inline DensePlan dense_stretches(int B, int L, double step, double products)
 {
     const int most = kStretches / B;

@@ -193,7 +193,7 @@ def test_rows_that_helpers_make_ahead_of_the_chain(L):
 
 # stretches of 32 steps and more (at most 256 of all sequences), whole and short last ones; a gradient on the last step only, where
 # stretches are run again behind the last border, on all steps, and on the first half
-@pytest.mark.parametrize("B,L", [(1, 320), (1, 321), (3, 352), (2, 383), (16, 577), (60, 701), (64, 1024)])
+@pytest.mark.parametrize("B,L", [(1, 320), (1, 321), (1, 2611), (3, 352), (2, 383), (16, 577), (60, 701), (64, 1024)])
 def test_weight_gradient_of_stretches(B, L):
     """dL/dW against the sum in 64 bits over the same dL/du and states.  A sum of n rows in 32 bits, added up in runs of at most 32 and
     then as partial sums: 2^-24 per addition of the largest partial sum, sqrt(additions) of them."""
