@@ -5,6 +5,12 @@ import subprocess
 
 import pytest
 
+#: problems (B, L) whose solves are cut into stretches, and whose backward passes are: test_gpu_dense_stretches.py runs them.  Of one to three
+#: sequences a stretch has 32 steps, so that the last one, or what is run again behind the first, ends at any step of its groups of eight.
+HELPED = [(3, l) for l in (295, 296, 297, 301, 304, 305, 311, 312, 313, 319, 320, 321, 328)]
+FORWARD = HELPED + [(1, 277), (3, 290), (2, 523), (1, 2050), (7, 400), (16, 1000), (60, 701), (100, 700), (128, 513)]
+BACKWARD = HELPED + [(1, 320), (1, 321), (1, 700), (3, 352), (2, 383), (16, 577), (60, 701), (64, 1024), (90, 2001)]
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
@@ -64,3 +70,10 @@ def test_short_sequences_are_not_cut(plan):
     assert plan([(1, 200, False), (64, 272, False), (1, 200, True), (64, 272, True), (16, 1000, True)]) == \
         [(1, 200), (1, 272), (1, 200), (1, 272), (0, 0)]
     assert [n for n, _ in plan([(1, 300, False), (6, 523, False), (64, 1024, False), (6, 523, True), (64, 1024, True)])] == [10, 17, 4, 17, 4]
+
+
+def test_sizes_of_the_gpu_tests_are_cut(plan):
+    for sizes, back in ((FORWARD, False), (BACKWARD, True)):
+        for (b, l), (n, _) in zip(sizes, plan([(b, l, back) for b, l in sizes])):
+            assert n > 1, (b, l, back)
+    assert {ln for _, ln in plan([(b, l, back) for b, l in HELPED for back in (False, True)])} == {32}

@@ -677,3 +677,22 @@ def test_forward_ex_options_travel_with_the_call(P, oracle_mod, cell):
     assert P.solve_plan(tol, 40) == plan_before
     with pytest.raises(RuntimeError, match="INVALID_ARG"):
         P.forward_ex(cell, params, u, h0, tol=tol, max_iter=40, first_block=9)
+
+
+@pytest.mark.parametrize("scale", [4.0, 10.0, 30.0])
+@pytest.mark.parametrize("B,L,H", [(2, 64, 64), (3, 1531, 96), (2, 700, 512)])
+def test_fixed_counts_with_saturated_gates(oracle_mod, B, L, H, scale):
+    """Derivatives near zero: sigmoids and tanh whose arguments are large.  Iterates of a fixed count depend on the Jacobian, which the
+    forward pass forms from products of the gates.  About ten roundings of an evaluation and what a forget gate of 1 adds up, each at
+    most 2^-24 of the largest value: sixteen of them."""
+    import paper_2510_21450_amd as P
+    gen = torch.Generator(device="cuda").manual_seed(int(L + scale))
+    u = torch.randn(B, L, 4, H, generator=gen, device="cuda") * scale
+    h0 = torch.randn(B, 2, H, generator=gen, device="cuda") * 3
+    p = torch.zeros(2, 4, H, device="cuda")
+    p[0] = torch.rand(4, H, generator=gen, device="cuda") * 1.8 - 0.9
+    p[1, 1] = 1.0
+    for k in (1, 2, 3, 4):
+        h = P.forward("lstm_diag", p, u, h0, tol=-1.0, max_iter=k)[0].double().cpu().numpy()
+        ref = oracle_mod.newton("lstm_diag", *(t.double().cpu().numpy() for t in (p, u, h0)), tol=-1.0, max_iter=k)[0]
+        assert np.abs(h - ref.reshape(h.shape)).max() <= 16 * 2.0 ** -24 * np.abs(ref).max(), k
