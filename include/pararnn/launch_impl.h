@@ -217,6 +217,13 @@ template <class Cell, int VEC, int LL, int C, typename UT> constexpr bool backwa
     return !IsRaw<Cell>::value && sizeof(UT) == 2 && VEC == 1 && LL == 1 && C % 8 == 0;
 }
 
+// The plain kernel with streamed rows: of the shapes that choose_tile and backward_tile take for rows of whole cache lines, but the
+// one that it does not pay for (backward_stream in driver.h).
+template <class Cell, int VEC, int LL, int C, int W> constexpr bool backward_stream_offered()
+{
+    return !IsRaw<Cell>::value && VEC == 1 && C != 12 && (LL == 1 || (LL == 2 && C == 8 && W == 8));
+}
+
 // static LDS of the staged backward kernel: its staging rows on top of the plain kernel's.  All of a compute unit's may be
 // taken: one workgroup of LSTM's 64 x 128 tile has 128 KB of rows on their way (8 x 2048 x 2048 bf16 260 -> 206 us).
 template <class Cell, int C, int W> constexpr bool backward_stage_fits_lds()
@@ -232,19 +239,25 @@ hipError_t Kernels<Cell, UT>::backward(const TileCfg &cfg, const BwdArgs &a, hip
 #define PARARNN_CASE(V, LLv, C, W)                                                             \
     if (cfg.vec == V && cfg.ll == LLv && cfg.c == C && cfg.w == W) {                           \
         if constexpr (shape_offered<Cell, V, C>() && backward_fits_lds<Cell, V, LLv, W>()) {   \
-            static int grid_cap[2] = {0, 0};                                                   \
+            static int grid_cap[3] = {0, 0, 0};                                                \
             auto kern = backward_kernel<Cell, V, LLv, C, W, UT, false>;                        \
-            int staged = 0;                                                                    \
+            int form = 0;                                                                      \
+            if constexpr (backward_stream_offered<Cell, V, LLv, C, W>()) {                     \
+                if (a.stream) {                                                                \
+                    kern = backward_kernel<Cell, V, LLv, C, W, UT, false, true>;               \
+                    form = 2;                                                                  \
+                }                                                                              \
+            }                                                                                  \
             if constexpr (backward_stage_offered<Cell, V, LLv, C, UT>()) {                     \
                 if constexpr (backward_stage_fits_lds<Cell, C, W>()) {                         \
                     if (a.stage) {                                                             \
                         kern = backward_kernel<Cell, V, LLv, C, W, UT, true>;                  \
-                        staged = 1;                                                            \
+                        form = 1;                                                              \
                     }                                                                          \
                 }                                                                              \
             }                                                                                  \
-            if (grid_cap[staged] == 0) grid_cap[staged] = persistent_grid(kern, kWave * W, 1 << 30); \
-            const int grid = a.g.n_tiles < grid_cap[staged] ? a.g.n_tiles : grid_cap[staged];  \
+            if (grid_cap[form] == 0) grid_cap[form] = persistent_grid(kern, kWave * W, 1 << 30); \
+            const int grid = a.g.n_tiles < grid_cap[form] ? a.g.n_tiles : grid_cap[form];      \
             hipLaunchKernelGGL(kern, dim3(grid), dim3(kWave * W), 0, st, a);                   \
             return hipGetLastError();                                                          \
         } else {                                                                               \

@@ -94,7 +94,7 @@ struct BwdArgs {
     unsigned long long *rec;
     Ctrl *ctrl;
     int stage;           // the tensors allow the LDS-staged kernel variant (16-byte aligned rows)
-    int stream;          // interior tiles read and write their rows as streams
+    int stream;          // interior tiles read and write their rows as streams, where there is a kernel for it
 };
 
 // ------------------------------------------------------------ small matrix ops
@@ -965,7 +965,11 @@ __global__ __launch_bounds__(256) void init_guess_kernel(const FwdArgs a)
 // smallest unfinished ticket never waits for an unfinished one and every wait
 // ends as before.  Tiles at the ragged edges of the tensor and the first tile of
 // a sequence (its h_{l-1} rows start before the sequence) take the register path.
-template <class Cell, int VEC, int LL, int C, int W, typename UT, bool STAGE = false>
+//
+// STREAM = true (not staged): interior tiles read and write their rows as streams.  A kernel of its own: as a branch at run
+// time, with a third copy of the loads, it made the tiles that are not streamed up to 16 % slower (us, without / with such a
+// branch: ParaLSTM bf16 8 x 700 x 333 26 / 30, 3 x 1531 x 1001 43.5 / 50, 5 x 50761 x 440 812 / 851; GRU fp32 3 x 1531 x 1001 39 / 43).
+template <class Cell, int VEC, int LL, int C, int W, typename UT, bool STAGE = false, bool STREAM = false>
 __global__ __launch_bounds__(kWave *W) void backward_kernel(const BwdArgs a)
 {
     constexpr int S = Cell::S, G = Cell::G, SS = S * S, PR = Cell::PR, NC = Cell::NC;
@@ -1135,9 +1139,9 @@ __global__ __launch_bounds__(kWave *W) void backward_kernel(const BwdArgs a)
         RawU uur[kRaw ? 1 : C][kRaw ? 1 : G], hpr[C][S], ggr[C][S];
         RawF jrr[kRaw ? C : 1][kRaw ? SS : 1];
         const bool full_tile = (lt + 1) * T <= g.L && (cg + 1) * CW <= g.H;
-        auto load_inputs = [&](auto guard, auto stream) {
+        auto load_inputs = [&](auto guard) {
             constexpr bool kGuard = decltype(guard)::value;
-            constexpr int kAux = decltype(stream)::value ? kAuxStream : kAuxNone;
+            constexpr int kAux = STREAM ? kAuxStream : kAuxNone;
 #pragma unroll
             for (int i = 0; i < C; ++i) {
                 const int l = l0 + i;
@@ -1258,8 +1262,8 @@ __global__ __launch_bounds__(kWave *W) void backward_kernel(const BwdArgs a)
                 thread_level(std::true_type{});
                 __builtin_amdgcn_s_waitcnt(0);       // every row has been read before it is overwritten
             } else {
-                if (full_tile) load_inputs(std::false_type{}, std::false_type{});
-                else load_inputs(std::true_type{}, std::false_type{});
+                if (full_tile) load_inputs(std::false_type{});
+                else load_inputs(std::true_type{});
                 thread_level(std::false_type{});
                 __builtin_amdgcn_s_waitcnt(0);
             }
@@ -1269,9 +1273,8 @@ __global__ __launch_bounds__(kWave *W) void backward_kernel(const BwdArgs a)
             if (next_staged) stage_tile(t_next);
             if (t_next < (unsigned int)g.n_tiles) load_params((int)(t_next % (unsigned int)g.n_groups) % g.n_cg, pn);
         } else {
-            if (full_tile && !kRaw && a.stream) load_inputs(std::false_type{}, std::bool_constant<!kRaw>{});
-            else if (full_tile) load_inputs(std::false_type{}, std::false_type{});
-            else load_inputs(std::true_type{}, std::false_type{});
+            if (full_tile) load_inputs(std::false_type{});
+            else load_inputs(std::true_type{});
             thread_level(std::false_type{});
         }
         // chunk aggregate before the wave-level scan overwrites it (nu at the chunk's first step)
@@ -1436,7 +1439,7 @@ __global__ __launch_bounds__(kWave *W) void backward_kernel(const BwdArgs a)
 #pragma unroll
             for (int s = 0; s < S; ++s) nu0[s][v] = n0[s];
         }
-        if (!kRaw && full_tile && a.stream) {
+        if (STAGE && full_tile && a.stream) {
 #pragma unroll
             for (int i = 0; i < C; ++i)
 #pragma unroll
@@ -1447,7 +1450,7 @@ __global__ __launch_bounds__(kWave *W) void backward_kernel(const BwdArgs a)
             for (int i = 0; i < C; ++i)
 #pragma unroll
                 for (int q = 0; q < G; ++q)
-                    buf_store<UT, VEC>(rdu, vu, (unsigned int)(i * G + q) * Hn * (unsigned int)sizeof(UT), duv[i][q]);
+                    buf_store<UT, VEC, STREAM ? kAuxStream : kAuxNone>(rdu, vu, (unsigned int)(i * G + q) * Hn * (unsigned int)sizeof(UT), duv[i][q]);
         } else {
 #pragma unroll
             for (int i = 0; i < C; ++i) {

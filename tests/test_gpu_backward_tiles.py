@@ -29,6 +29,12 @@ def test_tiles_agree(cell, dtype, B, L, H):
     again = P.backward(c, p, u, h0, h, g, want_dh0=True)
     assert all(torch.equal(x, y) for x, y in zip(got, again))
     try:
+        for mode in (1, 2):                      # rows read and written as streams or not: the same bits, whatever the rule takes
+            P.set_streaming(mode)
+            assert all(torch.equal(x, y) for x, y in zip(got, P.backward(c, p, u, h0, h, g, want_dh0=True)))
+    finally:
+        P.set_streaming(0)
+    try:
         P.set_tile(1, 1, 8, 8)
         P.set_staging(False)
         want = P.backward(c, p, u, h0, h, g, want_dh0=True)
