@@ -138,7 +138,8 @@ size_t pararnn_workspace_bytes_fused(int cell, int dtype, int B, int L, int H, i
  * limit this path can be exercised without any wait that does not end.  It bounds
  * the grid-wide barriers of the one-launch tails too, and, times the work there is
  * to wait for (one more limit per 32768 iterations of a tile), the wait of a solve
- * without blocks for the verdicts of its channel groups. */
+ * without blocks for the verdicts of its channel groups.  Stretches of the dense
+ * cell wait for nobody. */
 int pararnn_set_spin_limit(unsigned int polls);
 
 /* Test / tuning hook (host, process-wide): enable = 0 makes pararnn_forward

@@ -1074,8 +1074,9 @@ __global__ __launch_bounds__(256) void dense_guess_kernel(const DenseArgs a, uns
 // ahead of the chain what does not wait for it: the rows of the initial guess and their W h, or the row factors of the
 // backward pass.  Without helpers that is a launch in front (dense_guess_kernel, dense_residual_kernel), which reads u and
 // writes one or two more sets of rows.  us, with the launch / with helpers: forward 64 x 1024 97 / 87.5, 16 x 600 45.6 / 40.6, backward
-// 64 x 1024 97 / 82, 256 x 256 83 / 70.  Forward solves that are not cut keep the launch (64 x 64 30 / 33, 256 x 256 109 / 110), and so
-// do backward passes of more sequences than units, where a unit's second workgroup has no room for so many waves (300 x 200 73 / 95).
+// 64 x 1024 97 / 82, 256 x 256 83 / 70.  Forward solves that are not cut keep the launch (64 x 64 30 / 33, 256 x 256 109 / 110, both with a
+// fence in every wave behind a block of iterations; with one of a workgroup the launch has 24 and 80), and so do backward passes of
+// more sequences than units, where a unit's second workgroup has no room for so many waves (300 x 200 73 / 95).
 constexpr int kChain = 4, kMover = 4, kHelpers = 5, kWaves = 9;
 constexpr int kHelperUnits = 256;     // compute units
 constexpr int wave_threads(bool help) { return (help ? kWaves : kHelpers) * kWave; }
