@@ -86,6 +86,22 @@ inline int backward_stream(size_t bytes, bool pays)
     return pays && 2 * bytes >= 3 * kMemCacheBytes ? 1 : 0;
 }
 
+// Queues of a backward pass's tiles, one for each XCD.  Rows that are no multiple of 64 bytes: what two channel groups share of a
+// cache line is read and written by both, and where they are on different XCDs comes into two L2s and leaves them in two pieces.
+// With the queues neighbouring groups are on one XCD (GRU 16 x 4096 x 1025: read 1.86 -> 1.34 GB, written 0.88 -> 0.82; bf16 1.25 ->
+// 0.67, 0.52 -> 0.46).  What a launch pays: who finds its queue empty looks at the others and goes on with one that is not, a few us;
+// and a queue has whole groups, so there have to be enough of them.  us, one queue / eight:
+//   from 512 MB on    GRU fp32 16 x 4096 x 1021 551 / 464, 64 x 4096 x 300 666 / 555, 1 x 8192 x 4091 264 / 245, bf16 16 x 4096 x 1021 354 / 317; LSTM
+//                     fp32 8 x 1000 x 1531 160 / 157, 32 x 512 x 763 174 / 163, bf16 2 x 30000 x 1001 506 / 483; ParaLSTM 33 x 1999 x 500 342 / 328,
+//                     bf16 16 x 4096 x 1021 521 / 464; rot_tanh fp32 9 x 700 x 3333 175 / 176, bf16 1 x 8192 x 4091 190 / 191
+//   less              GRU fp32 32 x 512 x 763 114 / 109, 3 x 1531 x 1001 44 / 48, bf16 9 x 700 x 3333 117 / 123; rot_tanh 8 x 1000 x 1531 108 / 117
+//   few groups        GRU fp32 11 (1 x 65536 x 700) 368 / 429, 18 560 / 611, 24 742 / 723, 33 1034 / 1010, 40 1135 / 1058; bf16 28 202 / 214
+//   rows of 64 bytes  GRU fp32 1 x 60000 x 2800 1016 / 1129, LSTM 1625 / 1720
+inline bool backward_queues(size_t bytes, size_t row_bytes, int groups)
+{
+    return settings().streaming == 0 && row_bytes % 64 != 0 && bytes >= 2 * kMemCacheBytes && groups >= 32 && 32 * ((groups + 7) / 8) <= 5 * groups;
+}
+
 // Tile shape for a problem.  The table is the result of sweeps on MI355X over
 // the compiled shapes (fp32 and bf16 storage, forward and backward, GRU and
 // LSTM at 2^25..2^30 timestep-channels): one channel per lane
@@ -939,6 +955,7 @@ int backward_pass(const CellInfo &ci, int dtype, const float *params, const void
               (settings().tile[0] > 0 || backward_staged(ci, B, L, H));
     a.stream = backward_stream((size_t)B * L * H * esz * (2 * ci.G + 2 * ci.S),
                                lo.cfg.c != 12 && H * esz % 128 == 0 && aligned(u, 128) && aligned(h, 128) && aligned(dL_dh, 128) && aligned(dL_du, 128));
+    if (!a.stage && !a.stream && backward_queues((size_t)B * L * H * esz * (2 * ci.G + 2 * ci.S), H * esz, lo.g.n_groups)) a.stream = 2;
     const int rc = backward_diag<Cell>(ci, dtype, lo, a, st, dL_dparams);
     if (rc != PARARNN_OK) workspace_forget(workspace);
     return rc;

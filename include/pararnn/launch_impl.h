@@ -224,6 +224,12 @@ template <class Cell, int VEC, int LL, int C, int W> constexpr bool backward_str
     return !IsRaw<Cell>::value && VEC == 1 && C != 12 && (LL == 1 || (LL == 2 && C == 8 && W == 8));
 }
 
+// ... and the one with a queue for each XCD: of the shapes that are taken for rows of other lengths.
+template <class Cell, int VEC, int LL, int C, int W> constexpr bool backward_queues_offered()
+{
+    return !IsRaw<Cell>::value && Cell::S <= 2 && VEC == 1 && (LL == 1 || (LL == 2 && C == 8 && W == 8));
+}
+
 // static LDS of the staged backward kernel: its staging rows on top of the plain kernel's.  All of a compute unit's may be
 // taken: one workgroup of LSTM's 64 x 128 tile has 128 KB of rows on their way (8 x 2048 x 2048 bf16 260 -> 206 us).
 template <class Cell, int C, int W> constexpr bool backward_stage_fits_lds()
@@ -239,13 +245,19 @@ hipError_t Kernels<Cell, UT>::backward(const TileCfg &cfg, const BwdArgs &a, hip
 #define PARARNN_CASE(V, LLv, C, W)                                                             \
     if (cfg.vec == V && cfg.ll == LLv && cfg.c == C && cfg.w == W) {                           \
         if constexpr (shape_offered<Cell, V, C>() && backward_fits_lds<Cell, V, LLv, W>()) {   \
-            static int grid_cap[3] = {0, 0, 0};                                                \
+            static int grid_cap[4] = {0, 0, 0, 0};                                             \
             auto kern = backward_kernel<Cell, V, LLv, C, W, UT, false>;                        \
             int form = 0;                                                                      \
             if constexpr (backward_stream_offered<Cell, V, LLv, C, W>()) {                     \
-                if (a.stream) {                                                                \
+                if (a.stream == 1) {                                                           \
                     kern = backward_kernel<Cell, V, LLv, C, W, UT, false, true>;               \
                     form = 2;                                                                  \
+                }                                                                              \
+            }                                                                                  \
+            if constexpr (backward_queues_offered<Cell, V, LLv, C, W>()) {                     \
+                if (a.stream == 2) {                                                           \
+                    kern = backward_kernel<Cell, V, LLv, C, W, UT, false, false, true>;        \
+                    form = 3;                                                                  \
                 }                                                                              \
             }                                                                                  \
             if constexpr (backward_stage_offered<Cell, V, LLv, C, UT>()) {                     \

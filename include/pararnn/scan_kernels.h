@@ -94,7 +94,7 @@ struct BwdArgs {
     unsigned long long *rec;
     Ctrl *ctrl;
     int stage;           // the tensors allow the LDS-staged kernel variant (16-byte aligned rows)
-    int stream;          // interior tiles read and write their rows as streams, where there is a kernel for it
+    int stream;          // where there is a kernel for it: 1 interior tiles read and write their rows as streams, 2 tiles come from a queue for each XCD
 };
 
 // ------------------------------------------------------------ small matrix ops
@@ -944,6 +944,19 @@ __global__ __launch_bounds__(256) void init_guess_kernel(const FwdArgs a)
 }
 
 
+// Queues of a backward launch's tiles, one for each XCD, whose workgroups (block index modulo eight) then work on neighbouring
+// channel groups.  A queue hands out the tiles of its own run of groups, groups fastest, so a tile waits for smaller tickets of
+// its own queue only.
+constexpr int kTileQueues = 8;
+struct TileQueue { int first, n; };          // its groups
+__device__ __forceinline__ TileQueue tile_queue_of(int n_groups, int no)
+{
+    const int per = n_groups / kTileQueues, more = n_groups - per * kTileQueues;
+    return {no * per + min(no, more), per + (no < more ? 1 : 0)};
+}
+// tickets drawn: words of the control block behind what other launches use
+__device__ __forceinline__ unsigned int *tile_queue(Ctrl *ctrl, int no) { return reinterpret_cast<unsigned int *>(ctrl) + 32 + 4 * no; }
+
 // ======================================================================
 // Backward (Eq. (6)) as one reverse scan.  With nu_l = J_l^T lam_l the adjoint
 // recurrence lam_{l-1} = J_l^T lam_l + g_{l-1} reads
@@ -969,7 +982,9 @@ __global__ __launch_bounds__(256) void init_guess_kernel(const FwdArgs a)
 // STREAM = true (not staged): interior tiles read and write their rows as streams.  A kernel of its own: as a branch at run
 // time, with a third copy of the loads, it made the tiles that are not streamed up to 16 % slower (us, without / with such a
 // branch: ParaLSTM bf16 8 x 700 x 333 26 / 30, 3 x 1531 x 1001 43.5 / 50, 5 x 50761 x 440 812 / 851; GRU fp32 3 x 1531 x 1001 39 / 43).
-template <class Cell, int VEC, int LL, int C, int W, typename UT, bool STAGE = false, bool STREAM = false>
+//
+// QUEUES = true: a queue of tiles for each XCD.  A kernel of its own too: registers for the queue's place cost the others 5 to 8 %.
+template <class Cell, int VEC, int LL, int C, int W, typename UT, bool STAGE = false, bool STREAM = false, bool QUEUES = false>
 __global__ __launch_bounds__(kWave *W) void backward_kernel(const BwdArgs a)
 {
     constexpr int S = Cell::S, G = Cell::G, SS = S * S, PR = Cell::PR, NC = Cell::NC;
@@ -1083,6 +1098,11 @@ __global__ __launch_bounds__(kWave *W) void backward_kernel(const BwdArgs a)
         if (t < (unsigned int)g.n_tiles) load_params((int)(t % (unsigned int)g.n_groups) % g.n_cg, pn);
     }
 
+    if constexpr (QUEUES) {
+        if (threadIdx.x == 0) s_first[0] = blockIdx.x & (kTileQueues - 1);
+        __syncthreads();
+    }
+
     for (;;) {
         if constexpr (STAGE) {
             // the workgroup's third ticket, read after the first barrier below; the barrier here keeps
@@ -1090,6 +1110,35 @@ __global__ __launch_bounds__(kWave *W) void backward_kernel(const BwdArgs a)
             lds_barrier();
             if (t >= (unsigned int)g.n_tiles) break;
             if (threadIdx.x == 0) s_ticket = atomicAdd(&ctrl->ticket, 1u);
+        } else if constexpr (QUEUES) {
+            // s_first: the queue this workgroup draws from, and which of them are not through
+            for (;;) {
+                const unsigned int no = __builtin_amdgcn_readfirstlane(s_first[0]);
+                const TileQueue own = tile_queue_of(g.n_groups, (int)no);
+                if (threadIdx.x == 0) s_ticket = atomicAdd(tile_queue(ctrl, (int)no), 1u);
+                __syncthreads();
+                t = __builtin_amdgcn_readfirstlane(s_ticket);
+                if (t < (unsigned int)own.n * (unsigned int)g.n_lt) {
+                    t = t / (unsigned int)own.n * (unsigned int)g.n_groups + (unsigned int)own.first + t % (unsigned int)own.n;
+                    break;
+                }
+                // this queue is through: on to the next one that is not
+                t = (unsigned int)g.n_tiles;
+                if (threadIdx.x < kTileQueues) {
+                    int other = (int)threadIdx.x;
+                    asm volatile("" : "+v"(other));          // nothing of this is kept in registers from tile to tile
+                    const unsigned int at = __hip_atomic_load(tile_queue(ctrl, other), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    const int n = tile_queue_of(g.n_groups, other).n;
+                    const unsigned int left = (unsigned int)__ballot(at < (unsigned int)n * (unsigned int)g.n_lt);
+                    if (threadIdx.x == 0) {
+                        s_first[1] = left;
+                        if (left) s_first[0] = (no + __builtin_ctz(left >> no | left << (kTileQueues - no))) & (kTileQueues - 1);
+                    }
+                }
+                __syncthreads();
+                if (__builtin_amdgcn_readfirstlane(s_first[1]) == 0u) break;
+            }
+            if (t >= (unsigned int)g.n_tiles) break;
         } else {
             if (threadIdx.x == 0) s_ticket = atomicAdd(&ctrl->ticket, 1u);
             __syncthreads();
