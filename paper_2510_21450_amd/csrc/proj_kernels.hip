@@ -1806,8 +1806,8 @@ __global__ __launch_bounds__(512) void proj_dw_dma_kernel(const DwArgs a)
 }
 
 // ------------------------------- dWx and dbias of narrow heads: a whole gate of a head per workgroup
-// The same sums for heads of at most 256 channels (d_h = 64 KB): a workgroup holds all d_h x d_h sums of one gate of one head over a
-// range of rows, so that du is read once and x once per gate, and no part of a tile lies idle.  Rows go to LDS as they
+// The same sums for heads of at most 256 channels: a workgroup holds all d_h x d_h sums of one gate of one head over a
+// range of rows, so that du is read once and x once per gate, and no part of a tile lies idle (wider heads: below).  Rows go to LDS as they
 // are, NS steps deep.  A wave owns IB x JB blocks of 32 x 32 sums; MS waves share a part and take the 16-row slices of a
 // step in turn, their sums are added at the end.
 //
@@ -1815,31 +1815,39 @@ __global__ __launch_bounds__(512) void proj_dw_dma_kernel(const DwArgs a)
 //            128 bytes where a row is an odd number of those, for dw_swz does not fit it
 //   fp32     a lane reads its channel of eight rows, 32 neighbouring channels at a time, and rounds them
 //   dbias    is added up from the fragments of du (unrounded in fp32; eight rows before they join the sum); the waves that share a part's du blocks take one each
+//   tiles    heads of more than 256 in four of half a head, 160 to 256 wide: no part of a tile idle, and du and x read twice, through the
+//            L2 of one XCD; of three gates 15000 x 320 in fp32 60 -> 40 us, 60000 x 320 159 -> 119, four gates of two heads 15000 x 384
+//            136 -> 86, bf16 142 -> 85 (four heads of 320), 160 -> 92 (of 384), fp32 448 and 512 60000 x 1 260 -> 229, 282 -> 250.  Bound by the
+//            reads from LDS and the conversions of a 16-row slice, which nothing else of the wave overlaps
 //   bound    by memory, and where ranges are many by their sums: three gates, 65536 x 512 in heads of 64, bf16: 110 -> 55 us (4.9 TB/s);
 //            40000 x 512 in heads of 128, four gates: 67 -> 41; fp32: 16000 x 1024 in heads of 256 117 -> 100, 6993 x 768 in
 //            heads of 192, four gates: 57 -> 35, of which the sums of 16 ranges, written and added, are half
-template <typename AT, int KB> struct DwRows {
-    static constexpr int E = sizeof(AT), K = 64 * KB, ROW = K * E;
-    static constexpr int MS = KB == 1 ? (E == 2 ? 8 : 4) : KB == 2 ? 2 : 1;
-    static constexpr int IB = KB >= 3 ? KB : 2, JB = 2, WI = 2 * KB / IB, WJ = KB, WAVES = MS * WI * WJ;
-    static constexpr int R = E == 2 ? (KB == 1 ? 128 : KB == 2 ? 64 : 32) : (KB == 1 ? 64 : KB == 4 ? 16 : 32);
-    static constexpr int OP = R * ROW, STAGE = 2 * OP, NS = STAGE > 40 * 1024 ? 3 : 4;
+template <typename AT, int NB> struct DwRows {              // tiles of 32 NB channels
+    static constexpr int E = sizeof(AT), K = 32 * NB, ROW = K * E;
+    static constexpr bool ODD = NB & 1;
+    static constexpr int MS = NB == 2 ? (E == 2 ? 8 : 4) : NB == 4 ? 2 : 1;
+    static constexpr int IB = ODD ? NB : NB >= 6 ? NB / 2 : 2, JB = ODD ? 1 : 2, WI = NB / IB, WJ = NB / JB, WAVES = MS * WI * WJ;
+    static constexpr int R = E == 2 ? (NB == 2 ? 128 : NB == 4 ? 64 : 32) : (NB == 2 ? 64 : NB >= 7 ? 16 : 32);
+    static constexpr int OP = R * ROW, STAGE = 2 * OP, NS = STAGE >= 40 * 1024 ? 3 : 4;
     static constexpr int N = OP / 1024 / WAVES;             // copies of each operand of a wave per step
     static constexpr int SLICES = R / 16 / MS;              // of a wave per step
     static constexpr int DB = (IB + WJ - 1) / WJ;           // du blocks of which a wave adds up the rows
     static_assert(N * 1024 * WAVES == OP && SLICES >= 1 && (MS == 1 || WAVES * 16384 <= NS * STAGE), "");
-    static __device__ __forceinline__ int swz(int row) { return E == 4 ? 0 : (KB & 1) ? 2 * (row & 3) : dw_swz(row); }
+    // (rows of an odd number of 64 bytes lie in different parts of the banks by themselves)
+    static __device__ __forceinline__ int swz(int row) { return E == 4 || ODD ? 0 : (NB & 2) ? 2 * (row & 3) : dw_swz(row); }
 };
 
-template <typename AT, int KB> __global__ __launch_bounds__((64 * DwRows<AT, KB>::WAVES)) void proj_dw_rows_kernel(const DwArgs a)
+template <typename AT, int NB> __global__ __launch_bounds__((64 * DwRows<AT, NB>::WAVES)) void proj_dw_rows_kernel(const DwArgs a)
 {
-    typedef DwRows<AT, KB> S;
+    typedef DwRows<AT, NB> S;
     constexpr int E = S::E, K = S::K, R = S::R, ROW = S::ROW, NS = S::NS, N = S::N, IB = S::IB, JB = S::JB, MS = S::MS, DB = S::DB;
     __shared__ __attribute__((aligned(16))) unsigned char s_op[NS * S::STAGE];
     __shared__ float s_db[MS][K];
-    // numbered as above: the gates of a (head, range) on one XCD at a time
+    // numbered as above: the tiles and gates of a (head, range) on one XCD at a time
     int id = (int)(blockIdx.x & 7) * a.per_xcd + (int)(blockIdx.x >> 3);
     if (id >= a.n_blocks) return;
+    const int tj = id % a.tiles; id /= a.tiles;
+    const int ti = id % a.tiles; id /= a.tiles;
     const int g = id % a.G; id /= a.G;
     const int head = id % a.heads;
     const int s = id / a.heads;
@@ -1854,8 +1862,8 @@ template <typename AT, int KB> __global__ __launch_bounds__((64 * DwRows<AT, KB>
 
     // ---- the copying side
     const long long ld_du = (long long)a.G * a.H * E, ld_x = (long long)a.H * E;
-    unsigned long long p_du = (unsigned long long)a.du + (unsigned long long)(m_begin * ld_du + ((long long)g * a.H + head * K) * E);
-    unsigned long long p_x = (unsigned long long)a.x + (unsigned long long)(m_begin * ld_x + (long long)head * ROW);
+    unsigned long long p_du = (unsigned long long)a.du + (unsigned long long)(m_begin * ld_du + ((long long)g * a.H + head * a.dh + ti * K) * E);
+    unsigned long long p_x = (unsigned long long)a.x + (unsigned long long)(m_begin * ld_x + ((long long)head * a.dh + tj * K) * E);
     int left = rows;
     unsigned int va[N], vb[N];
 #pragma unroll
@@ -1912,7 +1920,7 @@ template <typename AT, int KB> __global__ __launch_bounds__((64 * DwRows<AT, KB>
         }
         return f;
     };
-    const bool do_db = a.dbpart != nullptr;
+    const bool do_db = a.dbpart && tj == 0;
     f16v acc[JB][IB];
 #pragma unroll
     for (int j = 0; j < JB; ++j)
@@ -1921,8 +1929,8 @@ template <typename AT, int KB> __global__ __launch_bounds__((64 * DwRows<AT, KB>
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[j][i][v] = 0.0f;
     // Sums of 512 rows of a wave at a time, added up: a range here is up to four times as long as with the smaller tiles, and one
-    // chain of roundings over it would be less exact.  Heads of 256 have no registers for it; their ranges are no longer.
-    constexpr bool TWO = KB < 4;
+    // chain of roundings over it would be less exact.  Tiles of 224 and more have no registers for it; their ranges are no longer.
+    constexpr bool TWO = NB < 7;
     f16v sum[TWO ? JB : 1][TWO ? IB : 1];
     if constexpr (TWO) {
 #pragma unroll
@@ -1983,10 +1991,10 @@ template <typename AT, int KB> __global__ __launch_bounds__((64 * DwRows<AT, KB>
             for (int i = 0; i < IB; ++i) acc[j][i] = sum[j][i];
     }
 
-    float *out = a.part + (((long long)s * a.G + g) * a.H + (long long)head * K) * K;
+    float *out = a.part + (((long long)s * a.G + g) * a.H + (long long)head * a.dh + ti * K) * a.dh + tj * K;
     auto put = [&](int i, int j, int q, const f4v &o) {
         const int row = 32 * (IB * wi + i) + l32, col = 32 * (JB * wj + j) + 8 * q + 4 * half;
-        *reinterpret_cast<f4v *>(out + (long long)row * K + col) = o;
+        *reinterpret_cast<f4v *>(out + (long long)row * a.dh + col) = o;
     };
     if constexpr (MS > 1) {
         // the sums of the waves that share a part, [part][wave][four of its 64 registers][lane]; each wave adds up a share
@@ -2031,7 +2039,7 @@ template <typename AT, int KB> __global__ __launch_bounds__((64 * DwRows<AT, KB>
             float t = 0.0f;
 #pragma unroll
             for (int r = 0; r < MS; ++r) t += s_db[r][c];
-            a.dbpart[((long long)s * a.G + g) * a.H + (long long)head * K + c] = t;
+            a.dbpart[((long long)s * a.G + g) * a.H + (long long)head * a.dh + ti * K + c] = t;
         }
     }
 }
@@ -2147,11 +2155,16 @@ bool dw_dma_shape_ok(int M, int H, int G, int dh)
 // same.  fp32: more sums have to be written and added, for a range is all of a compute unit's work, and that pays
 // with enough rows: by gates x heads x rows, heads of 128 and 192 24000 0.9-1.05 times as fast, 48000 1.1-1.2, a million
 // 1.6; of 256, 96000 0.94, 128000 to a million 1.1-1.2; of 64, level at 600 rows; one or two gates in all never.
+// Heads of 320 to 512 in four tiles of half a head, of the time with the tiles of 128 (bf16 from 448 on: those of 256, which are
+// full), by gates x heads x rows: bf16 320 and 384 5000 0.98-1.09, 12000 0.89-1.02, 18000 0.77-0.8, 32000 and more 0.54-0.68; fp32 7000
+// 1.03-1.2, 12000 0.99-1.06, 18000 0.88-0.92, 32000 and more 0.63-0.84; fp32 448 and 512 18000 1.17-1.2, 48000 0.94-1.08, 120000 and more 0.81-0.9.
+int dw_rows_tiles(int dh) { return dh > 256 ? 2 : 1; }
 bool dw_rows_shape_ok(int M, int H, int G, int dh, bool bf)
 {
-    if (dh % 64 || dh > 256 || M <= dw_one_range || (long long)G * H >= (1 << 22)) return false;
-    if (bf) return dh < 256;
+    if (dh % 64 || dh > 512 || M <= dw_one_range || (long long)G * H >= (1 << 22)) return false;
     const int units = G * (H / dh);
+    if (dh > 256) return (bf ? dh <= 384 : true) && (double)units * M >= (bf ? 12000.0 : dh <= 384 ? 15000.0 : 60000.0);
+    if (bf) return dh < 256;
     return dh == 64 || (units >= 3 && (double)units * M >= (dh == 256 ? 120000.0 : 40000.0));
 }
 
@@ -2159,11 +2172,12 @@ bool dw_rows_shape_ok(int M, int H, int G, int dh, bool bf)
 void dw_rows_split(int M, int G, int H, int dh, int n_heads, bool bf, int least, int *S, int *rows_per_split)
 {
     const int cus = device_cu_count() > 0 ? device_cu_count() : 256;
-    const int R = bf ? (dh == 64 ? 128 : dh == 128 ? 64 : 32) : (dh == 64 ? 64 : dh == 256 ? 16 : 32);
-    const int units = G * n_heads;
-    const double nw = (double)G * H * dh, row_us = 2.0 * dh * (bf ? 2 : 4) / 23e3;
+    const int tiles = dw_rows_tiles(dh), width = dh / tiles;
+    const int R = bf ? (dh == 64 ? 128 : dh == 128 ? 64 : 32) : (dh == 64 ? 64 : width >= 224 ? 16 : 32);
+    const int units = G * n_heads * tiles * tiles;
+    const double nw = (double)G * H * dh, row_us = 2.0 * width * (bf ? 2 : 4) / 23e3;
     double best_us = 0.0;
-    if (dh < 256) least = 1;                            // (heads of 256: no longer ranges than the smaller tiles have)
+    if (width < 224) least = 1;                         // (wider tiles: no longer ranges than the smaller ones have)
     for (int s = least; s <= 96; ++s) {
         int rps = (M + s - 1) / s;
         rps = (rps + R - 1) / R * R;
@@ -2359,15 +2373,19 @@ bool dx_rows_shape(int M, int H, int G, int n_heads, bool bf, DxArgs *a, int *bl
     return true;
 }
 
-template <typename AT> hipError_t launch_dw_rows(const DwArgs &a, int kb, int blocks, hipStream_t st)
+template <typename AT> hipError_t launch_dw_rows(const DwArgs &a, int nb, int blocks, hipStream_t st)
 {
-#define PARARNN_DW_ROWS(KB) hipLaunchKernelGGL((proj_dw_rows_kernel<AT, KB>), dim3((unsigned)blocks), dim3((64 * DwRows<AT, KB>::WAVES)), 0, st, a)
-    switch (kb) {
-        case 1: PARARNN_DW_ROWS(1); break;
+#define PARARNN_DW_ROWS(NB) hipLaunchKernelGGL((proj_dw_rows_kernel<AT, NB>), dim3((unsigned)blocks), dim3((64 * DwRows<AT, NB>::WAVES)), 0, st, a)
+    switch (nb) {
         case 2: PARARNN_DW_ROWS(2); break;
-        case 3: PARARNN_DW_ROWS(3); break;
+        case 4: PARARNN_DW_ROWS(4); break;
+        case 5: PARARNN_DW_ROWS(5); break;
+        case 6: PARARNN_DW_ROWS(6); break;
+        case 7:
+            if constexpr (sizeof(AT) == 4) PARARNN_DW_ROWS(7);
+            break;
         default:
-            if constexpr (sizeof(AT) == 4) PARARNN_DW_ROWS(4);
+            if constexpr (sizeof(AT) == 4) PARARNN_DW_ROWS(8);
     }
 #undef PARARNN_DW_ROWS
     return hipGetLastError();
@@ -2481,12 +2499,13 @@ int proj_backward(int dtype, const void *x, const float *Wx, const void *du, int
             if (dbias) a.dbpart = dbias;
         }
         a.rows_per_split = rows_kernel ? lo.rows_per_split3 : copy_kernel ? lo.rows_per_split2 : lo.rows_per_split;
-        a.tiles = rows_kernel ? 1 : copy_kernel ? lo.tiles2 : lo.tiles;
+        a.tiles = rows_kernel ? dw_rows_tiles(dh) : copy_kernel ? lo.tiles2 : lo.tiles;
         a.n_blocks = a.tiles * a.tiles * n_heads * G * a.S;
         a.per_xcd = (a.n_blocks + 7) / 8;
         blocks = 8 * a.per_xcd;
         if (rows_kernel) {
-            if ((bf ? launch_dw_rows<unsigned short>(a, dh / 64, blocks, st) : launch_dw_rows<float>(a, dh / 64, blocks, st)) != hipSuccess) return PARARNN_HIP_ERROR;
+            const int nb = dh / a.tiles / 32;
+            if ((bf ? launch_dw_rows<unsigned short>(a, nb, blocks, st) : launch_dw_rows<float>(a, nb, blocks, st)) != hipSuccess) return PARARNN_HIP_ERROR;
         } else if (copy_kernel) hipLaunchKernelGGL(proj_dw_dma_kernel, dim3(blocks), dim3(512), 0, st, a);
         else if (bf) hipLaunchKernelGGL(proj_dw_kernel<unsigned short>, dim3(blocks), dim3(256), 0, st, a);
         else hipLaunchKernelGGL(proj_dw_kernel<float>, dim3(blocks), dim3(256), 0, st, a);
