@@ -97,9 +97,13 @@ inline int backward_stream(size_t bytes, bool pays)
 //   less              GRU fp32 32 x 512 x 763 114 / 109, 3 x 1531 x 1001 44 / 48, bf16 9 x 700 x 3333 117 / 123; rot_tanh 8 x 1000 x 1531 108 / 117
 //   few groups        GRU fp32 11 (1 x 65536 x 700) 368 / 429, 18 560 / 611, 24 742 / 723, 33 1034 / 1010, 40 1135 / 1058; bf16 28 202 / 214
 //   rows of 64 bytes  GRU fp32 1 x 60000 x 2800 1016 / 1129, LSTM 1625 / 1720
+inline bool backward_queues_pay(size_t bytes, size_t row_bytes, int groups)
+{
+    return row_bytes % 64 != 0 && bytes >= 2 * kMemCacheBytes && groups >= 32 && 32 * ((groups + 7) / 8) <= 5 * groups;
+}
 inline bool backward_queues(size_t bytes, size_t row_bytes, int groups)
 {
-    return settings().streaming == 0 && row_bytes % 64 != 0 && bytes >= 2 * kMemCacheBytes && groups >= 32 && 32 * ((groups + 7) / 8) <= 5 * groups;
+    return settings().streaming == 0 && backward_queues_pay(bytes, row_bytes, groups);
 }
 
 // Tile shape for a problem.  The table is the result of sweeps on MI355X over
@@ -151,6 +155,28 @@ inline TileCfg choose_tile(const CellInfo &ci, int dtype, bool backward, int H, 
     return cfg;
 }
 
+// Channels that groups of `width` work on for H of them.
+inline int padded_channels(int H, int width) { return (H + width - 1) / width * width; }
+
+// The tile of the fused blocks of a scalar or 2x2 cell.  A group wider than H works for channels that are not there, and a short
+// tile makes a long chain of carries: so of 8 channels x 512 steps, 16 x 256, 32 and 64 the one whose channels, times what one
+// costs in it, are the fewest.  A channel costs 1.25 in groups of 8 and 1.15 in groups of 16 of what it does in 64 (scans between
+// the segments of a wave).  us, before / now: GRU fp32 12 x 48925 x 8 230 / 80, 42 x 3207 x 8 113 / 38, 31 x 35271 x 16 333 / 179, 18 x
+// 12000 x 24 94 / 81, 8 x 11690 x 40 83 / 68, 1 x 8609 x 72 44 / 35, 30 x 20768 x 96 509 / 442; LSTM bf16 12 x 48925 x 8 460 / 200, 31 x 35271 x
+// 16 700 / 543, 3 x 20000 x 48 173 / 153; ParaLSTM fp32 12 x 48925 x 8 439 / 182, 18 x 12000 x 24 164 / 127, 2 x 20000 x 288 227 / 199.
+inline TileCfg fused_tile(const CellInfo &ci, int L, int H, const TileCfg &table)
+{
+    if (ci.S > 2 || settings().tile[0] > 0 || L <= 256 || H > 320) return table;
+    struct Width { int channels; float costs; TileCfg tile; };
+    const bool two = ci.S == 2;
+    const Width w[] = {{64, 1.0f, two ? TileCfg{1, 1, 16, 4} : TileCfg{1, 1, 12, 8}}, {32, two ? 0.98f : 1.08f, two ? TileCfg{1, 2, 16, 4} : TileCfg{1, 2, 8, 8}},
+                       {16, 1.15f, {1, 4, 8, 8}}, {8, 1.25f, {1, 8, 8, 8}}};
+    const Width *best = w;
+    for (const Width &x : w)
+        if (x.costs * (float)padded_channels(H, x.channels) < best->costs * (float)padded_channels(H, best->channels)) best = &x;
+    return best->tile;
+}
+
 // The tile of a backward pass of a scalar or 2x2 cell with carry records, by sweeps over 300 to 60000 steps of 2048 to 65792
 // channels in all (times / times of choose_tile's shape with its rows staged whenever they can be).  Rows of whole lines
 // (64 channels, bf16) are worth staging once the tensors are far larger than the last-level cache; before that, and for
@@ -185,11 +211,33 @@ inline bool backward_tile_fits(const CellInfo &ci, const TileCfg &t)
     const size_t rows = (size_t)(ci.S * ci.S + ci.S > ci.PR ? ci.S * ci.S + ci.S : ci.PR);
     return (t.w * rows + ci.S) * (size_t)(64 / t.ll) * t.vec * sizeof(float) + 16 <= 65536;
 }
+// Narrow rows, as the fused blocks' tile above (a pass is bound by memory sooner, so that narrow groups cost more).  us, before /
+// now: GRU fp32 12 x 48925 x 8 190 / 48, 42 x 3207 x 8 67 / 19, 31 x 35271 x 16 352 / 163, 18 x 12000 x 24 70 / 54, 30 x 20768 x 96 434 / 401; LSTM bf16 12 x
+// 48925 x 8 179 / 62, 31 x 35271 x 16 345 / 171, 18 x 12000 x 24 82 / 68, 3 x 20000 x 48 52 / 42; ParaLSTM fp32 60 x 16549 x 8 289 / 101, 31 x 35271 x 16
+// 432 / 196, 30 x 20768 x 96 603 / 576; rot_tanh bf16 30 x 20768 x 96 494 / 351.  Groups of 16 for more than 16 channels on small tensors only: LSTM
+// fp32 64 x 12000 x 24 342, of 32 273.  Not where the tiles are in queues, for which these shapes are not built.
+inline TileCfg backward_tile_narrow(const CellInfo &ci, int dtype, int B, int L, int H, const TileCfg &wide)
+{
+    const bool bf = dtype == PARARNN_BF16, few = ci.S == 1 || ci.G <= 2;
+    const TileCfg x8 = {1, 8, 8, 8}, x16 = {1, 4, 8, 8}, x32 = ci.S == 1 ? TileCfg{1, 2, 8, 16} : few && bf ? TileCfg{1, 2, 16, 4} : TileCfg{1, 2, 8, 8};
+    if (L <= 256) return wide;
+    // (less than a workgroup of the short tile for each unit: LSTM bf16 7 x 1404 x 8 16.8, of 512 steps 19.2; 8 x 1800 18.4 / 17.8)
+    if (H <= 8) return ci.S == 2 && (double)B * L < 12800.0 ? wide : x8;
+    if (H <= 16) return x16;
+    const bool take16 = bf && !few && (double)B * L * H < 8e6;
+    if (H <= 32) return take16 ? x16 : x32;
+    const size_t row = (size_t)H * (bf ? 2 : 4);
+    if (H > 320 || backward_queues_pay((size_t)B * L * row * (2 * ci.G + 2 * ci.S), row, B * ((H + 63) / 64))) return wide;
+    const float c64 = (float)padded_channels(H, 64), c32 = (few ? (bf ? 1.05f : 1.2f) : 1.25f) * (float)padded_channels(H, 32),
+                c16 = 1.12f * (float)padded_channels(H, 16);
+    if (take16 && c16 < c64 && c16 < c32) return x16;
+    return c32 < c64 ? x32 : wide;
+}
 inline TileCfg backward_tile(const CellInfo &ci, int dtype, int B, int L, int H, const TileCfg &table)
 {
-    if (ci.S > 2 || H <= 32 || settings().tile[0] > 0) return table;
-    const TileCfg t = backward_tile_by_size(ci, dtype, B, L, H, table);
-    return backward_tile_fits(ci, t) ? t : table;
+    if (ci.S > 2 || settings().tile[0] > 0) return table;
+    const TileCfg wide = H <= 32 ? table : backward_tile_by_size(ci, dtype, B, L, H, table), t = backward_tile_narrow(ci, dtype, B, L, H, wide);
+    return backward_tile_fits(ci, t) ? t : backward_tile_fits(ci, wide) ? wide : table;
 }
 // ... and whether its rows are staged.  3x3 blocks: one workgroup of 64 x 64 steps on a compute unit then, for its rows take 99 KB of
 // LDS; tri_tanh staged / plain: 2e6 to 4e6 elements 1.05-1.27, 8e6 0.98-1.06, 1.2e7 0.95-1.0, 6e7 0.85-0.89.
@@ -235,6 +283,7 @@ inline Layout make_layout(const CellInfo &ci, int dtype, int B, int L, int H, bo
     Layout lo;
     lo.cfg = force ? *force : choose_tile(ci, dtype, backward, H, align_elems, fused);
     if (backward && !force) lo.cfg = backward_tile(ci, dtype, B, L, H, lo.cfg);
+    if (fused && !force) lo.cfg = fused_tile(ci, L, H, lo.cfg);
     const int CW = (kWave / lo.cfg.ll) * lo.cfg.vec, T = lo.cfg.c * lo.cfg.ll * lo.cfg.w;
     ScanGeom &g = lo.g;
     g.B = B; g.L = L; g.H = H; g.T = T;

@@ -350,7 +350,7 @@ void newton_fused_kernel(const FusedArgs a)
                     for (int s = 0; s < S; ++s) accB[v][s] = 0.0f;
                 }
                 auto thread_level = [&](auto gd) {
-                    constexpr bool kG = decltype(gd)::value, kMark = LL < 8;     // eight channels wide: few waves
+                    constexpr bool kG = decltype(gd)::value, kMark = W > 2;       // (two waves: none on the SIMD beside them)
 #pragma unroll
                     for (int i = 0; i < C; ++i) {
                         if (!kG || l0 + i < g.L) {
