@@ -164,12 +164,14 @@ inline int padded_channels(int H, int width) { return (H + width - 1) / width * 
 // the segments of a wave).  us, before / now: GRU fp32 12 x 48925 x 8 230 / 80, 42 x 3207 x 8 113 / 38, 31 x 35271 x 16 333 / 179, 18 x
 // 12000 x 24 94 / 81, 8 x 11690 x 40 83 / 68, 1 x 8609 x 72 44 / 35, 30 x 20768 x 96 509 / 442; LSTM bf16 12 x 48925 x 8 460 / 200, 31 x 35271 x
 // 16 700 / 543, 3 x 20000 x 48 173 / 153; ParaLSTM fp32 12 x 48925 x 8 439 / 182, 18 x 12000 x 24 164 / 127, 2 x 20000 x 288 227 / 199.
+// Cells of four gates and two states have their 64 channels in fewer instructions, the others of two states their 32 (64 / 32): LSTM fp32 3 x 27718 x 256
+// 499 / 522, bf16 192 438 / 480, 256 542 / 610; ParaLSTM fp32 192 269 / 258, 256 337 / 328; rot_tanh bf16 192 236 / 217.
 inline TileCfg fused_tile(const CellInfo &ci, int L, int H, const TileCfg &table)
 {
     if (ci.S > 2 || settings().tile[0] > 0 || L <= 256 || H > 320) return table;
     struct Width { int channels; float costs; TileCfg tile; };
     const bool two = ci.S == 2;
-    const Width w[] = {{64, 1.0f, two ? TileCfg{1, 1, 16, 4} : TileCfg{1, 1, 12, 8}}, {32, two ? 0.98f : 1.08f, two ? TileCfg{1, 2, 16, 4} : TileCfg{1, 2, 8, 8}},
+    const Width w[] = {{64, 1.0f, two ? TileCfg{1, 1, 16, 4} : TileCfg{1, 1, 12, 8}}, {32, !two ? 1.08f : ci.G >= 4 ? 1.06f : 0.98f, two ? TileCfg{1, 2, 16, 4} : TileCfg{1, 2, 8, 8}},
                        {16, 1.15f, {1, 4, 8, 8}}, {8, 1.25f, {1, 8, 8, 8}}};
     const Width *best = w;
     for (const Width &x : w)
@@ -225,7 +227,8 @@ inline TileCfg backward_tile_narrow(const CellInfo &ci, int dtype, int B, int L,
     if (H <= 8) return ci.S == 2 && (double)B * L < 12800.0 ? wide : x8;
     if (H <= 16) return x16;
     const bool take16 = bf && !few && (double)B * L * H < 8e6;
-    if (H <= 32) return take16 ? x16 : x32;
+    // (few tiles of 256 steps: GRU bf16 2 x 15789 x 24 25.3, of 128 steps 23.3; 12 x 3000 22.5 / 22.2; 1 x 60000 29.5 / 37.3)
+    if (H <= 32) return take16 ? x16 : ci.S == 1 && bf && (double)B * L < 4e4 ? TileCfg{1, 2, 8, 8} : x32;
     const size_t row = (size_t)H * (bf ? 2 : 4);
     if (H > 320 || backward_queues_pay((size_t)B * L * row * (2 * ci.G + 2 * ci.S), row, B * ((H + 63) / 64))) return wide;
     const float c64 = (float)padded_channels(H, 64), c32 = (few ? (bf ? 1.05f : 1.2f) : 1.25f) * (float)padded_channels(H, 32),
