@@ -166,8 +166,8 @@ int pararnn_set_staging(int enable);
  * streamed once u and the fp32 iterate together exceed that cache, the iterate
  * once it exceeds twice its size, the backward pass's tensors from one and a
  * half times its size on, where rows are whole cache lines); 1: never; 2: wherever
- * there is a kernel for it.  In mode 0 large backward passes over rows that are no multiple of
- * 64 bytes also hand out their tiles by XCD.  The results are the same bits in every mode.  Returns
+ * there is a kernel for it.  In mode 0 large backward passes whose rows are no multiple of
+ * 64 bytes and hold several channel groups also hand out their tiles by XCD.  The results are the same bits in every mode.  Returns
  * PARARNN_INVALID_ARG for another mode. */
 int pararnn_set_streaming(int mode);
 

@@ -97,13 +97,22 @@ inline int backward_stream(size_t bytes, bool pays)
 //   less              GRU fp32 32 x 512 x 763 114 / 109, 3 x 1531 x 1001 44 / 48, bf16 9 x 700 x 3333 117 / 123; rot_tanh 8 x 1000 x 1531 108 / 117
 //   few groups        GRU fp32 11 (1 x 65536 x 700) 368 / 429, 18 560 / 611, 24 742 / 723, 33 1034 / 1010, 40 1135 / 1058; bf16 28 202 / 214
 //   rows of 64 bytes  GRU fp32 1 x 60000 x 2800 1016 / 1129, LSTM 1625 / 1720
-inline bool backward_queues_pay(size_t bytes, size_t row_bytes, int groups)
+//   one group in a row (nothing is shared)  GRU fp32 64 x 16000 x 40 368 / 439, x 63 510 / 517, bf16 64 x 40000 x 50 887 / 943; LSTM fp32 64 x 12000 x 24
+//                     270 / 278, bf16 64 x 20000 x 41 681 / 693; ParaLSTM 64 x 16000 x 50 545 / 561; rot_tanh bf16 64 x 40000 x 60 980 / 1029
+inline bool backward_queues_pay(size_t bytes, size_t row_bytes, int n_cg, int groups)
 {
-    return row_bytes % 64 != 0 && bytes >= 2 * kMemCacheBytes && groups >= 32 && 32 * ((groups + 7) / 8) <= 5 * groups;
+    return n_cg > 1 && row_bytes % 64 != 0 && bytes >= 2 * kMemCacheBytes && groups >= 32 && 32 * ((groups + 7) / 8) <= 5 * groups;
 }
-inline bool backward_queues(size_t bytes, size_t row_bytes, int groups)
+// Two groups in a row of which the second has few channels: its lines are few, and scalar cells and two gates in bf16 gain less
+// from them than a launch pays.  One queue / eight, of 0.7 and 2 GB: GRU fp32 x 66 234 / 248, 667 / 685, x 70 235 / 237, 651 / 654, x 74 228 / 230,
+// 644 / 631, x 78 229 / 223, 643 / 599; bf16 x 70 385 / 393, 1091 / 1099, x 86 324 / 327, 925 / 904, x 90 316 / 314, 895 / 871; rot_tanh bf16 x 70 415 / 429,
+// 1167 / 1194, x 86 350 / 354, x 90 341 / 341, fp32 x 66 277 / 267.  The others: LSTM fp32 x 66 241 / 241, 704 / 670, bf16 430 / 424; ParaLSTM 265 / 265.
+inline bool backward_queues(const CellInfo &ci, int dtype, size_t bytes, const ScanGeom &g, const TileCfg &cfg)
 {
-    return settings().streaming == 0 && backward_queues_pay(bytes, row_bytes, groups);
+    const bool bf = dtype == PARARNN_BF16;
+    const int last = g.H - (g.n_cg - 1) * (kWave / cfg.ll) * cfg.vec;
+    if (g.n_cg == 2 && (ci.S == 1 || (ci.G <= 2 && bf)) && last < (bf ? 24 : 10)) return false;
+    return settings().streaming == 0 && backward_queues_pay(bytes, (size_t)g.H * (bf ? 2 : 4), g.n_cg, g.n_groups);
 }
 
 // Tile shape for a problem.  The table is the result of sweeps on MI355X over
@@ -217,7 +226,8 @@ inline bool backward_tile_fits(const CellInfo &ci, const TileCfg &t)
 // now: GRU fp32 12 x 48925 x 8 190 / 48, 42 x 3207 x 8 67 / 19, 31 x 35271 x 16 352 / 163, 18 x 12000 x 24 70 / 54, 30 x 20768 x 96 434 / 401; LSTM bf16 12 x
 // 48925 x 8 179 / 62, 31 x 35271 x 16 345 / 171, 18 x 12000 x 24 82 / 68, 3 x 20000 x 48 52 / 42; ParaLSTM fp32 60 x 16549 x 8 289 / 101, 31 x 35271 x 16
 // 432 / 196, 30 x 20768 x 96 603 / 576; rot_tanh bf16 30 x 20768 x 96 494 / 351.  Groups of 16 for more than 16 channels on small tensors only: LSTM
-// fp32 64 x 12000 x 24 342, of 32 273.  Not where the tiles are in queues, for which these shapes are not built.
+// fp32 64 x 12000 x 24 342, of 32 273.  Not at sizes and rows for which there are queues, for which these shapes are not built (GRU fp32 64 x 16000 x 90
+// in queues 796, these shapes 947; x 72 from one queue 734, 765).
 inline TileCfg backward_tile_narrow(const CellInfo &ci, int dtype, int B, int L, int H, const TileCfg &wide)
 {
     const bool bf = dtype == PARARNN_BF16, few = ci.S == 1 || ci.G <= 2;
@@ -230,7 +240,7 @@ inline TileCfg backward_tile_narrow(const CellInfo &ci, int dtype, int B, int L,
     // (few tiles of 256 steps: GRU bf16 2 x 15789 x 24 25.3, of 128 steps 23.3; 12 x 3000 22.5 / 22.2; 1 x 60000 29.5 / 37.3)
     if (H <= 32) return take16 ? x16 : ci.S == 1 && bf && (double)B * L < 4e4 ? TileCfg{1, 2, 8, 8} : x32;
     const size_t row = (size_t)H * (bf ? 2 : 4);
-    if (H > 320 || backward_queues_pay((size_t)B * L * row * (2 * ci.G + 2 * ci.S), row, B * ((H + 63) / 64))) return wide;
+    if (H > 320 || backward_queues_pay((size_t)B * L * row * (2 * ci.G + 2 * ci.S), row, (H + 63) / 64, B * ((H + 63) / 64))) return wide;
     const float c64 = (float)padded_channels(H, 64), c32 = (few ? (bf ? 1.05f : 1.2f) : 1.25f) * (float)padded_channels(H, 32),
                 c16 = 1.12f * (float)padded_channels(H, 16);
     if (take16 && c16 < c64 && c16 < c32) return x16;
@@ -1007,7 +1017,7 @@ int backward_pass(const CellInfo &ci, int dtype, const float *params, const void
               (settings().tile[0] > 0 || backward_staged(ci, B, L, H));
     a.stream = backward_stream((size_t)B * L * H * esz * (2 * ci.G + 2 * ci.S),
                                lo.cfg.c != 12 && H * esz % 128 == 0 && aligned(u, 128) && aligned(h, 128) && aligned(dL_dh, 128) && aligned(dL_du, 128));
-    if (!a.stage && !a.stream && backward_queues((size_t)B * L * H * esz * (2 * ci.G + 2 * ci.S), H * esz, lo.g.n_groups)) a.stream = 2;
+    if (!a.stage && !a.stream && backward_queues(ci, dtype, (size_t)B * L * H * esz * (2 * ci.G + 2 * ci.S), lo.g, lo.cfg)) a.stream = 2;
     const int rc = backward_diag<Cell>(ci, dtype, lo, a, st, dL_dparams);
     if (rc != PARARNN_OK) workspace_forget(workspace);
     return rc;

@@ -24,12 +24,13 @@ def tiles(tmp_path_factory):
     assert r.returncode == 0, r.stderr[-2000:]
 
     def run(problems):
-        """problems: (G, S, PR, kind, dtype, B, L, H); per problem the table's shape, the one taken, staged rows."""
+        """problems: (G, S, PR, kind, dtype, B, L, H); per problem the table's shape, the one taken, staged rows,
+        a queue of tiles for each XCD."""
         text = "\n".join(" ".join(str(int(x)) for x in p) for p in problems)
         out = subprocess.run([str(exe)], input=text, capture_output=True, text=True, check=True).stdout
         rows = [[int(x) for x in line.split()] for line in out.splitlines()]
         assert len(rows) == len(problems)
-        return [(tuple(r[:4]), tuple(r[4:8]), bool(r[8])) for r in rows]
+        return [(tuple(r[:4]), tuple(r[4:8]), bool(r[8]), bool(r[9])) for r in rows]
     return run
 
 
@@ -41,7 +42,7 @@ def test_a_shape_that_is_taken_is_built(tiles):
     ps = [(G, S, P, -1, dt, B, L, H) for G in (1, 2, 3, 4) for S in (1, 2) for P in range(1, 65) for dt in (F32, BF16) for B in (1, 8)
           for L in (700, 4096) for H in (64, 1001, 1024, 2048, 6144)]
     other = 0
-    for p, (table, taken, _) in zip(ps, tiles(ps)):
+    for p, (table, taken, *_) in zip(ps, tiles(ps)):
         S, P = p[1], p[2]
         assert taken in built, (p, taken)
         if fits(S, P, table):
@@ -56,5 +57,24 @@ STAGED = [(16, 1000, 64, 30.7, 23.9), (4, 500, 1024, 33.8, 27.5), (4, 4096, 192,
 
 
 def test_rows_of_3x3_blocks_are_staged_where_that_is_faster(tiles):
-    for m, (_, _, staged) in zip(STAGED, tiles([(3, 3, 9, -1, BF16, *m[:3]) for m in STAGED])):
+    for m, (_, _, staged, _) in zip(STAGED, tiles([(3, 3, 9, -1, BF16, *m[:3]) for m in STAGED])):
         assert staged == (m[3] < m[4]), m
+
+
+GRU, LSTM, PARALSTM, ROT = (3, 1, 6, 0), (4, 2, 8, 1), (3, 2, 8, 4), (2, 2, 2, -1)
+# us on MI355X with one queue of tiles / with one for each XCD.  Rows of one channel group share no cache line, whatever the number of sequences
+QUEUES = [(GRU, F32, 64, 16000, 40, 368, 439), (GRU, F32, 64, 16000, 63, 510, 517), (LSTM, F32, 64, 12000, 24, 270, 278),
+          (LSTM, BF16, 64, 20000, 41, 681, 693), (ROT, BF16, 64, 40000, 60, 980, 1029), (GRU, BF16, 64, 40000, 50, 887, 943),
+          (PARALSTM, F32, 64, 16000, 50, 545, 561),
+          # a second group of few channels
+          (GRU, F32, 40, 8285, 66, 234, 248), (GRU, F32, 40, 20032, 78, 643, 599), (GRU, BF16, 40, 15625, 70, 385, 393), (GRU, BF16, 40, 34722, 90, 895, 871),
+          (ROT, BF16, 40, 15625, 70, 415, 429), (ROT, F32, 40, 7812, 70, 270, 257), (LSTM, F32, 40, 4926, 74, 227, 221), (LSTM, BF16, 40, 11047, 66, 430, 424),
+          # many groups
+          (GRU, F32, 16, 4096, 1021, 551, 464), (GRU, F32, 64, 4096, 300, 666, 555), (LSTM, BF16, 2, 30000, 1001, 506, 483), (PARALSTM, F32, 33, 1999, 500, 342, 328),
+          # few, whole lines, small tensors
+          (GRU, F32, 1, 65536, 700, 368, 429), (GRU, F32, 1, 60000, 2800, 1016, 1129), (GRU, F32, 3, 1531, 1001, 44, 48)]
+
+
+def test_queues_where_channel_groups_share_lines(tiles):
+    for m, (*_, queues) in zip(QUEUES, tiles([(*m[0], *m[1:5]) for m in QUEUES])):
+        assert queues == (m[6] < m[5]), m
