@@ -78,3 +78,20 @@ QUEUES = [(GRU, F32, 64, 16000, 40, 368, 439), (GRU, F32, 64, 16000, 63, 510, 51
 def test_queues_where_channel_groups_share_lines(tiles):
     for m, (*_, queues) in zip(QUEUES, tiles([(*m[0], *m[1:5]) for m in QUEUES])):
         assert queues == (m[6] < m[5]), m
+
+
+def test_the_sizes_of_the_queue_test_take_queues(tiles):
+    """... of which nothing in its results would tell: they are the same bits from one queue."""
+    import torch
+    from test_gpu_backward_queues import SHAPES, steps
+    from test_gpu_backward_tiles import CELLS
+    known = {"gru_diag": GRU, "lstm_diag": LSTM, "paralstm_diag": PARALSTM, "rot_tanh": ROT}
+    ps, counts = [], set()
+    for cell, (G, S, _) in CELLS.items():
+        assert known[cell][:2] == (G, S)
+        for d, dt in ((F32, torch.float32), (BF16, torch.bfloat16)):
+            ps += [(*known[cell], d, B, steps(L, G, S, dt), H) for B, L, H in SHAPES]
+    for p, (_, (vec, ll, c, w), _, queues) in zip(ps, tiles(ps)):
+        assert queues, p
+        counts.add(p[5] * -(-p[7] // (vec * 64 // ll)))
+    assert {32, 33, 50, 99, 780} <= counts, counts

@@ -1,5 +1,6 @@
 """Backward passes whose tiles come from a queue for each XCD (rows that are no multiple of 64 bytes, large tensors): the same bits as
-from one queue, at numbers of groups that the queues share out evenly and not, also on a workspace that is kept and in a graph."""
+from one queue, at numbers of groups that the queues share out evenly and not, also on a workspace that is kept and in a graph.
+That these sizes do take queues is asserted on the host (test_backward_tile.py)."""
 import pytest
 import torch
 
@@ -7,8 +8,13 @@ pytestmark = pytest.mark.gpu
 
 from test_gpu_backward_tiles import CELLS      # noqa: E402
 
-# 32 groups of 64 channels (the fewest, four a queue), 33, 50, 1365 (several sequences a queue); last tiles and groups short
-SHAPES = [(1, 14001, 2047), (3, 3500, 2081), (2, 9000, 1571), (195, 700, 201)]
+# 32 groups of 64 channels (the fewest, four a queue), 99, 50, 780 (several sequences a queue), 33 (one queue has a fifth); last tiles and groups short
+SHAPES = [(1, 14001, 2047), (3, 3500, 2081), (2, 9000, 1571), (195, 700, 201), (1, 14001, 2081)]
+
+
+def steps(L, G, S, dtype):
+    """Timesteps of a shape for a cell of G gates and S state values: its tensors just reach the size from which on there are queues."""
+    return L * (1 if dtype == torch.float32 else 2) * 8 // (2 * G + 2 * S) + 1
 
 
 def inputs(cell, dtype, B, L, H):
@@ -29,7 +35,7 @@ def inputs(cell, dtype, B, L, H):
 def test_queues_agree(cell, dtype, B, L, H):
     import paper_2510_21450_amd as P
     G, S, _ = CELLS[cell]
-    L = L * (1 if dtype == torch.float32 else 2) * 8 // (2 * G + 2 * S) + 1
+    L = steps(L, G, S, dtype)
     assert B * L * H * (2 * G + 2 * S) * (4 if dtype == torch.float32 else 2) >= 512 << 20 and H % 32
     print(f"backward queues {cell} {dtype} {B}x{L}x{H}", flush=True)
     args = inputs(cell, dtype, B, L, H)
