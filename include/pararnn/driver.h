@@ -171,21 +171,28 @@ inline int padded_channels(int H, int width) { return (H + width - 1) / width * 
 // tile makes a long chain of carries: so of 8 channels x 512 steps, 16 x 256, 32 and 64 the one whose channels, times what one
 // costs in it, are the fewest.  A channel costs 1.25 in groups of 8 and 1.15 in groups of 16 of what it does in 64 (scans between
 // the segments of a wave).  us, before / now: GRU fp32 12 x 48925 x 8 230 / 80, 42 x 3207 x 8 113 / 38, 31 x 35271 x 16 333 / 179, 18 x
-// 12000 x 24 94 / 81, 8 x 11690 x 40 83 / 68, 1 x 8609 x 72 44 / 35, 30 x 20768 x 96 509 / 442; LSTM bf16 12 x 48925 x 8 460 / 200, 31 x 35271 x
+// 12000 x 24 94 / 81, 8 x 11690 x 40 83 / 68, 1 x 8609 x 72 44 / 35, 30 x 20768 x 96 509 / 442 (records asked for; else it is walked, 481); LSTM bf16 12 x 48925 x 8 460 / 200, 31 x 35271 x
 // 16 700 / 543, 3 x 20000 x 48 173 / 153; ParaLSTM fp32 12 x 48925 x 8 439 / 182, 18 x 12000 x 24 164 / 127, 2 x 20000 x 288 227 / 199.
 // Cells of four gates and two states have their 64 channels in fewer instructions, the others of two states their 32 (64 / 32): LSTM fp32 3 x 27718 x 256
 // 499 / 522, bf16 192 438 / 480, 256 542 / 610; ParaLSTM fp32 192 269 / 258, 256 337 / 328; rot_tanh bf16 192 236 / 217.
+// Beyond 320 channels what the padding still costs is little (64 / 32 channels): GRU fp32 2 x 30000 x 336 206 / 210, 352 204 / 202, bf16 217 / 205, 480
+// 298 / 300; LSTM fp32 352 889 / 880, bf16 336 603 / 642; ParaLSTM and rot_tanh, whose 32 channels cost less, could gain: fp32 352 361 / 329, 301 / 257.
+struct FusedWidth { int channels; float costs; TileCfg tile; };
+inline FusedWidth fused_width(const CellInfo &ci, int H)
+{
+    const bool two = ci.S == 2;
+    const FusedWidth w[] = {{64, 1.0f, two ? TileCfg{1, 1, 16, 4} : TileCfg{1, 1, 12, 8}},
+                            {32, !two ? 1.08f : ci.G >= 4 ? 1.06f : 0.98f, two ? TileCfg{1, 2, 16, 4} : TileCfg{1, 2, 8, 8}},
+                            {16, 1.15f, {1, 4, 8, 8}}, {8, 1.25f, {1, 8, 8, 8}}};
+    const FusedWidth *best = w;
+    for (const FusedWidth &x : w)
+        if (x.costs * (float)padded_channels(H, x.channels) < best->costs * (float)padded_channels(H, best->channels)) best = &x;
+    return *best;
+}
+inline bool fused_by_width(const CellInfo &ci, int L, int H) { return ci.S <= 2 && L > 256 && H <= 320; }
 inline TileCfg fused_tile(const CellInfo &ci, int L, int H, const TileCfg &table)
 {
-    if (ci.S > 2 || settings().tile[0] > 0 || L <= 256 || H > 320) return table;
-    struct Width { int channels; float costs; TileCfg tile; };
-    const bool two = ci.S == 2;
-    const Width w[] = {{64, 1.0f, two ? TileCfg{1, 1, 16, 4} : TileCfg{1, 1, 12, 8}}, {32, !two ? 1.08f : ci.G >= 4 ? 1.06f : 0.98f, two ? TileCfg{1, 2, 16, 4} : TileCfg{1, 2, 8, 8}},
-                       {16, 1.15f, {1, 4, 8, 8}}, {8, 1.25f, {1, 8, 8, 8}}};
-    const Width *best = w;
-    for (const Width &x : w)
-        if (x.costs * (float)padded_channels(H, x.channels) < best->costs * (float)padded_channels(H, best->channels)) best = &x;
-    return best->tile;
+    return settings().tile[0] <= 0 && fused_by_width(ci, L, H) ? fused_width(ci, H).tile : table;
 }
 
 // The tile of a backward pass of a scalar or 2x2 cell with carry records, by sweeps over 300 to 60000 steps of 2048 to 65792
@@ -365,7 +372,7 @@ constexpr int kShortIters = 5;        // iterations of a solve to a tolerance: w
 // n_iters: of a solve of a fixed count, 0 = to a tolerance
 inline float records_us(const ShortCost &k, const CellInfo &ci, int dtype, int B, int L, int H, int n_iters)
 {
-    // the fused blocks' tile
+    // the tiles that the constants are of: choose_tile's of the fused blocks
     const int width = H <= 8 ? 8 : H <= 32 ? 32 : 64, T = H <= 8 ? 64 : H <= 32 ? 128 : ci.S == 1 ? 96 : 64;
     const float groups = (float)B * (float)((H + width - 1) / width), n_lt = (float)((L + T - 1) / T);
     const float n = groups * (float)width * n_lt * (float)T * 1e-6f;
@@ -381,7 +388,21 @@ inline float records_us(const ShortCost &k, const CellInfo &ci, int dtype, int B
     // against 1284; with six iterations 1233 against 1302; 4200 x 50000 3237 against 4407, with seven 6916 against 4982).
     if (ci.kind == PARARNN_LSTM_DIAG && !n_iters) { step *= 1.45f; fixed += 8.7f; }
     const float narrow = groups < 512.0f ? log2f(512.0f / groups) : 0.0f;
-    return fixed + step * n * (1.0f + k.rec_narrow * narrow) + k.rec_tile * its * n_lt;
+    const float us = fixed + step * n * (1.0f + k.rec_narrow * narrow) + k.rec_tile * its * n_lt;
+    // Narrow rows take narrower tiles (fused_width), and the time is that of the channels that these work on; of 9 to 16 channels about
+    // half.  1.3 times that where it is less: against 13000 problems of 5 to 320 channels, timed with records, in one workgroup
+    // and walked, this changes 49 choices, 46 to kernels that take 0.58 to 0.97 of the time (GRU fp32 68 x 48892 x 16 walked 738,
+    // with records 424; LSTM fp32 47 x 14802 x 16, three iterations, one workgroup 254, 159; ParaLSTM 52 x 52160 x 16 1023 / 749), the worst 1.02.
+    // Without the factor it is a hundred slower by more than 3 % (worst 1.6), for the estimates of the others are up to a third
+    // above their times there; nor up to 2048 steps (GRU bf16 85 x 1664 x 16, eight iterations, 49 us, in one workgroup 44) and
+    // for two gates and two states (rot_tanh bf16 43 x 15499 x 16 186 / 159).
+    if (fused_by_width(ci, L, H) && L > 2048 && !(ci.S == 2 && ci.G <= 2)) {
+        const FusedWidth w = fused_width(ci, H);
+        const float part = w.costs * (float)padded_channels(H, w.channels) / (float)padded_channels(H, width);
+        const float by_width = 1.3f * (fixed + step * n * part * (1.0f + k.rec_narrow * narrow) + k.rec_tile * its * n_lt);
+        if (by_width < us) return by_width;
+    }
+    return us;
 }
 inline float short_us(const ShortCost &k, const CellInfo &ci, int dtype, const ShortShape &sh, int n_iters)
 {
@@ -434,8 +455,10 @@ inline bool short_one_tile(int L, int c, int want, int most, ShortShape *sh)
     return sh->w <= most;
 }
 
-// Channels that the kernels with records work on for each one there is: their groups are 8, 32 or 64 wide, and the time of a
-// narrow H is that of a full group (3x3 cells fp32, 478 steps x 52 x 19, 260 workgroups, three iterations: 0.66 of it).
+// Channels that the kernels with records work on for each one there is, in groups of choose_tile's width: the time of a
+// narrow H is that of a full group (3x3 cells fp32, 478 steps x 52 x 19, 260 workgroups, three iterations: 0.66 of it).  Backward passes of
+// scalar and 2x2 cells have narrower tiles there (backward_tile_narrow), but at the 257 to 2048 steps that ask for it, full groups are the better
+// estimate: of 5400 passes of 5 to 320 channels what they choose is 1.1 % above the faster kernel on the mean, the tiles' own widths 1.2 %.
 inline double records_padding(const CellInfo &ci, int dtype, int H, bool backward)
 {
     const TileCfg cfg = choose_tile(ci, dtype, backward, H, 1, !backward);

@@ -105,6 +105,24 @@ def test_the_faster_kernels_are_taken(choose):
     assert all(s[0] != WALK for s in choose([(TRI, F32, 16, 2000, 1024, 0), (GRU, F32, 1, 64, 8, 0), (GRU, BF16, 32, 1, 1024, 0)]))
 
 
+# narrow rows: us with records, in one workgroup, walked (0: no shape of its own)
+NARROW = [
+    (GRU, F32, 68, 48892, 16, 0, 424, 0, 738), (GRU, BF16, 38, 10933, 16, 0, 82, 137, 0), (LSTM, F32, 47, 14802, 16, 3, 159, 254, 0),
+    (LSTM, F32, 30, 18681, 16, 0, 263, 404, 0), (GRU, F32, 69, 14237, 16, 3, 108, 168, 164), (PARALSTM, BF16, 66, 7110, 16, 3, 106, 135, 150),
+    (PARALSTM, F32, 52, 52160, 16, 0, 749, 1023, 0), (LSTM, F32, 80, 15273, 16, 3, 247, 339, 365), (GRU, BF16, 50, 14045, 9, 3, 95, 126, 0),
+    # as before: the estimates would take records here if nothing were added to what narrow tiles are put at
+    (LSTM, F32, 2, 1846, 56, 0, 62, 36, 0), (LSTM, F32, 9, 3339, 56, 0, 102, 70, 0), (ROT, F32, 15, 47793, 72, 0, 851, 959, 675),
+    (PARALSTM, BF16, 56, 26759, 40, 0, 1338, 1049, 1029), (GRU, BF16, 85, 1664, 16, 8, 49, 44, 46), (ROT, BF16, 43, 15499, 16, 0, 186, 159, 0),
+    (LSTM, F32, 59, 2153, 39, 8, 191, 185, 157), (LSTM, BF16, 8, 26008, 72, 0, 568, 406, 0),
+]
+
+
+def test_the_fastest_kernel_of_narrow_rows_is_taken(choose):
+    for m, s in zip(NARROW, choose([m[:6] for m in NARROW])):
+        us = {RECORDS: m[6], WORKGROUP: m[7], WALK: m[8]}
+        assert us[s[0]] and us[s[0]] <= 1.07 * min(t for t in us.values() if t), (m, s)
+
+
 def test_cells_of_a_users_own_are_walked_where_they_are_tested(choose):
     for cell in ((3, 1, 6, -1), ROT):
         seen = set()
