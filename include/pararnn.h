@@ -107,8 +107,9 @@ int pararnn_device_info(int *info, int capacity);
  * shape of the scan kernels for all later calls -- vec channels per lane, ll
  * segments along L per wave, c timesteps per thread, w waves per workgroup.
  * Only shapes compiled into the library are accepted (else UNSUPPORTED); a
- * call whose H or pointer alignment does not allow `vec` keeps the automatic
- * choice.  vec = 0 restores the automatic choice.  Query workspace sizes
+ * call whose H or pointer alignment does not allow `vec`, or whose rows (H and
+ * gates) are too wide for the 32-bit offsets of a wave's steps, keeps the
+ * automatic choice.  vec = 0 restores the automatic choice.  Query workspace sizes
  * after setting it.  The environment variable PARARNN_TILE="vec,ll,c,w" has
  * the same effect at start-up. */
 int pararnn_set_tile(int vec, int ll, int c, int w);

@@ -157,8 +157,9 @@ inline TileCfg choose_tile(const CellInfo &ci, int dtype, bool backward, int H, 
         else if (bf) cfg = {1, 1, 8, 8};                 // 64 channels x 64 steps
         else cfg = {1, 1, 8, 16};                        // 64 channels x 128 steps (3-4 % faster than 32 x 256 on config 2)
     }
-    const int *ov = settings().tile;
-    if (ov[0] > 0 && ov[0] <= vmax) {
+    // 32-bit byte offsets from a wave's first row, of u or the states or, where there are no gates, of the Jacobians
+    const int *ov = settings().tile, rows = ci.PR == 0 ? ci.S * ci.S : ci.G > ci.S ? ci.G : ci.S;
+    if (ov[0] > 0 && ov[0] <= vmax && (double)ov[1] * ov[2] * rows * H * 4.0 <= 4294967296.0) {
         cfg.vec = ov[0]; cfg.ll = ov[1]; cfg.c = ov[2]; cfg.w = ov[3];
     }
     return cfg;
@@ -657,8 +658,9 @@ inline bool dims_ok(int B, int L, int H)
 {
     if (B < 1 || L < 1 || H < 1) return false;
     // keep every element count inside size_t/int ranges the kernels assume.  The bound on H keeps the
-    // 32-bit byte offsets of the buffer instructions in range: a wave addresses up to 128 rows of H
-    // elements of 4 bytes from its base (8 segments x 4 steps x 4 gates, or 2 x 16 x 4)
+    // 32-bit byte offsets of the buffer instructions in range: at any H the tiles that are chosen have a wave address
+    // up to 16 steps, of four gates 64 rows of H elements of 4 bytes from its base; one that is forced (64 steps in
+    // eight segments of eight) keeps to the range by choose_tile
     const double n = (double)B * (double)L * (double)H;
     return n < 3.0e10 && (double)B * H < 2.0e9 && L < (1 << 30) && H <= (1 << 22);
 }

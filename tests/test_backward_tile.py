@@ -23,11 +23,12 @@ def tiles(tmp_path_factory):
     r = subprocess.run(cmd, capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-2000:]
 
-    def run(problems):
-        """problems: (G, S, PR, kind, dtype, B, L, H); per problem the table's shape, the one taken, staged rows,
+    def run(problems, forced=None):
+        """problems: (G, S, PR, kind, dtype, B, L, H), a tile for all of them; per problem the table's shape, the one taken, staged rows,
         a queue of tiles for each XCD."""
         text = "\n".join(" ".join(str(int(x)) for x in p) for p in problems)
-        out = subprocess.run([str(exe)], input=text, capture_output=True, text=True, check=True).stdout
+        env = dict(os.environ, PARARNN_TILE=",".join(map(str, forced))) if forced else None
+        out = subprocess.run([str(exe)], input=text, capture_output=True, text=True, check=True, env=env).stdout
         rows = [[int(x) for x in line.split()] for line in out.splitlines()]
         assert len(rows) == len(problems)
         return [(tuple(r[:4]), tuple(r[4:8]), bool(r[8]), bool(r[9])) for r in rows]
@@ -49,6 +50,19 @@ def test_a_shape_that_is_taken_is_built(tiles):
             assert fits(S, P, taken), (p, table, taken)
         other += taken != table
     assert other > 1000
+
+
+def test_a_forced_shape_stays_within_32_bit_offsets(tiles):
+    """Cells of many gates, the widest rows: the steps that a wave addresses, or the automatic choice."""
+    kept = left = 0
+    for t in ((1, 8, 8, 8), (1, 4, 8, 8), (1, 8, 4, 2), (1, 2, 16, 4)):
+        ps = [(G, S, 4, -1, F32, 1, 300, H) for G in (1, 3, 4, 5, 8, 12) for S in (1, 2) for H in (8, 1 << 20, (1 << 22) - 1, 1 << 22)]
+        for p, (_, taken, *_) in zip(ps, tiles(ps, forced=t)):
+            G, S, H = max(p[0], p[1]), p[1], p[7]
+            fits = lambda x: ((x[1] - 1) * x[2] * G * H + 63 + ((x[2] - 1) * G + G - 1) * H) * 4 + 4 <= 2 ** 32
+            assert fits(taken) and (taken == t) == fits(t), (p, t, taken)
+            kept, left = kept + (taken == t), left + (taken != t)
+    assert kept > 100 and left > 10
 
 
 # 3x3 blocks (tri_tanh, bf16), us on MI355X with staged rows / without
