@@ -1,6 +1,6 @@
 // Host-only probe of the tile of a backward pass with carry records: reads problems "G S PR kind dtype B L H" from stdin and
 // prints one line each: the shape that choose_tile's table has, the one that is taken, whether rows are staged where
-// they can be, and whether there is a queue of tiles for each XCD.  No device call.
+// they can be, whether there is a queue of tiles for each XCD, and the shape of a forward solve's blocks with records.  No device call.
 #include <stdio.h>
 
 #include "pararnn/driver.h"
@@ -16,8 +16,9 @@ int main()
         const Layout lo = make_layout(ci, dtype, B, L, H, true, 4);
         const TileCfg &n = lo.cfg;
         const size_t bytes = (size_t)B * L * H * (dtype == PARARNN_BF16 ? 2 : 4) * (2 * G + 2 * S);
-        printf("%d %d %d %d %d %d %d %d %d %d\n", t.vec, t.ll, t.c, t.w, n.vec, n.ll, n.c, n.w, (int)backward_staged(ci, B, L, H),
-               (int)backward_queues(ci, dtype, bytes, lo.g, n));
+        const TileCfg f = make_layout(ci, dtype, B, L, H, false, 4, true, 5).cfg;
+        printf("%d %d %d %d %d %d %d %d %d %d %d %d %d %d\n", t.vec, t.ll, t.c, t.w, n.vec, n.ll, n.c, n.w, (int)backward_staged(ci, B, L, H),
+               (int)backward_queues(ci, dtype, bytes, lo.g, n), f.vec, f.ll, f.c, f.w);
     }
     return 0;
 }

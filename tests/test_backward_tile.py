@@ -25,20 +25,30 @@ def tiles(tmp_path_factory):
 
     def run(problems, forced=None):
         """problems: (G, S, PR, kind, dtype, B, L, H), a tile for all of them; per problem the table's shape, the one taken, staged rows,
-        a queue of tiles for each XCD."""
+        a queue of tiles for each XCD, the shape of the forward solve's blocks."""
         text = "\n".join(" ".join(str(int(x)) for x in p) for p in problems)
         env = dict(os.environ, PARARNN_TILE=",".join(map(str, forced))) if forced else None
         out = subprocess.run([str(exe)], input=text, capture_output=True, text=True, check=True, env=env).stdout
         rows = [[int(x) for x in line.split()] for line in out.splitlines()]
         assert len(rows) == len(problems)
-        return [(tuple(r[:4]), tuple(r[4:8]), bool(r[8]), bool(r[9])) for r in rows]
+        return [(tuple(r[:4]), tuple(r[4:8]), bool(r[8]), bool(r[9]), tuple(r[10:])) for r in rows]
     return run
+
+
+def built_shapes():
+    text = open(os.path.join(ROOT, "include", "pararnn", "launch.h")).read()
+    return {tuple(int(x) for x in m) for m in re.findall(r"X\((\d+), (\d+), (\d+), (\d+)\)", text[text.index("define PARARNN_SHAPES"):])}
+
+
+def test_the_shapes_that_are_tested_are_the_compiled_ones():
+    from test_gpu_parity import TILE_SHAPES
+    from test_gpu_random_cases import NARROW, TILES
+    assert set(TILE_SHAPES) == built_shapes() == {t for t in TILES + NARROW if t}
 
 
 def test_a_shape_that_is_taken_is_built(tiles):
     """However many parameter rows a cell has: of the list that is compiled, and within 64 KB of LDS wherever the table's shape is."""
-    text = open(os.path.join(ROOT, "include", "pararnn", "launch.h")).read()
-    built = {tuple(int(x) for x in m) for m in re.findall(r"X\((\d+), (\d+), (\d+), (\d+)\)", text[text.index("define PARARNN_SHAPES"):])}
+    built = built_shapes()
     fits = lambda S, P, t: (t[3] * max(S * S + S, P) + S) * (64 // t[1]) * t[0] * 4 + 16 <= 65536
     ps = [(G, S, P, -1, dt, B, L, H) for G in (1, 2, 3, 4) for S in (1, 2) for P in range(1, 65) for dt in (F32, BF16) for B in (1, 8)
           for L in (700, 4096) for H in (64, 1001, 1024, 2048, 6144)]
@@ -71,7 +81,7 @@ STAGED = [(16, 1000, 64, 30.7, 23.9), (4, 500, 1024, 33.8, 27.5), (4, 4096, 192,
 
 
 def test_rows_of_3x3_blocks_are_staged_where_that_is_faster(tiles):
-    for m, (_, _, staged, _) in zip(STAGED, tiles([(3, 3, 9, -1, BF16, *m[:3]) for m in STAGED])):
+    for m, (_, _, staged, *_) in zip(STAGED, tiles([(3, 3, 9, -1, BF16, *m[:3]) for m in STAGED])):
         assert staged == (m[3] < m[4]), m
 
 
@@ -90,7 +100,7 @@ QUEUES = [(GRU, F32, 64, 16000, 40, 368, 439), (GRU, F32, 64, 16000, 63, 510, 51
 
 
 def test_queues_where_channel_groups_share_lines(tiles):
-    for m, (*_, queues) in zip(QUEUES, tiles([(*m[0], *m[1:5]) for m in QUEUES])):
+    for m, (_, _, _, queues, _) in zip(QUEUES, tiles([(*m[0], *m[1:5]) for m in QUEUES])):
         assert queues == (m[6] < m[5]), m
 
 
@@ -105,7 +115,28 @@ def test_the_sizes_of_the_queue_test_take_queues(tiles):
         assert known[cell][:2] == (G, S)
         for d, dt in ((F32, torch.float32), (BF16, torch.bfloat16)):
             ps += [(*known[cell], d, B, steps(L, G, S, dt), H) for B, L, H in SHAPES]
-    for p, (_, (vec, ll, c, w), _, queues) in zip(ps, tiles(ps)):
+    for p, (_, (vec, ll, c, w), _, queues, _) in zip(ps, tiles(ps)):
         assert queues, p
         counts.add(p[5] * -(-p[7] // (vec * 64 // ll)))
     assert {32, 33, 50, 99, 780} <= counts, counts
+
+
+def test_the_sizes_of_the_narrow_test_take_the_narrow_tiles(tiles):
+    """Blocks and backward passes of every cell and type; tiles of 32 channels are no narrow ones for four gates in bf16."""
+    from test_gpu_narrow_tiles import CELLS, SIZES
+    x8, x16, before = (1, 8, 8, 8), (1, 4, 8, 8), (1, 8, 4, 2)
+    known = {"gru_diag": (GRU, (1, 2, 8, 16), (1, 2, 8, 16)), "lstm_diag": (LSTM, (1, 2, 8, 8), x16), "paralstm_diag": (PARALSTM, (1, 2, 8, 8), x16),
+             "rot_tanh": (ROT, (1, 2, 8, 8), (1, 2, 16, 4))}
+    for cell in CELLS:
+        for dt in (F32, BF16):
+            back, blocks = {}, {}
+            for size, (_, b, _, _, f) in zip(SIZES, tiles([(*known[cell][0], dt, *m) for m in SIZES])):
+                back.setdefault(size[2], set()).add(b)
+                blocks.setdefault(size[2], set()).add(f)
+            # two states: backward passes in groups of 8 only where there are enough tiles of 512 steps; either side of that
+            for H in (7, 8):
+                assert back[H] == ({x8} if cell == "gru_diag" else {x8, before}) and blocks[H] == {x8}, (cell, dt, H)
+            for H in (9, 16):
+                assert back[H] == {x16} and blocks[H] == {x16}, (cell, dt, H)
+            assert known[cell][1 + dt] in set().union(*(back[H] for H in (17, 24, 33, 48, 72, 96))), (cell, dt, back)
+            assert {t[1] for H in (33, 48, 72, 96) for t in blocks[H]} >= {2}, (cell, dt, blocks)

@@ -213,7 +213,7 @@ def test_invalid_arguments_are_rejected(P):
 
 
 TILE_SHAPES = [(1, 1, 8, 16), (1, 2, 8, 16), (1, 2, 16, 4), (1, 2, 8, 8), (1, 1, 8, 8), (2, 2, 8, 8), (1, 1, 4, 8), (1, 1, 16, 8),
-               (1, 8, 4, 2), (4, 4, 8, 8), (2, 4, 8, 8), (1, 1, 16, 4), (1, 1, 12, 8)]
+               (1, 8, 4, 2), (1, 8, 8, 8), (1, 4, 8, 8), (4, 4, 8, 8), (2, 4, 8, 8), (1, 1, 16, 4), (1, 1, 12, 8)]
 
 
 @pytest.mark.parametrize("cell", ["gru_diag", "lstm_diag", "paralstm_diag"])
@@ -259,7 +259,7 @@ def test_fixed_count_solve_in_one_launch(P, oracle_mod, cell, dtype):
     params, u, h0, _ = problem(cell, B, L, H, seed=2024, dtype=dtype)
     pn, un, h0n = to_np(params), to_np(u), to_np(h0)
     bound = 2e-5 if dtype == torch.float32 else TOL_BF16
-    for tile in [None, (1, 2, 8, 8), (2, 2, 8, 8), (1, 1, 4, 8)]:
+    for tile in [None, (1, 2, 8, 8), (2, 2, 8, 8), (1, 1, 4, 8), (1, 8, 8, 8), (1, 4, 8, 8)]:
         for K in (1, 2, 3, 5, 8):
             print(f"fused {cell} {dtype} tile={tile} K={K}", flush=True)
             try:
@@ -365,7 +365,7 @@ def test_solve_to_tolerance_in_fused_blocks(P, oracle_mod, cell, dtype):
     assert min(tr64[k - 1], tr32[k - 1]) >= 8 * tol and max(tr64[k], tr32[k]) <= tol / 8, (tr64, tr32)
     try:
         for head in (0, 1, 2, 3, 4, 5, 6, 8):
-            for tile in (None, (1, 2, 8, 8), (2, 2, 8, 8), (4, 4, 8, 8)):
+            for tile in (None, (1, 2, 8, 8), (2, 2, 8, 8), (4, 4, 8, 8), (1, 8, 8, 8), (1, 4, 8, 8)):
                 for max_iter in (40, it64, it64 - 1, 2):
                     print(f"blocks {cell} {dtype} head={head} tile={tile} max_iter={max_iter}", flush=True)
                     P.set_fused_head(head)

@@ -162,3 +162,27 @@ def test_block_cells_refuse_tile_shapes_that_are_not_built():
             assert int(iters.cpu()[1]) == 0
         finally:
             P.set_tile(0)
+
+
+@pytest.mark.parametrize("tile", [(1, 8, 8, 8), (1, 4, 8, 8)])
+def test_3x3_blocks_in_the_tiles_of_narrow_rows(oracle_mod, as_stored, tile):
+    """Built for them too, taken only where they are asked for."""
+    import paper_2510_21450_amd as P
+    cell = P.example_cell("tri_tanh")
+    for dtype, bound in ((torch.float32, TOL_F32), (torch.bfloat16, TOL_BF16)):
+        for B, L, H in ((2, 1100, 9), (1, 513, 40)):
+            print(f"tri_tanh {dtype} {B}x{L}x{H} tile={tile}", flush=True)
+            params, u, h0, g = problem(cell, B, L, H, seed=3500 + H, dtype=dtype)
+            pn, un, h0n = to_np(params), to_np(u), to_np(h0)
+            ref = oracle_mod.seq_unroll("tri_tanh", pn, un, h0n)
+            hs = as_stored(ref, u)
+            try:
+                P.set_tile(*tile)
+                h, iters, _ = P.forward(cell, params, u, h0, tol=1e-5, max_iter=40)
+                got = P.backward(cell, params, u, h0, hs, g)
+                torch.cuda.synchronize()
+            finally:
+                P.set_tile(0)
+            assert int(iters.cpu()[1]) == 0 and relerr(to_np(h), ref) <= bound
+            for x, y in zip(got, oracle_mod.backward("tri_tanh", pn, un, h0n, to_np(hs), to_np(g))):
+                assert relerr(to_np(x), y) <= bound

@@ -51,6 +51,11 @@ CASES = [
     ("C3 fused block", LSTM, 0, 8, 2048, 2048, False, (1, 1, 16, 4), 5),
     ("C3 backward", LSTM, 0, 8, 2048, 2048, True, (1, 1, 16, 8), 1),
     ("small H, eight segments", GRU, 0, 3, 1000, 8, False, (1, 8, 4, 2), 5),
+    ("8 channels x 512 steps, fused block", LSTM, 1, 12, 48925, 8, False, (1, 8, 8, 8), 5),
+    ("8 channels x 512 steps, backward", LSTM, 0, 12, 48925, 7, True, (1, 8, 8, 8), 1),
+    ("16 channels x 256 steps, fused block", GRU, 1, 31, 35271, 16, False, (1, 4, 8, 8), 5),
+    ("16 channels x 256 steps, backward", LSTM, 1, 18, 12000, 320, True, (1, 4, 8, 8), 1),
+    ("widest H allowed, 8 channels x 512 steps", LSTM, 0, 1, 64, 1 << 22, False, (1, 8, 8, 8), 1),
     ("widest H allowed", LSTM, 0, 1, 64, 1 << 22, False, (1, 2, 16, 4), 1),
 ]
 
