@@ -110,6 +110,7 @@ inline bool backward_queues_pay(size_t bytes, size_t row_bytes, int n_cg, int gr
 inline bool backward_queues(const CellInfo &ci, int dtype, size_t bytes, const ScanGeom &g, const TileCfg &cfg)
 {
     const bool bf = dtype == PARARNN_BF16;
+    if (!backward_queues_shape(ci.S, ci.G, cfg.vec, cfg.ll, cfg.c, cfg.w)) return false;
     const int last = g.H - (g.n_cg - 1) * (kWave / cfg.ll) * cfg.vec;
     if (g.n_cg == 2 && (ci.S == 1 || (ci.G <= 2 && bf)) && last < (bf ? 24 : 10)) return false;
     return settings().streaming == 0 && backward_queues_pay(bytes, (size_t)g.H * (bf ? 2 : 4), g.n_cg, g.n_groups);

@@ -21,6 +21,16 @@ struct TileCfg {
 #define PARARNN_SHAPES(X)                                                                       \
     X(1, 1, 8, 16) X(1, 2, 8, 16) X(1, 2, 16, 4) X(1, 2, 8, 8) X(1, 1, 8, 8) X(2, 2, 8, 8)            \
     X(1, 1, 16, 8) X(1, 1, 4, 8) X(1, 8, 4, 2) X(1, 8, 8, 8) X(1, 4, 8, 8) X(4, 4, 8, 8) X(2, 4, 8, 8) X(1, 1, 16, 4) X(1, 1, 12, 8)
+// Backward passes with a queue of tiles for each XCD: the shapes that backward_tile (driver.h) takes for large tensors whose rows
+// are no multiple of 64 bytes.
+constexpr bool backward_queues_shape(int S, int G, int vec, int ll, int c, int w)
+{
+    if (vec != 1) return false;
+    if (S == 1) return ll == 1 && c == 8 && (w == 8 || w == 16);
+    if (S != 2) return false;
+    if ((ll == 2 && c == 8 && w == 8) || (ll == 1 && c == 16 && w == 8)) return true;      // the tables' own, fp32 and bf16
+    return ll == 1 && (G <= 2 ? c == 16 && w == 4 : w == 8 && (c == 12 || c == 4));
+}
 // channels per lane compiled for the element-wise kernels
 #define PARARNN_VECS(X) X(1) X(2) X(4)
 

@@ -224,10 +224,10 @@ template <class Cell, int VEC, int LL, int C, int W> constexpr bool backward_str
     return !IsRaw<Cell>::value && VEC == 1 && C != 12 && (LL == 1 || (LL == 2 && C == 8 && W == 8));
 }
 
-// ... and the one with a queue for each XCD: of the shapes that are taken for rows of other lengths.
+// ... and the one with a queue for each XCD.
 template <class Cell, int VEC, int LL, int C, int W> constexpr bool backward_queues_offered()
 {
-    return !IsRaw<Cell>::value && Cell::S <= 2 && VEC == 1 && (LL == 1 || (LL == 2 && C == 8 && W == 8));
+    return !IsRaw<Cell>::value && backward_queues_shape(Cell::S, Cell::G, VEC, LL, C, W);
 }
 
 // static LDS of the staged backward kernel: its staging rows on top of the plain kernel's.  All of a compute unit's may be

@@ -104,6 +104,18 @@ def test_queues_where_channel_groups_share_lines(tiles):
         assert queues == (m[6] < m[5]), m
 
 
+def test_every_shape_that_is_taken_for_such_rows_has_queues(tiles):
+    """Cells of any number of gates and parameter rows: rows of three channel groups or more that are no multiple of 64 bytes, large tensors, many groups."""
+    ps = [(G, S, P, k, dt, B, L, H) for G, S, k in ((1, 1, -1), (3, 1, 0), (5, 1, -1), (1, 2, -1), (2, 2, -1), (3, 2, 4), (3, 2, -1), (4, 2, 1), (7, 2, -1))
+          for P in (2, 8, 40, 64) for dt in (F32, BF16) for H in (131, 333, 515, 1001, 2047, 4091, 9001)
+          for B in (16, 40, 64, 200) for L in (520, 2500, 9000) if 4 * (2 * G + 2 * S) * B * L * H < 1 << 36 and B * L * H * (2 * G + 2 * S) * (2 if dt else 4) >= 1 << 29]
+    seen = set()
+    for p, (_, taken, _, queues, _) in zip(ps, tiles(ps)):
+        assert queues, (p, taken)
+        seen.add((p[1], p[0] <= 2, taken))
+    assert {(1, False, (1, 1, 8, 8)), (1, False, (1, 1, 8, 16)), (2, True, (1, 1, 16, 4)), (2, False, (1, 1, 12, 8)), (2, False, (1, 1, 4, 8))} <= seen, seen
+
+
 def test_the_sizes_of_the_queue_test_take_queues(tiles):
     """... of which nothing in its results would tell: they are the same bits from one queue."""
     import torch
