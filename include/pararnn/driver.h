@@ -234,8 +234,12 @@ inline bool backward_tile_fits(const CellInfo &ci, const TileCfg &t)
 // Narrow rows, as the fused blocks' tile above (a pass is bound by memory sooner, so that narrow groups cost more).  us, before /
 // now: GRU fp32 12 x 48925 x 8 190 / 48, 42 x 3207 x 8 67 / 19, 31 x 35271 x 16 352 / 163, 18 x 12000 x 24 70 / 54, 30 x 20768 x 96 434 / 401; LSTM bf16 12 x
 // 48925 x 8 179 / 62, 31 x 35271 x 16 345 / 171, 18 x 12000 x 24 82 / 68, 3 x 20000 x 48 52 / 42; ParaLSTM fp32 60 x 16549 x 8 289 / 101, 31 x 35271 x 16
-// 432 / 196, 30 x 20768 x 96 603 / 576; rot_tanh bf16 30 x 20768 x 96 494 / 351.  Groups of 16 for more than 16 channels on small tensors only: LSTM
-// fp32 64 x 12000 x 24 342, of 32 273.  Not at sizes and rows for which there are queues, for which these shapes are not built (GRU fp32 64 x 16000 x 90
+// 432 / 196, 30 x 20768 x 96 603 / 576; rot_tanh bf16 30 x 20768 x 96 494 / 351.  Groups of 16 for more than 16 channels (16 / 32): cells of more gates
+// in bf16, on small tensors only (LSTM 3 x 2000 x 24 16.5 / 18.5, 12 x 12000 x 24 51 / 60, 18 x 12000 x 32 68 / 79, 4 x 2000 x 80 18.4 / 20.0, 20 x 9000 x 80 195 / 184;
+// ParaLSTM 167 / 169, 64 x 12000 x 24 241 / 293); in fp32 they lose more than they gain (LSTM 3 x 2000 x 24 16.3 / 18.1, 64 x 12000 x 24 340 / 279, 18 x 12000 x 32
+// 109 / 94; ParaLSTM 58 / 64 of 12 x 12000 x 24, 99 / 84 of 18 x 12000 x 32).  Beyond 320 channels the shapes by size are the faster ones or within 5 % but for
+// ParaLSTM fp32 4 x 4000 x 352 (56 / 52) and rot_tanh bf16 (3 x 6000 x 416 51 / 47, 2 x 9000 x 544 61 / 57): GRU fp32 4 x 4000 x 336 42 / 46, 352 41 / 40, bf16
+// 2 x 9000 x 544 56 / 60; LSTM fp32 3 x 6000 x 416 87 / 86, bf16 66 / 69; ParaLSTM bf16 3 x 6000 x 480 66 / 71.  Not at sizes and rows for which there are queues, for which these shapes are not built (GRU fp32 64 x 16000 x 90
 // in queues 796, these shapes 947; x 72 from one queue 734, 765).
 inline TileCfg backward_tile_narrow(const CellInfo &ci, int dtype, int B, int L, int H, const TileCfg &wide)
 {
@@ -246,8 +250,9 @@ inline TileCfg backward_tile_narrow(const CellInfo &ci, int dtype, int B, int L,
     if (H <= 8) return ci.S == 2 && (double)B * L < 12800.0 ? wide : x8;
     if (H <= 16) return x16;
     const bool take16 = bf && !few && (double)B * L * H < 8e6;
-    // (few tiles of 256 steps: GRU bf16 2 x 15789 x 24 25.3, of 128 steps 23.3; 12 x 3000 22.5 / 22.2; 1 x 60000 29.5 / 37.3)
-    if (H <= 32) return take16 ? x16 : ci.S == 1 && bf && (double)B * L < 4e4 ? TileCfg{1, 2, 8, 8} : x32;
+    // (few tiles of 256 steps, of 256 / of 128: GRU bf16 2 x 15789 x 24 25.2 / 23.1, 5 x 3500 x 24 21.1 / 17.4, 12 x 3000 x 17 22.4 / 21.8, x 24 22.6 / 22.9, 4 x 12000
+    // 24.0 / 27.7, 1 x 60000 29.5 / 37.3.  Rows of 32 are whole half lines, and level sooner: 2 x 15789 22.2 / 21.7, 12 x 3000 17.8 / 18.8, 6 x 6000 18.4 / 20.0)
+    if (H <= 32) return take16 ? x16 : ci.S == 1 && bf && (double)B * L < (H == 32 ? 3.4e4 : 4e4) ? TileCfg{1, 2, 8, 8} : x32;
     const size_t row = (size_t)H * (bf ? 2 : 4);
     if (H > 320 || backward_queues_pay((size_t)B * L * row * (2 * ci.G + 2 * ci.S), row, (H + 63) / 64, B * ((H + 63) / 64))) return wide;
     const float c64 = (float)padded_channels(H, 64), c32 = (few ? (bf ? 1.05f : 1.2f) : 1.25f) * (float)padded_channels(H, 32),

@@ -104,6 +104,16 @@ def test_queues_where_channel_groups_share_lines(tiles):
         assert queues == (m[6] < m[5]), m
 
 
+# bf16 GRU of 17 to 32 channels, us in tiles of 128 steps / of 256
+STEPS = [(2, 15789, 24, 23.1, 25.2), (2, 15789, 32, 21.7, 22.2), (12, 3000, 17, 21.8, 22.4), (12, 3000, 32, 18.8, 17.8), (6, 6000, 32, 20.0, 18.4),
+         (1, 36000, 32, 24.5, 23.0), (5, 3500, 32, 16.1, 18.7), (4, 12000, 17, 28.5, 25.7), (1, 60000, 24, 37.3, 29.5)]
+
+
+def test_steps_of_narrow_bf16_tiles(tiles):
+    for m, (_, taken, *_) in zip(STEPS, tiles([(*GRU, BF16, *m[:3]) for m in STEPS])):
+        assert taken == ((1, 2, 8, 8) if m[3] < m[4] else (1, 2, 8, 16)), m
+
+
 def test_every_shape_that_is_taken_for_such_rows_has_queues(tiles):
     """Cells of any number of gates and parameter rows: rows of three channel groups or more that are no multiple of 64 bytes, large tensors, many groups."""
     ps = [(G, S, P, k, dt, B, L, H) for G, S, k in ((1, 1, -1), (3, 1, 0), (5, 1, -1), (1, 2, -1), (2, 2, -1), (3, 2, 4), (3, 2, -1), (4, 2, 1), (7, 2, -1))
