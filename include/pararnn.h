@@ -152,9 +152,9 @@ int pararnn_set_fused(int enable);
 /* Test / tuning hook (host, process-wide; default 1): enable = 0 keeps the kernels
  * from copying their inputs straight from memory into LDS ahead of their use:
  * the backward kernel of the diagonal cells (bf16 storage, rows 16-byte
- * aligned, H % 8 == 0), the forward and dx products of the input projection
- * (d_h >= 128; either storage type) and its weight-gradient sums (bf16 storage,
- * d_h = 192, 256, 448 and up).  They then load through registers.  The
+ * aligned, H % 8 == 0), and the input projection's three products wherever they
+ * have such a kernel (by width of a head, rows and storage type).  They then load
+ * through registers.  The
  * backward kernel gives the same bits either way; the projection's kernels sum
  * in different orders and agree to fp32 rounding. */
 int pararnn_set_staging(int enable);

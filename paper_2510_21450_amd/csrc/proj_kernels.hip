@@ -1817,7 +1817,7 @@ __global__ __launch_bounds__(512) void proj_dw_dma_kernel(const DwArgs a)
 //   dbias    is added up from the fragments of du (unrounded in fp32; eight rows before they join the sum); the waves that share a part's du blocks take one each
 //   tiles    heads of more than 256 in four of half a head, 160 to 256 wide: no part of a tile idle, and du and x read twice, through the
 //            L2 of one XCD; of three gates 15000 x 320 in fp32 60 -> 40 us, 60000 x 320 159 -> 119, four gates of two heads 15000 x 384
-//            136 -> 86, bf16 142 -> 85 (four heads of 320), 160 -> 92 (of 384), fp32 448 and 512 60000 x 1 260 -> 229, 282 -> 250.  Bound by the
+//            136 -> 86, bf16 142 -> 85 (four heads of 320), 160 -> 92 (of 384), fp32 448 and 512 (60000 x one head, three gates) 249 -> 214, 269 -> 226.  Bound by the
 //            reads from LDS and the conversions of a 16-row slice, which nothing else of the wave overlaps
 //   bound    by memory, and where ranges are many by their sums: three gates, 65536 x 512 in heads of 64, bf16: 110 -> 55 us (4.9 TB/s);
 //            40000 x 512 in heads of 128, four gates: 67 -> 41; fp32: 16000 x 1024 in heads of 256 117 -> 100, 6993 x 768 in
