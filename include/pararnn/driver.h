@@ -177,7 +177,8 @@ inline int padded_channels(int H, int width) { return (H + width - 1) / width * 
 // 16 700 / 543, 3 x 20000 x 48 173 / 153; ParaLSTM fp32 12 x 48925 x 8 439 / 182, 18 x 12000 x 24 164 / 127, 2 x 20000 x 288 227 / 199.
 // Cells of four gates and two states have their 64 channels in fewer instructions, the others of two states their 32 (64 / 32): LSTM fp32 3 x 27718 x 256
 // 499 / 522, bf16 192 438 / 480, 256 542 / 610; ParaLSTM fp32 192 269 / 258, 256 337 / 328; rot_tanh bf16 192 236 / 217.
-// Scratch memory: LSTM in 32 x 128 56 to 72 bytes a lane, in 64 x 64 8 to 28, ParaLSTM in 32 x 128 28 to 52; GRU in 64 x 96 16 to 40.  Beyond 320 channels what the padding still costs is little (64 / 32 channels): GRU fp32 2 x 30000 x 336 206 / 210, 352 204 / 202, bf16 217 / 205, 480
+// Scratch memory: LSTM in 32 x 128 56 to 72 bytes a lane, in 64 x 64 8 to 28, ParaLSTM in 32 x 128 28 to 52; GRU in 64 x 96 16 to 40.
+// Beyond 320 channels what the padding still costs is little (64 / 32 channels): GRU fp32 2 x 30000 x 336 206 / 210, 352 204 / 202, bf16 217 / 205, 480
 // 298 / 300; LSTM fp32 352 889 / 880, bf16 336 603 / 642; ParaLSTM and rot_tanh, whose 32 channels cost less, could gain: fp32 352 361 / 329, 301 / 257.
 struct FusedWidth { int channels; float costs; TileCfg tile; };
 inline FusedWidth fused_width(const CellInfo &ci, int H)
@@ -239,8 +240,9 @@ inline bool backward_tile_fits(const CellInfo &ci, const TileCfg &t)
 // ParaLSTM 167 / 169, 64 x 12000 x 24 241 / 293); in fp32 they lose more than they gain (LSTM 3 x 2000 x 24 16.3 / 18.1, 64 x 12000 x 24 340 / 279, 18 x 12000 x 32
 // 109 / 94; ParaLSTM 58 / 64 of 12 x 12000 x 24, 99 / 84 of 18 x 12000 x 32).  Beyond 320 channels the shapes by size are the faster ones or within 5 % but for
 // ParaLSTM fp32 4 x 4000 x 352 (56 / 52) and rot_tanh bf16 (3 x 6000 x 416 51 / 47, 2 x 9000 x 544 61 / 57): GRU fp32 4 x 4000 x 336 42 / 46, 352 41 / 40, bf16
-// 2 x 9000 x 544 56 / 60; LSTM fp32 3 x 6000 x 416 87 / 86, bf16 66 / 69; ParaLSTM bf16 3 x 6000 x 480 66 / 71.  Not at sizes and rows for which there are queues, for which these shapes are not built (GRU fp32 64 x 16000 x 90
-// in queues 796, these shapes 947; x 72 from one queue 734, 765).  Registers (of 128 for four waves a SIMD): scalar cells take 129 in tiles of 512 steps
+// 2 x 9000 x 544 56 / 60; LSTM fp32 3 x 6000 x 416 87 / 86, bf16 66 / 69; ParaLSTM bf16 3 x 6000 x 480 66 / 71.  Not at sizes and rows for which there are
+// queues, for which these shapes are not built (GRU fp32 64 x 16000 x 90 in queues 796, these shapes 947; x 72 from one queue 734, 765; rot_tanh bf16
+// 40 x 20000 x 72 would gain, 528 / 449).  Registers (of 128 for four waves a SIMD): scalar cells take 129 in tiles of 512 steps
 // and of 16 channels, 131 in 32 x 128, so that a unit holds one workgroup of eight waves; 32 x 256 is one of sixteen within 128, with 20 bytes of
 // scratch a lane (35 x 14020 x 24 123, 32 x 128 168).
 inline TileCfg backward_tile_narrow(const CellInfo &ci, int dtype, int B, int L, int H, const TileCfg &wide)

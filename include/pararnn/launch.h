@@ -17,7 +17,7 @@ struct TileCfg {
 // Tile shapes compiled for every cell: X(VEC, LL, C, W).  A tile covers
 // (64/LL)*VEC channels x C*LL*W timesteps.  Measured on MI355X the narrow
 // shapes (one or two channels per lane: few registers, many resident waves)
-// beat wide vector loads; the automatic choice is in pararnn_api.hip.
+// beat wide vector loads; the automatic choice is in driver.h.
 #define PARARNN_SHAPES(X)                                                                       \
     X(1, 1, 8, 16) X(1, 2, 8, 16) X(1, 2, 16, 4) X(1, 2, 8, 8) X(1, 1, 8, 8) X(2, 2, 8, 8)            \
     X(1, 1, 16, 8) X(1, 1, 4, 8) X(1, 8, 4, 2) X(1, 8, 8, 8) X(1, 4, 8, 8) X(4, 4, 8, 8) X(2, 4, 8, 8) X(1, 1, 16, 4) X(1, 1, 12, 8)
