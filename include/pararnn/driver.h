@@ -180,22 +180,40 @@ inline int padded_channels(int H, int width) { return (H + width - 1) / width * 
 // Scratch memory: LSTM in 32 x 128 56 to 72 bytes a lane, in 64 x 64 8 to 28, ParaLSTM in 32 x 128 28 to 52; GRU in 64 x 96 16 to 40.
 // Beyond 320 channels what the padding still costs is little (64 / 32 channels): GRU fp32 2 x 30000 x 336 206 / 210, 352 204 / 202, bf16 217 / 205, 480
 // 298 / 300; LSTM fp32 352 889 / 880, bf16 336 603 / 642; ParaLSTM and rot_tanh, whose 32 channels cost less, could gain: fp32 352 361 / 329, 301 / 257.
+// Two-state cells have lines beside the costs (12000 problems of 5 to 340 channels with records, against the tiles before: 0.76 of the time on the mean; by costs
+// alone 364 were slower by more than 3 %, worst 1.31; with the lines 13, worst 1.04):
+//   25 to 32 channels   16 x 256 for few timesteps, for short tiles make long chains of carries (LSTM bf16 4 x 4721 x 32 32 x 128 in four waves 59.4, in eight 49.6,
+//                       16 x 256 46.8; rot_tanh 4 x 2324 41 / 38 / 36), four waves for many (ParaLSTM 0.78-0.83 of eight from 256000 on); LSTM with whole rows in between
+//                       eight (bf16 42 x 7228 x 32 524 / 428 / 433)
+//   large LSTM          32 and 64 only, and 32 at 1.15 (1.5e7 elements and more: fp32 10 x 39350 x 47 610 in 64 channels, in 16 689; 12 x 47928 x 35 834, in 8 922; bf16
+//                       4 x 36024 x 280 1137, in 32 1228; 6 x 39406 x 71 in 32 702, in 8 820)
+//   three gates         32 at 1.08 where there are many groups (ParaLSTM fp32 53 x 7016 x 117 950 in 64 channels, in 32 1014; 53 x 2458 x 240 399 / 436)
+//   up to 8 channels    more gates below 3000 timesteps the table's tile (ParaLSTM 1 x 1285 x 8 31.4, of 512 steps 33.0; LSTM 1 x 1567 34.3 / 36.5)
 struct FusedWidth { int channels; float costs; TileCfg tile; };
-inline FusedWidth fused_width(const CellInfo &ci, int H)
+inline FusedWidth fused_width(const CellInfo &ci, int B, int L, int H)
 {
-    const bool two = ci.S == 2;
-    const FusedWidth w[] = {{64, 1.0f, two ? TileCfg{1, 1, 16, 4} : TileCfg{1, 1, 12, 8}},
-                            {32, !two ? 1.08f : ci.G >= 4 ? 1.06f : 0.98f, two ? TileCfg{1, 2, 16, 4} : TileCfg{1, 2, 8, 8}},
-                            {16, 1.15f, {1, 4, 8, 8}}, {8, 1.25f, {1, 8, 8, 8}}};
-    const FusedWidth *best = w;
-    for (const FusedWidth &x : w)
-        if (x.costs * (float)padded_channels(H, x.channels) < best->costs * (float)padded_channels(H, best->channels)) best = &x;
-    return *best;
+    const bool two = ci.S == 2, more = two && ci.G >= 4;
+    const double steps = (double)B * L;
+    const bool large = more && steps * H >= 1.5e7;
+    const float c32 = !two ? 1.08f : more ? (large ? 1.15f : 1.06f) : ci.G == 3 && (double)B * ((H + 63) / 64) >= 100.0 ? 1.08f : 0.98f;
+    const FusedWidth x64 = {64, 1.0f, two ? TileCfg{1, 1, 16, 4} : TileCfg{1, 1, 12, 8}}, x32 = {32, c32, two ? TileCfg{1, 2, 16, 4} : TileCfg{1, 2, 8, 8}},
+                     x16 = {16, 1.15f, {1, 4, 8, 8}}, x8 = {8, 1.25f, {1, 8, 8, 8}};
+    if (two && ci.G > 2 && H <= 8 && steps < 3000.0) return {8, 1.25f, {1, 8, 4, 2}};
+    if (two && H > 24 && H <= 32) {
+        if (steps >= (more ? 6e5 : 5e4)) return x32;
+        return more && H == 32 && steps >= 2.5e5 ? FusedWidth{32, c32, {1, 2, 8, 8}} : x16;
+    }
+    FusedWidth best = x64;
+    for (const FusedWidth &x : {x32, x16, x8}) {
+        if (large && H > 32 && x.channels < 32) break;
+        if (x.costs * (float)padded_channels(H, x.channels) < best.costs * (float)padded_channels(H, best.channels)) best = x;
+    }
+    return best;
 }
 inline bool fused_by_width(const CellInfo &ci, int L, int H) { return ci.S <= 2 && L > 256 && H <= 320; }
-inline TileCfg fused_tile(const CellInfo &ci, int L, int H, const TileCfg &table)
+inline TileCfg fused_tile(const CellInfo &ci, int B, int L, int H, const TileCfg &table)
 {
-    return settings().tile[0] <= 0 && fused_by_width(ci, L, H) ? fused_width(ci, H).tile : table;
+    return settings().tile[0] <= 0 && fused_by_width(ci, L, H) ? fused_width(ci, B, L, H).tile : table;
 }
 
 // The tile of a backward pass of a scalar or 2x2 cell with carry records, by sweeps over 300 to 60000 steps of 2048 to 65792
@@ -314,7 +332,7 @@ inline Layout make_layout(const CellInfo &ci, int dtype, int B, int L, int H, bo
     Layout lo;
     lo.cfg = force ? *force : choose_tile(ci, dtype, backward, H, align_elems, fused);
     if (backward && !force) lo.cfg = backward_tile(ci, dtype, B, L, H, lo.cfg);
-    if (fused && !force) lo.cfg = fused_tile(ci, L, H, lo.cfg);
+    if (fused && !force) lo.cfg = fused_tile(ci, B, L, H, lo.cfg);
     const int CW = (kWave / lo.cfg.ll) * lo.cfg.vec, T = lo.cfg.c * lo.cfg.ll * lo.cfg.w;
     ScanGeom &g = lo.g;
     g.B = B; g.L = L; g.H = H; g.T = T;
@@ -408,7 +426,7 @@ inline float records_us(const ShortCost &k, const CellInfo &ci, int dtype, int B
     // above their times there; nor up to 2048 steps (GRU bf16 85 x 1664 x 16, eight iterations, 49 us, in one workgroup 44) and
     // for two gates and two states (rot_tanh bf16 43 x 15499 x 16 186 / 159).
     if (fused_by_width(ci, L, H) && L > 2048 && !(ci.S == 2 && ci.G <= 2)) {
-        const FusedWidth w = fused_width(ci, H);
+        const FusedWidth w = fused_width(ci, B, L, H);
         const float part = w.costs * (float)padded_channels(H, w.channels) / (float)padded_channels(H, width);
         const float by_width = 1.3f * (fixed + step * n * part * (1.0f + k.rec_narrow * narrow) + k.rec_tile * its * n_lt);
         if (by_width < us) return by_width;

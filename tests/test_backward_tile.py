@@ -114,6 +114,29 @@ def test_steps_of_narrow_bf16_tiles(tiles):
         assert taken == ((1, 2, 8, 8) if m[3] < m[4] else (1, 2, 8, 16)), m
 
 
+# narrow rows: the faster shape and another, with their times (us)
+NARROW_BLOCKS = [
+    (GRU, F32, 43, 3923, 24, (1, 8, 8, 8), 61.9, (1, 2, 8, 8), 73.3), (GRU, F32, 2, 2802, 96, (1, 2, 8, 8), 32.0, (1, 1, 12, 8), 36.6),
+    (GRU, F32, 1, 3225, 136, (1, 4, 8, 8), 30.8, (1, 1, 12, 8), 36.3), (GRU, F32, 2, 33363, 200, (1, 4, 8, 8), 147.6, (1, 1, 12, 8), 163.2),
+    (GRU, BF16, 10, 13358, 280, (1, 2, 8, 8), 329.2, (1, 1, 12, 8), 364.0), (LSTM, F32, 5, 7609, 32, (1, 4, 8, 8), 80.6, (1, 2, 8, 8), 83.1),
+    (LSTM, F32, 8, 7739, 48, (1, 4, 8, 8), 125.2, (1, 1, 16, 4), 148.3), (LSTM, F32, 2, 31673, 160, (1, 2, 16, 4), 298.7, (1, 1, 16, 4), 334.4),
+    (LSTM, BF16, 5, 4015, 40, (1, 8, 8, 8), 73.2, (1, 1, 16, 4), 97.0), (PARALSTM, F32, 2, 9236, 26, (1, 4, 8, 8), 48.3, (1, 2, 8, 8), 53.1),
+    (PARALSTM, F32, 71, 1586, 181, (1, 1, 16, 4), 287.4, (1, 2, 16, 4), 311.5),
+    (PARALSTM, F32, 53, 2458, 240, (1, 1, 16, 4), 399.4, (1, 2, 16, 4), 435.5), (PARALSTM, BF16, 2, 9535, 32, (1, 4, 8, 8), 50.7, (1, 2, 8, 8), 54.9),
+    (ROT, F32, 2, 4092, 26, (1, 4, 8, 8), 36.4, (1, 2, 8, 8), 39.4), (ROT, F32, 12, 15198, 40, (1, 8, 8, 8), 130.6, (1, 1, 16, 4), 169.2),
+    (ROT, BF16, 11, 11748, 101, (1, 2, 16, 4), 215.1, (1, 1, 16, 4), 240.6), (LSTM, F32, 10, 39350, 47, (1, 1, 16, 4), 609.9, (1, 4, 8, 8), 688.9),
+    (LSTM, BF16, 42, 7228, 32, (1, 2, 8, 8), 427.5, (1, 2, 16, 4), 523.8), (LSTM, BF16, 4, 4721, 32, (1, 4, 8, 8), 46.8, (1, 2, 16, 4), 59.4),
+    (LSTM, F32, 12, 47928, 35, (1, 1, 16, 4), 833.7, (1, 8, 8, 8), 921.7), (LSTM, BF16, 6, 39406, 71, (1, 2, 16, 4), 702.1, (1, 8, 8, 8), 820.1),
+    (PARALSTM, F32, 1, 1285, 8, (1, 8, 4, 2), 31.4, (1, 8, 8, 8), 33.0),
+]
+
+
+def test_the_faster_shape_of_narrow_rows_is_taken(tiles):
+    """The blocks of a forward solve."""
+    for m, (*_, blocks) in zip(NARROW_BLOCKS, tiles([(*m[0], *m[1:5]) for m in NARROW_BLOCKS])):
+        assert m[6] < m[8] and blocks == m[5], (m, blocks)
+
+
 def test_every_shape_that_is_taken_for_such_rows_has_queues(tiles):
     """Cells of any number of gates and parameter rows: rows of three channel groups or more that are no multiple of 64 bytes, large tensors, many groups."""
     ps = [(G, S, P, k, dt, B, L, H) for G, S, k in ((1, 1, -1), (3, 1, 0), (5, 1, -1), (1, 2, -1), (2, 2, -1), (3, 2, 4), (3, 2, -1), (4, 2, 1), (7, 2, -1))
