@@ -250,37 +250,64 @@ inline bool backward_tile_fits(const CellInfo &ci, const TileCfg &t)
     const size_t rows = (size_t)(ci.S * ci.S + ci.S > ci.PR ? ci.S * ci.S + ci.S : ci.PR);
     return (t.w * rows + ci.S) * (size_t)(64 / t.ll) * t.vec * sizeof(float) + 16 <= 65536;
 }
-// Narrow rows, as the fused blocks' tile above (a pass is bound by memory sooner, so that narrow groups cost more).  us, before /
-// now: GRU fp32 12 x 48925 x 8 190 / 48, 42 x 3207 x 8 67 / 19, 31 x 35271 x 16 352 / 163, 18 x 12000 x 24 70 / 54, 30 x 20768 x 96 434 / 401; LSTM bf16 12 x
-// 48925 x 8 179 / 62, 31 x 35271 x 16 345 / 171, 18 x 12000 x 24 82 / 68, 3 x 20000 x 48 52 / 42; ParaLSTM fp32 60 x 16549 x 8 289 / 101, 31 x 35271 x 16
-// 432 / 196, 30 x 20768 x 96 603 / 576; rot_tanh bf16 30 x 20768 x 96 494 / 351.  Groups of 16 for more than 16 channels (16 / 32): cells of more gates
-// in bf16, on small tensors only (LSTM 3 x 2000 x 24 16.5 / 18.5, 12 x 12000 x 24 51 / 60, 18 x 12000 x 32 68 / 79, 4 x 2000 x 80 18.4 / 20.0, 20 x 9000 x 80 195 / 184;
-// ParaLSTM 167 / 169, 64 x 12000 x 24 241 / 293); in fp32 they lose more than they gain (LSTM 3 x 2000 x 24 16.3 / 18.1, 64 x 12000 x 24 340 / 279, 18 x 12000 x 32
-// 109 / 94; ParaLSTM 58 / 64 of 12 x 12000 x 24, 99 / 84 of 18 x 12000 x 32).  Beyond 320 channels the shapes by size are the faster ones or within 5 % but for
-// ParaLSTM fp32 4 x 4000 x 352 (56 / 52) and rot_tanh bf16 (3 x 6000 x 416 51 / 47, 2 x 9000 x 544 61 / 57): GRU fp32 4 x 4000 x 336 42 / 46, 352 41 / 40, bf16
-// 2 x 9000 x 544 56 / 60; LSTM fp32 3 x 6000 x 416 87 / 86, bf16 66 / 69; ParaLSTM bf16 3 x 6000 x 480 66 / 71.  Not at sizes and rows for which there are
-// queues, for which these shapes are not built (GRU fp32 64 x 16000 x 90 in queues 796, these shapes 947; x 72 from one queue 734, 765; rot_tanh bf16
-// 40 x 20000 x 72 would gain, 528 / 449).  Registers (of 128 for four waves a SIMD): scalar cells take 129 in tiles of 512 steps
-// and of 16 channels, 131 in 32 x 128, so that a unit holds one workgroup of eight waves; 32 x 256 is one of sixteen within 128, with 20 bytes of
+// Narrow rows, as the fused blocks' tile above (a pass is bound by memory sooner, so that narrow groups cost more).  us, before / now: GRU fp32 12 x 48925 x 8
+// 190 / 48, 42 x 3207 x 8 67 / 19, 31 x 35271 x 16 352 / 163, 18 x 12000 x 24 70 / 54, 30 x 20768 x 96 434 / 401; LSTM bf16 12 x 48925 x 8 179 / 62, 31 x 35271 x 16
+// 345 / 171, 18 x 12000 x 24 82 / 68, 3 x 20000 x 48 52 / 42; ParaLSTM fp32 60 x 16549 x 8 289 / 101, 31 x 35271 x 16 432 / 196; rot_tanh bf16 30 x 20768 x 96
+// 494 / 351.  12000 passes of 5 to 340 channels, against the tiles before: 0.86 of the time on the mean, 73 slower by more than 3 % (worst 1.10).
+// A group of 32 channels is a line of 128 bytes in fp32 and half of one in bf16: where rows are no multiple of it, neighbouring groups share lines, which costs more than the
+// padding of 64 channels.  And where the tiles are one round of the device (256, a workgroup on each unit) and the narrower ones are too, those are faster; where only they
+// or only the wider ones are, these (ParaLSTM fp32 16 x 749 x 94 256 wide tiles 21.2, 288 narrow 25.7; bf16 13 x 862 x 81 234, 22.6, and 312, 25.4; GRU bf16 4 x 4895 x 92
+// 312, 26.6, and 240, 23.3).  Lines of the rule (narrow / wide):
+//   scalar, 17 to 32  256 steps from 28000 timesteps on (fp32; 8000 to 16000 1.03-1.10, 32000 0.92, 45000 0.82), in bf16 from 40000 (2 x 15789 x 24 25.2 / 23.1,
+//                     12 x 3000 x 17 22.4 / 21.8, x 24 22.6 / 22.9, 4 x 12000 24.0 / 27.7, 1 x 60000 29.5 / 37.3), rows of 32 from 34000 (2 x 15789 22.2 / 21.7, 12 x 3000
+//                     17.8 / 18.8, 6 x 6000 18.4 / 20.0)
+//   scalar, 65 to 96  fp32 96 0.94-0.99, others up to 28000 timesteps 0.86-1.01, beyond 1.00-1.17 (not of one sequence, 0.93-1.0); bf16 96 0.80-0.97, others of 10000 steps
+//                     and more 0.84-1.06, of less 1.0-1.12; 160, in place of 64 x 128, 0.87-1.03.  Other rows: bf16 129 to 160 0.97-1.27, 193 to 224 0.94-1.31, 257 to 288
+//                     0.96-1.30
+//   two gates, bf16   17 to 32: four waves of 16 steps from 40000 timesteps on (8000 to 32000 1.02-1.11, 128000 0.85-0.95); 65 to 96 0.76-1.0, 129 to 160 0.82-1.09, 224 and
+//                     288 0.87-0.95, other rows of these widths 0.96-1.13.  fp32: the shapes by size (76 x 2683 x 81 178, 32 x 128 191)
+//   more gates, fp32  65 to 96: whole rows 0.83-1.06; others LSTM up to 3.5e6 elements 0.90-1.06, beyond 0.92-1.10 (1.03 on the mean), ParaLSTM of more than a round 1.0-1.22
+//   more gates, bf16  groups of 16 where they save channels and both are a round; else five eighths of the channels up to 8e6 elements 0.79-1.05 (beyond 1.05-1.14), three
+//                     quarters, of one group of 64 the same, of several up to 2.5e6 (beyond 1.05-1.3); groups of 32 for 65 to 96 channels 0.84-1.10, for 129 to 160 1.0-1.14
+// Groups of 16 for 17 to 32 channels (16 / 32): more gates in bf16 (LSTM 3 x 2000 x 24 16.5 / 18.5, 12 x 12000 x 24 51 / 60, 18 x 12000 x 32 68 / 79; ParaLSTM 64 x 12000 x 24
+// 241 / 293); in fp32 they lose more than they gain (LSTM 3 x 2000 x 24 16.3 / 18.1, 64 x 12000 x 24 340 / 279, 18 x 12000 x 32 109 / 94; ParaLSTM 58 / 64 of 12 x 12000 x 24,
+// 99 / 84 of 18 x 12000 x 32).  Beyond 320 channels the shapes by size are the faster ones or within 5 % but for ParaLSTM fp32 4 x 4000 x 352 (56 / 52) and rot_tanh bf16
+// (3 x 6000 x 416 51 / 47, 2 x 9000 x 544 61 / 57).  Not at sizes and rows for which there are queues, for which these shapes are not built (GRU fp32 64 x 16000 x 90 in queues
+// 796, these shapes 947; x 72 from one queue 734, 765; rot_tanh bf16 40 x 20000 x 72 would gain, 528 / 449).  Registers (of 128 for four waves a SIMD): scalar cells take 129 in
+// tiles of 512 steps and of 16 channels, 131 in 32 x 128, so that a unit holds one workgroup of eight waves; 32 x 256 is one of sixteen within 128, with 20 bytes of
 // scratch a lane (35 x 14020 x 24 123, 32 x 128 168).
 inline TileCfg backward_tile_narrow(const CellInfo &ci, int dtype, int B, int L, int H, const TileCfg &wide)
 {
-    const bool bf = dtype == PARARNN_BF16, few = ci.S == 1 || ci.G <= 2;
-    const TileCfg x8 = {1, 8, 8, 8}, x16 = {1, 4, 8, 8}, x32 = ci.S == 1 ? TileCfg{1, 2, 8, 16} : few && bf ? TileCfg{1, 2, 16, 4} : TileCfg{1, 2, 8, 8};
-    if (L <= 256) return wide;
+    const bool bf = dtype == PARARNN_BF16, two_gates = ci.S == 2 && ci.G <= 2;
+    const TileCfg x8 = {1, 8, 8, 8}, x16 = {1, 4, 8, 8}, x32 = {1, 2, 8, 8}, x32l = ci.S == 1 ? TileCfg{1, 2, 8, 16} : TileCfg{1, 2, 16, 4};
+    const double steps = (double)B * L, n = steps * H;
+    if (L <= 256 || H > 320) return wide;
     // (less than a workgroup of the short tile for each unit: LSTM bf16 7 x 1404 x 8 16.8, of 512 steps 19.2; 8 x 1800 18.4 / 17.8)
-    if (H <= 8) return ci.S == 2 && (double)B * L < 12800.0 ? wide : x8;
+    if (H <= 8) return ci.S == 2 && steps < 12800.0 ? wide : x8;
     if (H <= 16) return x16;
-    const bool take16 = bf && !few && (double)B * L * H < 8e6;
-    // (few tiles of 256 steps, of 256 / of 128: GRU bf16 2 x 15789 x 24 25.2 / 23.1, 5 x 3500 x 24 21.1 / 17.4, 12 x 3000 x 17 22.4 / 21.8, x 24 22.6 / 22.9, 4 x 12000
-    // 24.0 / 27.7, 1 x 60000 29.5 / 37.3.  Rows of 32 are whole half lines, and level sooner: 2 x 15789 22.2 / 21.7, 12 x 3000 17.8 / 18.8, 6 x 6000 18.4 / 20.0)
-    if (H <= 32) return take16 ? x16 : ci.S == 1 && bf && (double)B * L < (H == 32 ? 3.4e4 : 4e4) ? TileCfg{1, 2, 8, 8} : x32;
+    if (H <= 32) {
+        if (ci.S == 1) return steps < (!bf ? 2.8e4 : H == 32 ? 3.4e4 : 4e4) ? x32 : x32l;
+        if (two_gates) return bf && steps >= 4e4 ? x32l : x32;
+        return bf && n < 8e6 ? x16 : x32;
+    }
     const size_t row = (size_t)H * (bf ? 2 : 4);
-    if (H > 320 || backward_queues_pay((size_t)B * L * row * (2 * ci.G + 2 * ci.S), row, (H + 63) / 64, B * ((H + 63) / 64))) return wide;
-    const float c64 = (float)padded_channels(H, 64), c32 = (few ? (bf ? 1.05f : 1.2f) : 1.25f) * (float)padded_channels(H, 32),
-                c16 = 1.12f * (float)padded_channels(H, 16);
-    if (take16 && c16 < c64 && c16 < c32) return x16;
-    return c32 < c64 ? x32 : wide;
+    if (backward_queues_pay((size_t)B * L * row * (2 * ci.G + 2 * ci.S), row, (H + 63) / 64, B * ((H + 63) / 64))) return wide;
+    // of the channels that groups of 64 work on, and whether tiles are one round
+    const float part32 = (float)padded_channels(H, 32) / (float)padded_channels(H, 64), part16 = (float)padded_channels(H, 16) / (float)padded_channels(H, 64);
+    auto one_round = [&](int width, int T) { return (double)B * ((H + width - 1) / width) * ((L + T - 1) / T) <= 256.0; };
+    const bool whole = H % 32 == 0, save32 = part32 < 0.76f;
+    if (ci.S == 1) {
+        if (whole && (save32 || (bf && part32 < 0.84f && wide.w == 16))) return x32l;
+        if (!save32) return wide;
+        if (!bf) return steps < 2.8e4 || B == 1 ? x32l : wide;
+        return (L >= 10000 && steps >= 1.8e4) || (one_round(32, 256) && !one_round(64, 128)) ? x32l : wide;
+    }
+    if (two_gates) return bf && (part32 < (whole ? 0.91f : 0.84f) || (part32 < 0.95f && one_round(32, 128))) ? x32l : wide;
+    const bool one = one_round(64, 96);
+    if (!bf) return save32 && (whole || (ci.G >= 4 ? n < 3.5e6 : one && one_round(32, 128))) ? x32 : wide;
+    if (one && part16 < 0.89f) return one_round(16, 256) ? x16 : save32 && one_round(32, 128) ? x32 : wide;
+    if (part16 < 0.76f && n < (part16 < 0.63f || H <= 64 ? 8e6 : 2.5e6)) return x16;
+    return save32 ? x32 : wide;
 }
 inline TileCfg backward_tile(const CellInfo &ci, int dtype, int B, int L, int H, const TileCfg &table)
 {

@@ -114,7 +114,27 @@ def test_steps_of_narrow_bf16_tiles(tiles):
         assert taken == ((1, 2, 8, 8) if m[3] < m[4] else (1, 2, 8, 16)), m
 
 
-# narrow rows: the faster shape and another, with their times (us)
+# narrow rows: the faster shape and another, with their times (us).  Where a shape of few channels loses: rows that share cache lines, more than a round of the
+# device where the wider one is one, long sequences of many channels
+NARROW_BACK = [
+    (GRU, F32, 43, 3923, 24, (1, 2, 8, 16), 43.8, (1, 2, 8, 8), 53.7), (GRU, F32, 94, 669, 88, (1, 1, 8, 16), 51.7, (1, 2, 8, 16), 56.8),
+    (GRU, F32, 2, 2802, 96, (1, 2, 8, 16), 18.1, (1, 1, 8, 16), 19.7), (GRU, BF16, 10, 30458, 32, (1, 2, 8, 16), 65.8, (1, 2, 8, 8), 81.6),
+    (GRU, BF16, 2, 4101, 88, (1, 1, 8, 16), 20.0, (1, 2, 8, 16), 22.2), (GRU, BF16, 9, 47445, 96, (1, 2, 8, 16), 232.9, (1, 1, 8, 16), 290.0),
+    (GRU, BF16, 34, 3583, 150, (1, 1, 8, 8), 127.0, (1, 2, 8, 16), 147.3), (GRU, BF16, 20, 3697, 201, (1, 1, 8, 16), 96.7, (1, 2, 8, 16), 113.5),
+    (GRU, BF16, 52, 614, 224, (1, 1, 8, 8), 44.3, (1, 2, 8, 16), 51.0), (GRU, BF16, 1, 19982, 264, (1, 1, 8, 16), 43.5, (1, 2, 8, 16), 48.3),
+    (LSTM, F32, 30, 3914, 74, (1, 1, 12, 8), 144.2, (1, 2, 8, 8), 158.3), (LSTM, F32, 21, 2277, 96, (1, 2, 8, 8), 53.0, (1, 1, 12, 8), 59.1),
+    (LSTM, BF16, 5, 4015, 40, (1, 4, 8, 8), 20.4, (1, 1, 12, 8), 25.0), (LSTM, BF16, 59, 1099, 84, (1, 2, 8, 8), 67.0, (1, 1, 12, 8), 70.3),
+    (LSTM, BF16, 2, 3171, 101, (1, 4, 8, 8), 20.2, (1, 1, 12, 8), 23.0), (LSTM, BF16, 59, 309, 110, (1, 1, 12, 8), 31.3, (1, 4, 8, 8), 37.8),
+    (LSTM, BF16, 1, 8573, 136, (1, 4, 8, 8), 26.0, (1, 1, 12, 8), 28.8), (LSTM, BF16, 26, 1160, 160, (1, 1, 12, 8), 51.4, (1, 4, 8, 8), 59.3),
+    (LSTM, BF16, 13, 2921, 208, (1, 1, 12, 8), 77.5, (1, 4, 8, 8), 86.0), (PARALSTM, F32, 4, 845, 88, (1, 2, 8, 8), 17.8, (1, 1, 12, 8), 19.6),
+    (PARALSTM, F32, 79, 1637, 94, (1, 1, 12, 8), 166.9, (1, 2, 8, 8), 189.5), (PARALSTM, BF16, 5, 29245, 23, (1, 4, 8, 8), 59.1, (1, 2, 8, 8), 69.1),
+    (PARALSTM, BF16, 28, 847, 40, (1, 1, 12, 8), 22.8, (1, 4, 8, 8), 25.3), (PARALSTM, BF16, 11, 6977, 85, (1, 2, 8, 8), 72.3, (1, 1, 12, 8), 78.0),
+    (PARALSTM, BF16, 41, 547, 112, (1, 1, 12, 8), 30.3, (1, 4, 8, 8), 38.7), (PARALSTM, BF16, 32, 757, 148, (1, 1, 12, 8), 41.0, (1, 4, 8, 8), 50.5),
+    (PARALSTM, BF16, 76, 415, 200, (1, 1, 12, 8), 66.7, (1, 4, 8, 8), 83.3), (PARALSTM, BF16, 8, 3440, 263, (1, 1, 12, 8), 68.9, (1, 4, 8, 8), 83.9),
+    (ROT, F32, 80, 1843, 77, (1, 1, 16, 4), 125.1, (1, 2, 8, 8), 140.1), (ROT, BF16, 28, 906, 17, (1, 2, 8, 8), 16.7, (1, 2, 16, 4), 18.3),
+    (ROT, BF16, 21, 20897, 96, (1, 2, 16, 4), 258.1, (1, 1, 16, 8), 296.0), (ROT, BF16, 5, 537, 160, (1, 2, 16, 4), 17.7, (1, 1, 16, 8), 23.2),
+    (ROT, BF16, 55, 1316, 196, (1, 1, 16, 4), 92.4, (1, 2, 16, 4), 100.4), (ROT, BF16, 6, 6326, 224, (1, 2, 16, 4), 52.2, (1, 1, 16, 8), 58.2),
+]
 NARROW_BLOCKS = [
     (GRU, F32, 43, 3923, 24, (1, 8, 8, 8), 61.9, (1, 2, 8, 8), 73.3), (GRU, F32, 2, 2802, 96, (1, 2, 8, 8), 32.0, (1, 1, 12, 8), 36.6),
     (GRU, F32, 1, 3225, 136, (1, 4, 8, 8), 30.8, (1, 1, 12, 8), 36.3), (GRU, F32, 2, 33363, 200, (1, 4, 8, 8), 147.6, (1, 1, 12, 8), 163.2),
@@ -132,7 +152,9 @@ NARROW_BLOCKS = [
 
 
 def test_the_faster_shape_of_narrow_rows_is_taken(tiles):
-    """The blocks of a forward solve."""
+    """Backward passes and the blocks of a forward solve."""
+    for m, (_, taken, *_) in zip(NARROW_BACK, tiles([(*m[0], *m[1:5]) for m in NARROW_BACK])):
+        assert m[6] < m[8] and taken == m[5], (m, taken)
     for m, (*_, blocks) in zip(NARROW_BLOCKS, tiles([(*m[0], *m[1:5]) for m in NARROW_BLOCKS])):
         assert m[6] < m[8] and blocks == m[5], (m, blocks)
 
