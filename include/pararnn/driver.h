@@ -189,17 +189,18 @@ inline int padded_channels(int H, int width) { return (H + width - 1) / width * 
 //                       4 x 36024 x 280 1137, in 32 1228; 6 x 39406 x 71 in 32 702, in 8 820)
 //   three gates         32 at 1.08 where there are many groups (ParaLSTM fp32 53 x 7016 x 117 950 in 64 channels, in 32 1014; 53 x 2458 x 240 399 / 436)
 //   up to 8 channels    more gates below 3000 timesteps the table's tile (ParaLSTM 1 x 1285 x 8 31.4, of 512 steps 33.0; LSTM 1 x 1567 34.3 / 36.5)
+// lines: false for the costs alone (a workspace that does not hold the records of the short tiles: fused_layout).
 struct FusedWidth { int channels; float costs; TileCfg tile; };
-inline FusedWidth fused_width(const CellInfo &ci, int B, int L, int H)
+inline FusedWidth fused_width(const CellInfo &ci, int B, int L, int H, bool lines = true)
 {
     const bool two = ci.S == 2, more = two && ci.G >= 4;
     const double steps = (double)B * L;
-    const bool large = more && steps * H >= 1.5e7;
-    const float c32 = !two ? 1.08f : more ? (large ? 1.15f : 1.06f) : ci.G == 3 && (double)B * ((H + 63) / 64) >= 100.0 ? 1.08f : 0.98f;
+    const bool large = lines && more && steps * H >= 1.5e7;
+    const float c32 = !two ? 1.08f : more ? (large ? 1.15f : 1.06f) : lines && ci.G == 3 && (double)B * ((H + 63) / 64) >= 100.0 ? 1.08f : 0.98f;
     const FusedWidth x64 = {64, 1.0f, two ? TileCfg{1, 1, 16, 4} : TileCfg{1, 1, 12, 8}}, x32 = {32, c32, two ? TileCfg{1, 2, 16, 4} : TileCfg{1, 2, 8, 8}},
                      x16 = {16, 1.15f, {1, 4, 8, 8}}, x8 = {8, 1.25f, {1, 8, 8, 8}};
-    if (two && ci.G > 2 && H <= 8 && steps < 3000.0) return {8, 1.25f, {1, 8, 4, 2}};
-    if (two && H > 24 && H <= 32) {
+    if (lines && two && ci.G > 2 && H <= 8 && steps < 3000.0) return {8, 1.25f, {1, 8, 4, 2}};
+    if (lines && two && H > 24 && H <= 32) {
         if (steps >= (more ? 6e5 : 5e4)) return x32;
         return more && H == 32 && steps >= 2.5e5 ? FusedWidth{32, c32, {1, 2, 8, 8}} : x16;
     }
@@ -381,6 +382,20 @@ inline Layout make_layout(const CellInfo &ci, int dtype, int B, int L, int H, bo
     if (backward) off += round256((size_t)g.n_lt * B * ci.PR * H * sizeof(float));
     lo.total = off;
     return lo;
+}
+
+// The layout of a solve's blocks that `fits` takes, given the layout and its bytes; false where there is none.  Short tiles need more records, 64 x 64
+// four times those of 16 x 256: a workspace that holds only the latter still has its iterations in one launch (LSTM fp32 10 x 39350 x 47 on 32 MiB 687 us, with
+// a launch for each iteration 1130).
+template <class F>
+inline bool fused_layout(const CellInfo &ci, int dtype, int B, int L, int H, int align_elems, int n_fused, bool to_tol, F fits, Layout *lf)
+{
+    *lf = make_layout(ci, dtype, B, L, H, false, align_elems, true, n_fused);
+    if (fits(*lf, to_tol ? lf->total : lf->off_bnd)) return true;
+    if (settings().tile[0] > 0 || !fused_by_width(ci, L, H)) return false;
+    const TileCfg other = fused_width(ci, B, L, H, false).tile;
+    *lf = make_layout(ci, dtype, B, L, H, false, align_elems, true, n_fused, &other);
+    return fits(*lf, to_tol ? lf->total : lf->off_bnd);
 }
 
 // Shape of the kernels of short_kernels.h for a problem: c steps per thread, 64 >> lps_log2 segments per wave, w waves;
@@ -983,20 +998,15 @@ int forward_solve(const CellInfo &ci, int dtype, const float *params, const void
     // workspace holds those.
     Layout lo = make_layout(ci, dtype, B, L, H, false, al), lf;
     int n_fused = fused_slots_wanted(tol, max_iter, opts);
-    size_t need = lo.total;
-    if (n_fused > 0) {
-        lf = make_layout(ci, dtype, B, L, H, false, al, true, n_fused);
-        need = tol < 0.0f ? lf.off_bnd : lf.total;
-    }
     WorkspaceRest rest = {nullptr, 0};
-    if (workspace_bytes < need) {
-        rest = workspace_rest(workspace);
-        auto fits = [&](const Layout &l, size_t whole) {
-            return rest.ptr ? workspace_bytes >= l.off_bnd && rest.bytes >= whole - l.off_bnd : workspace_bytes >= whole;
-        };
-        if (n_fused > 0 && !fits(lf, need)) n_fused = 0;
-        if (n_fused == 0 && !fits(lo, lo.total)) return PARARNN_WORKSPACE_TOO_SMALL;
-    }
+    bool asked = false;                    // for memory for the rest: only where the workspace is too small, and where there is some it is taken
+    auto fits = [&](const Layout &l, size_t whole) {
+        if (!rest.ptr && workspace_bytes >= whole) return true;
+        if (!asked) { rest = workspace_rest(workspace); asked = true; }
+        return rest.ptr && workspace_bytes >= l.off_bnd && rest.bytes >= whole - l.off_bnd;
+    };
+    if (n_fused > 0 && !fused_layout(ci, dtype, B, L, H, al, n_fused, tol >= 0.0f, fits, &lf)) n_fused = 0;
+    if (n_fused == 0 && !fits(lo, lo.total)) return PARARNN_WORKSPACE_TOO_SMALL;
     if (n_fused > 0) lo = lf;
     ShortShape sh;
     if (!delta_trace && without_blocks(ci, dtype, B, L, H, tol, max_iter, opts, &sh) &&

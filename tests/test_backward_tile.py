@@ -25,13 +25,13 @@ def tiles(tmp_path_factory):
 
     def run(problems, forced=None):
         """problems: (G, S, PR, kind, dtype, B, L, H), a tile for all of them; per problem the table's shape, the one taken, staged rows,
-        a queue of tiles for each XCD, the shape of the forward solve's blocks."""
+        a queue of tiles for each XCD, the shape of the forward solve's blocks, the one that 32 MiB hold."""
         text = "\n".join(" ".join(str(int(x)) for x in p) for p in problems)
         env = dict(os.environ, PARARNN_TILE=",".join(map(str, forced))) if forced else None
         out = subprocess.run([str(exe)], input=text, capture_output=True, text=True, check=True, env=env).stdout
         rows = [[int(x) for x in line.split()] for line in out.splitlines()]
         assert len(rows) == len(problems)
-        return [(tuple(r[:4]), tuple(r[4:8]), bool(r[8]), bool(r[9]), tuple(r[10:])) for r in rows]
+        return [(tuple(r[:4]), tuple(r[4:8]), bool(r[8]), bool(r[9]), tuple(r[10:14]), tuple(r[14:])) for r in rows]
     return run
 
 
@@ -100,7 +100,7 @@ QUEUES = [(GRU, F32, 64, 16000, 40, 368, 439), (GRU, F32, 64, 16000, 63, 510, 51
 
 
 def test_queues_where_channel_groups_share_lines(tiles):
-    for m, (_, _, _, queues, _) in zip(QUEUES, tiles([(*m[0], *m[1:5]) for m in QUEUES])):
+    for m, (_, _, _, queues, *_) in zip(QUEUES, tiles([(*m[0], *m[1:5]) for m in QUEUES])):
         assert queues == (m[6] < m[5]), m
 
 
@@ -155,7 +155,7 @@ def test_the_faster_shape_of_narrow_rows_is_taken(tiles):
     """Backward passes and the blocks of a forward solve."""
     for m, (_, taken, *_) in zip(NARROW_BACK, tiles([(*m[0], *m[1:5]) for m in NARROW_BACK])):
         assert m[6] < m[8] and taken == m[5], (m, taken)
-    for m, (*_, blocks) in zip(NARROW_BLOCKS, tiles([(*m[0], *m[1:5]) for m in NARROW_BLOCKS])):
+    for m, (*_, blocks, _) in zip(NARROW_BLOCKS, tiles([(*m[0], *m[1:5]) for m in NARROW_BLOCKS])):
         assert m[6] < m[8] and blocks == m[5], (m, blocks)
 
 
@@ -165,7 +165,7 @@ def test_every_shape_that_is_taken_for_such_rows_has_queues(tiles):
           for P in (2, 8, 40, 64) for dt in (F32, BF16) for H in (131, 333, 515, 1001, 2047, 4091, 9001)
           for B in (16, 40, 64, 200) for L in (520, 2500, 9000) if 4 * (2 * G + 2 * S) * B * L * H < 1 << 36 and B * L * H * (2 * G + 2 * S) * (2 if dt else 4) >= 1 << 29]
     seen = set()
-    for p, (_, taken, _, queues, _) in zip(ps, tiles(ps)):
+    for p, (_, taken, _, queues, *_) in zip(ps, tiles(ps)):
         assert queues, (p, taken)
         seen.add((p[1], p[0] <= 2, taken))
     assert {(1, False, (1, 1, 8, 8)), (1, False, (1, 1, 8, 16)), (2, True, (1, 1, 16, 4)), (2, False, (1, 1, 12, 8)), (2, False, (1, 1, 4, 8))} <= seen, seen
@@ -182,7 +182,7 @@ def test_the_sizes_of_the_queue_test_take_queues(tiles):
         assert known[cell][:2] == (G, S)
         for d, dt in ((F32, torch.float32), (BF16, torch.bfloat16)):
             ps += [(*known[cell], d, B, steps(L, G, S, dt), H) for B, L, H in SHAPES]
-    for p, (_, (vec, ll, c, w), _, queues, _) in zip(ps, tiles(ps)):
+    for p, (_, (vec, ll, c, w), _, queues, *_) in zip(ps, tiles(ps)):
         assert queues, p
         counts.add(p[5] * -(-p[7] // (vec * 64 // ll)))
     assert {32, 33, 50, 99, 780} <= counts, counts
@@ -197,7 +197,7 @@ def test_the_sizes_of_the_narrow_test_take_the_narrow_tiles(tiles):
     for cell in CELLS:
         for dt in (F32, BF16):
             back, blocks = {}, {}
-            for size, (_, b, _, _, f) in zip(SIZES, tiles([(*known[cell][0], dt, *m) for m in SIZES])):
+            for size, (_, b, _, _, f, _) in zip(SIZES, tiles([(*known[cell][0], dt, *m) for m in SIZES])):
                 back.setdefault(size[2], set()).add(b)
                 blocks.setdefault(size[2], set()).add(f)
             # two states: backward passes in groups of 8 only where there are enough tiles of 512 steps; either side of that
@@ -207,3 +207,15 @@ def test_the_sizes_of_the_narrow_test_take_the_narrow_tiles(tiles):
                 assert back[H] == {x16} and blocks[H] == {x16}, (cell, dt, H)
             assert known[cell][1 + dt] in set().union(*(back[H] for H in (17, 24, 33, 48, 72, 96))), (cell, dt, back)
             assert {t[1] for H in (33, 48, 72, 96) for t in blocks[H]} >= {2}, (cell, dt, blocks)
+
+
+def test_blocks_on_a_workspace_of_32_mib(tiles):
+    """Where the records of the faster tile do not fit, those of a longer one may: else every iteration is a launch of its own."""
+    large = [(*LSTM, F32, 10, 39350, 47), (*LSTM, F32, 12, 33817, 40), (*LSTM, F32, 6, 45762, 75)]
+    for p, (*_, blocks, held) in zip(large, tiles(large)):
+        assert blocks in ((1, 1, 16, 4), (1, 2, 16, 4)) and held in ((1, 4, 8, 8), (1, 8, 8, 8)), (p, blocks, held)
+    small = [(*LSTM, F32, 4, 4721, 32), (*GRU, F32, 2, 2802, 96), (*LSTM, BF16, 2, 3000, 200)]
+    for p, (*_, blocks, held) in zip(small, tiles(small)):
+        assert held == blocks, (p, blocks, held)
+    none = [(*LSTM, F32, 90, 39350, 47), (*LSTM, BF16, 10, 39350, 47), (*LSTM, F32, 8, 30000, 1024)]
+    assert all(t[-1] == (0, 0, 0, 0) for t in tiles(none))

@@ -102,3 +102,14 @@ def test_beyond_the_array_is_refused(P):
     # ... and the array still serves the next call
     ref, got = both(P, "gru_diag", 2, 333, 200, seed=4402, dtype=torch.float32, tol=1e-4, max_iter=30)
     assert got[1] == ref[1] and torch.equal(got[0], ref[0])
+
+
+def test_records_of_a_longer_tile_where_those_of_the_faster_one_do_not_fit(P):
+    """A large LSTM of few channels takes tiles of 64 x 64, whose records for a block of five iterations are more than the array; those of the tiles of
+    8 x 512 fit, so the solve keeps its blocks (test_backward_tile.py asserts the choice): the same iterations and states as with room for all."""
+    ref, got = both(P, "lstm_diag", 12, 33817, 40, seed=4300, dtype=torch.float32, tol=1e-4, max_iter=30)
+    assert got[1] == ref[1] and ref[1][1] == 0
+    assert relerr(got[0], ref[0]) <= 1e-5
+    k = got[1][0]
+    big = ref[2][:k] > 1e-4
+    assert np.all(np.abs(got[2][:k] - ref[2][:k])[big] <= 2e-3 * ref[2][:k][big])
